@@ -57,7 +57,9 @@ enum { HF_PHI_RELU = 0, HF_PHI_ELU1 = 1 };   /* hf_config.phi: max(x,0) | elu(x)
 enum {
   HF_FLAG_READOUT_KERNEL = 1,      /* history term (Eq. 3, 6) by a readout kernel of its own behind the attention
                                       kernel, instead of in that kernel's epilogue (bf16, head_dim 128, block_q
-                                      64 / 128; elsewhere that is the only path anyway) */
+                                      64 / 128; the other bf16, head_dim 128 shapes whose
+                                      block_q is a multiple of 64 have that path alone, and the fp32-arithmetic
+                                      attention kernel always adds the term itself) */
   HF_FLAG_HISTORY_TWO_PLANES = 2,  /* the fused epilogue multiplies with both bf16 planes of L (high part and
                                       remainder, ~2^-17 relative) instead of the high plane alone (2^-9) */
   HF_FLAG_BWD_FP32_KERNELS = 4,    /* hf_hybrid_attn_bwd through the fp32-arithmetic kernels also where the

@@ -26,7 +26,6 @@ SOURCES = [
     "hf_attn_generic.hip",
     "hf_attn_mfma.hip",
     "hf_attn_w64.hip",
-    "hf_readout.hip",
     "hf_readout_mfma.hip",
     "hf_rope.hip",
     "hf_bwd.hip",

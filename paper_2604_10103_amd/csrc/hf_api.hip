@@ -721,9 +721,12 @@ static int fwd_impl(const hf_config* cfg, const void* Q, const void* Q_hist, int
                                   st + (size_t)cfg->batch * cfg->heads * d * d, rope_cos_q, rope_sin_q, Q_hist, O, s,
                                   save ? lse2_out : nullptr, save ? O_local_out : nullptr);
   }
+  if (attn_wide_taken(*cfg))   // the fp32-arithmetic kernel adds the history term itself
+    return launch_attn_wide_hist(*cfg, Q, Q_hist, n_q, K_win, V_win, n_kv, block_idx, k,
+                                 static_cast<const float*>(state_or_null), rope_cos_q, rope_sin_q, O, s);
   void* o_local = static_cast<char*>(workspace) + w.olocal;
   HF_TRY(launch_attn(*cfg, Q, n_q, K_win, V_win, n_kv, block_idx, k, o_local, s));
-  return launch_readout(*cfg, Q_hist, n_q, o_local, static_cast<const float*>(state_or_null), rope_cos_q,
+  return launch_readout_mfma(*cfg, Q_hist, n_q, o_local, static_cast<const float*>(state_or_null), rope_cos_q,
                         rope_sin_q, static_cast<char*>(workspace) + w.planes, O, s);
 }
 
@@ -1169,7 +1172,7 @@ static int bwd_impl(const hf_config* cfg, const void* Q, const void* Q_hist, int
       add_to_dq = dqh32;
     }
   }
-  HF_TRY(launch_attn_generic(*cfg, Q, n_q, K_win, V_win, n_kv, block_idx, k, nullptr, s, lse2, dO, dvec));
+  HF_TRY(launch_attn_wide_stats(*cfg, Q, n_q, K_win, V_win, n_kv, block_idx, k, dO, lse2, dvec, s));
   return launch_bwd_generic(*cfg, Q, n_q, K_win, V_win, n_kv, block_idx, k, dO, lse2, dvec, inv_cnt, inv_list,
                             add_to_dq, dQ, dK, dV, s);
 }

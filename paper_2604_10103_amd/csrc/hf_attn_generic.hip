@@ -1,162 +1,741 @@
-// Block-sparse window attention (Eq. 5), shape-generic fp32-arithmetic kernel.
+// Block-sparse window attention (Eq. 5) with the history term (Eq. 3, 6), shape-generic, fp32 arithmetic.
 //
-// Used for fp32 inputs (all arithmetic fp32, so the fp32-mode error bound holds) and for
-// bf16 shapes the MFMA kernel does not cover.  One workgroup per (batch*head, query block);
-// each wavefront carries R query rows at a time through the selected KV blocks:
-//   scores : lane = key (64 keys per step), q broadcast from LDS, K row read by its lane
-//   softmax: online (running max m, running sum l) in the exp2 domain, wave reductions
-//   P V    : lanes = value features, p broadcast with a lane read, V row read coalesced
+// Used for fp32 inputs (every product and sum in fp32, so the fp32-mode error bound holds) and for bf16 shapes that the
+// bf16 matrix-core kernels do not cover.  Both products run on the fp32 matrix instruction (hf_f32_mfma.h), transposed as
+// in the bf16 kernel, so that every statistic of a query row lives in the lanes of one column:
+//   S^T (16 keys x 16 queries) = K (row form) x Q^T (row form)
+//   O^T (D x 16 queries)      += V^T (column form) x P^T (= the C layout of S^T)
+// A wavefront owns 16 NQ query rows; KS wavefronts share the same rows and split the list's 16-key tiles between them, and
+// their partial results meet in LDS once, after the list.  The history term is added before that meeting, each of the KS
+// wavefronts multiplying its share of the key features of L.
+//
+// Bound by the matrix pipes' fp32 rate (64 flops per cycle and SIMD): a tile's products take 1024 NQ cycles each at
+// D = 128, next to 16 KB requested from the caches one phase ahead.
 #include <stdlib.h>
 
-#include "hf_common.h"
+#include "hf_f32_mfma.h"
 
 namespace hf {
 
+struct WideHist {            // history term, or statistics for the backward pass
+  const float* L;            // [BH][D][D], NULL: none
+  const float* z;            // [BH][D]
+  const float* cosq;         // [n_q][D/2] rotation of phi(q) in the numerator, or NULL
+  const float* sinq;
+  const void* q_hist;        // [BH][n_q][D] queries of the history branch
+  float eps, z_scale;
+  int phi_kind;
+  float* lse2;               // [BH][n_q], given: row statistics instead of an output
+  const void* d_out;         // [BH][n_q][D]
+  float* dvec;               // [BH][n_q] d_out . O_local
+};
+
 namespace {
 
-template <typename T, int D, int R>
-__global__ __launch_bounds__(256) void attn_generic_kernel(const T* __restrict__ Q, const T* __restrict__ K,
-                                                           const T* __restrict__ V,
-                                                           const int32_t* __restrict__ idx, int k, int n_q,
-                                                           int n_kv, int kv_stride, int bq, int bkv, int t_m,
-                                                           int t_n, float scale_log2e, T* __restrict__ O,
-                                                           float* __restrict__ lse2, const T* __restrict__ dO,
-                                                           float* __restrict__ Dv) {
-  constexpr int E = Elem<T>::kPer16B;
-  constexpr int C = D / kWave;  // value features per lane
-  __shared__ float sq[4][R][D];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int qb = blockIdx.x, bh = blockIdx.y;
-  const T* Qh = Q + (size_t)bh * n_q * D;
+constexpr int kTile = 16;    // keys per tile
+
+template <typename T, int D, int NQ, int KS>
+__global__ __launch_bounds__(256, 2) void attn_wide_kernel(const T* __restrict__ Q, const T* __restrict__ K,
+                                                           const T* __restrict__ V, const int32_t* __restrict__ idx, int k,
+                                                           int n_q, int n_kv, int kv_stride, int bq, int bkv, int t_m,
+                                                           int t_n, int chunks, int per_xcd, int total, float scale_log2e,
+                                                           WideHist hist, T* __restrict__ O) {
+  constexpr int WR = 4 / KS;             // wavefronts along the rows
+  constexpr int ROWS = WR * 16 * NQ;     // query rows of a workgroup
+  constexpr int C = D / 16;              // row-form pieces of a token
+  constexpr int F = D / 64;              // column-form pieces of a token
+  constexpr int OST = D + 4;             // floats per row of a partial result in LDS (breaks the banks' period)
+  extern __shared__ __attribute__((aligned(16))) float smem[];
+  // one contiguous run of (head, query block, chunk of rows) per XCD: its L2 then holds the keys of few heads
+  const int item = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
+  if ((int)(blockIdx.x >> 3) >= per_xcd || item >= total) return;
+  const int bh = item / (t_m * chunks), in_head = item - bh * t_m * chunks;
+  const int qb = in_head / chunks, chunk = in_head - qb * chunks;
+  const int row0 = qb * bq + chunk * ROWS;
+  const int q_end = min(n_q, (qb + 1) * bq);
+  if (row0 >= q_end) return;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int l16 = lane & 15, g = lane >> 4;
+  const int wr = wave / KS, kz = wave % KS;
   const T* Kh = K + (size_t)bh * kv_stride * D;  // heads of a cache buffer are kv_stride tokens apart
   const T* Vh = V + (size_t)bh * kv_stride * D;
-  T* Oh = O + (size_t)bh * n_q * D;
   const int32_t* row_idx = idx ? idx + ((size_t)bh * t_m + qb) * k : nullptr;
   const int nsel = idx ? k : t_n;
-  const int q_end = min(n_q, (qb + 1) * bq);
+  const int subs = (bkv + kTile - 1) / kTile;
+  const int ntiles = nsel * subs;
 
-  // every wavefront runs the same number of passes; rows past the block end are computed on
-  // clamped addresses and never written
-  for (int pass0 = qb * bq; pass0 < q_end; pass0 += 4 * R) {
-    const int r0 = pass0 + wave * R;
-    for (int w = lane; w < R * D; w += kWave) {
-      const int rr = w / D, c = w % D;
-      const int row = min(r0 + rr, n_q - 1);
-      sq[wave][rr][c] = Elem<T>::load(Qh + (size_t)row * D + c) * scale_log2e;
-    }
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_s_waitcnt(0xc07f);
-
-    float m[R], l[R], o[R][C];
+  // rows past the block's end are computed on clamped addresses and never written
+  int row[NQ];
+  f32x4 qf[NQ][C];
 #pragma unroll
-    for (int rr = 0; rr < R; ++rr) {
-      m[rr] = -INFINITY;
-      l[rr] = 0.0f;
+  for (int n = 0; n < NQ; ++n) {
+    row[n] = row0 + 16 * (wr * NQ + n) + l16;
+    const T* qp = Q + ((size_t)bh * n_q + min(row[n], n_q - 1)) * D + 4 * g;
 #pragma unroll
-      for (int e = 0; e < C; ++e) o[rr][e] = 0.0f;
-    }
-
-    for (int s = 0; s < nsel; ++s) {
-      const int jb = row_idx ? row_idx[s] : s;
-      if ((unsigned)jb >= (unsigned)t_n) continue;  // ignore an out-of-range block index
-      const int k_end = min(n_kv, (jb + 1) * bkv);
-      for (int kc = jb * bkv; kc < k_end; kc += kWave) {
-        const int key = kc + lane;
-        const bool valid = key < k_end;
-        const T* krow = Kh + (size_t)(valid ? key : kc) * D;
-        float sc[R];
-#pragma unroll
-        for (int rr = 0; rr < R; ++rr) sc[rr] = 0.0f;
-#pragma unroll 4
-        for (int c = 0; c < D; c += E) {
-          float kv[E];
-          load16B<T>(krow + c, kv);
-#pragma unroll
-          for (int rr = 0; rr < R; ++rr)
-#pragma unroll
-            for (int e = 0; e < E; ++e) sc[rr] = fmaf(sq[wave][rr][c + e], kv[e], sc[rr]);
-        }
-        float p[R];
-#pragma unroll
-        for (int rr = 0; rr < R; ++rr) {
-          const float sv = valid ? sc[rr] : -INFINITY;
-          const float m_new = fmaxf(m[rr], wave_max(sv));  // finite: lane 0 of the step is a real key
-          const float alpha = exp2f(m[rr] - m_new);
-          p[rr] = valid ? exp2f(sv - m_new) : 0.0f;
-          l[rr] = l[rr] * alpha + wave_sum(p[rr]);
-          m[rr] = m_new;
-#pragma unroll
-          for (int e = 0; e < C; ++e) o[rr][e] *= alpha;
-        }
-        const int cnt = min(kWave, k_end - kc);
-        for (int kk = 0; kk < cnt; ++kk) {
-          const T* vrow = Vh + (size_t)(kc + kk) * D + lane * C;
-          float vv[C];
-#pragma unroll
-          for (int e = 0; e < C; ++e) vv[e] = Elem<T>::load(vrow + e);
-#pragma unroll
-          for (int rr = 0; rr < R; ++rr) {
-            const float pk = __shfl(p[rr], kk, kWave);
-#pragma unroll
-            for (int e = 0; e < C; ++e) o[rr][e] = fmaf(pk, vv[e], o[rr][e]);
-          }
-        }
-      }
-    }
-    if (lse2) {
-      // statistics for the backward pass instead of the output: log2 of the sum of 2^(scaled logit), and
-      // D = dO . O_local from the unrounded output (uniform branch: every lane of the wavefront takes it)
-#pragma unroll
-      for (int rr = 0; rr < R; ++rr) {
-        const int row = min(r0 + rr, n_q - 1);
-        const float inv = l[rr] > 0.0f ? 1.0f / l[rr] : 0.0f;   // a row without a single real key: O_local = 0
-        float acc = 0.0f;
-#pragma unroll
-        for (int e = 0; e < C; ++e)
-          acc = fmaf(o[rr][e] * inv, Elem<T>::load(dO + ((size_t)bh * n_q + row) * D + lane * C + e), acc);
-        acc = wave_sum(acc);
-        if (lane == 0 && r0 + rr < q_end) {
-          lse2[(size_t)bh * n_q + row] = l[rr] > 0.0f ? m[rr] + log2f(l[rr]) : INFINITY;  // no real key: P = 0
-          Dv[(size_t)bh * n_q + row] = acc;
-        }
-      }
-      __builtin_amdgcn_wave_barrier();
-      continue;
-    }
-#pragma unroll
-    for (int rr = 0; rr < R; ++rr) {
-      const int row = r0 + rr;
-      if (row < q_end) {
-        const float inv = l[rr] > 0.0f ? 1.0f / l[rr] : 0.0f;   // a row without a single real key: O_local = 0
-#pragma unroll
-        for (int e = 0; e < C; ++e) Elem<T>::store(Oh + (size_t)row * D + lane * C + e, o[rr][e] * inv);
-      }
-    }
-    __builtin_amdgcn_wave_barrier();
+    for (int c = 0; c < C; ++c) qf[n][c] = load4<T>(qp + 16 * c) * scale_log2e;
   }
+
+  f32x4 o[NQ][F][4];
+  float m[NQ], l[NQ];
+#pragma unroll
+  for (int n = 0; n < NQ; ++n) {
+    m[n] = -INFINITY;
+    l[n] = 0.0f;
+#pragma unroll
+    for (int f = 0; f < F; ++f)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) o[n][f][e] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+  }
+
+  // tile t of the list: first key and number of real keys (0: past the list, an index out of range, or an empty part of a
+  // short block; such a tile reads clamped rows and its scores are -inf)
+  auto tile_at = [&](int t, int& first, int& cnt) {
+    const int s = t / subs, sub = t - s * subs;
+    const int jb = row_idx ? row_idx[min(s, nsel - 1)] : s;
+    const int st = jb * bkv + kTile * sub;
+    const bool ok = s < nsel && (unsigned)jb < (unsigned)t_n;
+    const int n = ok ? min(kTile, min(n_kv, (jb + 1) * bkv) - st) : 0;
+    cnt = n > 0 ? n : 0;
+    first = n > 0 ? st : 0;
+  };
+  Piece<T> kp[C], vp[4][F];
+  auto load_k = [&](int first, int cnt) {
+    const T* p = Kh + (size_t)(first + min(l16, max(cnt - 1, 0))) * D + 4 * g;
+#pragma unroll
+    for (int c = 0; c < C; ++c) kp[c].load(p + 16 * c);
+  };
+  auto load_v = [&](int first, int cnt) {
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const T* p = Vh + (size_t)(first + min(4 * g + r, max(cnt - 1, 0))) * D + 4 * l16;
+#pragma unroll
+      for (int f = 0; f < F; ++f) vp[r][f].load(p + 64 * f);
+    }
+  };
+
+  // One tile ahead in every direction: trip t forms the scores of tile t + 1 next to the exponentials of tile t (the matrix
+  // instructions of the one hide the vector work of the other, also for a wavefront that is alone on its SIMD), then
+  // accumulates tile t.  Its keys were requested before tile t - 1 was accumulated, its values behind that.
+  f32x4 sc[NQ];
+  auto scores = [&]() {
+    f32x4 s[NQ][2];
+#pragma unroll
+    for (int n = 0; n < NQ; ++n) s[n][0] = s[n][1] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+    for (int c = 0; c < C; ++c) {
+      const f32x4 a = kp[c].get();
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+#pragma unroll
+        for (int n = 0; n < NQ; ++n) s[n][e & 1] = mfma_f32(a[e], qf[n][c][e], s[n][e & 1]);
+    }
+#pragma unroll
+    for (int n = 0; n < NQ; ++n) sc[n] = s[n][0] + s[n][1];
+  };
+  // missing keys of the tile to -inf, its maximum into the reference m; what was accumulated under a smaller reference is
+  // scaled (rarely: only once the maximum has grown by more than 2^8, any reference is exact in floating point)
+  auto maxima = [&](int cnt) {
+    bool grow = false;
+    float mx[NQ];
+#pragma unroll
+    for (int n = 0; n < NQ; ++n) {
+#pragma unroll
+      for (int r = 0; r < 4; ++r) sc[n][r] = 4 * g + r < cnt ? sc[n][r] : -INFINITY;
+      mx[n] = column_max(fmaxf(fmaxf(sc[n][0], sc[n][1]), fmaxf(sc[n][2], sc[n][3])));
+      grow |= mx[n] > m[n] + 8.0f;
+    }
+    if (__any(grow)) {
+#pragma unroll
+      for (int n = 0; n < NQ; ++n) {
+        const float m_new = fmaxf(m[n], mx[n]);
+        const float alpha = exp2f(m[n] - (m_new == -INFINITY ? 0.0f : m_new));
+        m[n] = m_new;
+        l[n] *= alpha;
+#pragma unroll
+        for (int f = 0; f < F; ++f)
+#pragma unroll
+          for (int e = 0; e < 4; ++e) o[n][f][e] *= alpha;
+      }
+    }
+  };
+  f32x4 p[NQ];
+  auto weights = [&]() {
+#pragma unroll
+    for (int n = 0; n < NQ; ++n) {
+      const float m_use = m[n] == -INFINITY ? 0.0f : m[n];   // nothing seen yet: keep the exponents finite
+#pragma unroll
+      for (int r = 0; r < 4; ++r) p[n][r] = __builtin_amdgcn_exp2f(sc[n][r] - m_use);
+      l[n] += (p[n][0] + p[n][1]) + (p[n][2] + p[n][3]);     // this lane's keys only; summed at the end
+    }
+  };
+  auto accumulate = [&]() {
+#pragma unroll
+    for (int r = 0; r < 4; ++r)
+#pragma unroll
+      for (int f = 0; f < F; ++f) {
+        const f32x4 a = vp[r][f].get();
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+#pragma unroll
+          for (int n = 0; n < NQ; ++n) o[n][f][e] = mfma_f32(a[e], p[n][r], o[n][f][e]);
+      }
+  };
+  int first_v, cnt, first_k, cnt_k;
+  tile_at(kz, first_v, cnt);
+  load_k(first_v, cnt);
+  tile_at(kz + KS, first_k, cnt_k);
+  scores();
+  load_k(first_k, cnt_k);
+  __builtin_amdgcn_sched_barrier(0);   // (requests are awaited in order: values behind keys, here as in the loop)
+  load_v(first_v, cnt);
+  __builtin_amdgcn_sched_barrier(0);
+  maxima(cnt);
+  for (int t = kz; t < ntiles; t += KS) {
+    first_v = first_k;
+    cnt = cnt_k;
+    tile_at(t + 2 * KS, first_k, cnt_k);
+    weights();
+    scores();
+#pragma unroll
+    for (int u = 0; u < 4 * C * NQ; ++u) {   // one matrix instruction, then the vector work it hides
+      __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+      __builtin_amdgcn_sched_group_barrier(0x002, 2, 0);
+    }
+    load_k(first_k, cnt_k);
+    __builtin_amdgcn_sched_barrier(0);
+    accumulate();
+    load_v(first_v, cnt);
+    __builtin_amdgcn_sched_barrier(0);
+    maxima(cnt);
+  }
+
+  // ---- weights of the KS parts of a row: w = 2^(m_part - m) / l
+  float w[NQ];
+#pragma unroll
+  for (int n = 0; n < NQ; ++n) l[n] = column_sum(l[n]);
+  float* parts = smem + (KS > 1 ? KS * (ROWS / WR) * WR * OST : 0);   // [ROWS][KS][2], behind the partial results
+  if (KS > 1) {
+#pragma unroll
+    for (int n = 0; n < NQ; ++n)
+      if (g == 0) {
+        float* q = parts + ((16 * (wr * NQ + n) + l16) * KS + kz) * 2;
+        q[0] = m[n];
+        q[1] = l[n];
+      }
+    __syncthreads();
+#pragma unroll
+    for (int n = 0; n < NQ; ++n) {
+      const float* q = parts + (16 * (wr * NQ + n) + l16) * KS * 2;
+      float mt = -INFINITY, lt = 0.0f;
+#pragma unroll
+      for (int u = 0; u < KS; ++u) mt = fmaxf(mt, q[2 * u]);
+      const float m_use = mt == -INFINITY ? 0.0f : mt;
+#pragma unroll
+      for (int u = 0; u < KS; ++u) lt = fmaf(q[2 * u + 1], exp2f(q[2 * u] - m_use), lt);
+      w[n] = exp2f(m[n] - m_use);
+      m[n] = mt;
+      l[n] = lt;
+    }
+  } else {
+#pragma unroll
+    for (int n = 0; n < NQ; ++n) w[n] = 1.0f;
+  }
+#pragma unroll
+  for (int n = 0; n < NQ; ++n) w[n] = l[n] > 0.0f ? w[n] / l[n] : 0.0f;   // a row without a single real key: O_local = 0
+
+  float den[NQ];
+#pragma unroll
+  for (int n = 0; n < NQ; ++n) den[n] = 1.0f;
+  if (hist.L) {
+    // ---- O += R(phi(q)) L / (z_scale phi(q).z + eps) (Eq. 3, 6): O_local is scaled by the denominator, the products add
+    // the numerator to the same accumulators (L in column form, its key features in the place of tokens), one division
+    // at the end.  Each of the KS wavefronts takes every KS-th run of 16 key features.
+    const float* L = hist.L + (size_t)bh * D * D + 4 * l16;
+    const float* z = hist.z + (size_t)bh * D + 4 * g;
+    const T* qh = static_cast<const T*>(hist.q_hist);
+    f32x4 ph[NQ][C];
+#pragma unroll
+    for (int n = 0; n < NQ; ++n) {
+      const size_t qrow = (size_t)min(row[n], n_q - 1);
+      float acc = 0.0f;
+#pragma unroll
+      for (int c = 0; c < C; ++c) {
+        f32x4 x = load4<T>(qh + ((size_t)bh * n_q + qrow) * D + 16 * c + 4 * g);
+        const f32x4 zz = *reinterpret_cast<const f32x4*>(z + 16 * c);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          x[e] = phi_apply(x[e], hist.phi_kind);
+          acc = fmaf(x[e], zz[e], acc);
+        }
+        if (hist.cosq) {
+          const size_t at = qrow * (D / 2) + 8 * c + 2 * g;
+          const float2 cs = *reinterpret_cast<const float2*>(hist.cosq + at), sn = *reinterpret_cast<const float2*>(hist.sinq + at);
+          x = rotate4(x, cs.x, sn.x, cs.y, sn.y);
+        }
+        ph[n][c] = x;
+      }
+      den[n] = hist.z_scale * column_sum(acc) + hist.eps;
+      w[n] *= den[n];
+#pragma unroll
+      for (int f = 0; f < F; ++f)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) o[n][f][e] *= w[n];
+    }
+#pragma unroll
+    for (int c = 0; c < C; ++c) {
+      if (c % KS != kz) continue;   // uniform
+      f32x4 lv[4][F];
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+#pragma unroll
+        for (int f = 0; f < F; ++f) lv[r][f] = *reinterpret_cast<const f32x4*>(L + (size_t)(16 * c + 4 * g + r) * D + 64 * f);
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+#pragma unroll
+        for (int f = 0; f < F; ++f)
+#pragma unroll
+          for (int e = 0; e < 4; ++e)
+#pragma unroll
+            for (int n = 0; n < NQ; ++n) o[n][f][e] = mfma_f32(lv[r][f][e], ph[n][c][r], o[n][f][e]);
+    }
+#pragma unroll
+    for (int n = 0; n < NQ; ++n) den[n] = 1.0f / den[n];
+  } else {
+#pragma unroll
+    for (int n = 0; n < NQ; ++n)
+#pragma unroll
+      for (int f = 0; f < F; ++f)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) o[n][f][e] *= w[n];
+  }
+
+  if (hist.lse2) {
+    // ---- statistics for the backward pass: log2 of the sum of 2^(scaled logit), and D = dO . O_local from the unrounded
+    // output.  The KS parts of O_local are summed as scalars.
+    const T* dO = static_cast<const T*>(hist.d_out);
+#pragma unroll
+    for (int n = 0; n < NQ; ++n) {
+      float acc = 0.0f;
+      const T* gp = dO + ((size_t)bh * n_q + min(row[n], n_q - 1)) * D + 16 * g;
+#pragma unroll
+      for (int f = 0; f < F; ++f)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          const f32x4 x = load4<T>(gp + 64 * f + 4 * r);
+#pragma unroll
+          for (int e = 0; e < 4; ++e) acc = fmaf(o[n][f][e][r], x[e], acc);
+        }
+      acc = column_sum(acc);
+      if (KS > 1) {
+        float* q = smem + (16 * (wr * NQ + n) + l16) * KS;   // (the partial results' place is not used here)
+        if (g == 0) q[kz] = acc;
+        __syncthreads();
+        acc = 0.0f;
+#pragma unroll
+        for (int u = 0; u < KS; ++u) acc += q[u];
+      }
+      if (g == 0 && kz == 0 && row[n] < q_end) {
+        hist.lse2[(size_t)bh * n_q + row[n]] = l[n] > 0.0f ? m[n] + log2f(l[n]) : INFINITY;  // no real key: P = 0
+        hist.dvec[(size_t)bh * n_q + row[n]] = acc;
+      }
+    }
+    return;
+  }
+
+  if (KS == 1) {
+#pragma unroll
+    for (int n = 0; n < NQ; ++n)
+      if (row[n] < q_end) {
+        T* op = O + ((size_t)bh * n_q + row[n]) * D + 16 * g;
+#pragma unroll
+        for (int f = 0; f < F; ++f)
+#pragma unroll
+          for (int r = 0; r < 4; ++r)
+            store4<T>(op + 64 * f + 4 * r,
+                      f32x4{o[n][f][0][r], o[n][f][1][r], o[n][f][2][r], o[n][f][3][r]} * den[n]);
+      }
+    return;
+  }
+  // ---- the KS parts of a row meet in LDS; the workgroup's threads add them and store whole rows
+#pragma unroll
+  for (int n = 0; n < NQ; ++n) {
+    float* dst = smem + ((size_t)kz * ROWS + 16 * (wr * NQ + n) + l16) * OST + 16 * g;
+#pragma unroll
+    for (int f = 0; f < F; ++f)
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+        *reinterpret_cast<f32x4*>(dst + 64 * f + 4 * r) =
+            f32x4{o[n][f][0][r], o[n][f][1][r], o[n][f][2][r], o[n][f][3][r]} * den[n];
+  }
+  __syncthreads();
+  for (int e = threadIdx.x; e < ROWS * (D / 4); e += 256) {
+    const int rr = e / (D / 4), c4 = e - rr * (D / 4);
+    if (row0 + rr >= q_end) continue;
+    f32x4 v = *reinterpret_cast<const f32x4*>(smem + (size_t)rr * OST + 4 * c4);
+#pragma unroll
+    for (int u = 1; u < KS; ++u) v += *reinterpret_cast<const f32x4*>(smem + ((size_t)u * ROWS + rr) * OST + 4 * c4);
+    store4<T>(O + ((size_t)bh * n_q + row0 + rr) * D + 4 * c4, v);
+  }
+}
+
+template <typename T, int D, int NQ, int KS>
+int launch_wide(const hf_config& c, const void* Q, int n_q, const void* K, const void* V, int n_kv, const int32_t* idx,
+                int k, void* O, const WideHist& hist, hipStream_t s) {
+  constexpr int ROWS = 16 * NQ * 4 / KS;
+  const int BH = c.batch * c.heads;
+  const int t_m = (n_q + c.block_q - 1) / c.block_q, t_n = (n_kv + c.block_kv - 1) / c.block_kv;
+  const int chunks = (c.block_q + ROWS - 1) / ROWS;
+  const long long total = (long long)BH * t_m * chunks;
+  if (total > (1ll << 30)) { set_error("too many query blocks"); return HF_ERR_SHAPE; }
+  const int per_xcd = (int)((total + 7) / 8);
+  const float scale = c.softmax_scale > 0.0f ? c.softmax_scale : 1.0f / sqrtf((float)c.head_dim);
+  const size_t lds = KS > 1 ? ((size_t)KS * ROWS * (D + 4) + (size_t)ROWS * KS * 2) * sizeof(float) : 0;
+  auto kern = attn_wide_kernel<T, D, NQ, KS>;
+  if (lds > 64 * 1024) {
+    static LdsGrant grant;   // (one per instantiation, i.e. per kernel)
+    const int rc = grant_lds(grant, reinterpret_cast<const void*>(kern), (int)lds, "the fp32 attention kernel");
+    if (rc != HF_OK) return rc;
+  }
+  hipLaunchKernelGGL(kern, dim3(8 * per_xcd), dim3(256), lds, s, static_cast<const T*>(Q), static_cast<const T*>(K),
+                     static_cast<const T*>(V), idx, k, n_q, n_kv, kv_stride_of(c, n_kv), c.block_q, c.block_kv, t_m, t_n,
+                     chunks, per_xcd, (int)total, scale * 1.4426950408889634f, hist, static_cast<T*>(O));
+  return check_launch("hf_hybrid_attn_fwd(attention)");
+}
+
+// ---- fp32 storage, block_q and block_kv multiples of 32: tiles of 32 keys x 32 queries on the 32 x 32 x 2 instruction.
+// A workgroup owns 32 query rows of a block; its four wavefronts take every fourth tile of the list and meet in LDS once,
+// at the end.  A trip forms the scores of the wavefront's next tile next to the exponentials of the current one and then
+// accumulates the current one; every 16-byte piece is requested one such phase (4096 cycles at D = 128) before its use,
+// into the registers of a piece that has just been used.  Tile addresses are scalar (the tile's first row moves into the
+// buffer descriptor, whose end is the tile's last real row: what lies behind reads as zero).
+// Measured at 832x480 in fp32 (12 heads of 128, 4680 x 9360, k = 37 of 147 blocks of 64; selection included): 4.84 ms with
+// one key per lane and FMA arithmetic, 0.67 ms with the 16 x 16 tiles below, 0.61 ms (115 of the 154 TFLOP/s the
+// instruction sustains) with this kernel: the pipes are 86 % busy while a compute unit has work, and the last of 3.5 rounds
+// of workgroups leaves an eighth of the chip idle.
+template <int D>
+__global__ __launch_bounds__(256, 2) void attn_wide32_kernel(const float* __restrict__ Q, const float* __restrict__ K,
+                                                             const float* __restrict__ V, const int32_t* __restrict__ idx,
+                                                             int k, int n_q, int n_kv, int kv_stride, int bq, int bkv,
+                                                             int t_m, int t_n, int per_xcd, int total, float scale_log2e,
+                                                             WideHist hist, float* __restrict__ O) {
+  constexpr int KS = 4;                  // wavefronts that share the rows
+  constexpr int C = D / 8;               // row-form pieces of a token
+  constexpr int E = D / 32;              // 32-row operands of a column-form piece (features E i + e)
+  constexpr int OST = D + 4;             // floats per row of a partial result in LDS
+  constexpr int ROWB = D * 4;
+  typedef float vpiece __attribute__((ext_vector_type(E)));
+  typedef int i32x4 __attribute__((ext_vector_type(4)));
+  __shared__ __attribute__((aligned(16))) float part[KS][32][OST];
+  __shared__ float stat[32][KS][2];
+  const int item = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
+  if ((int)(blockIdx.x >> 3) >= per_xcd || item >= total) return;
+  const int chunks = bq >> 5;
+  const int bh = item / (t_m * chunks), in_head = item - bh * t_m * chunks;
+  const int qb = in_head / chunks, row0 = qb * bq + 32 * (in_head - qb * chunks);
+  const int q_end = min(n_q, (qb + 1) * bq);
+  if (row0 >= q_end) return;
+  const int lane = threadIdx.x & 63, kz = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int l32 = lane & 31, h = lane >> 5;
+  const uint64_t kbase = reinterpret_cast<uint64_t>(K + (size_t)bh * kv_stride * D);  // heads are kv_stride tokens apart
+  const uint64_t vbase = reinterpret_cast<uint64_t>(V + (size_t)bh * kv_stride * D);
+  const int32_t* row_idx = idx ? idx + ((size_t)bh * t_m + qb) * k : nullptr;
+  const int nsel = idx ? k : t_n;
+  const int subs = bkv >> 5;
+  const int ntiles = nsel * subs;
+  const int row = row0 + l32;            // rows past the block's end: clamped addresses, never written
+
+  // the scaled queries sit in LDS, in the place of the first partial result (in registers they would leave no room for a
+  // tile on its way); a piece is read one step ahead of its four products
+  for (int e = threadIdx.x; e < 32 * (D / 4); e += 256) {
+    const int rr = e / (D / 4), c4 = e - rr * (D / 4);
+    *reinterpret_cast<f32x4*>(&part[0][rr][4 * c4]) =
+        *reinterpret_cast<const f32x4*>(Q + ((size_t)bh * n_q + min(row0 + rr, n_q - 1)) * D + 4 * c4) * scale_log2e;
+  }
+  __syncthreads();
+  const float* sq = &part[0][l32][4 * h];
+  f32x4 qf = *reinterpret_cast<const f32x4*>(sq);
+  auto score_step = [&](const f32x4& kpiece, int c, f32x16& acc) {   // qf holds piece c, and piece c + 1 (mod C) afterwards
+    const f32x4 qn = *reinterpret_cast<const f32x4*>(sq + 8 * ((c + 1) % C));
+#pragma unroll
+    for (int e = 0; e < 4; ++e) acc = mfma_f32_wide(kpiece[e], qf[e], acc);
+    qf = qn;
+  };
+  f32x16 o[E];
+#pragma unroll
+  for (int e = 0; e < E; ++e)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) o[e][r] = 0.0f;
+  float m = -INFINITY, l = 0.0f;
+
+  // tile t of the list: first key and number of real keys (0: past the list or an index out of range)
+  auto tile_at = [&](int t, int& first, int& cnt) {
+    const int s = t / subs, sub = t - s * subs;
+    const int jb = row_idx ? row_idx[min(s, nsel - 1)] : s;
+    const int st = jb * bkv + 32 * sub;
+    const bool ok = s < nsel && (unsigned)jb < (unsigned)t_n;
+    const int n = ok ? min(32, n_kv - st) : 0;
+    cnt = n > 0 ? n : 0;
+    first = n > 0 ? st : 0;
+  };
+  auto desc = [&](uint64_t base, int first, int cnt) {
+    const uint64_t b = base + (uint64_t)(uint32_t)__builtin_amdgcn_readfirstlane(first) * ROWB;
+    return __builtin_amdgcn_make_buffer_rsrc(reinterpret_cast<void*>(b), 0, __builtin_amdgcn_readfirstlane(cnt) * ROWB, 0x00020000);
+  };
+  int k_off = l32 * ROWB + 16 * h;
+  int v_off[4];
+#pragma unroll
+  for (int u = 0; u < 4; ++u) v_off[u] = (8 * u + 4 * h) * ROWB + 4 * E * l32;
+  f32x4 kb[C];
+  vpiece vb[16];
+  auto load_k = [&](__amdgpu_buffer_rsrc_t d, int c) {
+    kb[c] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(d, k_off + 32 * c, 0, 0));
+  };
+  auto load_v = [&](__amdgpu_buffer_rsrc_t d, int r) {
+    const int off = v_off[r >> 2] + (r & 3) * ROWB;
+    if constexpr (E == 4) vb[r] = __builtin_bit_cast(vpiece, __builtin_amdgcn_raw_buffer_load_b128(d, off, 0, 0));
+    else vb[r] = __builtin_bit_cast(vpiece, __builtin_amdgcn_raw_buffer_load_b64(d, off, 0, 0));
+  };
+
+  f32x16 sc;   // scores of the wavefront's next tile
+  // missing keys to -inf, the maximum into the reference m; what was accumulated under a smaller reference is scaled
+  // (rarely: only once the maximum has grown by more than 2^8; any reference is exact in floating point)
+  auto maxima = [&](int cnt) {
+    if (cnt < 32) {
+      const int mine = cnt - 4 * h;   // (one register; sixteen key numbers would be kept over the loop)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) sc[r] = 8 * (r >> 2) + (r & 3) < mine ? sc[r] : -INFINITY;
+    }
+    float mx = sc[0];
+#pragma unroll
+    for (int r = 1; r < 16; ++r) mx = fmaxf(mx, sc[r]);
+    const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(mx), __float_as_uint(mx), false, false);
+    mx = fmaxf(__uint_as_float(sw[0]), __uint_as_float(sw[1]));
+    if (__any(mx > m + 8.0f)) {
+      const float m_new = fmaxf(m, mx);
+      const float alpha = exp2f(m - (m_new == -INFINITY ? 0.0f : m_new));
+      m = m_new;
+      l *= alpha;
+#pragma unroll
+      for (int e = 0; e < E; ++e)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) o[e][r] *= alpha;
+    }
+  };
+
+  int first_v, cnt_v, first_k, cnt_k;
+  tile_at(kz, first_v, cnt_v);
+  tile_at(kz + KS, first_k, cnt_k);
+  {
+    const __amdgpu_buffer_rsrc_t dk = desc(kbase, first_v, cnt_v), dn = desc(kbase, first_k, cnt_k);
+#pragma unroll
+    for (int c = 0; c < C; ++c) load_k(dk, c);
+#pragma unroll
+    for (int r = 0; r < 16; ++r) sc[r] = 0.0f;
+#pragma unroll
+    for (int c = 0; c < C; ++c) {
+      score_step(kb[c], c, sc);
+      load_k(dn, c);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    maxima(cnt_v);
+  }
+  for (int t = kz; t < ntiles; t += KS) {
+    const __amdgpu_buffer_rsrc_t dv = desc(vbase, first_v, cnt_v);
+    int first_n, cnt_n;
+    tile_at(t + 2 * KS, first_n, cnt_n);
+    const __amdgpu_buffer_rsrc_t dk = desc(kbase, first_n, cnt_n);
+    // (opaque here, or the sums of offsets leave the loop as sixteen registers instead of becoming immediates)
+    asm volatile("" : "+v"(k_off), "+v"(v_off[0]), "+v"(v_off[1]), "+v"(v_off[2]), "+v"(v_off[3]));
+    const float m_use = m == -INFINITY ? 0.0f : m;   // nothing seen yet: keep the exponents finite
+    f32x16 p = sc;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) sc[r] = 0.0f;
+#pragma unroll
+    for (int c = 0; c < C; ++c) {   // scores of tile t + KS; weights of tile t; its values requested
+      score_step(kb[c], c, sc);
+#pragma unroll
+      for (int r = c * 16 / C; r < (c + 1) * 16 / C; ++r) {
+        p[r] = __builtin_amdgcn_exp2f(p[r] - m_use);
+        l += p[r];                  // this lane's keys only; summed at the end
+        load_v(dv, r);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    }
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {  // tile t accumulated; the keys of tile t + 2 KS requested
+#pragma unroll
+      for (int e = 0; e < E; ++e) o[e] = mfma_f32_wide(vb[r][e], p[r], o[e]);
+      if ((r + 1) * C / 16 > r * C / 16) load_k(dk, r * C / 16);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    maxima(cnt_k);
+    first_v = first_k;
+    cnt_v = cnt_k;
+    first_k = first_n;
+    cnt_k = cnt_n;
+  }
+
+  // ---- weights of the KS parts of a row: w = 2^(m_part - m) / l
+  auto both_halves = [](float x) {
+    const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+    return __uint_as_float(sw[0]) + __uint_as_float(sw[1]);
+  };
+  l = both_halves(l);
+  if (h == 0) {
+    stat[l32][kz][0] = m;
+    stat[l32][kz][1] = l;
+  }
+  __syncthreads();
+  float m_tot = -INFINITY, l_tot = 0.0f;
+#pragma unroll
+  for (int u = 0; u < KS; ++u) m_tot = fmaxf(m_tot, stat[l32][u][0]);
+  const float m_use = m_tot == -INFINITY ? 0.0f : m_tot;
+#pragma unroll
+  for (int u = 0; u < KS; ++u) l_tot = fmaf(stat[l32][u][1], exp2f(stat[l32][u][0] - m_use), l_tot);
+  float w = l_tot > 0.0f ? exp2f(m - m_use) / l_tot : 0.0f;   // a row without a single real key: O_local = 0
+
+  if (hist.lse2) {
+    // ---- statistics for the backward pass: log2 of the sum of 2^(scaled logit), and D = dO . O_local from the unrounded
+    // output, the four parts of which are summed as scalars
+    const float* gp = static_cast<const float*>(hist.d_out) + ((size_t)bh * n_q + min(row, n_q - 1)) * D;
+    float acc = 0.0f;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      const vpiece x = *reinterpret_cast<const vpiece*>(gp + E * (8 * (r >> 2) + 4 * h + (r & 3)));
+#pragma unroll
+      for (int e = 0; e < E; ++e) acc = fmaf(o[e][r] * w, x[e], acc);
+    }
+    acc = both_halves(acc);
+    if (h == 0) part[0][l32][kz] = acc;
+    __syncthreads();
+    if (threadIdx.x < 32 && row < q_end) {
+      const size_t at = (size_t)bh * n_q + row;
+      hist.lse2[at] = l_tot > 0.0f ? m_tot + log2f(l_tot) : INFINITY;  // no real key: P = 0
+      hist.dvec[at] = (part[0][l32][0] + part[0][l32][1]) + (part[0][l32][2] + part[0][l32][3]);
+    }
+    return;
+  }
+
+  float inv_den = 1.0f;
+  if (hist.L) {
+    // ---- O += R(phi(q)) L / (z_scale phi(q).z + eps) (Eq. 3, 6), as in attn_wide_kernel: O_local is scaled by the
+    // denominator, the products add the numerator; wavefront kz takes the key features [kz D / 4, (kz + 1) D / 4)
+    const float* L = hist.L + (size_t)bh * D * D;
+    const float* z = hist.z + (size_t)bh * D + 4 * h;
+    const float* qp = static_cast<const float*>(hist.q_hist) + ((size_t)bh * n_q + min(row, n_q - 1)) * D + 4 * h;
+    const size_t trow = (size_t)min(row, n_q - 1) * (D / 2) + 2 * h;
+    f32x4 ph[C / KS];
+    float acc = 0.0f;
+#pragma unroll
+    for (int c = 0; c < C; ++c) {
+      f32x4 x = *reinterpret_cast<const f32x4*>(qp + 8 * c);
+      const f32x4 zz = *reinterpret_cast<const f32x4*>(z + 8 * c);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        x[e] = phi_apply(x[e], hist.phi_kind);
+        acc = fmaf(x[e], zz[e], acc);
+      }
+      if (c / (C / KS) == kz) {   // uniform
+        if (hist.cosq) {
+          const f32x2 cs = *reinterpret_cast<const f32x2*>(hist.cosq + trow + 4 * c), sn = *reinterpret_cast<const f32x2*>(hist.sinq + trow + 4 * c);
+          x = rotate4(x, cs[0], sn[0], cs[1], sn[1]);
+        }
+        ph[c % (C / KS)] = x;
+      }
+    }
+    const float den = hist.z_scale * both_halves(acc) + hist.eps;
+    w *= den;
+    inv_den = 1.0f / den;
+#pragma unroll
+    for (int e = 0; e < E; ++e)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) o[e][r] *= w;
+#pragma unroll
+    for (int c = 0; c < C / KS; ++c) {
+      const float* Lp = L + (size_t)(8 * (kz * (C / KS) + c) + 4 * h) * D + E * l32;
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const vpiece a = *reinterpret_cast<const vpiece*>(Lp + (size_t)r * D);
+#pragma unroll
+        for (int e = 0; e < E; ++e) o[e] = mfma_f32_wide(a[e], ph[c][r], o[e]);
+      }
+    }
+    w = 1.0f;
+  }
+#pragma unroll
+  for (int r = 0; r < 16; ++r) {
+    vpiece x;
+#pragma unroll
+    for (int e = 0; e < E; ++e) x[e] = o[e][r] * w * inv_den;
+    *reinterpret_cast<vpiece*>(&part[kz][l32][E * (8 * (r >> 2) + 4 * h + (r & 3))]) = x;
+  }
+  __syncthreads();
+  for (int e = threadIdx.x; e < 32 * (D / 4); e += 256) {   // the four parts added, whole rows stored
+    const int rr = e / (D / 4), c4 = e - rr * (D / 4);
+    if (row0 + rr >= q_end) continue;
+    f32x4 v = *reinterpret_cast<const f32x4*>(&part[0][rr][4 * c4]);
+#pragma unroll
+    for (int u = 1; u < KS; ++u) v += *reinterpret_cast<const f32x4*>(&part[u][rr][4 * c4]);
+    *reinterpret_cast<f32x4*>(O + ((size_t)bh * n_q + row0 + rr) * D + 4 * c4) = v;
+  }
+}
+
+template <int D>
+int launch_wide32(const hf_config& c, const void* Q, int n_q, const void* K, const void* V, int n_kv, const int32_t* idx,
+                  int k, void* O, const WideHist& hist, hipStream_t s) {
+  const int t_m = (n_q + c.block_q - 1) / c.block_q, t_n = (n_kv + c.block_kv - 1) / c.block_kv;
+  const long long total = (long long)c.batch * c.heads * t_m * (c.block_q / 32);
+  if (total > (1ll << 30)) { set_error("too many query blocks"); return HF_ERR_SHAPE; }
+  const int per_xcd = (int)((total + 7) / 8);
+  const float scale = c.softmax_scale > 0.0f ? c.softmax_scale : 1.0f / sqrtf((float)c.head_dim);
+  hipLaunchKernelGGL((attn_wide32_kernel<D>), dim3(8 * per_xcd), dim3(256), 0, s, static_cast<const float*>(Q),
+                     static_cast<const float*>(K), static_cast<const float*>(V), idx, k, n_q, n_kv, kv_stride_of(c, n_kv),
+                     c.block_q, c.block_kv, t_m, t_n, per_xcd, (int)total, scale * 1.4426950408889634f, hist,
+                     static_cast<float*>(O));
+  return check_launch("hf_hybrid_attn_fwd(attention)");
+}
+
+// Rows per workgroup: the most of 128, 64, 32, 16 that leaves at most an eighth of them without a query row and still gives
+// two workgroups per compute unit; with fewer rows more wavefronts share them and a row's list is split further.
+template <typename T, int D>
+int launch_wide_rows(const hf_config& c, const void* Q, int n_q, const void* K, const void* V, int n_kv,
+                     const int32_t* idx, int k, void* O, const WideHist& hist, hipStream_t s) {
+  int rows = 128;
+  const long long blocks = (long long)c.batch * c.heads * ((n_q + c.block_q - 1) / c.block_q);
+  while (rows > 16) {
+    const int chunks = (c.block_q + rows - 1) / rows;
+    const bool waste = chunks * rows * 8 > c.block_q * 9;       // more than an eighth of the rows do not exist
+    const bool idle = blocks * chunks < 512;                     // fewer workgroups than two per compute unit
+    if (!waste && !idle) break;
+    rows >>= 1;
+  }
+  if (rows == 128) return launch_wide<T, D, 2, 1>(c, Q, n_q, K, V, n_kv, idx, k, O, hist, s);
+  if (rows == 64) return launch_wide<T, D, 2, 2>(c, Q, n_q, K, V, n_kv, idx, k, O, hist, s);
+  if (rows == 32) return launch_wide<T, D, 2, 4>(c, Q, n_q, K, V, n_kv, idx, k, O, hist, s);
+  return launch_wide<T, D, 1, 4>(c, Q, n_q, K, V, n_kv, idx, k, O, hist, s);
 }
 
 }  // namespace
 
-int launch_attn_generic(const hf_config& c, const void* Q, int n_q, const void* K, const void* V, int n_kv,
-                        const int32_t* idx, int k, void* O_local, hipStream_t s, float* lse2, const void* dO,
-                        float* Dv) {
-  const int BH = c.batch * c.heads;
-  const int t_m = (n_q + c.block_q - 1) / c.block_q, t_n = (n_kv + c.block_kv - 1) / c.block_kv;
-  const float scale = c.softmax_scale > 0.0f ? c.softmax_scale : 1.0f / sqrtf((float)c.head_dim);
-  const float sl2 = scale * 1.4426950408889634f;
-  const dim3 grid(t_m, BH), block(256);
-#define HF_LAUNCH_GENERIC(T, DD)                                                                           \
-  hipLaunchKernelGGL((attn_generic_kernel<T, DD, 4>), grid, block, 0, s, static_cast<const T*>(Q),         \
-                     static_cast<const T*>(K), static_cast<const T*>(V), idx, k, n_q, n_kv, kv_stride_of(c, n_kv), c.block_q, \
-                     c.block_kv, t_m, t_n, sl2, static_cast<T*>(O_local), lse2, static_cast<const T*>(dO), Dv)
-  if (c.dtype == HF_F32) {
-    if (c.head_dim == 128) HF_LAUNCH_GENERIC(float, 128); else HF_LAUNCH_GENERIC(float, 64);
-  } else {
-    if (c.head_dim == 128) HF_LAUNCH_GENERIC(bf16_t, 128); else HF_LAUNCH_GENERIC(bf16_t, 64);
-  }
-#undef HF_LAUNCH_GENERIC
-  return check_launch("hf_hybrid_attn_fwd(attention)");
+static int launch_attn_wide(const hf_config& c, const void* Q, int n_q, const void* K, const void* V, int n_kv,
+                            const int32_t* idx, int k, void* O, const WideHist& hist, hipStream_t s) {
+  if (c.dtype == HF_F32 && c.block_q % 32 == 0 && c.block_kv % 32 == 0)
+    return c.head_dim == 128 ? launch_wide32<128>(c, Q, n_q, K, V, n_kv, idx, k, O, hist, s)
+                             : launch_wide32<64>(c, Q, n_q, K, V, n_kv, idx, k, O, hist, s);
+  if (c.dtype == HF_F32)
+    return c.head_dim == 128 ? launch_wide_rows<float, 128>(c, Q, n_q, K, V, n_kv, idx, k, O, hist, s)
+                             : launch_wide_rows<float, 64>(c, Q, n_q, K, V, n_kv, idx, k, O, hist, s);
+  return c.head_dim == 128 ? launch_wide_rows<bf16_t, 128>(c, Q, n_q, K, V, n_kv, idx, k, O, hist, s)
+                           : launch_wide_rows<bf16_t, 64>(c, Q, n_q, K, V, n_kv, idx, k, O, hist, s);
+}
+
+int launch_attn_wide_stats(const hf_config& c, const void* Q, int n_q, const void* K, const void* V, int n_kv,
+                           const int32_t* idx, int k, const void* dO, float* lse2, float* dvec, hipStream_t s) {
+  WideHist h = {};
+  h.lse2 = lse2;
+  h.d_out = dO;
+  h.dvec = dvec;
+  return launch_attn_wide(c, Q, n_q, K, V, n_kv, idx, k, nullptr, h, s);
 }
 
 int launch_attn_mfma(const hf_config& c, const void* Q, int n_q, const void* K, const void* V, int n_kv,
@@ -166,17 +745,31 @@ int launch_attn_w64(const hf_config& c, const void* Q, int n_q, const void* K, c
                     const int32_t* idx, int k, void* O_local, hipStream_t s);  // hf_attn_w64.hip
 bool attn_w64_supported(const hf_config& c);
 
+// shapes whose attention kernel is the one of this file, which adds the history term itself
+bool attn_wide_taken(const hf_config& c) { return !attn_mfma_supported(c) && !attn_w64_supported(c); }
+
+int launch_attn_wide_hist(const hf_config& c, const void* Q, const void* Q_hist, int n_q, const void* K, const void* V,
+                          int n_kv, const int32_t* idx, int k, const float* state, const float* cosq, const float* sinq,
+                          void* O, hipStream_t s) {
+  WideHist h = {};
+  h.L = state;
+  h.z = state + (size_t)c.batch * c.heads * c.head_dim * c.head_dim;
+  h.cosq = cosq;
+  h.sinq = sinq;
+  h.q_hist = Q_hist;
+  h.eps = c.eps;
+  h.z_scale = c.z_scale;
+  h.phi_kind = c.phi;
+  return launch_attn_wide(c, Q, n_q, K, V, n_kv, idx, k, O, h, s);
+}
+
 int launch_attn(const hf_config& c, const void* Q, int n_q, const void* K, const void* V, int n_kv,
                 const int32_t* idx, int k, void* O_local, hipStream_t s) {
-  if (c.batch * c.heads > 65535 || (n_q + c.block_q - 1) / c.block_q > (1 << 30)) {
-    set_error("grid too large");
-    return HF_ERR_SHAPE;
-  }
   // bf16, head_dim 128: block_q 64 / 128 take the workgroup-per-query-block MFMA kernel, other
   // multiples of 64 the wavefront-per-64-rows MFMA kernel; everything else the fp32-arithmetic one
   if (attn_mfma_supported(c)) return launch_attn_mfma(c, Q, n_q, K, V, n_kv, idx, k, O_local, s);
   if (attn_w64_supported(c)) return launch_attn_w64(c, Q, n_q, K, V, n_kv, idx, k, O_local, s);
-  return launch_attn_generic(c, Q, n_q, K, V, n_kv, idx, k, O_local, s, nullptr, nullptr, nullptr);
+  return launch_attn_wide(c, Q, n_q, K, V, n_kv, idx, k, O_local, WideHist{}, s);
 }
 
 }  // namespace hf

@@ -110,9 +110,13 @@ int launch_score_select(const hf_config& c, const float* qbar, const float* kbar
                         int k, int32_t* idx, float* scores, hipStream_t s);
 int launch_attn(const hf_config& c, const void* Q, int n_q, const void* K, const void* V, int n_kv,
                 const int32_t* idx, int k, void* O_local, hipStream_t s);
-int launch_readout(const hf_config& c, const void* Q, int n_q, const void* O_local,
-                   const float* state, const float* cosq, const float* sinq, void* planes, void* O,
-                   hipStream_t s);
+// shapes whose attention kernel computes in fp32 and adds the history term itself
+bool attn_wide_taken(const hf_config& c);
+int launch_attn_wide_hist(const hf_config& c, const void* Q, const void* Q_hist, int n_q, const void* K, const void* V,
+                          int n_kv, const int32_t* idx, int k, const float* state, const float* cosq, const float* sinq,
+                          void* O, hipStream_t s);
+int launch_readout_mfma(const hf_config& c, const void* Q, int n_q, const void* O_local, const float* state,
+                        const float* cosq, const float* sinq, void* planes, void* O, hipStream_t s);
 size_t readout_planes_bytes(const hf_config& c);  // scratch for the bf16 planes of the state
 int launch_state_planes(const hf_config& c, const float* state, void* planes, hipStream_t s);
 bool attn_mfma_fused_supported(const hf_config& c);
@@ -136,9 +140,8 @@ int launch_attn_mfma_step(const hf_config& c, const void* Q, int n_q, const void
 int launch_attn_mfma_lse(const hf_config& c, const void* Q, int n_q, const void* K, const void* V, int n_kv,
                          const int32_t* idx, int k, void* O_local, float* lse2_out, hipStream_t s);
 // backward pass (training algorithm): lse2 = per-row log2 of the softmax denominator in the scaled-logit domain
-int launch_attn_generic(const hf_config& c, const void* Q, int n_q, const void* K, const void* V, int n_kv,
-                        const int32_t* idx, int k, void* O_local, hipStream_t s, float* lse2, const void* dO,
-                        float* Dv);  // lse2 given: writes lse2 and Dv = dO . O_local instead of O_local
+int launch_attn_wide_stats(const hf_config& c, const void* Q, int n_q, const void* K, const void* V, int n_kv,
+                           const int32_t* idx, int k, const void* dO, float* lse2, float* dvec, hipStream_t s);
 int launch_attn_mfma_stats(const hf_config& c, const void* Q, int n_q, const void* K, const void* V, int n_kv,
                            const int32_t* idx, int k, const void* dO, float* lse2, float* dvec, hipStream_t s);
 int launch_row_dot(const hf_config& c, const void* A, const void* B, long long rows, float* out, hipStream_t s);
