@@ -141,17 +141,16 @@ static WorkspaceLayout workspace_layout(const hf_config* c, int n_q, int n_kv) {
 }
 
 struct BwdLayout {
-  size_t lse2, dvec, dqh32, inv_cnt, inv_list, order, planes, total;  // byte offsets
+  size_t lse2, dvec, inv_cnt, inv_list, order, planes, total;  // byte offsets
 };
 
 static BwdLayout bwd_layout(const hf_config* c, int n_q, int n_kv) {
-  const size_t bh = (size_t)c->batch * c->heads, d = c->head_dim;
+  const size_t bh = (size_t)c->batch * c->heads;
   const size_t t_m = cdiv(n_q, c->block_q), t_n = cdiv(n_kv, c->block_kv);
   BwdLayout w;
   w.lse2 = 0;
   w.dvec = align256(bh * n_q * 4);
-  w.dqh32 = w.dvec + align256(bh * n_q * 4);
-  w.inv_cnt = w.dqh32 + align256(bh * (size_t)n_q * d * 4);
+  w.inv_cnt = w.dvec + align256(bh * n_q * 4);
   w.inv_list = w.inv_cnt + align256(bh * t_n * 4);
   w.order = w.inv_list + align256(bh * t_n * t_m * 4);   // launch order of the dK/dV workgroups (64 keys each):
   w.planes = w.order + align256(bh * t_n * cdiv(c->block_kv, 64) * 8 * 4);   // records of 8 words
@@ -1136,7 +1135,6 @@ static int bwd_impl(const hf_config* cfg, const void* Q, const void* Q_hist, int
   char* ws = static_cast<char*>(workspace);
   float* lse2 = reinterpret_cast<float*>(ws + w.lse2);
   float* dvec = reinterpret_cast<float*>(ws + w.dvec);
-  float* dqh32 = reinterpret_cast<float*>(ws + w.dqh32);
   int32_t* inv_cnt = block_idx ? reinterpret_cast<int32_t*>(ws + w.inv_cnt) : nullptr;
   int32_t* inv_list = block_idx ? reinterpret_cast<int32_t*>(ws + w.inv_list) : nullptr;
   const float* st = static_cast<const float*>(state_or_null);
@@ -1162,19 +1160,9 @@ static int bwd_impl(const hf_config* cfg, const void* Q, const void* Q_hist, int
                            reinterpret_cast<int32_t*>(ws + w.order), st, rope_cos_q, rope_sin_q, Q_hist, ws + w.planes,
                            dQ, dQ_hist, dK, dV, s);
   }
-  // history branch first: its gradient either is an output of its own or joins dQ before dQ's one rounding
-  const float* add_to_dq = nullptr;
-  if (st) {
-    if (split) {
-      HF_TRY(launch_bwd_hist_generic(*cfg, Q_hist, dO, st, n_q, rope_cos_q, rope_sin_q, dQ_hist, false, s));
-    } else {
-      HF_TRY(launch_bwd_hist_generic(*cfg, Q_hist, dO, st, n_q, rope_cos_q, rope_sin_q, dqh32, true, s));
-      add_to_dq = dqh32;
-    }
-  }
   HF_TRY(launch_attn_wide_stats(*cfg, Q, n_q, K_win, V_win, n_kv, block_idx, k, dO, lse2, dvec, s));
-  return launch_bwd_generic(*cfg, Q, n_q, K_win, V_win, n_kv, block_idx, k, dO, lse2, dvec, inv_cnt, inv_list,
-                            add_to_dq, dQ, dK, dV, s);
+  return launch_bwd_generic(*cfg, Q, Q_hist, n_q, K_win, V_win, n_kv, block_idx, k, dO, lse2, dvec, inv_cnt, inv_list, st,
+                            rope_cos_q, rope_sin_q, dQ, st ? dQ_hist : nullptr, dK, dV, s);
 }
 
 int hf_rope_window_indices(int32_t i_newest, int32_t n_frames, int32_t t0, int32_t* idx_out) {

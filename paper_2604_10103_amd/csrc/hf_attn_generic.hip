@@ -424,7 +424,6 @@ __global__ __launch_bounds__(256, 2) void attn_wide32_kernel(const float* __rest
   constexpr int OST = D + 4;             // floats per row of a partial result in LDS
   constexpr int ROWB = D * 4;
   typedef float vpiece __attribute__((ext_vector_type(E)));
-  typedef int i32x4 __attribute__((ext_vector_type(4)));
   __shared__ __attribute__((aligned(16))) float part[KS][32][OST];
   __shared__ float stat[32][KS][2];
   const int item = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);

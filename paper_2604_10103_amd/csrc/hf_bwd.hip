@@ -2,7 +2,7 @@
 // chunk that runs with gradients enabled): dQ, dK, dV of the block-sparse softmax attention (Eq. 5)
 // for a fixed Top-K mask, and the gradient of the history readout (Eq. 3) with respect to its
 // queries for a constant state.  This file: the kernels every shape and type can take (fp32
-// arithmetic, one wavefront per few rows) and the small helpers shared with the matrix-core path.
+// arithmetic on the fp32 matrix instruction, hf_f32_mfma.h) and the small helpers shared with the bf16 path.
 //
 // With P recomputed from the saved row statistic lse2 = log2 sum_j 2^(c s_ij) (c = scale log2 e):
 //     D_i  = dO_i . O_local_i      (from the recomputed forward pass, before O_local is rounded)
@@ -13,7 +13,7 @@
 // selected a KV block), so both accumulate in registers and nothing is added atomically.
 #include <math.h>
 
-#include "hf_common.h"
+#include "hf_f32_mfma.h"
 
 namespace hf {
 namespace {
@@ -91,310 +91,494 @@ __global__ __launch_bounds__(64 * kInvWaves) void invert_index_lds_kernel(const 
     }
 }
 
-// ---- dQ: R query rows per wavefront, lanes = keys for the dot products, lanes = features for dQ ------
-template <typename T, int D, int R>
-__global__ __launch_bounds__(256) void bwd_dq_generic_kernel(
+// History branch (Eq. 3) in the dQ kernel's epilogue, as in the bf16 kernel: with f = phi(q), r = R f,
+// den = z_scale f.z + eps, num = r L:   dnum = g / den, dden = -(g . num) / den^2,
+// dq = (R^T (dnum L^T) + z_scale dden z) phi'(q)
+struct WideBwdHist {
+  const float* L;        // [BH][D][D], NULL: none
+  const float* z;        // [BH][D]
+  const float* cosq;     // [n_q][D/2] or NULL
+  const float* sinq;
+  const void* q_hist;    // [BH][n_q][D] queries of the history branch
+  void* dq_hist;         // given: their gradient on its own; NULL: it joins dQ before the one rounding
+  float eps, z_scale;
+  int phi_kind;
+};
+
+constexpr int kParts = 4;   // wavefronts of a workgroup: they share its rows (keys) and split the list between them
+
+// the parts of a [16 N][D] result (column-form accumulators) meet in LDS; whole rows are stored
+template <typename T, int D, int N>
+__device__ __forceinline__ void add_parts_and_store(float* smem, const f32x4 (&acc)[N][D / 64][4], float mul, int kz, int l16,
+                                                    int g, T* dst, int rows) {
+  constexpr int OST = D + 4, F = D / 64;
+#pragma unroll
+  for (int n = 0; n < N; ++n) {
+    float* p = smem + ((size_t)kz * 16 * N + 16 * n + l16) * OST + 16 * g;
+#pragma unroll
+    for (int f = 0; f < F; ++f)
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+        *reinterpret_cast<f32x4*>(p + 64 * f + 4 * r) =
+            f32x4{acc[n][f][0][r], acc[n][f][1][r], acc[n][f][2][r], acc[n][f][3][r]} * mul;
+  }
+  __syncthreads();
+  for (int e = threadIdx.x; e < 16 * N * (D / 4); e += 64 * kParts) {
+    const int rr = e / (D / 4), c4 = e - rr * (D / 4);
+    if (rr >= rows) continue;
+    f32x4 v = *reinterpret_cast<const f32x4*>(smem + (size_t)rr * OST + 4 * c4);
+#pragma unroll
+    for (int u = 1; u < kParts; ++u) v += *reinterpret_cast<const f32x4*>(smem + ((size_t)u * 16 * N + rr) * OST + 4 * c4);
+    store4<T>(dst + (size_t)rr * D + 4 * c4, v);
+  }
+}
+
+// ---- dQ: a workgroup per 16 NQ query rows; S^T and dP^T = V dO^T (row form), dS^T = P^T (dP^T - D), dQ^T += K^T dS^T
+// (column form), all on 16 x 16 x 4 fp32 products.  Q and dO wait in LDS (B operands, shared by the four wavefronts); the
+// keys' and values' pieces travel one product phase ahead, each into the registers of a piece that has just been used.
+// Bound by the fp32 matrix rate.  12 heads of 128, 1170 x 2340, k = 10 of 37 blocks of 64: 92 us (0.71 ms with one key per
+// lane and FMA arithmetic, plus 0.21 ms for the history branch's gradient as a kernel of its own).
+template <typename T, int D, int NQ>
+__global__ __launch_bounds__(64 * kParts, 2) void bwd_dq_wide_kernel(
     const T* __restrict__ Q, const T* __restrict__ K, const T* __restrict__ V, const T* __restrict__ dO,
-    const int32_t* __restrict__ idx, int k, int n_q, int n_kv, int kv_stride, int bq, int bkv, int t_m, int t_n,
-    float scale_log2e, float scale, const float* __restrict__ lse2, const float* __restrict__ Dv,
-    const float* __restrict__ dqh32, T* __restrict__ dQ) {
-  constexpr int E = Elem<T>::kPer16B;
-  constexpr int C = D / kWave;
-  __shared__ float sq[4][R][D];
-  __shared__ float sdo[4][R][D];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int qb = blockIdx.x, bh = blockIdx.y;
-  const T* Qh = Q + (size_t)bh * n_q * D;
-  const T* dOh = dO + (size_t)bh * n_q * D;
+    const int32_t* __restrict__ idx, int k, int n_q, int n_kv, int kv_stride, int bq, int bkv, int t_m, int t_n, int chunks,
+    int per_xcd, int total, float scale_log2e, float scale, const float* __restrict__ lse2, const float* __restrict__ Dv,
+    WideBwdHist hist, T* __restrict__ dQ) {
+  constexpr int ROWS = 16 * NQ, C = D / 16, F = D / 64, OST = D + 4;
+  extern __shared__ __attribute__((aligned(16))) float smem[];   // [ROWS][OST] Q, [ROWS][OST] dO; later four partial results
+  __shared__ float gpart[ROWS][kParts];
+  float* sQ = smem;
+  float* sG = smem + ROWS * OST;
+  const int item = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
+  if ((int)(blockIdx.x >> 3) >= per_xcd || item >= total) return;
+  const int bh = item / (t_m * chunks), in_head = item - bh * t_m * chunks;
+  const int qb = in_head / chunks, row0 = qb * bq + (in_head - qb * chunks) * ROWS;
+  const int q_end = min(n_q, (qb + 1) * bq);
+  if (row0 >= q_end) return;
+  const int lane = threadIdx.x & 63, kz = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int l16 = lane & 15, g = lane >> 4;
   const T* Kh = K + (size_t)bh * kv_stride * D;
   const T* Vh = V + (size_t)bh * kv_stride * D;
   const int32_t* row_idx = idx ? idx + ((size_t)bh * t_m + qb) * k : nullptr;
-  const int nsel = idx ? k : t_n;
-  const int q_end = min(n_q, (qb + 1) * bq);
+  const int nsel = idx ? k : t_n, subs = (bkv + 15) / 16, ntiles = nsel * subs;
 
-  for (int pass0 = qb * bq; pass0 < q_end; pass0 += 4 * R) {
-    const int r0 = pass0 + wave * R;
-    for (int w = lane; w < R * D; w += kWave) {
-      const int rr = w / D, c = w % D;
-      const int row = min(r0 + rr, n_q - 1);
-      sq[wave][rr][c] = Elem<T>::load(Qh + (size_t)row * D + c) * scale_log2e;
-      sdo[wave][rr][c] = Elem<T>::load(dOh + (size_t)row * D + c);
+  for (int e = threadIdx.x; e < ROWS * (D / 4); e += 64 * kParts) {
+    const int rr = e / (D / 4), c4 = e - rr * (D / 4);
+    const size_t off = ((size_t)bh * n_q + min(row0 + rr, n_q - 1)) * D + 4 * c4;
+    *reinterpret_cast<f32x4*>(sQ + rr * OST + 4 * c4) = load4<T>(Q + off) * scale_log2e;
+    *reinterpret_cast<f32x4*>(sG + rr * OST + 4 * c4) = load4<T>(dO + off);
+  }
+  float lse[NQ], dv[NQ];
+  f32x4 dq[NQ][F][4];
+#pragma unroll
+  for (int n = 0; n < NQ; ++n) {
+    const size_t at = (size_t)bh * n_q + min(row0 + 16 * n + l16, n_q - 1);
+    lse[n] = lse2[at];
+    dv[n] = Dv[at];
+#pragma unroll
+    for (int f = 0; f < F; ++f)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) dq[n][f][e] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+  }
+  __syncthreads();
+
+  auto tile_at = [&](int t, int& first, int& cnt) {   // cnt 0: past the list, an index out of range, or no such keys
+    const int s = t / subs, sub = t - s * subs;
+    const int jb = row_idx ? row_idx[min(s, nsel - 1)] : s;
+    const int st = jb * bkv + 16 * sub;
+    const bool ok = s < nsel && (unsigned)jb < (unsigned)t_n;
+    const int n = ok ? min(16, min(n_kv, (jb + 1) * bkv) - st) : 0;
+    cnt = n > 0 ? n : 0;
+    first = n > 0 ? st : 0;
+  };
+  Piece<T> kr[C], vr[C], kc[4][F];
+  int first, cnt, first_n, cnt_n;
+  tile_at(kz, first, cnt);
+  {
+    const size_t base = (size_t)__builtin_amdgcn_readfirstlane(first) * D;
+    const uint32_t off = min(l16, max(cnt - 1, 0)) * D + 4 * g;
+#pragma unroll
+    for (int c = 0; c < C; ++c) {
+      kr[c].load(Kh + base + (off + 16 * c));
+      vr[c].load(Vh + base + (off + 16 * c));
+      __builtin_amdgcn_sched_barrier(0);   // (requests are awaited in order: in this order here and in the loop)
     }
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_s_waitcnt(0xc07f);
-    float lse[R], dv[R], dq[R][C];
+  }
+  const float* bq0 = sQ + l16 * OST + 4 * g;
+  const float* bg0 = sG + l16 * OST + 4 * g;
+  for (int t = kz; t < ntiles; t += kParts) {
+    tile_at(t + kParts, first_n, cnt_n);
+    // uniform bases and 32-bit offsets of the lane: a tile's first row is scalar
+    const size_t cbase = (size_t)__builtin_amdgcn_readfirstlane(first) * D, base = (size_t)__builtin_amdgcn_readfirstlane(first_n) * D;
+    uint32_t col[4];
 #pragma unroll
-    for (int rr = 0; rr < R; ++rr) {
-      const size_t row = (size_t)bh * n_q + min(r0 + rr, n_q - 1);
-      lse[rr] = lse2[row];
-      dv[rr] = Dv[row];
+    for (int r = 0; r < 4; ++r) col[r] = min(4 * g + r, max(cnt - 1, 0)) * D + 4 * l16;
+    const uint32_t off = min(l16, max(cnt_n - 1, 0)) * D + 4 * g;
+    f32x4 s[NQ], p[NQ];
 #pragma unroll
-      for (int e = 0; e < C; ++e) dq[rr][e] = 0.0f;
+    for (int n = 0; n < NQ; ++n) s[n] = p[n] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+    for (int c = 0; c < C; ++c) {
+      const f32x4 a = kr[c].get(), v = vr[c].get();
+      f32x4 b[NQ], gg[NQ];
+#pragma unroll
+      for (int n = 0; n < NQ; ++n) {
+        b[n] = *reinterpret_cast<const f32x4*>(bq0 + 16 * n * OST + 16 * c);
+        gg[n] = *reinterpret_cast<const f32x4*>(bg0 + 16 * n * OST + 16 * c);
+      }
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+#pragma unroll
+        for (int n = 0; n < NQ; ++n) {
+          s[n] = mfma_f32(a[e], b[n][e], s[n]);
+          p[n] = mfma_f32(v[e], gg[n][e], p[n]);
+        }
+#pragma unroll
+      for (int u = c * 4 * F / C; u < (c + 1) * 4 * F / C; ++u) kc[u / F][u % F].load(Kh + cbase + (col[u / F] + 64 * (u % F)));
+      __builtin_amdgcn_sched_barrier(0);
     }
-    for (int s = 0; s < nsel; ++s) {
-      const int jb = row_idx ? row_idx[s] : s;
-      if ((unsigned)jb >= (unsigned)t_n) continue;
-      const int k_end = min(n_kv, (jb + 1) * bkv);
-      for (int kc = jb * bkv; kc < k_end; kc += kWave) {
-        const int key = kc + lane;
-        const bool valid = key < k_end;
-        const T* krow = Kh + (size_t)(valid ? key : kc) * D;
-        const T* vrow = Vh + (size_t)(valid ? key : kc) * D;
-        float sc[R], dp[R];
+    // dS = P (dP - D); a key that does not exist has probability zero
 #pragma unroll
-        for (int rr = 0; rr < R; ++rr) { sc[rr] = 0.0f; dp[rr] = 0.0f; }
+    for (int n = 0; n < NQ; ++n)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const float w = 4 * g + r < cnt ? __builtin_amdgcn_exp2f(s[n][r] - lse[n]) : 0.0f;
+        s[n][r] = w * (p[n][r] - dv[n]);
+      }
+#pragma unroll
+    for (int u = 0; u < 4 * F; ++u) {
+      const f32x4 a = kc[u / F][u % F].get();
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+#pragma unroll
+        for (int n = 0; n < NQ; ++n) dq[n][u % F][e] = mfma_f32(a[e], s[n][u / F], dq[n][u % F][e]);
+#pragma unroll
+      for (int c = u * C / (4 * F); c < (u + 1) * C / (4 * F); ++c) {
+        kr[c].load(Kh + base + (off + 16 * c));
+        vr[c].load(Vh + base + (off + 16 * c));
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    first = first_n;
+    cnt = cnt_n;
+  }
+#pragma unroll
+  for (int n = 0; n < NQ; ++n)
+#pragma unroll
+    for (int f = 0; f < F; ++f)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) dq[n][f][e] *= scale;
+  __syncthreads();   // Q and dO are read no more as operands of the loop
+
+  if (hist.L) {
+    // ---- wavefront kz < 2 F computes, for every row, the value features (of num) and key features (of the gradient)
+    // 64 f + 4 i + 2 pr and + 1, f = kz / 2, pr = kz % 2: one rotation pair in one lane
+    const float* L = hist.L + (size_t)bh * D * D;
+    const float* z = hist.z + (size_t)bh * D;
+    const T* qh = static_cast<const T*>(hist.q_hist);
+    float den[NQ];
+#pragma unroll
+    for (int n = 0; n < NQ; ++n) {
+      const size_t qrow = (size_t)min(row0 + 16 * n + l16, n_q - 1);
+      float acc = 0.0f;
+#pragma unroll
+      for (int c = 0; c < C; ++c) {
+        f32x4 x = load4<T>(qh + ((size_t)bh * n_q + qrow) * D + 16 * c + 4 * g);
+        const f32x4 zz = *reinterpret_cast<const f32x4*>(z + 16 * c + 4 * g);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          x[e] = phi_apply(x[e], hist.phi_kind);
+          acc = fmaf(x[e], zz[e], acc);
+        }
+        if (c % kParts == kz) {   // uniform: R(phi(q)) into Q's place, every wavefront its share
+          if (hist.cosq) {
+            const size_t at = qrow * (D / 2) + 8 * c + 2 * g;
+            const f32x2 cs = *reinterpret_cast<const f32x2*>(hist.cosq + at), sn = *reinterpret_cast<const f32x2*>(hist.sinq + at);
+            x = rotate4(x, cs[0], sn[0], cs[1], sn[1]);
+          }
+          *reinterpret_cast<f32x4*>(sQ + (16 * n + l16) * OST + 16 * c + 4 * g) = x;
+        }
+      }
+      den[n] = 1.0f / (hist.z_scale * column_sum(acc) + hist.eps);   // (the reciprocal from here on)
+    }
+    __syncthreads();
+    const int f0 = kz >> 1, pr = kz & 1;
+    const bool active = kz < 2 * F;   // uniform
+    if (active) {
+      f32x4 num[NQ][2];
+#pragma unroll
+      for (int n = 0; n < NQ; ++n) num[n][0] = num[n][1] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll 2
-        for (int c = 0; c < D; c += E) {
-          float kv[E], vv[E];
-          load16B<T>(krow + c, kv);
-          load16B<T>(vrow + c, vv);
+      for (int c = 0; c < C; ++c) {
+        f32x2 a[4];
 #pragma unroll
-          for (int rr = 0; rr < R; ++rr)
+        for (int r = 0; r < 4; ++r)
+          a[r] = *reinterpret_cast<const f32x2*>(L + (size_t)(16 * c + 4 * g + r) * D + 64 * f0 + 4 * l16 + 2 * pr);
 #pragma unroll
-            for (int e = 0; e < E; ++e) {
-              sc[rr] = fmaf(sq[wave][rr][c + e], kv[e], sc[rr]);
-              dp[rr] = fmaf(sdo[wave][rr][c + e], vv[e], dp[rr]);
+        for (int n = 0; n < NQ; ++n) {
+          const f32x4 b = *reinterpret_cast<const f32x4*>(bq0 + 16 * n * OST + 16 * c);
+#pragma unroll
+          for (int r = 0; r < 4; ++r) {
+            num[n][0] = mfma_f32(a[r][0], b[r], num[n][0]);
+            num[n][1] = mfma_f32(a[r][1], b[r], num[n][1]);
+          }
+        }
+      }
+#pragma unroll
+      for (int n = 0; n < NQ; ++n) {
+        float acc = 0.0f;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          const f32x2 x = *reinterpret_cast<const f32x2*>(sG + (16 * n + l16) * OST + 64 * f0 + 16 * g + 4 * r + 2 * pr);
+          acc = fmaf(num[n][0][r], x[0], fmaf(num[n][1][r], x[1], acc));
+        }
+        acc = column_sum(acc);
+        if (g == 0) gpart[16 * n + l16][kz] = acc;
+      }
+    }
+    __syncthreads();
+    if (active) {
+      f32x4 tt[NQ][2];
+#pragma unroll
+      for (int n = 0; n < NQ; ++n) tt[n][0] = tt[n][1] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+      const float* La = L + (size_t)(64 * f0 + 4 * l16 + 2 * pr) * D + 4 * g;
+#pragma unroll 2
+      for (int c = 0; c < C; ++c) {
+        const f32x4 a0 = *reinterpret_cast<const f32x4*>(La + 16 * c), a1 = *reinterpret_cast<const f32x4*>(La + D + 16 * c);
+#pragma unroll
+        for (int n = 0; n < NQ; ++n) {
+          const f32x4 b = *reinterpret_cast<const f32x4*>(bg0 + 16 * n * OST + 16 * c);
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            tt[n][0] = mfma_f32(a0[e], b[e], tt[n][0]);
+            tt[n][1] = mfma_f32(a1[e], b[e], tt[n][1]);
+          }
+        }
+      }
+#pragma unroll
+      for (int n = 0; n < NQ; ++n) {
+        const int rr = row0 + 16 * n + l16;
+        const size_t qrow = (size_t)min(rr, n_q - 1);
+        float gn = 0.0f;
+#pragma unroll
+        for (int u = 0; u < 2 * F; ++u) gn += gpart[16 * n + l16][u];
+        const float dden = -gn * den[n] * den[n] * hist.z_scale;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          const int feat = 64 * f0 + 16 * g + 4 * r + 2 * pr;
+          float t0 = tt[n][0][r] * den[n], t1 = tt[n][1][r] * den[n];
+          if (hist.cosq) {   // the opposite angle
+            const float cs = hist.cosq[qrow * (D / 2) + feat / 2], sn = hist.sinq[qrow * (D / 2) + feat / 2];
+            const float u0 = t0 * cs + t1 * sn;
+            t1 = t1 * cs - t0 * sn;
+            t0 = u0;
+          }
+          const T* qp = qh + ((size_t)bh * n_q + qrow) * D + feat;
+          const float q0 = Elem<T>::load(qp), q1 = Elem<T>::load(qp + 1);
+          const bool relu = hist.phi_kind == HF_PHI_RELU;
+          const float d0 = q0 > 0.0f ? 1.0f : (relu ? 0.0f : __expf(q0)), d1 = q1 > 0.0f ? 1.0f : (relu ? 0.0f : __expf(q1));
+          const f32x2 zz = *reinterpret_cast<const f32x2*>(z + feat);
+          const float v0 = fmaf(dden, zz[0], t0) * d0, v1 = fmaf(dden, zz[1], t1) * d1;
+          if (hist.dq_hist) {
+            if (rr < q_end) {
+              T* dst = static_cast<T*>(hist.dq_hist) + ((size_t)bh * n_q + rr) * D + feat;
+              Elem<T>::store(dst, v0);
+              Elem<T>::store(dst + 1, v1);
             }
-        }
-        float ds[R];
+          } else {
 #pragma unroll
-        for (int rr = 0; rr < R; ++rr) {
-          const float p = valid ? exp2f(sc[rr] - lse[rr]) : 0.0f;
-          ds[rr] = p * (dp[rr] - dv[rr]);
-        }
-        const int cnt = min(kWave, k_end - kc);
-        for (int kk = 0; kk < cnt; ++kk) {
-          const T* kr = Kh + (size_t)(kc + kk) * D + lane * C;
-          float kv[C];
+            for (int f = 0; f < F; ++f)   // (constant indices into the accumulators)
 #pragma unroll
-          for (int e = 0; e < C; ++e) kv[e] = Elem<T>::load(kr + e);
-#pragma unroll
-          for (int rr = 0; rr < R; ++rr) {
-            const float d1 = __shfl(ds[rr], kk, kWave);
-#pragma unroll
-            for (int e = 0; e < C; ++e) dq[rr][e] = fmaf(d1, kv[e], dq[rr][e]);
+              for (int q = 0; q < 2; ++q)
+                if (f == f0 && q == pr) {
+                  dq[n][f][2 * q][r] += v0;
+                  dq[n][f][2 * q + 1][r] += v1;
+                }
           }
         }
       }
     }
-#pragma unroll
-    for (int rr = 0; rr < R; ++rr) {
-      const int row = r0 + rr;
-      if (row < q_end) {
-        const size_t off = ((size_t)bh * n_q + row) * D + lane * C;
-#pragma unroll
-        for (int e = 0; e < C; ++e)
-          Elem<T>::store(dQ + off + e, dq[rr][e] * scale + (dqh32 ? dqh32[off + e] : 0.0f));
-      }
-    }
-    __builtin_amdgcn_wave_barrier();
+    __syncthreads();
   }
+  add_parts_and_store<T, D, NQ>(smem, dq, 1.0f, kz, l16, g, dQ + ((size_t)bh * n_q + row0) * D, q_end - row0);
 }
 
-// ---- dK, dV: R keys per wavefront, lanes = query rows for the dot products, lanes = features after ---
-template <typename T, int D, int R>
-__global__ __launch_bounds__(256) void bwd_dkv_generic_kernel(
+// ---- dK, dV: a workgroup per 16 NK keys of a KV block, its four wavefronts taking every fourth 16-row tile of the query
+// blocks on the inverse list.  S = Q K^T, dP = dO V^T (row form; K and V wait in LDS), P = 2^(S - lse2), dS = P (dP - D),
+// dV^T += dO^T P, dK^T += Q^T dS (column form).  Bound by the fp32 matrix rate, at the same shape 124 us (1.01 ms with one
+// query per lane and FMA arithmetic).
+template <typename T, int D, int NK>
+__global__ __launch_bounds__(64 * kParts, 2) void bwd_dkv_wide_kernel(
     const T* __restrict__ Q, const T* __restrict__ K, const T* __restrict__ V, const T* __restrict__ dO,
-    const int32_t* __restrict__ inv_cnt, const int32_t* __restrict__ inv_list, int n_q, int n_kv, int kv_stride,
-    int bq, int bkv, int t_m, int t_n, float scale_log2e, float scale, const float* __restrict__ lse2,
-    const float* __restrict__ Dv, T* __restrict__ dK, T* __restrict__ dV) {
-  constexpr int E = Elem<T>::kPer16B;
-  constexpr int C = D / kWave;
-  __shared__ float sk[4][R][D];
-  __shared__ float sv[4][R][D];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int jb = blockIdx.x, bh = blockIdx.y;
+    const int32_t* __restrict__ inv_cnt, const int32_t* __restrict__ inv_list, int n_q, int n_kv, int kv_stride, int bq,
+    int bkv, int t_m, int t_n, int chunks, int per_xcd, int total, float scale_log2e, float scale,
+    const float* __restrict__ lse2, const float* __restrict__ Dv, T* __restrict__ dK, T* __restrict__ dV) {
+  constexpr int ROWS = 16 * NK, C = D / 16, F = D / 64, OST = D + 4;
+  extern __shared__ __attribute__((aligned(16))) float smem[];   // [ROWS][OST] K, [ROWS][OST] V; later four partial results
+  float* sK = smem;
+  float* sV = smem + ROWS * OST;
+  const int item = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
+  if ((int)(blockIdx.x >> 3) >= per_xcd || item >= total) return;
+  const int bh = item / (t_n * chunks), in_head = item - bh * t_n * chunks;
+  const int jb = in_head / chunks, key0 = jb * bkv + (in_head - jb * chunks) * ROWS;
+  const int k_end = min(n_kv, (jb + 1) * bkv);
+  if (key0 >= k_end) return;
+  const int lane = threadIdx.x & 63, kz = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int l16 = lane & 15, g = lane >> 4;
   const T* Qh = Q + (size_t)bh * n_q * D;
-  const T* dOh = dO + (size_t)bh * n_q * D;
-  const T* Kh = K + (size_t)bh * kv_stride * D;
-  const T* Vh = V + (size_t)bh * kv_stride * D;
+  const T* Gh = dO + (size_t)bh * n_q * D;
   const float* lseh = lse2 + (size_t)bh * n_q;
-  const float* Dvh = Dv + (size_t)bh * n_q;
+  const float* dvh = Dv + (size_t)bh * n_q;
   const int n_lists = inv_cnt ? inv_cnt[(size_t)bh * t_n + jb] : t_m;   // no lists: every query block (dense)
   const int32_t* list = inv_list ? inv_list + ((size_t)bh * t_n + jb) * t_m : nullptr;
-  const int k_end = min(n_kv, (jb + 1) * bkv);
+  const int subs = (bq + 15) / 16, ntiles = n_lists * subs;
 
-  for (int pass0 = jb * bkv; pass0 < k_end; pass0 += 4 * R) {
-    const int r0 = pass0 + wave * R;
-    for (int w = lane; w < R * D; w += kWave) {
-      const int rr = w / D, c = w % D;
-      const int key = min(r0 + rr, n_kv - 1);
-      sk[wave][rr][c] = Elem<T>::load(Kh + (size_t)key * D + c) * scale_log2e;
-      sv[wave][rr][c] = Elem<T>::load(Vh + (size_t)key * D + c);
-    }
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_s_waitcnt(0xc07f);
-    float dk[R][C], dv[R][C];
-#pragma unroll
-    for (int rr = 0; rr < R; ++rr)
-#pragma unroll
-      for (int e = 0; e < C; ++e) { dk[rr][e] = 0.0f; dv[rr][e] = 0.0f; }
-    for (int t = 0; t < n_lists; ++t) {
-      const int qb = list ? list[t] : t;
-      const int q_end = min(n_q, (qb + 1) * bq);
-      for (int qc = qb * bq; qc < q_end; qc += kWave) {
-        const int row = qc + lane;
-        const bool valid = row < q_end;
-        const int rrow = valid ? row : qc;
-        const T* qrow = Qh + (size_t)rrow * D;
-        const T* drow = dOh + (size_t)rrow * D;
-        const float lse = lseh[rrow], dvec = Dvh[rrow];
-        float sc[R], dp[R];
-#pragma unroll
-        for (int rr = 0; rr < R; ++rr) { sc[rr] = 0.0f; dp[rr] = 0.0f; }
-#pragma unroll 2
-        for (int c = 0; c < D; c += E) {
-          float qv[E], dv_[E];
-          load16B<T>(qrow + c, qv);
-          load16B<T>(drow + c, dv_);
-#pragma unroll
-          for (int rr = 0; rr < R; ++rr)
-#pragma unroll
-            for (int e = 0; e < E; ++e) {
-              sc[rr] = fmaf(sk[wave][rr][c + e], qv[e], sc[rr]);
-              dp[rr] = fmaf(sv[wave][rr][c + e], dv_[e], dp[rr]);
-            }
-        }
-        float p[R], ds[R];
-#pragma unroll
-        for (int rr = 0; rr < R; ++rr) {
-          p[rr] = valid ? exp2f(sc[rr] - lse) : 0.0f;
-          ds[rr] = p[rr] * (dp[rr] - dvec);
-        }
-        const int cnt = min(kWave, q_end - qc);
-        for (int kk = 0; kk < cnt; ++kk) {
-          const T* qr = Qh + (size_t)(qc + kk) * D + lane * C;
-          const T* dr = dOh + (size_t)(qc + kk) * D + lane * C;
-          float qv[C], dov[C];
-#pragma unroll
-          for (int e = 0; e < C; ++e) { qv[e] = Elem<T>::load(qr + e); dov[e] = Elem<T>::load(dr + e); }
-#pragma unroll
-          for (int rr = 0; rr < R; ++rr) {
-            const float p1 = __shfl(p[rr], kk, kWave), d1 = __shfl(ds[rr], kk, kWave);
-#pragma unroll
-            for (int e = 0; e < C; ++e) {
-              dv[rr][e] = fmaf(p1, dov[e], dv[rr][e]);
-              dk[rr][e] = fmaf(d1, qv[e], dk[rr][e]);
-            }
-          }
-        }
-      }
-    }
-#pragma unroll
-    for (int rr = 0; rr < R; ++rr) {
-      const int key = r0 + rr;
-      if (key < k_end) {
-        const size_t off = ((size_t)bh * kv_stride + key) * D + lane * C;
-#pragma unroll
-        for (int e = 0; e < C; ++e) {
-          Elem<T>::store(dK + off + e, dk[rr][e] * scale);
-          Elem<T>::store(dV + off + e, dv[rr][e]);
-        }
-      }
-    }
-    __builtin_amdgcn_wave_barrier();
+  for (int e = threadIdx.x; e < ROWS * (D / 4); e += 64 * kParts) {
+    const int rr = e / (D / 4), c4 = e - rr * (D / 4);
+    const size_t off = ((size_t)bh * kv_stride + min(key0 + rr, n_kv - 1)) * D + 4 * c4;
+    *reinterpret_cast<f32x4*>(sK + rr * OST + 4 * c4) = load4<T>(K + off) * scale_log2e;
+    *reinterpret_cast<f32x4*>(sV + rr * OST + 4 * c4) = load4<T>(V + off);
   }
+  f32x4 ak[NK][F][4], av[NK][F][4];
+#pragma unroll
+  for (int n = 0; n < NK; ++n)
+#pragma unroll
+    for (int f = 0; f < F; ++f)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) ak[n][f][e] = av[n][f][e] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+  __syncthreads();
+
+  auto tile_at = [&](int t, int& first, int& cnt) {   // cnt 0: past the list or past the last query
+    const int s = t / subs, sub = t - s * subs;
+    const int qb = s < n_lists ? (list ? list[s] : s) : 0;
+    const int st = qb * bq + 16 * sub;
+    const int n = s < n_lists ? min(16, min(n_q, (qb + 1) * bq) - st) : 0;
+    cnt = n > 0 ? n : 0;
+    first = n > 0 ? st : 0;
+  };
+  Piece<T> qr[C], gr[C], qc[4][F], gc[4][F];
+  int first, cnt, first_n, cnt_n;
+  tile_at(kz, first, cnt);
+  {
+    const size_t base = (size_t)__builtin_amdgcn_readfirstlane(first) * D;
+    const uint32_t off = min(l16, max(cnt - 1, 0)) * D + 4 * g;
+#pragma unroll
+    for (int c = 0; c < C; ++c) {
+      qr[c].load(Qh + base + (off + 16 * c));
+      gr[c].load(Gh + base + (off + 16 * c));
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  }
+  const float* bk0 = sK + l16 * OST + 4 * g;
+  const float* bv0 = sV + l16 * OST + 4 * g;
+  for (int t = kz; t < ntiles; t += kParts) {
+    tile_at(t + kParts, first_n, cnt_n);
+    const int first_s = __builtin_amdgcn_readfirstlane(first);
+    const size_t cbase = (size_t)first_s * D, base = (size_t)__builtin_amdgcn_readfirstlane(first_n) * D;
+    uint32_t col[4];
+    float lse[4], dv[4];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const uint32_t row = min(4 * g + r, max(cnt - 1, 0));
+      col[r] = row * D + 4 * l16;
+      lse[r] = lseh[first_s + row];
+      dv[r] = dvh[first_s + row];
+    }
+    const uint32_t off = min(l16, max(cnt_n - 1, 0)) * D + 4 * g;
+    f32x4 s[NK], p[NK];
+#pragma unroll
+    for (int n = 0; n < NK; ++n) s[n] = p[n] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+    for (int c = 0; c < C; ++c) {
+      const f32x4 a = qr[c].get(), v = gr[c].get();
+      f32x4 b[NK], gg[NK];
+#pragma unroll
+      for (int n = 0; n < NK; ++n) {
+        b[n] = *reinterpret_cast<const f32x4*>(bk0 + 16 * n * OST + 16 * c);
+        gg[n] = *reinterpret_cast<const f32x4*>(bv0 + 16 * n * OST + 16 * c);
+      }
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+#pragma unroll
+        for (int n = 0; n < NK; ++n) {
+          s[n] = mfma_f32(a[e], b[n][e], s[n]);
+          p[n] = mfma_f32(v[e], gg[n][e], p[n]);
+        }
+#pragma unroll
+      for (int u = c * 4 * F / C; u < (c + 1) * 4 * F / C; ++u) {
+        gc[u / F][u % F].load(Gh + cbase + (col[u / F] + 64 * (u % F)));
+        qc[u / F][u % F].load(Qh + cbase + (col[u / F] + 64 * (u % F)));
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    // P and dS; a query that does not exist has probability zero
+#pragma unroll
+    for (int n = 0; n < NK; ++n)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const float w = 4 * g + r < cnt ? __builtin_amdgcn_exp2f(s[n][r] - lse[r]) : 0.0f;
+        s[n][r] = w;
+        p[n][r] = w * (p[n][r] - dv[r]);
+      }
+#pragma unroll
+    for (int u = 0; u < 4 * F; ++u) {
+      const f32x4 a = gc[u / F][u % F].get(), b = qc[u / F][u % F].get();
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+#pragma unroll
+        for (int n = 0; n < NK; ++n) {
+          av[n][u % F][e] = mfma_f32(a[e], s[n][u / F], av[n][u % F][e]);
+          ak[n][u % F][e] = mfma_f32(b[e], p[n][u / F], ak[n][u % F][e]);
+        }
+#pragma unroll
+      for (int c = u * C / (4 * F); c < (u + 1) * C / (4 * F); ++c) {
+        qr[c].load(Qh + base + (off + 16 * c));
+        gr[c].load(Gh + base + (off + 16 * c));
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    first = first_n;
+    cnt = cnt_n;
+  }
+  __syncthreads();   // K and V are read no more
+  const size_t out = ((size_t)bh * kv_stride + key0) * D;
+  add_parts_and_store<T, D, NK>(smem, ak, scale, kz, l16, g, dK + out, k_end - key0);
+  __syncthreads();
+  add_parts_and_store<T, D, NK>(smem, av, 1.0f, kz, l16, g, dV + out, k_end - key0);
 }
 
-// ---- gradient of the history readout with respect to its queries, one wavefront per row -------------
-//   f = phi(q), r = R f, num = r L, den = z_scale f.z + eps, out = num / den
-//   dnum = g / den, dden = -(g . num) / den^2, df = R^T (dnum L^T) + z_scale dden z, dq = df phi'(q)
-// TO = float writes the result for the dQ kernel to add before its one rounding; TO = T writes the
-// gradient of a query tensor of its own.
-template <typename T, typename TO, int D>
-__global__ __launch_bounds__(256) void bwd_hist_generic_kernel(const T* __restrict__ Qh, const T* __restrict__ dO,
-                                                               const float* __restrict__ state, int BH, int n_q,
-                                                               const float* __restrict__ cosq,
-                                                               const float* __restrict__ sinq, int phi_kind,
-                                                               float eps, float z_scale, TO* __restrict__ out) {
-  constexpr int C = D / kWave;   // 2 (one rotation pair per lane) or 1 (pair = lanes l, l^1)
-  __shared__ float sr[4][D];
-  __shared__ float sd[4][D];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int bh = blockIdx.y;
-  const int row = blockIdx.x * 4 + wave;
-  if (row >= n_q) return;
-  const float* L = state + (size_t)bh * D * D;
-  const float* z = state + (size_t)BH * D * D + (size_t)bh * D;
-  const size_t off = ((size_t)bh * n_q + row) * D + lane * C;
-  float q[C], f[C], r[C], g[C];
-  float den = 0.0f;
-#pragma unroll
-  for (int e = 0; e < C; ++e) {
-    q[e] = Elem<T>::load(Qh + off + e);
-    g[e] = Elem<T>::load(dO + off + e);
-    f[e] = phi_apply(q[e], phi_kind);
-    den = fmaf(f[e], z[lane * C + e], den);
+template <typename T, int D, int N>
+int launch_bwd_wide(const hf_config& c, const void* Q, int n_q, const void* K, const void* V, int n_kv, const int32_t* idx,
+                    int k, const void* dO, const float* lse2, const float* Dv, const int32_t* inv_cnt, const int32_t* inv_list,
+                    const WideBwdHist& hist, void* dQ, void* dK, void* dV, bool keys, hipStream_t s) {
+  constexpr int ROWS = 16 * N;
+  const int BH = c.batch * c.heads;
+  const int t_m = (n_q + c.block_q - 1) / c.block_q, t_n = (n_kv + c.block_kv - 1) / c.block_kv;
+  const float scale = c.softmax_scale > 0.0f ? c.softmax_scale : 1.0f / sqrtf((float)c.head_dim);
+  const float sl2 = scale * 1.4426950408889634f;
+  const int kvs = kv_stride_of(c, n_kv);
+  const int chunks = ((keys ? c.block_kv : c.block_q) + ROWS - 1) / ROWS;
+  const long long total = (long long)BH * (keys ? t_n : t_m) * chunks;
+  if (total > (1ll << 30)) { set_error("too many blocks"); return HF_ERR_SHAPE; }
+  const int per_xcd = (int)((total + 7) / 8);
+  constexpr int lds = kParts * ROWS * (D + 4) * (int)sizeof(float);
+  const dim3 grid(8 * per_xcd), block(64 * kParts);
+  const T *q = static_cast<const T*>(Q), *kk = static_cast<const T*>(K), *v = static_cast<const T*>(V), *g = static_cast<const T*>(dO);
+  const void* fn = keys ? reinterpret_cast<const void*>(bwd_dkv_wide_kernel<T, D, N>)
+                        : reinterpret_cast<const void*>(bwd_dq_wide_kernel<T, D, N>);
+  if (lds > 64 * 1024) {
+    static LdsGrant grants[2];
+    const int rc = grant_lds(grants[keys], fn, lds, "the fp32 backward kernels");
+    if (rc != HF_OK) return rc;
   }
-  den = z_scale * wave_sum(den) + eps;
-  // rotation of adjacent pairs (2p, 2p+1)
-  float cs = 1.0f, sn = 0.0f;
-  if (cosq) {
-    const int pair = C == 2 ? lane : lane >> 1;
-    cs = cosq[(size_t)row * (D / 2) + pair];
-    sn = sinq[(size_t)row * (D / 2) + pair];
-  }
-  if (C == 2) {
-    r[0] = f[0] * cs - f[C - 1] * sn;
-    r[C - 1] = f[0] * sn + f[C - 1] * cs;
-  } else {
-    const float other = __shfl_xor(f[0], 1, kWave);
-    r[0] = (lane & 1) ? other * sn + f[0] * cs : f[0] * cs - other * sn;
-  }
-#pragma unroll
-  for (int e = 0; e < C; ++e) sr[wave][lane * C + e] = r[e];
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_s_waitcnt(0xc07f);
-  // num_j = sum_i r_i L[i][j], lanes = j
-  float num[C];
-#pragma unroll
-  for (int e = 0; e < C; ++e) num[e] = 0.0f;
-  for (int i = 0; i < D; ++i) {
-    const float ri = sr[wave][i];
-#pragma unroll
-    for (int e = 0; e < C; ++e) num[e] = fmaf(ri, L[(size_t)i * D + lane * C + e], num[e]);
-  }
-  float gn = 0.0f;
-#pragma unroll
-  for (int e = 0; e < C; ++e) gn = fmaf(g[e], num[e], gn);
-  const float inv = 1.0f / den;
-  const float dden = -wave_sum(gn) * inv * inv;
-#pragma unroll
-  for (int e = 0; e < C; ++e) sd[wave][lane * C + e] = g[e] * inv;   // dnum
-  __builtin_amdgcn_wave_barrier();
-  __builtin_amdgcn_s_waitcnt(0xc07f);
-  // t_i = sum_j dnum_j L[i][j], lanes = i
-  float t[C];
-#pragma unroll
-  for (int e = 0; e < C; ++e) {
-    const float* Lrow = L + (size_t)(lane * C + e) * D;
-    float acc = 0.0f;
-    for (int j = 0; j < D; j += 4) {
-      const float4 l4 = *reinterpret_cast<const float4*>(Lrow + j);
-      acc = fmaf(sd[wave][j], l4.x, acc);
-      acc = fmaf(sd[wave][j + 1], l4.y, acc);
-      acc = fmaf(sd[wave][j + 2], l4.z, acc);
-      acc = fmaf(sd[wave][j + 3], l4.w, acc);
-    }
-    t[e] = acc;
-  }
-  // back through the rotation (opposite angle), add the denominator's share, times phi'
-  float df[C];
-  if (C == 2) {
-    df[0] = t[0] * cs + t[C - 1] * sn;
-    df[C - 1] = -t[0] * sn + t[C - 1] * cs;
-  } else {
-    const float other = __shfl_xor(t[0], 1, kWave);
-    df[0] = (lane & 1) ? -other * sn + t[0] * cs : t[0] * cs + other * sn;
-  }
-#pragma unroll
-  for (int e = 0; e < C; ++e) {
-    const float d1 = df[e] + z_scale * dden * z[lane * C + e];
-    const float dphi = phi_kind == HF_PHI_RELU ? (q[e] > 0.0f ? 1.0f : 0.0f) : (q[e] > 0.0f ? 1.0f : __expf(q[e]));
-    const float v = d1 * dphi;
-    if (sizeof(TO) == 4) reinterpret_cast<float*>(out)[off + e] = v;
-    else reinterpret_cast<bf16_t*>(out)[off + e] = f32_to_bf16(v);
-  }
+  if (keys)
+    hipLaunchKernelGGL((bwd_dkv_wide_kernel<T, D, N>), grid, block, lds, s, q, kk, v, g, inv_cnt, inv_list, n_q, n_kv, kvs,
+                       c.block_q, c.block_kv, t_m, t_n, chunks, per_xcd, (int)total, sl2, scale, lse2, Dv,
+                       static_cast<T*>(dK), static_cast<T*>(dV));
+  else
+    hipLaunchKernelGGL((bwd_dq_wide_kernel<T, D, N>), grid, block, lds, s, q, kk, v, g, idx, k, n_q, n_kv, kvs, c.block_q,
+                       c.block_kv, t_m, t_n, chunks, per_xcd, (int)total, sl2, scale, lse2, Dv, hist, static_cast<T*>(dQ));
+  return check_launch("hf_hybrid_attn_bwd(dQ, dK, dV)");
 }
 
 }  // namespace
@@ -412,49 +596,41 @@ int launch_invert_index(const hf_config& c, const int32_t* idx, int k, int t_m, 
   return check_launch("hf_hybrid_attn_bwd(inverse lists)");
 }
 
-int launch_bwd_generic(const hf_config& c, const void* Q, int n_q, const void* K, const void* V, int n_kv,
+// dQ (with the history branch where a state is given), then dK and dV.  32 rows or keys per workgroup, 16 where a block has
+// no more (or would leave over a quarter of the 32 empty): the second half of the products would be work on nothing.
+int launch_bwd_generic(const hf_config& c, const void* Q, const void* Q_hist, int n_q, const void* K, const void* V, int n_kv,
                        const int32_t* idx, int k, const void* dO, const float* lse2, const float* Dv,
-                       const int32_t* inv_cnt, const int32_t* inv_list, const float* dqh32, void* dQ, void* dK,
-                       void* dV, hipStream_t s) {
-  const int BH = c.batch * c.heads;
-  const int t_m = (n_q + c.block_q - 1) / c.block_q, t_n = (n_kv + c.block_kv - 1) / c.block_kv;
-  const float scale = c.softmax_scale > 0.0f ? c.softmax_scale : 1.0f / sqrtf((float)c.head_dim);
-  const float sl2 = scale * 1.4426950408889634f;
-  const int kvs = kv_stride_of(c, n_kv);
-#define HF_LAUNCH_BWD(T, DD)                                                                                        \
-  do {                                                                                                              \
-    hipLaunchKernelGGL((bwd_dq_generic_kernel<T, DD, 4>), dim3(t_m, BH), dim3(256), 0, s, static_cast<const T*>(Q), \
-                       static_cast<const T*>(K), static_cast<const T*>(V), static_cast<const T*>(dO), idx, k, n_q,  \
-                       n_kv, kvs, c.block_q, c.block_kv, t_m, t_n, sl2, scale, lse2, Dv, dqh32,                     \
-                       static_cast<T*>(dQ));                                                                        \
-    hipLaunchKernelGGL((bwd_dkv_generic_kernel<T, DD, 4>), dim3(t_n, BH), dim3(256), 0, s,                          \
-                       static_cast<const T*>(Q), static_cast<const T*>(K), static_cast<const T*>(V),                \
-                       static_cast<const T*>(dO), inv_cnt, inv_list, n_q, n_kv, kvs, c.block_q, c.block_kv, t_m,    \
-                       t_n, sl2, scale, lse2, Dv, static_cast<T*>(dK), static_cast<T*>(dV));                        \
-  } while (0)
-  if (c.dtype == HF_F32) { if (c.head_dim == 128) HF_LAUNCH_BWD(float, 128); else HF_LAUNCH_BWD(float, 64); }
-  else { if (c.head_dim == 128) HF_LAUNCH_BWD(bf16_t, 128); else HF_LAUNCH_BWD(bf16_t, 64); }
-#undef HF_LAUNCH_BWD
-  return check_launch("hf_hybrid_attn_bwd(dQ, dK, dV)");
-}
-
-int launch_bwd_hist_generic(const hf_config& c, const void* Q_hist, const void* dO, const float* state, int n_q,
-                            const float* cosq, const float* sinq, void* out, bool out_f32, hipStream_t s) {
-  const int BH = c.batch * c.heads;
-  const dim3 grid((n_q + 3) / 4, BH), block(256);
-#define HF_LAUNCH_HIST(T, TO, DD)                                                                                  \
-  hipLaunchKernelGGL((bwd_hist_generic_kernel<T, TO, DD>), grid, block, 0, s, static_cast<const T*>(Q_hist),        \
-                     static_cast<const T*>(dO), state, BH, n_q, cosq, sinq, c.phi, c.eps, c.z_scale,               \
-                     static_cast<TO*>(out))
-  if (c.dtype == HF_F32) {
-    if (c.head_dim == 128) HF_LAUNCH_HIST(float, float, 128); else HF_LAUNCH_HIST(float, float, 64);
-  } else if (out_f32) {
-    if (c.head_dim == 128) HF_LAUNCH_HIST(bf16_t, float, 128); else HF_LAUNCH_HIST(bf16_t, float, 64);
-  } else {
-    if (c.head_dim == 128) HF_LAUNCH_HIST(bf16_t, bf16_t, 128); else HF_LAUNCH_HIST(bf16_t, bf16_t, 64);
+                       const int32_t* inv_cnt, const int32_t* inv_list, const float* state, const float* cosq,
+                       const float* sinq, void* dQ, void* dQ_hist, void* dK, void* dV, hipStream_t s) {
+  WideBwdHist h = {};
+  if (state) {
+    h.L = state;
+    h.z = state + (size_t)c.batch * c.heads * c.head_dim * c.head_dim;
+    h.cosq = cosq;
+    h.sinq = sinq;
+    h.q_hist = Q_hist;
+    h.dq_hist = dQ_hist;
+    h.eps = c.eps;
+    h.z_scale = c.z_scale;
+    h.phi_kind = c.phi;
   }
-#undef HF_LAUNCH_HIST
-  return check_launch("hf_hybrid_attn_bwd(history)");
+  for (int keys = 0; keys < 2; ++keys) {
+    const int b = keys ? c.block_kv : c.block_q;
+    const bool two = (b + 31) / 32 * 32 * 3 <= b * 4;
+    int rc;
+#define HF_BWD_WIDE(T, DD, N)                                                                                          \
+  rc = launch_bwd_wide<T, DD, N>(c, Q, n_q, K, V, n_kv, idx, k, dO, lse2, Dv, inv_cnt, inv_list, h, dQ, dK, dV, keys != 0, s)
+    if (c.dtype == HF_F32) {
+      if (c.head_dim == 128) { if (two) HF_BWD_WIDE(float, 128, 2); else HF_BWD_WIDE(float, 128, 1); }
+      else { if (two) HF_BWD_WIDE(float, 64, 2); else HF_BWD_WIDE(float, 64, 1); }
+    } else {
+      if (c.head_dim == 128) { if (two) HF_BWD_WIDE(bf16_t, 128, 2); else HF_BWD_WIDE(bf16_t, 128, 1); }
+      else { if (two) HF_BWD_WIDE(bf16_t, 64, 2); else HF_BWD_WIDE(bf16_t, 64, 1); }
+    }
+#undef HF_BWD_WIDE
+    if (rc != HF_OK) return rc;
+  }
+  return HF_OK;
 }
 
 // out[row] = A[row] . B[row] over head_dim features (bf16 storage, fp32 arithmetic): D = dO . O_local from a

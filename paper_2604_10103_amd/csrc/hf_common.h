@@ -154,12 +154,10 @@ int launch_bwd_mfma(const hf_config& c, const void* Q, int n_q, const void* K, c
                     void* dK, void* dV, hipStream_t s);
 int launch_invert_index(const hf_config& c, const int32_t* idx, int k, int t_m, int t_n, int32_t* inv_cnt,
                         int32_t* inv_list, hipStream_t s);
-int launch_bwd_generic(const hf_config& c, const void* Q, int n_q, const void* K, const void* V, int n_kv,
+int launch_bwd_generic(const hf_config& c, const void* Q, const void* Q_hist, int n_q, const void* K, const void* V, int n_kv,
                        const int32_t* idx, int k, const void* dO, const float* lse2, const float* Dv,
-                       const int32_t* inv_cnt, const int32_t* inv_list, const float* dqh32, void* dQ, void* dK,
-                       void* dV, hipStream_t s);
-int launch_bwd_hist_generic(const hf_config& c, const void* Q_hist, const void* dO, const float* state, int n_q,
-                            const float* cosq, const float* sinq, void* out, bool out_f32, hipStream_t s);
+                       const int32_t* inv_cnt, const int32_t* inv_list, const float* state, const float* cosq,
+                       const float* sinq, void* dQ, void* dQ_hist, void* dK, void* dV, hipStream_t s);
 int launch_rope_tables(const int32_t* frame_idx, int n_frames, int height, int width, int pairs_t, int pairs_h,
                        int pairs_w, double theta, int temporal_only, float* cosv, float* sinv, hipStream_t s);
 int launch_rope_apply(const hf_config& c, const void* X, int n, const float* cosv, const float* sinv, void* Y,
