@@ -25,6 +25,7 @@ SOURCES = [
     "hf_select.hip",
     "hf_attn_generic.hip",
     "hf_attn_mfma.hip",
+    "hf_attn_d64.hip",
     "hf_attn_w64.hip",
     "hf_readout_mfma.hip",
     "hf_rope.hip",

@@ -17,19 +17,6 @@
 
 namespace hf {
 
-struct WideHist {            // history term, or statistics for the backward pass
-  const float* L;            // [BH][D][D], NULL: none
-  const float* z;            // [BH][D]
-  const float* cosq;         // [n_q][D/2] rotation of phi(q) in the numerator, or NULL
-  const float* sinq;
-  const void* q_hist;        // [BH][n_q][D] queries of the history branch
-  float eps, z_scale;
-  int phi_kind;
-  float* lse2;               // [BH][n_q], given: row statistics instead of an output
-  const void* d_out;         // [BH][n_q][D]
-  float* dvec;               // [BH][n_q] d_out . O_local
-};
-
 namespace {
 
 constexpr int kTile = 16;    // keys per tile
@@ -716,8 +703,14 @@ int launch_wide_rows(const hf_config& c, const void* Q, int n_q, const void* K, 
 
 }  // namespace
 
+bool attn_d64_supported(const hf_config& c, int n_kv);   // hf_attn_d64.hip
+int launch_attn_d64(const hf_config& c, const void* Q, int n_q, const void* K, const void* V, int n_kv, const int32_t* idx,
+                    int k, void* O, const WideHist& hist, hipStream_t s);
+
 static int launch_attn_wide(const hf_config& c, const void* Q, int n_q, const void* K, const void* V, int n_kv,
                             const int32_t* idx, int k, void* O, const WideHist& hist, hipStream_t s) {
+  // (row statistics for the backward pass come from the kernels of this file)
+  if (attn_d64_supported(c, n_kv) && !hist.lse2) return launch_attn_d64(c, Q, n_q, K, V, n_kv, idx, k, O, hist, s);
   if (c.dtype == HF_F32 && c.block_q % 32 == 0 && c.block_kv % 32 == 0)
     return c.head_dim == 128 ? launch_wide32<128>(c, Q, n_q, K, V, n_kv, idx, k, O, hist, s)
                              : launch_wide32<64>(c, Q, n_q, K, V, n_kv, idx, k, O, hist, s);

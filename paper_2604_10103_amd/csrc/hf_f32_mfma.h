@@ -31,6 +31,20 @@ typedef float f32x2 __attribute__((ext_vector_type(2)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 
+// what the attention kernels that add the history term from the fp32 state take for it
+struct WideHist {            // history term, or statistics for the backward pass
+  const float* L;            // [BH][D][D], NULL: none
+  const float* z;            // [BH][D]
+  const float* cosq;         // [n_q][D/2] rotation of phi(q) in the numerator, or NULL
+  const float* sinq;
+  const void* q_hist;        // [BH][n_q][D] queries of the history branch
+  float eps, z_scale;
+  int phi_kind;
+  float* lse2;               // [BH][n_q], given: row statistics instead of an output
+  const void* d_out;         // [BH][n_q][D]
+  float* dvec;               // [BH][n_q] d_out . O_local
+};
+
 __device__ __forceinline__ f32x4 mfma_f32(float a, float b, f32x4 c) {
   return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, c, 0, 0, 0);
 }

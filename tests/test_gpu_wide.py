@@ -20,7 +20,8 @@ SHAPES = [  # dtype, head_dim, block_q, block_kv, n_q, n_kv, keep (None: dense)
     ("f32", 128, 20, 24, 41, 100, 0.5), ("f32", 64, 16, 16, 17, 129, 0.25), ("f32", 128, 200, 48, 210, 500, 0.4),
     ("bf16", 128, 32, 32, 33, 100, 0.5), ("bf16", 64, 16, 48, 70, 140, 0.5), ("bf16", 64, 64, 64, 1, 1, 1.0),
     ("bf16", 64, 64, 64, 65, 127, 0.5), ("bf16", 64, 128, 128, 200, 900, 0.3), ("bf16", 64, 64, 32, 130, 300, None),
-    ("bf16", 64, 128, 48, 129, 500, 0.4),
+    ("bf16", 64, 128, 48, 129, 500, 0.4), ("bf16", 64, 192, 96, 193, 450, 0.5), ("bf16", 64, 64, 64, 66, 4300, None),
+    ("bf16", 64, 128, 32, 257, 33, 1.0),
 ]
 
 
