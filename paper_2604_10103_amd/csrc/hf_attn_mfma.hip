@@ -38,6 +38,7 @@
 namespace hf {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef float f32x4 __attribute__((ext_vector_type(4)));
 typedef float f32x16 __attribute__((ext_vector_type(16)));
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 
@@ -96,10 +97,10 @@ struct HistArgs {
 // idx_row.  All scratch lies in the tile space, which is not in use yet.  t_n <= kSelMaxBlocks.
 constexpr int kSelMaxBlocks = kMaxFusedSelectBlocks;
 
-template <int NW>
+template <int NW, int BQ>
 __device__ __forceinline__ int* select_in_workgroup(char* smem, const bf16_t* Qh, int q0, int n_q, const float* kbar_head,
                                                     int t_n, int k, int32_t* idx_row, float* scores_row) {
-  constexpr int NT = 64 * NW, BQ = 32 * NW, G = NT / 16, CW = D / 4 / NW;
+  constexpr int NT = 64 * NW, G = NT / 16, CW = D / 4 / NW;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int t_pad = (t_n + 3) & ~3;
@@ -126,7 +127,7 @@ __device__ __forceinline__ int* select_in_workgroup(char* smem, const bf16_t* Qh
     const u32v4 r = __builtin_amdgcn_raw_buffer_load_b128(krsrc, j * 16, (wave * CW + c) * t_n * 16, 0);
     return make_float4(__uint_as_float(r[0]), __uint_as_float(r[1]), __uint_as_float(r[2]), __uint_as_float(r[3]));
   };
-  constexpr int U = 48 / CW;   // KV blocks per lane and pass (3 or 6): 48 loads of 16 bytes in flight
+  constexpr int U = NW == 2 ? 3 : 4;   // KV blocks per lane and pass: 48, 32 or 16 loads of 16 bytes in flight
   float4 kv[U][CW];
 #pragma unroll
   for (int u = 0; u < U; ++u) {
@@ -343,11 +344,12 @@ struct AbsorbArgs {
 template <int NW>
 __device__ __forceinline__ void absorb_role(char* smem, const AbsorbArgs& ab) {
   constexpr int NT = 64 * NW;
-  constexpr int IB = 4 / NW;                 // 32-row blocks of key features per wavefront
+  constexpr int IB = NW == 2 ? 2 : 1;        // 32-row blocks of key features per wavefront
+  constexpr int JB = NW == 8 ? 2 : 4;        // 32-column blocks of value features per wavefront
   constexpr int PARTB = 16 * KSTR;           // bytes of 16 tokens of K (or V)
   constexpr int STAGE = 2 * PARTB;           // a stage: 16 tokens of K, then of V (8 KB)
   constexpr int NSTG = 5;
-  constexpr int HP = (PARTB / 1024) / NW;    // 1 KB pieces (4 token rows) of a part per wavefront (2 or 1)
+  constexpr int RPS = (STAGE / 1024) / NW;   // 1 KB pieces (4 token rows) of a stage per wavefront (4, 2 or 1)
   constexpr int PART = D * D + D;
   typedef int i32x4 __attribute__((ext_vector_type(4)));
   typedef short s16x4 __attribute__((ext_vector_type(4)));
@@ -367,11 +369,11 @@ __device__ __forceinline__ void absorb_role(char* smem, const AbsorbArgs& ab) {
   const uint64_t vbase = reinterpret_cast<uint64_t>(ab.V + (size_t)bh * ab.stride * D);
   const int head_bytes = ab.n * (D * 2);
   const uint32_t lds0 = (uint32_t)(uintptr_t)smem;
-  int lane_off[HP];
+  int lane_off[RPS];
 #pragma unroll
-  for (int j = 0; j < HP; ++j) {
-    const int r = 4 * (wave + NW * j) + (lane >> 4), u = lane & 15;
-    lane_off[j] = r * (D * 2) + ((u ^ (((r & 3) << 2) | ((r >> 2) & 3))) * 16);
+  for (int q = 0; q < RPS; ++q) {
+    const int r = 4 * ((wave + NW * q) & 3) + (lane >> 4), u = lane & 15;
+    lane_off[q] = r * (D * 2) + ((u ^ (((r & 3) << 2) | ((r >> 2) & 3))) * 16);
   }
   // stage c of this slice (16 tokens from token 16 (st0 + c)) into slot c mod NSTG; stages past the slice's end
   // get an empty descriptor (zeros, nothing read), so that every wavefront issues the same number of requests
@@ -381,15 +383,13 @@ __device__ __forceinline__ void absorb_role(char* smem, const AbsorbArgs& ab) {
     const int left = c < nst ? min(head_bytes - skip, 16 * D * 2) : 0;   // the slice's own tokens only
     const uint32_t slot = lds0 + (uint32_t)(c % NSTG) * STAGE;
 #pragma unroll
-    for (int part = 0; part < 2; ++part) {
-      const uint64_t base = (part ? vbase : kbase) + (uint64_t)(uint32_t)(left > 0 ? skip : 0);
+    for (int q = 0; q < RPS; ++q) {
+      const int piece = wave + NW * q;        // pieces 0..3 of K, 4..7 of V
+      const uint64_t base = (piece >> 2 ? vbase : kbase) + (uint64_t)(uint32_t)(left > 0 ? skip : 0);
       const i32x4 d2 = {(int)(uint32_t)base, (int)(uint32_t)(base >> 32), left > 0 ? left : 0, 0x00020000};
-#pragma unroll
-      for (int j = 0; j < HP; ++j) {
-        const uint32_t dst = slot + part * PARTB + 4 * (wave + NW * j) * KSTR;
-        asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds"
-                     :: "s"(dst), "v"(lane_off[j]), "s"(d2) : "memory", "m0");
-      }
+      const uint32_t dst = slot + (piece >> 2) * PARTB + 4 * (piece & 3) * KSTR;
+      asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds"
+                   :: "s"(dst), "v"(lane_off[q]), "s"(d2) : "memory", "m0");
     }
   };
   // transposing reads of a 16-token part: feature 32 dt + l32 as the row, the lane's eight tokens as the k index
@@ -415,39 +415,40 @@ __device__ __forceinline__ void absorb_role(char* smem, const AbsorbArgs& ab) {
 #pragma unroll
   for (int c = 0; c < NSTG - 1; ++c) fetch(c);
   if (claimer) {
-    asm volatile("s_waitcnt vmcnt(%1)" : "+v"(seen) : "n"(2 * HP * (NSTG - 1)) : "memory");
+    asm volatile("s_waitcnt vmcnt(%1)" : "+v"(seen) : "n"(RPS * (NSTG - 1)) : "memory");
     if ((seen >> 16) != ab.tag)
       (void)__hip_atomic_compare_exchange_strong(ctr, &seen, ab.tag << 16, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
                                                  __HIP_MEMORY_SCOPE_AGENT);
   }
 
-  f32x16 acc[IB][4], zacc[IB];
+  const int ib0 = NW == 8 ? wave & 3 : IB * wave, jb0 = NW == 8 ? 2 * (wave >> 2) : 0;   // (scalar)
+  f32x16 acc[IB][JB], zacc[IB];
 #pragma unroll
   for (int ib = 0; ib < IB; ++ib) {
 #pragma unroll
     for (int r = 0; r < 16; ++r) zacc[ib][r] = 0.0f;
 #pragma unroll
-    for (int jb = 0; jb < 4; ++jb)
+    for (int jb = 0; jb < JB; ++jb)
 #pragma unroll
       for (int r = 0; r < 16; ++r) acc[ib][jb][r] = 0.0f;
   }
   const s16x8 zero8 = {0, 0, 0, 0, 0, 0, 0, 0};
   const s16x8 ones8 = {0x3f80, 0x3f80, 0x3f80, 0x3f80, 0x3f80, 0x3f80, 0x3f80, 0x3f80};   // bf16 1.0
   for (int c = 0; c < nst; ++c) {
-    asm volatile("s_waitcnt vmcnt(%0)" :: "n"(2 * HP * (NSTG - 2)) : "memory");   // this wavefront's rows of stage c
+    asm volatile("s_waitcnt vmcnt(%0)" :: "n"(RPS * (NSTG - 2)) : "memory");   // this wavefront's rows of stage c
     __syncthreads();             // ... and everybody's; everybody has read stage c - 1
     fetch(c + NSTG - 1);         // into the slot of stage c - 1
     const char* st = smem + (c % NSTG) * STAGE;
-    bf16x8 a[IB], b[4];
+    bf16x8 a[IB], b[JB];
 #pragma unroll
     for (int ib = 0; ib < IB; ++ib)   // phi = ReLU on bf16 values as a packed signed-integer max with zero
-      a[ib] = __builtin_bit_cast(bf16x8, __builtin_elementwise_max(frag(st, IB * wave + ib), zero8));
+      a[ib] = __builtin_bit_cast(bf16x8, __builtin_elementwise_max(frag(st, ib0 + ib), zero8));
 #pragma unroll
-    for (int jb = 0; jb < 4; ++jb) b[jb] = __builtin_bit_cast(bf16x8, frag(st + PARTB, jb));
+    for (int jb = 0; jb < JB; ++jb) b[jb] = __builtin_bit_cast(bf16x8, frag(st + PARTB, jb0 + jb));
 #pragma unroll
     for (int ib = 0; ib < IB; ++ib) {
 #pragma unroll
-      for (int jb = 0; jb < 4; ++jb) acc[ib][jb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[ib], b[jb], acc[ib][jb], 0, 0, 0);
+      for (int jb = 0; jb < JB; ++jb) acc[ib][jb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[ib], b[jb], acc[ib][jb], 0, 0, 0);
       zacc[ib] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[ib], __builtin_bit_cast(bf16x8, ones8), zacc[ib], 0, 0, 0);
     }
   }
@@ -460,11 +461,11 @@ __device__ __forceinline__ void absorb_role(char* smem, const AbsorbArgs& ab) {
   for (int ib = 0; ib < IB; ++ib)
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
-      const int i = 32 * (IB * wave + ib) + 8 * (r >> 2) + 4 * h + (r & 3);
+      const int i = 32 * (ib0 + ib) + 8 * (r >> 2) + 4 * h + (r & 3);
 #pragma unroll
-      for (int jb = 0; jb < 4; ++jb)
-        __hip_atomic_store(part + i * D + 32 * jb + l32, acc[ib][jb][r], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-      if (l32 == 0) __hip_atomic_store(part + D * D + i, zacc[ib][r], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      for (int jb = 0; jb < JB; ++jb)
+        __hip_atomic_store(part + i * D + 32 * (jb0 + jb) + l32, acc[ib][jb][r], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      if (l32 == 0 && jb0 == 0) __hip_atomic_store(part + D * D + i, zacc[ib][r], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
   // ---- arrival: every store above has been acknowledged before the workgroup draws its ticket
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
@@ -542,23 +543,28 @@ __device__ __forceinline__ void absorb_role(char* smem, const AbsorbArgs& ab) {
 
 // kSel: 1 = the workgroup first selects its KV blocks itself (Eq. 4 from hist.kbar_t, list to hist.idx_out); the
 // first ab.role_blocks workgroup ids (a multiple of eight) absorb evicted tokens instead (absorb_role)
-template <int NW, int kFused, int kSel = 0>
-__global__ __launch_bounds__(64 * NW, 2) void attn_mfma_kernel(
+// KS: groups of NW wavefronts that share the query block, group g the tiles g, g + KS, ... of its list; their partial (m, l, O)
+// meet in LDS behind the loop and every group finishes 4 / KS of the four 32-feature blocks
+template <int NW, int kFused, int kSel, int KS>
+__global__ __launch_bounds__(64 * NW * KS, 2) void attn_mfma_kernel(
     const bf16_t* __restrict__ Q, const bf16_t* __restrict__ K, const bf16_t* __restrict__ V,
     const int32_t* __restrict__ idx, int k, int n_q, int n_kv, int kv_stride, int bkv, int t_m, int t_n,
     int items_per_xcd, int total_items, float c_scale, HistArgs hist, AbsorbArgs ab, bf16_t* __restrict__ O) {
-  constexpr int NT = 64 * NW;
+  constexpr int NT = 64 * NW * KS;
   constexpr int BQ = 32 * NW;
-  constexpr int CPT = (TK * D * 2 / 16) / NT;  // 1 KB pieces (4 key rows) of a tile per wavefront (4 or 2)
-  __shared__ __attribute__((aligned(16))) char smem[5 * KTILE];
-  char* const sK = smem;                // three K tiles (requested two tiles ahead)
-  char* const sV = smem + 3 * KTILE;    // two V tiles (requested one tile ahead)
-  static_assert(BQ * OSTR <= 5 * KTILE, "staged output must fit in the tiles");
+  constexpr int CPT = (TK * D * 2 / 16) / (64 * NW);  // 1 KB pieces (4 key rows) of a tile per wavefront (4 or 2)
+  constexpr int ND = 4 / KS;                   // 32-feature blocks that a wavefront finishes
+  // a group's space: three K tiles (requested two tiles ahead) and two V tiles (one ahead); behind the loop its ND tiles of
+  // the state's plane, its row statistics and the accumulators that the other groups finish
+  constexpr int PSTAT = ND * KTILE, PPART = PSTAT + BQ * 8, PEND = PPART + (4 - ND) * NW * 4096;
+  constexpr int GB = KS > 1 && PEND > 5 * KTILE ? PEND : 5 * KTILE;
+  __shared__ __attribute__((aligned(16))) char smem[KS * GB];
+  static_assert(BQ * OSTR <= KS * GB, "staged output must fit in the tiles");
 
   // consecutive workgroup ids go to consecutive XCDs: give every XCD one contiguous run of
   // (head, query block) items so that its L2 sees few heads
   if (kSel && (int)blockIdx.x < ab.role_blocks) {
-    absorb_role<NW>(smem, ab);
+    absorb_role<NW * KS>(smem, ab);
     return;
   }
   const int wgid = kSel ? (int)blockIdx.x - ab.role_blocks : (int)blockIdx.x;
@@ -568,7 +574,10 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_mfma_kernel(
   const int bh = item / t_m, qb = item % t_m;
 
   const int tid = threadIdx.x, lane = tid & 63;
-  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);   // uniform: keeps LDS slot arithmetic on the scalar unit
+  const int wave_in_wg = __builtin_amdgcn_readfirstlane(tid >> 6);   // uniform: keeps LDS slot arithmetic on the scalar unit
+  const int wave = KS == 1 ? wave_in_wg : wave_in_wg % NW, grp = KS == 1 ? 0 : wave_in_wg / NW;
+  char* const sK = smem + grp * GB;
+  char* const sV = sK + 3 * KTILE;
   const int l32 = lane & 31, h = lane >> 5;
   const bf16_t* Qh = Q + (size_t)bh * n_q * D;
   const bf16_t* Kh = K + (size_t)bh * kv_stride * D;  // heads of a cache buffer are kv_stride tokens apart
@@ -578,11 +587,11 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_mfma_kernel(
   const int nsel = (kSel || idx) ? k : t_n;
   const int* sel_lds = nullptr;   // kSel: the list in LDS, valid until the first tile is requested
   if (kSel)
-    sel_lds = select_in_workgroup<NW>(smem, Qh, qb * BQ, n_q, hist.kbar_t + (size_t)bh * (D / 4) * t_n * 4, t_n, k,
+    sel_lds = select_in_workgroup<NW * KS, BQ>(smem, Qh, qb * BQ, n_q, hist.kbar_t + (size_t)bh * (D / 4) * t_n * 4, t_n, k,
                                       hist.idx_out + ((size_t)bh * t_m + qb) * k,
                                       hist.scores_out ? hist.scores_out + ((size_t)bh * t_m + qb) * t_n : nullptr);
   const int subs = (bkv + TK - 1) / TK;
-  const int ntiles = nsel * subs;
+  const int ntiles = (nsel * subs + KS - 1) / KS;   // every group the same number: the barriers are the workgroup's
 
   // ---- this lane's query row as B-operand fragments (d = 16 s + 8 h .. +8)
   const int q_row = qb * BQ + 32 * wave + l32;
@@ -607,7 +616,7 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_mfma_kernel(
   // out of the tile loop.
   int d_tile = 0, tq = 0;  // first key (24 bits: the window has fewer than 2^23 keys) | real keys << 24
   auto refill = [&](int t0) {
-    const int t = t0 + lane;
+    const int t = grp + KS * (t0 + lane);
     const int sel = t / subs, sub = t - sel * subs;
     const int sc = min(sel, nsel - 1);
     int jb;
@@ -826,24 +835,91 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_mfma_kernel(
     const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(l_run), __float_as_uint(l_run), false, false);
     l_tot = __uint_as_float(sw[0]) + __uint_as_float(sw[1]);
   }
+  // The plane of the state is on its way before anything else: it travels global -> LDS like the tiles ("tiles" of 32 value
+  // features x 128 key features in the K layout, so that an A fragment is the K fragment's read), under the meeting of the
+  // groups and the arithmetic of the denominator.
+  auto dma_plane = [&](int plane) {
+    const uint64_t b = reinterpret_cast<uint64_t>(hist.planes + (size_t)bh * 2 * D * D) + (uint64_t)plane * (D * D * 2);
+    const i32x4 p_desc = {(int)(uint32_t)b, (int)(uint32_t)(b >> 32), D * D * 2, 0x00020000};
+#pragma unroll
+    for (int i = 0; i < ND; ++i) dma_tile(p_desc, sK_lds + i * KTILE, 32 * (ND * grp + i), k_lane_off);
+  };
+  if (KS > 1) {
+    if (kFused == 1 || kFused == 2) dma_plane(0);
+    // ---- the groups' parts of a row meet: 16-byte pieces [block of another group][wavefront][quad][lane], row statistics
+    f32x4* const part = reinterpret_cast<f32x4*>(sK + PPART) + wave * 256 + lane;
+#pragma unroll
+    for (int dt = 0; dt < 4; ++dt)
+      if (dt / ND != grp) {   // uniform
+        f32x4* p = part + (dt - (dt / ND > grp ? ND : 0)) * NW * 256;
+#pragma unroll
+        for (int rq = 0; rq < 4; ++rq) p[rq * 64] = f32x4{o[dt][4 * rq], o[dt][4 * rq + 1], o[dt][4 * rq + 2], o[dt][4 * rq + 3]};
+      }
+    if (h == 0) *reinterpret_cast<float2*>(sK + PSTAT + (32 * wave + l32) * 8) = make_float2(m_ref, l_tot);
+    __syncthreads();
+    float wu[KS], lu[KS];
+    const float m_own = m_ref;
+#pragma unroll
+    for (int u = 0; u < KS; ++u) {
+      const float2 st = *reinterpret_cast<const float2*>(smem + u * GB + PSTAT + (32 * wave + l32) * 8);
+      wu[u] = st.x;
+      lu[u] = st.y;
+      m_ref = fmaxf(m_ref, st.x);
+    }
+    const float m_use = m_ref == -INFINITY ? 0.0f : m_ref;
+    l_tot = 0.0f;
+#pragma unroll
+    for (int u = 0; u < KS; ++u) {
+      wu[u] = __builtin_amdgcn_exp2f(wu[u] - m_use);
+      l_tot = fmaf(lu[u], wu[u], l_tot);
+    }
+    const float w_own = __builtin_amdgcn_exp2f(m_own - m_use);
+    // this group's blocks move to the front (constant indices: accumulators stay in registers)
+#pragma unroll
+    for (int g = 1; g < KS; ++g)
+      if (grp == g) {   // uniform
+#pragma unroll
+        for (int i = 0; i < ND; ++i) o[i] = o[ND * g + i];
+      }
+#pragma unroll
+    for (int i = 0; i < ND; ++i)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) o[i][r] *= w_own;
+#pragma unroll
+    for (int u = 0; u < KS; ++u)
+      if (u != grp) {   // uniform; group order
+#pragma unroll
+        for (int i = 0; i < ND; ++i) {
+          const int slot = ND * grp + i - (grp > u ? ND : 0);   // where group u keeps the block
+          const f32x4* p = reinterpret_cast<const f32x4*>(smem + u * GB + PPART) + (slot * NW + wave) * 256 + lane;
+#pragma unroll
+          for (int rq = 0; rq < 4; ++rq) {
+            const f32x4 x = p[rq * 64];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) o[i][4 * rq + e] = fmaf(x[e], wu[u], o[i][4 * rq + e]);
+          }
+        }
+      }
+  }
+  const int dt0 = ND * grp;   // o[i], i < ND, holds feature block dt0 + i from here on
   const float inv = l_tot > 0.0f ? 1.0f / l_tot : 0.0f;
 #pragma unroll
-  for (int dt = 0; dt < 4; ++dt)
+  for (int i = 0; i < ND; ++i)
 #pragma unroll
-    for (int r = 0; r < 16; ++r) o[dt][r] *= inv;
+    for (int r = 0; r < 16; ++r) o[i][r] *= inv;
 
   // the accumulators as bf16 rows of a [n_q][d] head: transposed through LDS (whose tiles or planes are dead at
   // every call), stored as coalesced rows; LDS may be reused after the barrier that follows the last call
   auto store_rows = [&](bf16_t* dst_head) {
     char* stage = smem;
 #pragma unroll
-    for (int dt = 0; dt < 4; ++dt)
+    for (int i = 0; i < ND; ++i)
 #pragma unroll
       for (int rq = 0; rq < 4; ++rq) {
         uint2 w;
-        w.x = (uint32_t)f32_to_bf16(o[dt][4 * rq]) | ((uint32_t)f32_to_bf16(o[dt][4 * rq + 1]) << 16);
-        w.y = (uint32_t)f32_to_bf16(o[dt][4 * rq + 2]) | ((uint32_t)f32_to_bf16(o[dt][4 * rq + 3]) << 16);
-        *reinterpret_cast<uint2*>(stage + (32 * wave + l32) * OSTR + (32 * dt + 8 * rq + 4 * h) * 2) = w;
+        w.x = (uint32_t)f32_to_bf16(o[i][4 * rq]) | ((uint32_t)f32_to_bf16(o[i][4 * rq + 1]) << 16);
+        w.y = (uint32_t)f32_to_bf16(o[i][4 * rq + 2]) | ((uint32_t)f32_to_bf16(o[i][4 * rq + 3]) << 16);
+        *reinterpret_cast<uint2*>(stage + (32 * wave + l32) * OSTR + (32 * (dt0 + i) + 8 * rq + 4 * h) * 2) = w;
       }
     __syncthreads();
 #pragma unroll
@@ -856,11 +932,16 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_mfma_kernel(
   };
   if (kFused != 3) {
     // ---- by-products for a later backward pass (training forward): the row statistic and O_local itself
-    if (hist.lse2_out && h == 0 && q_row < n_q)
+    if (hist.lse2_out && h == 0 && grp == 0 && q_row < n_q)
       hist.lse2_out[(size_t)bh * n_q + q_row] = l_tot > 0.0f ? m_ref + __log2f(l_tot) : INFINITY;
     if (kFused != 0 && hist.olocal_out) {   // (without a history term O is O_local)
+      if (KS > 1) {   // every part has been read, the plane has landed: both lie where the rows are staged
+        asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+        __syncthreads();
+      }
       store_rows(hist.olocal_out + (size_t)bh * n_q * D);
       __syncthreads();
+      if (KS > 1) dma_plane(0);   // (once more: the rows were staged over it)
     }
   }
 
@@ -892,17 +973,7 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_mfma_kernel(
     // ---- O += R(phi(q)) L / (z_scale phi(q).z + eps) (Eq. 3, 6): the query fragments already in
     // registers become the B operand of O_hist^T = Lt x R(phi(Q))^T; the A operand comes from the
     // L2-resident plane(s) through LDS.
-    // The plane of the state is on its way before anything else: it travels global -> LDS like the tiles (four
-    // "tiles" of 32 value features x 128 key features in the K layout, so that an A fragment is the K fragment's
-    // read), under the arithmetic of the denominator.
-    const uint64_t plane_base = reinterpret_cast<uint64_t>(hist.planes + (size_t)bh * 2 * D * D);
-    auto dma_plane = [&](int plane) {
-      const uint64_t b = plane_base + (uint64_t)plane * (D * D * 2);
-      const i32x4 p_desc = {(int)(uint32_t)b, (int)(uint32_t)(b >> 32), D * D * 2, 0x00020000};
-#pragma unroll
-      for (int dt = 0; dt < 4; ++dt) dma_tile(p_desc, sK_lds + dt * KTILE, 32 * dt, k_lane_off);
-    };
-    dma_plane(0);
+    if (KS == 1) dma_plane(0);
     const float* zv = hist.zvec + (size_t)bh * D + 8 * h;
     float den = 0.0f;
     if (kFused == 1) {
@@ -960,9 +1031,9 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_mfma_kernel(
     // same accumulators, and one multiplication by 1/denominator finishes O_local + O_hist
     const float den_eps = hist.z_scale * den + hist.eps;
 #pragma unroll
-    for (int dt = 0; dt < 4; ++dt)
+    for (int i = 0; i < ND; ++i)
 #pragma unroll
-      for (int r = 0; r < 16; ++r) o[dt][r] *= den_eps;
+      for (int r = 0; r < 16; ++r) o[i][r] *= den_eps;
     static_assert(D * D * 2 <= 4 * KTILE, "a state plane must fit in the tiles' space");
     for (int plane = 0; plane < hist.n_planes; ++plane) {  // each plane goes through LDS once per workgroup
       if (plane) {
@@ -974,17 +1045,19 @@ __global__ __launch_bounds__(64 * NW, 2) void attn_mfma_kernel(
 #pragma unroll
       for (int s = 0; s < 8; ++s)
 #pragma unroll
-        for (int dt = 0; dt < 4; ++dt) {
-          const bf16x8 a = *reinterpret_cast<const bf16x8*>(sK + k_addr[s] + dt * KTILE);
-          o[dt] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, qf[s], o[dt], 0, 0, 0);
+        for (int i = 0; i < ND; ++i) {
+          const bf16x8 a = *reinterpret_cast<const bf16x8*>(sK + k_addr[s] + i * KTILE);
+          o[i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, qf[s], o[i], 0, 0, 0);
         }
     }
     const float inv_den = 1.0f / den_eps;
 #pragma unroll
-    for (int dt = 0; dt < 4; ++dt)
+    for (int i = 0; i < ND; ++i)
 #pragma unroll
-      for (int r = 0; r < 16; ++r) o[dt][r] *= inv_den;
+      for (int r = 0; r < 16; ++r) o[i][r] *= inv_den;
     __syncthreads();  // the plane's space becomes the output staging area
+  } else if (KS > 1) {
+    __syncthreads();  // every part has been read
   }
 
   store_rows(Oh);
@@ -998,6 +1071,19 @@ bool attn_mfma_supported(const hf_config& c) {
 
 // byte offsets inside one head are 32-bit in the buffer loads
 constexpr int kMfmaMaxKeys = 1 << 23;
+
+// How many groups of wavefronts share a query block's list.  A compute unit holds eight wavefronts of this kernel: four
+// workgroups of one group at block_q 64, two at block_q 128, half as many of two groups.  Two groups cost 5 to 8 % where the
+// chip is full either way, and win where they leave less of it idle: launches that fit in one round of twice-as-large
+// workgroups, and at block_q 64 those of which the last round of small ones is at most half full (a second round of 1025
+// workgroups takes as long as one of 1537).
+// hf_step_fwd, one / two groups: 2 heads x 15 blocks 27.7 / 25.6 us, 4 x 33 32.8 / 25.3, 6 x 43 48.3 / 38.0, 8 x 52 55.5 / 43.4,
+// 12 x 47 56.9 / 61.2, 16 x 66 128 / 120, 16 x 74 143 / 133, 24 x 74 196 / 206; block_q 128: 4 x 24 41.3 / 37.0, 8 x 36 73 / 90.
+// (Four groups of two wavefronts were never better than two.)
+static int key_groups(const hf_config& c, long long workgroups) {
+  if (c.block_q != 64) return workgroups <= 256 ? 2 : 1;
+  return workgroups <= 512 || (workgroups > 1024 && workgroups <= 1536) ? 2 : 1;
+}
 
 static int launch_attn_mfma_impl(const hf_config& c, const void* Q, int n_q, const void* K, const void* V, int n_kv,
                                  const int32_t* idx, int k, const HistArgs* hist, void* O, hipStream_t s,
@@ -1017,9 +1103,15 @@ static int launch_attn_mfma_impl(const hf_config& c, const void* Q, int n_q, con
   const bf16_t* v = static_cast<const bf16_t*>(V);
   bf16_t* o = static_cast<bf16_t*>(O);
   const HistArgs h = hist ? *hist : HistArgs{};
-#define HF_LAUNCH_ATTN_SEL(NWV, FUSED, SEL)                                                                      \
-  hipLaunchKernelGGL((attn_mfma_kernel<NWV, FUSED, SEL>), grid, dim3(64 * NWV), 0, s, q, kk, v, idx, k, n_q, n_kv, \
+  const int ks = key_groups(c, total + (ab.role_blocks ? 2 * BH : 0));   // (as step_absorb_slices counts)
+#define HF_LAUNCH_ATTN_KS(NWV, FUSED, SEL, KS)                                                                         \
+  hipLaunchKernelGGL((attn_mfma_kernel<NWV, FUSED, SEL, KS>), grid, dim3(64 * NWV * KS), 0, s, q, kk, v, idx, k, n_q, n_kv, \
                      kv_stride_of(c, n_kv), c.block_kv, t_m, t_n, per_xcd, (int)total, c_scale, h, ab, o)
+#define HF_LAUNCH_ATTN_SEL(NWV, FUSED, SEL)                                                                            \
+  do {                                                                                                                 \
+    if (ks == 2) HF_LAUNCH_ATTN_KS(NWV, FUSED, SEL, 2);                                                           \
+    else HF_LAUNCH_ATTN_KS(NWV, FUSED, SEL, 1);                                                                        \
+  } while (0)
 #define HF_LAUNCH_ATTN(NWV, FUSED) HF_LAUNCH_ATTN_SEL(NWV, FUSED, 0)
   const int fused = !h.planes && !h.lse2 ? 0 : (h.lse2 ? 3 : ((h.phi_kind == HF_PHI_RELU && h.cosq == nullptr && h.q_hist == nullptr) ? 1 : 2));
   if (ab.role_blocks && !h.kbar_t) { set_error("absorbing workgroups ride only in the selecting launch"); return HF_ERR_SHAPE; }
@@ -1039,12 +1131,13 @@ static int launch_attn_mfma_impl(const hf_config& c, const void* Q, int n_q, con
     return check_launch("hf_select_attn_fwd(attention)");
   }
   if (c.block_q == 64) {
-    if (fused == 0) HF_LAUNCH_ATTN(2, 0); else if (fused == 1) HF_LAUNCH_ATTN(2, 1); else if (fused == 2) HF_LAUNCH_ATTN(2, 2); else HF_LAUNCH_ATTN(2, 3);
+    if (fused == 0) HF_LAUNCH_ATTN(2, 0); else if (fused == 1) HF_LAUNCH_ATTN(2, 1); else if (fused == 2) HF_LAUNCH_ATTN(2, 2); else HF_LAUNCH_ATTN_KS(2, 3, 0, 1);
   } else {
-    if (fused == 0) HF_LAUNCH_ATTN(4, 0); else if (fused == 1) HF_LAUNCH_ATTN(4, 1); else if (fused == 2) HF_LAUNCH_ATTN(4, 2); else HF_LAUNCH_ATTN(4, 3);
+    if (fused == 0) HF_LAUNCH_ATTN(4, 0); else if (fused == 1) HF_LAUNCH_ATTN(4, 1); else if (fused == 2) HF_LAUNCH_ATTN(4, 2); else HF_LAUNCH_ATTN_KS(4, 3, 0, 1);
   }
 #undef HF_LAUNCH_ATTN
 #undef HF_LAUNCH_ATTN_SEL
+#undef HF_LAUNCH_ATTN_KS
   return check_launch("hf_hybrid_attn_fwd(attention)");
 }
 
@@ -1081,7 +1174,7 @@ int launch_attn_mfma_fused(const hf_config& c, const void* Q, int n_q, const voi
 int step_absorb_slices(const hf_config& c, int n_q, int n_ev) {
   const int BH = c.batch * c.heads;
   const long long attending = (long long)BH * ((n_q + c.block_q - 1) / c.block_q);
-  const long long slots = 256ll * (c.block_q == 64 ? 4 : 2);
+  const long long slots = 256ll * (c.block_q == 64 ? 4 : 2) / key_groups(c, attending + 2 * BH);
   long long room = slots - attending;          // a launch of several rounds has no room to speak of: few, long slices
   int s = room >= BH ? (int)(room / BH) : 2;
   if (s > 8) s = 8;
