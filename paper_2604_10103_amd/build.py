@@ -1,9 +1,9 @@
-"""Build libhf.so (the gfx950 C-ABI library) in-tree with hipcc.
+"""Build libhf.so (the gfx950 C-ABI library, hipcc) and _marshal.so (the binding's native part, g++) in-tree.
 
     python -m paper_2604_10103_amd.build
 
-Cross-compiles without a GPU.  Object files go to ``_build/`` (ignored); the shared library
-lands next to this file so that it travels with the source tree.
+Cross-compiles without a GPU.  Object files go to ``_build/`` (ignored); the shared libraries
+land next to this file so that they travel with the source tree.
 """
 from __future__ import annotations
 
@@ -11,12 +11,14 @@ import os
 import shutil
 import subprocess
 import sys
+import sysconfig
 from concurrent.futures import ThreadPoolExecutor
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(HERE)
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libhf.so")
+MARSHAL = os.path.join(HERE, "_marshal.so")
 
 SOURCES = [
     "hf_api.hip",
@@ -65,6 +67,26 @@ def hipcc() -> str:
     return exe
 
 
+def build_marshal() -> None:
+    """Host code only: Python, torch and the ROCm runtime's headers."""
+    import torch
+    from torch.utils import cpp_extension
+
+    cc = shutil.which("g++")
+    if cc is None:
+        raise RuntimeError("g++ not found")
+    rocm = os.environ.get("ROCM_PATH", "/opt/rocm")
+    system = [*cpp_extension.include_paths(), os.path.join(rocm, "include"), sysconfig.get_paths()["include"]]
+    libs = os.path.join(os.path.dirname(torch.__file__), "lib")
+    cmd = [cc, "-O2", "-std=c++17", "-fPIC", "-shared", "-fvisibility=hidden", "-Wall", "-D__HIP_PLATFORM_AMD__=1",
+           f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}",
+           *[a for d in system for a in ("-isystem", d)], "-I" + os.path.join(ROOT, "include"),
+           os.path.join(CSRC, "hf_marshal.cpp"), "-o", MARSHAL, "-L" + libs, "-lc10", "-lc10_hip", "-ltorch_cpu", "-ltorch_python"]
+    r = subprocess.run(cmd, capture_output=True, text=True)
+    if r.returncode != 0:
+        raise RuntimeError(f"g++ failed on hf_marshal.cpp:\n{r.stdout}\n{r.stderr}")
+
+
 def build(verbose: bool = False, jobs: int = 8) -> str:
     out_dir = os.path.join(ROOT, "_build")
     os.makedirs(out_dir, exist_ok=True)
@@ -86,7 +108,9 @@ def build(verbose: bool = False, jobs: int = 8) -> str:
         return obj
 
     with ThreadPoolExecutor(max_workers=jobs) as ex:
+        marshal = ex.submit(build_marshal)
         objs = list(ex.map(compile_one, SOURCES))
+        marshal.result()
     cmd = [cc, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB, *objs]
     r = subprocess.run(cmd, capture_output=True, text=True)
     if r.returncode != 0:
