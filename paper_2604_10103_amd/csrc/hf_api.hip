@@ -1144,22 +1144,17 @@ static int bwd_impl(const hf_config* cfg, const void* Q, const void* Q_hist, int
     const size_t bytes = (size_t)cfg->batch * cfg->heads * n_q * cfg->head_dim * esize(cfg);
     HF_TRY(launch_fill_zero(static_cast<float*>(dQ_hist), bytes / 4, s));
   }
-  if (block_idx) HF_TRY(launch_invert_index(*cfg, block_idx, k, t_m, t_n, inv_cnt, inv_list, s));
   if (mfma) {
-    // row statistics of the softmax and D = dO . O_local (unrounded) from a recomputed forward pass; the history
-    // branch rides in the dQ kernel's epilogue
-    const float* lse2_in = lse2;
-    if (saved) {
-      // D = dO . O_local from the saved (once rounded) O_local; the row statistic as saved
-      HF_TRY(launch_row_dot(*cfg, dO, O_local, (long long)cfg->batch * cfg->heads * n_q, dvec, s));
-      lse2_in = lse2_saved;
-    } else {
-      HF_TRY(launch_attn_mfma_stats(*cfg, Q, n_q, K_win, V_win, n_kv, block_idx, k, dO, lse2, dvec, s));
-    }
-    return launch_bwd_mfma(*cfg, Q, n_q, K_win, V_win, n_kv, block_idx, k, dO, lse2_in, dvec, inv_cnt, inv_list,
-                           reinterpret_cast<int32_t*>(ws + w.order), st, rope_cos_q, rope_sin_q, Q_hist, ws + w.planes,
-                           dQ, dQ_hist, dK, dV, s);
+    // row statistics of the softmax and D = dO . O_local: saved by the forward pass (D then from the once rounded O_local),
+    // or from a recomputed one (unrounded); the history branch rides in the dQ kernel's epilogue
+    int32_t* order = block_idx && !(cfg->flags & HF_FLAG_DKV_INDEX_ORDER) ? reinterpret_cast<int32_t*>(ws + w.order) : nullptr;
+    HF_TRY(launch_bwd_prep(*cfg, block_idx, k, t_m, t_n, inv_cnt, inv_list, &order, st, ws + w.planes, saved ? dO : nullptr,
+                           O_local, (long long)cfg->batch * cfg->heads * n_q, dvec, s));
+    if (!saved) HF_TRY(launch_attn_mfma_stats(*cfg, Q, n_q, K_win, V_win, n_kv, block_idx, k, dO, lse2, dvec, s));
+    return launch_bwd_mfma(*cfg, Q, n_q, K_win, V_win, n_kv, block_idx, k, dO, saved ? lse2_saved : lse2, dvec, inv_cnt, inv_list,
+                           order, st, rope_cos_q, rope_sin_q, Q_hist, ws + w.planes, dQ, dQ_hist, dK, dV, s);
   }
+  HF_TRY(launch_bwd_prep(*cfg, block_idx, k, t_m, t_n, inv_cnt, inv_list, nullptr, nullptr, nullptr, nullptr, nullptr, 0, nullptr, s));
   HF_TRY(launch_attn_wide_stats(*cfg, Q, n_q, K_win, V_win, n_kv, block_idx, k, dO, lse2, dvec, s));
   return launch_bwd_generic(*cfg, Q, Q_hist, n_q, K_win, V_win, n_kv, block_idx, k, dO, lse2, dvec, inv_cnt, inv_list, st,
                             rope_cos_q, rope_sin_q, dQ, st ? dQ_hist : nullptr, dK, dV, s);

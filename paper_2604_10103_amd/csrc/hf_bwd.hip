@@ -42,53 +42,185 @@ __global__ __launch_bounds__(256) void invert_index_kernel(const int32_t* __rest
   if (lane == 0) inv_cnt[(size_t)bh * t_n + j] = cnt;
 }
 
-// The same lists by counting, one workgroup per head (used when a head's index rows and eight histograms fit in
-// LDS): the rows are copied to LDS once; wavefront w owns a contiguous run of query blocks and walks it in order,
-// first counting the hits per KV block, then, from the exclusive sums over the wavefronts, placing its query blocks
-// behind those of the wavefronts before it.  Lanes of a wavefront work on one row at a time, whose entries are
-// distinct by contract, so their counters are distinct: no atomics.  Ascending lists, as above.
-constexpr int kInvWaves = 8;
-__global__ __launch_bounds__(64 * kInvWaves) void invert_index_lds_kernel(const int32_t* __restrict__ idx, int k,
-                                                                          int t_m, int t_n,
-                                                                          int32_t* __restrict__ inv_cnt,
-                                                                          int32_t* __restrict__ inv_list) {
-  extern __shared__ int32_t inv_smem[];
-  int32_t* rows = inv_smem;              // [t_m][k]
-  int32_t* hist = inv_smem + t_m * k;    // [kInvWaves][t_n]
-  const int bh = blockIdx.x, tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-  const int32_t* src = idx + (size_t)bh * t_m * k;
-  for (int e = tid; e < t_m * k; e += 64 * kInvWaves) rows[e] = src[e];
-  for (int e = tid; e < kInvWaves * t_n; e += 64 * kInvWaves) hist[e] = 0;
+// ---- what the gradient kernels need prepared, in one launch (each part alone is shorter than a launch costs): workgroups
+// take a part by their number.
+//
+//   order   one per XCD's share of the dK/dV items: launch order, see below
+//   invert  one per head: the inverse lists
+//   planes  two 32 x 32 tiles of a head's state each: fp32 -> the bf16 planes L^T and L of the history branch's gradient
+//   dots    32 rows each: D = dO . O_local from a saved O_local
+//
+// 832x480 (12 heads, 4680 x 9360, blocks of 64, k = 37): 11.1 us, where launches of their own took 7.4 + 6.2 + 5.0 + 6.7 us
+// and three gaps; the whole training step 395 -> 382 us, one of 35 heads x 282 tokens 72.4 -> 65.7 us.
+constexpr int kPrepThreads = 512;
+struct PrepArgs {
+  const int32_t* idx;            // [BH][t_m][k]
+  int k, t_m, t_n;
+  int order_wgs, invert_wgs, plane_wgs;
+  int32_t *inv_cnt, *inv_list;   // [BH][t_n], [BH][t_n][t_m]
+  int slabs, items_per_xcd, total_items;
+  int32_t* order;                // [8 items_per_xcd][kOrderRec]
+  const float* state;
+  bf16_t* planes;
+  const bf16_t *A, *B;
+  long long rows;
+  float* dots;
+};
+
+// The inverse lists as bit masks in LDS: for KV blocks [b0, b0 + n) (numbered over all heads) one bit per query block that
+// selected it, 32 to a word.  One pass over the index rows of the heads they belong to, every entry on its own; a block's
+// list is then the positions of its bits, its length their number, and bit i stands at the number of bits below it.
+__device__ __forceinline__ void selected_by(uint32_t* mask, const PrepArgs& p, int b0, int n, int words) {
+  const int tid = threadIdx.x;
+  for (int e = tid; e < n * words; e += kPrepThreads) mask[e] = 0;
   __syncthreads();
-  const int seg = (t_m + kInvWaves - 1) / kInvWaves;
-  const int i_begin = min(w * seg, t_m), i_end = min(i_begin + seg, t_m);
-  int32_t* mine = hist + w * t_n;
-  for (int i = i_begin; i < i_end; ++i)
-    for (int s = lane; s < k; s += 64) {
-      const int j = rows[i * k + s];
-      if ((unsigned)j < (unsigned)t_n) mine[j] += 1;
+  const int row_words = p.t_m * p.k;   // entries of a head
+  const int h0 = b0 / p.t_n, entries = ((b0 + n - 1) / p.t_n - h0 + 1) * row_words;
+  const int32_t* src = p.idx + (size_t)h0 * row_words;
+  const uint32_t per_k = 0xffffffffu / (uint32_t)p.k + 1u;   // e / k = e per_k / 2^32 (e k < 2^32 wherever the masks fit)
+  constexpr int U = 8;                 // entries in flight per thread: the pass is round trips to memory
+  for (int e0 = tid; e0 < entries; e0 += U * kPrepThreads) {
+    int entry[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) entry[u] = src[min(e0 + u * kPrepThreads, entries - 1)];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      int e = e0 + u * kPrepThreads, at = h0 * p.t_n - b0;
+      if (e >= entries) break;
+      while (e >= row_words) {         // (the blocks of a share belong to a few heads)
+        e -= row_words;
+        at += p.t_n;
+      }
+      const int j = entry[u], i = p.k == 1 ? e : (int)__umulhi((uint32_t)e, per_k);
+      if ((unsigned)j < (unsigned)p.t_n && (unsigned)(at + j) < (unsigned)n) atomicOr(&mask[(at + j) * words + (i >> 5)], 1u << (i & 31));
     }
-  __syncthreads();
-  for (int j = tid; j < t_n; j += 64 * kInvWaves) {
-    int base = 0;
-    for (int v = 0; v < kInvWaves; ++v) {
-      const int c = hist[v * t_n + j];
-      hist[v * t_n + j] = base;
-      base += c;
-    }
-    inv_cnt[(size_t)bh * t_n + j] = min(base, t_m);
   }
   __syncthreads();
-  int32_t* out = inv_list + (size_t)bh * t_n * t_m;
-  for (int i = i_begin; i < i_end; ++i)
-    for (int s = lane; s < k; s += 64) {
-      const int j = rows[i * k + s];
-      if ((unsigned)j < (unsigned)t_n) {
-        const int pos = mine[j];
-        mine[j] = pos + 1;
-        if (pos < t_m) out[(size_t)j * t_m + pos] = i;   // (a row that breaks the contract cannot write past a list)
+}
+
+// Launch order of the dK/dV workgroups.  A workgroup's time is proportional to the length of its KV block's list of query
+// blocks, and the lists differ (top-k selection: a binomial spread around t_m k / t_n), while a GPU takes workgroups in index
+// order as slots free up.  Longest first within every XCD's share of the items leaves the short ones to fill the end.  One
+// record of kOrderRec words per place: the item that runs there, the length of its list and the list's first three entries, so that a workgroup has all it needs for its first
+// tiles after ONE dependent load (it is alone on its two SIMDs: every round trip to memory before its first MFMA is idle
+// time).  The masks are formed here once more, for the share's blocks: waiting for the workgroups that write the lists would
+// take another launch.
+__device__ __forceinline__ void order_share(int32_t* smem, const PrepArgs& p, int share, int words) {
+  const int first = share * p.items_per_xcd;
+  const int n = min(p.items_per_xcd, p.total_items - first);
+  if (n <= 0) return;
+  const int b0 = first / p.slabs, nb = (first + n - 1) / p.slabs - b0 + 1;   // KV blocks (of all heads) of the share
+  int32_t* const key = smem;                                                  // [n] list length
+  int32_t* const bucket = key + p.items_per_xcd;                              // [t_m + 1] items of a length; their places
+  uint32_t* const mask = reinterpret_cast<uint32_t*>(bucket + p.t_m + 1);     // [nb][words]
+  const int tid = threadIdx.x;
+  for (int e = tid; e <= p.t_m; e += kPrepThreads) bucket[e] = 0;
+  selected_by(mask, p, b0, nb, words);
+  for (int j = tid; j < n; j += kPrepThreads) {
+    const uint32_t* m = mask + ((first + j) / p.slabs - b0) * words;
+    int len = 0;
+    for (int w = 0; w < words; ++w) len += __popc(m[w]);
+    key[j] = len;
+    atomicAdd(&bucket[len], 1);
+  }
+  __syncthreads();
+  // exclusive sums from the longest down: where each length's items start
+  if (tid < kWave) {
+    int before = 0;
+    for (int top = p.t_m; top >= 0; top -= kWave) {
+      const int own = top - tid >= 0 ? bucket[top - tid] : 0;
+      int sum = own;
+#pragma unroll
+      for (int o = 1; o < kWave; o <<= 1) {
+        const int up = __shfl_up(sum, o, kWave);
+        if (tid >= o) sum += up;
       }
+      if (top - tid >= 0) bucket[top - tid] = before + sum - own;
+      before += __shfl(sum, kWave - 1, kWave);
     }
+  }
+  __syncthreads();
+  for (int j = tid; j < n; j += kPrepThreads) {
+    const uint32_t* m = mask + ((first + j) / p.slabs - b0) * words;
+    int entry[3] = {0, 0, 0}, w = 0;
+    uint32_t bits = m[0];
+#pragma unroll
+    for (int q = 0; q < 3; ++q)
+      if (q < key[j]) {
+        while (!bits) bits = m[++w];   // (key[j] bits are set: ends)
+        entry[q] = 32 * w + __ffs(bits) - 1;
+        bits &= bits - 1;
+      }
+    // (which of two equally long lists comes first does not matter: every item runs once, whatever its place)
+    int4* rec = reinterpret_cast<int4*>(p.order + (size_t)(first + atomicAdd(&bucket[key[j]], 1)) * kOrderRec);
+    rec[0] = int4{first + j, key[j], entry[0], entry[1]};
+    rec[1] = int4{entry[2], 0, 0, 0};
+  }
+}
+
+__global__ __launch_bounds__(kPrepThreads) void bwd_prep_kernel(PrepArgs p) {
+  extern __shared__ int32_t prep_smem[];
+  int wg = blockIdx.x;
+  const int words = (p.t_m + 31) >> 5;
+  if (wg < p.order_wgs) {
+    order_share(prep_smem, p, wg, words);
+    return;
+  }
+  wg -= p.order_wgs;
+  if (wg < p.invert_wgs) {
+    uint32_t* const mask = reinterpret_cast<uint32_t*>(prep_smem);
+    selected_by(mask, p, wg * p.t_n, p.t_n, words);
+    int32_t* const out = p.inv_list + (size_t)wg * p.t_n * p.t_m;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    for (int j = wave; j < p.t_n; j += kPrepThreads / 64) {   // a wavefront per list, two words of its mask at a time
+      const uint32_t* m = mask + j * words;
+      int below = 0;
+      for (int w = 0; w < words; w += 2) {
+        const unsigned long long both = m[w] | (w + 1 < words ? (unsigned long long)m[w + 1] << 32 : 0ull);
+        if (both >> lane & 1ull) out[(size_t)j * p.t_m + below + __popcll(both & ((1ull << lane) - 1ull))] = 32 * w + lane;
+        below += __popcll(both);
+      }
+      if (lane == 0) p.inv_cnt[(size_t)wg * p.t_n + j] = below;
+    }
+    return;
+  }
+  wg -= p.invert_wgs;
+  const int tid = threadIdx.x;
+  if (wg < p.plane_wgs) {
+    constexpr int D = 128;
+    const int half = tid >> 8, t = tid & 255, tx = t & 31, ty = t >> 5;   // 32 x 8 threads per tile
+    float* tile = reinterpret_cast<float*>(prep_smem) + half * 32 * 33;
+    const int bh = wg >> 3, which = 2 * (wg & 7) + half, i0 = 32 * (which >> 2), j0 = 32 * (which & 3);
+    const float* L = p.state + (size_t)bh * D * D;
+    bf16_t* lt = p.planes + (size_t)bh * 2 * D * D;
+    bf16_t* ln = lt + D * D;
+    for (int r = ty; r < 32; r += 8) {
+      const float v = L[(size_t)(i0 + r) * D + j0 + tx];
+      tile[r * 33 + tx] = v;
+      ln[(size_t)(i0 + r) * D + j0 + tx] = f32_to_bf16(v);
+    }
+    __syncthreads();
+    for (int r = ty; r < 32; r += 8) lt[(size_t)(j0 + r) * D + i0 + tx] = f32_to_bf16(tile[tx * 33 + r]);
+    return;
+  }
+  wg -= p.plane_wgs;
+  // 16 lanes per row, 16 bytes per lane and tensor, fp32 arithmetic
+  const long long row = (long long)wg * (kPrepThreads / 16) + (tid >> 4);
+  const int part = tid & 15;
+  float acc = 0.0f;
+  if (row < p.rows) {
+    const uint4 a = *reinterpret_cast<const uint4*>(p.A + row * 128 + part * 8);
+    const uint4 b = *reinterpret_cast<const uint4*>(p.B + row * 128 + part * 8);
+    const uint32_t aw[4] = {a.x, a.y, a.z, a.w}, bw[4] = {b.x, b.y, b.z, b.w};
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      acc = fmaf(__uint_as_float(aw[i] << 16), __uint_as_float(bw[i] << 16), acc);
+      acc = fmaf(__uint_as_float(aw[i] & 0xffff0000u), __uint_as_float(bw[i] & 0xffff0000u), acc);
+    }
+  }
+#pragma unroll
+  for (int off = 8; off >= 1; off >>= 1) acc += __shfl_xor(acc, off, 16);
+  if (row < p.rows && part == 0) p.dots[row] = acc;
 }
 
 // History branch (Eq. 3) in the dQ kernel's epilogue, as in the bf16 kernel: with f = phi(q), r = R f,
@@ -583,17 +715,66 @@ int launch_bwd_wide(const hf_config& c, const void* Q, int n_q, const void* K, c
 
 }  // namespace
 
-int launch_invert_index(const hf_config& c, const int32_t* idx, int k, int t_m, int t_n, int32_t* inv_cnt,
-                        int32_t* inv_list, hipStream_t s) {
-  const size_t lds = ((size_t)t_m * k + (size_t)kInvWaves * t_n) * sizeof(int32_t);
-  if (lds <= 48 * 1024) {
-    hipLaunchKernelGGL(invert_index_lds_kernel, dim3(c.batch * c.heads), dim3(64 * kInvWaves), lds, s, idx, k, t_m, t_n,
-                       inv_cnt, inv_list);
-    return check_launch("hf_hybrid_attn_bwd(inverse lists)");
+// idx given: the inverse lists; order_inout: where the dK/dV items' launch order goes, NULL on return if it was not formed
+// (a share's lists and ranks have to fit in LDS); state given: planes (bf16, head_dim 128); A given: row dots (likewise).
+int launch_bwd_prep(const hf_config& c, const int32_t* idx, int k, int t_m, int t_n, int32_t* inv_cnt, int32_t* inv_list,
+                    int32_t** order_inout, const float* state, void* planes, const void* A, const void* B, long long rows,
+                    float* dots, hipStream_t s) {
+  const int BH = c.batch * c.heads;
+  PrepArgs p = {};
+  p.idx = idx;
+  p.k = k;
+  p.t_m = t_m;
+  p.t_n = t_n;
+  p.inv_cnt = inv_cnt;
+  p.inv_list = inv_list;
+  int32_t* order = order_inout ? *order_inout : nullptr;
+  if (order_inout) *order_inout = nullptr;
+  size_t lds = 0;
+  if (idx) {
+    const size_t words = ((size_t)t_m + 31) / 32;
+    if ((size_t)t_n * words * 4 <= 48 * 1024) {
+      p.invert_wgs = BH;
+      lds = (size_t)t_n * words * 4;
+      const int slabs = (c.block_kv + 63) / 64;
+      const long long items = (long long)BH * t_n * slabs, share = (items + 7) / 8;
+      const size_t need = ((size_t)share + t_m + 1 + ((size_t)share / slabs + 2) * words) * 4;
+      if (order && need <= 150 * 1024) {
+        p.order_wgs = 8;
+        p.slabs = slabs;
+        p.items_per_xcd = (int)share;
+        p.total_items = (int)items;
+        p.order = order;
+        *order_inout = order;
+        if (need > lds) lds = need;
+      }
+    } else {
+      hipLaunchKernelGGL(invert_index_kernel, dim3((t_n + 3) / 4, BH), dim3(256), 0, s, idx, k, t_m, t_n, inv_cnt, inv_list);
+    }
   }
-  hipLaunchKernelGGL(invert_index_kernel, dim3((t_n + 3) / 4, c.batch * c.heads), dim3(256), 0, s, idx, k, t_m, t_n,
-                     inv_cnt, inv_list);
-  return check_launch("hf_hybrid_attn_bwd(inverse lists)");
+  if (state) {
+    p.plane_wgs = 8 * BH;
+    p.state = state;
+    p.planes = static_cast<bf16_t*>(planes);
+    if (lds < 2 * 32 * 33 * sizeof(float)) lds = 2 * 32 * 33 * sizeof(float);
+  }
+  long long dot_wgs = 0;
+  if (A) {
+    if (rows > (1ll << 34)) { set_error("too many rows"); return HF_ERR_SHAPE; }
+    p.A = static_cast<const bf16_t*>(A);
+    p.B = static_cast<const bf16_t*>(B);
+    p.rows = rows;
+    p.dots = dots;
+    dot_wgs = (rows + kPrepThreads / 16 - 1) / (kPrepThreads / 16);
+  }
+  const long long wgs = p.order_wgs + p.invert_wgs + p.plane_wgs + dot_wgs;
+  if (lds > 64 * 1024) {
+    static LdsGrant grant;
+    const int rc = grant_lds(grant, reinterpret_cast<const void*>(bwd_prep_kernel), 150 * 1024, "the backward pass's preparation");
+    if (rc != HF_OK) return rc;
+  }
+  if (wgs) hipLaunchKernelGGL(bwd_prep_kernel, dim3((unsigned)wgs), dim3(kPrepThreads), lds, s, p);
+  return check_launch("hf_hybrid_attn_bwd(lists, planes, D)");
 }
 
 // dQ (with the history branch where a state is given), then dK and dV.  32 rows or keys per workgroup, 16 where a block has
@@ -631,36 +812,6 @@ int launch_bwd_generic(const hf_config& c, const void* Q, const void* Q_hist, in
     if (rc != HF_OK) return rc;
   }
   return HF_OK;
-}
-
-// out[row] = A[row] . B[row] over head_dim features (bf16 storage, fp32 arithmetic): D = dO . O_local from a
-// saved O_local.  16 lanes per row, 16 bytes per lane and tensor.
-__global__ __launch_bounds__(256) void row_dot_kernel(const bf16_t* __restrict__ A, const bf16_t* __restrict__ B,
-                                                      long long rows, float* __restrict__ out) {
-  const long long row = (long long)blockIdx.x * 16 + (threadIdx.x >> 4);
-  const int part = threadIdx.x & 15;
-  float acc = 0.0f;
-  if (row < rows) {
-    const uint4 a = *reinterpret_cast<const uint4*>(A + row * 128 + part * 8);
-    const uint4 b = *reinterpret_cast<const uint4*>(B + row * 128 + part * 8);
-    const uint32_t aw[4] = {a.x, a.y, a.z, a.w}, bw[4] = {b.x, b.y, b.z, b.w};
-#pragma unroll
-    for (int i = 0; i < 4; ++i) {
-      acc = fmaf(__uint_as_float(aw[i] << 16), __uint_as_float(bw[i] << 16), acc);
-      acc = fmaf(__uint_as_float(aw[i] & 0xffff0000u), __uint_as_float(bw[i] & 0xffff0000u), acc);
-    }
-  }
-#pragma unroll
-  for (int off = 8; off >= 1; off >>= 1) acc += __shfl_xor(acc, off, 16);
-  if (row < rows && part == 0) out[row] = acc;
-}
-
-int launch_row_dot(const hf_config& c, const void* A, const void* B, long long rows, float* out, hipStream_t s) {
-  if (c.dtype != HF_BF16 || c.head_dim != 128) { set_error("row dot: bf16, head_dim 128 only"); return HF_ERR_SHAPE; }
-  if (rows > (1ll << 34)) { set_error("too many rows"); return HF_ERR_SHAPE; }
-  hipLaunchKernelGGL(row_dot_kernel, dim3((unsigned)((rows + 15) / 16)), dim3(256), 0, s,
-                     static_cast<const bf16_t*>(A), static_cast<const bf16_t*>(B), rows, out);
-  return check_launch("hf_hybrid_attn_bwd_saved(D)");
 }
 
 }  // namespace hf

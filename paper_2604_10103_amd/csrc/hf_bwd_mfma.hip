@@ -175,24 +175,6 @@ struct BwdHist {
   int phi_kind;
 };
 
-// fp32 state -> the two bf16 planes of the backward pass: Lt (transposed) and L
-__global__ __launch_bounds__(256) void state_planes_bwd_kernel(const float* __restrict__ state,
-                                                               bf16_t* __restrict__ planes) {
-  __shared__ float tile[32][33];
-  const int bh = blockIdx.z, i0 = blockIdx.y * 32, j0 = blockIdx.x * 32;
-  const float* L = state + (size_t)bh * D * D;
-  const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;  // 32 x 8
-  bf16_t* lt = planes + (size_t)bh * 2 * D * D;
-  bf16_t* ln = lt + D * D;
-  for (int r = ty; r < 32; r += 8) {
-    const float v = L[(size_t)(i0 + r) * D + j0 + tx];
-    tile[r][tx] = v;
-    ln[(size_t)(i0 + r) * D + j0 + tx] = f32_to_bf16(v);
-  }
-  __syncthreads();
-  for (int r = ty; r < 32; r += 8) lt[(size_t)(j0 + r) * D + i0 + tx] = f32_to_bf16(tile[tx][r]);
-}
-
 // acc += A B with the accumulator pinned to the accumulation half of the register file (the compiler, left to
 // itself, keeps such accumulators in ordinary registers and shuttles others through that half).  The compiler
 // counts no wait states for inline assembly, so they are provided here: A comes from LDS reads, which it awaits as
@@ -623,63 +605,6 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(1, 1)))
 }
 
 // ------------------------------------------------------------------------------------------ dK, dV
-// Launch order of the dK/dV workgroups.  A workgroup's time is proportional to the length of its KV block's list
-// of query blocks, and the lists differ (top-k selection: a binomial spread around t_m k / t_n), while a GPU takes
-// workgroups in index order as slots free up.  Longest first within every XCD's share of the items leaves the short
-// ones to fill the end.  The kernel writes one record of 8 words per place: the item that runs there (rank by list
-// length descending, item ascending, found by counting), the length of its list and the list's first three entries,
-// so that a workgroup has all it needs for its first tiles after ONE dependent load (a workgroup is alone on its
-// two SIMDs: every round trip to memory before its first MFMA is idle time).
-// One workgroup per share; the share's keys sit in LDS.
-constexpr int kOrderMax = 4096;   // items per share this kernel takes (4 per thread, 2 x 16 KB of LDS)
-constexpr int kOrderRec = 8;      // words per record
-__global__ __launch_bounds__(1024) void dkv_order_kernel(const int32_t* __restrict__ inv_cnt,
-                                                          const int32_t* __restrict__ inv_list, int t_m, int slabs,
-                                                          int items_per_xcd, int total_items,
-                                                          int32_t* __restrict__ order) {
-  __shared__ int32_t key[kOrderMax], rank[kOrderMax];
-  const int first = blockIdx.x * items_per_xcd;
-  const int n = max(0, min(items_per_xcd, total_items - first));
-  // a thread per item: list length and first entries, all loads in flight together
-  int4 head[kOrderMax / 1024];
-#pragma unroll
-  for (int q = 0; q < kOrderMax / 1024; ++q) {
-    const int j = threadIdx.x + 1024 * q;
-    if (j < n) {
-      const int kvb = (first + j) / slabs;
-      const int32_t* list = inv_list + (size_t)kvb * t_m;
-      head[q] = int4{inv_cnt[kvb], list[0], list[min(1, t_m - 1)], list[min(2, t_m - 1)]};
-      key[j] = head[q].x;
-      rank[j] = 0;
-    }
-  }
-  __syncthreads();
-  // the n x n comparisons spread over all threads: `per` threads share an item, each takes every per-th key and
-  // adds its count to the item's rank
-  int per = 1;
-  while (per < 64 && 2 * per * n <= 1024) per *= 2;
-  const int sub = threadIdx.x & (per - 1);
-  for (int j = threadIdx.x / per; j < n; j += 1024 / per) {
-    const int mine = key[j];
-    int before = 0;
-    for (int i = sub; i < n; i += per) {
-      const int other = key[i];
-      before += (other > mine || (other == mine && i < j)) ? 1 : 0;
-    }
-    atomicAdd(&rank[j], before);
-  }
-  __syncthreads();
-#pragma unroll
-  for (int q = 0; q < kOrderMax / 1024; ++q) {
-    const int j = threadIdx.x + 1024 * q;
-    if (j < n) {
-      int4* rec = reinterpret_cast<int4*>(order + (size_t)(first + rank[j]) * kOrderRec);
-      rec[0] = int4{first + j, head[q].x, head[q].y, head[q].z};
-      rec[1] = int4{head[q].w, 0, 0, 0};
-    }
-  }
-}
-
 // One workgroup per slab of 64 keys of a KV block, two wavefronts of 32 keys each; a wavefront owns all 128
 // features of dK and dV of its keys: 128 accumulator registers that only MFMAs touch until the end, which is what
 // the second half of the register file (one wavefront per SIMD: 512 registers) is for.  Per tile of 32 query rows
@@ -1002,11 +927,12 @@ size_t bwd_planes_bytes(const hf_config& c) {
   return bwd_mfma_supported(c) ? (size_t)c.batch * c.heads * 2 * D * D * sizeof(bf16_t) : 0;
 }
 
+// order NULL (equal lists, or shares too long for the ordering): the dK/dV items run in index order.
 // state == NULL: no history branch.  Q_hist != Q: its gradient goes to dQ_hist, else it joins dQ.
 int launch_bwd_mfma(const hf_config& c, const void* Q, int n_q, const void* K, const void* V, int n_kv,
                     const int32_t* idx, int k, const void* dO, const float* lse2, const float* Dv,
-                    const int32_t* inv_cnt, const int32_t* inv_list, int32_t* dkv_order, const float* state,
-                    const float* cosq, const float* sinq, const void* Q_hist, void* planes, void* dQ, void* dQ_hist,
+                    const int32_t* inv_cnt, const int32_t* inv_list, const int32_t* order, const float* state,
+                    const float* cosq, const float* sinq, const void* Q_hist, const void* planes, void* dQ, void* dQ_hist,
                     void* dK, void* dV, hipStream_t s) {
   if (n_kv >= (1 << 23) || n_q >= (1 << 23)) { set_error("more than 2^23 tokens"); return HF_ERR_SHAPE; }
   const int BH = c.batch * c.heads;
@@ -1021,8 +947,6 @@ int launch_bwd_mfma(const hf_config& c, const void* Q, int n_q, const void* K, c
   const int hist_mode = !state ? 0 : (Q_hist != Q ? 2 : 1);
   BwdHist hist = {};
   if (hist_mode) {
-    hipLaunchKernelGGL(state_planes_bwd_kernel, dim3(D / 32, D / 32, BH), dim3(256), 0, s, state,
-                       static_cast<bf16_t*>(planes));
     hist.planes = static_cast<const bf16_t*>(planes);
     hist.zvec = state + (size_t)BH * D * D;
     hist.cosq = cosq;
@@ -1064,12 +988,6 @@ int launch_bwd_mfma(const hf_config& c, const void* Q, int n_q, const void* K, c
   static LdsGrant dkv_grant;
   const int rc_dkv = grant_lds(dkv_grant, reinterpret_cast<const void*>(bwd_dkv_mfma_kernel), kDkvLds, "the dK/dV kernel");
   if (rc_dkv != HF_OK) return rc_dkv;
-  const int32_t* order = nullptr;   // equal lists (dense), or a share too long for the ordering kernel: index order
-  if (inv_cnt && dkv_order && kv_per_xcd <= kOrderMax && !(c.flags & HF_FLAG_DKV_INDEX_ORDER)) {
-    hipLaunchKernelGGL(dkv_order_kernel, dim3(8), dim3(1024), 0, s, inv_cnt, inv_list, t_m, slabs, kv_per_xcd,
-                       (int)kv_items, dkv_order);
-    order = dkv_order;
-  }
   hipLaunchKernelGGL(bwd_dkv_mfma_kernel, dim3(8 * kv_per_xcd), dim3(128), kDkvLds, s, q, kk, v, g, inv_cnt, inv_list, n_q,
                      n_kv, kvs, c.block_q, c.block_kv, t_m, t_n, slabs, kv_per_xcd, (int)kv_items, order, c_scale, scale,
                      lse2, Dv, static_cast<bf16_t*>(dK), static_cast<bf16_t*>(dV));

@@ -144,16 +144,18 @@ int launch_attn_wide_stats(const hf_config& c, const void* Q, int n_q, const voi
                            const int32_t* idx, int k, const void* dO, float* lse2, float* dvec, hipStream_t s);
 int launch_attn_mfma_stats(const hf_config& c, const void* Q, int n_q, const void* K, const void* V, int n_kv,
                            const int32_t* idx, int k, const void* dO, float* lse2, float* dvec, hipStream_t s);
-int launch_row_dot(const hf_config& c, const void* A, const void* B, long long rows, float* out, hipStream_t s);
 bool bwd_mfma_supported(const hf_config& c);
 size_t bwd_planes_bytes(const hf_config& c);
 int launch_bwd_mfma(const hf_config& c, const void* Q, int n_q, const void* K, const void* V, int n_kv,
                     const int32_t* idx, int k, const void* dO, const float* lse2, const float* Dv,
-                    const int32_t* inv_cnt, const int32_t* inv_list, int32_t* dkv_order, const float* state,
-                    const float* cosq, const float* sinq, const void* Q_hist, void* planes, void* dQ, void* dQ_hist,
+                    const int32_t* inv_cnt, const int32_t* inv_list, const int32_t* order, const float* state,
+                    const float* cosq, const float* sinq, const void* Q_hist, const void* planes, void* dQ, void* dQ_hist,
                     void* dK, void* dV, hipStream_t s);
-int launch_invert_index(const hf_config& c, const int32_t* idx, int k, int t_m, int t_n, int32_t* inv_cnt,
-                        int32_t* inv_list, hipStream_t s);
+// inverse lists, launch order of the dK/dV items, bf16 planes of the state, row dots: what is asked for, in one launch
+constexpr int kOrderRec = 8;   // words per record of the launch order
+int launch_bwd_prep(const hf_config& c, const int32_t* idx, int k, int t_m, int t_n, int32_t* inv_cnt, int32_t* inv_list,
+                    int32_t** order_inout, const float* state, void* planes, const void* A, const void* B, long long rows,
+                    float* dots, hipStream_t s);
 int launch_bwd_generic(const hf_config& c, const void* Q, const void* Q_hist, int n_q, const void* K, const void* V, int n_kv,
                        const int32_t* idx, int k, const void* dO, const float* lse2, const float* Dv,
                        const int32_t* inv_cnt, const int32_t* inv_list, const float* state, const float* cosq,
