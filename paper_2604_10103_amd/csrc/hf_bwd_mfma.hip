@@ -220,16 +220,16 @@ __device__ __forceinline__ void mfma_acc_piece(f32x16& acc, const bf16x8 a, cons
 // to be masked (they are keys of the next block).
 constexpr int kDqSlots = 4;   // tiles in LDS: K and V each
 constexpr int kDqLds = kDqSlots * 2 * RTILE;
-template <int NW, int kHist, bool kRagged>
-__global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(1, 1))) void bwd_dq_mfma_kernel(
-    const bf16_t* __restrict__ Q, const bf16_t* __restrict__ K, const bf16_t* __restrict__ V,
-    const bf16_t* __restrict__ dO, const int32_t* __restrict__ idx, int k, int n_q, int n_kv, int kv_stride, int bkv,
+template <int kHist, bool kRagged>
+__device__ __forceinline__ void dq_rows(
+    char* smem, const int wg, const bf16_t* __restrict__ Q, const bf16_t* __restrict__ K, const bf16_t* __restrict__ V,
+    const bf16_t* __restrict__ dO, const int32_t* __restrict__ idx, int k, int n_q, int n_kv, int kv_stride, int bq, int bkv,
     int t_m, int t_n, int items_per_xcd, int total_items, float c_scale, float scale,
-    const float* __restrict__ lse2, const float* __restrict__ Dv, BwdHist hist, bf16_t* __restrict__ dQ) {
+    const float* __restrict__ lse2, const float* __restrict__ Dv, const BwdHist& hist, bf16_t* __restrict__ dQ) {
+  constexpr int NW = 2;
   constexpr int NT = 64 * NW;
   constexpr int BQ = 32 * NW;
-  constexpr int NSLOT = kDqSlots;
-  extern __shared__ __attribute__((aligned(16))) char smem[];   // kDqLds bytes: K and V per slot; a state plane later
+  constexpr int NSLOT = kDqSlots;   // smem: K and V per slot; a state plane later
   static_assert(4 * RTILE <= kDqLds, "a state plane (four pieces of 32 rows) must fit in the tiles' space");
   char* const sK = smem;
   char* const sV = smem + NSLOT * RTILE;
@@ -237,10 +237,13 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(1, 1)))
 
   // consecutive workgroup ids go to consecutive XCDs: every XCD gets one contiguous run of (head, query
   // block) items, so that its L2 holds the keys and values of few heads
-  const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
+  const int xcd = wg & 7, slot = wg >> 3;
   const int item = xcd * items_per_xcd + slot;
   if (slot >= items_per_xcd || item >= total_items) return;
-  const int bh = item / t_m, qb = item - bh * t_m;
+  const int chunks = bq / BQ;   // 64-row workgroups per query block
+  const int bh = item / (t_m * chunks), in_head = item - bh * (t_m * chunks);
+  const int qb = in_head / chunks, row0 = qb * bq + BQ * (in_head - qb * chunks);
+  if (row0 >= n_q) return;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int l32 = lane & 31, h = lane >> 5;
@@ -255,7 +258,7 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(1, 1)))
   const int nsel = idx ? k : t_n;
   const int subs = (bkv + TT - 1) / TT;
 
-  const int q_row = qb * BQ + 32 * wave + l32;   // rows past n_q read zeros and are not stored
+  const int q_row = row0 + 32 * wave + l32;   // rows past n_q read zeros and are not stored
   bf16x8 qf[8], dof[8];
   row_frags(q_rsrc, q_row, h, qf);
   row_frags(do_rsrc, q_row, h, dof);
@@ -597,8 +600,8 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(1, 1)))
 #pragma unroll
     for (int i = 0; i < (BQ * 16) / NT; ++i) {
       const int c = tid + NT * i, row = c >> 4, col = c & 15;
-      if (qb * BQ + row < n_q)
-        *reinterpret_cast<uint4*>(out + (size_t)(qb * BQ + row) * D + col * 8) =
+      if (row0 + row < n_q)
+        *reinterpret_cast<uint4*>(out + (size_t)(row0 + row) * D + col * 8) =
             *reinterpret_cast<const uint4*>(smem + row * OSTR + col * 16);
     }
   }
@@ -611,22 +614,22 @@ __global__ __launch_bounds__(64 * NW) __attribute__((amdgpu_waves_per_eu(1, 1)))
 // a wavefront issues 16 MFMAs for S and dP and 16 for dV and dK, nothing is computed twice.
 constexpr int kDkvSlots = 4;   // tiles in LDS: one in use, three on their way
 constexpr int kDkvLds = kDkvSlots * (2 * RTILE + 512);
-__global__ __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(1, 1))) void bwd_dkv_mfma_kernel(
-    const bf16_t* __restrict__ Q, const bf16_t* __restrict__ K, const bf16_t* __restrict__ V,
+__device__ __forceinline__ void dkv_keys(
+    char* smem, const int wg, const bf16_t* __restrict__ Q, const bf16_t* __restrict__ K, const bf16_t* __restrict__ V,
     const bf16_t* __restrict__ dO, const int32_t* __restrict__ inv_cnt, const int32_t* __restrict__ inv_list,
     int n_q, int n_kv, int kv_stride, int bq, int bkv, int t_m, int t_n, int slabs, int items_per_xcd,
     int total_items, const int32_t* __restrict__ order, float c_scale, float scale,
     const float* __restrict__ lse2, const float* __restrict__ Dv, bf16_t* __restrict__ dK, bf16_t* __restrict__ dV) {
   constexpr int NT = 128;
   constexpr int NSLOT = kDkvSlots;
-  extern __shared__ __attribute__((aligned(16))) char smem[];   // kDkvLds bytes: Q, dO, row statistics per slot
+  // smem: Q, dO, row statistics per slot
   char* const sQ = smem;
   char* const sdO = smem + NSLOT * RTILE;
   float* const sStat = reinterpret_cast<float*>(smem + 2 * NSLOT * RTILE);   // per slot: lse2[32] twice, D[32] twice
   static_assert(64 * OSTR <= 2 * NSLOT * RTILE, "staged output must fit");
 
   // XCD-aware placement as in the dQ kernel: an XCD's L2 then holds the queries and output gradients of few heads
-  const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
+  const int xcd = wg & 7, slot = wg >> 3;
   const int place = xcd * items_per_xcd + slot;   // the slot-th workgroup of this XCD's share, longest lists first
   if (slot >= items_per_xcd || place >= total_items) return;
   // the record of this place: item, list length, first three list entries (no record: index order, entries loaded)
@@ -917,6 +920,39 @@ __global__ __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(1, 1))) voi
   }
 }
 
+// ------------------------------------------------------------------------------------------ one launch for both
+// dQ's and dK/dV's workgroups are independent, have the same size and sit two to a compute unit, so they share a launch: dQ's
+// first (equally long), then dK/dV's, longest first, in the slots as they come free.  On their own dQ's 888 workgroups leave
+// a quarter of the chip idle in their second round at 832x480, and a small problem runs both for its latency.
+// block_q 128: two workgroups of 64 rows per query block, each with the block's list.
+struct BwdOperands {
+  const bf16_t *Q, *K, *V, *dO;
+  int n_q, n_kv, kv_stride, bq, bkv, t_m, t_n;
+  float c_scale, scale;
+  const float *lse2, *Dv;
+  // dQ
+  const int32_t* idx;
+  int k, q_per_xcd, q_items;
+  bf16_t* dQ;
+  // dK, dV
+  const int32_t *inv_cnt, *inv_list, *order;
+  int slabs, kv_per_xcd, kv_items;
+  bf16_t *dK, *dV;
+};
+constexpr int kBwdLds = kDqLds > kDkvLds ? kDqLds : kDkvLds;
+
+template <int kHist, bool kRagged>
+__global__ __launch_bounds__(128) __attribute__((amdgpu_waves_per_eu(1, 1))) void bwd_mfma_kernel(BwdOperands p, BwdHist hist) {
+  extern __shared__ __attribute__((aligned(16))) char smem[];   // kBwdLds bytes
+  const int wg = blockIdx.x, dq_wgs = 8 * p.q_per_xcd;          // (a multiple of eight: the XCD of a number stays the same)
+  if (wg < dq_wgs)
+    dq_rows<kHist, kRagged>(smem, wg, p.Q, p.K, p.V, p.dO, p.idx, p.k, p.n_q, p.n_kv, p.kv_stride, p.bq, p.bkv, p.t_m, p.t_n,
+                            p.q_per_xcd, p.q_items, p.c_scale, p.scale, p.lse2, p.Dv, hist, p.dQ);
+  else
+    dkv_keys(smem, wg - dq_wgs, p.Q, p.K, p.V, p.dO, p.inv_cnt, p.inv_list, p.n_q, p.n_kv, p.kv_stride, p.bq, p.bkv, p.t_m, p.t_n,
+             p.slabs, p.kv_per_xcd, p.kv_items, p.order, p.c_scale, p.scale, p.lse2, p.Dv, p.dK, p.dV);
+}
+
 }  // namespace
 
 bool bwd_mfma_supported(const hf_config& c) {
@@ -940,10 +976,6 @@ int launch_bwd_mfma(const hf_config& c, const void* Q, int n_q, const void* K, c
   const float scale = c.softmax_scale > 0.0f ? c.softmax_scale : 1.0f / sqrtf((float)c.head_dim);
   const float c_scale = scale * 1.4426950408889634f;
   const int kvs = kv_stride_of(c, n_kv);
-  const bf16_t* q = static_cast<const bf16_t*>(Q);
-  const bf16_t* kk = static_cast<const bf16_t*>(K);
-  const bf16_t* v = static_cast<const bf16_t*>(V);
-  const bf16_t* g = static_cast<const bf16_t*>(dO);
   const int hist_mode = !state ? 0 : (Q_hist != Q ? 2 : 1);
   BwdHist hist = {};
   if (hist_mode) {
@@ -957,41 +989,29 @@ int launch_bwd_mfma(const hf_config& c, const void* Q, int n_q, const void* K, c
     hist.z_scale = c.z_scale;
     hist.phi_kind = c.phi;
   }
-  const long long q_items = (long long)BH * t_m;
-  if (q_items > (1ll << 30)) { set_error("too many query blocks"); return HF_ERR_SHAPE; }
-  const int q_per_xcd = (int)((q_items + 7) / 8);
+  const int slabs = (c.block_kv + 63) / 64;   // 64 keys per dK/dV workgroup, 64 rows per dQ workgroup
+  const long long q_items = (long long)BH * t_m * (c.block_q / 64), kv_items = (long long)BH * t_n * slabs;
+  if (q_items > (1ll << 29) || kv_items > (1ll << 29)) { set_error("too many blocks"); return HF_ERR_SHAPE; }
+  BwdOperands p = {static_cast<const bf16_t*>(Q), static_cast<const bf16_t*>(K), static_cast<const bf16_t*>(V),
+                   static_cast<const bf16_t*>(dO), n_q, n_kv, kvs, c.block_q, c.block_kv, t_m, t_n, c_scale, scale, lse2, Dv,
+                   idx, k, (int)((q_items + 7) / 8), (int)q_items, static_cast<bf16_t*>(dQ),
+                   inv_cnt, inv_list, order, slabs, (int)((kv_items + 7) / 8), (int)kv_items, static_cast<bf16_t*>(dK),
+                   static_cast<bf16_t*>(dV)};
   // more than 64 KB of LDS has to be granted per kernel instance, once
-#define HF_LAUNCH_DQ3(NWV, HM, RG)                                                                                  \
-  do {                                                                                                             \
-    static LdsGrant grant;                                                                                         \
-    const int rc_grant = grant_lds(grant, reinterpret_cast<const void*>(bwd_dq_mfma_kernel<NWV, HM, RG>), kDqLds,  \
-                                   "the dQ kernel");                                                               \
-    if (rc_grant != HF_OK) return rc_grant;                                                                        \
-    hipLaunchKernelGGL((bwd_dq_mfma_kernel<NWV, HM, RG>), dim3(8 * q_per_xcd), dim3(64 * NWV), kDqLds, s, q, kk, v, \
-                       g, idx, k, n_q, n_kv, kvs, c.block_kv, t_m, t_n, q_per_xcd, (int)q_items, c_scale, scale,    \
-                       lse2, Dv, hist, static_cast<bf16_t*>(dQ));                                                  \
+#define HF_LAUNCH_BWD(HM, RG)                                                                                         \
+  do {                                                                                                                \
+    static LdsGrant grant;                                                                                            \
+    const int rc = grant_lds(grant, reinterpret_cast<const void*>(bwd_mfma_kernel<HM, RG>), kBwdLds, "the gradient kernel"); \
+    if (rc != HF_OK) return rc;                                                                                       \
+    hipLaunchKernelGGL((bwd_mfma_kernel<HM, RG>), dim3(8 * (p.q_per_xcd + p.kv_per_xcd)), dim3(128), kBwdLds, s, p, hist);   \
   } while (0)
-#define HF_LAUNCH_DQ(NWV, HM) do { if (c.block_kv % 32) HF_LAUNCH_DQ3(NWV, HM, true); else HF_LAUNCH_DQ3(NWV, HM, false); } while (0)
-  if (c.block_q == 64) {
-    if (hist_mode == 0) HF_LAUNCH_DQ(2, 0); else if (hist_mode == 1) HF_LAUNCH_DQ(2, 1); else HF_LAUNCH_DQ(2, 2);
+  if (c.block_kv % 32) {
+    if (hist_mode == 0) HF_LAUNCH_BWD(0, true); else if (hist_mode == 1) HF_LAUNCH_BWD(1, true); else HF_LAUNCH_BWD(2, true);
   } else {
-    if (hist_mode == 0) HF_LAUNCH_DQ(4, 0); else if (hist_mode == 1) HF_LAUNCH_DQ(4, 1); else HF_LAUNCH_DQ(4, 2);
+    if (hist_mode == 0) HF_LAUNCH_BWD(0, false); else if (hist_mode == 1) HF_LAUNCH_BWD(1, false); else HF_LAUNCH_BWD(2, false);
   }
-#undef HF_LAUNCH_DQ
-#undef HF_LAUNCH_DQ3
-  int rc = check_launch("hf_hybrid_attn_bwd(dQ)");
-  if (rc != HF_OK) return rc;
-  const int slabs = (c.block_kv + 63) / 64;   // 64 keys per workgroup
-  const long long kv_items = (long long)BH * t_n * slabs;
-  if (kv_items > (1ll << 30)) { set_error("too many KV slabs"); return HF_ERR_SHAPE; }
-  const int kv_per_xcd = (int)((kv_items + 7) / 8);
-  static LdsGrant dkv_grant;
-  const int rc_dkv = grant_lds(dkv_grant, reinterpret_cast<const void*>(bwd_dkv_mfma_kernel), kDkvLds, "the dK/dV kernel");
-  if (rc_dkv != HF_OK) return rc_dkv;
-  hipLaunchKernelGGL(bwd_dkv_mfma_kernel, dim3(8 * kv_per_xcd), dim3(128), kDkvLds, s, q, kk, v, g, inv_cnt, inv_list, n_q,
-                     n_kv, kvs, c.block_q, c.block_kv, t_m, t_n, slabs, kv_per_xcd, (int)kv_items, order, c_scale, scale,
-                     lse2, Dv, static_cast<bf16_t*>(dK), static_cast<bf16_t*>(dV));
-  return check_launch("hf_hybrid_attn_bwd(dK, dV)");
+#undef HF_LAUNCH_BWD
+  return check_launch("hf_hybrid_attn_bwd(dQ, dK, dV)");
 }
 
 }  // namespace hf
