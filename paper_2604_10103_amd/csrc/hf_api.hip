@@ -1020,17 +1020,9 @@ int hf_ring_last_step(const hf_config* cfg, hf_ring* ring, const void* Q, const 
   } else {
     HF_TRY(hf_ring_step(cfg, ring, Q, Q_hist, K_cache, V_cache, step_in_chunk, block_idx, state_or_null, rope_cos_q,
                         rope_sin_q, O, workspace, workspace_bytes, stream));
-    // the state is copied and the chunk absorbed into the copy, behind the step
-    if (state_or_null) {
-      if (hipMemcpyAsync(state_out, state_or_null, state_bytes, hipMemcpyDeviceToDevice, s) != hipSuccess) {
-        set_error("copy of the state: %s", hipGetErrorString(hipGetLastError()));
-        return HF_ERR_HIP;
-      }
-    } else {
-      HF_TRY(launch_fill_zero(static_cast<float*>(state_out), bh * (d * d + d), s));
-    }
-    HF_TRY(launch_absorb(*cfg, static_cast<float*>(state_out), K_ev, V_ev, ring->n_chunk, cfg->kv_capacity, rope_cos_ev,
-                         rope_sin_ev, step_workspace, step_workspace ? step_workspace_bytes : 0, s));
+    HF_TRY(launch_absorb_into(*cfg, static_cast<const float*>(state_or_null), static_cast<float*>(state_out), K_ev, V_ev,
+                              ring->n_chunk, cfg->kv_capacity, rope_cos_ev, rope_sin_ev, step_workspace,
+                              step_workspace ? step_workspace_bytes : 0, s));
   }
   ring->absorbed_ahead = 1;
   if (absorbed_out) *absorbed_out = 1;

@@ -119,6 +119,9 @@ int launch_readout_mfma(const hf_config& c, const void* Q, int n_q, const void* 
                         const float* cosq, const float* sinq, void* planes, void* O, hipStream_t s);
 size_t readout_planes_bytes(const hf_config& c);  // scratch for the bf16 planes of the state
 int launch_state_planes(const hf_config& c, const float* state, void* planes, hipStream_t s);
+int launch_absorb_into(const hf_config& c, const float* state_in, float* state_out, const void* K, const void* V, int n,
+                       int head_stride, const float* cosv, const float* sinv, void* workspace, size_t workspace_bytes,
+                       hipStream_t s);
 bool attn_mfma_fused_supported(const hf_config& c);
 int launch_attn_mfma_fused(const hf_config& c, const void* Q, int n_q, const void* K, const void* V, int n_kv,
                            const int32_t* idx, int k, const void* planes, const float* zvec, const float* cosq,
