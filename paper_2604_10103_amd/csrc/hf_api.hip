@@ -791,14 +791,14 @@ static int step_one_launch(const hf_config* cfg, const void* Q, const void* Q_hi
   char* ws = static_cast<char*>(workspace);
   float* kbar = reinterpret_cast<float*>(ws + w.kbar);
   hipStream_t s = static_cast<hipStream_t>(stream);
-  if (kv_end > kv_first)
-    HF_TRY(launch_pool_both(*cfg, nullptr, 0, 0, K, n_kv, t_n, kv_first, kv_end, nullptr, kbar, s));
+  // the state is frozen during a chunk's denoising steps: its planes are converted on the first and stay in the workspace
+  const float* fresh = step_in_chunk == 0 ? static_cast<const float*>(state_or_null) : nullptr;
+  if (kv_end > kv_first || fresh)
+    HF_TRY(launch_pool_both(*cfg, nullptr, 0, 0, K, n_kv, t_n, kv_first, kv_end, nullptr, kbar, s, fresh, ws + w.planes));
   *done = true;
   if (!state_or_null) return launch_attn_mfma_select(*cfg, Q, n_q, K, V, n_kv, k, kbar, block_idx, nullptr, O, s);
   const float* st = static_cast<const float*>(state_or_null);
   const size_t d = cfg->head_dim;
-  // the state is frozen during a chunk's denoising steps: its planes are converted on the first and stay here
-  if (step_in_chunk == 0) HF_TRY(launch_state_planes(*cfg, st, ws + w.planes, s));
   return launch_attn_mfma_fused(*cfg, Q, n_q, K, V, n_kv, nullptr, k, ws + w.planes,
                                 st + (size_t)cfg->batch * cfg->heads * d * d, rope_cos_q, rope_sin_q, Q_hist, O, s, nullptr,
                                 nullptr, kbar, block_idx, nullptr);
@@ -1011,9 +1011,8 @@ int hf_ring_last_step(const hf_config* cfg, hf_ring* ring, const void* Q, const 
       set_error("step_workspace of %zu bytes needed, %zu given", need, step_workspace ? step_workspace_bytes : (size_t)0);
       return HF_ERR_WORKSPACE;
     }
-    HF_TRY(launch_pool_both(*cfg, nullptr, 0, 0, K_cache, n_kv, t_n, kv_first, kv_end, nullptr, kbar, s));
-    if (state_or_null && step_in_chunk == 0)
-      HF_TRY(launch_state_planes(*cfg, static_cast<const float*>(state_or_null), ws + w.planes, s));
+    HF_TRY(launch_pool_both(*cfg, nullptr, 0, 0, K_cache, n_kv, t_n, kv_first, kv_end, nullptr, kbar, s,
+                            step_in_chunk == 0 ? static_cast<const float*>(state_or_null) : nullptr, ws + w.planes));
     HF_TRY(select_attn_impl(cfg, Q, Q_hist, n_q, K_cache, V_cache, n_kv, kbar, state_or_null,
                             state_or_null ? ws + w.planes : nullptr, rope_cos_q, rope_sin_q, O, block_idx, nullptr, K_ev, V_ev,
                             ring->n_chunk, cfg->kv_capacity, state_out, nullptr, step_workspace, step_workspace_bytes, stream));

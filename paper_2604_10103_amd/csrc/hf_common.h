@@ -70,6 +70,24 @@ __device__ __forceinline__ float wave_sum(float v) {
   return v;
 }
 
+// head_dim 128: one 32 x 32 tile of a head's state L[i][j] fp32 -> planes hi/lo, transposed: Lt[plane][j][i] bf16.  256 threads
+__device__ __forceinline__ void state_planes_tile(const float* __restrict__ state, bf16_t* __restrict__ planes, int bh, int i0,
+                                                  int j0, float (*tile)[33]) {
+  constexpr int D = 128;
+  const float* L = state + (size_t)bh * D * D;
+  const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;  // 32 x 8
+  for (int r = ty; r < 32; r += 8) tile[r][tx] = L[(size_t)(i0 + r) * D + j0 + tx];
+  __syncthreads();
+  bf16_t* hi = planes + (size_t)bh * 2 * D * D;
+  bf16_t* lo = hi + D * D;
+  for (int r = ty; r < 32; r += 8) {
+    const float v = tile[tx][r];  // i = i0 + tx, j = j0 + r
+    const bf16_t h = f32_to_bf16(v);
+    hi[(size_t)(j0 + r) * D + i0 + tx] = h;
+    lo[(size_t)(j0 + r) * D + i0 + tx] = f32_to_bf16(v - bf16_to_f32(h));
+  }
+}
+
 // ---- host side -------------------------------------------------------------------------
 void set_error(const char* fmt, ...);
 int check_launch(const char* what);
@@ -101,11 +119,16 @@ int launch_fold_linear(const hf_config& c, const float* state_in, const float* W
 int launch_absorb(const hf_config& c, float* state, const void* K, const void* V, int n, int head_stride,
                   const float* cosv, const float* sinv, void* workspace, size_t workspace_bytes,
                   hipStream_t s, void* planes_out = nullptr);
+int launch_absorb_into(const hf_config& c, const float* state_in, float* state_out, const void* K, const void* V, int n,
+                       int head_stride, const float* cosv, const float* sinv, void* workspace, size_t workspace_bytes,
+                       hipStream_t s);
 int launch_window_shift(const hf_config& c, void* K, void* V, int n_kv, int first, int n_evict, hipStream_t s);
 size_t absorb_workspace_bytes(const hf_config& c, int n);
 // pools every query block and the KV blocks [kv_first, kv_end); the other KV blocks keep what kbar_t holds
+// state given (bf16, head_dim 128): its bf16 planes in the same launch
 int launch_pool_both(const hf_config& c, const void* Q, int n_q, int t_m, const void* K, int n_kv, int t_n,
-                     int kv_first, int kv_end, float* qbar, float* kbar_t, hipStream_t s);
+                     int kv_first, int kv_end, float* qbar, float* kbar_t, hipStream_t s, const float* state = nullptr,
+                     void* planes = nullptr);
 int launch_score_select(const hf_config& c, const float* qbar, const float* kbar_t, int t_m, int t_n,
                         int k, int32_t* idx, float* scores, hipStream_t s);
 int launch_attn(const hf_config& c, const void* Q, int n_q, const void* K, const void* V, int n_kv,
@@ -119,9 +142,6 @@ int launch_readout_mfma(const hf_config& c, const void* Q, int n_q, const void* 
                         const float* cosq, const float* sinq, void* planes, void* O, hipStream_t s);
 size_t readout_planes_bytes(const hf_config& c);  // scratch for the bf16 planes of the state
 int launch_state_planes(const hf_config& c, const float* state, void* planes, hipStream_t s);
-int launch_absorb_into(const hf_config& c, const float* state_in, float* state_out, const void* K, const void* V, int n,
-                       int head_stride, const float* cosv, const float* sinv, void* workspace, size_t workspace_bytes,
-                       hipStream_t s);
 bool attn_mfma_fused_supported(const hf_config& c);
 int launch_attn_mfma_fused(const hf_config& c, const void* Q, int n_q, const void* K, const void* V, int n_kv,
                            const int32_t* idx, int k, const void* planes, const float* zvec, const float* cosq,

@@ -22,23 +22,10 @@ constexpr int LSTR = 272;  // bytes per row of a bf16 plane in LDS (256 + 16)
 constexpr int OSTR = 528;  // bytes per staged fp32 output row in LDS (512 + 16)
 constexpr int PLANE = D * LSTR;
 
-// state L[i][j] fp32 -> planes hi/lo, transposed: Lt[plane][j][i] bf16
 __global__ __launch_bounds__(256) void state_planes_kernel(const float* __restrict__ state,
                                                            bf16_t* __restrict__ planes) {
   __shared__ float tile[32][33];
-  const int bh = blockIdx.z, i0 = blockIdx.y * 32, j0 = blockIdx.x * 32;
-  const float* L = state + (size_t)bh * D * D;
-  const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;  // 32 x 8
-  for (int r = ty; r < 32; r += 8) tile[r][tx] = L[(size_t)(i0 + r) * D + j0 + tx];
-  __syncthreads();
-  bf16_t* hi = planes + (size_t)bh * 2 * D * D;
-  bf16_t* lo = hi + D * D;
-  for (int r = ty; r < 32; r += 8) {
-    const float v = tile[tx][r];  // i = i0 + tx, j = j0 + r
-    const bf16_t h = f32_to_bf16(v);
-    hi[(size_t)(j0 + r) * D + i0 + tx] = h;
-    lo[(size_t)(j0 + r) * D + i0 + tx] = f32_to_bf16(v - bf16_to_f32(h));
-  }
+  state_planes_tile(state, planes, blockIdx.z, blockIdx.y * 32, blockIdx.x * 32, tile);
 }
 
 template <bool kPlain>

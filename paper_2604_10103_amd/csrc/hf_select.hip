@@ -21,13 +21,24 @@ template <typename T, int D>
 __global__ __launch_bounds__(256) void pool_kernel(const T* __restrict__ Q, int n_q, int bq, int t_m,
                                                    const T* __restrict__ K, int n_kv, int kv_stride, int bkv,
                                                    int t_n, int kv_first, int kv_end, float* __restrict__ qbar,
-                                                   float* __restrict__ kbar_t) {
+                                                   float* __restrict__ kbar_t, const float* __restrict__ state,
+                                                   bf16_t* __restrict__ planes, int pool_wgs) {
   constexpr int E = Elem<T>::kPer16B;  // elements per 16-byte load
   constexpr int LPR = D / E;           // lanes covering one row
   constexpr int RPP = kWave / LPR;     // rows per pass of the wavefront
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   int blk = blockIdx.x * 4 + wave;
   const int bh = blockIdx.y;
+  if constexpr (D == 128 && E == 8) {
+    // the workgroups behind those that pool (launched only with a state) form its planes, one tile each: independent work
+    // that cost a chunk's first step a launch of its own (3.6 us and a gap at 3 heads, 5.7 us at 12)
+    __shared__ float tile[32][33];
+    if ((int)blockIdx.x >= pool_wgs) {
+      const int t = blockIdx.x - pool_wgs;
+      state_planes_tile(state, planes, bh, 32 * (t >> 2), 32 * (t & 3), tile);
+      return;
+    }
+  }
   if (blk >= t_m + kv_end - kv_first) return;
   const bool is_q = blk < t_m;
   if (!is_q) blk += kv_first - t_m;  // KV blocks outside [kv_first, kv_end) keep the pooled means already stored
@@ -59,11 +70,14 @@ __global__ __launch_bounds__(256) void pool_kernel(const T* __restrict__ Q, int 
 #pragma unroll
       for (int e = 0; e < E; ++e) acc[e] += v[u][e];
   }
-  for (; r < r1; r += RPP) {
-    float v[E];
-    load16B<T>(base + (size_t)r * D, v);
+  if (r < r1) {   // fewer than eight rows left: requested together all the same (clamped rows are dropped)
+    float v[8][E];
 #pragma unroll
-    for (int e = 0; e < E; ++e) acc[e] += v[e];
+    for (int u = 0; u < 8; ++u) load16B<T>(base + (size_t)min(r + u * RPP, r1 - 1) * D, v[u]);
+#pragma unroll
+    for (int u = 0; u < 8; ++u)
+#pragma unroll
+      for (int e = 0; e < E; ++e) acc[e] += r + u * RPP < r1 ? v[u][e] : 0.0f;
   }
 #pragma unroll
   for (int o = LPR; o < kWave; o <<= 1)
@@ -321,12 +335,14 @@ __global__ __launch_bounds__(512) void score_select3_kernel(const float* __restr
 }  // namespace
 
 int launch_pool_both(const hf_config& c, const void* Q, int n_q, int t_m, const void* K, int n_kv, int t_n,
-                     int kv_first, int kv_end, float* qbar, float* kbar_t, hipStream_t s) {
+                     int kv_first, int kv_end, float* qbar, float* kbar_t, hipStream_t s, const float* state, void* planes) {
   const int BH = c.batch * c.heads;
-  const dim3 grid((t_m + kv_end - kv_first + 3) / 4, BH), block(256);
+  const int pool_wgs = (t_m + kv_end - kv_first + 3) / 4;
+  const dim3 grid(pool_wgs + (state ? 16 : 0), BH), block(256);
 #define HF_LAUNCH_POOL(T, DD)                                                                                  \
   hipLaunchKernelGGL((pool_kernel<T, DD>), grid, block, 0, s, static_cast<const T*>(Q), n_q, c.block_q, t_m,   \
-                     static_cast<const T*>(K), n_kv, kv_stride_of(c, n_kv), c.block_kv, t_n, kv_first, kv_end, qbar, kbar_t)
+                     static_cast<const T*>(K), n_kv, kv_stride_of(c, n_kv), c.block_kv, t_n, kv_first, kv_end, qbar, \
+                     kbar_t, state, static_cast<bf16_t*>(planes), pool_wgs)
   if (c.dtype == HF_BF16) {
     if (c.head_dim == 128) HF_LAUNCH_POOL(bf16_t, 128); else HF_LAUNCH_POOL(bf16_t, 64);
   } else {
