@@ -119,14 +119,25 @@ int32_t* i32(PyObject* o, const char* name, Shape shape) { return static_cast<in
 void* bytes(PyObject* o, const char* name) { return ptr(o, name, at::kByte); }
 size_t size_of(PyObject* o) { return o == Py_None ? 0 : (size_t)THPVariable_Unpack(o).numel(); }   // after bytes()
 
-int to_int(PyObject* o) {
-  PyObject* n = PyNumber_Long(o);
+int narrow(PyObject* n) {   // takes the reference
   if (!n) throw Raised();
   const long v = PyLong_AsLong(n);
   Py_DECREF(n);
   if (v == -1 && PyErr_Occurred()) throw Raised();
   if (v != (long)(int)v) raise(PyExc_OverflowError, "%ld does not fit in 32 bits", v);
   return (int)v;
+}
+
+int to_int(PyObject* o) { return narrow(PyNumber_Long(o)); }     // what int() takes
+int index(PyObject* o) { return narrow(PyNumber_Index(o)); }     // whole numbers only
+
+bool equals(PyObject* o, int64_t v) {
+  PyObject* n = PyLong_FromLongLong(v);
+  if (!n) throw Raised();
+  const int same = PyObject_RichCompareBool(o, n, Py_EQ);
+  Py_DECREF(n);
+  if (same < 0) throw Raised();
+  return same;
 }
 
 void* stream() { return c10::hip::getCurrentHIPStream().stream(); }
@@ -164,7 +175,7 @@ struct Config : Struct<hf_config> {
       if (held != get()->kv_capacity) raise(PyExc_ValueError, "K_win must hold kv_capacity=%d tokens per head", (int)get()->kv_capacity);
       return to_int(n_kv);
     }
-    if (n_kv != Py_None && to_int(n_kv) != held) raise(PyExc_ValueError, "n_kv differs from the packed window length");
+    if (n_kv != Py_None && !equals(n_kv, held)) raise(PyExc_ValueError, "n_kv differs from the packed window length");
     return (int)held;
   }
 };
@@ -309,7 +320,7 @@ PyObject* pool_keys(Args a) {   // cfg, K_win, pooled_K, n_cached_kv_blocks, n_k
   const Config c(a[0]);
   const int64_t held = length(a[1], "K_win", 2);
   const int n_kv = c.kv_len(held, a[4]);
-  call(lib.hf_pool_keys, c.get(), c.tokens(a[1], "K_win", held), n_kv, to_int(a[3]), bytes(a[2], "pooled_K"), stream());
+  call(lib.hf_pool_keys, c.get(), c.tokens(a[1], "K_win", held), n_kv, index(a[3]), bytes(a[2], "pooled_K"), stream());
   return none();
 }
 
@@ -390,7 +401,7 @@ PyObject* rope_append_keys(Args a) {   // cfg, K_new, rope_cos, rope_sin, K_win,
   const int64_t held = length(a[4], "K_win", 2);
   const int n_kv = c.kv_len(held, a[7]);
   call(lib.hf_rope_append_keys, c.get(), c.tokens(a[1], "K_new", n), n, c.table(a[2], "rope_cos", n), c.table(a[3], "rope_sin", n),
-       c.tokens(a[4], "K_win", held), to_int(a[5]), n_kv, bytes(a[6], "pooled_K"), stream());
+       c.tokens(a[4], "K_win", held), index(a[5]), n_kv, bytes(a[6], "pooled_K"), stream());
   return none();
 }
 
@@ -460,7 +471,7 @@ PyObject* ring_last_step(Args a) {
   int32_t done = 0;
   void *ws = bytes(a[9], "workspace"), *sws = bytes(a[11], "step_workspace");
   call(lib.hf_ring_last_step, c.get(), ring.get(), c.tokens(a[2], "Q", n_q), c.tokens(a[14], "Q_hist", n_q),
-       c.tokens(a[3], "K_cache", cap), c.tokens(a[4], "V_cache", cap), to_int(a[5]),
+       c.tokens(a[3], "K_cache", cap), c.tokens(a[4], "V_cache", cap), index(a[5]),
        i32(a[6], "block_idx", {c.B, c.H, c.t_m(n_q), k}), c.state(a[7], "state"), c.table(a[12], "rope_cos_q", n_q),
        c.table(a[13], "rope_sin_q", n_q), c.tokens(a[8], "O", n_q), ws, size_of(a[9]), c.state(a[10], "state_out"),
        c.table(a[15], "rope_cos_ev", n_q), c.table(a[16], "rope_sin_ev", n_q), sws, size_of(a[11]), &done, stream());

@@ -5,6 +5,7 @@ import os
 import re
 
 import pytest
+import torch
 
 import oracle as orc
 import paper_2604_10103_amd as hf
@@ -357,3 +358,11 @@ def test_ring_struct_layout_and_last_step_arguments(lib):
     assert lib.hf_ring_last_step(*args(full, so=None)) == -1        # a full ring needs somewhere to put the new state
     assert lib.hf_ring_last_step(*args(full, so=fake)) == -2        # ... other than the state it reads
     assert lib.hf_ring_last_step(*args(hf.hf_ring(200, 400, 3, 0, 2, 7))) == -2   # bookkeeping out of range
+
+
+@pytest.mark.parametrize("n_kv", [7.5, 6.0, 6])
+def test_length_of_a_packed_window_is_compared_not_truncated(lib, n_kv):
+    cfg = hf.make_config(1, 1, 128, "bf16", 64, 64, 0.25)
+    K = torch.zeros((1, 1, 7, 128), dtype=torch.bfloat16)   # (its length is looked at before its device)
+    with pytest.raises(ValueError, match="n_kv differs"):
+        hf.hf_pool_keys(cfg, K, None, n_kv=n_kv)
