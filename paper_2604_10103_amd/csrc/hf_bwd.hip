@@ -77,7 +77,7 @@ __device__ __forceinline__ void selected_by(uint32_t* mask, const PrepArgs& p, i
   const int row_words = p.t_m * p.k;   // entries of a head
   const int h0 = b0 / p.t_n, entries = ((b0 + n - 1) / p.t_n - h0 + 1) * row_words;
   const int32_t* src = p.idx + (size_t)h0 * row_words;
-  const uint32_t per_k = 0xffffffffu / (uint32_t)p.k + 1u;   // e / k = e per_k / 2^32 (e k < 2^32 wherever the masks fit)
+  const uint32_t per_k = 0xffffffffu / (uint32_t)p.k + 1u;   // e / k = e per_k / 2^32, as e k < t_m k^2 < 2^32
   constexpr int U = 8;                 // entries in flight per thread: the pass is round trips to memory
   for (int e0 = tid; e0 < entries; e0 += U * kPrepThreads) {
     int entry[U];
@@ -101,9 +101,9 @@ __device__ __forceinline__ void selected_by(uint32_t* mask, const PrepArgs& p, i
 // Launch order of the dK/dV workgroups.  A workgroup's time is proportional to the length of its KV block's list of query
 // blocks, and the lists differ (top-k selection: a binomial spread around t_m k / t_n), while a GPU takes workgroups in index
 // order as slots free up.  Longest first within every XCD's share of the items leaves the short ones to fill the end.  One
-// record of kOrderRec words per place: the item that runs there, the length of its list and the list's first three entries, so that a workgroup has all it needs for its first
-// tiles after ONE dependent load (it is alone on its two SIMDs: every round trip to memory before its first MFMA is idle
-// time).  The masks are formed here once more, for the share's blocks: waiting for the workgroups that write the lists would
+// record of kOrderRec words per place: the item that runs there, the length of its list and the list's first three entries,
+// so that a workgroup has all it needs for its first tiles after ONE dependent load (it is alone on its two SIMDs: every
+// round trip to memory before its first MFMA is idle time).  The masks are formed here once more, for the share's blocks: waiting for the workgroups that write the lists would
 // take another launch.
 __device__ __forceinline__ void order_share(int32_t* smem, const PrepArgs& p, int share, int words) {
   const int first = share * p.items_per_xcd;
@@ -733,7 +733,8 @@ int launch_bwd_prep(const hf_config& c, const int32_t* idx, int k, int t_m, int 
   size_t lds = 0;
   if (idx) {
     const size_t words = ((size_t)t_m + 31) / 32;
-    if ((size_t)t_n * words * 4 <= 48 * 1024) {
+    // (the masks of a head in LDS, and a division by k in selected_by that is exact; the kernel of its own takes the rest)
+    if ((size_t)t_n * words * 4 <= 48 * 1024 && (unsigned long long)t_m * k * k < (1ull << 32)) {
       p.invert_wgs = BH;
       lds = (size_t)t_n * words * 4;
       const int slabs = (c.block_kv + 63) / 64;

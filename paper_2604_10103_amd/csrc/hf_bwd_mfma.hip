@@ -20,7 +20,7 @@
 // No staging registers, no LDS stores, no transposing permutes; one barrier per tile.  Both kernels run one
 // wavefront per SIMD with their accumulators and loop-invariant operands in the accumulation half of the register
 // file, all MFMAs of their loops as inline assembly, four tile slots and a loop pipelined over three tiles; the
-// dK/dV workgroups are launched longest list first (dkv_order_kernel).
+// dK/dV workgroups are launched longest list first.
 #include <math.h>
 #include <stdlib.h>
 

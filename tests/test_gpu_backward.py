@@ -386,3 +386,20 @@ def test_saving_entry_points_refuse_what_they_do_not_cover():
     bws = torch.empty(hf.hf_bwd_workspace_bytes(cfg, w.n_q, w.n_kv), dtype=torch.uint8, device=DEV)
     with pytest.raises(hf.HFError, match="bf16"):
         hf.hf_hybrid_attn_bwd_saved(cfg, Q.to(DEV), K.to(DEV), V.to(DEV), idx, None, O, Ol, lse, dQ, dK, dV, bws)
+
+
+@pytest.mark.parametrize("t_n", [11585, 11586, 12282, 12288])
+def test_longest_lists_of_one_mask_word(t_n):
+    """32 query blocks that select every block, around t_m k^2 = 2^32 (k = 11585.2, where the lists change kernels) and up to
+    the most blocks whose masks fit: the same sums in the same order as the dense window's.  A list short of one query block
+    would be 1 / sqrt(32 t_n) = 1.6e-3 off in all, and 0.2 in the block concerned."""
+    b, t_m = 16, 32
+    cfg = hf.make_config(1, 1, 64, "f32", b, b, 1.0)
+    Q, dO = (wl.randn((1, 1, b * t_m, 64), 94_000 + i, 1.0, torch.float32) for i in range(2))
+    K, V = (wl.randn((1, 1, b * t_n, 64), 94_010 + i, 1.0, torch.float32) for i in range(2))
+    idx = torch.arange(t_n, dtype=torch.int32, device=DEV).expand(1, 1, t_m, t_n).contiguous()
+    got = run_bwd(cfg, None, Q, K, V, idx, None, dO)[:3]
+    ref = run_bwd(cfg, None, Q, K, V, None, None, dO)[:3]
+    for name, a, r in zip(("dQ", "dK", "dV"), got, ref):
+        a, r = a.double().reshape(-1, b, 64), r.double().reshape(-1, b, 64)
+        assert ((a - r).flatten(1).norm(dim=1) / r.flatten(1).norm(dim=1)).max().item() <= 5e-5, name
