@@ -103,8 +103,8 @@ __device__ __forceinline__ void selected_by(uint32_t* mask, const PrepArgs& p, i
 // order as slots free up.  Longest first within every XCD's share of the items leaves the short ones to fill the end.  One
 // record of kOrderRec words per place: the item that runs there, the length of its list and the list's first three entries,
 // so that a workgroup has all it needs for its first tiles after ONE dependent load (it is alone on its two SIMDs: every
-// round trip to memory before its first MFMA is idle time).  The masks are formed here once more, for the share's blocks: waiting for the workgroups that write the lists would
-// take another launch.
+// round trip to memory before its first MFMA is idle time).  The masks are formed here once more, for the share's blocks:
+// waiting for the workgroups that write the lists would take another launch.
 __device__ __forceinline__ void order_share(int32_t* smem, const PrepArgs& p, int share, int words) {
   const int first = share * p.items_per_xcd;
   const int n = min(p.items_per_xcd, p.total_items - first);

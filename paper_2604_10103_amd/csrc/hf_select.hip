@@ -17,7 +17,10 @@ namespace {
 // Pooled keys are stored feature-group-major, kbar_t[bh][D/4][t_n][4], so that in the scoring
 // kernel consecutive lanes (= consecutive KV blocks) read consecutive 16-byte groups.
 // Pooled queries stay row-major, qbar[bh][t_m][D].
-template <typename T, int D>
+// kPlanes: the launch has workgroups that form the state's planes (their LDS costs the others 0.3 us: 8.27 us for the keys of 12
+// heads x 9360 with it, 7.97 without, so plain
+// pooling keeps an instance without)
+template <typename T, int D, bool kPlanes>
 __global__ __launch_bounds__(256) void pool_kernel(const T* __restrict__ Q, int n_q, int bq, int t_m,
                                                    const T* __restrict__ K, int n_kv, int kv_stride, int bkv,
                                                    int t_n, int kv_first, int kv_end, float* __restrict__ qbar,
@@ -29,7 +32,7 @@ __global__ __launch_bounds__(256) void pool_kernel(const T* __restrict__ Q, int 
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   int blk = blockIdx.x * 4 + wave;
   const int bh = blockIdx.y;
-  if constexpr (D == 128 && E == 8) {
+  if constexpr (kPlanes) {
     // the workgroups behind those that pool (launched only with a state) form its planes, one tile each: independent work
     // that cost a chunk's first step a launch of its own (3.6 us and a gap at 3 heads, 5.7 us at 12)
     __shared__ float tile[32][33];
@@ -339,14 +342,15 @@ int launch_pool_both(const hf_config& c, const void* Q, int n_q, int t_m, const 
   const int BH = c.batch * c.heads;
   const int pool_wgs = (t_m + kv_end - kv_first + 3) / 4;
   const dim3 grid(pool_wgs + (state ? 16 : 0), BH), block(256);
-#define HF_LAUNCH_POOL(T, DD)                                                                                  \
-  hipLaunchKernelGGL((pool_kernel<T, DD>), grid, block, 0, s, static_cast<const T*>(Q), n_q, c.block_q, t_m,   \
+#define HF_LAUNCH_POOL(T, DD, PLANES)                                                                                  \
+  hipLaunchKernelGGL((pool_kernel<T, DD, PLANES>), grid, block, 0, s, static_cast<const T*>(Q), n_q, c.block_q, t_m,   \
                      static_cast<const T*>(K), n_kv, kv_stride_of(c, n_kv), c.block_kv, t_n, kv_first, kv_end, qbar, \
                      kbar_t, state, static_cast<bf16_t*>(planes), pool_wgs)
   if (c.dtype == HF_BF16) {
-    if (c.head_dim == 128) HF_LAUNCH_POOL(bf16_t, 128); else HF_LAUNCH_POOL(bf16_t, 64);
+    if (c.head_dim != 128) HF_LAUNCH_POOL(bf16_t, 64, false);
+    else if (state) HF_LAUNCH_POOL(bf16_t, 128, true); else HF_LAUNCH_POOL(bf16_t, 128, false);
   } else {
-    if (c.head_dim == 128) HF_LAUNCH_POOL(float, 128); else HF_LAUNCH_POOL(float, 64);
+    if (c.head_dim == 128) HF_LAUNCH_POOL(float, 128, false); else HF_LAUNCH_POOL(float, 64, false);
   }
 #undef HF_LAUNCH_POOL
   return check_launch("hf_block_select(pool)");
