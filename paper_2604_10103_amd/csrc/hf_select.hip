@@ -17,9 +17,8 @@ namespace {
 // Pooled keys are stored feature-group-major, kbar_t[bh][D/4][t_n][4], so that in the scoring
 // kernel consecutive lanes (= consecutive KV blocks) read consecutive 16-byte groups.
 // Pooled queries stay row-major, qbar[bh][t_m][D].
-// kPlanes: the launch has workgroups that form the state's planes (their LDS costs the others 0.3 us: 8.27 us for the keys of 12
-// heads x 9360 with it, 7.97 without, so plain
-// pooling keeps an instance without)
+// kPlanes: the launch has workgroups that form the state's planes.  Their LDS costs the others 0.3 us (the keys of 12 heads x
+// 9360: 8.27 us with it, 7.97 without), so plain pooling keeps an instance without.
 template <typename T, int D, bool kPlanes>
 __global__ __launch_bounds__(256) void pool_kernel(const T* __restrict__ Q, int n_q, int bq, int t_m,
                                                    const T* __restrict__ K, int n_kv, int kv_stride, int bkv,
