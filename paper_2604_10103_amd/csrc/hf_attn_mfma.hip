@@ -97,41 +97,47 @@ struct HistArgs {
 // idx_row.  All scratch lies in the tile space, which is not in use yet.  t_n <= kSelMaxBlocks.
 constexpr int kSelMaxBlocks = kMaxFusedSelectBlocks;
 
-template <int NW, int BQ>
+// KS groups of NW wavefronts share the work, but every sum keeps the terms and the order it has with one group, so that a
+// query block's list does not depend on how many groups its launch takes: a thread of the q-bar sums takes 8 / KS features
+// of the same rows, group g the KV blocks 64 (g + KS u) + lane of its wavefront's slice of the head dimension.
+template <int NW, int KS>
 __device__ __forceinline__ int* select_in_workgroup(char* smem, const bf16_t* Qh, int q0, int n_q, const float* kbar_head,
                                                     int t_n, int k, int32_t* idx_row, float* scores_row) {
-  constexpr int NT = 64 * NW, G = NT / 16, CW = D / 4 / NW;
+  constexpr int NT = 64 * NW * KS, BQ = 32 * NW, G = 4 * NW, CW = D / 4 / NW;
+  constexpr int E = 8 / KS;             // features of a thread of the q-bar sums
+  typedef __bf16 row_piece __attribute__((ext_vector_type(E)));
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int slice = KS == 1 ? wave : wave % NW, first_j = KS == 1 ? lane : lane + 64 * (wave / NW);
   const int t_pad = (t_n + 3) & ~3;
   float* qpart = reinterpret_cast<float*>(smem);      // [G][D] partial column sums
   float* qbar = qpart + G * D;                          // [D]
   float* part = qbar + D;                               // [NW][t_pad]
   float* sc = part + NW * t_pad;                        // [t_pad]
   int* sel = reinterpret_cast<int*>(sc + t_pad);        // [k]
-  int* wave_count = sel + t_n;                          // [2][NW]
+  int* wave_count = sel + t_n;                          // [2][NW KS]
   const int rows = min(BQ, n_q - q0);
   // the block's rows and, right behind them, the first pass of pooled keys: both are on their way while the
   // pooled query is formed (the chain of this prologue is memory round trips, not arithmetic)
-  const int u16 = tid & 15, g = tid >> 4;
-  bf16x8 v[BQ / G];
+  const int f0 = E * (tid % (D / E)), g = tid / (D / E);
+  row_piece v[BQ / G];
 #pragma unroll
   for (int i = 0; i < BQ / G; ++i)
-    v[i] = *reinterpret_cast<const bf16x8*>(Qh + (size_t)min(q0 + g + G * i, n_q - 1) * D + 8 * u16);
+    v[i] = *reinterpret_cast<const row_piece*>(Qh + (size_t)min(q0 + g + G * i, n_q - 1) * D + f0);
   // pooled keys through a buffer descriptor: one offset register per block, the feature group's offset is scalar
   // (forty-eight 64-bit addresses would not fit next to the loads they feed)
   const __amdgpu_buffer_rsrc_t krsrc =
       __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(kbar_head), 0, (D / 4) * t_n * 16, 0x00020000);
   auto kload = [&](int j, int c) {
     typedef unsigned int u32v4 __attribute__((vector_size(16)));
-    const u32v4 r = __builtin_amdgcn_raw_buffer_load_b128(krsrc, j * 16, (wave * CW + c) * t_n * 16, 0);
+    const u32v4 r = __builtin_amdgcn_raw_buffer_load_b128(krsrc, j * 16, (slice * CW + c) * t_n * 16, 0);
     return make_float4(__uint_as_float(r[0]), __uint_as_float(r[1]), __uint_as_float(r[2]), __uint_as_float(r[3]));
   };
-  constexpr int U = NW == 2 ? 3 : 4;   // KV blocks per lane and pass: 48, 32 or 16 loads of 16 bytes in flight
+  constexpr int U = KS == 2 ? 2 : (NW == 2 ? 3 : 4);   // KV blocks per lane and pass: 48, 32 or 16 loads of 16 bytes in flight
   float4 kv[U][CW];
 #pragma unroll
   for (int u = 0; u < U; ++u) {
-    const int j = min(lane + 64 * u, t_n - 1);   // clamped: a valid address, the result is dropped
+    const int j = min(first_j + 64 * KS * u, t_n - 1);   // clamped: a valid address, the result is dropped
 #pragma unroll
     for (int c = 0; c < CW; ++c) kv[u][c] = kload(j, c);
   }
@@ -139,21 +145,22 @@ __device__ __forceinline__ int* select_in_workgroup(char* smem, const bf16_t* Qh
     // column sums of the thread's rows, two rows per instruction: (x_r, x_r') . (1, 1) + acc in fp32
     typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
     const bf16x2 one2 = {static_cast<__bf16>(1.0f), static_cast<__bf16>(1.0f)};
-    const bf16x8 zero = {};
-    float acc[8];
+    const row_piece zero = {};
+    float acc[E];
 #pragma unroll
-    for (int e = 0; e < 8; ++e) acc[e] = 0.0f;
+    for (int e = 0; e < E; ++e) acc[e] = 0.0f;
 #pragma unroll
     for (int i = 0; i < BQ / G; i += 2) {
-      const bf16x8 r0 = (g + G * i < rows) ? v[i] : zero, r1 = (g + G * (i + 1) < rows) ? v[i + 1] : zero;
+      const row_piece r0 = (g + G * i < rows) ? v[i] : zero, r1 = (g + G * (i + 1) < rows) ? v[i + 1] : zero;
 #pragma unroll
-      for (int e = 0; e < 8; ++e) {
+      for (int e = 0; e < E; ++e) {
         const bf16x2 pr = {r0[e], r1[e]};
         acc[e] = __builtin_amdgcn_fdot2_f32_bf16(pr, one2, acc[e], false);
       }
     }
-    *reinterpret_cast<float4*>(qpart + g * D + 8 * u16) = make_float4(acc[0], acc[1], acc[2], acc[3]);
-    *reinterpret_cast<float4*>(qpart + g * D + 8 * u16 + 4) = make_float4(acc[4], acc[5], acc[6], acc[7]);
+#pragma unroll
+    for (int e = 0; e < E; e += 4)
+      *reinterpret_cast<float4*>(qpart + g * D + f0 + e) = make_float4(acc[e], acc[e + 1], acc[e + 2], acc[e + 3]);
   }
   __syncthreads();
   if (tid < D) {
@@ -165,13 +172,13 @@ __device__ __forceinline__ int* select_in_workgroup(char* smem, const bf16_t* Qh
   if (tid < t_pad - t_n) sc[t_n + tid] = -INFINITY;   // padding never outranks a block
   __syncthreads();
 
-  // ---- scores: wavefront w a slice of the head dimension, lane l the KV blocks l, l + 64, ...
-  const float4* q4 = reinterpret_cast<const float4*>(qbar) + wave * CW;
-  for (int j0 = lane; j0 < t_n; j0 += 64 * U) {
-    if (j0 != lane) {   // (uniform) windows of more than 64 U blocks: further passes
+  // ---- scores: a wavefront's slice of the head dimension, lane l the KV blocks l, l + 64 KS, ... of its group
+  const float4* q4 = reinterpret_cast<const float4*>(qbar) + slice * CW;
+  for (int j0 = first_j; j0 < t_n; j0 += 64 * KS * U) {
+    if (j0 != first_j) {   // (uniform) windows of more than 64 KS U blocks: further passes
 #pragma unroll
       for (int u = 0; u < U; ++u) {
-        const int j = min(j0 + 64 * u, t_n - 1);
+        const int j = min(j0 + 64 * KS * u, t_n - 1);
 #pragma unroll
         for (int c = 0; c < CW; ++c) kv[u][c] = kload(j, c);
       }
@@ -193,7 +200,7 @@ __device__ __forceinline__ int* select_in_workgroup(char* smem, const bf16_t* Qh
     }
 #pragma unroll
     for (int u = 0; u < U; ++u)
-      if (j0 + 64 * u < t_n) part[wave * t_pad + j0 + 64 * u] = a0[u] + a1[u];
+      if (j0 + 64 * KS * u < t_n) part[slice * t_pad + j0 + 64 * KS * u] = a0[u] + a1[u];
   }
   __syncthreads();
 
@@ -296,14 +303,14 @@ __device__ __forceinline__ int* select_in_workgroup(char* smem, const bf16_t* Qh
       const unsigned long long bal_a = __ballot(keep_a), bal_b = __ballot(keep_b);
       if (lane == 0) {
         wave_count[wave] = __popcll(bal_a);
-        wave_count[NW + wave] = __popcll(bal_b);
+        wave_count[NW * KS + wave] = __popcll(bal_b);
       }
       __syncthreads();
       const unsigned long long below = (1ull << lane) - 1ull;
       int pos_a = base + __popcll(bal_a & below), pos_b = __popcll(bal_b & below), tot_a = 0, tot_b = 0;
 #pragma unroll
-      for (int w = 0; w < NW; ++w) {
-        const int ca = wave_count[w], cb = wave_count[NW + w];
+      for (int w = 0; w < NW * KS; ++w) {
+        const int ca = wave_count[w], cb = wave_count[NW * KS + w];
         if (w < wave) { pos_a += ca; pos_b += cb; }
         tot_a += ca;
         tot_b += cb;
@@ -587,7 +594,7 @@ __global__ __launch_bounds__(64 * NW * KS, 2) void attn_mfma_kernel(
   const int nsel = (kSel || idx) ? k : t_n;
   const int* sel_lds = nullptr;   // kSel: the list in LDS, valid until the first tile is requested
   if (kSel)
-    sel_lds = select_in_workgroup<NW * KS, BQ>(smem, Qh, qb * BQ, n_q, hist.kbar_t + (size_t)bh * (D / 4) * t_n * 4, t_n, k,
+    sel_lds = select_in_workgroup<NW, KS>(smem, Qh, qb * BQ, n_q, hist.kbar_t + (size_t)bh * (D / 4) * t_n * 4, t_n, k,
                                       hist.idx_out + ((size_t)bh * t_m + qb) * k,
                                       hist.scores_out ? hist.scores_out + ((size_t)bh * t_m + qb) * t_n : nullptr);
   const int subs = (bkv + TK - 1) / TK;
@@ -629,6 +636,11 @@ __global__ __launch_bounds__(64 * NW * KS, 2) void attn_mfma_kernel(
     d_tile = ok ? (st | (max(0, min(TK, min(n_kv, (jb + 1) * bkv) - st)) << 24)) : 0;
   };
   refill(0);
+  int valid_head = 0;   // KS > 1: real keys of the list's first tile
+  if (KS > 1) {
+    const int jb = kSel ? sel_lds[0] : (row_idx ? row_idx[0] : 0);
+    if ((unsigned)jb < (unsigned)t_n) valid_head = min(TK, min(n_kv, (jb + 1) * bkv) - jb * bkv);
+  }
   if (kSel) __syncthreads();   // every wavefront has its descriptors before a tile lands on the list
   auto next_tile = [&](int& start, int& valid) {
     if ((tq & 63) == 0 && tq > 0) refill(tq);  // uniform
@@ -714,6 +726,36 @@ __global__ __launch_bounds__(64 * NW * KS, 2) void attn_mfma_kernel(
   for (int s = 0; s < 8; ++s) kf[s] = *reinterpret_cast<const bf16x8*>(sK + k_addr[s]);
 
   int va = valid0, vb = valid1, vc = valid2, vd = valid3;  // real keys of tiles t .. t+3
+  auto mask_tile = [&](f32x16& sacc, const int valid) {
+    if (valid < TK) {  // keys that do not exist never contribute
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        const int key = 8 * (r >> 2) + 4 * h + (r & 3);
+        if (key >= valid) sacc[r] = -INFINITY;
+      }
+    }
+  };
+  auto row_max = [&](float mx) {   // of the lane's maximum; both lanes of a query agree
+    const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(mx), __float_as_uint(mx), false, false);
+    return max2f(__uint_as_float(sw[0]), __uint_as_float(sw[1])) * c_scale;
+  };
+  // The first reference of a row is the maximum of the list's first tile in every group, as it is with one group: P is rounded
+  // to bf16 against it, so an output does not depend on the number of groups but for the order of its fp32 sums.  (Each group
+  // against its own first tile: 2.3e-3 between the two, as far apart as two roundings of P and O are.)  Group 0's tile is
+  // read where it lies; it is overwritten behind the next barrier.
+  if (KS > 1 && grp != 0) {   // uniform
+    f32x16 head;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) head[r] = 0.0f;
+#pragma unroll
+    for (int s = 0; s < 8; ++s)
+      head = __builtin_amdgcn_mfma_f32_32x32x16_bf16(*reinterpret_cast<const bf16x8*>(smem + k_addr[s]), qf[s], head, 0, 0, 0);
+    mask_tile(head, __builtin_amdgcn_readfirstlane(valid_head));
+    float mx = head[0];   // (not max3f: the compiler has to see who reads an MFMA's result this soon, to wait for it)
+#pragma unroll
+    for (int r = 1; r < 16; ++r) mx = fmaxf(mx, head[r]);
+    m_ref = row_max(mx);
+  }
   // One tile (kslot = t mod 3, par = t mod 2, literals at every call site).  The scores of tile t are formed from
   // fragments already in registers; the one barrier of the iteration follows them.  Behind it every wavefront is
   // done with K slot kslot (fragments of tile t were read during tile t-1) and with V half par^1 (tile t-1), so V
@@ -758,23 +800,14 @@ __global__ __launch_bounds__(64 * NW * KS, 2) void attn_mfma_kernel(
     for (int s = 0; s < 8; ++s) kf[s] = *reinterpret_cast<const bf16x8*>(sK + k_addr[s] + ((kslot + 1) % 3) * KTILE);
     __builtin_amdgcn_sched_barrier(0);
 
-    if (valid_cur < TK) {  // keys that do not exist never contribute
-#pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const int key = 8 * (r >> 2) + 4 * h + (r & 3);
-        if (key >= valid_cur) sacc[r] = -INFINITY;
-      }
-    }
-
+    mask_tile(sacc, valid_cur);
     // ---- online softmax in the exp2 domain; statistics are per lane (= per query)
     float mx;
     {
       const float m0 = max3f(sacc[0], sacc[1], sacc[2]), m1 = max3f(sacc[3], sacc[4], sacc[5]);
       const float m2 = max3f(sacc[6], sacc[7], sacc[8]), m3 = max3f(sacc[9], sacc[10], sacc[11]);
       const float m4 = max3f(sacc[12], sacc[13], sacc[14]);
-      mx = max2f(max3f(m0, m1, m2), max3f(m3, m4, sacc[15]));
-      const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(mx), __float_as_uint(mx), false, false);
-      mx = max2f(__uint_as_float(sw[0]), __uint_as_float(sw[1])) * c_scale;  // both lanes of a query agree
+      mx = row_max(max2f(max3f(m0, m1, m2), max3f(m3, m4, sacc[15])));
     }
     // lazy rescale: keep the reference max unless some row's max grew by more than the threshold
     if (__any(mx > m_ref + kRescaleThreshold)) {

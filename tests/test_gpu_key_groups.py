@@ -72,3 +72,42 @@ def test_both_sides_of_the_line(case):
             assert rel_l2(wl.to_f64(got)[0, h], want) <= 1e-2, (name, h)
         Ln, zn = orc.state_absorb(*state, one(Kn), one(Vn))
         assert rel_l2(L2[h], Ln) <= 1e-5 and rel_l2(z2[h], zn) <= 1e-5
+
+
+@pytest.mark.parametrize("b,heads,n_q,n_kv", [(64, 60, 640, 3000), (64, 60, 620, 64 * 262 + 9), (128, 30, 1200, 4000)])
+def test_a_head_alone_and_among_many(b, heads, n_q, n_kv):
+    """The same two heads in a launch of their own (two groups) and repeated to one with a single group.  Scores and lists are
+    the same bits: their sums keep terms and order.  Outputs differ by the order of fp32 sums alone, P being rounded against
+    the same reference: 1e-6 moves one bf16 rounding in 4000 by 2^-8, 6e-5 in all, where P rounded against another
+    reference is 2.3e-3 away."""
+    d = 128
+    mk = lambda n, s: wl.randn((1, 2, n, d), 47_100 + s, 0.5, torch.bfloat16).to(DEV)
+    Q, K, V, Ke, Ve = mk(n_q, 0), mk(n_kv, 1), mk(n_kv, 2), mk(90, 3), mk(90, 4)
+
+    def run(H):
+        cfg = hf.make_config(1, H, d, "bf16", b, b, 0.3)
+        q, kk, v, ke, ve = (t.repeat(1, H // 2, 1, 1) for t in (Q, K, V, Ke, Ve))
+        st = torch.empty(hf.hf_state_bytes(cfg) // 4, dtype=torch.float32, device=DEV)
+        hf.hf_state_init(cfg, st)
+        hf.hf_absorb_evicted(cfg, st, ke, ve)
+        byte = lambda n: torch.empty(max(int(n), 256), dtype=torch.uint8, device=DEV)
+        planes, pooled = byte(hf.hf_state_planes_bytes(cfg)), byte(hf.hf_pooled_keys_bytes(cfg, n_kv))
+        hf.hf_state_planes(cfg, st, planes)
+        hf.hf_pool_keys(cfg, kk, pooled)
+        t_m, t_n = -(-n_q // b), -(-n_kv // b)
+        idx = torch.full((1, H, t_m, hf.hf_select_k(cfg, n_kv)), -1, dtype=torch.int32, device=DEV)
+        scores = torch.full((1, H, t_m, t_n), float("nan"), dtype=torch.float32, device=DEV)
+        O, Os, Ol = (torch.full(q.shape, float("nan"), dtype=torch.bfloat16, device=DEV) for _ in range(3))
+        lse2 = torch.full((H, n_q), float("nan"), dtype=torch.float32, device=DEV)
+        hf.hf_select_attn_fwd(cfg, q, kk, v, pooled, st, planes, O, idx, scores)
+        hf.hf_hybrid_attn_fwd_save(cfg, q, kk, v, idx, st, Os, Ol, lse2, byte(hf.hf_workspace_bytes(cfg, n_q, n_kv)))
+        torch.cuda.synchronize()
+        return idx, scores, lse2[None], O, Os, Ol
+
+    few, many = run(2), run(heads)
+    for h in (0, heads - 2):
+        pair = [t[:, h:h + 2] for t in many]
+        assert torch.equal(few[1], pair[1]) and torch.equal(few[0], pair[0])
+        assert (few[2] - pair[2]).abs().max().item() <= 1e-5   # log2 of fp32 sums
+        for name, a, r in zip(("O", "saved O", "O_local"), few[3:], pair[3:]):
+            assert rel_l2(wl.to_f64(a), wl.to_f64(r)) <= 3e-4, name
