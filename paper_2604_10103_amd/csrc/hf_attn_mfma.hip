@@ -1113,7 +1113,11 @@ constexpr int kMfmaMaxKeys = 1 << 23;
 // hf_step_fwd, one / two groups: 2 heads x 15 blocks 27.7 / 25.6 us, 4 x 33 32.8 / 25.3, 6 x 43 48.3 / 38.0, 8 x 52 55.5 / 43.4,
 // 12 x 47 56.9 / 61.2, 16 x 66 128 / 120, 16 x 74 143 / 133, 24 x 74 196 / 206; block_q 128: 4 x 24 41.3 / 37.0, 8 x 36 73 / 90.
 // (Four groups of two wavefronts were never better than two.)
-static int key_groups(const hf_config& c, long long workgroups) {
+// Every launch counts two absorbing workgroups per head, also one that absorbs nothing: hf_step_fwd and hf_select_attn_fwd
+// then run the same instance for the same Q, K, V and give the same bits.  (The attending workgroups alone would send steps
+// of just one full round to two groups, whose absorbing workgroups wait for the round's end.)
+static int key_groups(const hf_config& c, long long attending) {
+  const long long workgroups = attending + 2ll * c.batch * c.heads;
   if (c.block_q != 64) return workgroups <= 256 ? 2 : 1;
   return workgroups <= 512 || (workgroups > 1024 && workgroups <= 1536) ? 2 : 1;
 }
@@ -1136,7 +1140,7 @@ static int launch_attn_mfma_impl(const hf_config& c, const void* Q, int n_q, con
   const bf16_t* v = static_cast<const bf16_t*>(V);
   bf16_t* o = static_cast<bf16_t*>(O);
   const HistArgs h = hist ? *hist : HistArgs{};
-  const int ks = key_groups(c, total + (ab.role_blocks ? 2 * BH : 0));   // (as step_absorb_slices counts)
+  const int ks = key_groups(c, total);
 #define HF_LAUNCH_ATTN_KS(NWV, FUSED, SEL, KS)                                                                         \
   hipLaunchKernelGGL((attn_mfma_kernel<NWV, FUSED, SEL, KS>), grid, dim3(64 * NWV * KS), 0, s, q, kk, v, idx, k, n_q, n_kv, \
                      kv_stride_of(c, n_kv), c.block_kv, t_m, t_n, per_xcd, (int)total, c_scale, h, ab, o)
@@ -1207,7 +1211,7 @@ int launch_attn_mfma_fused(const hf_config& c, const void* Q, int n_q, const voi
 int step_absorb_slices(const hf_config& c, int n_q, int n_ev) {
   const int BH = c.batch * c.heads;
   const long long attending = (long long)BH * ((n_q + c.block_q - 1) / c.block_q);
-  const long long slots = 256ll * (c.block_q == 64 ? 4 : 2) / key_groups(c, attending + 2 * BH);
+  const long long slots = 256ll * (c.block_q == 64 ? 4 : 2) / key_groups(c, attending);
   long long room = slots - attending;          // a launch of several rounds has no room to speak of: few, long slices
   int s = room >= BH ? (int)(room / BH) : 2;
   if (s > 8) s = 8;

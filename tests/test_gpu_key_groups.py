@@ -15,10 +15,12 @@ pytestmark = pytest.mark.gpu
 DEV = "cuda:0"
 
 CASES = [  # heads, block, n_q, n_kv, keep: workgroups
+    # (attending workgroups + the two absorbing ones per head that the launch counts)
     (1, 64, 1, 20, 1.0), (2, 64, 130, 1000, 0.4), (1, 64, 65, 4400, 1.0),      # two groups: one tile, a few, more than 64 each
-    (32, 64, 1024, 150, 0.5), (27, 64, 1217, 150, 0.5),                        # 512 two groups, 540 one
-    (40, 64, 1601, 100, 0.6), (49, 64, 2000, 70, 1.0),                         # 1040 two groups, 1568 one
-    (2, 128, 129, 400, 0.5), (32, 128, 1000, 130, 1.0), (37, 128, 830, 260, 0.4),  # block 128: 4 and 256 two groups, 259 one
+    (32, 64, 1024, 150, 0.5), (27, 64, 1217, 150, 0.5), (32, 64, 896, 150, 0.5),  # 512 + 64 and 540 + 54 one, 448 + 64 two
+    (40, 64, 1601, 100, 0.6), (49, 64, 2000, 70, 1.0),                         # 1040 + 80 two groups, 1568 + 98 one
+    (2, 128, 129, 400, 0.5), (32, 128, 768, 130, 1.0),                         # block 128: 4 + 4 and 192 + 64 two groups
+    (32, 128, 1000, 130, 1.0), (37, 128, 830, 260, 0.4),                       # 256 + 64 and 259 + 74 one
 ]
 
 
@@ -111,3 +113,30 @@ def test_a_head_alone_and_among_many(b, heads, n_q, n_kv):
         assert (few[2] - pair[2]).abs().max().item() <= 1e-5   # log2 of fp32 sums
         for name, a, r in zip(("O", "saved O", "O_local"), few[3:], pair[3:]):
             assert rel_l2(wl.to_f64(a), wl.to_f64(r)) <= 3e-4, name
+
+
+@pytest.mark.parametrize("b,heads,n_q", [(64, 25, 64 * 20), (64, 20, 64 * 50), (128, 16, 128 * 16)])
+def test_an_absorb_in_the_launch_does_not_change_its_bits(b, heads, n_q):
+    """Launches of just one full round (500, 1000 and 256 attending workgroups): the absorbing ones are counted either way."""
+    d, n_kv, n_ev = 128, 700, 90
+    cfg = hf.make_config(1, heads, d, "bf16", b, b, 0.4)
+    mk = lambda n, s: wl.randn((1, heads, n, d), 47_200 + s, 0.5, torch.bfloat16).to(DEV)
+    Q, K, V, Ke, Ve = mk(n_q, 0), mk(n_kv, 1), mk(n_kv, 2), mk(n_ev, 3), mk(n_ev, 4)
+    byte = lambda n: torch.empty(max(int(n), 256), dtype=torch.uint8, device=DEV)
+    st = torch.empty(hf.hf_state_bytes(cfg) // 4, dtype=torch.float32, device=DEV)
+    hf.hf_state_init(cfg, st)
+    hf.hf_absorb_evicted(cfg, st, Ke, Ve)
+    planes, pooled = byte(hf.hf_state_planes_bytes(cfg)), byte(hf.hf_pooled_keys_bytes(cfg, n_kv))
+    hf.hf_state_planes(cfg, st, planes)
+    hf.hf_pool_keys(cfg, K, pooled)
+    out = []
+    for absorb in (False, True):
+        idx = torch.full((1, heads, -(-n_q // b), hf.hf_select_k(cfg, n_kv)), -1, dtype=torch.int32, device=DEV)
+        O = torch.full(Q.shape, float("nan"), dtype=torch.bfloat16, device=DEV)
+        if absorb:
+            hf.hf_step_fwd(cfg, Q, K, V, pooled, st, planes, O, idx, Ke, Ve, torch.empty_like(st), torch.empty_like(planes),
+                           byte(hf.hf_step_workspace_bytes(cfg, n_q, n_ev)))
+        else:
+            hf.hf_select_attn_fwd(cfg, Q, K, V, pooled, st, planes, O, idx)
+        out.append((idx, O))
+    assert torch.equal(out[0][0], out[1][0]) and torch.equal(out[0][1], out[1][1])
