@@ -617,8 +617,9 @@ __global__ __launch_bounds__(64 * NW * KS, 2) void attn_mfma_kernel(
   float m_ref = -INFINITY, l_run = 0.0f;
 
   // ---- tile list: (selected block, 32-key part) -> (first key, number of real keys).  Tiles past
-  // the end of the list and out-of-range block indices give (0, 0): such a tile reads real rows and
-  // is masked entirely.  The descriptors are formed 64 tiles at a time, lane l holding tile 64 c + l,
+  // the end of the list (KS > 1, an odd number of tiles) and out-of-range block indices give (n_kv, 0):
+  // such a tile reads as zeros and is masked entirely (the weight of its values is zero, which a NaN or
+  // an infinity of a real row would survive).  The descriptors are formed 64 tiles at a time, lane l holding tile 64 c + l,
   // and handed out with one v_readlane per tile: the bookkeeping and the load of the block index stay
   // out of the tile loop.
   int d_tile = 0, tq = 0;  // first key (24 bits: the window has fewer than 2^23 keys) | real keys << 24
@@ -633,7 +634,7 @@ __global__ __launch_bounds__(64 * NW * KS, 2) void attn_mfma_kernel(
       jb = row_idx ? row_idx[sc] : sc;
     const bool ok = (sel < nsel) && ((unsigned)jb < (unsigned)t_n);
     const int st = jb * bkv + TK * sub;
-    d_tile = ok ? (st | (max(0, min(TK, min(n_kv, (jb + 1) * bkv) - st)) << 24)) : 0;
+    d_tile = ok ? (st | (max(0, min(TK, min(n_kv, (jb + 1) * bkv) - st)) << 24)) : n_kv;
   };
   refill(0);
   int valid_head = 0;   // KS > 1: real keys of the list's first tile

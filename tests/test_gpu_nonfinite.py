@@ -1,0 +1,52 @@
+"""NaN and infinities among the valid tokens reach the rows that select their block and no others, whatever parts of short
+blocks and ends of lists the kernels pad their tiles with.  A call on poisoned inputs is compared bit for bit with the same
+call on finite ones."""
+import pytest
+import torch
+
+import paper_2604_10103_amd as hf
+import workloads as wl
+
+pytestmark = pytest.mark.gpu
+
+DEV = "cuda:0"
+NAN, INF = float("nan"), float("inf")
+
+
+def _inputs(dtype, d, n_q, n_kv, seed):
+    td = torch.bfloat16 if dtype == "bf16" else torch.float32
+    mk = lambda n, s: wl.randn((1, 2, n, d), 61_000 + seed + s, 0.5, td).to(DEV)
+    return mk(n_q, 0), mk(n_kv, 1), mk(n_kv, 2), mk(n_q, 3)
+
+
+def _lists(rows):
+    return torch.tensor(rows, dtype=torch.int32, device=DEV).expand(1, 2, len(rows), len(rows[0])).contiguous()
+
+
+def _attend(cfg, Q, K, V, idx):
+    O = torch.full_like(Q, 7.0)
+    ws = torch.empty(max(hf.hf_workspace_bytes(cfg, Q.shape[2], K.shape[2]), 256), dtype=torch.uint8, device=DEV)
+    hf.hf_hybrid_attn_fwd(cfg, Q, K, V, idx, None, O, ws)
+    torch.cuda.synchronize()
+    return O
+
+
+# dtype, head_dim, block_q, block_kv, keys, list of a query block without block 0
+FORWARD = {
+    "mfma_groups": ("bf16", 128, 64, 32, 300, [2, 5, 8]),          # two groups of wavefronts, an odd number of tiles
+    "mfma_groups_b128": ("bf16", 128, 128, 32, 300, [2, 5, 9]),
+}
+
+
+@pytest.mark.parametrize("case", FORWARD, ids=str)
+@pytest.mark.parametrize("bad", [NAN, INF])
+def test_an_unselected_block_is_not_read(case, bad):
+    dtype, d, bq, bkv, n_kv, sel = FORWARD[case]
+    n_q = 2 * bq + 5
+    cfg = hf.make_config(1, 2, d, dtype, bq, bkv, 0.5)
+    Q, K, V, _ = _inputs(dtype, d, n_q, n_kv, 0)
+    idx = _lists([sel] * 3)
+    want = _attend(cfg, Q, K, V, idx)
+    K[:, :, :min(bkv, 32)] = bad
+    V[:, :, :min(bkv, 32)] = bad
+    assert want.isfinite().all() and torch.equal(_attend(cfg, Q, K, V, idx), want)
