@@ -96,15 +96,16 @@ __global__ __launch_bounds__(128 * KS, 4) void attn_d64_kernel(
   float m_ref = -INFINITY, l_run = 0.0f;
 
   // tiles of the group's part of the list, 64 at a time, lane l holding tile t0 + l: first key | real keys << 24.  Tiles past
-  // the end, empty parts of short blocks and indices out of range hold no real key.
+  // the end, empty parts of short blocks and indices out of range hold no real key: they start at the head's end, where
+  // rows read as zeros (a real row of weight zero would pass a NaN or an infinity on).
   int d_tile = 0, tq = 0;
   auto refill = [&](int t0) {
     const int t = grp + KS * (t0 + lane);
     const int sel = t / subs, sub = t - sel * subs;
     const int jb = row_idx ? row_idx[min(sel, nsel - 1)] : min(sel, nsel - 1);
     const bool ok = sel < nsel && (unsigned)jb < (unsigned)t_n;
-    const int st = jb * bkv + TK * sub;
-    d_tile = ok ? (st | (max(0, min(TK, n_kv - st)) << 24)) : 0;
+    const int st = jb * bkv + TK * sub, real = ok ? min(TK, n_kv - st) : 0;
+    d_tile = real > 0 ? (st | (real << 24)) : n_kv;
   };
   refill(0);
   auto next_tile = [&](int& start, int& valid) {

@@ -35,6 +35,8 @@ def _attend(cfg, Q, K, V, idx):
 FORWARD = {
     "mfma_groups": ("bf16", 128, 64, 32, 300, [2, 5, 8]),          # two groups of wavefronts, an odd number of tiles
     "mfma_groups_b128": ("bf16", 128, 128, 32, 300, [2, 5, 9]),
+    "d64": ("bf16", 64, 64, 32, 300, [2, 5, 8]),
+    "d64_short": ("bf16", 64, 128, 96, 96 * 3 + 10, [1, 2, 3]),    # the last block's parts 1 and 2 are empty
 }
 
 
