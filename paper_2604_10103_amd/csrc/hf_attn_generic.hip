@@ -75,7 +75,7 @@ __global__ __launch_bounds__(256, 2) void attn_wide_kernel(const T* __restrict__
   }
 
   // tile t of the list: first key and number of real keys (0: past the list, an index out of range, or an empty part of a
-  // short block; such a tile reads clamped rows and its scores are -inf)
+  // short block); the rows behind them read as zeros and their scores are -inf
   auto tile_at = [&](int t, int& first, int& cnt) {
     const int s = t / subs, sub = t - s * subs;
     const int jb = row_idx ? row_idx[min(s, nsel - 1)] : s;
@@ -86,18 +86,18 @@ __global__ __launch_bounds__(256, 2) void attn_wide_kernel(const T* __restrict__
     first = n > 0 ? st : 0;
   };
   Piece<T> kp[C], vp[4][F];
+  const int k_at = l16 * D + 4 * g, v_at = 4 * g * D + 4 * l16;
   auto load_k = [&](int first, int cnt) {
-    const T* p = Kh + (size_t)(first + min(l16, max(cnt - 1, 0))) * D + 4 * g;
+    const __amdgpu_buffer_rsrc_t rows = tile_rows<T, D>(Kh, first, cnt);
 #pragma unroll
-    for (int c = 0; c < C; ++c) kp[c].load(p + 16 * c);
+    for (int c = 0; c < C; ++c) kp[c].load(rows, k_at + 16 * c);
   };
   auto load_v = [&](int first, int cnt) {
+    const __amdgpu_buffer_rsrc_t rows = tile_rows<T, D>(Vh, first, cnt);
 #pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      const T* p = Vh + (size_t)(first + min(4 * g + r, max(cnt - 1, 0))) * D + 4 * l16;
+    for (int r = 0; r < 4; ++r)
 #pragma unroll
-      for (int f = 0; f < F; ++f) vp[r][f].load(p + 64 * f);
-    }
+      for (int f = 0; f < F; ++f) vp[r][f].load(rows, v_at + r * D + 64 * f);
   };
 
   // One tile ahead in every direction: trip t forms the scores of tile t + 1 next to the exponentials of tile t (the matrix

@@ -70,17 +70,31 @@ template <> __device__ __forceinline__ void store4<bf16_t>(bf16_t* p, f32x4 v) {
   *reinterpret_cast<uint2*>(p) = w;
 }
 
-// what a lane keeps of the memory it asked for: the storage type's own words, widened when they are used, so that a tile
-// on its way takes no more registers than it has bytes
+// tokens first .. first + cnt - 1 of a head (whole wavefronts agree on them) as a buffer: rows behind them read as zeros.  A
+// real row in their place would pass a NaN or an infinity on to rows that have nothing to do with it, also with weight zero.
+template <typename T, int D>
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t tile_rows(const T* head, int first, int cnt) {
+  const T* p = head + (size_t)__builtin_amdgcn_readfirstlane(first) * D;
+  return __builtin_amdgcn_make_buffer_rsrc(const_cast<T*>(p), 0, __builtin_amdgcn_readfirstlane(cnt) * D * (int)sizeof(T), 0x00020000);
+}
+
+// what a lane keeps of the memory it asked for (four elements, e elements from the buffer's start): the storage type's own
+// words, widened when they are used, so that a tile on its way takes no more registers than it has bytes
 template <typename T> struct Piece;
 template <> struct Piece<float> {
   f32x4 v;
   __device__ __forceinline__ void load(const float* p) { v = *reinterpret_cast<const f32x4*>(p); }
+  __device__ __forceinline__ void load(__amdgpu_buffer_rsrc_t rows, int e) {
+    v = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(rows, 4 * e, 0, 0));
+  }
   __device__ __forceinline__ f32x4 get() const { return v; }
 };
 template <> struct Piece<bf16_t> {
   uint2 w;
   __device__ __forceinline__ void load(const bf16_t* p) { w = *reinterpret_cast<const uint2*>(p); }
+  __device__ __forceinline__ void load(__amdgpu_buffer_rsrc_t rows, int e) {
+    w = __builtin_bit_cast(uint2, __builtin_amdgcn_raw_buffer_load_b64(rows, 2 * e, 0, 0));
+  }
   __device__ __forceinline__ f32x4 get() const {
     return f32x4{__uint_as_float(w.x << 16), __uint_as_float(w.x & 0xffff0000u), __uint_as_float(w.y << 16),
                  __uint_as_float(w.y & 0xffff0000u)};

@@ -37,6 +37,11 @@ FORWARD = {
     "mfma_groups_b128": ("bf16", 128, 128, 32, 300, [2, 5, 9]),
     "d64": ("bf16", 64, 64, 32, 300, [2, 5, 8]),
     "d64_short": ("bf16", 64, 128, 96, 96 * 3 + 10, [1, 2, 3]),    # the last block's parts 1 and 2 are empty
+    "wide_f32": ("f32", 128, 48, 48, 48 * 3 + 10, [1, 2, 3]),      # fp32 arithmetic, 16-key tiles: likewise
+    "wide_f32_d64": ("f32", 64, 20, 40, 40 * 3 + 5, [1, 3]),
+    "wide_bf16": ("bf16", 128, 48, 40, 40 * 3 + 5, [1, 2, 3]),
+    "wide_bf16_d64": ("bf16", 64, 40, 33, 33 * 3 + 10, [1, 2, 3]),
+    "wide32_f32": ("f32", 128, 64, 64, 64 * 3 + 10, [1, 3]),
 }
 
 
@@ -52,3 +57,18 @@ def test_an_unselected_block_is_not_read(case, bad):
     K[:, :, :min(bkv, 32)] = bad
     V[:, :, :min(bkv, 32)] = bad
     assert want.isfinite().all() and torch.equal(_attend(cfg, Q, K, V, idx), want)
+
+
+@pytest.mark.parametrize("case", ["mfma_groups", "wide_f32", "wide_f32_d64", "wide_bf16", "wide_bf16_d64", "wide32_f32"])
+def test_a_selected_infinity_stays_one(case):
+    """In the last key of a short tile: nothing repeats that row with weight zero (zero times infinity is NaN)."""
+    dtype, d, bq, bkv, n_kv, sel = FORWARD[case]
+    n_q = 2 * bq + 5
+    cfg = hf.make_config(1, 2, d, dtype, bq, bkv, 0.5)
+    Q, K, V, _ = _inputs(dtype, d, n_q, n_kv, 10)
+    last = (n_kv - 1) // bkv
+    idx = _lists([[0, last], [1, last], [0, 1]])
+    want = _attend(cfg, Q, K, V, idx)
+    V[:, :, n_kv - 1] = INF
+    O = _attend(cfg, Q, K, V, idx)
+    assert (O[:, :, :2 * bq] == INF).all() and torch.equal(O[:, :, 2 * bq:], want[:, :, 2 * bq:])
