@@ -86,18 +86,19 @@ __global__ __launch_bounds__(256, 2) void attn_wide_kernel(const T* __restrict__
     first = n > 0 ? st : 0;
   };
   Piece<T> kp[C], vp[4][F];
-  const int k_at = l16 * D + 4 * g, v_at = 4 * g * D + 4 * l16;
+  constexpr int B = sizeof(T);
+  int k_at = (l16 * D + 4 * g) * B, v_at = (4 * g * D + 4 * l16) * B;
   auto load_k = [&](int first, int cnt) {
     const __amdgpu_buffer_rsrc_t rows = tile_rows<T, D>(Kh, first, cnt);
 #pragma unroll
-    for (int c = 0; c < C; ++c) kp[c].load(rows, k_at + 16 * c);
+    for (int c = 0; c < C; ++c) kp[c].load(rows, k_at + 16 * c * B);
   };
   auto load_v = [&](int first, int cnt) {
     const __amdgpu_buffer_rsrc_t rows = tile_rows<T, D>(Vh, first, cnt);
 #pragma unroll
     for (int r = 0; r < 4; ++r)
 #pragma unroll
-      for (int f = 0; f < F; ++f) vp[r][f].load(rows, v_at + r * D + 64 * f);
+      for (int f = 0; f < F; ++f) vp[r][f].load(rows, v_at + (r * D + 64 * f) * B);
   };
 
   // One tile ahead in every direction: trip t forms the scores of tile t + 1 next to the exponentials of tile t (the matrix
@@ -178,6 +179,7 @@ __global__ __launch_bounds__(256, 2) void attn_wide_kernel(const T* __restrict__
   __builtin_amdgcn_sched_barrier(0);
   maxima(cnt);
   for (int t = kz; t < ntiles; t += KS) {
+    asm volatile("" : "+v"(k_at), "+v"(v_at));   // (opaque here, or their sums leave the loop as registers instead of immediates)
     first_v = first_k;
     cnt = cnt_k;
     tile_at(t + 2 * KS, first_k, cnt_k);

@@ -326,26 +326,24 @@ __global__ __launch_bounds__(64 * kParts, 2) void bwd_dq_wide_kernel(
   Piece<T> kr[C], vr[C], kc[4][F];
   int first, cnt, first_n, cnt_n;
   tile_at(kz, first, cnt);
+  constexpr int B = sizeof(T);
+  int row_at = (l16 * D + 4 * g) * B, col_at = (4 * g * D + 4 * l16) * B;   // rows behind a tile's last real key read as zeros
+  __amdgpu_buffer_rsrc_t k_rows = tile_rows<T, D>(Kh, first, cnt);
   {
-    const size_t base = (size_t)__builtin_amdgcn_readfirstlane(first) * D;
-    const uint32_t off = min(l16, max(cnt - 1, 0)) * D + 4 * g;
+    const __amdgpu_buffer_rsrc_t v_rows = tile_rows<T, D>(Vh, first, cnt);
 #pragma unroll
     for (int c = 0; c < C; ++c) {
-      kr[c].load(Kh + base + (off + 16 * c));
-      vr[c].load(Vh + base + (off + 16 * c));
+      kr[c].load(k_rows, row_at + 16 * c * B);
+      vr[c].load(v_rows, row_at + 16 * c * B);
       __builtin_amdgcn_sched_barrier(0);   // (requests are awaited in order: in this order here and in the loop)
     }
   }
   const float* bq0 = sQ + l16 * OST + 4 * g;
   const float* bg0 = sG + l16 * OST + 4 * g;
   for (int t = kz; t < ntiles; t += kParts) {
+    asm volatile("" : "+v"(row_at), "+v"(col_at));   // (opaque here, or their sums leave the loop as registers instead of immediates)
     tile_at(t + kParts, first_n, cnt_n);
-    // uniform bases and 32-bit offsets of the lane: a tile's first row is scalar
-    const size_t cbase = (size_t)__builtin_amdgcn_readfirstlane(first) * D, base = (size_t)__builtin_amdgcn_readfirstlane(first_n) * D;
-    uint32_t col[4];
-#pragma unroll
-    for (int r = 0; r < 4; ++r) col[r] = min(4 * g + r, max(cnt - 1, 0)) * D + 4 * l16;
-    const uint32_t off = min(l16, max(cnt_n - 1, 0)) * D + 4 * g;
+    const __amdgpu_buffer_rsrc_t kn_rows = tile_rows<T, D>(Kh, first_n, cnt_n), vn_rows = tile_rows<T, D>(Vh, first_n, cnt_n);
     f32x4 s[NQ], p[NQ];
 #pragma unroll
     for (int n = 0; n < NQ; ++n) s[n] = p[n] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
@@ -366,16 +364,16 @@ __global__ __launch_bounds__(64 * kParts, 2) void bwd_dq_wide_kernel(
           p[n] = mfma_f32(v[e], gg[n][e], p[n]);
         }
 #pragma unroll
-      for (int u = c * 4 * F / C; u < (c + 1) * 4 * F / C; ++u) kc[u / F][u % F].load(Kh + cbase + (col[u / F] + 64 * (u % F)));
+      for (int u = c * 4 * F / C; u < (c + 1) * 4 * F / C; ++u) kc[u / F][u % F].load(k_rows, col_at + (u / F * D + 64 * (u % F)) * B);
       __builtin_amdgcn_sched_barrier(0);
     }
-    // dS = P (dP - D); a key that does not exist has probability zero
+    // dS = P (dP - D); zero for a key that does not exist
 #pragma unroll
     for (int n = 0; n < NQ; ++n)
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
-        const float w = 4 * g + r < cnt ? __builtin_amdgcn_exp2f(s[n][r] - lse[n]) : 0.0f;
-        s[n][r] = w * (p[n][r] - dv[n]);
+        const float ds = __builtin_amdgcn_exp2f(s[n][r] - lse[n]) * (p[n][r] - dv[n]);
+        s[n][r] = 4 * g + r < cnt ? ds : 0.0f;
       }
 #pragma unroll
     for (int u = 0; u < 4 * F; ++u) {
@@ -386,12 +384,12 @@ __global__ __launch_bounds__(64 * kParts, 2) void bwd_dq_wide_kernel(
         for (int n = 0; n < NQ; ++n) dq[n][u % F][e] = mfma_f32(a[e], s[n][u / F], dq[n][u % F][e]);
 #pragma unroll
       for (int c = u * C / (4 * F); c < (u + 1) * C / (4 * F); ++c) {
-        kr[c].load(Kh + base + (off + 16 * c));
-        vr[c].load(Vh + base + (off + 16 * c));
+        kr[c].load(kn_rows, row_at + 16 * c * B);
+        vr[c].load(vn_rows, row_at + 16 * c * B);
       }
       __builtin_amdgcn_sched_barrier(0);
     }
-    first = first_n;
+    k_rows = kn_rows;
     cnt = cnt_n;
   }
 #pragma unroll
@@ -591,32 +589,28 @@ __global__ __launch_bounds__(64 * kParts, 2) void bwd_dkv_wide_kernel(
   Piece<T> qr[C], gr[C], qc[4][F], gc[4][F];
   int first, cnt, first_n, cnt_n;
   tile_at(kz, first, cnt);
-  {
-    const size_t base = (size_t)__builtin_amdgcn_readfirstlane(first) * D;
-    const uint32_t off = min(l16, max(cnt - 1, 0)) * D + 4 * g;
+  constexpr int B = sizeof(T);
+  int row_at = (l16 * D + 4 * g) * B, col_at = (4 * g * D + 4 * l16) * B;   // rows behind a tile's last real query read as zeros
+  __amdgpu_buffer_rsrc_t q_rows = tile_rows<T, D>(Qh, first, cnt), g_rows = tile_rows<T, D>(Gh, first, cnt);
 #pragma unroll
-    for (int c = 0; c < C; ++c) {
-      qr[c].load(Qh + base + (off + 16 * c));
-      gr[c].load(Gh + base + (off + 16 * c));
-      __builtin_amdgcn_sched_barrier(0);
-    }
+  for (int c = 0; c < C; ++c) {
+    qr[c].load(q_rows, row_at + 16 * c * B);
+    gr[c].load(g_rows, row_at + 16 * c * B);
+    __builtin_amdgcn_sched_barrier(0);
   }
   const float* bk0 = sK + l16 * OST + 4 * g;
   const float* bv0 = sV + l16 * OST + 4 * g;
   for (int t = kz; t < ntiles; t += kParts) {
+    asm volatile("" : "+v"(row_at), "+v"(col_at));   // (opaque here, or their sums leave the loop as registers instead of immediates)
     tile_at(t + kParts, first_n, cnt_n);
-    const int first_s = __builtin_amdgcn_readfirstlane(first);
-    const size_t cbase = (size_t)first_s * D, base = (size_t)__builtin_amdgcn_readfirstlane(first_n) * D;
-    uint32_t col[4];
-    float lse[4], dv[4];
+    const __amdgpu_buffer_rsrc_t qn_rows = tile_rows<T, D>(Qh, first_n, cnt_n), gn_rows = tile_rows<T, D>(Gh, first_n, cnt_n);
+    float lse[4], dv[4];   // (of the tile's last query for those that do not exist: what they give is dropped)
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
-      const uint32_t row = min(4 * g + r, max(cnt - 1, 0));
-      col[r] = row * D + 4 * l16;
-      lse[r] = lseh[first_s + row];
-      dv[r] = dvh[first_s + row];
+      const int row = __builtin_amdgcn_readfirstlane(first) + min(4 * g + r, max(cnt - 1, 0));
+      lse[r] = lseh[row];
+      dv[r] = dvh[row];
     }
-    const uint32_t off = min(l16, max(cnt_n - 1, 0)) * D + 4 * g;
     f32x4 s[NK], p[NK];
 #pragma unroll
     for (int n = 0; n < NK; ++n) s[n] = p[n] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
@@ -638,19 +632,20 @@ __global__ __launch_bounds__(64 * kParts, 2) void bwd_dkv_wide_kernel(
         }
 #pragma unroll
       for (int u = c * 4 * F / C; u < (c + 1) * 4 * F / C; ++u) {
-        gc[u / F][u % F].load(Gh + cbase + (col[u / F] + 64 * (u % F)));
-        qc[u / F][u % F].load(Qh + cbase + (col[u / F] + 64 * (u % F)));
+        gc[u / F][u % F].load(g_rows, col_at + (u / F * D + 64 * (u % F)) * B);
+        qc[u / F][u % F].load(q_rows, col_at + (u / F * D + 64 * (u % F)) * B);
       }
       __builtin_amdgcn_sched_barrier(0);
     }
-    // P and dS; a query that does not exist has probability zero
+    // P and dS; zero for a query that does not exist
 #pragma unroll
     for (int n = 0; n < NK; ++n)
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
-        const float w = 4 * g + r < cnt ? __builtin_amdgcn_exp2f(s[n][r] - lse[r]) : 0.0f;
-        s[n][r] = w;
-        p[n][r] = w * (p[n][r] - dv[r]);
+        const bool real = 4 * g + r < cnt;
+        const float w = __builtin_amdgcn_exp2f(s[n][r] - lse[r]), ds = w * (p[n][r] - dv[r]);
+        s[n][r] = real ? w : 0.0f;
+        p[n][r] = real ? ds : 0.0f;
       }
 #pragma unroll
     for (int u = 0; u < 4 * F; ++u) {
@@ -664,12 +659,14 @@ __global__ __launch_bounds__(64 * kParts, 2) void bwd_dkv_wide_kernel(
         }
 #pragma unroll
       for (int c = u * C / (4 * F); c < (u + 1) * C / (4 * F); ++c) {
-        qr[c].load(Qh + base + (off + 16 * c));
-        gr[c].load(Gh + base + (off + 16 * c));
+        qr[c].load(qn_rows, row_at + 16 * c * B);
+        gr[c].load(gn_rows, row_at + 16 * c * B);
       }
       __builtin_amdgcn_sched_barrier(0);
     }
     first = first_n;
+    q_rows = qn_rows;
+    g_rows = gn_rows;
     cnt = cnt_n;
   }
   __syncthreads();   // K and V are read no more

@@ -78,22 +78,20 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t tile_rows(const T* head, int f
   return __builtin_amdgcn_make_buffer_rsrc(const_cast<T*>(p), 0, __builtin_amdgcn_readfirstlane(cnt) * D * (int)sizeof(T), 0x00020000);
 }
 
-// what a lane keeps of the memory it asked for (four elements, e elements from the buffer's start): the storage type's own
+// what a lane keeps of the memory it asked for (four elements, at a byte offset): the storage type's own
 // words, widened when they are used, so that a tile on its way takes no more registers than it has bytes
 template <typename T> struct Piece;
 template <> struct Piece<float> {
   f32x4 v;
-  __device__ __forceinline__ void load(const float* p) { v = *reinterpret_cast<const f32x4*>(p); }
-  __device__ __forceinline__ void load(__amdgpu_buffer_rsrc_t rows, int e) {
-    v = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(rows, 4 * e, 0, 0));
+  __device__ __forceinline__ void load(__amdgpu_buffer_rsrc_t rows, int at) {
+    v = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(rows, at, 0, 0));
   }
   __device__ __forceinline__ f32x4 get() const { return v; }
 };
 template <> struct Piece<bf16_t> {
   uint2 w;
-  __device__ __forceinline__ void load(const bf16_t* p) { w = *reinterpret_cast<const uint2*>(p); }
-  __device__ __forceinline__ void load(__amdgpu_buffer_rsrc_t rows, int e) {
-    w = __builtin_bit_cast(uint2, __builtin_amdgcn_raw_buffer_load_b64(rows, 2 * e, 0, 0));
+  __device__ __forceinline__ void load(__amdgpu_buffer_rsrc_t rows, int at) {
+    w = __builtin_bit_cast(uint2, __builtin_amdgcn_raw_buffer_load_b64(rows, at, 0, 0));
   }
   __device__ __forceinline__ f32x4 get() const {
     return f32x4{__uint_as_float(w.x << 16), __uint_as_float(w.x & 0xffff0000u), __uint_as_float(w.y << 16),

@@ -72,3 +72,29 @@ def test_a_selected_infinity_stays_one(case):
     V[:, :, n_kv - 1] = INF
     O = _attend(cfg, Q, K, V, idx)
     assert (O[:, :, :2 * bq] == INF).all() and torch.equal(O[:, :, 2 * bq:], want[:, :, 2 * bq:])
+
+
+@pytest.mark.parametrize("bad", [NAN, INF])
+@pytest.mark.parametrize("dtype,d,b", [("f32", 128, 48), ("f32", 64, 40), ("f32", 64, 64), ("bf16", 128, 48), ("bf16", 64, 33), ("bf16", 128, 64)])
+def test_gradients_of_other_blocks(dtype, d, b, bad):
+    """Keys and values of block 0 and queries and output gradients of query block 0 are bad.  Query blocks 1 and 2 select
+    neither, KV blocks 2 and 3 are selected by neither; the last block on either side is short, with empty parts behind it."""
+    n_q, n_kv = 2 * b + 10, 3 * b + 10
+    cfg = hf.make_config(1, 2, d, dtype, b, b, 0.5)
+    Q, K, V, dO = _inputs(dtype, d, n_q, n_kv, 20)
+    idx = _lists([[0, 1], [1, 3], [2, 3]])
+
+    def gradients():
+        out = [torch.full_like(t, 7.0) for t in (Q, K, V)]
+        ws = torch.empty(hf.hf_bwd_workspace_bytes(cfg, n_q, n_kv), dtype=torch.uint8, device=DEV)
+        hf.hf_hybrid_attn_bwd(cfg, Q, K, V, idx, None, dO, *out, ws)
+        torch.cuda.synchronize()
+        return [t[:, :, n:] for t, n in zip(out, (b, 2 * b, 2 * b))]
+
+    want = gradients()
+    K[:, :, :16] = bad
+    V[:, :, :16] = bad
+    Q[:, :, :16] = bad
+    dO[:, :, :16] = bad
+    for name, a, r in zip(("dQ", "dK", "dV"), gradients(), want):
+        assert r.isfinite().all() and torch.equal(a, r), name
