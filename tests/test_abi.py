@@ -366,3 +366,9 @@ def test_length_of_a_packed_window_is_compared_not_truncated(lib, n_kv):
     K = torch.zeros((1, 1, 7, 128), dtype=torch.bfloat16)   # (its length is looked at before its device)
     with pytest.raises(ValueError, match="n_kv differs"):
         hf.hf_pool_keys(cfg, K, None, n_kv=n_kv)
+
+
+@pytest.mark.parametrize("n_frames", [3.5, 3.0, "3"])
+def test_rope_window_indices_take_whole_numbers_of_frames(lib, n_frames):
+    with pytest.raises(TypeError):
+        hf.hf_rope_window_indices(30, n_frames, 21)
