@@ -360,7 +360,7 @@ PyObject* step_fwd(Args a) {
 
 PyObject* rope_window_indices(Args a) {   // i_newest, n_frames, t0
   const int n = index(a[1]);
-  std::vector<int32_t> out(n > 0 ? n : 0);
+  std::vector<int32_t> out(n > 0 ? n : 1);   // (an empty one has no address: the library would name that, not the number)
   check(lib.hf_rope_window_indices(to_int(a[0]), n, to_int(a[2]), out.data()));
   PyObject* list = PyList_New(n);
   if (!list) throw Raised();

@@ -372,3 +372,9 @@ def test_length_of_a_packed_window_is_compared_not_truncated(lib, n_kv):
 def test_rope_window_indices_take_whole_numbers_of_frames(lib, n_frames):
     with pytest.raises(TypeError):
         hf.hf_rope_window_indices(30, n_frames, 21)
+
+
+def test_rope_window_indices_of_no_frames_name_their_number(lib):
+    with pytest.raises(hf.HFError, match="n_frames") as e:
+        hf.hf_rope_window_indices(30, 0, 21)
+    assert e.value.code == -2
