@@ -152,7 +152,10 @@ struct Config : Struct<hf_config> {
     B = get()->batch;
     H = get()->heads;
     D = get()->head_dim;
-    if (get()->block_q < 1 || get()->block_kv < 1) raise(PyExc_ValueError, "block sizes must be >= 1");
+    if (get()->block_q < 1 || get()->block_kv < 1) {   // (t_m and t_n divide by them): the library's own error
+      size_t n = 0;
+      check(lib.hf_state_bytes(get(), &n));
+    }
   }
   void* tokens(PyObject* o, const char* name, int64_t n) const { return ptr(o, name, type, {B, H, n, D}); }
   float* table(PyObject* o, const char* name, int64_t n) const { return f32(o, name, {n, D / 2}); }

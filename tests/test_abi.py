@@ -378,3 +378,13 @@ def test_rope_window_indices_of_no_frames_name_their_number(lib):
     with pytest.raises(hf.HFError, match="n_frames") as e:
         hf.hf_rope_window_indices(30, 0, 21)
     assert e.value.code == -2
+
+
+@pytest.mark.parametrize("kw", [dict(block_q=0), dict(block_kv=0), dict(block_q=-64)])
+def test_bad_block_sizes_are_the_librarys_error_in_every_call(lib, kw):
+    cfg = hf.make_config(**{**dict(batch=1, heads=1, head_dim=128, dtype="bf16", block_q=64, block_kv=64), **kw})
+    x = torch.zeros((1, 1, 64, 128), dtype=torch.bfloat16)
+    for call in (lambda: hf.hf_state_init(cfg, None), lambda: hf.hf_pool_keys(cfg, x, None), lambda: hf.hf_hybrid_attn_fwd(cfg, x, x, x, None, None, x)):
+        with pytest.raises(hf.HFError, match="block sizes") as e:
+            call()
+        assert e.value.code == -2
