@@ -139,7 +139,8 @@ def load():
         from . import _marshal
     except ImportError as e:
         raise RuntimeError(f"the marshalling module does not load ({e}): build it with `python -m paper_2604_10103_amd.build`") from e
-    _marshal.bind({name: ctypes.cast(getattr(lib, name), ctypes.c_void_p).value for name in _marshal.entry_names()}, HFError)
+    _marshal.bind({name: ctypes.cast(getattr(lib, name), ctypes.c_void_p).value for name in _marshal.entry_names()}, HFError,
+                  hf_config, hf_window, hf_ring)
     _lib, _native = lib, _marshal
     return lib
 

@@ -49,18 +49,16 @@ void check(int code) {
   throw Raised();
 }
 
+// the binding's class of a structure
+template <class T> struct Class { static PyTypeObject* type; };
+template <class T> PyTypeObject* Class<T>::type = nullptr;
+
 // the memory of a ctypes structure
 template <class T> struct Struct {
   Py_buffer b;
   Struct(PyObject* o, const char* name) {
-    if (PyObject_GetBuffer(o, &b, PyBUF_WRITABLE) < 0) {
-      PyErr_Clear();
-      raise(PyExc_TypeError, "%s must be an %s structure, got %s", name, name, Py_TYPE(o)->tp_name);
-    }
-    if (b.len != (Py_ssize_t)sizeof(T)) {
-      PyBuffer_Release(&b);
-      raise(PyExc_TypeError, "%s must be an %s structure, got %s", name, name, Py_TYPE(o)->tp_name);
-    }
+    if (!PyObject_TypeCheck(o, Class<T>::type)) raise(PyExc_TypeError, "%s must be an %s structure, got %s", name, name, Py_TYPE(o)->tp_name);
+    if (PyObject_GetBuffer(o, &b, PyBUF_WRITABLE) < 0) throw Raised();
   }
   Struct(const Struct&) = delete;
   ~Struct() { PyBuffer_Release(&b); }
@@ -504,7 +502,7 @@ PyObject* hybrid_attn_bwd_saved(Args a) {
   return none();
 }
 
-// bind(addresses by name, HFError)
+// bind(addresses by name, HFError, hf_config, hf_window, hf_ring)
 PyObject* bind(Args a) {
   if (!PyDict_Check(a[0])) raise(PyExc_TypeError, "bind takes a dict of addresses");
   auto address = [&](const char* name) -> void* {
@@ -514,8 +512,16 @@ PyObject* bind(Args a) {
     if (!p) raise(PyExc_ValueError, "no address for %s", name);
     return p;
   };
+  auto structure = [](PyObject* o) {   // (kept for good, like the module)
+    if (!PyType_Check(o)) raise(PyExc_TypeError, "bind takes the structures' classes");
+    Py_INCREF(o);
+    return reinterpret_cast<PyTypeObject*>(o);
+  };
 #define HF_TAKE(name) lib.name = reinterpret_cast<decltype(lib.name)>(address(#name));
   HF_ENTRIES(HF_TAKE)
+  Class<hf_config>::type = structure(a[2]);
+  Class<hf_window>::type = structure(a[3]);
+  Class<hf_ring>::type = structure(a[4]);
   Py_INCREF(a[1]);
   Py_XDECREF(error_class);
   error_class = a[1];
@@ -548,7 +554,7 @@ template <PyObject* (*F)(Args), int N> PyObject* method(PyObject*, PyObject* con
 
 #define HF_METHOD(name, n) {#name, (PyCFunction)(void*)(&method<name, n>), METH_FASTCALL, nullptr}
 PyMethodDef methods[] = {
-    HF_METHOD(bind, 2), HF_METHOD(entry_names, 0), HF_METHOD(state_init, 2), HF_METHOD(state_fold_linear, 4),
+    HF_METHOD(bind, 5), HF_METHOD(entry_names, 0), HF_METHOD(state_init, 2), HF_METHOD(state_fold_linear, 4),
     HF_METHOD(state_planes, 3), HF_METHOD(absorb_evicted, 7), HF_METHOD(absorb_evicted_planes, 8), HF_METHOD(window_evict, 10),
     HF_METHOD(block_select, 8), HF_METHOD(block_select_static, 6), HF_METHOD(hybrid_attn_fwd, 12),
     HF_METHOD(hybrid_attn_fwd_planes, 12), HF_METHOD(hybrid_attn_fwd_save, 14), HF_METHOD(pool_keys, 5),

@@ -388,3 +388,15 @@ def test_bad_block_sizes_are_the_librarys_error_in_every_call(lib, kw):
         with pytest.raises(hf.HFError, match="block sizes") as e:
             call()
         assert e.value.code == -2
+
+
+def test_only_the_bindings_own_structures_are_taken(lib):
+    """Not any writable memory of their size."""
+    cfg = hf.make_config(1, 2, 128, "bf16", 64, 64, 0.25, kv_capacity=300)
+    K = torch.zeros((1, 2, 300, 128), dtype=torch.bfloat16)
+    size = ctypes.sizeof
+    for call in (lambda: hf.hf_state_init(bytearray(size(hf.hf_config)), None),
+                 lambda: hf.hf_stream_open_chunk(cfg, ctypes.c_double(0.0), 100, K, K, None),
+                 lambda: hf.hf_ring_open_chunk(cfg, bytearray(size(hf.hf_ring)), K, K, None)):
+        with pytest.raises(TypeError, match="structure"):
+            call()
