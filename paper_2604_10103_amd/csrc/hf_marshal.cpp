@@ -181,51 +181,53 @@ struct Config : Struct<hf_config> {
   }
 };
 
-// the call itself, without the GIL
-template <class F, class... A> void call(F f, A... a) {
-  int code;
-  Py_BEGIN_ALLOW_THREADS
-  code = f(a...);
-  Py_END_ALLOW_THREADS
-  check(code);
-}
+// the call itself, without the GIL.  A type, not a function: a braced list is evaluated in its order, so of several bad arguments
+// the first is reported, and the stream is asked for behind the checks
+struct call {
+  template <class F, class... A> call(F f, A... a) {
+    int code;
+    Py_BEGIN_ALLOW_THREADS
+    code = f(a...);
+    Py_END_ALLOW_THREADS
+    check(code);
+  }
+};
 
 typedef PyObject* const* Args;
 PyObject* none() { Py_RETURN_NONE; }
 
 PyObject* state_init(Args a) {   // cfg, state
   const Config c(a[0]);
-  call(lib.hf_state_init, c.get(), c.state(a[1], "state"), stream());
+  call{lib.hf_state_init, c.get(), c.state(a[1], "state"), stream()};
   return none();
 }
 
 PyObject* state_fold_linear(Args a) {   // cfg, state_in, W, state_out
   const Config c(a[0]);
-  call(lib.hf_state_fold_linear, c.get(), c.state(a[1], "state_in"), f32(a[2], "W", {c.H, c.D, c.D}), c.state(a[3], "state_out"), stream());
+  call{lib.hf_state_fold_linear, c.get(), c.state(a[1], "state_in"), f32(a[2], "W", {c.H, c.D, c.D}), c.state(a[3], "state_out"), stream()};
   return none();
 }
 
 PyObject* state_planes(Args a) {   // cfg, state, planes_out
   const Config c(a[0]);
-  call(lib.hf_state_planes, c.get(), c.state(a[1], "state"), bytes(a[2], "planes_out"), stream());
+  call{lib.hf_state_planes, c.get(), c.state(a[1], "state"), bytes(a[2], "planes_out"), stream()};
   return none();
 }
 
 PyObject* absorb_evicted(Args a) {   // cfg, state, K_ev, V_ev, rope_cos, rope_sin, workspace
   const Config c(a[0]);
   const int n = (int)length(a[2], "K_ev", 2);
-  void* ws = bytes(a[6], "workspace");
-  call(lib.hf_absorb_evicted, c.get(), c.state(a[1], "state"), c.tokens(a[2], "K_ev", n), c.tokens(a[3], "V_ev", n), n,
-       c.table(a[4], "rope_cos", n), c.table(a[5], "rope_sin", n), ws, size_of(a[6]), stream());
+  call{lib.hf_absorb_evicted, c.get(), c.state(a[1], "state"), c.tokens(a[2], "K_ev", n), c.tokens(a[3], "V_ev", n), n,
+       c.table(a[4], "rope_cos", n), c.table(a[5], "rope_sin", n), bytes(a[6], "workspace"), size_of(a[6]), stream()};
   return none();
 }
 
 PyObject* absorb_evicted_planes(Args a) {   // cfg, state, K_ev, V_ev, planes_out, rope_cos, rope_sin, workspace
   const Config c(a[0]);
   const int n = (int)length(a[2], "K_ev", 2);
-  void* ws = bytes(a[7], "workspace");
-  call(lib.hf_absorb_evicted_planes, c.get(), c.state(a[1], "state"), c.tokens(a[2], "K_ev", n), c.tokens(a[3], "V_ev", n), n,
-       c.table(a[5], "rope_cos", n), c.table(a[6], "rope_sin", n), ws, size_of(a[7]), bytes(a[4], "planes_out"), stream());
+  call{lib.hf_absorb_evicted_planes, c.get(), c.state(a[1], "state"), c.tokens(a[2], "K_ev", n), c.tokens(a[3], "V_ev", n), n,
+       c.table(a[5], "rope_cos", n), c.table(a[6], "rope_sin", n), bytes(a[7], "workspace"), size_of(a[7]),
+       bytes(a[4], "planes_out"), stream()};
   return none();
 }
 
@@ -233,9 +235,9 @@ PyObject* window_evict(Args a) {   // cfg, K_win, V_win, n_evict, state, rope_co
   const Config c(a[0]);
   const int64_t held = length(a[1], "K_win", 2);
   const int n_kv = c.kv_len(held, a[9]), n = to_int(a[3]);
-  void* ws = bytes(a[7], "workspace");
-  call(lib.hf_window_evict, c.get(), c.tokens(a[1], "K_win", held), c.tokens(a[2], "V_win", held), n_kv, to_int(a[8]), n,
-       c.state(a[4], "state"), c.table(a[5], "rope_cos", n), c.table(a[6], "rope_sin", n), ws, size_of(a[7]), stream());
+  call{lib.hf_window_evict, c.get(), c.tokens(a[1], "K_win", held), c.tokens(a[2], "V_win", held), n_kv, to_int(a[8]), n,
+       c.state(a[4], "state"), c.table(a[5], "rope_cos", n), c.table(a[6], "rope_sin", n),
+       bytes(a[7], "workspace"), size_of(a[7]), stream()};
   return none();
 }
 
@@ -248,8 +250,8 @@ PyObject* block_select(Args a) {   // cfg, Q, K_win, n_cached or None, block_idx
   const void *q = c.tokens(a[1], "Q", n_q), *kw = c.tokens(a[2], "K_win", held);
   int32_t* idx = i32(a[4], "block_idx", {c.B, c.H, c.t_m(n_q), k});
   float* sc = f32(a[5], "scores", {c.B, c.H, c.t_m(n_q), c.t_n(n_kv)});
-  if (a[3] == Py_None) call(lib.hf_block_select, c.get(), q, n_q, kw, n_kv, idx, sc, ws, size_of(a[6]), stream());
-  else call(lib.hf_block_select_cached, c.get(), q, n_q, kw, n_kv, to_int(a[3]), idx, sc, ws, size_of(a[6]), stream());
+  if (a[3] == Py_None) call{lib.hf_block_select, c.get(), q, n_q, kw, n_kv, idx, sc, ws, size_of(a[6]), stream()};
+  else call{lib.hf_block_select_cached, c.get(), q, n_q, kw, n_kv, to_int(a[3]), idx, sc, ws, size_of(a[6]), stream()};
   return none();
 }
 
@@ -258,8 +260,8 @@ PyObject* block_select_static(Args a) {   // cfg, Q, K_win, block_idx, scores, n
   const int n_q = (int)length(a[1], "Q", 2);
   const int64_t held = length(a[2], "K_win", 2);
   const int n_kv = c.kv_len(held, a[5]), k = c.select_k(n_kv);
-  call(lib.hf_block_select_static, c.get(), c.tokens(a[1], "Q", n_q), n_q, c.tokens(a[2], "K_win", held), n_kv,
-       i32(a[3], "block_idx", {c.B, c.H, c.t_m(n_q), k}), f32(a[4], "scores", {c.B, c.H, c.t_m(n_q), c.t_n(n_kv)}), stream());
+  call{lib.hf_block_select_static, c.get(), c.tokens(a[1], "Q", n_q), n_q, c.tokens(a[2], "K_win", held), n_kv,
+       i32(a[3], "block_idx", {c.B, c.H, c.t_m(n_q), k}), f32(a[4], "scores", {c.B, c.H, c.t_m(n_q), c.t_n(n_kv)}), stream()};
   return none();
 }
 
@@ -291,29 +293,29 @@ PyObject* hybrid_attn_fwd(Args a) {   // cfg, Q, K_win, V_win, block_idx, state,
   const float *st = c.state(a[5], "state"), *cs = c.table(a[8], "rope_cos_q", t.n_q), *sn = c.table(a[9], "rope_sin_q", t.n_q);
   void *o = c.tokens(a[6], "O", t.n_q), *ws = bytes(a[7], "workspace");
   if (a[10] == Py_None)
-    call(lib.hf_hybrid_attn_fwd, c.get(), t.q, t.n_q, t.kw, t.vw, t.n_kv, t.idx, t.k, st, cs, sn, o, ws, size_of(a[7]), stream());
+    call{lib.hf_hybrid_attn_fwd, c.get(), t.q, t.n_q, t.kw, t.vw, t.n_kv, t.idx, t.k, st, cs, sn, o, ws, size_of(a[7]), stream()};
   else
-    call(lib.hf_hybrid_attn_fwd_split, c.get(), t.q, t.q_hist, t.n_q, t.kw, t.vw, t.n_kv, t.idx, t.k, st, cs, sn, o, ws,
-         size_of(a[7]), stream());
+    call{lib.hf_hybrid_attn_fwd_split, c.get(), t.q, t.q_hist, t.n_q, t.kw, t.vw, t.n_kv, t.idx, t.k, st, cs, sn, o, ws,
+         size_of(a[7]), stream()};
   return none();
 }
 
 PyObject* hybrid_attn_fwd_planes(Args a) {   // cfg, Q, K_win, V_win, block_idx, state, planes, O, rope_cos_q, rope_sin_q, Q_hist, n_kv
   const Config c(a[0]);
   const Attn t(c, a[1], a[2], a[3], a[4], a[10], a[11]);
-  call(lib.hf_hybrid_attn_fwd_planes, c.get(), t.q, t.q_hist, t.n_q, t.kw, t.vw, t.n_kv, t.idx, t.k, c.state(a[5], "state"),
+  call{lib.hf_hybrid_attn_fwd_planes, c.get(), t.q, t.q_hist, t.n_q, t.kw, t.vw, t.n_kv, t.idx, t.k, c.state(a[5], "state"),
        bytes(a[6], "planes"), c.table(a[8], "rope_cos_q", t.n_q), c.table(a[9], "rope_sin_q", t.n_q), c.tokens(a[7], "O", t.n_q),
-       stream());
+       stream()};
   return none();
 }
 
 PyObject* hybrid_attn_fwd_save(Args a) {   // cfg, Q, K_win, V_win, block_idx, state, O, O_local_out, lse2_out, workspace, cos, sin, Q_hist, n_kv
   const Config c(a[0]);
   const Attn t(c, a[1], a[2], a[3], a[4], a[12], a[13]);
-  void* ws = bytes(a[9], "workspace");
-  call(lib.hf_hybrid_attn_fwd_save, c.get(), t.q, t.q_hist, t.n_q, t.kw, t.vw, t.n_kv, t.idx, t.k, c.state(a[5], "state"),
+  call{lib.hf_hybrid_attn_fwd_save, c.get(), t.q, t.q_hist, t.n_q, t.kw, t.vw, t.n_kv, t.idx, t.k, c.state(a[5], "state"),
        c.table(a[10], "rope_cos_q", t.n_q), c.table(a[11], "rope_sin_q", t.n_q), c.tokens(a[6], "O", t.n_q),
-       c.tokens(a[7], "O_local_out", t.n_q), f32(a[8], "lse2_out", {c.B * c.H, t.n_q}), ws, size_of(a[9]), stream());
+       c.tokens(a[7], "O_local_out", t.n_q), f32(a[8], "lse2_out", {c.B * c.H, t.n_q}),
+       bytes(a[9], "workspace"), size_of(a[9]), stream()};
   return none();
 }
 
@@ -321,7 +323,7 @@ PyObject* pool_keys(Args a) {   // cfg, K_win, pooled_K, n_cached_kv_blocks, n_k
   const Config c(a[0]);
   const int64_t held = length(a[1], "K_win", 2);
   const int n_kv = c.kv_len(held, a[4]);
-  call(lib.hf_pool_keys, c.get(), c.tokens(a[1], "K_win", held), n_kv, index(a[3]), bytes(a[2], "pooled_K"), stream());
+  call{lib.hf_pool_keys, c.get(), c.tokens(a[1], "K_win", held), n_kv, index(a[3]), bytes(a[2], "pooled_K"), stream()};
   return none();
 }
 
@@ -337,9 +339,9 @@ PyObject* select_attn_fwd(Args a) {   // cfg, Q, K_win, V_win, pooled_K, state, 
   const Config c(a[0]);
   const Attn t(c, a[1], a[2], a[3], Py_None, a[12], a[13]);
   int32_t* idx = list_out(c, a[8], t.n_q, t.n_kv);
-  call(lib.hf_select_attn_fwd, c.get(), t.q, t.q_hist, t.n_q, t.kw, t.vw, t.n_kv, bytes(a[4], "pooled_K"), c.state(a[5], "state"),
+  call{lib.hf_select_attn_fwd, c.get(), t.q, t.q_hist, t.n_q, t.kw, t.vw, t.n_kv, bytes(a[4], "pooled_K"), c.state(a[5], "state"),
        bytes(a[6], "planes"), c.table(a[10], "rope_cos_q", t.n_q), c.table(a[11], "rope_sin_q", t.n_q), c.tokens(a[7], "O", t.n_q),
-       idx, f32(a[9], "scores", {c.B, c.H, c.t_m(t.n_q), c.t_n(t.n_kv)}), stream());
+       idx, f32(a[9], "scores", {c.B, c.H, c.t_m(t.n_q), c.t_n(t.n_kv)}), stream()};
   return none();
 }
 
@@ -350,12 +352,12 @@ PyObject* step_fwd(Args a) {
   const Attn t(c, a[1], a[2], a[3], Py_None, a[17], a[18]);
   int32_t* idx = list_out(c, a[8], t.n_q, t.n_kv);
   const int ev_stride = (int)length(a[9], "K_ev", 2), n_ev = a[19] == Py_None ? ev_stride : to_int(a[19]);
-  void* ws = bytes(a[13], "workspace");
-  call(lib.hf_step_fwd, c.get(), t.q, t.q_hist, t.n_q, t.kw, t.vw, t.n_kv, bytes(a[4], "pooled_K"), c.state(a[5], "state_in"),
+  call{lib.hf_step_fwd, c.get(), t.q, t.q_hist, t.n_q, t.kw, t.vw, t.n_kv, bytes(a[4], "pooled_K"), c.state(a[5], "state_in"),
        bytes(a[6], "planes"), c.table(a[15], "rope_cos_q", t.n_q), c.table(a[16], "rope_sin_q", t.n_q), c.tokens(a[7], "O", t.n_q),
        idx, f32(a[14], "scores", {c.B, c.H, c.t_m(t.n_q), c.t_n(t.n_kv)}), c.tokens(a[9], "K_ev", ev_stride),
-       c.tokens(a[10], "V_ev", ev_stride), n_ev, ev_stride, c.state(a[11], "state_out"), bytes(a[12], "planes_out"), ws,
-       size_of(a[13]), stream());
+       c.tokens(a[10], "V_ev", ev_stride), n_ev, ev_stride, c.state(a[11], "state_out"), bytes(a[12], "planes_out"),
+       bytes(a[13], "workspace"),
+       size_of(a[13]), stream()};
   return none();
 }
 
@@ -391,8 +393,8 @@ PyObject* rope_tables(Args a) {   // frame_idx, height, width, pairs, cos_out, s
   const int temporal = PyObject_IsTrue(a[7]);
   if (temporal < 0) throw Raised();
   const int64_t rows = (int64_t)frames.size() * height * width, cols = (int64_t)pairs[0] + pairs[1] + pairs[2];
-  call(lib.hf_rope_tables, frames.data(), (int)frames.size(), height, width, pairs[0], pairs[1], pairs[2], theta, temporal,
-       f32(a[4], "cos_out", {rows, cols}), f32(a[5], "sin_out", {rows, cols}), stream());
+  call{lib.hf_rope_tables, frames.data(), (int)frames.size(), height, width, pairs[0], pairs[1], pairs[2], theta, temporal,
+       f32(a[4], "cos_out", {rows, cols}), f32(a[5], "sin_out", {rows, cols}), stream()};
   return none();
 }
 
@@ -401,16 +403,16 @@ PyObject* rope_append_keys(Args a) {   // cfg, K_new, rope_cos, rope_sin, K_win,
   const int n = (int)length(a[1], "K_new", 2);
   const int64_t held = length(a[4], "K_win", 2);
   const int n_kv = c.kv_len(held, a[7]);
-  call(lib.hf_rope_append_keys, c.get(), c.tokens(a[1], "K_new", n), n, c.table(a[2], "rope_cos", n), c.table(a[3], "rope_sin", n),
-       c.tokens(a[4], "K_win", held), index(a[5]), n_kv, bytes(a[6], "pooled_K"), stream());
+  call{lib.hf_rope_append_keys, c.get(), c.tokens(a[1], "K_new", n), n, c.table(a[2], "rope_cos", n), c.table(a[3], "rope_sin", n),
+       c.tokens(a[4], "K_win", held), index(a[5]), n_kv, bytes(a[6], "pooled_K"), stream()};
   return none();
 }
 
 PyObject* rope_apply(Args a) {   // cfg, X, rope_cos, rope_sin, Y
   const Config c(a[0]);
   const int n = (int)length(a[1], "X", 2);
-  call(lib.hf_rope_apply, c.get(), c.tokens(a[1], "X", n), n, c.table(a[2], "rope_cos", n), c.table(a[3], "rope_sin", n),
-       c.tokens(a[4], "Y", n), stream());
+  call{lib.hf_rope_apply, c.get(), c.tokens(a[1], "X", n), n, c.table(a[2], "rope_cos", n), c.table(a[3], "rope_sin", n),
+       c.tokens(a[4], "Y", n), stream()};
   return none();
 }
 
@@ -420,10 +422,10 @@ PyObject* stream_open_chunk(Args a) {   // cfg, win, n_chunk, K_win, V_win, stat
   const int cap = c->kv_capacity, n = to_int(a[2]);
   const int64_t over = (int64_t)win->n_tokens + n > cap ? (int64_t)win->n_tokens + n - cap : 0;
   int32_t first = -1, n_ev = -1;
-  void* ws = bytes(a[8], "workspace");
-  call(lib.hf_stream_open_chunk, c.get(), win.get(), n, c.tokens(a[3], "K_win", cap), c.tokens(a[4], "V_win", cap),
-       c.state(a[5], "state"), c.table(a[6], "rope_cos_ev", over), c.table(a[7], "rope_sin_ev", over), ws, size_of(a[8]), &first,
-       &n_ev, stream());
+  call{lib.hf_stream_open_chunk, c.get(), win.get(), n, c.tokens(a[3], "K_win", cap), c.tokens(a[4], "V_win", cap),
+       c.state(a[5], "state"), c.table(a[6], "rope_cos_ev", over), c.table(a[7], "rope_sin_ev", over),
+       bytes(a[8], "workspace"), size_of(a[8]), &first,
+       &n_ev, stream()};
   return Py_BuildValue("ii", first, n_ev);
 }
 
@@ -431,11 +433,11 @@ PyObject* stream_step(Args a) {   // cfg, win, Q, K_win, V_win, step_in_chunk, b
   const Config c(a[0]);
   const Struct<hf_window> win(a[1], "hf_window");
   const int cap = c->kv_capacity, n_q = (int)length(a[2], "Q", 2), k = c.select_k(win->n_tokens);
-  void* ws = bytes(a[9], "workspace");
-  call(lib.hf_stream_step, c.get(), win.get(), c.tokens(a[2], "Q", n_q), c.tokens(a[12], "Q_hist", n_q), n_q,
+  call{lib.hf_stream_step, c.get(), win.get(), c.tokens(a[2], "Q", n_q), c.tokens(a[12], "Q_hist", n_q), n_q,
        c.tokens(a[3], "K_win", cap), c.tokens(a[4], "V_win", cap), to_int(a[5]), i32(a[6], "block_idx", {c.B, c.H, c.t_m(n_q), k}),
-       c.state(a[7], "state"), c.table(a[10], "rope_cos_q", n_q), c.table(a[11], "rope_sin_q", n_q), c.tokens(a[8], "O", n_q), ws,
-       size_of(a[9]), stream());
+       c.state(a[7], "state"), c.table(a[10], "rope_cos_q", n_q), c.table(a[11], "rope_sin_q", n_q), c.tokens(a[8], "O", n_q),
+       bytes(a[9], "workspace"),
+       size_of(a[9]), stream()};
   return none();
 }
 
@@ -444,10 +446,10 @@ PyObject* ring_open_chunk(Args a) {   // cfg, ring, K_cache, V_cache, state, rop
   const Struct<hf_ring> ring(a[1], "hf_ring");
   const int cap = c->kv_capacity, n = ring->n_chunk;
   int32_t first = -1, n_ev = -1;
-  void* ws = bytes(a[7], "workspace");
-  call(lib.hf_ring_open_chunk, c.get(), ring.get(), c.tokens(a[2], "K_cache", cap), c.tokens(a[3], "V_cache", cap),
-       c.state(a[4], "state"), c.table(a[5], "rope_cos_ev", n), c.table(a[6], "rope_sin_ev", n), ws, size_of(a[7]), &first, &n_ev,
-       stream());
+  call{lib.hf_ring_open_chunk, c.get(), ring.get(), c.tokens(a[2], "K_cache", cap), c.tokens(a[3], "V_cache", cap),
+       c.state(a[4], "state"), c.table(a[5], "rope_cos_ev", n), c.table(a[6], "rope_sin_ev", n),
+       bytes(a[7], "workspace"), size_of(a[7]), &first, &n_ev,
+       stream()};
   return Py_BuildValue("ii", first, n_ev);
 }
 
@@ -455,11 +457,10 @@ PyObject* ring_step(Args a) {   // cfg, ring, Q, K_cache, V_cache, step_in_chunk
   const Config c(a[0]);
   const Struct<hf_ring> ring(a[1], "hf_ring");
   const int cap = c->kv_capacity, n_q = ring->n_chunk, k = c.select_k(ring->n_sink + ring->n_filled * ring->n_chunk);
-  void* ws = bytes(a[9], "workspace");
-  call(lib.hf_ring_step, c.get(), ring.get(), c.tokens(a[2], "Q", n_q), c.tokens(a[12], "Q_hist", n_q),
+  call{lib.hf_ring_step, c.get(), ring.get(), c.tokens(a[2], "Q", n_q), c.tokens(a[12], "Q_hist", n_q),
        c.tokens(a[3], "K_cache", cap), c.tokens(a[4], "V_cache", cap), to_int(a[5]),
        i32(a[6], "block_idx", {c.B, c.H, c.t_m(n_q), k}), c.state(a[7], "state"), c.table(a[10], "rope_cos_q", n_q),
-       c.table(a[11], "rope_sin_q", n_q), c.tokens(a[8], "O", n_q), ws, size_of(a[9]), stream());
+       c.table(a[11], "rope_sin_q", n_q), c.tokens(a[8], "O", n_q), bytes(a[9], "workspace"), size_of(a[9]), stream()};
   return none();
 }
 
@@ -470,23 +471,24 @@ PyObject* ring_last_step(Args a) {
   const Struct<hf_ring> ring(a[1], "hf_ring");
   const int cap = c->kv_capacity, n_q = ring->n_chunk, k = c.select_k(ring->n_sink + ring->n_filled * ring->n_chunk);
   int32_t done = 0;
-  void *ws = bytes(a[9], "workspace"), *sws = bytes(a[11], "step_workspace");
-  call(lib.hf_ring_last_step, c.get(), ring.get(), c.tokens(a[2], "Q", n_q), c.tokens(a[14], "Q_hist", n_q),
+  call{lib.hf_ring_last_step, c.get(), ring.get(), c.tokens(a[2], "Q", n_q), c.tokens(a[14], "Q_hist", n_q),
        c.tokens(a[3], "K_cache", cap), c.tokens(a[4], "V_cache", cap), index(a[5]),
        i32(a[6], "block_idx", {c.B, c.H, c.t_m(n_q), k}), c.state(a[7], "state"), c.table(a[12], "rope_cos_q", n_q),
-       c.table(a[13], "rope_sin_q", n_q), c.tokens(a[8], "O", n_q), ws, size_of(a[9]), c.state(a[10], "state_out"),
-       c.table(a[15], "rope_cos_ev", n_q), c.table(a[16], "rope_sin_ev", n_q), sws, size_of(a[11]), &done, stream());
+       c.table(a[13], "rope_sin_q", n_q), c.tokens(a[8], "O", n_q), bytes(a[9], "workspace"),
+       size_of(a[9]), c.state(a[10], "state_out"),
+       c.table(a[15], "rope_cos_ev", n_q), c.table(a[16], "rope_sin_ev", n_q), bytes(a[11], "step_workspace"),
+       size_of(a[11]), &done, stream()};
   return PyBool_FromLong(done);
 }
 
 PyObject* hybrid_attn_bwd(Args a) {   // cfg, Q, K_win, V_win, block_idx, state, dO, dQ, dK, dV, workspace, cos, sin, Q_hist, dQ_hist, n_kv
   const Config c(a[0]);
   const Attn t(c, a[1], a[2], a[3], a[4], a[13], a[15]);
-  void* ws = bytes(a[10], "workspace");
-  call(lib.hf_hybrid_attn_bwd, c.get(), t.q, t.q_hist, t.n_q, t.kw, t.vw, t.n_kv, t.idx, t.k, c.state(a[5], "state"),
+  call{lib.hf_hybrid_attn_bwd, c.get(), t.q, t.q_hist, t.n_q, t.kw, t.vw, t.n_kv, t.idx, t.k, c.state(a[5], "state"),
        c.table(a[11], "rope_cos_q", t.n_q), c.table(a[12], "rope_sin_q", t.n_q), c.tokens(a[6], "dO", t.n_q),
-       c.tokens(a[7], "dQ", t.n_q), c.tokens(a[14], "dQ_hist", t.n_q), c.tokens(a[8], "dK", t.held), c.tokens(a[9], "dV", t.held), ws,
-       size_of(a[10]), stream());
+       c.tokens(a[7], "dQ", t.n_q), c.tokens(a[14], "dQ_hist", t.n_q), c.tokens(a[8], "dK", t.held), c.tokens(a[9], "dV", t.held),
+       bytes(a[10], "workspace"),
+       size_of(a[10]), stream()};
   return none();
 }
 
@@ -494,11 +496,11 @@ PyObject* hybrid_attn_bwd(Args a) {   // cfg, Q, K_win, V_win, block_idx, state,
 PyObject* hybrid_attn_bwd_saved(Args a) {
   const Config c(a[0]);
   const Attn t(c, a[1], a[2], a[3], a[4], a[15], a[17]);
-  void* ws = bytes(a[12], "workspace");
-  call(lib.hf_hybrid_attn_bwd_saved, c.get(), t.q, t.q_hist, t.n_q, t.kw, t.vw, t.n_kv, t.idx, t.k, c.state(a[5], "state"),
+  call{lib.hf_hybrid_attn_bwd_saved, c.get(), t.q, t.q_hist, t.n_q, t.kw, t.vw, t.n_kv, t.idx, t.k, c.state(a[5], "state"),
        c.table(a[13], "rope_cos_q", t.n_q), c.table(a[14], "rope_sin_q", t.n_q), c.tokens(a[6], "dO", t.n_q),
        c.tokens(a[7], "O_local", t.n_q), f32(a[8], "lse2", {c.B * c.H, t.n_q}), c.tokens(a[9], "dQ", t.n_q),
-       c.tokens(a[16], "dQ_hist", t.n_q), c.tokens(a[10], "dK", t.held), c.tokens(a[11], "dV", t.held), ws, size_of(a[12]), stream());
+       c.tokens(a[16], "dQ_hist", t.n_q), c.tokens(a[10], "dK", t.held), c.tokens(a[11], "dV", t.held),
+       bytes(a[12], "workspace"), size_of(a[12]), stream()};
   return none();
 }
 

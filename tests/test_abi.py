@@ -400,3 +400,22 @@ def test_only_the_bindings_own_structures_are_taken(lib):
                  lambda: hf.hf_ring_open_chunk(cfg, bytearray(size(hf.hf_ring)), K, K, None)):
         with pytest.raises(TypeError, match="structure"):
             call()
+
+
+def test_arguments_are_checked_in_their_order_before_the_device_is_asked(lib):
+    cfg = hf.make_config(1, 2, 128, "bf16", 64, 64, 0.25, kv_capacity=300)
+    K, st = torch.zeros((1, 2, 300, 128), dtype=torch.bfloat16), torch.zeros(hf.hf_state_bytes(cfg) // 4)
+
+    class Mine(hf.hf_window):   # (a subclass of a structure is one)
+        pass
+
+    for call, first in ((lambda: hf.hf_state_init(cfg, st), "state"),
+                        (lambda: hf.hf_absorb_evicted(cfg, st, K, K, workspace=K), "state"),
+                        (lambda: hf.hf_absorb_evicted(cfg, None, K, K, workspace=K), "K_ev"),
+                        (lambda: hf.hf_pool_keys(cfg, K, st, n_kv=100), "K_win"),
+                        (lambda: hf.hf_block_select(cfg, K, K, K, workspace=st, n_kv=100), "workspace"),
+                        (lambda: hf.hf_hybrid_attn_fwd(cfg, K, K, K, None, None, K, st, n_kv=100), "Q"),
+                        (lambda: hf.hf_stream_open_chunk(cfg, Mine(100, 100), 100, K, K, None), "K_win"),
+                        (lambda: hf.hf_hybrid_attn_bwd(cfg, K, K, K, None, None, K, K, K, K, st, n_kv=100), "Q")):
+        with pytest.raises(TypeError, match=f"^{first} must be a GPU tensor"):
+            call()
