@@ -308,6 +308,8 @@ def hf_probe_mfma_bf16(iters: int, scratch) -> float:
     flops = ctypes.c_double(0.0)
     if not scratch.is_cuda or scratch.dtype != torch.float32:
         raise TypeError("scratch must be a float32 GPU tensor")
+    if not scratch.is_contiguous():
+        raise ValueError("scratch must be contiguous")
     _check(load().hf_probe_mfma_bf16(int(iters), scratch.data_ptr(), ctypes.byref(flops),
                                      torch.cuda.current_stream().cuda_stream))
     return flops.value

@@ -419,3 +419,9 @@ def test_arguments_are_checked_in_their_order_before_the_device_is_asked(lib):
                         (lambda: hf.hf_hybrid_attn_bwd(cfg, K, K, K, None, None, K, K, K, K, st, n_kv=100), "Q")):
         with pytest.raises(TypeError, match=f"^{first} must be a GPU tensor"):
             call()
+
+
+@pytest.mark.gpu
+def test_the_issue_rate_probe_refuses_strided_scratch(lib):
+    with pytest.raises(ValueError, match="contiguous"):
+        hf.hf_probe_mfma_bf16(1, torch.zeros((4096, 2), dtype=torch.float32, device="cuda:0")[:, 0])
