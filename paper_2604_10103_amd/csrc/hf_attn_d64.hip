@@ -317,6 +317,45 @@ __global__ __launch_bounds__(128 * KS, 4) void attn_d64_kernel(
       for (int e = 0; e < 4; ++e) os[4 * rq + e] = fmaf(x[e], w, os[4 * rq + e]);
     }
   }
+  // ---- a selected infinity: the small terms of the split made NaN of it (0 inf, inf - inf).  What is not finite is summed again,
+  // p v in fp32; where the weights themselves are not finite NaN is right.  (rolled, and never reached on finite inputs)
+  bool bad = false;
+#pragma unroll
+  for (int r = 0; r < 16; ++r) bad |= !(fabsf(os[r]) < INFINITY);
+  if (__any(bad && l_tot < INFINITY)) {
+    f32x16 again = {};
+    int at_lane = lane;
+    asm volatile("" : "+v"(at_lane));   // (opaque: addresses of its own, or those of the prologue stay in registers through the loop)
+    const int half = at_lane >> 5;
+    const bf16_t* qp = Q + ((size_t)bh * n_q + min(row0 + 32 * wr + (at_lane & 31), n_q - 1)) * D + 8 * half;
+#pragma unroll 1
+    for (int sel = 0; sel < nsel; ++sel) {
+      const int jb = __builtin_amdgcn_readfirstlane(row_idx ? row_idx[sel] : sel);
+      if ((unsigned)jb >= (unsigned)t_n) continue;
+      const int end = min(n_kv, (jb + 1) * bkv);
+#pragma unroll 1
+      for (int key = jb * bkv; key < end; ++key) {
+        const size_t at = ((size_t)bh * kv_stride + key) * D;
+        float dot = 0.0f;
+#pragma unroll 1
+        for (int s = 0; s < 8; ++s) {   // features 16 (s / 2) + 8 h + 4 (s % 2) .. + 4
+          const int f = 16 * (s >> 1) + 4 * (s & 1);
+          const f32x4 x = load4<bf16_t>(qp + f), y = load4<bf16_t>(K + at + 8 * half + f);
+#pragma unroll
+          for (int e = 0; e < 4; ++e) dot = fmaf(x[e], y[e], dot);
+        }
+        const float p = __builtin_amdgcn_exp2f(fmaf(both_halves_sum(dot), c_scale, -m_use));
+#pragma unroll
+        for (int rq = 0; rq < 4; ++rq) {
+          const f32x4 v = load4<bf16_t>(V + at + 32 * grp + 8 * rq + 4 * half);
+#pragma unroll
+          for (int e = 0; e < 4; ++e) again[4 * rq + e] = fmaf(p, v[e], again[4 * rq + e]);
+        }
+      }
+    }
+#pragma unroll
+    for (int r = 0; r < 16; ++r) os[r] = fabsf(os[r]) < INFINITY ? os[r] : again[r];
+  }
   float w = l_tot > 0.0f ? 1.0f / l_tot : 0.0f;   // a row without a single real key: O_local = 0
   if (hist.L) {
     // ---- O += R(phi(q)) L / (z_scale phi(q).z + eps) (Eq. 3, 6) on the fp32 matrix instruction, whose results lie as those

@@ -74,6 +74,38 @@ def test_a_selected_infinity_stays_one(case):
     assert (O[:, :, :2 * bq] == INF).all() and torch.equal(O[:, :, 2 * bq:], want[:, :, 2 * bq:])
 
 
+@pytest.mark.parametrize("case,head_stride", [("d64", 0), ("d64_short", 400)])
+def test_a_selected_infinity_at_head_dim_64(case, head_stride):
+    """Probabilities are split into terms of which some are zero or negative: no NaN comes of an infinite value.  Features 3
+    and 40 (one of either group of wavefronts) of two keys; the other features and the rows of other blocks keep their bits."""
+    dtype, d, bq, bkv, n_kv, _ = FORWARD[case]
+    n_q = 2 * bq + 5
+    cfg = hf.make_config(1, 2, d, dtype, bq, bkv, 0.5, kv_capacity=head_stride)
+    Q, K, V, Qh = _inputs(dtype, d, n_q, head_stride or n_kv, 30)
+    st = torch.empty(hf.hf_state_bytes(cfg) // 4, dtype=torch.float32, device=DEV)
+    hf.hf_state_init(cfg, st)
+    hf.hf_absorb_evicted(cfg, st, Qh[:, :, :bq].contiguous(), Q[:, :, :bq].contiguous())
+    last = (n_kv - 1) // bkv
+    idx = _lists([[0, last], [last, 2], [0, 1]])
+
+    def attend():
+        O = torch.full_like(Q, 7.0)
+        ws = torch.empty(max(hf.hf_workspace_bytes(cfg, n_q, n_kv), 256), dtype=torch.uint8, device=DEV)
+        hf.hf_hybrid_attn_fwd(cfg, Q, K, V, idx, st, O, ws, n_kv=n_kv if head_stride else None)
+        torch.cuda.synchronize()
+        return O
+
+    want = attend()
+    V[:, :, n_kv - 1, 3] = INF
+    V[:, :, n_kv - 1, 40] = -INF
+    V[:, 1, 2 * bkv, 40] = INF       # block 2, head 1: rows of query block 1 meet both signs
+    O = attend()
+    same = [f for f in range(d) if f not in (3, 40)]
+    assert torch.equal(O[..., same], want[..., same]) and torch.equal(O[:, :, 2 * bq:], want[:, :, 2 * bq:])
+    assert (O[:, :, :2 * bq, 3] == INF).all()
+    assert (O[:, 0, :2 * bq, 40] == -INF).all() and (O[:, 1, :bq, 40] == -INF).all() and O[:, 1, bq:2 * bq, 40].isnan().all()
+
+
 @pytest.mark.parametrize("bad", [NAN, INF])
 @pytest.mark.parametrize("dtype,d,b", [("f32", 128, 48), ("f32", 64, 40), ("f32", 64, 64), ("bf16", 128, 48), ("bf16", 64, 33), ("bf16", 128, 64)])
 def test_gradients_of_other_blocks(dtype, d, b, bad):
