@@ -1139,7 +1139,7 @@ static int bwd_impl(const hf_config* cfg, const void* Q, const void* Q_hist, int
     // row statistics of the softmax and D = dO . O_local: saved by the forward pass (D then from the once rounded O_local),
     // or from a recomputed one (unrounded); the history branch rides in the dQ kernel's epilogue
     int32_t* order = block_idx && !(cfg->flags & HF_FLAG_DKV_INDEX_ORDER) ? reinterpret_cast<int32_t*>(ws + w.order) : nullptr;
-    HF_TRY(launch_bwd_prep(*cfg, block_idx, k, t_m, t_n, inv_cnt, inv_list, &order, st, ws + w.planes, saved ? dO : nullptr,
+    HF_TRY(launch_bwd_prep(*cfg, block_idx, k, t_m, t_n, inv_cnt, inv_list, order, st, ws + w.planes, saved ? dO : nullptr,
                            O_local, (long long)cfg->batch * cfg->heads * n_q, dvec, s));
     if (!saved) HF_TRY(launch_attn_mfma_stats(*cfg, Q, n_q, K_win, V_win, n_kv, block_idx, k, dO, lse2, dvec, s));
     return launch_bwd_mfma(*cfg, Q, n_q, K_win, V_win, n_kv, block_idx, k, dO, saved ? lse2_saved : lse2, dvec, inv_cnt, inv_list,

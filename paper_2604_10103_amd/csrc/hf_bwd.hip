@@ -98,6 +98,26 @@ __device__ __forceinline__ void selected_by(uint32_t* mask, const PrepArgs& p, i
   __syncthreads();
 }
 
+// bucket[len] = number of items of a length, 0 .. longest -> where they start: exclusive sums from the longest down
+__device__ __forceinline__ void starts_from_longest(int32_t* bucket, int longest) {
+  const int tid = threadIdx.x;
+  if (tid < kWave) {
+    int before = 0;
+    for (int top = longest; top >= 0; top -= kWave) {
+      const int own = top - tid >= 0 ? bucket[top - tid] : 0;
+      int sum = own;
+#pragma unroll
+      for (int o = 1; o < kWave; o <<= 1) {
+        const int up = __shfl_up(sum, o, kWave);
+        if (tid >= o) sum += up;
+      }
+      if (top - tid >= 0) bucket[top - tid] = before + sum - own;
+      before += __shfl(sum, kWave - 1, kWave);
+    }
+  }
+  __syncthreads();
+}
+
 // Launch order of the dK/dV workgroups.  A workgroup's time is proportional to the length of its KV block's list of query
 // blocks, and the lists differ (top-k selection: a binomial spread around t_m k / t_n), while a GPU takes workgroups in index
 // order as slots free up.  Longest first within every XCD's share of the items leaves the short ones to fill the end.  One
@@ -124,22 +144,7 @@ __device__ __forceinline__ void order_share(int32_t* smem, const PrepArgs& p, in
     atomicAdd(&bucket[len], 1);
   }
   __syncthreads();
-  // exclusive sums from the longest down: where each length's items start
-  if (tid < kWave) {
-    int before = 0;
-    for (int top = p.t_m; top >= 0; top -= kWave) {
-      const int own = top - tid >= 0 ? bucket[top - tid] : 0;
-      int sum = own;
-#pragma unroll
-      for (int o = 1; o < kWave; o <<= 1) {
-        const int up = __shfl_up(sum, o, kWave);
-        if (tid >= o) sum += up;
-      }
-      if (top - tid >= 0) bucket[top - tid] = before + sum - own;
-      before += __shfl(sum, kWave - 1, kWave);
-    }
-  }
-  __syncthreads();
+  starts_from_longest(bucket, p.t_m);
   for (int j = tid; j < n; j += kPrepThreads) {
     const uint32_t* m = mask + ((first + j) / p.slabs - b0) * words;
     int entry[3] = {0, 0, 0}, w = 0;
@@ -221,6 +226,35 @@ __global__ __launch_bounds__(kPrepThreads) void bwd_prep_kernel(PrepArgs p) {
 #pragma unroll
   for (int off = 8; off >= 1; off >>= 1) acc += __shfl_xor(acc, off, 16);
   if (row < p.rows && part == 0) p.dots[row] = acc;
+}
+
+// The same order from finished lists, in a launch behind them, where a share's masks do not fit in LDS (long windows).  Lengths
+// go to kLengths buckets, several to one where a list can be longer than that.  Gradients of 8 heads, 1024 query and 1150 KV
+// blocks of 64, k = 64: 5.73 ms in index order, 4.00 with this launch.
+constexpr int kLengths = 8192;
+constexpr int kOrderThreads = 1024;
+__global__ __launch_bounds__(kOrderThreads) void dkv_order_kernel(const int32_t* __restrict__ inv_cnt,
+                                                                  const int32_t* __restrict__ inv_list, int t_m, int slabs,
+                                                                  int items_per_xcd, int total_items, int shift,
+                                                                  int32_t* __restrict__ order) {
+  __shared__ int32_t bucket[kLengths];
+  const int first = blockIdx.x * items_per_xcd, n = min(items_per_xcd, total_items - first), tid = threadIdx.x;
+  if (n <= 0) return;
+  for (int e = tid; e <= t_m >> shift; e += kOrderThreads) bucket[e] = 0;
+  __syncthreads();
+  for (int j = tid; j < n; j += kOrderThreads) atomicAdd(&bucket[inv_cnt[(first + j) / slabs] >> shift], 1);
+  __syncthreads();
+  starts_from_longest(bucket, t_m >> shift);
+  for (int j = tid; j < n; j += kOrderThreads) {
+    const int kvb = (first + j) / slabs, len = inv_cnt[kvb];
+    const int32_t* list = inv_list + (size_t)kvb * t_m;
+    int entry[3];
+#pragma unroll
+    for (int q = 0; q < 3; ++q) entry[q] = q < len ? list[q] : 0;
+    int4* rec = reinterpret_cast<int4*>(order + (size_t)(first + atomicAdd(&bucket[len >> shift], 1)) * kOrderRec);
+    rec[0] = int4{first + j, len, entry[0], entry[1]};
+    rec[1] = int4{entry[2], 0, 0, 0};
+  }
 }
 
 // History branch (Eq. 3) in the dQ kernel's epilogue, as in the bf16 kernel: with f = phi(q), r = R f,
@@ -712,11 +746,12 @@ int launch_bwd_wide(const hf_config& c, const void* Q, int n_q, const void* K, c
 
 }  // namespace
 
-// idx given: the inverse lists; order_inout: where the dK/dV items' launch order goes, NULL on return if it was not formed
-// (a share's lists and ranks have to fit in LDS); state given: planes (bf16, head_dim 128); A given: row dots (likewise).
+// idx given: the inverse lists, and with order given the dK/dV items' launch order; state given: planes (bf16, head_dim 128);
+// A given: row dots (likewise).
 int launch_bwd_prep(const hf_config& c, const int32_t* idx, int k, int t_m, int t_n, int32_t* inv_cnt, int32_t* inv_list,
-                    int32_t** order_inout, const float* state, void* planes, const void* A, const void* B, long long rows,
+                    int32_t* order, const float* state, void* planes, const void* A, const void* B, long long rows,
                     float* dots, hipStream_t s) {
+  constexpr size_t kPrepLds = 150 * 1024;   // granted to the kernel below
   const int BH = c.batch * c.heads;
   PrepArgs p = {};
   p.idx = idx;
@@ -725,30 +760,31 @@ int launch_bwd_prep(const hf_config& c, const int32_t* idx, int k, int t_m, int 
   p.t_n = t_n;
   p.inv_cnt = inv_cnt;
   p.inv_list = inv_list;
-  int32_t* order = order_inout ? *order_inout : nullptr;
-  if (order_inout) *order_inout = nullptr;
   size_t lds = 0;
+  bool order_behind = false;
+  const int slabs = (c.block_kv + 63) / 64;
+  const long long items = (long long)BH * t_n * slabs, share = (items + 7) / 8;
+  if (order && items > (1ll << 29)) { set_error("too many blocks"); return HF_ERR_SHAPE; }
   if (idx) {
-    const size_t words = ((size_t)t_m + 31) / 32;
-    // (the masks of a head in LDS, and a division by k in selected_by that is exact; the kernel of its own takes the rest)
-    if ((size_t)t_n * words * 4 <= 48 * 1024 && (unsigned long long)t_m * k * k < (1ull << 32)) {
+    const size_t words = ((size_t)t_m + 31) / 32, masks = (size_t)t_n * words * 4;
+    const size_t need = ((size_t)share + t_m + 1 + ((size_t)share / slabs + 2) * words) * 4;
+    // (the masks of a head in LDS, and a division by k in selected_by that is exact; the kernel of its own takes the rest:
+    // 4 heads, 512 query and 1024 KV blocks, k = 256, 64 KB of masks: gradients 3.47 ms so, 4.54 through it in index order)
+    if (masks <= kPrepLds && (unsigned long long)t_m * k * k < (1ull << 32)) {
       p.invert_wgs = BH;
-      lds = (size_t)t_n * words * 4;
-      const int slabs = (c.block_kv + 63) / 64;
-      const long long items = (long long)BH * t_n * slabs, share = (items + 7) / 8;
-      const size_t need = ((size_t)share + t_m + 1 + ((size_t)share / slabs + 2) * words) * 4;
-      if (order && need <= 150 * 1024) {
+      lds = masks;
+      if (order && need <= kPrepLds) {
         p.order_wgs = 8;
         p.slabs = slabs;
         p.items_per_xcd = (int)share;
         p.total_items = (int)items;
         p.order = order;
-        *order_inout = order;
         if (need > lds) lds = need;
       }
     } else {
       hipLaunchKernelGGL(invert_index_kernel, dim3((t_n + 3) / 4, BH), dim3(256), 0, s, idx, k, t_m, t_n, inv_cnt, inv_list);
     }
+    order_behind = order && !p.order_wgs;
   }
   if (state) {
     p.plane_wgs = 8 * BH;
@@ -768,10 +804,16 @@ int launch_bwd_prep(const hf_config& c, const int32_t* idx, int k, int t_m, int 
   const long long wgs = p.order_wgs + p.invert_wgs + p.plane_wgs + dot_wgs;
   if (lds > 64 * 1024) {
     static LdsGrant grant;
-    const int rc = grant_lds(grant, reinterpret_cast<const void*>(bwd_prep_kernel), 150 * 1024, "the backward pass's preparation");
+    const int rc = grant_lds(grant, reinterpret_cast<const void*>(bwd_prep_kernel), (int)kPrepLds, "the backward pass's preparation");
     if (rc != HF_OK) return rc;
   }
   if (wgs) hipLaunchKernelGGL(bwd_prep_kernel, dim3((unsigned)wgs), dim3(kPrepThreads), lds, s, p);
+  if (order_behind) {
+    int shift = 0;
+    while (t_m >> shift >= kLengths) ++shift;
+    hipLaunchKernelGGL(dkv_order_kernel, dim3(8), dim3(kOrderThreads), 0, s, inv_cnt, inv_list, t_m, slabs, (int)share, (int)items,
+                       shift, order);
+  }
   return check_launch("hf_hybrid_attn_bwd(lists, planes, D)");
 }
 

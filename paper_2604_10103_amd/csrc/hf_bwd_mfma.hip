@@ -963,7 +963,7 @@ size_t bwd_planes_bytes(const hf_config& c) {
   return bwd_mfma_supported(c) ? (size_t)c.batch * c.heads * 2 * D * D * sizeof(bf16_t) : 0;
 }
 
-// order NULL (equal lists, or shares too long for the ordering): the dK/dV items run in index order.
+// order NULL (equal lists, or HF_FLAG_DKV_INDEX_ORDER): the dK/dV items run in index order.
 // state == NULL: no history branch.  Q_hist != Q: its gradient goes to dQ_hist, else it joins dQ.
 int launch_bwd_mfma(const hf_config& c, const void* Q, int n_q, const void* K, const void* V, int n_kv,
                     const int32_t* idx, int k, const void* dO, const float* lse2, const float* Dv,

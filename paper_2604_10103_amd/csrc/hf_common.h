@@ -177,7 +177,7 @@ int launch_bwd_mfma(const hf_config& c, const void* Q, int n_q, const void* K, c
 // inverse lists, launch order of the dK/dV items, bf16 planes of the state, row dots: what is asked for, in one launch
 constexpr int kOrderRec = 8;   // words per record of the launch order
 int launch_bwd_prep(const hf_config& c, const int32_t* idx, int k, int t_m, int t_n, int32_t* inv_cnt, int32_t* inv_list,
-                    int32_t** order_inout, const float* state, void* planes, const void* A, const void* B, long long rows,
+                    int32_t* order, const float* state, void* planes, const void* A, const void* B, long long rows,
                     float* dots, hipStream_t s);
 int launch_bwd_generic(const hf_config& c, const void* Q, const void* Q_hist, int n_q, const void* K, const void* V, int n_kv,
                        const int32_t* idx, int k, const void* dO, const float* lse2, const float* Dv,

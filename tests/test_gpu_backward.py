@@ -403,3 +403,52 @@ def test_longest_lists_of_one_mask_word(t_n):
     for name, a, r in zip(("dQ", "dK", "dV"), got, ref):
         a, r = a.double().reshape(-1, b, 64), r.double().reshape(-1, b, 64)
         assert ((a - r).flatten(1).norm(dim=1) / r.flatten(1).norm(dim=1)).max().item() <= 5e-5, name
+
+
+@pytest.mark.parametrize("heads,t_m,t_n,slabs", [
+    (2, 40, 100, 2), (4, 512, 1024, 1),           # masks of 0.8 and 64 KB: lists and order in one launch
+    (1, 512, 2400, 1), (1, 512, 2401, 1),         # ... of 150 KB, the most it takes, and more: order from finished lists
+    (8, 1024, 1150, 1),                           # masks fit (144 KB), those of a share beside its lengths do not
+    (1, 8200, 160, 1),                            # likewise (161 KB); lists of up to 8200 entries, two lengths to a bucket
+])
+def test_launch_order_is_formed_at_every_size(heads, t_m, t_n, slabs):
+    """Records in the workspace: within every eighth of the items each item once, longest list first, with the list's length and
+    first three entries.  Gradients are the same bits as in index order."""
+    b, k, d = 64, 4, 128
+    n_q, n_kv = b * t_m, b * slabs * t_n
+    cfg = hf.make_config(1, heads, d, "bf16", b, b * slabs, keep_k=k)
+    g = torch.Generator(device=DEV).manual_seed(5)
+    mk = lambda n: torch.randn((1, heads, n, d), generator=g, dtype=torch.bfloat16, device=DEV)
+    Q, K, V, dO = mk(n_q), mk(n_kv), mk(n_kv), mk(n_q)
+    weight = (torch.arange(t_n, device=DEV) % 7 + 0.2).expand(heads * t_m, t_n)   # lists of different lengths
+    idx = torch.multinomial(weight, k, generator=g).sort(dim=1).values.int().view(1, heads, t_m, k).contiguous()
+    ws = torch.full((hf.hf_bwd_workspace_bytes(cfg, n_q, n_kv),), 0xFF, dtype=torch.uint8, device=DEV)
+
+    def gradients():
+        out = [torch.full_like(t, float("nan")) for t in (Q, K, V)]
+        hf.hf_hybrid_attn_bwd(cfg, Q, K, V, idx, None, dO, *out, ws)
+        torch.cuda.synchronize()
+        return out
+
+    ordered = gradients()
+    up = lambda n: -(-n // 256) * 256
+    at = 2 * up(heads * n_q * 4) + up(heads * t_n * 4) + up(heads * t_n * t_m * 4)
+    items = heads * t_n * slabs
+    rec = ws[at:at + items * 32].view(torch.int32).view(items, 8).cpu().numpy()
+    lists = [[] for _ in range(heads * t_n)]
+    for h, rows in enumerate(idx[0].cpu().tolist()):
+        for i, row in enumerate(rows):
+            for j in row:
+                lists[h * t_n + j].append(i)
+    share = -(-items // 8)
+    for first in range(0, items, share):
+        part = rec[first:first + share]
+        assert sorted(part[:, 0]) == list(range(first, min(first + share, items)))
+        step = 1 if t_m < 8192 else 2
+        assert (np.diff(part[:, 1] // step) <= 0).all()
+        for item, length, *entries in part[:, :5].tolist():
+            own = lists[item // slabs]
+            assert length == len(own) and entries == (own + [0, 0, 0])[:3]
+    cfg.flags |= hf.HF_FLAG_DKV_INDEX_ORDER
+    for a, r in zip(ordered, gradients()):
+        assert r.isfinite().all() and torch.equal(a, r)
