@@ -8,7 +8,7 @@ import torch
 import oracle as orc
 import paper_2604_10103_amd as hf
 import workloads as wl
-from parity import BF16_MAX_ABS, BF16_REL_L2, heads_of, max_abs, oracle_state, rel_l2, split_state
+from parity import BF16_MAX_ABS, BF16_REL_L2, check_block_idx, heads_of, max_abs, oracle_state, rel_l2, split_state
 
 pytestmark = pytest.mark.gpu
 
@@ -140,3 +140,69 @@ def test_an_absorb_in_the_launch_does_not_change_its_bits(b, heads, n_q):
             hf.hf_select_attn_fwd(cfg, Q, K, V, pooled, st, planes, O, idx)
         out.append((idx, O))
     assert torch.equal(out[0][0], out[1][0]) and torch.equal(out[0][1], out[1][1])
+
+
+# heads, block, n_q, n_kv, keep: attending workgroups + absorbing ones counted
+ROTATED = [
+    (40, 64, 840, 700, 0.4), (64, 64, 832, 150, 0.6),             # one group: 560 + 80 and 832 + 128
+    (32, 128, 1030, 900, 0.5), (49, 128, 600, 300, 1.0),          # one group: 288 + 64 and 245 + 98
+    (3, 64, 200, 700, 0.4), (2, 128, 300, 900, 0.5),              # two groups
+    (40, 64, 840, 64 * 300 + 7, 0.02), (32, 128, 1030, 128 * 262 + 5, 0.02),   # one group, more than 256 KV blocks
+]
+
+
+@pytest.mark.parametrize("case", ROTATED, ids=lambda c: "-".join(map(str, c)))
+def test_rotated_readout_on_both_sides(case):
+    """ELU features, rotated queries and keys of the history term, queries of its own: by the selecting launch and, the same
+    bits, from the list handed in."""
+    H, b, n_q, n_kv, keep = case
+    d, n_ev = 128, 70
+    cfg = hf.make_config(1, H, d, "bf16", b, b, keep, phi=hf.HF_PHI_ELU1)
+    mk = lambda n, s: wl.randn((1, H, n, d), 47_300 + s, 0.5, torch.bfloat16)
+    Q, Qh, K, V, Ke, Ve = mk(n_q, 0), mk(n_q, 1), mk(n_kv, 2), mk(n_kv, 3), mk(n_ev, 4), mk(n_ev, 5)
+    qtab, etab = wl.rope_tables(n_q, d, first_position=5.0, tokens_per_position=50), wl.rope_tables(n_ev, d, first_position=1.0)
+    on = lambda *t: [x.to(DEV) for x in t]
+    byte = lambda n: torch.empty(max(int(n), 256), dtype=torch.uint8, device=DEV)
+    st = torch.empty(hf.hf_state_bytes(cfg) // 4, dtype=torch.float32, device=DEV)
+    hf.hf_state_init(cfg, st)
+    hf.hf_absorb_evicted(cfg, st, *on(Ke, Ve, *etab))
+    planes, pooled = byte(hf.hf_state_planes_bytes(cfg)), byte(hf.hf_pooled_keys_bytes(cfg, n_kv))
+    hf.hf_state_planes(cfg, st, planes)
+    Qd, Qhd, Kd, Vd, cos, sin = on(Q, Qh, K, V, *qtab)
+    hf.hf_pool_keys(cfg, Kd, pooled)
+    t_m, t_n, k = -(-n_q // b), -(-n_kv // b), hf.hf_select_k(cfg, n_kv)
+    idx = torch.full((1, H, t_m, k), -1, dtype=torch.int32, device=DEV)
+    scores = torch.full((1, H, t_m, t_n), float("nan"), dtype=torch.float32, device=DEV)
+    O, Ol = (torch.full(Q.shape, float("nan"), dtype=torch.bfloat16, device=DEV) for _ in range(2))
+    hf.hf_select_attn_fwd(cfg, Qd, Kd, Vd, pooled, st, planes, O, idx, scores, cos, sin, Qhd)
+    hf.hf_hybrid_attn_fwd_planes(cfg, Qd, Kd, Vd, idx, st, planes, Ol, cos, sin, Qhd)
+    torch.cuda.synchronize()
+    assert torch.equal(O, Ol)
+    idxc, cs, sn = idx.cpu().numpy(), wl.to_f64(qtab[0]), wl.to_f64(qtab[1])
+    for h in sorted({0, H // 2, H - 1}):
+        one = lambda t: heads_of(t[:, h:h + 1])[0]
+        q, kk = one(Q), one(K)
+        L, z = oracle_state([Ke[:, h:h + 1]], [Ve[:, h:h + 1]], d, cfg.phi, [etab])[0]
+        A = orc.block_scores(q, kk, b, b)
+        assert np.abs(wl.to_f64(scores)[0, h] - A).max() <= 1e-5 * max(1.0, np.abs(A).max())
+        check_block_idx(idxc[0, h], A, k)
+        ref = orc.sparse_attention(q, kk, one(V), idxc[0, h], b, b) + orc.history_readout(one(Qh), L, z, cfg.phi, cs, sn, cfg.eps, cfg.z_scale)
+        x = wl.to_f64(O)[0, h]
+        assert rel_l2(x, ref) <= BF16_REL_L2 and max_abs(x, ref) <= BF16_MAX_ABS, (h, rel_l2(x, ref))
+
+
+@pytest.mark.parametrize("heads,b,n_q", [(2, 64, 130), (40, 64, 840), (2, 128, 130), (32, 128, 1030)])
+def test_the_second_plane_of_the_state(heads, b, n_q):
+    """Every element of L is c = 1 + 2^-8 - 2^-12, of which the high plane is 1, every element of z is 0.998 and V is zero: every
+    output is c / 0.998 = 1.0057, next to 1 + 2^-7, with both planes and 1 / 0.998 = 1.002, next to 1, with one."""
+    d, n_kv = 128, 300
+    Q, K = (wl.randn((1, heads, n, d), 47_400, 0.5, torch.bfloat16).to(DEV) for n in (n_q, n_kv))
+    for flags, want in ((hf.HF_FLAG_HISTORY_TWO_PLANES, 1 + 2.0 ** -7), (0, 1.0)):
+        cfg = hf.make_config(1, heads, d, "bf16", b, b, 0.5, flags=flags)
+        st = torch.full((hf.hf_state_bytes(cfg) // 4,), 1 + 2.0 ** -8 - 2.0 ** -12, dtype=torch.float32, device=DEV)
+        st[heads * d * d:] = 0.998
+        ws = torch.empty(hf.hf_workspace_bytes(cfg, n_q, n_kv), dtype=torch.uint8, device=DEV)
+        O = torch.full(Q.shape, float("nan"), dtype=torch.bfloat16, device=DEV)
+        hf.hf_hybrid_attn_fwd(cfg, Q, K, torch.zeros_like(K), None, st, O, ws)
+        torch.cuda.synchronize()
+        assert (O == want).all()
