@@ -4,6 +4,8 @@
 //
 // This file: the fill kernel and the fp32-arithmetic absorb kernel (fp32 inputs, or head_dim 64).
 // bf16 inputs with head_dim 128 take the MFMA kernel of hf_state_mfma.hip.
+#include <type_traits>
+
 #include "hf_f32_mfma.h"
 
 namespace hf {
@@ -77,6 +79,8 @@ int launch_fold_linear(const hf_config& c, const float* state_in, const float* W
 // l % 32 of token l / 32 of both: operands come straight from memory, 128 contiguous bytes per token.  A workgroup owns one
 // 32 x 32 tile of L and a slice of the tokens; its eight wavefronts take every eighth run of 16 tokens, the loads of the next
 // run in flight under the products of the current one, and meet in LDS.
+// Eight wavefronts on one compute unit are bound by their issue, so a round has no branch, mask or address per token (1000
+// tokens of one head of 64, plain / rotated: 9.6 / 12.2 us; 14.7 / 16.9 with them, more than the 12.7 / 13.2 before).
 // A chunk of a small stream is one slice: the tile is then written as state_in + sum by plain stores, into another buffer
 // if the caller wants, where more slices add to the state with float atomics (state_in == state_out).
 // Latency-bound at the sizes of fp32 streams.  256 threads per (head, 64 tokens or more) with FMA arithmetic, tokens staged
@@ -84,7 +88,7 @@ int launch_fold_linear(const hf_config& c, const float* state_in, const float* W
 // 3.9 us, without a copy (ring of 2 heads of 64, window of 256: 37 -> 27 us a chunk).
 constexpr int kAbsorbWaves = 8;
 constexpr int kAbsorbRun = 16 * kAbsorbWaves;   // tokens per round of the workgroup
-constexpr int kAbsorbOneSlice = 1024;           // up to eight rounds: shorter than a copy of the state and the atomics
+constexpr int kAbsorbOneSlice = 1024;           // up to eight rounds (one head of 64: 9.6 us; slices and atomics took 12.7 with FMA)
 
 template <typename T, int D>
 __global__ __launch_bounds__(64 * kAbsorbWaves) void absorb_wide_kernel(const float* state_in, float* state_out,
@@ -110,36 +114,65 @@ __global__ __launch_bounds__(64 * kAbsorbWaves) void absorb_wide_kernel(const fl
   float zsum = 0.0f;
   T kr[8], vr[8];
   float cs[8], sn[8];
-  auto load = [&](int base) {                   // tokens past the slice: clamped addresses, zeroed below
+  // a whole run at offsets from one address, without masks: with them address and mask arithmetic is most of a round
+  auto load = [&](int base) {
+    if (base + 16 <= t1) {                      // uniform
+      const T *kp = Kh + (size_t)(base + h) * D, *vp = Vh + (size_t)(base + h) * D;
+#pragma unroll
+      for (int u = 0; u < 8; ++u) {
+        kr[u] = kp[2 * u * D];
+        vr[u] = vp[2 * u * D];
+      }
+      if (cosv) {
+        const size_t at = (size_t)(base + h) * (D / 2) + fi / 2;
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+          cs[u] = cosv[at + u * D];
+          sn[u] = sinv[at + u * D];
+        }
+      }
+    } else {
+#pragma unroll
+      for (int u = 0; u < 8; ++u) {             // tokens past the slice: clamped addresses, zeroed below
+        const size_t t = (size_t)min(base + 2 * u + h, t1 - 1);
+        kr[u] = Kh[t * D];
+        vr[u] = Vh[t * D];
+        if (cosv) {
+          cs[u] = cosv[t * (D / 2) + fi / 2];
+          sn[u] = sinv[t * (D / 2) + fi / 2];
+        }
+      }
+    }
+  };
+  float a[8], b[8];
+  auto operands = [&](int base, auto whole) {   // (each choice once for all eight: a branch per token keeps them apart)
+    auto real = [&](int u) { return whole.value || base + 2 * u + h < t1; };
+    if (phi_kind == HF_PHI_RELU) {
+#pragma unroll
+      for (int u = 0; u < 8; ++u) a[u] = phi_apply(Elem<T>::load(&kr[u]), HF_PHI_RELU);
+    } else {
+#pragma unroll
+      for (int u = 0; u < 8; ++u) a[u] = phi_apply(Elem<T>::load(&kr[u]), HF_PHI_ELU1);
+    }
 #pragma unroll
     for (int u = 0; u < 8; ++u) {
-      const size_t t = (size_t)min(base + 2 * u + h, t1 - 1);
-      kr[u] = Kh[t * D];
-      vr[u] = Vh[t * D];
-      if (cosv) {
-        cs[u] = cosv[t * (D / 2) + fi / 2];
-        sn[u] = sinv[t * (D / 2) + fi / 2];
+      a[u] = real(u) ? a[u] : 0.0f;
+      b[u] = real(u) ? Elem<T>::load(&vr[u]) : 0.0f;
+      zsum += a[u];                             // the normaliser takes the un-rotated phi(k)
+    }
+    if (cosv) {                                 // pairs (2 p, 2 p + 1) are neighbouring lanes
+#pragma unroll
+      for (int u = 0; u < 8; ++u) {
+        const float other = __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(a[u]), 0xb1, 0xf, 0xf, false));   // lane ^ 1
+        const float x = (l32 & 1) ? other * sn[u] + a[u] * cs[u] : a[u] * cs[u] - other * sn[u];
+        a[u] = real(u) ? x : 0.0f;
       }
     }
   };
   int base = t0 + 16 * wave;
   if (base < t1) load(base);
   for (; base < t1; base += kAbsorbRun) {
-    float a[8], b[8];
-#pragma unroll
-    for (int u = 0; u < 8; ++u) {
-      const bool real = base + 2 * u + h < t1;
-      float x = phi_apply(Elem<T>::load(&kr[u]), phi_kind);
-      x = real ? x : 0.0f;
-      zsum += x;                                // the normaliser takes the un-rotated phi(k)
-      if (cosv) {                               // pairs (2 p, 2 p + 1) are neighbouring lanes
-        const float other = __shfl_xor(x, 1, kWave);
-        x = (l32 & 1) ? other * sn[u] + x * cs[u] : x * cs[u] - other * sn[u];
-        x = real ? x : 0.0f;
-      }
-      a[u] = x;
-      b[u] = real ? Elem<T>::load(&vr[u]) : 0.0f;
-    }
+    if (base + 16 <= t1) operands(base, std::true_type{}); else operands(base, std::false_type{});
     if (base + kAbsorbRun < t1) load(base + kAbsorbRun);
 #pragma unroll
     for (int u = 0; u < 8; ++u) acc = mfma_f32_wide(a[u], b[u], acc);
