@@ -59,6 +59,22 @@ def test_an_unselected_block_is_not_read(case, bad):
     assert want.isfinite().all() and torch.equal(_attend(cfg, Q, K, V, idx), want)
 
 
+@pytest.mark.parametrize("heads,bq,bkv,n_kv,sel", [
+    (180, 64, 32, 300, [2, 5, 8]), (100, 128, 32, 300, [2, 5, 9]),   # one group of wavefronts (540 and 300 workgroups)
+    (2, 192, 64, 64 * 4 + 10, [1, 2, 4]), (2, 256, 48, 48 * 3 + 10, [1, 2, 3]),   # larger query blocks
+])
+@pytest.mark.parametrize("bad", [NAN, INF])
+def test_an_unselected_block_is_not_read_by_the_other_bf16_kernels(heads, bq, bkv, n_kv, sel, bad):
+    n_q = 2 * bq + 5
+    cfg = hf.make_config(1, heads, 128, "bf16", bq, bkv, 0.5)
+    Q, K, V, _ = (t.repeat(1, heads // 2, 1, 1) for t in _inputs("bf16", 128, n_q, n_kv, 40))
+    idx = _lists([sel] * 3).repeat(1, heads // 2, 1, 1)
+    want = _attend(cfg, Q, K, V, idx)
+    K[:, :, :bkv] = bad
+    V[:, :, :bkv] = bad
+    assert want.isfinite().all() and torch.equal(_attend(cfg, Q, K, V, idx), want)
+
+
 @pytest.mark.parametrize("case", ["mfma_groups", "wide_f32", "wide_f32_d64", "wide_bf16", "wide_bf16_d64", "wide32_f32"])
 def test_a_selected_infinity_stays_one(case):
     """In the last key of a short tile: nothing repeats that row with weight zero (zero times infinity is NaN)."""
