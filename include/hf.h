@@ -25,6 +25,14 @@
  *    real keys take part).  T_m = ceil(n_q / block_q), T_n = ceil(n_kv / block_kv).
  *  - The window buffer holds [older cached tokens ... | current chunk]; sink frames are
  *    ordinary leading tokens.  There is no causal mask inside the window.
+ *  - Given its list, a query row depends on the blocks of that list alone: a NaN or an
+ *    infinity in a key or value reaches the rows that select its block and no others
+ *    (bf16 at head_dim 128 with a block_kv that is no multiple of 32: also those that
+ *    select the block before it).
+ *  - bf16 launches that would leave compute units idle let two groups of wavefronts share a
+ *    query block's list.  A head on its own and the same head among many may therefore
+ *    differ by the order of fp32 sums (a last bf16 bit here and there); block lists and
+ *    scores are the same bits, and so are calls of one size with or without an absorb.
  *  - Return value: HF_OK (0) or a negative HF_ERR_* code; on error nothing was enqueued
  *    and hf_last_error() describes the problem.  No C++ exception crosses this boundary.
  *

@@ -302,7 +302,7 @@ __device__ __forceinline__ void add_parts_and_store(float* smem, const f32x4 (&a
 // ---- dQ: a workgroup per 16 NQ query rows; S^T and dP^T = V dO^T (row form), dS^T = P^T (dP^T - D), dQ^T += K^T dS^T
 // (column form), all on 16 x 16 x 4 fp32 products.  Q and dO wait in LDS (B operands, shared by the four wavefronts); the
 // keys' and values' pieces travel one product phase ahead, each into the registers of a piece that has just been used.
-// Bound by the fp32 matrix rate.  12 heads of 128, 1170 x 2340, k = 10 of 37 blocks of 64: 92 us (0.71 ms with one key per
+// Bound by the fp32 matrix rate.  12 heads of 128, 1170 x 2340, k = 10 of 37 blocks of 64: 88 us (0.71 ms with one key per
 // lane and FMA arithmetic, plus 0.21 ms for the history branch's gradient as a kernel of its own).
 template <typename T, int D, int NQ>
 __global__ __launch_bounds__(64 * kParts, 2) void bwd_dq_wide_kernel(
@@ -569,7 +569,7 @@ __global__ __launch_bounds__(64 * kParts, 2) void bwd_dq_wide_kernel(
 
 // ---- dK, dV: a workgroup per 16 NK keys of a KV block, its four wavefronts taking every fourth 16-row tile of the query
 // blocks on the inverse list.  S = Q K^T, dP = dO V^T (row form; K and V wait in LDS), P = 2^(S - lse2), dS = P (dP - D),
-// dV^T += dO^T P, dK^T += Q^T dS (column form).  Bound by the fp32 matrix rate, at the same shape 124 us (1.01 ms with one
+// dV^T += dO^T P, dK^T += Q^T dS (column form).  Bound by the fp32 matrix rate, at the same shape 118 us (1.01 ms with one
 // query per lane and FMA arithmetic).
 template <typename T, int D, int NK>
 __global__ __launch_bounds__(64 * kParts, 2) void bwd_dkv_wide_kernel(

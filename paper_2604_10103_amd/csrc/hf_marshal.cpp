@@ -2,7 +2,7 @@
 // pointers and the current stream, and calls the C ABI without the GIL.  No step of the method happens here.
 //
 // Native because a small launch is shorter than the same checks in Python: twelve to twenty attribute look-ups and tuple
-// comparisons per call cost 5 to 14 us, next to 3 us for a launch (hf_pool_keys 7.9 -> 3.5 us per call, a two-call step of a
+// comparisons per call cost 5 to 14 us, next to 3 us for a launch (hf_pool_keys 8.2 -> 3.0 us per call, a two-call step of a
 // small stream 25 -> 7 us).  The entry points come as addresses from the library that the binding loaded; this file links
 // against Python and torch only.
 #define PY_SSIZE_T_CLEAN
