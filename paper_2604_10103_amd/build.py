@@ -28,6 +28,7 @@ SOURCES = [
     "hf_attn_generic.hip",
     "hf_attn_mfma.hip",
     "hf_attn_d64.hip",
+    "hf_attn_f32.hip",
     "hf_attn_w64.hip",
     "hf_readout_mfma.hip",
     "hf_rope.hip",

@@ -391,7 +391,7 @@ int launch_wide(const hf_config& c, const void* Q, int n_q, const void* K, const
   return check_launch("hf_hybrid_attn_fwd(attention)");
 }
 
-// ---- fp32 storage, block_q and block_kv multiples of 32: tiles of 32 keys x 32 queries on the 32 x 32 x 2 instruction.
+// ---- fp32 storage, block_q and block_kv multiples of 32, few rows: tiles of 32 keys x 32 queries on the 32 x 32 x 2 instruction.
 // A workgroup owns 32 query rows of a block; its four wavefronts take every fourth tile of the list and meet in LDS once,
 // at the end.  A trip forms the scores of the wavefront's next tile next to the exponentials of the current one and then
 // accumulates the current one; every 16-byte piece is requested one such phase (4096 cycles at D = 128) before its use,
@@ -400,7 +400,8 @@ int launch_wide(const hf_config& c, const void* Q, int n_q, const void* K, const
 // Measured at 832x480 in fp32 (12 heads of 128, 4680 x 9360, k = 37 of 147 blocks of 64; selection included): 4.84 ms with
 // one key per lane and FMA arithmetic, 0.67 ms with the 16 x 16 tiles below, 0.61 ms (115 of the 154 TFLOP/s the
 // instruction sustains) with this kernel: the pipes are 86 % busy while a compute unit has work, and the last of 3.5 rounds
-// of workgroups leaves an eighth of the chip idle.
+// of workgroups leaves an eighth of the chip idle.  Launches of more than 128 blocks of 64 rows are faster still in bf16 products
+// (hf_attn_f32.hip).
 template <int D>
 __global__ __launch_bounds__(256, 2) void attn_wide32_kernel(const float* __restrict__ Q, const float* __restrict__ K,
                                                              const float* __restrict__ V, const int32_t* __restrict__ idx,
@@ -708,11 +709,15 @@ int launch_wide_rows(const hf_config& c, const void* Q, int n_q, const void* K, 
 bool attn_d64_supported(const hf_config& c, int n_kv);   // hf_attn_d64.hip
 int launch_attn_d64(const hf_config& c, const void* Q, int n_q, const void* K, const void* V, int n_kv, const int32_t* idx,
                     int k, void* O, const WideHist& hist, hipStream_t s);
+bool attn_split_supported(const hf_config& c, int n_q, int n_kv);   // hf_attn_f32.hip
+int launch_attn_split(const hf_config& c, const void* Q, int n_q, const void* K, const void* V, int n_kv, const int32_t* idx,
+                      int k, void* O, const WideHist& hist, hipStream_t s);
 
 static int launch_attn_wide(const hf_config& c, const void* Q, int n_q, const void* K, const void* V, int n_kv,
                             const int32_t* idx, int k, void* O, const WideHist& hist, hipStream_t s) {
   // (row statistics for the backward pass come from the kernels of this file)
   if (attn_d64_supported(c, n_kv) && !hist.lse2) return launch_attn_d64(c, Q, n_q, K, V, n_kv, idx, k, O, hist, s);
+  if (attn_split_supported(c, n_q, n_kv)) return launch_attn_split(c, Q, n_q, K, V, n_kv, idx, k, O, hist, s);
   if (c.dtype == HF_F32 && c.block_q % 32 == 0 && c.block_kv % 32 == 0)
     return c.head_dim == 128 ? launch_wide32<128>(c, Q, n_q, K, V, n_kv, idx, k, O, hist, s)
                              : launch_wide32<64>(c, Q, n_q, K, V, n_kv, idx, k, O, hist, s);

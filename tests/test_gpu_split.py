@@ -1,0 +1,119 @@
+"""fp32 attention in bf16 products of values split in three (launches of more than 128 blocks of 64 rows): one, two and four
+groups of wavefronts at both head sizes, ragged rows and keys, empty parts of blocks, lists that the groups do not divide, the
+history term, the statistics the backward pass takes; NaN, infinities and the type's lowest value among the keys."""
+import numpy as np
+import pytest
+import torch
+
+import oracle as orc
+import paper_2604_10103_amd as hf
+import workloads as wl
+from parity import F32_REL_L2, max_abs, oracle_state, rel_l2
+
+pytestmark = pytest.mark.gpu
+
+DEV = "cuda:0"
+NAN, INF, LOWEST = float("nan"), float("inf"), torch.finfo(torch.float32).min
+
+
+def _tensors(heads, n, d, seed, gain=1.0):
+    """Three heads repeated: what the oracle has to follow."""
+    return [(wl.randn((1, 3, m, d), 71_000 + seed + i, gain, torch.float32)).repeat(1, heads // 3, 1, 1) for i, m in enumerate(n)]
+
+
+def _attend(cfg, Q, K, V, idx, st=None, tab=(None, None)):
+    O = torch.full_like(Q, 7.0)
+    ws = torch.empty(max(hf.hf_workspace_bytes(cfg, Q.shape[2], K.shape[2]), 256), dtype=torch.uint8, device=DEV)
+    hf.hf_hybrid_attn_fwd(cfg, Q, K, V, idx, st, O, ws, *tab)
+    torch.cuda.synchronize()
+    return O
+
+
+# heads, head_dim, block_q, block_kv, n_q, n_kv, keep (None: dense); blocks of 64 rows: 129 .. 256, .. 768, more
+SHAPES = [
+    (66, 128, 64, 64, 65, 100, 1.0), (45, 128, 128, 32, 130, 257, 0.5), (129, 128, 64, 96, 1, 96 * 3 + 1, 0.5),
+    (150, 128, 64, 32, 129, 33, 1.0), (300, 128, 64, 64, 70, 300, None), (390, 128, 64, 64, 100, 200, 0.5),
+    (270, 128, 128, 64, 200, 130, 0.4), (66, 64, 64, 64, 65, 100, 1.0), (45, 64, 192, 32, 200, 300, 0.3),
+    (390, 64, 64, 96, 100, 200, None), (270, 64, 64, 32, 193, 65, 0.4),
+]
+
+
+@pytest.mark.parametrize("case", SHAPES, ids=lambda c: "-".join(map(str, c)))
+@pytest.mark.parametrize("gain,phi,rope", [(1.0, hf.HF_PHI_RELU, False), (4.0, hf.HF_PHI_ELU1, True)])
+def test_forward_and_gradients(case, gain, phi, rope):
+    heads, d, bq, bkv, n_q, n_kv, keep = case
+    cfg = hf.make_config(1, heads, d, "f32", bq, bkv, 1.0 if keep is None else keep, phi=phi)
+    Q, K, V, dO, Ke, Ve = _tensors(heads, (n_q, n_kv, n_kv, n_q, 50, 50), d, 0, 0.5)
+    Q = Q * gain
+    tab = wl.rope_tables(n_q, d, first_position=9.0) if rope else (None, None)
+    dtab = tuple(None if t is None else t.to(DEV) for t in tab)
+    q, k, v, g = (t.to(DEV) for t in (Q, K, V, dO))
+    st = torch.empty(hf.hf_state_bytes(cfg) // 4, dtype=torch.float32, device=DEV)
+    hf.hf_state_init(cfg, st)
+    hf.hf_absorb_evicted(cfg, st, Ke.to(DEV), Ve.to(DEV))
+    t_m, t_n, kk = -(-n_q // bq), -(-n_kv // bkv), hf.hf_select_k(cfg, n_kv)
+    idx = torch.empty((1, heads, t_m, kk), dtype=torch.int32, device=DEV)
+    ws = torch.empty(hf.hf_workspace_bytes(cfg, n_q, n_kv), dtype=torch.uint8, device=DEV)
+    hf.hf_block_select(cfg, q, k, idx, None, ws)
+    use = None if keep is None else idx
+    O, O0 = _attend(cfg, q, k, v, use, st, dtab), _attend(cfg, q, k, v, use)
+    dQ, dK, dV = (torch.full_like(t, NAN) for t in (q, k, v))
+    bws = torch.empty(hf.hf_bwd_workspace_bytes(cfg, n_q, n_kv), dtype=torch.uint8, device=DEV)
+    hf.hf_hybrid_attn_bwd(cfg, q, k, v, use, st, g, dQ, dK, dV, bws, *dtab)
+    torch.cuda.synchronize()
+    states = oracle_state([Ke[:, :3]], [Ve[:, :3]], d, phi)
+    lists = idx.cpu().numpy() if keep is not None else np.tile(np.arange(t_n), (1, heads, t_m, 1))
+    tabs = tuple(None if t is None else wl.to_f64(t) for t in tab)
+    for h in (0, 1, heads - 1):
+        a = [wl.to_f64(t[0, h]) for t in (Q, K, V, dO)]
+        for got, state in ((O, states[h % 3]), (O0, None)):
+            ref, *_ = orc.hybrid_attention(*a[:3], state, bq, bkv, lists.shape[-1], phi, *tabs, cfg.eps, cfg.z_scale,
+                                           block_idx=lists[0, h])
+            x = wl.to_f64(got[0, h])
+            assert rel_l2(x, ref) <= F32_REL_L2 and max_abs(x, ref) <= 1e-4 * max(1.0, np.abs(ref).max()), (h, rel_l2(x, ref))
+        dq, dqh, dk, dv = orc.hybrid_attention_bwd(*a[:3], states[h % 3], bq, bkv, lists[0, h], a[3], phi, *tabs, cfg.eps, cfg.z_scale)
+        for name, got, ref in (("dQ", dQ, dq + dqh), ("dK", dK, dk), ("dV", dV, dv)):   # (bounds as in test_gpu_wide.py)
+            x = wl.to_f64(got[0, h])
+            assert rel_l2(x, ref) <= 5e-5 and max_abs(x, ref) <= 1e-4 * max(np.abs(ref).max(), 1e-2), (name, h, rel_l2(x, ref))
+
+
+BAD = [(66, 128), (150, 128), (390, 128), (66, 64), (390, 64)]   # four, two and one group; two and one
+
+
+def _bad_case(heads, d):
+    b, n_kv = 64, 64 * 3 + 10
+    cfg = hf.make_config(1, heads, d, "f32", b, b, 0.5)
+    Q, K, V = (t.to(DEV) for t in _tensors(heads, (2 * b + 5, n_kv, n_kv), d, 20))
+    idx = torch.tensor([[0, 3], [1, 2], [2, 3]], dtype=torch.int32, device=DEV).expand(1, heads, 3, 2).contiguous()
+    return cfg, Q, K, V, idx
+
+
+@pytest.mark.parametrize("heads,d", BAD)
+@pytest.mark.parametrize("bad", [NAN, INF, LOWEST])
+def test_an_unselected_block_is_not_read(heads, d, bad):
+    cfg, Q, K, V, idx = _bad_case(heads, d)
+    want = _attend(cfg, Q, K, V, idx)
+    K[:, :, :64] = bad
+    V[:, :, :64] = bad
+    assert want.isfinite().all() and torch.equal(_attend(cfg, Q, K, V, idx)[:, :, 64:], want[:, :, 64:])
+
+
+@pytest.mark.parametrize("heads,d", BAD)
+def test_values_without_a_finite_remainder(heads, d):
+    """A selected infinite value stays one; a key of an infinitely small score, or of the lowest finite one, has no weight."""
+    cfg, Q, K, V, idx = _bad_case(heads, d)
+    Q[..., 0] = Q[..., 0].abs() + 0.1
+    n_kv = K.shape[2]
+    for value in (-INF, LOWEST):
+        K2 = K.clone()
+        K2[:, :, n_kv - 1, 0] = value          # the last key of block 3: query blocks 0 and 2
+        short, V2 = K2[:, :, :n_kv - 1].contiguous(), V[:, :, :n_kv - 1].contiguous()
+        got, want = _attend(cfg, Q, K2, V, idx), _attend(cfg, Q, short, V2, idx)
+        assert want.isfinite().all() and ((got - want).norm() / want.norm()).item() <= F32_REL_L2
+    V[:, :, n_kv - 1, 3] = INF
+    V[:, :, n_kv - 1, 40] = LOWEST
+    O, want = _attend(cfg, Q, K, V, idx), want
+    assert (O[:, :, :64, 3] == INF).all() and (O[:, :, 128:, 3] == INF).all() and O[:, :, 64:128].isfinite().all()
+    assert (O[:, :, :64, 40] < -1e30).all() and (O[:, :, 128:, 40] < -1e30).all()
+    K[:, :, n_kv - 1, 0] = INF                 # a score of +infinity: no softmax
+    assert _attend(cfg, Q, K, V, idx)[:, :, :64].isnan().all()
