@@ -372,12 +372,16 @@ static int check_select_args(const hf_config* cfg, const void* Q, int32_t n_q, c
   return HF_OK;
 }
 
-// the two launches of a selection call; qbar / kbar = pooled means [BH, T_m, d] and (feature-group-major) [BH, d/4, T_n, 4]
+// the launches of a selection call; qbar / kbar = pooled means [BH, T_m, d] and (feature-group-major) [BH, d/4, T_n, 4]
 static int select_launches(const hf_config* cfg, const void* Q, int32_t n_q, const void* K_win, int32_t n_kv,
                            int32_t n_cached_kv_blocks, int k, int32_t* block_idx, float* scores_or_null, float* qbar,
                            float* kbar, hipStream_t s, int kv_end = -1) {
   const int t_m = cdiv(n_q, cfg->block_q), t_n = cdiv(n_kv, cfg->block_kv);
-  HF_TRY(launch_pool_both(*cfg, Q, n_q, t_m, K_win, n_kv, t_n, n_cached_kv_blocks, kv_end < 0 ? t_n : kv_end, qbar, kbar, s));
+  if (kv_end < 0) kv_end = t_n;
+  if (pool_select_supported(*cfg, t_n, n_cached_kv_blocks, kv_end))
+    return launch_pool_select(*cfg, Q, n_q, t_m, K_win, n_kv, t_n, n_cached_kv_blocks, kv_end, k, qbar, kbar, block_idx,
+                              scores_or_null, s);
+  HF_TRY(launch_pool_both(*cfg, Q, n_q, t_m, K_win, n_kv, t_n, n_cached_kv_blocks, kv_end, qbar, kbar, s));
   return launch_score_select(*cfg, qbar, kbar, t_m, t_n, k, block_idx, scores_or_null, s);
 }
 

@@ -14,6 +14,55 @@ namespace hf {
 
 namespace {
 
+// Mean of the rows [r0, r1) of X (rows of D elements from base, which points at the lane's columns), by one wavefront: what the
+// lanes with sub = 0 return are the E columns of theirs.
+template <typename T, int D>
+struct Pool {
+  static constexpr int E = Elem<T>::kPer16B;  // elements per 16-byte load
+  static constexpr int LPR = D / E;           // lanes covering one row
+  static constexpr int RPP = kWave / LPR;     // rows per pass of the wavefront
+  static __device__ __forceinline__ void mean(const T* __restrict__ base, int r0, int r1, int sub, float (&acc)[E]) {
+#pragma unroll
+    for (int e = 0; e < E; ++e) acc[e] = 0.0f;
+    int r = r0 + sub;
+    // sixteen, then eight independent 16-byte loads in flight per lane
+    for (; r + 15 * RPP < r1; r += 16 * RPP) {
+      float v[16][E];
+#pragma unroll
+      for (int u = 0; u < 16; ++u) load16B<T>(base + (size_t)(r + u * RPP) * D, v[u]);
+#pragma unroll
+      for (int u = 0; u < 16; ++u)
+#pragma unroll
+        for (int e = 0; e < E; ++e) acc[e] += v[u][e];
+    }
+    for (; r + 7 * RPP < r1; r += 8 * RPP) {
+      float v[8][E];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) load16B<T>(base + (size_t)(r + u * RPP) * D, v[u]);
+#pragma unroll
+      for (int u = 0; u < 8; ++u)
+#pragma unroll
+        for (int e = 0; e < E; ++e) acc[e] += v[u][e];
+    }
+    if (r < r1) {   // fewer than eight rows left: requested together all the same (clamped rows are dropped)
+      float v[8][E];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) load16B<T>(base + (size_t)min(r + u * RPP, r1 - 1) * D, v[u]);
+#pragma unroll
+      for (int u = 0; u < 8; ++u)
+#pragma unroll
+        for (int e = 0; e < E; ++e) acc[e] += r + u * RPP < r1 ? v[u][e] : 0.0f;
+    }
+#pragma unroll
+    for (int o = LPR; o < kWave; o <<= 1)
+#pragma unroll
+      for (int e = 0; e < E; ++e) acc[e] += __shfl_xor(acc[e], o, kWave);
+    const float inv = 1.0f / (float)(r1 - r0);
+#pragma unroll
+    for (int e = 0; e < E; ++e) acc[e] *= inv;
+  }
+};
+
 // Pooled keys are stored feature-group-major, kbar_t[bh][D/4][t_n][4], so that in the scoring
 // kernel consecutive lanes (= consecutive KV blocks) read consecutive 16-byte groups.
 // Pooled queries stay row-major, qbar[bh][t_m][D].
@@ -25,9 +74,8 @@ __global__ __launch_bounds__(256) void pool_kernel(const T* __restrict__ Q, int 
                                                    int t_n, int kv_first, int kv_end, float* __restrict__ qbar,
                                                    float* __restrict__ kbar_t, const float* __restrict__ state,
                                                    bf16_t* __restrict__ planes, int pool_wgs) {
-  constexpr int E = Elem<T>::kPer16B;  // elements per 16-byte load
-  constexpr int LPR = D / E;           // lanes covering one row
-  constexpr int RPP = kWave / LPR;     // rows per pass of the wavefront
+  using P = Pool<T, D>;
+  constexpr int E = P::E;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   int blk = blockIdx.x * 4 + wave;
   const int bh = blockIdx.y;
@@ -47,49 +95,13 @@ __global__ __launch_bounds__(256) void pool_kernel(const T* __restrict__ Q, int 
   const T* X = is_q ? Q : K;
   const int n = is_q ? n_q : n_kv, b = is_q ? bq : bkv;
   const int r0 = blk * b, r1 = min(n, r0 + b);
-  const int sub = lane / LPR, col = (lane % LPR) * E;
-  const T* base = X + (size_t)bh * (is_q ? n_q : kv_stride) * D + col;
+  const int sub = lane / P::LPR, col = (lane % P::LPR) * E;
   float acc[E];
-#pragma unroll
-  for (int e = 0; e < E; ++e) acc[e] = 0.0f;
-  int r = r0 + sub;
-  // sixteen, then eight independent 16-byte loads in flight per lane
-  for (; r + 15 * RPP < r1; r += 16 * RPP) {
-    float v[16][E];
-#pragma unroll
-    for (int u = 0; u < 16; ++u) load16B<T>(base + (size_t)(r + u * RPP) * D, v[u]);
-#pragma unroll
-    for (int u = 0; u < 16; ++u)
-#pragma unroll
-      for (int e = 0; e < E; ++e) acc[e] += v[u][e];
-  }
-  for (; r + 7 * RPP < r1; r += 8 * RPP) {
-    float v[8][E];
-#pragma unroll
-    for (int u = 0; u < 8; ++u) load16B<T>(base + (size_t)(r + u * RPP) * D, v[u]);
-#pragma unroll
-    for (int u = 0; u < 8; ++u)
-#pragma unroll
-      for (int e = 0; e < E; ++e) acc[e] += v[u][e];
-  }
-  if (r < r1) {   // fewer than eight rows left: requested together all the same (clamped rows are dropped)
-    float v[8][E];
-#pragma unroll
-    for (int u = 0; u < 8; ++u) load16B<T>(base + (size_t)min(r + u * RPP, r1 - 1) * D, v[u]);
-#pragma unroll
-    for (int u = 0; u < 8; ++u)
-#pragma unroll
-      for (int e = 0; e < E; ++e) acc[e] += r + u * RPP < r1 ? v[u][e] : 0.0f;
-  }
-#pragma unroll
-  for (int o = LPR; o < kWave; o <<= 1)
-#pragma unroll
-    for (int e = 0; e < E; ++e) acc[e] += __shfl_xor(acc[e], o, kWave);
+  P::mean(X + (size_t)bh * (is_q ? n_q : kv_stride) * D + col, r0, r1, sub, acc);
   if (sub == 0) {
-    const float inv = 1.0f / (float)(r1 - r0);
 #pragma unroll
     for (int e = 0; e < E; e += 4) {
-      const float4 v = make_float4(acc[e] * inv, acc[e + 1] * inv, acc[e + 2] * inv, acc[e + 3] * inv);
+      const float4 v = make_float4(acc[e], acc[e + 1], acc[e + 2], acc[e + 3]);
       if (is_q)
         *reinterpret_cast<float4*>(qbar + ((size_t)bh * t_m + blk) * D + col + e) = v;
       else
@@ -218,29 +230,15 @@ __global__ __launch_bounds__(256) void score_select_kernel(const float* __restri
 // (more than k kept), redoes that row with the tie rule.
 constexpr int kRows = 3;
 
+// sq: [kRows][D] queries (in LDS, behind a barrier); keys: the head's pooled keys, in memory or in LDS; part, sc: scratch in LDS,
+// [8][kRows][t_pad] partials (later: keep flags) and [kRows][t_pad] scores
 template <int D>
-__global__ __launch_bounds__(512) void score_select3_kernel(const float* __restrict__ qbar,
-                                                            const float* __restrict__ kbar_t, int t_m, int t_n,
-                                                            int k, int32_t* __restrict__ idx,
-                                                            float* __restrict__ scores) {
-  // LDS: [kRows][D] queries | [8][kRows][t_pad] partials (later: keep flags) | [kRows][t_pad] scores
-  extern __shared__ __attribute__((aligned(16))) float smem[];
+__device__ __forceinline__ void select_rows(const float* sq, const float4* keys, float* part, float* sc, int t_m, int t_n, int k,
+                                            int row0, int bh, int32_t* __restrict__ idx, float* __restrict__ scores) {
   constexpr int CW = D / 32;  // 16-byte feature groups per wavefront
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int row0 = blockIdx.x * kRows, bh = blockIdx.y;
   const int t_pad = (t_n + 3) & ~3;
-  float* sq = smem;
-  float* part = smem + kRows * D;
-  float* sc = part + 8 * kRows * t_pad;
-  if (tid < kRows * D) {
-    const int r = min(row0 + tid / D, t_m - 1);  // rows past the end repeat the last one; never written
-    sq[tid] = qbar[((size_t)bh * t_m + r) * D + (tid % D)];
-  }
-  const int pad = t_pad - t_n;  // at most 3
-  if (pad > 0 && tid < kRows * pad) sc[(tid / pad) * t_pad + t_n + tid % pad] = -INFINITY;  // never outranks a block
-  __syncthreads();
-
-  const float4* kt = reinterpret_cast<const float4*>(kbar_t) + ((size_t)bh * (D / 4) + wave * CW) * t_n;
+  const float4* kt = keys + wave * CW * t_n;
   float4 q[kRows][CW];
 #pragma unroll
   for (int r = 0; r < kRows; ++r)
@@ -334,6 +332,79 @@ __global__ __launch_bounds__(512) void score_select3_kernel(const float* __restr
   }
 }
 
+template <int D>
+__global__ __launch_bounds__(512) void score_select3_kernel(const float* __restrict__ qbar,
+                                                            const float* __restrict__ kbar_t, int t_m, int t_n,
+                                                            int k, int32_t* __restrict__ idx,
+                                                            float* __restrict__ scores) {
+  extern __shared__ __attribute__((aligned(16))) float smem[];   // queries, partials, scores
+  const int tid = threadIdx.x;
+  const int row0 = blockIdx.x * kRows, bh = blockIdx.y;
+  const int t_pad = (t_n + 3) & ~3;
+  float* sq = smem;
+  float* part = smem + kRows * D;
+  float* sc = part + 8 * kRows * t_pad;
+  if (tid < kRows * D) {
+    const int r = min(row0 + tid / D, t_m - 1);  // rows past the end repeat the last one; never written
+    sq[tid] = qbar[((size_t)bh * t_m + r) * D + (tid % D)];
+  }
+  const int pad = t_pad - t_n;  // at most 3
+  if (pad > 0 && tid < kRows * pad) sc[(tid / pad) * t_pad + t_n + tid % pad] = -INFINITY;  // never outranks a block
+  __syncthreads();
+  select_rows<D>(sq, reinterpret_cast<const float4*>(kbar_t) + (size_t)bh * (D / 4) * t_n, part, sc, t_m, t_n, k, row0, bh, idx, scores);
+}
+
+// Pooling and selection in one launch, for heads with little to pool: every workgroup pools its own three query blocks and ALL
+// of the head's KV blocks in [kv_first, kv_end) (the others' means are read), the sums in the order of pool_kernel, and selects
+// from LDS.  The first workgroup of a head stores the keys' means for later calls.
+template <typename T, int D>
+__global__ __launch_bounds__(512) void pool_select_kernel(const T* __restrict__ Q, int n_q, int bq, int t_m,
+                                                          const T* __restrict__ K, int n_kv, int kv_stride, int bkv, int t_n,
+                                                          int kv_first, int kv_end, int k, float* __restrict__ qbar,
+                                                          float* __restrict__ kbar_t, int32_t* __restrict__ idx,
+                                                          float* __restrict__ scores) {
+  extern __shared__ __attribute__((aligned(16))) float smem[];   // queries, partials, scores, the head's pooled keys
+  using P = Pool<T, D>;
+  constexpr int E = P::E;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int row0 = blockIdx.x * kRows, bh = blockIdx.y;
+  const int t_pad = (t_n + 3) & ~3;
+  float* sq = smem;
+  float* part = smem + kRows * D;
+  float* sc = part + 8 * kRows * t_pad;
+  float4* keys = reinterpret_cast<float4*>(sc + kRows * t_pad);
+  float4* stored = reinterpret_cast<float4*>(kbar_t) + (size_t)bh * (D / 4) * t_n;
+  for (int e = tid; e < (D / 4) * t_n; e += 512) {
+    const int j = e % t_n;
+    if (j < kv_first || j >= kv_end) keys[e] = stored[e];
+  }
+  const int pad = t_pad - t_n;
+  if (pad > 0 && tid < kRows * pad) sc[(tid / pad) * t_pad + t_n + tid % pad] = -INFINITY;
+  const int sub = lane / P::LPR, col = (lane % P::LPR) * E;
+  for (int it = wave; it < kRows + kv_end - kv_first; it += 8) {   // uniform
+    const bool is_q = it < kRows;
+    const int blk = is_q ? min(row0 + it, t_m - 1) : it - kRows + kv_first;   // rows past the end repeat the last one
+    const int n = is_q ? n_q : n_kv, b = is_q ? bq : bkv, r0 = blk * b;
+    float acc[E];
+    P::mean((is_q ? Q + (size_t)bh * n_q * D : K + (size_t)bh * kv_stride * D) + col, r0, min(n, r0 + b), sub, acc);
+    if (sub == 0) {
+#pragma unroll
+      for (int e = 0; e < E; e += 4) {
+        const float4 v = make_float4(acc[e], acc[e + 1], acc[e + 2], acc[e + 3]);
+        if (is_q) {
+          *reinterpret_cast<float4*>(sq + it * D + col + e) = v;
+          if (row0 + it < t_m) *reinterpret_cast<float4*>(qbar + ((size_t)bh * t_m + blk) * D + col + e) = v;
+        } else {
+          keys[(col + e) / 4 * t_n + blk] = v;
+          if (row0 == 0) stored[(col + e) / 4 * t_n + blk] = v;
+        }
+      }
+    }
+  }
+  __syncthreads();
+  select_rows<D>(sq, keys, part, sc, t_m, t_n, k, row0, bh, idx, scores);
+}
+
 }  // namespace
 
 int launch_pool_both(const hf_config& c, const void* Q, int n_q, int t_m, const void* K, int n_kv, int t_n,
@@ -353,6 +424,37 @@ int launch_pool_both(const hf_config& c, const void* Q, int n_q, int t_m, const 
   }
 #undef HF_LAUNCH_POOL
   return check_launch("hf_block_select(pool)");
+}
+
+// Heads of which a workgroup can pool all that is to be pooled by itself
+static size_t pool_select_lds(const hf_config& c, int t_n) {
+  const int t_pad = (t_n + 3) & ~3;
+  return (size_t)(kRows * c.head_dim + 9 * kRows * t_pad + c.head_dim * t_n) * sizeof(float);
+}
+// Every workgroup pools the head's blocks again, eight at a time, against a launch and a gap saved.  One launch / two launches,
+// us: fp32, head_dim 64: 4 blocks of 16 4.2 / 5.2, 16 of 16 5.2 / 5.6, 32 of 16 6.7 / 6.2, 10 of 64 5.2 / 6.2, 24 of 64 7.1 / 6.0;
+// head_dim 128: 4 of 64 5.2 / 6.5, 7 of 64 6.9 / 7.1, 10 of 64 7.3 / 6.9; bf16 (half the bytes a row, as many blocks):
+// 6 of 16 5.2 / 5.6, 16 of 16 6.5 / 6.0, 10 of 64 6.5 / 6.9, 24 of 64 8.8 / 7.0.
+bool pool_select_supported(const hf_config& c, int t_n, int kv_first, int kv_end) {
+  const int blocks = kv_end - kv_first, es = c.dtype == HF_BF16 ? 2 : 4;
+  return blocks <= (c.dtype == HF_BF16 ? 10 : 16) && (long long)blocks * c.block_kv * c.head_dim * es <= 220 * 1024 &&
+         pool_select_lds(c, t_n) <= 64 * 1024;
+}
+
+int launch_pool_select(const hf_config& c, const void* Q, int n_q, int t_m, const void* K, int n_kv, int t_n, int kv_first,
+                       int kv_end, int k, float* qbar, float* kbar_t, int32_t* idx, float* scores, hipStream_t s) {
+  const dim3 grid((t_m + kRows - 1) / kRows, c.batch * c.heads), block(512);
+#define HF_LAUNCH_POOL_SELECT(T, DD)                                                                                       \
+  hipLaunchKernelGGL((pool_select_kernel<T, DD>), grid, block, pool_select_lds(c, t_n), s, static_cast<const T*>(Q), n_q,  \
+                     c.block_q, t_m, static_cast<const T*>(K), n_kv, kv_stride_of(c, n_kv), c.block_kv, t_n, kv_first,     \
+                     kv_end, k, qbar, kbar_t, idx, scores)
+  if (c.dtype == HF_BF16) {
+    if (c.head_dim == 128) HF_LAUNCH_POOL_SELECT(bf16_t, 128); else HF_LAUNCH_POOL_SELECT(bf16_t, 64);
+  } else {
+    if (c.head_dim == 128) HF_LAUNCH_POOL_SELECT(float, 128); else HF_LAUNCH_POOL_SELECT(float, 64);
+  }
+#undef HF_LAUNCH_POOL_SELECT
+  return check_launch("hf_block_select(pool, select)");
 }
 
 int launch_score_select(const hf_config& c, const float* qbar, const float* kbar_t, int t_m, int t_n, int k,
