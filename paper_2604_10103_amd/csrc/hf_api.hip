@@ -517,7 +517,7 @@ static int select_attn_impl(const hf_config* cfg, const void* Q, const void* Q_h
                             const void* planes, const float* rope_cos_q, const float* rope_sin_q, void* O,
                             int32_t* block_idx_out, float* scores_or_null, const void* K_ev, const void* V_ev,
                             int32_t n_ev, int32_t ev_stride, void* state_out, void* planes_out, void* workspace,
-                            size_t workspace_bytes, void* stream) {
+                            size_t workspace_bytes, void* stream, int pool_first = 0, int pool_end = 0) {
   HF_TRY(check_cfg(cfg));
   if (!attn_mfma_fused_supported(*cfg)) {
     set_error("selection inside the attention launch covers bf16, head_dim 128, block_q 64 or 128 "
@@ -607,7 +607,8 @@ static int select_attn_impl(const hf_config* cfg, const void* Q, const void* Q_h
   }
   return launch_attn_mfma_step(*cfg, Q, n_q, K_win, V_win, n_kv, k, kbar, block_idx_out, scores_or_null,
                                st ? planes : nullptr, st ? st + bh * d * d : nullptr, rope_cos_q, rope_sin_q, Q_hist, O,
-                               K_ev, V_ev, n_ev, ev_stride, st_in, static_cast<float*>(state_out), planes_out, workspace, s);
+                               K_ev, V_ev, n_ev, ev_stride, st_in, static_cast<float*>(state_out), planes_out, workspace, s, pool_first,
+                               pool_end);
 }
 
 int hf_select_attn_fwd(const hf_config* cfg, const void* Q, const void* Q_hist, int32_t n_q, const void* K_win,
@@ -797,15 +798,20 @@ static int step_one_launch(const hf_config* cfg, const void* Q, const void* Q_hi
   hipStream_t s = static_cast<hipStream_t>(stream);
   // the state is frozen during a chunk's denoising steps: its planes are converted on the first and stay in the workspace
   const float* fresh = step_in_chunk == 0 ? static_cast<const float*>(state_or_null) : nullptr;
-  if (kv_end > kv_first || fresh)
+  int pool_first = 0, pool_end = 0;
+  if (!fresh && attn_pools_itself(*cfg, n_q, t_n, kv_first, kv_end)) {
+    pool_first = kv_first;
+    pool_end = kv_end;
+  } else if (kv_end > kv_first || fresh)
     HF_TRY(launch_pool_both(*cfg, nullptr, 0, 0, K, n_kv, t_n, kv_first, kv_end, nullptr, kbar, s, fresh, ws + w.planes));
   *done = true;
-  if (!state_or_null) return launch_attn_mfma_select(*cfg, Q, n_q, K, V, n_kv, k, kbar, block_idx, nullptr, O, s);
+  if (!state_or_null)
+    return launch_attn_mfma_select(*cfg, Q, n_q, K, V, n_kv, k, kbar, block_idx, nullptr, O, s, pool_first, pool_end);
   const float* st = static_cast<const float*>(state_or_null);
   const size_t d = cfg->head_dim;
   return launch_attn_mfma_fused(*cfg, Q, n_q, K, V, n_kv, nullptr, k, ws + w.planes,
                                 st + (size_t)cfg->batch * cfg->heads * d * d, rope_cos_q, rope_sin_q, Q_hist, O, s, nullptr,
-                                nullptr, kbar, block_idx, nullptr);
+                                nullptr, kbar, block_idx, nullptr, pool_first, pool_end);
 }
 
 int hf_stream_step(const hf_config* cfg, const hf_window* win, const void* Q, const void* Q_hist, int32_t n_q,
@@ -1015,11 +1021,14 @@ int hf_ring_last_step(const hf_config* cfg, hf_ring* ring, const void* Q, const 
       set_error("step_workspace of %zu bytes needed, %zu given", need, step_workspace ? step_workspace_bytes : (size_t)0);
       return HF_ERR_WORKSPACE;
     }
-    HF_TRY(launch_pool_both(*cfg, nullptr, 0, 0, K_cache, n_kv, t_n, kv_first, kv_end, nullptr, kbar, s,
-                            step_in_chunk == 0 ? static_cast<const float*>(state_or_null) : nullptr, ws + w.planes));
+    const float* fresh = step_in_chunk == 0 ? static_cast<const float*>(state_or_null) : nullptr;
+    const bool pools_itself = !fresh && attn_pools_itself(*cfg, n_q, t_n, kv_first, kv_end);
+    if (!pools_itself)
+      HF_TRY(launch_pool_both(*cfg, nullptr, 0, 0, K_cache, n_kv, t_n, kv_first, kv_end, nullptr, kbar, s, fresh, ws + w.planes));
     HF_TRY(select_attn_impl(cfg, Q, Q_hist, n_q, K_cache, V_cache, n_kv, kbar, state_or_null,
                             state_or_null ? ws + w.planes : nullptr, rope_cos_q, rope_sin_q, O, block_idx, nullptr, K_ev, V_ev,
-                            ring->n_chunk, cfg->kv_capacity, state_out, nullptr, step_workspace, step_workspace_bytes, stream));
+                            ring->n_chunk, cfg->kv_capacity, state_out, nullptr, step_workspace, step_workspace_bytes, stream,
+                            pools_itself ? kv_first : 0, pools_itself ? kv_end : 0));
   } else {
     HF_TRY(hf_ring_step(cfg, ring, Q, Q_hist, K_cache, V_cache, step_in_chunk, block_idx, state_or_null, rope_cos_q,
                         rope_sin_q, O, workspace, workspace_bytes, stream));

@@ -33,7 +33,7 @@
 // twice the time of its MFMAs.
 #include <stdlib.h>
 
-#include "hf_common.h"
+#include "hf_pool.h"
 
 namespace hf {
 
@@ -87,6 +87,7 @@ struct HistArgs {
   const float* kbar_t;   // [BH][d/4][T_n][4] pooled keys, feature-group-major (pool kernel)
   int32_t* idx_out;      // [BH][T_m][k] the ascending block list of every query block (also read back by the kernel)
   float* scores_out;     // [BH][T_m][T_n] the scores A of Eq. 4, or NULL
+  int pool_first, pool_end;   // kSel == 2: KV blocks that the workgroups pool themselves (kbar_t holds the others)
 };
 
 // ---- Eq. 4 and the Top-K of a query block inside the attention workgroup (kSel).
@@ -100,9 +101,15 @@ constexpr int kSelMaxBlocks = kMaxFusedSelectBlocks;
 // KS groups of NW wavefronts share the work, but every sum keeps the terms and the order it has with one group, so that a
 // query block's list does not depend on how many groups its launch takes: a thread of the q-bar sums takes 8 / KS features
 // of the same rows, group g the KV blocks 64 (g + KS u) + lane of its wavefront's slice of the head dimension.
-template <int NW, int KS>
+//
+// kPool: the KV blocks [pool_first, pool_end) are not in kbar_head; every workgroup pools them itself first (sums and order of
+// pool_kernel) and keeps the means in LDS, and the one of the head's first query block stores them for later calls.  Launches
+// of few workgroups last as long as their chain, and a launch of its own for some hundred keys is 3 us and a gap of it: a ring chunk
+// of four steps with 3 heads x 400 queries, 7 blocks to pool, 68.8 -> 65.1 us, with 40 heads x 128 queries, 2 blocks, 62.1 -> 56.5.
+template <int NW, int KS, bool kPool>
 __device__ __forceinline__ int* select_in_workgroup(char* smem, const bf16_t* Qh, int q0, int n_q, const float* kbar_head,
-                                                    int t_n, int k, int32_t* idx_row, float* scores_row) {
+                                                    int t_n, int k, int32_t* idx_row, float* scores_row, const bf16_t* Kh,
+                                                    int n_kv, int bkv, int pool_first, int pool_end) {
   constexpr int NT = 64 * NW * KS, BQ = 32 * NW, G = 4 * NW, CW = D / 4 / NW;
   constexpr int E = 8 / KS;             // features of a thread of the q-bar sums
   typedef __bf16 row_piece __attribute__((ext_vector_type(E)));
@@ -116,6 +123,8 @@ __device__ __forceinline__ int* select_in_workgroup(char* smem, const bf16_t* Qh
   float* sc = part + NW * t_pad;                        // [t_pad]
   int* sel = reinterpret_cast<int*>(sc + t_pad);        // [k]
   int* wave_count = sel + t_n;                          // [2][NW KS]
+  constexpr int KB = D + 4;                             // floats per row of the means formed here
+  float* fresh = reinterpret_cast<float*>(smem) + ((G * D + D + (NW + 1) * t_pad + t_n + 2 * NW * KS + 3) & ~3);
   const int rows = min(BQ, n_q - q0);
   // the block's rows and, right behind them, the first pass of pooled keys: both are on their way while the
   // pooled query is formed (the chain of this prologue is memory round trips, not arithmetic)
@@ -124,6 +133,22 @@ __device__ __forceinline__ int* select_in_workgroup(char* smem, const bf16_t* Qh
 #pragma unroll
   for (int i = 0; i < BQ / G; ++i)
     v[i] = *reinterpret_cast<const row_piece*>(Qh + (size_t)min(q0 + g + G * i, n_q - 1) * D + f0);
+  if constexpr (kPool) {
+    using P = Pool<bf16_t, D>;
+    const int sub = lane / P::LPR, col = (lane % P::LPR) * P::E;
+    for (int b = pool_first + wave; b < pool_end; b += NW * KS) {
+      float acc[P::E];
+      P::mean(Kh + col, b * bkv, min(n_kv, (b + 1) * bkv), sub, acc);
+      if (sub == 0) {
+#pragma unroll
+        for (int e = 0; e < P::E; e += 4) {
+          const float4 m = make_float4(acc[e], acc[e + 1], acc[e + 2], acc[e + 3]);
+          *reinterpret_cast<float4*>(fresh + (b - pool_first) * KB + col + e) = m;
+          if (q0 == 0) *reinterpret_cast<float4*>(const_cast<float*>(kbar_head) + ((size_t)((col + e) / 4) * t_n + b) * 4) = m;
+        }
+      }
+    }
+  }
   // pooled keys through a buffer descriptor: one offset register per block, the feature group's offset is scalar
   // (forty-eight 64-bit addresses would not fit next to the loads they feed)
   const __amdgpu_buffer_rsrc_t krsrc =
@@ -181,6 +206,16 @@ __device__ __forceinline__ int* select_in_workgroup(char* smem, const bf16_t* Qh
         const int j = min(j0 + 64 * KS * u, t_n - 1);
 #pragma unroll
         for (int c = 0; c < CW; ++c) kv[u][c] = kload(j, c);
+      }
+    }
+    if constexpr (kPool) {   // (the means formed above, in place of what memory held for their blocks)
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const int j = min(j0 + 64 * KS * u, t_n - 1);
+        if (j >= pool_first && j < pool_end) {
+#pragma unroll
+          for (int c = 0; c < CW; ++c) kv[u][c] = *reinterpret_cast<const float4*>(fresh + (j - pool_first) * KB + 4 * (slice * CW + c));
+        }
       }
     }
     // (feature groups outermost: the pooled query passes through a few registers instead of staying in sixty-four)
@@ -548,8 +583,8 @@ __device__ __forceinline__ void absorb_role(char* smem, const AbsorbArgs& ab) {
   }
 }
 
-// kSel: 1 = the workgroup first selects its KV blocks itself (Eq. 4 from hist.kbar_t, list to hist.idx_out); the
-// first ab.role_blocks workgroup ids (a multiple of eight) absorb evicted tokens instead (absorb_role)
+// kSel: 1 = the workgroup first selects its KV blocks itself (Eq. 4 from hist.kbar_t, list to hist.idx_out), 2 = and pools
+// some of them first; the first ab.role_blocks workgroup ids (a multiple of eight) absorb evicted tokens instead (absorb_role)
 // KS: groups of NW wavefronts that share the query block, group g the tiles g, g + KS, ... of its list; their partial (m, l, O)
 // meet in LDS behind the loop and every group finishes 4 / KS of the four 32-feature blocks
 template <int NW, int kFused, int kSel, int KS>
@@ -594,9 +629,10 @@ __global__ __launch_bounds__(64 * NW * KS, 2) void attn_mfma_kernel(
   const int nsel = (kSel || idx) ? k : t_n;
   const int* sel_lds = nullptr;   // kSel: the list in LDS, valid until the first tile is requested
   if (kSel)
-    sel_lds = select_in_workgroup<NW, KS>(smem, Qh, qb * BQ, n_q, hist.kbar_t + (size_t)bh * (D / 4) * t_n * 4, t_n, k,
-                                      hist.idx_out + ((size_t)bh * t_m + qb) * k,
-                                      hist.scores_out ? hist.scores_out + ((size_t)bh * t_m + qb) * t_n : nullptr);
+    sel_lds = select_in_workgroup<NW, KS, kSel == 2>(smem, Qh, qb * BQ, n_q, hist.kbar_t + (size_t)bh * (D / 4) * t_n * 4, t_n, k,
+                                                 hist.idx_out + ((size_t)bh * t_m + qb) * k,
+                                                 hist.scores_out ? hist.scores_out + ((size_t)bh * t_m + qb) * t_n : nullptr,
+                                                 Kh, n_kv, bkv, hist.pool_first, hist.pool_end);
   const int subs = (bkv + TK - 1) / TK;
   const int ntiles = (nsel * subs + KS - 1) / KS;   // every group the same number: the barriers are the workgroup's
 
@@ -1123,6 +1159,15 @@ static int key_groups(const hf_config& c, long long attending) {
   return workgroups <= 512 || (workgroups > 1024 && workgroups <= 1536) ? 2 : 1;
 }
 
+// Whether the selecting launch pools the KV blocks [first, end) itself: launches with two groups of wavefronts and at most
+// two blocks per wavefront.  Up to 16 of them, ring chunks of four steps with / without: 8 blocks 96.5 / 99.5 us (40 heads x 480),
+// 10 blocks 76.6 / 75.0 (4 x 600) and 77.6 / 76.9 (8 x 600), 15 blocks 91.4 / 85.7 (8 x 940).
+constexpr int kMaxOwnBlocks = 8;
+bool attn_pools_itself(const hf_config& c, int n_q, int t_n, int first, int end) {
+  const long long attending = (long long)c.batch * c.heads * ((n_q + c.block_q - 1) / c.block_q);
+  return end > first && end - first <= kMaxOwnBlocks && t_n <= 512 && key_groups(c, attending) == 2;
+}
+
 static int launch_attn_mfma_impl(const hf_config& c, const void* Q, int n_q, const void* K, const void* V, int n_kv,
                                  const int32_t* idx, int k, const HistArgs* hist, void* O, hipStream_t s,
                                  const AbsorbArgs* absorb = nullptr) {
@@ -1161,7 +1206,14 @@ static int launch_attn_mfma_impl(const hf_config& c, const void* Q, int n_q, con
                 kSelMaxBlocks);
       return HF_ERR_SHAPE;
     }
-    if (c.block_q == 64) {
+    if (h.pool_end > h.pool_first) {
+      if (!attn_pools_itself(c, n_q, t_n, h.pool_first, h.pool_end)) { set_error("in-kernel pooling: too many blocks"); return HF_ERR_SHAPE; }
+      if (c.block_q == 64) {
+        if (fused == 0) HF_LAUNCH_ATTN_KS(2, 0, 2, 2); else if (fused == 1) HF_LAUNCH_ATTN_KS(2, 1, 2, 2); else HF_LAUNCH_ATTN_KS(2, 2, 2, 2);
+      } else {
+        if (fused == 0) HF_LAUNCH_ATTN_KS(4, 0, 2, 2); else if (fused == 1) HF_LAUNCH_ATTN_KS(4, 1, 2, 2); else HF_LAUNCH_ATTN_KS(4, 2, 2, 2);
+      }
+    } else if (c.block_q == 64) {
       if (fused == 0) HF_LAUNCH_ATTN_SEL(2, 0, 1); else if (fused == 1) HF_LAUNCH_ATTN_SEL(2, 1, 1); else HF_LAUNCH_ATTN_SEL(2, 2, 1);
     } else {
       if (fused == 0) HF_LAUNCH_ATTN_SEL(4, 0, 1); else if (fused == 1) HF_LAUNCH_ATTN_SEL(4, 1, 1); else HF_LAUNCH_ATTN_SEL(4, 2, 1);
@@ -1198,12 +1250,12 @@ bool attn_mfma_fused_supported(const hf_config& c) { return attn_mfma_supported(
 int launch_attn_mfma_fused(const hf_config& c, const void* Q, int n_q, const void* K, const void* V, int n_kv,
                            const int32_t* idx, int k, const void* planes, const float* zvec, const float* cosq,
                            const float* sinq, const void* Q_hist, void* O, hipStream_t s, float* lse2_out,
-                           void* olocal_out, const float* kbar_t, int32_t* idx_out, float* scores_out) {
+                           void* olocal_out, const float* kbar_t, int32_t* idx_out, float* scores_out, int pool_first, int pool_end) {
   // One bf16 plane of L (2^-9 per element, errors of the d terms of a readout average out) costs the
   // output nothing measurable next to the bf16 rounding of P and O; HF_FLAG_HISTORY_TWO_PLANES adds the low plane.
   const HistArgs h = {static_cast<const bf16_t*>(planes), zvec, c.eps, c.z_scale, (c.flags & HF_FLAG_HISTORY_TWO_PLANES) ? 2 : 1,
                       c.phi, cosq, sinq, Q_hist == Q ? nullptr : static_cast<const bf16_t*>(Q_hist), nullptr, nullptr, nullptr,
-                      lse2_out, static_cast<bf16_t*>(olocal_out), kbar_t, idx_out, scores_out};
+                      lse2_out, static_cast<bf16_t*>(olocal_out), kbar_t, idx_out, scores_out, pool_first, pool_end};
   return launch_attn_mfma_impl(c, Q, n_q, K, V, n_kv, idx, k, &h, O, s);
 }
 
@@ -1232,7 +1284,7 @@ int launch_attn_mfma_step(const hf_config& c, const void* Q, int n_q, const void
                           const float* kbar_t, int32_t* idx_out, float* scores_out, const void* planes,
                           const float* zvec, const float* cosq, const float* sinq, const void* Q_hist, void* O,
                           const void* K_ev, const void* V_ev, int n_ev, int ev_stride, const float* state_in,
-                          float* state_out, void* planes_out, void* workspace, hipStream_t s) {
+                          float* state_out, void* planes_out, void* workspace, hipStream_t s, int pool_first, int pool_end) {
   const int BH = c.batch * c.heads;
   AbsorbArgs ab = {};
   ab.K = static_cast<const bf16_t*>(K_ev);
@@ -1252,22 +1304,27 @@ int launch_attn_mfma_step(const hf_config& c, const void* Q, int n_q, const void
   if (planes) {
     h = HistArgs{static_cast<const bf16_t*>(planes), zvec, c.eps, c.z_scale, (c.flags & HF_FLAG_HISTORY_TWO_PLANES) ? 2 : 1,
                  c.phi, cosq, sinq, Q_hist == Q ? nullptr : static_cast<const bf16_t*>(Q_hist), nullptr, nullptr, nullptr,
-                 nullptr, nullptr, kbar_t, idx_out, scores_out};
+                 nullptr, nullptr, kbar_t, idx_out, scores_out, pool_first, pool_end};
   } else {
     h.kbar_t = kbar_t;
     h.idx_out = idx_out;
     h.scores_out = scores_out;
+    h.pool_first = pool_first;
+    h.pool_end = pool_end;
   }
   return launch_attn_mfma_impl(c, Q, n_q, K, V, n_kv, nullptr, k, &h, O, s, &ab);
 }
 
 // selection (Eq. 4) and attention (Eq. 5) in one launch, no history term
 int launch_attn_mfma_select(const hf_config& c, const void* Q, int n_q, const void* K, const void* V, int n_kv, int k,
-                            const float* kbar_t, int32_t* idx_out, float* scores_out, void* O_local, hipStream_t s) {
+                            const float* kbar_t, int32_t* idx_out, float* scores_out, void* O_local, hipStream_t s, int pool_first,
+                            int pool_end) {
   HistArgs h = {};
   h.kbar_t = kbar_t;
   h.idx_out = idx_out;
   h.scores_out = scores_out;
+  h.pool_first = pool_first;
+  h.pool_end = pool_end;
   return launch_attn_mfma_impl(c, Q, n_q, K, V, n_kv, nullptr, k, &h, O_local, s);
 }
 
@@ -1275,7 +1332,7 @@ int launch_attn_mfma_select(const hf_config& c, const void* Q, int n_q, const vo
 int launch_attn_mfma_stats(const hf_config& c, const void* Q, int n_q, const void* K, const void* V, int n_kv,
                            const int32_t* idx, int k, const void* dO, float* lse2, float* dvec, hipStream_t s) {
   const HistArgs h = {nullptr, nullptr, 0.0f, 0.0f, 0, 0, nullptr, nullptr, nullptr, static_cast<const bf16_t*>(dO),
-                      lse2, dvec, nullptr, nullptr, nullptr, nullptr, nullptr};
+                      lse2, dvec, nullptr, nullptr, nullptr, nullptr, nullptr, 0, 0};
   return launch_attn_mfma_impl(c, Q, n_q, K, V, n_kv, idx, k, &h, nullptr, s);
 }
 

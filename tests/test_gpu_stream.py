@@ -270,3 +270,43 @@ def test_ring_arguments_are_checked():
                         torch.empty((1, 2, 400, 128), dtype=torch.bfloat16, device=DEV),
                         torch.empty(1 << 20, dtype=torch.uint8, device=DEV))
     assert "open" in str(e.value)
+
+
+@pytest.mark.parametrize("heads,block,n_chunk,n_sink,slots", [
+    (2, 64, 64, 0, 2), (3, 64, 100, 10, 3), (2, 64, 450, 30, 2), (2, 64, 513, 0, 2), (40, 64, 65, 63, 2), (3, 128, 300, 0, 3),
+    (2, 128, 1000, 5, 2), (2, 64, 70, 7, 40),
+])
+@pytest.mark.parametrize("last", [False, True])
+def test_steps_that_pool_the_chunk_in_the_attention_launch(heads, block, n_chunk, n_sink, slots, last):
+    """A later denoising step of small chunks pools the chunk's blocks in the workgroups that select: same lists and same bits as
+    pooling the whole window first, whatever part of a block the chunk shares with its neighbours."""
+    cap = n_sink + slots * n_chunk
+    cfg = hf.make_config(1, heads, 128, "bf16", block, block, 0.3, kv_capacity=cap)
+    packed = hf.make_config(1, heads, 128, "bf16", block, block, 0.3)   # (the cache is full: a window of its length)
+    mk = lambda n, s: wl.randn((1, heads, n, 128), 91_000 + s, 0.5, torch.bfloat16).to(DEV)
+    K, V, Q = mk(cap, 0), mk(cap, 1), mk(n_chunk, 2)
+    ring = hf.make_ring(n_sink, n_chunk)
+    ring.n_filled, ring.cur_slot, ring.next_slot, ring.absorbed_ahead = slots, slots - 2, slots - 1, 0
+    st = torch.empty(hf.hf_state_bytes(cfg) // 4, dtype=torch.float32, device=DEV)
+    hf.hf_state_init(cfg, st)
+    hf.hf_absorb_evicted(cfg, st, mk(50, 3), mk(50, 4))
+    st2 = torch.empty_like(st)
+    ws = torch.full((hf.hf_workspace_bytes(cfg, n_chunk, cap),), 255, dtype=torch.uint8, device=DEV)
+    step_ws = torch.empty(max(hf.hf_step_workspace_bytes(cfg, n_chunk, n_chunk), 256), dtype=torch.uint8, device=DEV)
+    idx = torch.full((1, heads, -(-n_chunk // block), hf.hf_select_k(cfg, cap)), -1, dtype=torch.int32, device=DEV)
+    idx2, O, O2 = torch.full_like(idx, -1), torch.full_like(Q, 7.0), torch.full_like(Q, 7.0)
+    hf.hf_ring_step(cfg, ring, Q, K, V, 0, idx, st, O, ws)
+    first = n_sink + (slots - 2) * n_chunk
+    for step in (1, 2):
+        K[:, :, first:first + n_chunk] = mk(n_chunk, 10 + step)
+        if last and step == 2:
+            assert hf.hf_ring_last_step(cfg, ring, Q, K, V, step, idx, st, O, ws, st2, step_ws)
+        else:
+            hf.hf_ring_step(cfg, ring, Q, K, V, step, idx, st, O, ws)
+        planes = torch.empty(hf.hf_state_planes_bytes(cfg), dtype=torch.uint8, device=DEV)
+        hf.hf_state_planes(cfg, st, planes)
+        pooled = torch.empty(hf.hf_pooled_keys_bytes(packed, cap), dtype=torch.uint8, device=DEV)
+        hf.hf_pool_keys(packed, K, pooled)
+        hf.hf_select_attn_fwd(packed, Q, K, V, pooled, st, planes, O2, idx2)
+        torch.cuda.synchronize()
+        assert torch.equal(idx, idx2) and torch.equal(O, O2), step
