@@ -360,38 +360,61 @@ __global__ __launch_bounds__(128 * KS, 4) void attn_d64_kernel(
   if (hist.L) {
     // ---- O += R(phi(q)) L / (z_scale phi(q).z + eps) (Eq. 3, 6) on the fp32 matrix instruction, whose results lie as those
     // of the bf16 one: O_local is scaled by the denominator, the products add the numerator, one division at the end
-    const float* L = hist.L + (size_t)bh * D * D;
-    const float* z = hist.z + (size_t)bh * D + 8 * h;
-    const bf16_t* qp = static_cast<const bf16_t*>(hist.q_hist) + q_at * D + 8 * h;
-    const size_t trow = (size_t)min(q_row, n_q - 1) * (D / 2) + 4 * h;
-    // (rolled: what is in flight here is not to cost the loop above its registers)
-    float den = 0.0f;
-#pragma unroll 1
-    for (int s = 0; s < 8; ++s) {
-      const f32x4 x = load4<bf16_t>(qp + 16 * (s >> 1) + 4 * (s & 1));
-      const f32x4 zz = *reinterpret_cast<const f32x4*>(z + 16 * (s >> 1) + 4 * (s & 1));
+    const size_t trow = (size_t)min(q_row, n_q - 1) * (D / 2);
+    // the lane's features 16 (i / 2) + 8 h + 4 (i % 2) .. + 4, i < 8, in one round trip; L's rows of half of them at a time
+    int half = h;
+    asm volatile("" : "+v"(half));   // (opaque: addresses of its own, or those of the prologue stay in registers through the loop)
+    const float* L = hist.L + (size_t)bh * D * D + 32 * grp + l32;
+    const float* z = hist.z + (size_t)bh * D + 8 * half;
+    const bf16_t* qp = static_cast<const bf16_t*>(hist.q_hist) + q_at * D + 8 * half;
+    f32x4 x[8];
 #pragma unroll
-      for (int e = 0; e < 4; ++e) den = fmaf(phi_apply(x[e], hist.phi_kind), zz[e], den);
+    for (int i = 0; i < 8; ++i) x[i] = load4<bf16_t>(qp + 16 * (i >> 1) + 4 * (i & 1));
+    f32x4 a[4];
+    auto rows_of = [&](int i0) {
+#pragma unroll
+      for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) a[i][e] = L[(16 * ((i0 + i) >> 1) + 8 * half + 4 * (i & 1) + e) * D];
+    };
+    rows_of(0);
+    if (hist.phi_kind == HF_PHI_RELU) {   // uniform
+#pragma unroll
+      for (int i = 0; i < 8; ++i)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) x[i][e] = phi_apply(x[i][e], HF_PHI_RELU);
+    } else {
+#pragma unroll
+      for (int i = 0; i < 8; ++i)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) x[i][e] = phi_apply(x[i][e], HF_PHI_ELU1);
+    }
+    float den = 0.0f;
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      const f32x4 zz = *reinterpret_cast<const f32x4*>(z + 16 * (i >> 1) + 4 * (i & 1));
+#pragma unroll
+      for (int e = 0; e < 4; ++e) den = fmaf(x[i][e], zz[e], den);
+    }
+    if (hist.cosq) {
+#pragma unroll
+      for (int i = 0; i < 8; ++i) {
+        const size_t at = trow + 4 * half + 8 * (i >> 1) + 2 * (i & 1);
+        const f32x2 cs = *reinterpret_cast<const f32x2*>(hist.cosq + at), sn = *reinterpret_cast<const f32x2*>(hist.sinq + at);
+        x[i] = rotate4(x[i], cs[0], sn[0], cs[1], sn[1]);
+      }
     }
     den = hist.z_scale * both_halves_sum(den) + hist.eps;
     w *= den;
 #pragma unroll
     for (int r = 0; r < 16; ++r) os[r] *= w;
-#pragma unroll 1
-    for (int s = 0; s < 8; ++s) {   // key features 16 (s / 2) + 8 h + 4 (s % 2) .. + 4
-      f32x4 x = load4<bf16_t>(qp + 16 * (s >> 1) + 4 * (s & 1));
-      float a[4];
 #pragma unroll
-      for (int e = 0; e < 4; ++e) a[e] = L[(16 * (s >> 1) + 8 * h + 4 * (s & 1) + e) * D + 32 * grp + l32];
+    for (int i0 = 0; i0 < 8; i0 += 4) {
+      if (i0) rows_of(i0);
 #pragma unroll
-      for (int e = 0; e < 4; ++e) x[e] = phi_apply(x[e], hist.phi_kind);
-      if (hist.cosq) {
-        const f32x2 cs = *reinterpret_cast<const f32x2*>(hist.cosq + trow + 8 * (s >> 1) + 2 * (s & 1));
-        const f32x2 sn = *reinterpret_cast<const f32x2*>(hist.sinq + trow + 8 * (s >> 1) + 2 * (s & 1));
-        x = rotate4(x, cs[0], sn[0], cs[1], sn[1]);
-      }
+      for (int i = 0; i < 4; ++i)
 #pragma unroll
-      for (int e = 0; e < 4; ++e) os = mfma_f32_wide(a[e], x[e], os);
+        for (int e = 0; e < 4; ++e) os = mfma_f32_wide(a[i][e], x[i0 + i][e], os);
     }
     w = 1.0f / den;
   }
