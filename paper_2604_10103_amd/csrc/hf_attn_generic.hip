@@ -13,6 +13,8 @@
 // D = 128, next to 16 KB requested from the caches one phase ahead.
 #include <stdlib.h>
 
+#include <type_traits>
+
 #include "hf_f32_mfma.h"
 
 namespace hf {
@@ -243,25 +245,43 @@ __global__ __launch_bounds__(256, 2) void attn_wide_kernel(const T* __restrict__
     const float* z = hist.z + (size_t)bh * D + 4 * g;
     const T* qh = static_cast<const T*>(hist.q_hist);
     f32x4 ph[NQ][C];
+    // (all loads first, one uniform choice of the feature map: a branch for every feature kept the loads apart)
+#pragma unroll
+    for (int n = 0; n < NQ; ++n)
+#pragma unroll
+      for (int c = 0; c < C; ++c) ph[n][c] = load4<T>(qh + ((size_t)bh * n_q + min(row[n], n_q - 1)) * D + 16 * c + 4 * g);
+    if (hist.phi_kind == HF_PHI_RELU) {
+#pragma unroll
+      for (int n = 0; n < NQ; ++n)
+#pragma unroll
+        for (int c = 0; c < C; ++c)
+#pragma unroll
+          for (int e = 0; e < 4; ++e) ph[n][c][e] = phi_apply(ph[n][c][e], HF_PHI_RELU);
+    } else {
+#pragma unroll
+      for (int n = 0; n < NQ; ++n)
+#pragma unroll
+        for (int c = 0; c < C; ++c)
+#pragma unroll
+          for (int e = 0; e < 4; ++e) ph[n][c][e] = phi_apply(ph[n][c][e], HF_PHI_ELU1);
+    }
 #pragma unroll
     for (int n = 0; n < NQ; ++n) {
       const size_t qrow = (size_t)min(row[n], n_q - 1);
       float acc = 0.0f;
 #pragma unroll
       for (int c = 0; c < C; ++c) {
-        f32x4 x = load4<T>(qh + ((size_t)bh * n_q + qrow) * D + 16 * c + 4 * g);
         const f32x4 zz = *reinterpret_cast<const f32x4*>(z + 16 * c);
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          x[e] = phi_apply(x[e], hist.phi_kind);
-          acc = fmaf(x[e], zz[e], acc);
-        }
-        if (hist.cosq) {
+        for (int e = 0; e < 4; ++e) acc = fmaf(ph[n][c][e], zz[e], acc);
+      }
+      if (hist.cosq) {
+#pragma unroll
+        for (int c = 0; c < C; ++c) {
           const size_t at = qrow * (D / 2) + 8 * c + 2 * g;
           const float2 cs = *reinterpret_cast<const float2*>(hist.cosq + at), sn = *reinterpret_cast<const float2*>(hist.sinq + at);
-          x = rotate4(x, cs.x, sn.x, cs.y, sn.y);
+          ph[n][c] = rotate4(ph[n][c], cs.x, sn.x, cs.y, sn.y);
         }
-        ph[n][c] = x;
       }
       den[n] = hist.z_scale * column_sum(acc) + hist.eps;
       w[n] *= den[n];
@@ -615,21 +635,26 @@ __global__ __launch_bounds__(256, 2) void attn_wide32_kernel(const float* __rest
     const size_t trow = (size_t)min(row, n_q - 1) * (D / 2) + 2 * h;
     f32x4 ph[C / KS];
     float acc = 0.0f;
+    auto features = [&](auto relu) {   // (one uniform choice of the feature map: a branch for every feature kept the loads apart)
 #pragma unroll
-    for (int c = 0; c < C; ++c) {
-      f32x4 x = *reinterpret_cast<const f32x4*>(qp + 8 * c);
-      const f32x4 zz = *reinterpret_cast<const f32x4*>(z + 8 * c);
+      for (int c = 0; c < C; ++c) {
+        f32x4 x = *reinterpret_cast<const f32x4*>(qp + 8 * c);
+        const f32x4 zz = *reinterpret_cast<const f32x4*>(z + 8 * c);
 #pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        x[e] = phi_apply(x[e], hist.phi_kind);
-        acc = fmaf(x[e], zz[e], acc);
-      }
-      if (c / (C / KS) == kz) {   // uniform
-        if (hist.cosq) {
-          const f32x2 cs = *reinterpret_cast<const f32x2*>(hist.cosq + trow + 4 * c), sn = *reinterpret_cast<const f32x2*>(hist.sinq + trow + 4 * c);
-          x = rotate4(x, cs[0], sn[0], cs[1], sn[1]);
+        for (int e = 0; e < 4; ++e) {
+          x[e] = phi_apply(x[e], relu.value ? HF_PHI_RELU : HF_PHI_ELU1);
+          acc = fmaf(x[e], zz[e], acc);
         }
-        ph[c % (C / KS)] = x;
+        if (c / (C / KS) == kz) ph[c % (C / KS)] = x;   // uniform
+      }
+    };
+    if (hist.phi_kind == HF_PHI_RELU) features(std::true_type{}); else features(std::false_type{});
+    if (hist.cosq) {
+#pragma unroll
+      for (int i = 0; i < C / KS; ++i) {
+        const size_t at = trow + 4 * (kz * (C / KS) + i);
+        const f32x2 cs = *reinterpret_cast<const f32x2*>(hist.cosq + at), sn = *reinterpret_cast<const f32x2*>(hist.sinq + at);
+        ph[i] = rotate4(ph[i], cs[0], sn[0], cs[1], sn[1]);
       }
     }
     const float den = hist.z_scale * both_halves(acc) + hist.eps;
