@@ -624,7 +624,7 @@ int launch_split(const hf_config& c, const void* Q, int n_q, const void* K, cons
 
 // The descriptors hold the first key in 24 bits.  Launches of few query rows stay with the kernel that gives every 32 rows a
 // workgroup of their own, which fills the chip with half as many rows and splits a list over four wavefronts with less around
-// the loop: 114 workgroups of 64 rows (6 heads x 1170 rows, k = 10 of 37) 38 us there and 48 here, 152 of them 62 and 49.
+// the loop: 114 workgroups of 64 rows (6 heads x 1170 rows, k = 10 of 37) 35 us there and 48 here, 152 of them 57 and 45.
 bool attn_split_supported(const hf_config& c, int n_q, int n_kv) {
   const long long wgs = (long long)c.batch * c.heads * ((n_q + c.block_q - 1) / c.block_q) * (c.block_q / 64);
   return c.dtype == HF_F32 && c.block_q % 64 == 0 && c.block_kv % TK == 0 && n_kv < (1 << 23) && wgs > 128;

@@ -35,6 +35,8 @@ SHAPES = [
     (150, 128, 64, 32, 129, 33, 1.0), (300, 128, 64, 64, 70, 300, None), (390, 128, 64, 64, 100, 200, 0.5),
     (270, 128, 128, 64, 200, 130, 0.4), (66, 64, 64, 64, 65, 100, 1.0), (45, 64, 192, 32, 200, 300, 0.3),
     (390, 64, 64, 96, 100, 200, None), (270, 64, 64, 32, 193, 65, 0.4),
+    # (between the small launches and these: fp32 products, 32 rows a workgroup)
+    (90, 128, 64, 64, 33, 300, 0.4), (201, 128, 32, 32, 40, 100, 0.5), (90, 64, 64, 32, 40, 200, 0.5), (201, 64, 32, 64, 33, 150, None),
 ]
 
 
@@ -77,7 +79,8 @@ def test_forward_and_gradients(case, gain, phi, rope):
             assert rel_l2(x, ref) <= 5e-5 and max_abs(x, ref) <= 1e-4 * max(np.abs(ref).max(), 1e-2), (name, h, rel_l2(x, ref))
 
 
-BAD = [(66, 128), (150, 128), (390, 128), (66, 64), (390, 64)]   # four, two and one group; two and one
+# four, two and one group; two and one; fp32 products, 32 rows a workgroup
+BAD = [(66, 128), (150, 128), (390, 128), (66, 64), (390, 64), (30, 128), (30, 64)]
 
 
 def _bad_case(heads, d):
@@ -112,8 +115,29 @@ def test_values_without_a_finite_remainder(heads, d):
         assert want.isfinite().all() and ((got - want).norm() / want.norm()).item() <= F32_REL_L2
     V[:, :, n_kv - 1, 3] = INF
     V[:, :, n_kv - 1, 40] = LOWEST
-    O, want = _attend(cfg, Q, K, V, idx), want
+    O = _attend(cfg, Q, K, V, idx)
     assert (O[:, :, :64, 3] == INF).all() and (O[:, :, 128:, 3] == INF).all() and O[:, :, 64:128].isfinite().all()
     assert (O[:, :, :64, 40] < -1e30).all() and (O[:, :, 128:, 40] < -1e30).all()
     K[:, :, n_kv - 1, 0] = INF                 # a score of +infinity: no softmax
     assert _attend(cfg, Q, K, V, idx)[:, :, :64].isnan().all()
+
+
+@pytest.mark.parametrize("bad", [NAN, INF])
+@pytest.mark.parametrize("bq,bkv,n_kv", [(64, 32, 300), (128, 96, 96 * 3 + 10)])
+def test_bf16_at_head_dim_64_beyond_small_launches(bq, bkv, n_kv, bad):
+    """More than 64 blocks of 64 rows take the kernel that splits the probabilities: infinite values of selected keys stay
+    infinite in their feature alone, unselected blocks are not read."""
+    heads, n_q = 33, 2 * bq + 5
+    cfg = hf.make_config(1, heads, 64, "bf16", bq, bkv, 0.5)
+    Q, K, V = (t.bfloat16().to(DEV) for t in _tensors(heads, (n_q, n_kv, n_kv), 64, 40, 0.5))
+    last = (n_kv - 1) // bkv
+    idx = torch.tensor([[1, last], [last, 2], [1, 2]], dtype=torch.int32, device=DEV).expand(1, heads, 3, 2).contiguous()
+    want = _attend(cfg, Q, K, V, idx)
+    K[:, :, :bkv] = bad
+    V[:, :, :bkv] = bad
+    V[:, :, n_kv - 1, 3] = INF
+    V[:, :, n_kv - 1, 40] = -INF
+    O = _attend(cfg, Q, K, V, idx)
+    same = [f for f in range(64) if f not in (3, 40)]
+    assert want.isfinite().all() and torch.equal(O[..., same], want[..., same]) and torch.equal(O[:, :, 2 * bq:], want[:, :, 2 * bq:])
+    assert (O[:, :, :2 * bq, 3] == INF).all() and (O[:, :, :2 * bq, 40] == -INF).all()
