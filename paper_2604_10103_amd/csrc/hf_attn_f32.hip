@@ -3,7 +3,7 @@
 //
 // An fp32 value is the sum of three bf16 values (8 + 8 + 8 bits of its 24), x = hi + mid + lo, each remainder exact.  A product
 // of two of them is six bf16 products, each exact, summed in fp32 by the matrix cores:
-//   x y = hi hi' + (hi mid' + mid hi') + (hi lo' + mid mid' + lo hi')     (what is left out is below 2^-22 of it)
+//   x y = hi hi' + (hi mid' + mid hi') + (hi lo' + mid mid' + lo hi')     (what is left out is below 2^-21 of it)
 // The bf16 instruction has sixteen times the rate of the fp32 one, so six products take 6/16 of its matrix time, and a sum is
 // rounded once per sixteen terms instead of once per two.  A tile's P V is summed for itself and added to the output once.
 // Against 64 bits (Gaussian inputs of standard deviation 0.5, 1, 2; 2100 to 9360 keys): 1.4e-7..2.3e-7, 2.8e-7..4.0e-7,
@@ -33,8 +33,8 @@ constexpr int TK = 32;            // keys per tile
 constexpr int RG = 2;             // wavefronts along the rows
 constexpr float kGrow = 8.0f;     // log2 units: rescale only when a row's maximum grew by more than 2^8
 
-// 16-byte unit u of token row r sits at u ^ swizzle(r): fragment reads (one unit of 32 rows) and transposing reads (four units
-// of four rows) are free of bank conflicts; what is written at a time is whole rows
+// Keys: 16-byte unit u of row r sits at u ^ swizzle(r), and fragment reads (one unit of 32 rows) are free of bank conflicts; what
+// is written at a time is whole rows.
 template <int D> __device__ __forceinline__ int k_swizzle(int r) {
   if (D == 128) return r & 15;
   return ((r >> 1) & 1) | (((r >> 2) ^ (r >> 3)) & 1) << 1 | (((r >> 3) ^ (r >> 4)) & 1) << 2;
