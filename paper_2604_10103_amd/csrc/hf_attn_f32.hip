@@ -1,13 +1,18 @@
 // Block-sparse window attention (Eq. 5) with the history term (Eq. 3, 6) for fp32 storage on the bf16 matrix instruction:
 // block_q a multiple of 64, block_kv of 32.
 //
-// An fp32 value is the sum of three bf16 values (8 + 8 + 8 bits of its 24), x = hi + mid + lo, each remainder exact.  A product
-// of two of them is six bf16 products, each exact, summed in fp32 by the matrix cores:
-//   x y = hi hi' + (hi mid' + mid hi') + (hi lo' + mid mid' + lo hi')     (what is left out is below 2^-21 of it)
+// An fp32 value is the sum of three bf16 values, x = hi + mid + lo, each the rest so far rounded to nearest: |mid| <= 2^-8 and
+// |lo| <= 2^-17 of x's leading bit, the remainders exact.  A product of two of them is six bf16 products, each exact, summed in
+// fp32 by the matrix cores:
+//   x y = hi hi' + (hi mid' + mid hi') + (hi lo' + mid mid' + lo hi')
+// What is left out, mid lo' + lo mid' + lo lo', is at most 2^-24 of the product (one rounding to fp32) and of either sign.
 // The bf16 instruction has sixteen times the rate of the fp32 one, so six products take 6/16 of its matrix time, and a sum is
 // rounded once per sixteen terms instead of once per two.  A tile's P V is summed for itself and added to the output once.
-// Against 64 bits (Gaussian inputs of standard deviation 0.5, 1, 2; 2100 to 9360 keys): 1.4e-7..2.3e-7, 2.8e-7..4.0e-7,
-// 6.2e-7..1.4e-6, with both products on the fp32 instruction 2.5e-7..7.8e-7, 3.8e-7..9.0e-7, 8.7e-7..2.2e-6.
+// Against 64 bits, with both products on the fp32 instruction / here (32 to 4096 keys): Gaussian inputs of standard deviation 0.5
+// 1.3e-7..5.9e-7 / 1.0e-7..2.1e-7, 1 2.5e-7..7.2e-7 / 1.8e-7..3.7e-7, 2 4.3e-7..1.7e-6 / 3.1e-7..1.2e-6; low fifteen bits all
+// set, both signs 1.2e-7..6.0e-7 / 0.8e-7..1.9e-7, one sign 0.75e-7..2.7e-7 / 0.76e-7..1.2e-7.  Parts cut off instead of rounded leave out
+// up to 2^-21, always of the product's sign: with such inputs up to 1.2 times the error of the fp32 instruction, for 16 us less
+// of 468 (832x480).  Eight products (2^-30 left out) take 545.
 //
 // Layout as in the bf16 kernels (hf_attn_mfma.hip): a wavefront owns 32 query rows and walks tiles of 32 keys, both products are
 // formed transposed (S^T = K Q^T, O^T += V^T P^T), a lane's sixteen scores belong to one query, and the exponentials split into
@@ -17,10 +22,9 @@
 // in LDS behind the loop and every group finishes DT / KG feature blocks.  Of the three planes of Q two stay in registers, the
 // third (one product of six) in LDS.
 //
-// 832x480 in fp32 (12 heads of 128, 4680 x 9360, k = 37 of 147 blocks of 64): 584 us on the fp32 instruction, 428 us here, 425
-// GFLOP of bf16 products at 1.0 PFLOP/s; the library's bf16 matrix product reaches 1.2 on this card.  Splitting next to the
-// matrix instructions instead of behind them, transposing reads for V, and remainders by dot products with (-1, 0) instead of
-// subtractions (they run on the matrix pipe) all took the same 470 us; cutting bits off instead of rounding took 452.
+// 832x480 in fp32 (12 heads of 128, 4680 x 9360, k = 37 of 147 blocks of 64; selection included): 613 us on the fp32 instruction,
+// 468 here.  Splitting next to the matrix instructions instead of behind them, transposing reads for V, and remainders by dot
+// products with (-1, 0) instead of subtractions (they run on the matrix pipe) gained nothing.
 #include "hf_f32_mfma.h"
 
 namespace hf {
@@ -28,6 +32,7 @@ namespace hf {
 namespace {
 
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
+typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 
 constexpr int TK = 32;            // keys per tile
 constexpr int RG = 2;             // wavefronts along the rows
@@ -51,7 +56,7 @@ __device__ __forceinline__ float both_halves_sum(float x) {
   return __uint_as_float(sw[0]) + __uint_as_float(sw[1]);
 }
 
-// Eight values split together: the upper sixteen bits of a float are a bf16 value, what they leave out is exact.
+// Eight values split together.  (The last remainder has at most eight significant bits: its upper half is all of it.)
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 struct Split {
   u32x4 part[3];
@@ -61,11 +66,14 @@ struct Split {
 #pragma unroll
     for (int u = 0; u < 3; ++u) {
 #pragma unroll
-      for (int e = 0; e < 4; ++e)
-        part[u][e] = __builtin_amdgcn_perm(__float_as_uint(x[2 * e + 1]), __float_as_uint(x[2 * e]), 0x07060302u);
-      if (u < 2) {
-#pragma unroll
-        for (int e = 0; e < 8; ++e) x[e] -= __uint_as_float(__float_as_uint(x[e]) & 0xffff0000u);
+      for (int e = 0; e < 4; ++e) {
+        if (u == 2) {
+          part[u][e] = __builtin_amdgcn_perm(__float_as_uint(x[2 * e + 1]), __float_as_uint(x[2 * e]), 0x07060302u);
+          continue;
+        }
+        part[u][e] = __builtin_bit_cast(uint32_t, __builtin_convertvector(f32x2{x[2 * e], x[2 * e + 1]}, bf16x2));
+        x[2 * e] -= __uint_as_float(part[u][e] << 16);
+        x[2 * e + 1] -= __uint_as_float(part[u][e] & 0xffff0000u);
       }
     }
   }

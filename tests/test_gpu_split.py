@@ -79,8 +79,8 @@ def test_forward_and_gradients(case, gain, phi, rope):
             assert rel_l2(x, ref) <= 5e-5 and max_abs(x, ref) <= 1e-4 * max(np.abs(ref).max(), 1e-2), (name, h, rel_l2(x, ref))
 
 
-# four, two and one group; two and one; fp32 products, 32 rows a workgroup
-BAD = [(66, 128), (150, 128), (390, 128), (66, 64), (390, 64), (30, 128), (30, 64)]
+# three query blocks of 64 rows a head: four, two and one group; two and one; fp32 products
+BAD = [(66, 128), (150, 128), (300, 128), (66, 64), (390, 64), (30, 128), (30, 64)]
 
 
 def _bad_case(heads, d):
@@ -120,6 +120,46 @@ def test_values_without_a_finite_remainder(heads, d):
     assert (O[:, :, :64, 40] < -1e30).all() and (O[:, :, 128:, 40] < -1e30).all()
     K[:, :, n_kv - 1, 0] = INF                 # a score of +infinity: no softmax
     assert _attend(cfg, Q, K, V, idx)[:, :, :64].isnan().all()
+
+
+def _low_bits(n, seed):
+    """n values in [1, 1.25) whose parts behind the first eight bits are as large as they get: the upper bits random, then ones."""
+    g = torch.Generator().manual_seed(seed)
+    return (1.0 + torch.randint(0, 32, (n,), generator=g) / 128.0 + (2.0 ** 16 - 1) / 2.0 ** 23).float()
+
+
+@pytest.mark.parametrize("heads,d", BAD)
+def test_products_are_as_exact_as_one_rounding(heads, d):
+    """A product of the window's two contractions or the history term is off by no more than 2^-24 of itself, half a unit of
+    fp32's last place (what is left out of cut-off parts is up to 2^-21).  Single products, so that nothing averages out."""
+    n_q, n_kv = 130, 64
+    scale = np.float32(16.0 / np.float32(1.4426950408889634))
+    assert scale * np.float32(1.4426950408889634) == 16.0   # (the queries' low bits are not touched)
+    cfg = hf.make_config(1, heads, d, "f32", 64, 64, 1.0, softmax_scale=float(scale))
+    x = [_low_bits(heads * m, 40 + i).view(1, heads, m) for i, m in enumerate((n_q, 1, d, d))]
+    Q, K, V = (torch.zeros((1, heads, m, d)) for m in (n_q, n_kv, n_kv))
+    # scores: key 0 has one of zero, key 1 one product of about -17, the others none (2^-1000)
+    Q[..., 0], K[:, :, 1, 0], K[:, :, 2:, 0], V[:, :, 1] = x[0], -x[1][..., 0], -60.0, 1.0
+    got = wl.to_f64(_attend(cfg, Q.to(DEV), K.to(DEV), V.to(DEV), None))[0]
+    s = 16.0 * wl.to_f64(x[0])[0] * wl.to_f64(x[1])[0]
+    p = 2.0 ** -s
+    # the score: left out 2^-24 of it, rounded 2^-20 (its last place is 2^-19); then the exponential, 1 + p, 1 / l and the product
+    bound = np.log(2) * (s.max() * 2.0 ** -24 + 2.0 ** -20) + 5 * 2.0 ** -24
+    assert np.abs(got / (p / (1 + p))[..., None] - 1).max() <= bound
+    # values: one key of any weight w next to one without a value; O = w x, w from a feature whose value is one
+    V[:, :, 1] = x[2]
+    V[:, :, 1, 5] = 1.0
+    K[:, :, 1, 0] = -x[1][..., 0] / 64.0
+    got = wl.to_f64(_attend(cfg, Q.to(DEV), K.to(DEV), V.to(DEV), None))[0]
+    want = got[..., 5:6] * wl.to_f64(V)[0, :, 1:2]
+    assert np.abs(got / want - 1).max() <= 5 * 2.0 ** -24   # left out, rounded to fp32, scaled by 1 / l here and there
+    # history: no value in the window, a state of one row, denominator one: O is the product
+    st = torch.zeros(hf.hf_state_bytes(cfg) // 4)
+    st[:heads * d * d].view(heads, d, d)[:, 0] = x[3][0]
+    cfg.eps = 1.0
+    got = wl.to_f64(_attend(cfg, Q.to(DEV), K.to(DEV), torch.zeros_like(V).to(DEV), None, st.to(DEV)))[0]
+    want = wl.to_f64(x[0])[0][..., None] * wl.to_f64(x[3])[0][:, None]
+    assert np.abs(got / want - 1).max() <= 2.01 * 2.0 ** -24
 
 
 @pytest.mark.parametrize("bad", [NAN, INF])
