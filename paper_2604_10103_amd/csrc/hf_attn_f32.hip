@@ -1,5 +1,5 @@
-// Block-sparse window attention (Eq. 5) with the history term (Eq. 3, 6) for fp32 storage on the bf16 matrix instruction:
-// block_q a multiple of 64, block_kv of 32.
+// Block-sparse window attention (Eq. 5) for fp32 storage on the bf16 matrix instruction, and the history term (Eq. 3, 6): block_q
+// a multiple of 64, block_kv of 32.
 //
 // An fp32 value is the sum of three bf16 values, x = hi + mid + lo, each the rest so far rounded to nearest: |mid| <= 2^-8 and
 // |lo| <= 2^-17 of x's leading bit, the remainders exact.  A product of two of them is six bf16 products, each exact, summed in
@@ -25,6 +25,8 @@
 // 832x480 in fp32 (12 heads of 128, 4680 x 9360, k = 37 of 147 blocks of 64; selection included): 613 us on the fp32 instruction,
 // 468 here.  Splitting next to the matrix instructions instead of behind them, transposing reads for V, and remainders by dot
 // products with (-1, 0) instead of subtractions (they run on the matrix pipe) gained nothing.
+#include <type_traits>
+
 #include "hf_f32_mfma.h"
 
 namespace hf {
@@ -519,80 +521,83 @@ __global__ __launch_bounds__(64 * RG * KG, (SplitShape<D, KG>::WAVES)) void attn
 
   if (hist.L) {
     // ---- O += R(phi(q)) L / (z_scale phi(q).z + eps) (Eq. 3, 6): O_local is scaled by the denominator, the products add the
-    // numerator (L's key features in the place of keys, R(phi(q)) in that of the exponentials), one division at the end
-    const float* L = hist.L + (size_t)bh * D * D;
+    // numerator (L's key features in the place of keys, R(phi(q)) in that of the exponentials), one division at the end.  On the
+    // fp32 instruction: an infinite entry of the state has no finite remainder, and of a head's products these are D / (k block_kv).
+    // A lane takes features 8 i + 4 h .. + 4 of its query and the rows of L that go with them, a piece ahead of their products.
+    const float* L = hist.L + (size_t)bh * D * D + (size_t)4 * h * D + f0 + l32;
     const float* z = hist.z + (size_t)bh * D + 4 * h;
     const float* qp = static_cast<const float*>(hist.q_hist) + q_at + 4 * h;
     const size_t trow = (size_t)min(row, n_q - 1) * (D / 2) + 2 * h;
-    load_v(L, 32 * grp, 32);
-    // (everything this lane takes of its query in one round trip: features 8 i + 4 h .. + 4)
-    f32x4 ph[D / 8];
-#pragma unroll
-    for (int i = 0; i < D / 8; ++i) ph[i] = *reinterpret_cast<const f32x4*>(qp + 8 * i);
-    if (hist.phi_kind == HF_PHI_RELU) {   // uniform
-#pragma unroll
-      for (int i = 0; i < D / 8; ++i)
-#pragma unroll
-        for (int e = 0; e < 4; ++e) ph[i][e] = phi_apply(ph[i][e], HF_PHI_RELU);
-    } else {
-#pragma unroll
-      for (int i = 0; i < D / 8; ++i)
-#pragma unroll
-        for (int e = 0; e < 4; ++e) ph[i][e] = phi_apply(ph[i][e], HF_PHI_ELU1);
-    }
     float den = 0.0f;
+    auto readout = [&](auto relu, auto rotated) {
+      auto feature_map = [&](f32x4 x) {
 #pragma unroll
-    for (int i = 0; i < D / 8; ++i) {
-      const f32x4 zz = *reinterpret_cast<const f32x4*>(z + 8 * i);
+        for (int e = 0; e < 4; ++e) x[e] = phi_apply(x[e], relu.value ? HF_PHI_RELU : HF_PHI_ELU1);
+        return x;
+      };
+#pragma unroll 1
+      for (int i0 = 0; i0 < D / 8; i0 += 4) {
+        f32x4 x[4], zz[4];
 #pragma unroll
-      for (int e = 0; e < 4; ++e) den = fmaf(ph[i][e], zz[e], den);
-    }
-    if (hist.cosq) {
-#pragma unroll
-      for (int i = 0; i < D / 8; ++i) {
-        const f32x2 cs = *reinterpret_cast<const f32x2*>(hist.cosq + trow + 4 * i), sn = *reinterpret_cast<const f32x2*>(hist.sinq + trow + 4 * i);
-        ph[i] = rotate4(ph[i], cs[0], sn[0], cs[1], sn[1]);
-      }
-    }
-    den = hist.z_scale * both_halves_sum(den) + hist.eps;
-    w *= den;
-#pragma unroll
-    for (int i = 0; i < ND; ++i)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) o[i][r] *= w;
-#pragma unroll
-    for (int it0 = 0; it0 < DT; it0 += KG) {   // a group brings 32 key features, everybody multiplies all of them
-      split_tile();
-      write_v();
-      if (it0 + KG < DT) load_v(L, 32 * (it0 + KG + grp), 32);
-      __syncthreads();
-#pragma unroll
-      for (int u = 0; u < KG; ++u) {
-        const char* planes = smem + Sh::QL + u * Sh::GBUF + (Sh::TWO ? 3 * PLANE : 0) + 2048 * ND * grp;
-        Split x[2];
-#pragma unroll
-        for (int t2 = 0; t2 < 2; ++t2) {
-#pragma unroll
-          for (int e = 0; e < 8; ++e) x[t2].x[e] = ph[4 * (it0 + u) + 2 * t2 + (e >> 2)][e & 3];
-          x[t2].all();
+        for (int i = 0; i < 4; ++i) {
+          x[i] = *reinterpret_cast<const f32x4*>(qp + 8 * (i0 + i));
+          zz[i] = *reinterpret_cast<const f32x4*>(z + 8 * (i0 + i));
         }
 #pragma unroll
-        for (int i = 0; i < ND; ++i) {
-          f32x16 part;
+        for (int i = 0; i < 4; ++i) {
+          x[i] = feature_map(x[i]);
 #pragma unroll
-          for (int r = 0; r < 16; ++r) part[r] = 0.0f;
+          for (int e = 0; e < 4; ++e) den = fmaf(x[i][e], zz[i][e], den);
+        }
+      }
+      den = hist.z_scale * both_halves_sum(den) + hist.eps;
+      w *= den;
 #pragma unroll
-          for (int t2 = 0; t2 < 2; ++t2) {
-            bf16x8 a[3];
+      for (int i = 0; i < ND; ++i)
 #pragma unroll
-            for (int e = 0; e < 3; ++e) a[e] = v_frag(planes + e * PLANE, i, t2);
+        for (int r = 0; r < 16; ++r) o[i][r] *= w;
+      constexpr int NB = ND < 2 ? ND : 2;   // value blocks at a time: what four of them need does not fit the registers
 #pragma unroll
-            for (int e = 0; e < 6; ++e) part = mfma_bf16(a[prod_a(e)], x[t2][prod_b(e)], part);
+      for (int j0 = 0; j0 < ND; j0 += NB) {
+        f32x4 x[2];
+        f32x2 cs[2], sn[2];
+        float a[2][4][NB];
+        auto request = [&](int i, int u) {
+          x[u] = *reinterpret_cast<const f32x4*>(qp + 8 * i);
+          if constexpr (rotated.value) {
+            cs[u] = *reinterpret_cast<const f32x2*>(hist.cosq + trow + 4 * i);
+            sn[u] = *reinterpret_cast<const f32x2*>(hist.sinq + trow + 4 * i);
           }
-          o[i] += part;
+#pragma unroll
+          for (int e = 0; e < 4; ++e)
+#pragma unroll
+            for (int j = 0; j < NB; ++j) a[u][e][j] = L[(size_t)(8 * i + e) * D + 32 * (j0 + j)];
+        };
+        request(0, 0);
+#pragma unroll 1
+        for (int i = 0; i < D / 8; i += 4) {   // 32 key features, summed for themselves
+          f32x16 part[NB];
+#pragma unroll
+          for (int j = 0; j < NB; ++j) part[j] = {};
+#pragma unroll
+          for (int u = 0; u < 4; ++u) {
+            if (i + u + 1 < D / 8) request(i + u + 1, (u + 1) & 1);
+            f32x4 ph = feature_map(x[u & 1]);
+            if constexpr (rotated.value) ph = rotate4(ph, cs[u & 1][0], sn[u & 1][0], cs[u & 1][1], sn[u & 1][1]);
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+#pragma unroll
+              for (int j = 0; j < NB; ++j) part[j] = mfma_f32_wide(a[u & 1][e][j], ph[e], part[j]);
+          }
+#pragma unroll
+          for (int j = 0; j < NB; ++j) o[j0 + j] += part[j];
         }
       }
-      __syncthreads();
+    };
+    if (hist.phi_kind == HF_PHI_RELU) {   // uniform
+      if (hist.cosq) readout(std::true_type{}, std::true_type{}); else readout(std::true_type{}, std::false_type{});
+    } else {
+      if (hist.cosq) readout(std::false_type{}, std::true_type{}); else readout(std::false_type{}, std::false_type{});
     }
     w = 1.0f / den;
   }

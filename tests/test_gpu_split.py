@@ -122,6 +122,24 @@ def test_values_without_a_finite_remainder(heads, d):
     assert _attend(cfg, Q, K, V, idx)[:, :, :64].isnan().all()
 
 
+@pytest.mark.parametrize("heads,d", BAD)
+def test_infinities_of_the_state(heads, d):
+    """An infinite entry of the state (of an infinite value that was absorbed) is one of its feature's outputs, two of either
+    sign make NaN there; the other features keep their bits.  phi = ELU + 1, which is positive."""
+    cfg, Q, K, V, idx = _bad_case(heads, d)
+    cfg.phi = hf.HF_PHI_ELU1
+    st = torch.empty(hf.hf_state_bytes(cfg) // 4, dtype=torch.float32, device=DEV)
+    hf.hf_state_init(cfg, st)
+    hf.hf_absorb_evicted(cfg, st, K, V)
+    want = _attend(cfg, Q, K, V, idx, st)
+    L = st[:heads * d * d].view(1, heads, d, d)
+    L[:, :, 5, 3], L[:, :, 9, 40], L[:, :, 5, d - 1], L[:, :, d - 2, d - 1] = INF, -INF, INF, -INF
+    O = _attend(cfg, Q, K, V, idx, st)
+    same = [f for f in range(d) if f not in (3, 40, d - 1)]
+    assert want.isfinite().all() and torch.equal(O[..., same], want[..., same])
+    assert (O[..., 3] == INF).all() and (O[..., 40] == -INF).all() and O[..., d - 1].isnan().all()
+
+
 def _low_bits(n, seed):
     """n values in [1, 1.25) whose parts behind the first eight bits are as large as they get: the upper bits random, then ones."""
     g = torch.Generator().manual_seed(seed)
