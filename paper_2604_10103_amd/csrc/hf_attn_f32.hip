@@ -123,7 +123,7 @@ __global__ __launch_bounds__(64 * RG * KG, (SplitShape<D, KG>::WAVES)) void attn
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wr = wave % RG, grp = wave / RG;
-  const int l32 = lane & 31, h = lane >> 5;
+  int l32 = lane & 31, h = lane >> 5;
   char* const sK = smem + Sh::QL + grp * Sh::GBUF;
   char* const sV = sK + (Sh::TWO ? 3 * PLANE : 0);
   const float* Kh = K + (size_t)bh * kv_stride * D;     // heads of a cache buffer are kv_stride tokens apart
@@ -132,8 +132,9 @@ __global__ __launch_bounds__(64 * RG * KG, (SplitShape<D, KG>::WAVES)) void attn
   const int nsel = idx ? k : t_n;
   const int subs = bkv / TK;
   const int ntiles = (nsel * subs + KG - 1) / KG;       // every group the same number: the barriers are the workgroup's
-  const int row = row0 + 32 * wr + l32;                 // rows past the block's end: clamped addresses, never written
-  const size_t q_at = ((size_t)bh * n_q + min(row, n_q - 1)) * D;
+  // rows past the block's end: clamped addresses, never written
+  auto query_row = [&]() { return row0 + 32 * wr + l32; };
+  auto query_at = [&]() { return ((size_t)bh * n_q + min(query_row(), n_q - 1)) * D; };
 
   // tiles of the group's part of the list, 64 at a time, lane l holding tile t0 + l: first key | real keys << 24; none past the
   // end, for empty parts of short blocks and for indices out of range (rows that do not exist read as zeros)
@@ -230,7 +231,7 @@ __global__ __launch_bounds__(64 * RG * KG, (SplitShape<D, KG>::WAVES)) void attn
   bf16x8 qf[S][2];
 #pragma unroll
   for (int s = 0; s < S; ++s) {
-    const float* qp = Q + q_at + 16 * s + 8 * h;
+    const float* qp = Q + query_at() + 16 * s + 8 * h;
     const f32x4 a = *reinterpret_cast<const f32x4*>(qp) * scale_log2e, b = *reinterpret_cast<const f32x4*>(qp + 4) * scale_log2e;
     Split sp;
 #pragma unroll
@@ -370,6 +371,13 @@ __global__ __launch_bounds__(64 * RG * KG, (SplitShape<D, KG>::WAVES)) void attn
     __builtin_amdgcn_sched_barrier(0);
   }
   __syncthreads();
+  // (the lane's place opaque from here on: what is formed of it is not kept over the loop)
+  int place = lane;
+  asm volatile("" : "+v"(place));
+  l32 = place & 31;
+  h = place >> 5;
+  const int row = query_row();
+  const size_t q_at = query_at();
   float l_tot = both_halves_sum(l);
 
   if (KG > 1) {
@@ -436,7 +444,10 @@ __global__ __launch_bounds__(64 * RG * KG, (SplitShape<D, KG>::WAVES)) void attn
   const int f0 = 32 * ND * grp;   // o[i], i < ND, holds features f0 + 32 i .. + 32 from here on
 
   // ---- what is not finite: an infinity has no finite remainder (inf - inf), and the small terms of the split multiply it by
-  // zero.  Such a row is done again, key by key in plain fp32.  (rolled, and never reached on finite inputs)
+  // zero.  A wavefront with such a row does its rows again on the fp32 instruction, operands straight from memory (K and Q pieces
+  // of a row, V a key's 32 features), and takes the rows that need it.  Finite inputs up to bf16's largest value never get here; one
+  // infinite value or NaN that every query block selects: 832x480 470 -> 1350 us (620 with fp32
+  // products throughout; key after key took 13400).
   {
     float bad = l_tot < INFINITY ? 0.0f : 1.0f;
 #pragma unroll
@@ -450,36 +461,66 @@ __global__ __launch_bounds__(64 * RG * KG, (SplitShape<D, KG>::WAVES)) void attn
       for (int i = 0; i < ND; ++i) again[i] = {};
       float m2 = -INFINITY, l2 = 0.0f;
       const float* qp = Q + q_at + 4 * h;
+      const int k2_at = (l32 * D + 4 * h) * 4, v2_at = (4 * h * D + f0 + l32) * 4;
 #pragma unroll 1
-      for (int sel = 0; sel < nsel; ++sel) {
-        const int jb = __builtin_amdgcn_readfirstlane(row_idx ? row_idx[sel] : sel);
+      for (int t = 0; t < nsel * subs; ++t) {
+        const int sel = t / subs, jb = __builtin_amdgcn_readfirstlane(row_idx ? row_idx[sel] : sel);
         if ((unsigned)jb >= (unsigned)t_n) continue;
-        const int end = min(n_kv, (jb + 1) * bkv);
+        const int first = jb * bkv + TK * (t - sel * subs), cnt = min(TK, n_kv - first);
+        if (cnt <= 0) continue;
+        const __amdgpu_buffer_rsrc_t kr = tile_rows<float, D>(Kh, first, cnt), vr = tile_rows<float, D>(Vh, first, cnt);
+        f32x16 sc = {};
 #pragma unroll 1
-        for (int key = jb * bkv; key < end; ++key) {
-          float dot = 0.0f;
-#pragma unroll 1
-          for (int f = 0; f < D; f += 8) {
-            const f32x4 x = *reinterpret_cast<const f32x4*>(qp + f) * scale_log2e;
-            const f32x4 y = *reinterpret_cast<const f32x4*>(Kh + (size_t)key * D + 4 * h + f);
+        for (int i0 = 0; i0 < D / 8; i0 += 4) {
+          f32x4 x[4], y[4];
 #pragma unroll
-            for (int e = 0; e < 4; ++e) dot = fmaf(x[e], y[e], dot);
+          for (int i = 0; i < 4; ++i) {
+            y[i] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(kr, k2_at + 32 * (i0 + i), 0, 0));
+            x[i] = *reinterpret_cast<const f32x4*>(qp + 8 * (i0 + i)) * scale_log2e;
           }
-          dot = both_halves_sum(dot);
-          const float m_new = fmaxf(m2, dot), ref = m_new == -INFINITY ? 0.0f : m_new;
-          const float alpha = __builtin_amdgcn_exp2f(m2 - ref), p = __builtin_amdgcn_exp2f(dot - ref);
+#pragma unroll
+          for (int i = 0; i < 4; ++i)
+#pragma unroll
+            for (int e = 0; e < 4; ++e) sc = mfma_f32_wide(y[i][e], x[i][e], sc);
+        }
+#pragma unroll
+        for (int r = 0; r < 16; ++r) sc[r] = 8 * (r >> 2) + (r & 3) < cnt - 4 * h ? sc[r] : -INFINITY;
+        float mx = sc[0];
+#pragma unroll
+        for (int r = 1; r < 16; ++r) mx = fmaxf(mx, sc[r]);
+        const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(mx), __float_as_uint(mx), false, false);
+        mx = fmaxf(__uint_as_float(sw[0]), __uint_as_float(sw[1]));
+        if (__any(mx > m2 + kGrow)) {
+          const float m_new = fmaxf(m2, mx);
+          const float alpha = __builtin_amdgcn_exp2f(m2 - (m_new == -INFINITY ? 0.0f : m_new));
           m2 = m_new;
-          l2 = fmaf(l2, alpha, p);
+          l2 *= alpha;
 #pragma unroll
           for (int i = 0; i < ND; ++i)
 #pragma unroll
-            for (int rq = 0; rq < 4; ++rq) {
-              const f32x4 v = *reinterpret_cast<const f32x4*>(Vh + (size_t)key * D + f0 + 32 * i + 8 * rq + 4 * h);
+            for (int r = 0; r < 16; ++r) again[i][r] *= alpha;
+        }
+        const float ref = m2 == -INFINITY ? 0.0f : m2;
 #pragma unroll
-              for (int e = 0; e < 4; ++e) again[i][4 * rq + e] = fmaf(p, v[e], again[i][4 * rq + e] * alpha);
-            }
+        for (int r = 0; r < 16; ++r) {
+          sc[r] = __builtin_amdgcn_exp2f(sc[r] - ref);
+          l2 += sc[r];   // this lane's keys only; summed at the end
+        }
+#pragma unroll
+        for (int rq = 0; rq < 4; ++rq) {
+          float v[4][ND];
+#pragma unroll
+          for (int e = 0; e < 4; ++e)
+#pragma unroll
+            for (int i = 0; i < ND; ++i)
+              v[e][i] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(vr, v2_at + ((8 * rq + e) * D + 32 * i) * 4, 0, 0));
+#pragma unroll
+          for (int e = 0; e < 4; ++e)
+#pragma unroll
+            for (int i = 0; i < ND; ++i) again[i] = mfma_f32_wide(v[e][i], sc[4 * rq + e], again[i]);
         }
       }
+      l2 = both_halves_sum(l2);
       if (bad > 0.0f) {
         m = m2;
         l_tot = l2;
