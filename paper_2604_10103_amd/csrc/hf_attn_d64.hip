@@ -20,6 +20,8 @@
 // issue (an exponential 8 cycles, three-operand and conversion instructions 4, plain additions and products 2).
 // 832x480 with 24 heads of 64 (4680 x 9360, k = 37 of 147 blocks of 64; selection included): 0.66 ms with both products on the
 // fp32 matrix instruction, 0.172 ms with this kernel; of those, 12 us are the tiles' transfers, 18 us the selection.
+#include <type_traits>
+
 #include "hf_f32_mfma.h"
 
 namespace hf {
@@ -72,7 +74,7 @@ __global__ __launch_bounds__(128 * KS, 4) void attn_d64_kernel(
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wr = wave & 1, grp = wave >> 1;
-  const int l32 = lane & 31, h = lane >> 5;
+  int l32 = lane & 31, h = lane >> 5;
   char* const sK = smem + grp * GB;
   char* const sV = sK + 3 * TILE;
   const int32_t* row_idx = idx ? idx + ((size_t)bh * t_m + qb) * k : nullptr;
@@ -82,11 +84,11 @@ __global__ __launch_bounds__(128 * KS, 4) void attn_d64_kernel(
 
   // this lane's query row as B-operand fragments (features 16 s + 8 h .. + 8); rows past the block's end read clamped
   // addresses and are never stored
-  const int q_row = row0 + 32 * wr + l32;
-  const size_t q_at = (size_t)bh * n_q + min(q_row, n_q - 1);
+  auto query_row = [&]() { return row0 + 32 * wr + l32; };
+  auto query_at = [&]() { return (size_t)bh * n_q + min(query_row(), n_q - 1); };
   bf16x8 qf[4];
 #pragma unroll
-  for (int s = 0; s < 4; ++s) qf[s] = *reinterpret_cast<const bf16x8*>(Q + q_at * D + 16 * s + 8 * h);
+  for (int s = 0; s < 4; ++s) qf[s] = *reinterpret_cast<const bf16x8*>(Q + query_at() * D + 16 * s + 8 * h);
 
   f32x16 o[2];
 #pragma unroll
@@ -277,11 +279,18 @@ __global__ __launch_bounds__(128 * KS, 4) void attn_d64_kernel(
   }
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // nothing may land in LDS after the tiles' space is reused
   __syncthreads();
+  // (the lane's place opaque from here on: what is formed of it is not kept, or spilled, over the loop)
+  int place = lane;
+  asm volatile("" : "+v"(place));
+  l32 = place & 31;
+  h = place >> 5;
+  const int q_row = query_row();
+  const size_t q_at = query_at();
   float l_tot = both_halves_sum(l_run);
 
   // ---- the groups' parts of a row meet: [wavefront][feature block][quad][lane] in each group's tile space, then the row
   // statistics; each group finishes one 32-feature block
-  f32x4* part = reinterpret_cast<f32x4*>(sK) + wr * 512 + lane;
+  f32x4* part = reinterpret_cast<f32x4*>(sK) + wr * 512 + place;
 #pragma unroll
   for (int dt = 0; dt < 2; ++dt)
 #pragma unroll
@@ -309,7 +318,7 @@ __global__ __launch_bounds__(128 * KS, 4) void attn_d64_kernel(
   for (int u = 0; u < KS; ++u) {
     const float w = __builtin_amdgcn_exp2f(mu[u] - m_use);
     l_tot = fmaf(lu[u], w, l_tot);
-    const f32x4* q = reinterpret_cast<const f32x4*>(smem + u * GB) + wr * 512 + 4 * grp * 64 + lane;
+    const f32x4* q = reinterpret_cast<const f32x4*>(smem + u * GB) + wr * 512 + 4 * grp * 64 + place;
 #pragma unroll
     for (int rq = 0; rq < 4; ++rq) {
       const f32x4 x = q[rq * 64];
@@ -324,10 +333,7 @@ __global__ __launch_bounds__(128 * KS, 4) void attn_d64_kernel(
   for (int r = 0; r < 16; ++r) bad |= !(fabsf(os[r]) < INFINITY);
   if (__any(bad && l_tot < INFINITY)) {
     f32x16 again = {};
-    int at_lane = lane;
-    asm volatile("" : "+v"(at_lane));   // (opaque: addresses of its own, or those of the prologue stay in registers through the loop)
-    const int half = at_lane >> 5;
-    const bf16_t* qp = Q + ((size_t)bh * n_q + min(row0 + 32 * wr + (at_lane & 31), n_q - 1)) * D + 8 * half;
+    const bf16_t* qp = Q + q_at * D + 8 * h;
 #pragma unroll 1
     for (int sel = 0; sel < nsel; ++sel) {
       const int jb = __builtin_amdgcn_readfirstlane(row_idx ? row_idx[sel] : sel);
@@ -340,14 +346,14 @@ __global__ __launch_bounds__(128 * KS, 4) void attn_d64_kernel(
 #pragma unroll 1
         for (int s = 0; s < 8; ++s) {   // features 16 (s / 2) + 8 h + 4 (s % 2) .. + 4
           const int f = 16 * (s >> 1) + 4 * (s & 1);
-          const f32x4 x = load4<bf16_t>(qp + f), y = load4<bf16_t>(K + at + 8 * half + f);
+          const f32x4 x = load4<bf16_t>(qp + f), y = load4<bf16_t>(K + at + 8 * h + f);
 #pragma unroll
           for (int e = 0; e < 4; ++e) dot = fmaf(x[e], y[e], dot);
         }
         const float p = __builtin_amdgcn_exp2f(fmaf(both_halves_sum(dot), c_scale, -m_use));
 #pragma unroll
         for (int rq = 0; rq < 4; ++rq) {
-          const f32x4 v = load4<bf16_t>(V + at + 32 * grp + 8 * rq + 4 * half);
+          const f32x4 v = load4<bf16_t>(V + at + 32 * grp + 8 * rq + 4 * h);
 #pragma unroll
           for (int e = 0; e < 4; ++e) again[4 * rq + e] = fmaf(p, v[e], again[4 * rq + e]);
         }
@@ -361,61 +367,65 @@ __global__ __launch_bounds__(128 * KS, 4) void attn_d64_kernel(
     // ---- O += R(phi(q)) L / (z_scale phi(q).z + eps) (Eq. 3, 6) on the fp32 matrix instruction, whose results lie as those
     // of the bf16 one: O_local is scaled by the denominator, the products add the numerator, one division at the end
     const size_t trow = (size_t)min(q_row, n_q - 1) * (D / 2);
-    // the lane's features 16 (i / 2) + 8 h + 4 (i % 2) .. + 4, i < 8, in one round trip; L's rows of half of them at a time
-    int half = h;
-    asm volatile("" : "+v"(half));   // (opaque: addresses of its own, or those of the prologue stay in registers through the loop)
-    const float* L = hist.L + (size_t)bh * D * D + 32 * grp + l32;
-    const float* z = hist.z + (size_t)bh * D + 8 * half;
-    const bf16_t* qp = static_cast<const bf16_t*>(hist.q_hist) + q_at * D + 8 * half;
-    f32x4 x[8];
+    // the lane's features 16 s + 8 h .. + 8, s < 4, in one round trip and in their storage type, L's rows of half of them at a
+    // time (as floats, or with an address per row of L, they do not fit the registers: fifteen went to scratch, which cost launches
+    // without a state too, 10 heads x 640 rows x 128 keys 6.48 -> 6.13 us)
+    const float* z = hist.z + (size_t)bh * D + 8 * h;
+    const bf16_t* qp = static_cast<const bf16_t*>(hist.q_hist) + q_at * D + 8 * h;
+    bf16x8 qh[4];
 #pragma unroll
-    for (int i = 0; i < 8; ++i) x[i] = load4<bf16_t>(qp + 16 * (i >> 1) + 4 * (i & 1));
-    f32x4 a[4];
-    auto rows_of = [&](int i0) {
+    for (int s = 0; s < 4; ++s) qh[s] = *reinterpret_cast<const bf16x8*>(qp + 16 * s);
+    const __amdgpu_buffer_rsrc_t L = tile_rows<float, D>(hist.L + (size_t)bh * D * D, 0, D);
+    const int l_at = (8 * h * D + 32 * grp + l32) * 4;
+    float a[16];
+    auto rows_of = [&](int s0) {
 #pragma unroll
-      for (int i = 0; i < 4; ++i)
-#pragma unroll
-        for (int e = 0; e < 4; ++e) a[i][e] = L[(16 * ((i0 + i) >> 1) + 8 * half + 4 * (i & 1) + e) * D];
+      for (int i = 0; i < 16; ++i)
+        a[i] = __builtin_bit_cast(float, __builtin_amdgcn_raw_buffer_load_b32(L, l_at, (16 * (s0 + (i >> 3)) + (i & 7)) * D * 4, 0));
     };
     rows_of(0);
-    if (hist.phi_kind == HF_PHI_RELU) {   // uniform
-#pragma unroll
-      for (int i = 0; i < 8; ++i)
-#pragma unroll
-        for (int e = 0; e < 4; ++e) x[i][e] = phi_apply(x[i][e], HF_PHI_RELU);
-    } else {
-#pragma unroll
-      for (int i = 0; i < 8; ++i)
-#pragma unroll
-        for (int e = 0; e < 4; ++e) x[i][e] = phi_apply(x[i][e], HF_PHI_ELU1);
-    }
     float den = 0.0f;
+    auto readout = [&](auto relu) {
+      auto piece = [&](int s, int e0) {
+        f32x4 x;
 #pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      const f32x4 zz = *reinterpret_cast<const f32x4*>(z + 16 * (i >> 1) + 4 * (i & 1));
-#pragma unroll
-      for (int e = 0; e < 4; ++e) den = fmaf(x[i][e], zz[e], den);
-    }
-    if (hist.cosq) {
+        for (int e = 0; e < 4; ++e) x[e] = phi_apply(static_cast<float>(qh[s][e0 + e]), relu.value ? HF_PHI_RELU : HF_PHI_ELU1);
+        return x;
+      };
 #pragma unroll
       for (int i = 0; i < 8; ++i) {
-        const size_t at = trow + 4 * half + 8 * (i >> 1) + 2 * (i & 1);
-        const f32x2 cs = *reinterpret_cast<const f32x2*>(hist.cosq + at), sn = *reinterpret_cast<const f32x2*>(hist.sinq + at);
-        x[i] = rotate4(x[i], cs[0], sn[0], cs[1], sn[1]);
+        const f32x4 zz = *reinterpret_cast<const f32x4*>(z + 16 * (i >> 1) + 4 * (i & 1)), x = piece(i >> 1, 4 * (i & 1));
+#pragma unroll
+        for (int e = 0; e < 4; ++e) den = fmaf(x[e], zz[e], den);
       }
-    }
-    den = hist.z_scale * both_halves_sum(den) + hist.eps;
-    w *= den;
+      den = hist.z_scale * both_halves_sum(den) + hist.eps;
+      w *= den;
 #pragma unroll
-    for (int r = 0; r < 16; ++r) os[r] *= w;
+      for (int r = 0; r < 16; ++r) os[r] *= w;
 #pragma unroll
-    for (int i0 = 0; i0 < 8; i0 += 4) {
-      if (i0) rows_of(i0);
+      for (int s = 0; s < 4; ++s) asm volatile("" : "+v"(qh[s]));   // (opaque: what the denominator made of them is not kept)
 #pragma unroll
-      for (int i = 0; i < 4; ++i)
+      for (int s0 = 0; s0 < 4; s0 += 2) {
+        f32x2 cs[4], sn[4];
+        if (hist.cosq) {
 #pragma unroll
-        for (int e = 0; e < 4; ++e) os = mfma_f32_wide(a[i][e], x[i0 + i][e], os);
-    }
+          for (int i = 0; i < 4; ++i) {
+            const size_t at = trow + 4 * h + 8 * (s0 + (i >> 1)) + 2 * (i & 1);
+            cs[i] = *reinterpret_cast<const f32x2*>(hist.cosq + at);
+            sn[i] = *reinterpret_cast<const f32x2*>(hist.sinq + at);
+          }
+        }
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          f32x4 x = piece(s0 + (i >> 1), 4 * (i & 1));
+          if (hist.cosq) x = rotate4(x, cs[i][0], sn[i][0], cs[i][1], sn[i][1]);
+#pragma unroll
+          for (int e = 0; e < 4; ++e) os = mfma_f32_wide(a[4 * i + e], x[e], os);
+        }
+        if (s0 == 0) rows_of(2);
+      }
+    };
+    if (hist.phi_kind == HF_PHI_RELU) readout(std::true_type{}); else readout(std::false_type{});   // uniform
     w = 1.0f / den;
   }
   // ---- rows through LDS, stored coalesced
@@ -425,7 +435,7 @@ __global__ __launch_bounds__(128 * KS, 4) void attn_d64_kernel(
     store4<bf16_t>(reinterpret_cast<bf16_t*>(smem + (32 * wr + l32) * OSTR) + 32 * grp + 8 * rq + 4 * h,
                    f32x4{os[4 * rq], os[4 * rq + 1], os[4 * rq + 2], os[4 * rq + 3]} * w);
   __syncthreads();
-  for (int e = tid; e < 64 * 8; e += 128 * KS) {
+  for (int e = 64 * wave + place; e < 64 * 8; e += 128 * KS) {
     const int row = e >> 3, u = e & 7;
     if (row0 + row < q_end)
       *reinterpret_cast<uint4*>(O + ((size_t)bh * n_q + row0 + row) * D + 8 * u) =

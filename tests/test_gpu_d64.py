@@ -1,0 +1,110 @@
+"""bf16 at head_dim 64 in launches beyond the small ones (more than 64 blocks of 64 rows), where one kernel splits the probabilities
+in three: query blocks of one to three workgroups, KV blocks of one to three tiles, ragged ends, lists that the two groups of
+wavefronts do not share evenly, heads further apart than the window is long; the history term; infinities among the values."""
+import numpy as np
+import pytest
+import torch
+
+import oracle as orc
+import paper_2604_10103_amd as hf
+import workloads as wl
+from parity import BF16_MAX_ABS, BF16_REL_L2, max_abs, oracle_state, rel_l2
+
+pytestmark = pytest.mark.gpu
+
+DEV = "cuda:0"
+NAN, INF = float("nan"), float("inf")
+
+
+def _tensors(heads, n, seed):
+    """Three heads repeated: what the oracle has to follow."""
+    return [wl.randn((1, 3, m, 64), 73_000 + seed + i, 0.5, torch.bfloat16).repeat(1, -(-heads // 3), 1, 1)[:, :heads].contiguous()
+            for i, m in enumerate(n)]
+
+
+def _window(t, cap):
+    """The tokens of t in a buffer whose heads are cap tokens apart; nothing behind them is to be read."""
+    buf = torch.full((1, t.shape[1], cap, 64), NAN, dtype=t.dtype)
+    buf[:, :, :t.shape[2]] = t
+    return buf.to(DEV)
+
+
+def _attend(cfg, Q, K, V, idx, st, n_kv, tab=(None, None)):
+    O = torch.full_like(Q, 7.0)
+    ws = torch.empty(max(hf.hf_workspace_bytes(cfg, Q.shape[2], n_kv), 256), dtype=torch.uint8, device=DEV)
+    hf.hf_hybrid_attn_fwd(cfg, Q, K, V, idx, st, O, ws, *tab, n_kv=n_kv if cfg.kv_capacity else None)
+    torch.cuda.synchronize()
+    return O
+
+
+def _state(cfg, Ke, Ve):
+    st = torch.empty(hf.hf_state_bytes(cfg) // 4, dtype=torch.float32, device=DEV)
+    hf.hf_state_init(cfg, st)
+    hf.hf_absorb_evicted(cfg, st, Ke.to(DEV), Ve.to(DEV))
+    return st
+
+
+# heads, block_q, block_kv, n_q, n_kv, keep (None: dense), tokens between heads (0: n_kv)
+SHAPES = [
+    (33, 64, 64, 65, 127, 1.0, 0), (33, 64, 32, 129, 33, 1.0, 0), (24, 128, 32, 257, 300, 0.3, 0), (23, 192, 96, 193, 450, 0.5, 0),
+    (65, 64, 96, 1, 96 * 3 + 1, 0.5, 0), (30, 128, 64, 130, 500, None, 0), (66, 64, 64, 64, 200, 0.6, 301), (22, 192, 32, 200, 257, 0.4, 320),
+    (12, 64, 64, 400, 4300, None, 0),
+]
+
+
+@pytest.mark.parametrize("case", SHAPES, ids=lambda c: "-".join(map(str, c)))
+@pytest.mark.parametrize("phi", [hf.HF_PHI_RELU, hf.HF_PHI_ELU1])
+@pytest.mark.parametrize("rope", [False, True])
+def test_forward(case, phi, rope):
+    heads, bq, bkv, n_q, n_kv, keep, cap = case
+    assert heads * (n_q // bq * (bq // 64) + -(-(n_q % bq) // 64)) > 64
+    cfg = hf.make_config(1, heads, 64, "bf16", bq, bkv, 1.0 if keep is None else keep, phi=phi, kv_capacity=cap)
+    Q, K, V, Ke, Ve = _tensors(heads, (n_q, n_kv, n_kv, 50, 50), 0)
+    Q = Q * 4.0
+    tab = wl.rope_tables(n_q, 64, first_position=9.0) if rope else (None, None)
+    q, k, v = Q.to(DEV), _window(K, cap or n_kv), _window(V, cap or n_kv)
+    st = _state(hf.make_config(1, heads, 64, "bf16", bq, bkv, 1.0, phi=phi), Ke, Ve)
+    t_m, t_n, kk = -(-n_q // bq), -(-n_kv // bkv), hf.hf_select_k(cfg, n_kv)
+    idx = torch.empty((1, heads, t_m, kk), dtype=torch.int32, device=DEV)
+    ws = torch.empty(hf.hf_workspace_bytes(cfg, n_q, n_kv), dtype=torch.uint8, device=DEV)
+    hf.hf_block_select(cfg, q, k, idx, None, ws, n_kv=n_kv if cap else None)
+    use = None if keep is None else idx
+    O = _attend(cfg, q, k, v, use, st, n_kv, tuple(None if t is None else t.to(DEV) for t in tab))
+    O0 = _attend(cfg, q, k, v, use, None, n_kv)
+    states = oracle_state([Ke[:, :3]], [Ve[:, :3]], 64, phi)
+    lists = idx.cpu().numpy() if keep is not None else np.tile(np.arange(t_n), (1, heads, t_m, 1))
+    tabs = tuple(None if t is None else wl.to_f64(t) for t in tab)
+    for h in (0, 1, heads - 1):
+        a = [wl.to_f64(t[0, h]) for t in (Q, K, V)]
+        for got, state in ((O, states[h % 3]), (O0, None)):
+            ref, *_ = orc.hybrid_attention(*a, state, bq, bkv, lists.shape[-1], phi, *tabs, cfg.eps, cfg.z_scale, block_idx=lists[0, h])
+            x = wl.to_f64(got[0, h])
+            assert rel_l2(x, ref) <= BF16_REL_L2 and max_abs(x, ref) <= BF16_MAX_ABS * max(1.0, np.abs(ref).max()), (h, rel_l2(x, ref))
+
+
+@pytest.mark.parametrize("heads,bq,bkv,n_kv,cap,with_state", [
+    (33, 64, 32, 300, 0, True), (33, 64, 32, 300, 0, False), (24, 128, 96, 96 * 3 + 10, 400, True), (24, 192, 64, 64 * 4 + 10, 300, False),
+])
+def test_infinities(heads, bq, bkv, n_kv, cap, with_state):
+    """Probabilities are split into terms of which some are zero or negative: no NaN comes of an infinite value.  Features 3 and
+    40 (one of either group of wavefronts); the other features and the rows of other blocks keep their bits, and what no row
+    selects is not read."""
+    n_q = 2 * bq + 5
+    cfg = hf.make_config(1, heads, 64, "bf16", bq, bkv, 0.5, kv_capacity=cap)
+    Q, K, V, Ke, Ve = _tensors(heads, (n_q, n_kv, n_kv, 50, 50), 20)
+    Q, K, V = Q.to(DEV), _window(K, cap or n_kv), _window(V, cap or n_kv)
+    st = _state(hf.make_config(1, heads, 64, "bf16", bq, bkv, 0.5), Ke, Ve) if with_state else None
+    last = (n_kv - 1) // bkv
+    idx = torch.tensor([[1, last], [2, last], [1, 2]], dtype=torch.int32, device=DEV).expand(1, heads, 3, 2).contiguous()
+    want = _attend(cfg, Q, K, V, idx, st, n_kv)
+    V[:, :, n_kv - 1, 3] = INF
+    V[:, :, n_kv - 1, 40] = -INF
+    V[:, 1, 2 * bkv, 40] = INF        # block 2, head 1: rows of query block 1 meet both signs
+    K[:, :, :bkv], V[:, :, :bkv] = NAN, INF   # block 0: selected by nobody
+    O = _attend(cfg, Q, K, V, idx, st, n_kv)
+    same = [f for f in range(64) if f not in (3, 40)]
+    others = [h for h in range(heads) if h != 1]
+    assert want.isfinite().all() and torch.equal(O[..., same], want[..., same])
+    assert torch.equal(O[:, others, 2 * bq:], want[:, others, 2 * bq:]) and (O[:, 1, 2 * bq:, 40] == INF).all()
+    assert (O[:, :, :2 * bq, 3] == INF).all() and (O[:, others, :2 * bq, 40] == -INF).all()
+    assert (O[:, 1, :bq, 40] == -INF).all() and O[:, 1, bq:2 * bq, 40].isnan().all()
