@@ -680,8 +680,7 @@ int launch_split(const hf_config& c, const void* Q, int n_q, const void* K, cons
 // workgroup of their own, which fills the chip with half as many rows and splits a list over four wavefronts with less around
 // the loop: 114 workgroups of 64 rows (6 heads x 1170 rows, k = 10 of 37) 35 us there and 48 here, 152 of them 57 and 45.
 bool attn_split_supported(const hf_config& c, int n_q, int n_kv) {
-  const long long wgs = (long long)c.batch * c.heads * ((n_q + c.block_q - 1) / c.block_q) * (c.block_q / 64);
-  return c.dtype == HF_F32 && c.block_q % 64 == 0 && c.block_kv % TK == 0 && n_kv < (1 << 23) && wgs > 128;
+  return c.dtype == HF_F32 && c.block_q % 64 == 0 && c.block_kv % TK == 0 && n_kv < (1 << 23) && row_groups(c, n_q, 64) > 128;
 }
 
 // Groups per workgroup: four while that is one round of the chip (a compute unit has room for eight wavefronts at head_dim 128);
@@ -691,7 +690,7 @@ bool attn_split_supported(const hf_config& c, int n_q, int n_kv) {
 // head_dim 64 (one / two): 228 46 / 29, 592 212 / 188, 840 173 / 177, 1480 215 / 236, 5640 291 / 342.
 int launch_attn_split(const hf_config& c, const void* Q, int n_q, const void* K, const void* V, int n_kv, const int32_t* idx,
                       int k, void* O, const WideHist& hist, hipStream_t s) {
-  const long long wgs = (long long)c.batch * c.heads * ((n_q + c.block_q - 1) / c.block_q) * (c.block_q / 64);
+  const long long wgs = row_groups(c, n_q, 64);
   if (c.head_dim == 64) {
     if (wgs <= 768) return launch_split<64, 2>(c, Q, n_q, K, V, n_kv, idx, k, O, hist, s);
     return launch_split<64, 1>(c, Q, n_q, K, V, n_kv, idx, k, O, hist, s);

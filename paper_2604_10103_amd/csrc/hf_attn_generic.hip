@@ -715,11 +715,10 @@ template <typename T, int D>
 int launch_wide_rows(const hf_config& c, const void* Q, int n_q, const void* K, const void* V, int n_kv,
                      const int32_t* idx, int k, void* O, const WideHist& hist, hipStream_t s) {
   int rows = 128;
-  const long long blocks = (long long)c.batch * c.heads * ((n_q + c.block_q - 1) / c.block_q);
   while (rows > 16) {
     const int chunks = (c.block_q + rows - 1) / rows;
     const bool waste = chunks * rows * 8 > c.block_q * 9;       // more than an eighth of the rows do not exist
-    const bool idle = blocks * chunks < 512;                     // fewer workgroups than two per compute unit
+    const bool idle = row_groups(c, n_q, rows) < 512;           // fewer workgroups than two per compute unit
     if (!waste && !idle) break;
     rows >>= 1;
   }
@@ -740,19 +739,18 @@ int launch_attn_split(const hf_config& c, const void* Q, int n_q, const void* K,
 
 static int launch_attn_wide(const hf_config& c, const void* Q, int n_q, const void* K, const void* V, int n_kv,
                             const int32_t* idx, int k, void* O, const WideHist& hist, hipStream_t s) {
-  const long long blocks = (long long)c.batch * c.heads * ((n_q + c.block_q - 1) / c.block_q);
   const long long keys = idx ? (long long)k * c.block_kv : n_kv;   // of a query row
   // bf16 at head_dim 64: launches of few rows and short lists are a chain of latencies, shorter with sixteen rows a workgroup and
   // the list split over its four wavefronts.  Those against these, us: 8 blocks of 64 rows x 192 keys 7.9 / 9.6, 56 x 320 10.0 /
   // 11.0; 44 x 640 15.2 / 14.2, 114 x 640 22.0 / 14.6.  (Row statistics for the backward pass come from the kernels of this file.)
-  const bool short_chain = blocks * (c.block_q / 64) <= 64 && keys <= 384;
+  const bool short_chain = row_groups(c, n_q, 64) <= 64 && keys <= 384;
   if (attn_d64_supported(c, n_kv) && !hist.lse2 && !short_chain) return launch_attn_d64(c, Q, n_q, K, V, n_kv, idx, k, O, hist, s);
   if (attn_split_supported(c, n_q, n_kv)) return launch_attn_split(c, Q, n_q, K, V, n_kv, idx, k, O, hist, s);
   // fp32: a compute unit takes two workgroups of sixteen rows in the time of one of 32 (of which it holds two as well, but a
   // second round of 256 is not shared), so sixteen rows win while there are fewer than compute units, and at the start of that
   // round.  Sixteen / 32 rows, us, head_dim 128: 14 workgroups of 32 rows 11.9 / 20.0, 88 23.8 / 32.5, 112 15.6 / 24.5 (320 keys),
   // 222 36.6 / 34.9, 296 50.2 / 57.2, 444 67.5 / 58.7; head_dim 64: 14 7.3 / 11.4, 222 20.8 / 19.5, 296 27.4 / 31.5, 444 34.0 / 31.4.
-  const long long wgs32 = blocks * (c.block_q / 32);
+  const long long wgs32 = row_groups(c, n_q, 32);
   if (c.dtype == HF_F32 && c.block_q % 32 == 0 && c.block_kv % 32 == 0 && wgs32 > 160 && (wgs32 <= 256 || wgs32 > 352))
     return c.head_dim == 128 ? launch_wide32<128>(c, Q, n_q, K, V, n_kv, idx, k, O, hist, s)
                              : launch_wide32<64>(c, Q, n_q, K, V, n_kv, idx, k, O, hist, s);

@@ -119,4 +119,10 @@ __device__ __forceinline__ f32x4 rotate4(f32x4 x, float c0, float s0, float c1, 
   return f32x4{x[0] * c0 - x[1] * s0, x[0] * s0 + x[1] * c0, x[2] * c1 - x[3] * s1, x[2] * s1 + x[3] * c1};
 }
 
+// workgroups of `rows` rows of a query block that have a row: what the launch rules count.  (A block longer than
+// n_q, or the end of the last one, has workgroups without any; they return at once.)
+inline long long row_groups(const hf_config& c, int n_q, int rows) {
+  return (long long)c.batch * c.heads * ((long long)(n_q / c.block_q) * ((c.block_q + rows - 1) / rows) + (n_q % c.block_q + rows - 1) / rows);
+}
+
 }  // namespace hf

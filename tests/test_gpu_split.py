@@ -221,3 +221,15 @@ def test_bf16_at_head_dim_64_beyond_small_launches(bq, bkv, n_kv, bad):
     same = [f for f in range(64) if f not in (3, 40)]
     assert want.isfinite().all() and torch.equal(O[..., same], want[..., same]) and torch.equal(O[:, :, 2 * bq:], want[:, :, 2 * bq:])
     assert (O[:, :, :2 * bq, 3] == INF).all() and (O[:, :, :2 * bq, 40] == -INF).all()
+
+
+@pytest.mark.parametrize("dtype,d,heads,n_q", [("f32", 128, 9, 64), ("f32", 64, 9, 64), ("f32", 128, 7, 33), ("bf16", 64, 5, 64)])
+def test_rows_that_do_not_exist_choose_no_kernel(dtype, d, heads, n_q):
+    """A query block far longer than the queries has the kernel, and so the bits, of a block they fill."""
+    td = torch.bfloat16 if dtype == "bf16" else torch.float32
+    Q, K, V, Ke = (wl.randn((1, heads, n, d), 72_000 + i, 0.5, td).to(DEV) for i, n in enumerate((n_q, 200, 200, 50)))
+    cfg, long = (hf.make_config(1, heads, d, dtype, bq, 64, 1.0) for bq in (64, 1024))
+    st = torch.empty(hf.hf_state_bytes(cfg) // 4, dtype=torch.float32, device=DEV)
+    hf.hf_state_init(cfg, st)
+    hf.hf_absorb_evicted(cfg, st, Ke, Ke)
+    assert torch.equal(_attend(cfg, Q, K, V, None, st), _attend(long, Q, K, V, None, st))
