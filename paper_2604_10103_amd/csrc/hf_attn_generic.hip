@@ -740,10 +740,11 @@ int launch_attn_split(const hf_config& c, const void* Q, int n_q, const void* K,
 static int launch_attn_wide(const hf_config& c, const void* Q, int n_q, const void* K, const void* V, int n_kv,
                             const int32_t* idx, int k, void* O, const WideHist& hist, hipStream_t s) {
   const long long keys = idx ? (long long)k * c.block_kv : n_kv;   // of a query row
-  // bf16 at head_dim 64: launches of few rows and short lists are a chain of latencies, shorter with sixteen rows a workgroup and
-  // the list split over its four wavefronts.  Those against these, us: 8 blocks of 64 rows x 192 keys 7.9 / 9.6, 56 x 320 10.0 /
-  // 11.0; 44 x 640 15.2 / 14.2, 114 x 640 22.0 / 14.6.  (Row statistics for the backward pass come from the kernels of this file.)
-  const bool short_chain = row_groups(c, n_q, 64) <= 64 && keys <= 384;
+  // bf16 at head_dim 64: the history term is a chain of loads and fp32 products behind the list, half as long with sixteen rows a
+  // workgroup; behind a short list, in launches of few rows, that is what counts.  (Row statistics for the backward pass come from
+  // the kernels of this file.)  Those against these, us, 2 to 64 blocks of 64 rows: with the term 64 keys 7.6..7.9 / 6.4..6.8, 128
+  // 8.2..8.5 / 7.3..7.7, 256 9.5..9.8 / 9.2..9.8, 384 10.6..11.0 / 11.2..11.9; without 64 5.3..5.5 / 5.4..5.7, 256 7.1..7.3 / 8.1..8.6.
+  const bool short_chain = hist.L && row_groups(c, n_q, 64) <= 64 && keys <= 256;
   if (attn_d64_supported(c, n_kv) && !hist.lse2 && !short_chain) return launch_attn_d64(c, Q, n_q, K, V, n_kv, idx, k, O, hist, s);
   if (attn_split_supported(c, n_q, n_kv)) return launch_attn_split(c, Q, n_q, K, V, n_kv, idx, k, O, hist, s);
   // fp32: a compute unit takes two workgroups of sixteen rows in the time of one of 32 (of which it holds two as well, but a
