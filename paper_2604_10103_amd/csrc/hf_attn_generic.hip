@@ -747,12 +747,18 @@ static int launch_attn_wide(const hf_config& c, const void* Q, int n_q, const vo
   const bool short_chain = hist.L && row_groups(c, n_q, 64) <= 64 && keys <= 256;
   if (attn_d64_supported(c, n_kv) && !hist.lse2 && !short_chain) return launch_attn_d64(c, Q, n_q, K, V, n_kv, idx, k, O, hist, s);
   if (attn_split_supported(c, n_q, n_kv)) return launch_attn_split(c, Q, n_q, K, V, n_kv, idx, k, O, hist, s);
-  // fp32: a compute unit takes two workgroups of sixteen rows in the time of one of 32 (of which it holds two as well, but a
-  // second round of 256 is not shared), so sixteen rows win while there are fewer than compute units, and at the start of that
-  // round.  Sixteen / 32 rows, us, head_dim 128: 14 workgroups of 32 rows 11.9 / 20.0, 88 23.8 / 32.5, 112 15.6 / 24.5 (320 keys),
-  // 222 36.6 / 34.9, 296 50.2 / 57.2, 444 67.5 / 58.7; head_dim 64: 14 7.3 / 11.4, 222 20.8 / 19.5, 296 27.4 / 31.5, 444 34.0 / 31.4.
+  // fp32: 32 rows a workgroup or sixteen, in rounds of 256 compute units.  Up to 128 workgroups of 32 rows those of sixteen are one
+  // round, up to 384 three (a second workgroup of 32 rows on a compute unit takes as long as two of sixteen more); between, they are
+  // two for one, and pay where a list is short, whose chain they halve.  Sixteen / 32 rows, us, head_dim 128, history term off:
+  // workgroups of 32 rows   14           120          132, 144     240          260          384          480
+  //   64 keys               6.9 / 11.4   7.4 / 12.0   10.3 / 12.0  10.9 / 12.5  13.4 / 18.6  14.4 / 19.4  21.0 / 19.8
+  //   192 keys              9.7 / 16.1   10.5 / 16.8  16.5 / 17.0  17.5 / 17.9  22.7 / 28.0  24.1 / 29.1  31.4 / 30.8
+  //   384 keys              14.3 / 20.4  15.5 / 21.6  24.4 / 21.9  25.9 / 23.1  35.1 / 39.2  37.0 / 40.5  46.9 / 42.1
+  //   1536 keys             42 / 55      50 / 61      70 / 61      74 / 66      101 / 111    107 / 115    142 / 123
+  // (with the term and at head_dim 64 alike: 384 keys 14.1 / 13.2 at 144, 20.0 / 21.5 at 260, 21.2 / 22.2 at 384, 26.4 / 23.0 at 480)
   const long long wgs32 = row_groups(c, n_q, 32);
-  if (c.dtype == HF_F32 && c.block_q % 32 == 0 && c.block_kv % 32 == 0 && wgs32 > 160 && (wgs32 <= 256 || wgs32 > 352))
+  const bool rows32 = wgs32 > 384 || (wgs32 > 128 && wgs32 <= 256 && keys > 192);
+  if (c.dtype == HF_F32 && c.block_q % 32 == 0 && c.block_kv % 32 == 0 && rows32)
     return c.head_dim == 128 ? launch_wide32<128>(c, Q, n_q, K, V, n_kv, idx, k, O, hist, s)
                              : launch_wide32<64>(c, Q, n_q, K, V, n_kv, idx, k, O, hist, s);
   if (c.dtype == HF_F32)

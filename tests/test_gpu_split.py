@@ -35,7 +35,7 @@ SHAPES = [
     (150, 128, 64, 32, 129, 33, 1.0), (300, 128, 64, 64, 70, 300, None), (390, 128, 64, 64, 100, 200, 0.5),
     (270, 128, 128, 64, 200, 130, 0.4), (66, 64, 64, 64, 65, 100, 1.0), (45, 64, 192, 32, 200, 300, 0.3),
     (390, 64, 64, 96, 100, 200, None), (270, 64, 64, 32, 193, 65, 0.4),
-    # (between the small launches and these: fp32 products, 32 rows a workgroup)
+    # (smaller launches: fp32 products)
     (90, 128, 64, 64, 33, 300, 0.4), (201, 128, 32, 32, 40, 100, 0.5), (90, 64, 64, 32, 40, 200, 0.5), (201, 64, 32, 64, 33, 150, None),
 ]
 
@@ -233,3 +233,33 @@ def test_rows_that_do_not_exist_choose_no_kernel(dtype, d, heads, n_q):
     hf.hf_state_init(cfg, st)
     hf.hf_absorb_evicted(cfg, st, Ke, Ke)
     assert torch.equal(_attend(cfg, Q, K, V, None, st), _attend(long, Q, K, V, None, st))
+
+
+# fp32 products with 32 rows a workgroup: 129 to 256 of them with lists of more than 192 keys, more than 384 of any; sixteen rows in
+# all others (heads, head_dim, block_q, block_kv, n_q, n_kv, keep)
+SHAPES_32 = [
+    (90, 128, 64, 64, 33, 300, None), (75, 128, 32, 32, 40, 300, 0.8), (126, 64, 64, 32, 40, 300, 0.8), (66, 64, 32, 64, 50, 257, None),
+    (195, 128, 32, 32, 33, 100, 0.5), (129, 64, 96, 64, 97, 200, 0.4), (150, 128, 32, 64, 40, 300, 0.5),
+]
+
+
+@pytest.mark.parametrize("case", SHAPES_32, ids=lambda c: "-".join(map(str, c)))
+@pytest.mark.parametrize("gain,phi,rope", [(1.0, hf.HF_PHI_RELU, False), (4.0, hf.HF_PHI_ELU1, True)])
+def test_fp32_products_at_either_number_of_rows(case, gain, phi, rope):
+    test_forward_and_gradients(case, gain, phi, rope)
+
+
+@pytest.mark.parametrize("d", [128, 64])
+@pytest.mark.parametrize("bad", [NAN, INF, LOWEST])
+def test_what_is_not_finite_in_32_rows_a_workgroup(d, bad):
+    """Block 0 is selected by nobody, the infinite value of the last key by query blocks 0 and 2."""
+    heads, b, n_kv = 30, 64, 64 * 4 + 10   # 150 workgroups of 32 rows, 202 keys and more a list
+    cfg = hf.make_config(1, heads, d, "f32", b, b, 0.8)
+    Q, K, V = (t.to(DEV) for t in _tensors(heads, (2 * b + 5, n_kv, n_kv), d, 30))
+    idx = torch.tensor([[1, 2, 3, 4], [1, 2, 3, 3], [1, 2, 3, 4]], dtype=torch.int32, device=DEV).expand(1, heads, 3, 4).contiguous()
+    want = _attend(cfg, Q, K, V, idx)
+    K[:, :, :64], V[:, :, :64], V[:, :, n_kv - 1, 3] = bad, bad, INF
+    O = _attend(cfg, Q, K, V, idx)
+    same = [f for f in range(d) if f != 3]
+    assert want.isfinite().all() and torch.equal(O[..., same], want[..., same]) and torch.equal(O[:, :, 64:128], want[:, :, 64:128])
+    assert (O[:, :, :64, 3] == INF).all() and (O[:, :, 128:, 3] == INF).all()
