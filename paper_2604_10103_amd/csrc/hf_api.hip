@@ -378,7 +378,7 @@ static int select_launches(const hf_config* cfg, const void* Q, int32_t n_q, con
                            float* kbar, hipStream_t s, int kv_end = -1) {
   const int t_m = cdiv(n_q, cfg->block_q), t_n = cdiv(n_kv, cfg->block_kv);
   if (kv_end < 0) kv_end = t_n;
-  if (pool_select_supported(*cfg, t_n, n_cached_kv_blocks, kv_end))
+  if (pool_select_supported(*cfg, t_m, t_n, n_cached_kv_blocks, kv_end))
     return launch_pool_select(*cfg, Q, n_q, t_m, K_win, n_kv, t_n, n_cached_kv_blocks, kv_end, k, qbar, kbar, block_idx,
                               scores_or_null, s);
   HF_TRY(launch_pool_both(*cfg, Q, n_q, t_m, K_win, n_kv, t_n, n_cached_kv_blocks, kv_end, qbar, kbar, s));

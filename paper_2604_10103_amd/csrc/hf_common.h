@@ -129,8 +129,8 @@ size_t absorb_workspace_bytes(const hf_config& c, int n);
 int launch_pool_both(const hf_config& c, const void* Q, int n_q, int t_m, const void* K, int n_kv, int t_n,
                      int kv_first, int kv_end, float* qbar, float* kbar_t, hipStream_t s, const float* state = nullptr,
                      void* planes = nullptr);
-// both in one launch, where a head has little to pool
-bool pool_select_supported(const hf_config& c, int t_n, int kv_first, int kv_end);
+// both in one launch, where a head has little to pool and the workgroups are few
+bool pool_select_supported(const hf_config& c, int t_m, int t_n, int kv_first, int kv_end);
 int launch_pool_select(const hf_config& c, const void* Q, int n_q, int t_m, const void* K, int n_kv, int t_n, int kv_first,
                        int kv_end, int k, float* qbar, float* kbar_t, int32_t* idx, float* scores, hipStream_t s);
 int launch_score_select(const hf_config& c, const float* qbar, const float* kbar_t, int t_m, int t_n,

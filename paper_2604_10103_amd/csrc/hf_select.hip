@@ -383,13 +383,21 @@ static size_t pool_select_lds(const hf_config& c, int t_n) {
   return (size_t)(kRows * c.head_dim + 9 * kRows * t_pad + c.head_dim * t_n) * sizeof(float);
 }
 // Every workgroup pools the head's blocks again, eight at a time, against a launch and a gap saved.  One launch / two launches,
-// us: fp32, head_dim 64: 4 blocks of 16 4.2 / 5.2, 16 of 16 5.2 / 5.6, 32 of 16 6.7 / 6.2, 10 of 64 5.2 / 6.2, 24 of 64 7.1 / 6.0;
-// head_dim 128: 4 of 64 5.2 / 6.5, 7 of 64 6.9 / 7.1, 10 of 64 7.3 / 6.9; bf16 (half the bytes a row, as many blocks):
-// 6 of 16 5.2 / 5.6, 16 of 16 6.5 / 6.0, 10 of 64 6.5 / 6.9, 24 of 64 8.8 / 7.0.
-bool pool_select_supported(const hf_config& c, int t_n, int kv_first, int kv_end) {
+// us, 2 to 12 heads, up to 100 workgroups: fp32, head_dim 64: 4 blocks of 16 4.2 / 5.2, 16 of 16 5.2 / 5.6, 32 of 16 6.7 / 6.2, 10 of
+// 64 5.2 / 6.2, 24 of 64 7.1 / 6.0; head_dim 128: 4 of 64 5.2 / 6.5, 7 of 64 6.9 / 7.1, 10 of 64 7.3 / 6.9; bf16 (half the bytes a
+// row, as many blocks): 6 of 16 5.2 / 5.6, 16 of 16 6.5 / 6.0, 10 of 64 6.5 / 6.9, 24 of 64 8.8 / 7.0.
+// A compute unit holds one of these workgroups in bf16 (its registers), two in fp32, but then they share it: 264 of 6 blocks of 16 in
+// bf16 8.3 / 6.6, 320 of 8 of 64 in fp32 10.5 / 6.9; up to five blocks in fp32, one for a wavefront, still pay there (384 of 2 of
+// 64 5.8 / 7.7, 640 10.0 / 9.7).  A head's keys go to the L2 of every XCD that has one of its workgroups, and with many heads
+// that, not the launch, is what counts: 196 KB a head, 12 heads x 20 workgroups (19 MB) 5.3 / 6.1, 20 x 10 (31 MB) 6.1 / 6.1, 40 x 6
+// (47 MB) 9.6 / 6.2; 128 KB, 40 x 5 (26 MB) 5.4 / 6.1, 120 x 2 (31 MB) 6.3 / 6.1.  Heads of one workgroup read nothing twice.
+bool pool_select_supported(const hf_config& c, int t_m, int t_n, int kv_first, int kv_end) {
   const int blocks = kv_end - kv_first, es = c.dtype == HF_BF16 ? 2 : 4;
-  return blocks <= (c.dtype == HF_BF16 ? 10 : 16) && (long long)blocks * c.block_kv * c.head_dim * es <= 220 * 1024 &&
-         pool_select_lds(c, t_n) <= 64 * 1024;
+  const long long heads = (long long)c.batch * c.heads, per_head = (t_m + kRows - 1) / kRows;
+  const long long bytes = (long long)blocks * c.block_kv * c.head_dim * es;
+  return blocks <= (c.dtype == HF_BF16 ? 10 : 16) && bytes <= 220 * 1024 && pool_select_lds(c, t_n) <= 64 * 1024 &&
+         heads * per_head <= (c.dtype == HF_F32 && blocks <= 5 ? 384 : 256) &&
+         (per_head == 1 || heads * (per_head < 8 ? per_head : 8) * bytes <= 27 * 1024 * 1024);
 }
 
 int launch_pool_select(const hf_config& c, const void* Q, int n_q, int t_m, const void* K, int n_kv, int t_n, int kv_first,

@@ -58,3 +58,35 @@ def test_ties_keep_the_lower_index():
     ws = torch.empty(hf.hf_workspace_bytes(cfg, 50, 224), dtype=torch.uint8, device=DEV)
     idx, _ = _select(cfg, Q.to(DEV), K.to(DEV), 0, ws, 5, 4, 14)
     assert np.array_equal(idx, np.broadcast_to(np.arange(5, dtype=np.int32), idx.shape))
+
+
+# either side of the limits on workgroups (three query blocks each) and on what they read together
+MANY = [  # heads, dtype, head_dim, block_kv, query blocks of 16, KV blocks, of which reused
+    (12, "bf16", 128, 16, 63, 6, 0), (12, "bf16", 128, 16, 64, 6, 0), (40, "f32", 128, 64, 9, 6, 0), (40, "f32", 128, 64, 12, 6, 0),
+    (48, "f32", 64, 64, 24, 7, 2), (48, "f32", 64, 64, 25, 7, 2), (255, "f32", 128, 64, 2, 6, 1), (258, "f32", 128, 64, 2, 6, 0),
+    (40, "bf16", 64, 128, 12, 10, 3), (40, "bf16", 64, 128, 15, 10, 0),
+]
+
+
+@pytest.mark.parametrize("case", MANY, ids=lambda c: "-".join(map(str, c)))
+def test_many_heads(case):
+    """Three heads repeated: the oracle's scores and lists, and the same bits in every repetition and next to kept means."""
+    H, dtype, d, bkv, t_m, t_n, cached = case
+    tdt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    cfg = hf.make_config(1, H, d, dtype, 16, bkv, 0.5)
+    n_q, n_kv = 16 * t_m - 3, bkv * t_n - 5
+    Q, K = (wl.randn((1, 3, n, d), 83_000 + i, 0.5, tdt) for i, n in enumerate((n_q, n_kv)))
+    q, kk = (t.repeat(1, -(-H // 3), 1, 1)[:, :H].contiguous().to(DEV) for t in (Q, K))
+    k = hf.hf_select_k(cfg, n_kv)
+    ws = torch.full((hf.hf_workspace_bytes(cfg, n_q, n_kv),), 255, dtype=torch.uint8, device=DEV)   # (NaN)
+    idx, scores = _select(cfg, q, kk, 0, ws, k, t_m, t_n)
+    for h, (a, b) in enumerate(zip(heads_of(Q), heads_of(K))):
+        A = orc.block_scores(a, b, 16, bkv)
+        assert np.abs(scores[0, h] - A).max() <= 1e-5 * max(1.0, np.abs(A).max())
+        check_block_idx(idx[0, h], A, k)
+    for h in range(H):
+        assert np.array_equal(idx[0, h], idx[0, h % 3]) and np.array_equal(scores[0, h], scores[0, h % 3])
+    if cached:
+        kk[:, :, :cached * bkv] = float("nan")   # the means of these are not formed again
+        again = _select(cfg, q, kk, cached, ws, k, t_m, t_n)
+        assert np.array_equal(again[0], idx) and np.array_equal(again[1], scores)
