@@ -310,3 +310,36 @@ def test_steps_that_pool_the_chunk_in_the_attention_launch(heads, block, n_chunk
         hf.hf_select_attn_fwd(packed, Q, K, V, pooled, st, planes, O2, idx2)
         torch.cuda.synchronize()
         assert torch.equal(idx, idx2) and torch.equal(O, O2), step
+
+
+@pytest.mark.parametrize("heads,block,n_chunk,n_sink,slots", [(2, 64, 64, 0, 2), (3, 64, 100, 10, 3), (40, 64, 65, 63, 2), (3, 128, 300, 0, 3),
+                                                              (2, 128, 129, 5, 7), (2, 64, 170, 0, 3)])
+@pytest.mark.parametrize("cache", ["ring", "stream"])
+def test_steps_without_a_state_pool_the_window_in_the_attention_launch(heads, block, n_chunk, n_sink, slots, cache):
+    """Without a state nothing is prepared on a chunk's first step: a window of at most eight blocks is pooled in the workgroups
+    that select, and later steps read the means which that launch kept, in a workspace that held NaN."""
+    cap = n_sink + slots * n_chunk
+    assert -(-cap // block) <= 8
+    cfg = hf.make_config(1, heads, 128, "bf16", block, block, 0.3, kv_capacity=cap)
+    packed = hf.make_config(1, heads, 128, "bf16", block, block, 0.3)   # (the cache is full: a window of its length)
+    mk = lambda n, s: wl.randn((1, heads, n, 128), 92_000 + s, 0.5, torch.bfloat16).to(DEV)
+    K, V, Q = mk(cap, 0), mk(cap, 1), mk(n_chunk, 2)
+    if cache == "ring":
+        ring = hf.make_ring(n_sink, n_chunk)
+        ring.n_filled, ring.cur_slot, ring.next_slot, ring.absorbed_ahead = slots, slots - 2, slots - 1, 0
+        first = n_sink + (slots - 2) * n_chunk
+        call = lambda step: hf.hf_ring_step(cfg, ring, Q, K, V, step, idx, None, O, ws)
+    else:
+        win, first = hf.hf_window(n_sink, cap), cap - n_chunk
+        call = lambda step: hf.hf_stream_step(cfg, win, Q, K, V, step, idx, None, O, ws)
+    ws = torch.full((hf.hf_workspace_bytes(cfg, n_chunk, cap),), 255, dtype=torch.uint8, device=DEV)
+    idx = torch.full((1, heads, -(-n_chunk // block), hf.hf_select_k(cfg, cap)), -1, dtype=torch.int32, device=DEV)
+    idx2, O, O2 = torch.full_like(idx, -1), torch.full_like(Q, 7.0), torch.full_like(Q, 7.0)
+    for step in (0, 1, 2):
+        K[:, :, first:first + n_chunk] = mk(n_chunk, 10 + step)
+        call(step)
+        pooled = torch.empty(hf.hf_pooled_keys_bytes(packed, cap), dtype=torch.uint8, device=DEV)
+        hf.hf_pool_keys(packed, K, pooled)
+        hf.hf_select_attn_fwd(packed, Q, K, V, pooled, None, None, O2, idx2)
+        torch.cuda.synchronize()
+        assert torch.equal(idx, idx2) and torch.equal(O, O2) and O.isfinite().all(), step
