@@ -5,7 +5,9 @@
 // |lo| <= 2^-17 of x's leading bit, the remainders exact.  A product of two of them is six bf16 products, each exact, summed in
 // fp32 by the matrix cores:
 //   x y = hi hi' + (hi mid' + mid hi') + (hi lo' + mid mid' + lo hi')
-// What is left out, mid lo' + lo mid' + lo lo', is at most 2^-24 of the product (one rounding to fp32) and of either sign.
+// What is left out, mid lo' + lo mid' + lo lo', is at most 2^-24 of the product (one rounding to fp32) and of either sign.  (Parts
+// below 2^-133 vanish: a score is off by 2^-134 of the other operand, which counts next to one above 2^100 alone; outputs so small
+// are formed again behind the loop.)
 // The bf16 instruction has sixteen times the rate of the fp32 one, so six products take 6/16 of its matrix time, and a sum is
 // rounded once per sixteen terms instead of once per two.  A tile's P V is summed for itself and added to the output once.
 // Against 64 bits, with both products on the fp32 instruction / here (32 to 4096 keys): Gaussian inputs of standard deviation 0.5
@@ -444,16 +446,21 @@ __global__ __launch_bounds__(64 * RG * KG, (SplitShape<D, KG>::WAVES)) void attn
   const int f0 = 32 * ND * grp;   // o[i], i < ND, holds features f0 + 32 i .. + 32 from here on
 
   // ---- what is not finite: an infinity has no finite remainder (inf - inf), and the small terms of the split multiply it by
-  // zero.  A wavefront with such a row does its rows again on the fp32 instruction, operands straight from memory (K and Q pieces
+  // zero.  And what is below 2^-106: the third part of such a value lies under bf16's smallest (2^-133; an output of 2^-120 was off by
+  // 3.5e-5 of itself).  A wavefront with such a row does its rows again on the fp32 instruction, operands straight from memory (K and Q pieces
   // of a row, V a key's 32 features), and takes the rows that need it.  Finite inputs up to bf16's largest value never get here; one
   // infinite value or NaN that every query block selects: 832x480 470 -> 1350 us (620 with fp32
   // products throughout; key after key took 13400).
   {
     float bad = l_tot < INFINITY ? 0.0f : 1.0f;
+    const float tiny = l_tot * 0x1p-106f;
 #pragma unroll
     for (int i = 0; i < ND; ++i)
 #pragma unroll
-      for (int r = 0; r < 16; ++r) bad = fabsf(o[i][r]) < INFINITY ? bad : 1.0f;
+      for (int r = 0; r < 16; ++r) {
+        const float a = fabsf(o[i][r]);
+        bad = a == 0.0f || (a >= tiny && a < INFINITY) ? bad : 1.0f;
+      }
     bad = both_halves_sum(bad);
     if (__any(bad > 0.0f)) {
       f32x16 again[ND];

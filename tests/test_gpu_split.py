@@ -263,3 +263,20 @@ def test_what_is_not_finite_in_32_rows_a_workgroup(d, bad):
     same = [f for f in range(d) if f != 3]
     assert want.isfinite().all() and torch.equal(O[..., same], want[..., same]) and torch.equal(O[:, :, 64:128], want[:, :, 64:128])
     assert (O[:, :, :64, 3] == INF).all() and (O[:, :, 128:, 3] == INF).all()
+
+
+@pytest.mark.parametrize("heads,d", BAD)
+def test_small_values_keep_their_bits(heads, d):
+    """Values around 2^-100 and below have parts under bf16's smallest.  Powers of two change no rounding above fp32's smallest
+    normal value, so that outputs are those of the values times 2^s, up to fp32 sums in two orders (6e-7 at most)."""
+    cfg, Q, K, V, idx = _bad_case(heads, d)
+    want = _attend(cfg, Q, K, V, idx).double()
+    for s in (90, 104, 110, 120):
+        got = _attend(cfg, Q, K, V * 2.0 ** -s, idx).double() * 2.0 ** s
+        assert ((got - want).norm() / want.norm()).item() <= 1e-6, s
+    W = V.clone()
+    W[..., 5] *= 2.0 ** -118                    # one feature of a row is enough
+    got = _attend(cfg, Q, K, W, idx).double()[..., 5] * 2.0 ** 118
+    assert ((got - want[..., 5]).norm() / want[..., 5].norm()).item() <= 1e-6
+    W[..., 5] = 0.0
+    assert (_attend(cfg, Q, K, W, idx)[..., 5] == 0).all()
