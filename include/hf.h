@@ -29,10 +29,16 @@
  *    infinity in a key or value reaches the rows that select its block and no others
  *    (bf16 at head_dim 128 with a block_kv that is no multiple of 32: also those that
  *    select the block before it).
- *  - bf16 launches that would leave compute units idle let two groups of wavefronts share a
- *    query block's list.  A head on its own and the same head among many may therefore
- *    differ by the order of fp32 sums (a last bf16 bit here and there); block lists and
- *    scores are the same bits, and so are calls of one size with or without an absorb.
+ *  - Launches of different sizes may take different kernels.  bf16 at head_dim 128: launches
+ *    that would leave compute units idle let two groups of wavefronts share a query block's
+ *    list.  bf16 at head_dim 64 and fp32: the rows of a workgroup and the groups that share
+ *    a list follow the number of query rows in the launch and the length of the lists (at
+ *    head_dim 64 also whether there is a state), and in fp32, with blocks that are multiples
+ *    of 64 queries and 32 keys, so does the instruction: products are formed in fp32, or as
+ *    six bf16 products of values split in three, off by 2^-24 of themselves at most.  A head
+ *    on its own and the same head among many may therefore differ by the rounding of fp32
+ *    products and sums (in bf16 a last bit here and there, in fp32 some 1e-6); block lists
+ *    and scores are the same bits, and so are calls of one size with or without an absorb.
  *  - Return value: HF_OK (0) or a negative HF_ERR_* code; on error nothing was enqueued
  *    and hf_last_error() describes the problem.  No C++ exception crosses this boundary.
  *

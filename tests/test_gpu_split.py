@@ -280,3 +280,27 @@ def test_small_values_keep_their_bits(heads, d):
     assert ((got - want[..., 5]).norm() / want[..., 5].norm()).item() <= 1e-6
     W[..., 5] = 0.0
     assert (_attend(cfg, Q, K, W, idx)[..., 5] == 0).all()
+
+
+@pytest.mark.parametrize("dtype,d", [("f32", 128), ("f32", 64), ("bf16", 64)])
+def test_a_head_alone_and_among_many(dtype, d):
+    """Launch sizes choose kernels: a head's lists and scores keep their bits, its output differs by rounding (of fp32 products and
+    sums; in bf16 of the stored value, whose last bit is 2^-8 of it)."""
+    td = torch.bfloat16 if dtype == "bf16" else torch.float32
+    Q, K, V, Ke = (wl.randn((1, 1, n, d), 74_000 + i, 0.5, td).to(DEV) for i, n in enumerate((130, 330, 330, 50)))
+    outs = []
+    for heads in (1, 30, 47, 80, 200, 300, 420):
+        cfg = hf.make_config(1, heads, d, dtype, 64, 64, 0.7)
+        q, k, v, e = (t.expand(1, heads, -1, -1).contiguous() for t in (Q, K, V, Ke))
+        st = torch.empty(hf.hf_state_bytes(cfg) // 4, dtype=torch.float32, device=DEV)
+        hf.hf_state_init(cfg, st)
+        hf.hf_absorb_evicted(cfg, st, e, e)
+        idx = torch.empty((1, heads, 3, hf.hf_select_k(cfg, 330)), dtype=torch.int32, device=DEV)
+        scores = torch.empty((1, heads, 3, 6), dtype=torch.float32, device=DEV)
+        hf.hf_block_select(cfg, q, k, idx, scores, torch.empty(hf.hf_workspace_bytes(cfg, 130, 330), dtype=torch.uint8, device=DEV))
+        O = _attend(cfg, q, k, v, idx, st)
+        assert (O == O[:, :1]).all() and (idx == idx[:, :1]).all() and (scores == scores[:, :1]).all()
+        outs.append((idx[:, 0].clone(), scores[:, 0].clone(), O[:, 0].double()))
+    for idx, scores, O in outs[1:]:
+        assert torch.equal(idx, outs[0][0]) and torch.equal(scores, outs[0][1])
+        assert ((O - outs[0][2]).norm() / O.norm()).item() <= (2e-6 if dtype == "f32" else 1e-3)
