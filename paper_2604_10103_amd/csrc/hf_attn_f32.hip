@@ -683,27 +683,35 @@ int launch_split(const hf_config& c, const void* Q, int n_q, const void* K, cons
 
 }  // namespace
 
-// The descriptors hold the first key in 24 bits.  Launches of few query rows stay with the kernel that gives every 32 rows a
-// workgroup of their own, which fills the chip with half as many rows and splits a list over four wavefronts with less around
-// the loop: 114 workgroups of 64 rows (6 heads x 1170 rows, k = 10 of 37) 35 us there and 48 here, 152 of them 57 and 45.
+// The descriptors hold the first key in 24 bits.  Launches of few query rows stay with the kernels in fp32 products, which fill
+// the chip with half or a quarter as many rows a workgroup: theirs / the best here, us, head_dim 128: 128 workgroups of 64 rows x 64
+// keys 10.2 / 12.3, x 384 21.5 / 27.2, x 1536 60 / 78; 132 x 64 12.8 / 12.3, x 384 32.2 / 27.0, x 1536 96 / 77.  (With the history term
+// 19.7 / 20.8 at 132 x 64, 24.2 / 21.2 at 200 x 64; head_dim 64 alike, 6.7 / 7.9 at 128 x 64, 8.2 / 7.8 at 132 x 64.)
 bool attn_split_supported(const hf_config& c, int n_q, int n_kv) {
   return c.dtype == HF_F32 && c.block_q % 64 == 0 && c.block_kv % TK == 0 && n_kv < (1 << 23) && row_groups(c, n_q, 64) > 128;
 }
 
-// Groups per workgroup: four while that is one round of the chip (a compute unit has room for eight wavefronts at head_dim 128);
-// two up to three quarters of a round of workgroups of one group, and at head_dim 128 where the second such round would be at
-// most 5/8 full; one elsewhere.  One / two / four groups, us: 228 workgroups 80 / 56 / 51, 384 156 / 107 / 129, 684 300 / 282 /
-// 306, 840 329 / 341, 888 427 / 439 / 500, 1088 466 / 419 / 481, 1480 512 / 448, 1760 298 / 293, 2048 377 / 393, 5640 651 / 717;
-// head_dim 64 (one / two): 228 46 / 29, 592 212 / 188, 840 173 / 177, 1480 215 / 236, 5640 291 / 342.
+// Groups per workgroup: as many as finish in the fewest rounds of the chip (a compute unit has room for eight wavefronts at head_dim
+// 128, twelve at 64), of equal ones the fewest where lists are short, whose parts take longer to meet than they save: a round of
+// four groups is 256 workgroups, one of two 512 (768), one of one 1024 (1536).  One / two / four groups, us, head_dim 128:
+//   workgroups   132               512               520               768              900          1030         1600         2048
+//    64 keys     15.5/12.3/16.4    21.2/18.6/31.6    23.3/27.3/45.5    25.2/28.2/47.0   26.4/32.3    37.3/40.6    47.4/53.4    54.2/59.9
+//   192          27.0/19.3/21.6    38.9/29.8/42.9    40.5/42.7/62.3    43.8/43.8/63.3   48.3/51.8    66.3/64.1    -            94  /98
+//   256          33.4/23.4/22.5    -                 50.1/52.3/63.6    54.2/53.3/65.3   -            82.8/78.8    106 /105     118 /121
+//   320          38.4/25.8/26.5    -                 59.4/60.8/80.0    63.9/61.5/81.3   -            -            -            -
+//   384          44.2/29.6/27.0    65.5/47.0/54.9    67.4/68.0/79.5    73.0/68.6/81.5   80.5/83.3    112 /104     147 /142     160 /162
+//   1536         149 /93  /77      227 /150 /160     231 /218 /231     248 /225 /237    276 /277     392 /347     523 /487     572 /561
+// head_dim 64 (one / two): 512 x 64 12.3 / 11.1, 520 x 64 13.3 / 15.6, x 256 28.9 / 29.0, x 384 38.5 / 37.7, x 1536 131 / 121, 780 x 1536
+// 143 / 147.  Above, one group is at most 7 % behind on long lists (1700 x 1536 531 / 495 at head_dim 128) and up to a quarter ahead on short ones.
 int launch_attn_split(const hf_config& c, const void* Q, int n_q, const void* K, const void* V, int n_kv, const int32_t* idx,
                       int k, void* O, const WideHist& hist, hipStream_t s) {
-  const long long wgs = row_groups(c, n_q, 64);
+  const long long wgs = row_groups(c, n_q, 64), keys = idx ? (long long)k * c.block_kv : n_kv;
   if (c.head_dim == 64) {
-    if (wgs <= 768) return launch_split<64, 2>(c, Q, n_q, K, V, n_kv, idx, k, O, hist, s);
+    if (wgs <= (keys > 256 ? 768 : 512)) return launch_split<64, 2>(c, Q, n_q, K, V, n_kv, idx, k, O, hist, s);
     return launch_split<64, 1>(c, Q, n_q, K, V, n_kv, idx, k, O, hist, s);
   }
-  if (wgs <= 256) return launch_split<128, 4>(c, Q, n_q, K, V, n_kv, idx, k, O, hist, s);
-  if (wgs <= 768 || (wgs > 1024 && wgs <= 1664)) return launch_split<128, 2>(c, Q, n_q, K, V, n_kv, idx, k, O, hist, s);
+  if (wgs <= 256 && keys > 320) return launch_split<128, 4>(c, Q, n_q, K, V, n_kv, idx, k, O, hist, s);
+  if (wgs <= (keys > 256 ? 768 : 512) || (wgs > 1024 && wgs <= 1664 && keys > 128)) return launch_split<128, 2>(c, Q, n_q, K, V, n_kv, idx, k, O, hist, s);
   return launch_split<128, 1>(c, Q, n_q, K, V, n_kv, idx, k, O, hist, s);
 }
 

@@ -29,12 +29,16 @@ def _attend(cfg, Q, K, V, idx, st=None, tab=(None, None)):
     return O
 
 
-# heads, head_dim, block_q, block_kv, n_q, n_kv, keep (None: dense); blocks of 64 rows: 129 .. 256, .. 768, more
+# heads, head_dim, block_q, block_kv, n_q, n_kv, keep (None: dense); the groups follow the blocks of 64 rows and the list's keys
 SHAPES = [
     (66, 128, 64, 64, 65, 100, 1.0), (45, 128, 128, 32, 130, 257, 0.5), (129, 128, 64, 96, 1, 96 * 3 + 1, 0.5),
     (150, 128, 64, 32, 129, 33, 1.0), (300, 128, 64, 64, 70, 300, None), (390, 128, 64, 64, 100, 200, 0.5),
     (270, 128, 128, 64, 200, 130, 0.4), (66, 64, 64, 64, 65, 100, 1.0), (45, 64, 192, 32, 200, 300, 0.3),
     (390, 64, 64, 96, 100, 200, None), (270, 64, 64, 32, 193, 65, 0.4),
+    # (129 to 256 blocks and more than 320 keys: four groups; up to 512 two; up to 768 by 256 keys; 1025 to 1664 by 128 keys)
+    (66, 128, 64, 64, 65, 400, 1.0), (45, 128, 128, 32, 130, 700, 0.5), (129, 128, 64, 96, 1, 96 * 8 + 1, 0.5), (66, 128, 64, 64, 65, 321, None),
+    (66, 128, 64, 64, 65, 320, None), (300, 128, 64, 64, 70, 200, 0.6), (270, 128, 128, 64, 200, 300, 0.6), (300, 64, 64, 64, 70, 200, 0.6),
+    (300, 64, 64, 64, 70, 300, None),
     # (smaller launches: fp32 products)
     (90, 128, 64, 64, 33, 300, 0.4), (201, 128, 32, 32, 40, 100, 0.5), (90, 64, 64, 32, 40, 200, 0.5), (201, 64, 32, 64, 33, 150, None),
 ]
@@ -79,32 +83,32 @@ def test_forward_and_gradients(case, gain, phi, rope):
             assert rel_l2(x, ref) <= 5e-5 and max_abs(x, ref) <= 1e-4 * max(np.abs(ref).max(), 1e-2), (name, h, rel_l2(x, ref))
 
 
-# three query blocks of 64 rows a head: four, two and one group; two and one; fp32 products
-BAD = [(66, 128), (150, 128), (300, 128), (66, 64), (390, 64), (30, 128), (30, 64)]
+# three query blocks of 64 rows a head, lists of two KV blocks: two, four, two and one group; two and one; fp32 products
+BAD = [(66, 128, 64), (66, 128, 192), (150, 128, 64), (300, 128, 64), (66, 64, 64), (390, 64, 64), (30, 128, 64), (30, 64, 64)]
 
 
-def _bad_case(heads, d):
-    b, n_kv = 64, 64 * 3 + 10
-    cfg = hf.make_config(1, heads, d, "f32", b, b, 0.5)
+def _bad_case(heads, d, bkv):
+    b, n_kv = 64, bkv * 3 + 10
+    cfg = hf.make_config(1, heads, d, "f32", b, bkv, 0.5)
     Q, K, V = (t.to(DEV) for t in _tensors(heads, (2 * b + 5, n_kv, n_kv), d, 20))
     idx = torch.tensor([[0, 3], [1, 2], [2, 3]], dtype=torch.int32, device=DEV).expand(1, heads, 3, 2).contiguous()
     return cfg, Q, K, V, idx
 
 
-@pytest.mark.parametrize("heads,d", BAD)
+@pytest.mark.parametrize("heads,d,bkv", BAD)
 @pytest.mark.parametrize("bad", [NAN, INF, LOWEST])
-def test_an_unselected_block_is_not_read(heads, d, bad):
-    cfg, Q, K, V, idx = _bad_case(heads, d)
+def test_an_unselected_block_is_not_read(heads, d, bkv, bad):
+    cfg, Q, K, V, idx = _bad_case(heads, d, bkv)
     want = _attend(cfg, Q, K, V, idx)
-    K[:, :, :64] = bad
-    V[:, :, :64] = bad
+    K[:, :, :bkv] = bad
+    V[:, :, :bkv] = bad
     assert want.isfinite().all() and torch.equal(_attend(cfg, Q, K, V, idx)[:, :, 64:], want[:, :, 64:])
 
 
-@pytest.mark.parametrize("heads,d", BAD)
-def test_values_without_a_finite_remainder(heads, d):
+@pytest.mark.parametrize("heads,d,bkv", BAD)
+def test_values_without_a_finite_remainder(heads, d, bkv):
     """A selected infinite value stays one; a key of an infinitely small score, or of the lowest finite one, has no weight."""
-    cfg, Q, K, V, idx = _bad_case(heads, d)
+    cfg, Q, K, V, idx = _bad_case(heads, d, bkv)
     Q[..., 0] = Q[..., 0].abs() + 0.1
     n_kv = K.shape[2]
     for value in (-INF, LOWEST):
@@ -122,11 +126,11 @@ def test_values_without_a_finite_remainder(heads, d):
     assert _attend(cfg, Q, K, V, idx)[:, :, :64].isnan().all()
 
 
-@pytest.mark.parametrize("heads,d", BAD)
-def test_infinities_of_the_state(heads, d):
+@pytest.mark.parametrize("heads,d,bkv", BAD)
+def test_infinities_of_the_state(heads, d, bkv):
     """An infinite entry of the state (of an infinite value that was absorbed) is one of its feature's outputs, two of either
     sign make NaN there; the other features keep their bits.  phi = ELU + 1, which is positive."""
-    cfg, Q, K, V, idx = _bad_case(heads, d)
+    cfg, Q, K, V, idx = _bad_case(heads, d, bkv)
     cfg.phi = hf.HF_PHI_ELU1
     st = torch.empty(hf.hf_state_bytes(cfg) // 4, dtype=torch.float32, device=DEV)
     hf.hf_state_init(cfg, st)
@@ -168,11 +172,11 @@ def _low_bits(n, seed):
     return (1.0 + torch.randint(0, 32, (n,), generator=g) / 128.0 + (2.0 ** 16 - 1) / 2.0 ** 23).float()
 
 
-@pytest.mark.parametrize("heads,d", BAD)
-def test_products_are_as_exact_as_one_rounding(heads, d):
+@pytest.mark.parametrize("heads,d,bkv", BAD)
+def test_products_are_as_exact_as_one_rounding(heads, d, bkv):
     """A product of the window's two contractions or the history term is off by no more than 2^-24 of itself, half a unit of
     fp32's last place (what is left out of cut-off parts is up to 2^-21).  Single products, so that nothing averages out."""
-    n_q, n_kv = 130, 64
+    n_q, n_kv = 130, 64 if bkv == 64 else 2 * bkv
     scale = np.float32(16.0 / np.float32(1.4426950408889634))
     assert scale * np.float32(1.4426950408889634) == 16.0   # (the queries' low bits are not touched)
     cfg = hf.make_config(1, heads, d, "f32", 64, 64, 1.0, softmax_scale=float(scale))
@@ -265,11 +269,11 @@ def test_what_is_not_finite_in_32_rows_a_workgroup(d, bad):
     assert (O[:, :, :64, 3] == INF).all() and (O[:, :, 128:, 3] == INF).all()
 
 
-@pytest.mark.parametrize("heads,d", BAD)
-def test_small_values_keep_their_bits(heads, d):
+@pytest.mark.parametrize("heads,d,bkv", BAD)
+def test_small_values_keep_their_bits(heads, d, bkv):
     """Values around 2^-100 and below have parts under bf16's smallest.  Powers of two change no rounding above fp32's smallest
     normal value, so that outputs are those of the values times 2^s, up to fp32 sums in two orders (6e-7 at most)."""
-    cfg, Q, K, V, idx = _bad_case(heads, d)
+    cfg, Q, K, V, idx = _bad_case(heads, d, bkv)
     want = _attend(cfg, Q, K, V, idx).double()
     for s in (90, 104, 110, 120):
         got = _attend(cfg, Q, K, V * 2.0 ** -s, idx).double() * 2.0 ** s
