@@ -108,3 +108,24 @@ def test_infinities(heads, bq, bkv, n_kv, cap, with_state):
     assert torch.equal(O[:, others, 2 * bq:], want[:, others, 2 * bq:]) and (O[:, 1, 2 * bq:, 40] == INF).all()
     assert (O[:, :, :2 * bq, 3] == INF).all() and (O[:, others, :2 * bq, 40] == -INF).all()
     assert (O[:, 1, :bq, 40] == -INF).all() and O[:, 1, bq:2 * bq, 40].isnan().all()
+
+
+def test_a_nan_does_not_make_a_call_serial():
+    """What is not finite is summed again in tiles of 32 keys: 3.6 times the time of a call without (key after key it was 67 times).
+    The bound leaves a factor of two and a half."""
+    cfg = hf.make_config(1, 12, 64, "bf16", 64, 64, 1.0)
+    Q, K, V = (t.to(DEV) for t in _tensors(12, (1560, 4096, 4096), 40))
+    O = torch.empty_like(Q)
+
+    def us():
+        t = [torch.cuda.Event(enable_timing=True) for _ in range(5)]
+        hf.hf_hybrid_attn_fwd(cfg, Q, K, V, None, None, O)
+        for e in t:
+            e.record()
+            hf.hf_hybrid_attn_fwd(cfg, Q, K, V, None, None, O)
+        torch.cuda.synchronize()
+        return min(a.elapsed_time(b) for a, b in zip(t, t[1:]))
+
+    clean = us()
+    V[:, :, 77, 5] = NAN
+    assert us() <= 9 * clean
