@@ -572,11 +572,15 @@ __global__ __launch_bounds__(64 * RG * KG, (SplitShape<D, KG>::WAVES)) void attn
     // numerator (L's key features in the place of keys, R(phi(q)) in that of the exponentials), one division at the end.  On the
     // fp32 instruction: an infinite entry of the state has no finite remainder, and of a head's products these are D / (k block_kv).
     // A lane takes features 8 i + 4 h .. + 4 of its query and the rows of L that go with them, a piece ahead of their products.
+    // The normaliser is summed in four parts, the products in parts of 16 features: against 64 bits the term alone is off by 7.6e-8 of
+    // itself at head_dim 128 and 8.0e-8 at 64, on the fp32 kernels before 9.1e-8 and 8.5e-8 (in one chain and parts of 32 features
+    // 9.3e-8 and 9.2e-8).
     const float* L = hist.L + (size_t)bh * D * D + (size_t)4 * h * D + f0 + l32;
     const float* z = hist.z + (size_t)bh * D + 4 * h;
     const float* qp = static_cast<const float*>(hist.q_hist) + q_at + 4 * h;
     const size_t trow = (size_t)min(row, n_q - 1) * (D / 2) + 2 * h;
-    float den = 0.0f;
+    float den;
+    f32x4 dens = {};
     auto readout = [&](auto relu, auto rotated) {
       auto feature_map = [&](f32x4 x) {
 #pragma unroll
@@ -595,10 +599,10 @@ __global__ __launch_bounds__(64 * RG * KG, (SplitShape<D, KG>::WAVES)) void attn
         for (int i = 0; i < 4; ++i) {
           x[i] = feature_map(x[i]);
 #pragma unroll
-          for (int e = 0; e < 4; ++e) den = fmaf(x[i][e], zz[i][e], den);
+          for (int e = 0; e < 4; ++e) dens[e] = fmaf(x[i][e], zz[i][e], dens[e]);
         }
       }
-      den = hist.z_scale * both_halves_sum(den) + hist.eps;
+      den = hist.z_scale * both_halves_sum((dens[0] + dens[1]) + (dens[2] + dens[3])) + hist.eps;
       w *= den;
 #pragma unroll
       for (int i = 0; i < ND; ++i)
@@ -623,19 +627,19 @@ __global__ __launch_bounds__(64 * RG * KG, (SplitShape<D, KG>::WAVES)) void attn
         };
         request(0, 0);
 #pragma unroll 1
-        for (int i = 0; i < D / 8; i += 4) {   // 32 key features, summed for themselves
+        for (int i = 0; i < D / 8; i += 2) {   // 16 key features, summed for themselves
           f32x16 part[NB];
 #pragma unroll
           for (int j = 0; j < NB; ++j) part[j] = {};
 #pragma unroll
-          for (int u = 0; u < 4; ++u) {
-            if (i + u + 1 < D / 8) request(i + u + 1, (u + 1) & 1);
-            f32x4 ph = feature_map(x[u & 1]);
-            if constexpr (rotated.value) ph = rotate4(ph, cs[u & 1][0], sn[u & 1][0], cs[u & 1][1], sn[u & 1][1]);
+          for (int u = 0; u < 2; ++u) {
+            if (i + u + 1 < D / 8) request(i + u + 1, u ^ 1);
+            f32x4 ph = feature_map(x[u]);
+            if constexpr (rotated.value) ph = rotate4(ph, cs[u][0], sn[u][0], cs[u][1], sn[u][1]);
 #pragma unroll
             for (int e = 0; e < 4; ++e)
 #pragma unroll
-              for (int j = 0; j < NB; ++j) part[j] = mfma_f32_wide(a[u & 1][e][j], ph[e], part[j]);
+              for (int j = 0; j < NB; ++j) part[j] = mfma_f32_wide(a[u][e][j], ph[e], part[j]);
           }
 #pragma unroll
           for (int j = 0; j < NB; ++j) o[j0 + j] += part[j];

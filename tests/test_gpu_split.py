@@ -308,3 +308,19 @@ def test_a_head_alone_and_among_many(dtype, d):
     for idx, scores, O in outs[1:]:
         assert torch.equal(idx, outs[0][0]) and torch.equal(scores, outs[0][1])
         assert ((O - outs[0][2]).norm() / O.norm()).item() <= (2e-6 if dtype == "f32" else 1e-3)
+
+
+@pytest.mark.parametrize("heads,d,bkv", BAD)
+def test_sums_of_the_history_term(heads, d, bkv):
+    """History term alone (no value in the window), positive terms.  A rounding at full size is off by 2.5e-8 of the result (2^-24
+    over a mantissa of 1 to 2); the products' sum, the normaliser's, its reciprocal and the scaling are about ten of them: 8.0e-8.
+    With the normaliser's 64 or 32 terms of a lane in one chain, or 32 products in one, it was 9.2e-8 and 11.3e-8."""
+    cfg = hf.make_config(1, heads, d, "f32", 64, 64, 1.0)
+    g = torch.Generator().manual_seed(heads)
+    Q, K = torch.randn(1, heads, 130, d, generator=g), torch.zeros(1, heads, 64 if bkv == 64 else 2 * bkv, d)
+    st = torch.rand(hf.hf_state_bytes(cfg) // 4, generator=g) + 0.5
+    L, z = st[:heads * d * d].view(heads, d, d).double(), st[heads * d * d:heads * d * (d + 1)].view(heads, 1, d).double()
+    phi = Q[0].double().clamp(min=0)
+    want = (phi @ L) / (cfg.z_scale * (phi * z).sum(-1, keepdim=True) + cfg.eps)
+    got = _attend(cfg, Q.to(DEV), K.to(DEV), K.to(DEV), None, st.to(DEV))[0].cpu().double()
+    assert ((got - want).norm() / want.norm()).item() <= 8.4e-8
