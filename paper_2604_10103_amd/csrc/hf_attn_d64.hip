@@ -19,7 +19,7 @@
 // split.  Per wavefront and tile 16 MFMAs (512 cycles of matrix pipe, ~13 each of the issue port) next to ~530 cycles of vector
 // issue (an exponential 8 cycles, three-operand and conversion instructions 4, plain additions and products 2).
 // 832x480 with 24 heads of 64 (4680 x 9360, k = 37 of 147 blocks of 64; selection included): 0.66 ms with both products on the
-// fp32 matrix instruction, 0.172 ms with this kernel; of those, 12 us are the tiles' transfers, 18 us the selection.
+// fp32 matrix instruction, 0.165 ms with this kernel; of those, 12 us are the tiles' transfers, 18 us the selection.
 #include <type_traits>
 
 #include "hf_f32_mfma.h"
