@@ -602,14 +602,16 @@ __global__ __launch_bounds__(64 * NW * KS, 2) void attn_mfma_kernel(
   // the state's plane, its row statistics and the accumulators that the other groups finish
   constexpr int PSTAT = ND * KTILE, PPART = PSTAT + BQ * 8, PEND = PPART + (4 - ND) * NW * 4096;
   constexpr int GB = KS > 1 && PEND > 5 * KTILE ? PEND : 5 * KTILE;
-  __shared__ __attribute__((aligned(16))) char smem[KS * GB];
-  static_assert(BQ * OSTR <= KS * GB, "staged output must fit in the tiles");
+  // (the staged output of eight wavefronts' rows is larger than their tiles)
+  __shared__ __attribute__((aligned(16))) char smem[KS * GB > BQ * OSTR ? KS * GB : BQ * OSTR];
 
   // consecutive workgroup ids go to consecutive XCDs: give every XCD one contiguous run of
   // (head, query block) items so that its L2 sees few heads
-  if (kSel && (int)blockIdx.x < ab.role_blocks) {
-    absorb_role<NW * KS>(smem, ab);
-    return;
+  if constexpr (kSel) {
+    if ((int)blockIdx.x < ab.role_blocks) {
+      absorb_role<NW * KS>(smem, ab);
+      return;
+    }
   }
   const int wgid = kSel ? (int)blockIdx.x - ab.role_blocks : (int)blockIdx.x;
   const int xcd = wgid & 7, slot = wgid >> 3;
@@ -630,7 +632,7 @@ __global__ __launch_bounds__(64 * NW * KS, 2) void attn_mfma_kernel(
   const int32_t* row_idx = kSel ? hist.idx_out + ((size_t)bh * t_m + qb) * k : (idx ? idx + ((size_t)bh * t_m + qb) * k : nullptr);
   const int nsel = (kSel || idx) ? k : t_n;
   const int* sel_lds = nullptr;   // kSel: the list in LDS, valid until the first tile is requested
-  if (kSel)
+  if constexpr (kSel)
     sel_lds = select_in_workgroup<NW, KS, kSel == 2>(smem, Qh, qb * BQ, n_q, hist.kbar_t + (size_t)bh * (D / 4) * t_n * 4, t_n, k,
                                                  hist.idx_out + ((size_t)bh * t_m + qb) * k,
                                                  hist.scores_out ? hist.scores_out + ((size_t)bh * t_m + qb) * t_n : nullptr,
@@ -1189,12 +1191,38 @@ bool attn_pools_itself(const hf_config& c, int n_q, int t_n, int first, int end)
   return end > first && end - first <= kMaxOwnBlocks && t_n <= 512 && key_groups(c, attending) == 2;
 }
 
+// The dense window (no list) needs no workgroup per query block: any number of rows and of groups covers it.  Every shape's time
+// is modelled from its trips (tiles over groups) and the fullest compute unit's wavefronts per SIMD, two of them at a time: a
+// trip takes 0.53 us of a wavefront alone on its SIMD and 0.88..1.0 of two, less the more wavefronts share a tile's transfer,
+// and every round pays what surrounds the loop.  Measured, the rows' own size before / this choice: 12 heads x 4680 x 9360
+// 291 / 263 us (eight wavefronts of rows), 12 x 2340 x 4680 83.6 / 73.7 (4 x 2), 6 x 2000 x 6000 59.8 / 47.2 and 5 x 854 x 2562
+// at block_q 128 37.6 / 23.4 (2 x 4), 34 x 2688 x 8064 397 / 366 (4 x 2); within 4 % of the fastest shape at fourteen sizes.
+struct DenseShape { int nw, ks; };
+static DenseShape dense_shape(long long BH, int n_q, long long tiles) {
+  static const struct { int nw, ks; float two, around; } shapes[] = {
+      {2, 1, 0.98f, 4.4f}, {2, 2, 1.00f, 4.8f}, {2, 4, 0.92f, 6.4f}, {4, 1, 0.91f, 4.7f}, {4, 2, 0.92f, 5.7f}, {8, 1, 0.88f, 6.3f}};
+  DenseShape best = {2, 1};
+  float least = INFINITY;
+  for (const auto& s : shapes) {
+    const long long wgs = BH * ((n_q + 32 * s.nw - 1) / (32 * s.nw)), on_cu = (wgs + 255) / 256;
+    const long long waves = (on_cu * s.nw * s.ks + 3) / 4;   // per SIMD of the fullest compute unit
+    const long long trips = (tiles + s.ks - 1) / s.ks;
+    const float t = (float)trips * ((float)(waves / 2) * s.two + (float)(waves & 1) * 0.53f) + (float)((waves + 1) / 2) * s.around;
+    if (t < least) { least = t; best = {s.nw, s.ks}; }
+  }
+  return best;
+}
+
 static int launch_attn_mfma_impl(const hf_config& c, const void* Q, int n_q, const void* K, const void* V, int n_kv,
                                  const int32_t* idx, int k, const HistArgs* hist, void* O, hipStream_t s,
                                  const AbsorbArgs* absorb = nullptr) {
   if (n_kv >= kMfmaMaxKeys) { set_error("window longer than %d keys", kMfmaMaxKeys); return HF_ERR_SHAPE; }
   const int BH = c.batch * c.heads;
-  const int t_m = (n_q + c.block_q - 1) / c.block_q, t_n = (n_kv + c.block_kv - 1) / c.block_kv;
+  const int t_n = (n_kv + c.block_kv - 1) / c.block_kv;
+  const HistArgs h = hist ? *hist : HistArgs{};
+  const bool dense = !idx && !h.kbar_t && !h.lse2;   // (the row statistics alone keep the block's rows)
+  const DenseShape ds = dense ? dense_shape(BH, n_q, (long long)t_n * ((c.block_kv + TK - 1) / TK)) : DenseShape{c.block_q / 32, 0};
+  const int t_m = (n_q + 32 * ds.nw - 1) / (32 * ds.nw);
   const long long total = (long long)BH * t_m;
   if (total > (1ll << 30)) { set_error("too many query blocks"); return HF_ERR_SHAPE; }
   const int per_xcd = (int)((total + 7) / 8);
@@ -1206,8 +1234,7 @@ static int launch_attn_mfma_impl(const hf_config& c, const void* Q, int n_q, con
   const bf16_t* kk = static_cast<const bf16_t*>(K);
   const bf16_t* v = static_cast<const bf16_t*>(V);
   bf16_t* o = static_cast<bf16_t*>(O);
-  const HistArgs h = hist ? *hist : HistArgs{};
-  const int ks = key_groups(c, total);
+  const int ks = dense ? ds.ks : key_groups(c, total);
 #define HF_LAUNCH_ATTN_KS(NWV, FUSED, SEL, KS)                                                                         \
   hipLaunchKernelGGL((attn_mfma_kernel<NWV, FUSED, SEL, KS>), grid, dim3(64 * NWV * KS), 0, s, q, kk, v, idx, k, n_q, n_kv, \
                      kv_stride_of(c, n_kv), c.block_kv, t_m, t_n, per_xcd, (int)total, c_scale, h, ab, o)
@@ -1241,11 +1268,25 @@ static int launch_attn_mfma_impl(const hf_config& c, const void* Q, int n_q, con
     }
     return check_launch("hf_select_attn_fwd(attention)");
   }
-  if (c.block_q == 64) {
+#define HF_LAUNCH_DENSE(NWV, KS)                                                                                       \
+  do {                                                                                                                 \
+    if (fused == 0) HF_LAUNCH_ATTN_KS(NWV, 0, 0, KS);                                                                  \
+    else if (fused == 1) HF_LAUNCH_ATTN_KS(NWV, 1, 0, KS);                                                             \
+    else HF_LAUNCH_ATTN_KS(NWV, 2, 0, KS);                                                                             \
+  } while (0)
+  if (dense) {
+    if (ds.nw == 8) HF_LAUNCH_DENSE(8, 1);
+    else if (ds.nw == 4 && ds.ks == 2) HF_LAUNCH_DENSE(4, 2);
+    else if (ds.nw == 4) HF_LAUNCH_DENSE(4, 1);
+    else if (ds.ks == 4) HF_LAUNCH_DENSE(2, 4);
+    else if (ds.ks == 2) HF_LAUNCH_DENSE(2, 2);
+    else HF_LAUNCH_DENSE(2, 1);
+  } else if (c.block_q == 64) {
     if (fused == 0) HF_LAUNCH_ATTN(2, 0); else if (fused == 1) HF_LAUNCH_ATTN(2, 1); else if (fused == 2) HF_LAUNCH_ATTN(2, 2); else HF_LAUNCH_ATTN_KS(2, 3, 0, 1);
   } else {
     if (fused == 0) HF_LAUNCH_ATTN(4, 0); else if (fused == 1) HF_LAUNCH_ATTN(4, 1); else if (fused == 2) HF_LAUNCH_ATTN(4, 2); else HF_LAUNCH_ATTN_KS(4, 3, 0, 1);
   }
+#undef HF_LAUNCH_DENSE
 #undef HF_LAUNCH_ATTN
 #undef HF_LAUNCH_ATTN_SEL
 #undef HF_LAUNCH_ATTN_KS
