@@ -720,10 +720,12 @@ static int fwd_impl(const hf_config* cfg, const void* Q, const void* Q_hist, int
     char* planes = static_cast<char*>(workspace) + w.planes;
     const float* st = static_cast<const float*>(state_or_null);
     const size_t d = cfg->head_dim;
-    HF_TRY(launch_state_planes(*cfg, st, planes, s));
-    return launch_attn_mfma_fused(*cfg, Q, n_q, K_win, V_win, n_kv, block_idx, k, planes,
+    const bool direct = attn_rounds_state_itself(*cfg, n_q, n_kv, block_idx == nullptr);   // no planes, no launch for them
+    if (!direct) HF_TRY(launch_state_planes(*cfg, st, planes, s));
+    return launch_attn_mfma_fused(*cfg, Q, n_q, K_win, V_win, n_kv, block_idx, k, direct ? nullptr : planes,
                                   st + (size_t)cfg->batch * cfg->heads * d * d, rope_cos_q, rope_sin_q, Q_hist, O, s,
-                                  save ? lse2_out : nullptr, save ? O_local_out : nullptr);
+                                  save ? lse2_out : nullptr, save ? O_local_out : nullptr, nullptr, nullptr, nullptr, 0, 0,
+                                  direct ? st : nullptr);
   }
   if (attn_wide_taken(*cfg))   // the fp32-arithmetic kernel adds the history term itself
     return launch_attn_wide_hist(*cfg, Q, Q_hist, n_q, K_win, V_win, n_kv, block_idx, k,

@@ -90,6 +90,7 @@ struct HistArgs {
   int32_t* idx_out;      // [BH][T_m][k] the ascending block list of every query block (also read back by the kernel)
   float* scores_out;     // [BH][T_m][T_n] the scores A of Eq. 4, or NULL
   int pool_first, pool_end;   // kSel == 2: KV blocks that the workgroups pool themselves (kbar_t holds the others)
+  const float* state;    // L [BH][d][d]: every workgroup forms the high plane from it (planes = NULL, n_planes = 1)
 };
 
 // ---- Eq. 4 and the Top-K of a query block inside the attention workgroup (kSel).
@@ -947,6 +948,35 @@ __global__ __launch_bounds__(64 * NW * KS, 2) void attn_mfma_kernel(
 #pragma unroll
     for (int i = 0; i < ND; ++i) dma_tile(p_desc, sK_lds + i * KTILE, 32 * (ND * grp + i), k_lane_off);
   };
+  // Without kept planes the workgroup rounds the fp32 state itself, into the same places: a thread owns one value feature, whose
+  // key features lie a row of L apart (a wavefront reads 256 bytes of a row), eight of them a 16-byte unit.
+  auto stage_state = [&]() {
+    constexpr int JN = 32 * ND, UPT = 16 * JN / (64 * NW), UB = UPT < 8 ? UPT : 8;   // units per thread, and in flight
+    const int t = 64 * wave + lane, j = t & (JN - 1), u0 = t / JN * UPT;
+    const float* src = hist.state + (size_t)bh * D * D + JN * grp + j;
+    char* const dst = sK + (j >> 5) * KTILE + (j & 31) * KSTR;
+#pragma unroll
+    for (int ub = 0; ub < UPT; ub += UB) {
+      float x[UB][8];
+#pragma unroll
+      for (int u = 0; u < UB; ++u)
+#pragma unroll
+        for (int e = 0; e < 8; ++e) x[u][e] = src[(size_t)(8 * (u0 + ub + u) + e) * D];
+#pragma unroll
+      for (int u = 0; u < UB; ++u) {
+        uint32_t w[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) w[e] = (uint32_t)f32_to_bf16(x[u][2 * e]) | ((uint32_t)f32_to_bf16(x[u][2 * e + 1]) << 16);
+        *reinterpret_cast<uint4*>(dst + (((u0 + ub + u) ^ (j & 15)) * 16)) = make_uint4(w[0], w[1], w[2], w[3]);
+      }
+    }
+  };
+  auto first_plane = [&]() {
+    if constexpr (KS > 1 && kSel == 0) {
+      if (hist.state) { stage_state(); return; }   // uniform
+    }
+    dma_plane(0);
+  };
   // (two groups: the normaliser too travels under their meeting)
   constexpr bool kZEarly = KS > 1 && kFused == 1;   // (with rotation tables the registers do not hold both)
   float4 z_of[kZEarly ? 16 : 1];
@@ -956,7 +986,7 @@ __global__ __launch_bounds__(64 * NW * KS, 2) void attn_mfma_kernel(
     for (int s = 0; s < 16; ++s) z_of[s] = *reinterpret_cast<const float4*>(zv + 16 * (s >> 1) + 4 * (s & 1));
   }
   if (KS > 1) {
-    if (kFused == 1 || kFused == 2) dma_plane(0);
+    if (kFused == 1 || kFused == 2) first_plane();
     // ---- the groups' parts of a row meet: 16-byte pieces [block of another group][wavefront][quad][lane], row statistics
     f32x4* const part = reinterpret_cast<f32x4*>(sK + PPART) + wave * 256 + lane;
 #pragma unroll
@@ -1052,7 +1082,7 @@ __global__ __launch_bounds__(64 * NW * KS, 2) void attn_mfma_kernel(
       }
       store_rows(hist.olocal_out + (size_t)bh * n_q * D);
       __syncthreads();
-      if (KS > 1) dma_plane(0);   // (once more: the rows were staged over it)
+      if (KS > 1) first_plane();   // (once more: the rows were staged over it)
     }
   }
 
@@ -1084,7 +1114,7 @@ __global__ __launch_bounds__(64 * NW * KS, 2) void attn_mfma_kernel(
     // ---- O += R(phi(q)) L / (z_scale phi(q).z + eps) (Eq. 3, 6): the query fragments already in
     // registers become the B operand of O_hist^T = Lt x R(phi(Q))^T; the A operand comes from the
     // L2-resident plane(s) through LDS.
-    if (KS == 1) dma_plane(0);
+    if (KS == 1) first_plane();
     const float* zv = hist.zvec + (size_t)bh * D + 8 * h;
     float den = 0.0f;
     if (kFused == 1) {
@@ -1232,6 +1262,17 @@ static DenseShape dense_shape(long long BH, int n_q, long long tiles) {
   return best;
 }
 
+// Whether the attending workgroups round the fp32 state themselves, where no planes are kept: 64 KB of L a workgroup from its
+// XCD's L2 instead of 32 KB of a plane, and no launch in front.  Launches of two or more groups of wavefronts and at most half the
+// chip's workgroups gain that launch (block selection + attention, 7 heads x 5 query blocks 16.7 -> 15.1 us, 5 x 38 36.0 -> 33.7,
+// 20 x 8 of 128 rows 30.5 -> 28.1), full ones gain nothing (12 x 74: 99.2 / 99.5), several rounds lose (30 x 74: 225 / 230).
+bool attn_rounds_state_itself(const hf_config& c, int n_q, int n_kv, bool dense) {
+  const long long bh = (long long)c.batch * c.heads, workgroups = bh * ((n_q + c.block_q - 1) / c.block_q);
+  const long long tiles = (long long)((n_kv + c.block_kv - 1) / c.block_kv) * ((c.block_kv + TK - 1) / TK);
+  return !(c.flags & HF_FLAG_HISTORY_TWO_PLANES) && workgroups <= (c.block_q == 64 ? 512 : 256) &&
+         (dense ? dense_shape(bh, n_q, tiles).ks : key_groups(c, workgroups)) > 1;
+}
+
 static int launch_attn_mfma_impl(const hf_config& c, const void* Q, int n_q, const void* K, const void* V, int n_kv,
                                  const int32_t* idx, int k, const HistArgs* hist, void* O, hipStream_t s,
                                  const AbsorbArgs* absorb = nullptr) {
@@ -1263,7 +1304,7 @@ static int launch_attn_mfma_impl(const hf_config& c, const void* Q, int n_q, con
     else HF_LAUNCH_ATTN_KS(NWV, FUSED, SEL, 1);                                                                        \
   } while (0)
 #define HF_LAUNCH_ATTN(NWV, FUSED) HF_LAUNCH_ATTN_SEL(NWV, FUSED, 0)
-  const int fused = !h.planes && !h.lse2 ? 0 : (h.lse2 ? 3 : ((h.phi_kind == HF_PHI_RELU && h.cosq == nullptr && h.q_hist == nullptr) ? 1 : 2));
+  const int fused = !h.planes && !h.state && !h.lse2 ? 0 : (h.lse2 ? 3 : ((h.phi_kind == HF_PHI_RELU && h.cosq == nullptr && h.q_hist == nullptr) ? 1 : 2));
   if (ab.role_blocks && !h.kbar_t) { set_error("absorbing workgroups ride only in the selecting launch"); return HF_ERR_SHAPE; }
   if (h.kbar_t) {
     // the workgroups select their KV blocks themselves
@@ -1331,12 +1372,13 @@ bool attn_mfma_fused_supported(const hf_config& c) { return attn_mfma_supported(
 int launch_attn_mfma_fused(const hf_config& c, const void* Q, int n_q, const void* K, const void* V, int n_kv,
                            const int32_t* idx, int k, const void* planes, const float* zvec, const float* cosq,
                            const float* sinq, const void* Q_hist, void* O, hipStream_t s, float* lse2_out,
-                           void* olocal_out, const float* kbar_t, int32_t* idx_out, float* scores_out, int pool_first, int pool_end) {
+                           void* olocal_out, const float* kbar_t, int32_t* idx_out, float* scores_out, int pool_first, int pool_end,
+                           const float* state) {
   // One bf16 plane of L (2^-9 per element, errors of the d terms of a readout average out) costs the
   // output nothing measurable next to the bf16 rounding of P and O; HF_FLAG_HISTORY_TWO_PLANES adds the low plane.
   const HistArgs h = {static_cast<const bf16_t*>(planes), zvec, c.eps, c.z_scale, (c.flags & HF_FLAG_HISTORY_TWO_PLANES) ? 2 : 1,
                       c.phi, cosq, sinq, Q_hist == Q ? nullptr : static_cast<const bf16_t*>(Q_hist), nullptr, nullptr, nullptr,
-                      lse2_out, static_cast<bf16_t*>(olocal_out), kbar_t, idx_out, scores_out, pool_first, pool_end};
+                      lse2_out, static_cast<bf16_t*>(olocal_out), kbar_t, idx_out, scores_out, pool_first, pool_end, state};
   return launch_attn_mfma_impl(c, Q, n_q, K, V, n_kv, idx, k, &h, O, s);
 }
 

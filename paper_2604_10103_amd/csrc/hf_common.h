@@ -152,7 +152,9 @@ int launch_attn_mfma_fused(const hf_config& c, const void* Q, int n_q, const voi
                            const float* sinq, const void* Q_hist, void* O, hipStream_t s, float* lse2_out = nullptr,
                            void* olocal_out = nullptr,    // by-products for hf_hybrid_attn_bwd_saved, each optional
                            const float* kbar_t = nullptr, int32_t* idx_out = nullptr, float* scores_out = nullptr,
-                           int pool_first = 0, int pool_end = 0);
+                           int pool_first = 0, int pool_end = 0,
+                           const float* state = nullptr);   // L in place of planes (NULL then): rounded in the epilogue
+bool attn_rounds_state_itself(const hf_config& c, int n_q, int n_kv, bool dense);
 // kbar_t given (idx NULL): every workgroup selects its KV blocks itself (Eq. 4) and writes its list to idx_out; the blocks
 // [pool_first, pool_end) it pools itself and stores in kbar_t (only where attn_pools_itself says so)
 bool attn_pools_itself(const hf_config& c, int n_q, int t_n, int first, int end);
