@@ -24,6 +24,12 @@ __device__ __forceinline__ bf16_t f32_to_bf16(float f) {
   __bf16 b = static_cast<__bf16>(f);
   return __builtin_bit_cast(bf16_t, b);
 }
+// two of them, the first in the low half: one v_cvt_pk_bf16_f32 (joined from two scalars by shifts it is four instructions)
+__device__ __forceinline__ uint32_t pack_bf16(float lo, float hi) {
+  typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+  const bf16x2 v = {static_cast<__bf16>(lo), static_cast<__bf16>(hi)};
+  return __builtin_bit_cast(uint32_t, v);
+}
 
 template <typename T> struct Elem;
 template <> struct Elem<float> {

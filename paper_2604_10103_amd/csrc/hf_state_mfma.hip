@@ -9,15 +9,13 @@
 //
 // The kernel is bound by the HBM read of K_ev and V_ev, which at this size (tens of MB) is a
 // latency problem.  Two kernels:
-//   - absorb_quad_kernel (ReLU, no rotation, caller workspace: the fast path, see there): tiles travel
+//   - absorb_quad_kernel (caller workspace: the fast path, see there): tiles travel
 //     global -> LDS directly, operands by transposing LDS reads, ONE launch that also reduces;
-//   - absorb_mfma_kernel (any feature map, rotated keys, or no workspace): register-staged, described above; a
+//   - absorb_mfma_kernel (no workspace): register-staged, described above; a
 //     workgroup requests ALL the tokens of its run (up to 320) before it touches the first one.  The evicted
-//     tokens of one head are cut into slices, one workgroup each; slice partials are combined through the
-//     workspace by a small reduction kernel, or, without workspace, with device-scope float atomics straight
+//     tokens of one head are cut into slices, one workgroup each, combined with device-scope float atomics straight
 //     into the state (the L2 atomic units retire one dword per channel and clock, which costs more than the
 //     read itself).
-#include <stdlib.h>
 
 #include <type_traits>
 
@@ -66,8 +64,7 @@ __device__ __forceinline__ uint32_t relu_pk(uint32_t x) {
 }
 
 template <bool kPlain>
-__global__ __launch_bounds__(NT, 1) void absorb_mfma_kernel(float* __restrict__ state, float* __restrict__ partials,
-                                                             const bf16_t* __restrict__ K,
+__global__ __launch_bounds__(NT, 1) void absorb_mfma_kernel(float* __restrict__ state, const bf16_t* __restrict__ K,
                                                              const bf16_t* __restrict__ V, int n, int head_stride,
                                                              int tokens_per_slice, const float* __restrict__ cosv,
                                                              const float* __restrict__ sinv, int phi_kind, int BH,
@@ -76,17 +73,10 @@ __global__ __launch_bounds__(NT, 1) void absorb_mfma_kernel(float* __restrict__ 
   __shared__ __attribute__((aligned(16))) uint32_t Vt[D * SP];
   __shared__ float zs[D];
 
-  int bh, slice;
-  if (partials) {  // plain (head, slice) order: every XCD streams the same number of bytes
-    bh = blockIdx.x / slices;
-    slice = blockIdx.x - bh * slices;
-  } else {
-    // Consecutive workgroup ids land on consecutive XCDs; all slices of one (batch, head) go to
-    // one XCD (head index mod 8), which keeps that head's atomics in a single L2.
-    const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
-    bh = xcd + 8 * (slot / slices);
-    slice = slot % slices;
-  }
+  // Consecutive workgroup ids land on consecutive XCDs; all slices of one (batch, head) go to
+  // one XCD (head index mod 8), which keeps that head's atomics in a single L2.
+  const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
+  const int bh = xcd + 8 * (slot / slices), slice = slot % slices;
   if (bh >= BH) return;
   const int t0 = slice * tokens_per_slice;
   const int t1 = min(n, t0 + tokens_per_slice);
@@ -237,15 +227,8 @@ __global__ __launch_bounds__(NT, 1) void absorb_mfma_kernel(float* __restrict__ 
   }
 
   // ---- hand the partial over
-  float* L;
-  float* z;
-  if (partials) {
-    L = partials + ((size_t)bh * slices + slice) * PART;
-    z = L + D * D;
-  } else {
-    L = state + (size_t)bh * D * D;
-    z = state + (size_t)BH * D * D + (size_t)bh * D;
-  }
+  float* L = state + (size_t)bh * D * D;
+  float* z = state + (size_t)BH * D * D + (size_t)bh * D;
   // lanes l, l + 8, l + 16, l + 24 of a half-wavefront hold the same feature group: sum them first
 #pragma unroll
   for (int e = 0; e < 8; ++e) {
@@ -257,40 +240,22 @@ __global__ __launch_bounds__(NT, 1) void absorb_mfma_kernel(float* __restrict__ 
     for (int e = 0; e < 8; ++e) atomicAdd(&zs[8 * g + e], zacc[e]);
   }
   // The tiles were accumulated transposed (V fragment as the A operand): a lane holds, for ONE key
-  // feature i, four consecutive value features j per register group, i.e. 16 contiguous bytes of
-  // row i of L.  Two straight-line epilogues (a choice per element costs a branch each).
-  if (partials) {
+  // feature i, four consecutive value features j per register group.
 #pragma unroll
-    for (int a = 0; a < TA; ++a)
+  for (int a = 0; a < TA; ++a)
 #pragma unroll
-      for (int b = 0; b < 2; ++b)
+    for (int b = 0; b < 2; ++b)
 #pragma unroll
-        for (int rq = 0; rq < 4; ++rq) {
-          const int i = 32 * (mi0 + a) + l32;
-          const int j = 32 * (nj0 + b) + 8 * rq + 4 * h;
-          *reinterpret_cast<float4*>(L + i * D + j) =
-              make_float4(acc[a][b][4 * rq], acc[a][b][4 * rq + 1], acc[a][b][4 * rq + 2], acc[a][b][4 * rq + 3]);
-        }
-  } else {
-#pragma unroll
-    for (int a = 0; a < TA; ++a)
-#pragma unroll
-      for (int b = 0; b < 2; ++b)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          const int i = 32 * (mi0 + a) + l32;
-          const int j = 32 * (nj0 + b) + 8 * (r >> 2) + 4 * h + (r & 3);
-          atomicAdd(L + i * D + j, acc[a][b][r]);
-        }
-  }
+      for (int r = 0; r < 16; ++r) {
+        const int i = 32 * (mi0 + a) + l32;
+        const int j = 32 * (nj0 + b) + 8 * (r >> 2) + 4 * h + (r & 3);
+        atomicAdd(L + i * D + j, acc[a][b][r]);
+      }
   __syncthreads();
-  if (tid < D) {
-    if (partials) z[tid] = zs[tid];
-    else atomicAdd(z + tid, zs[tid]);
-  }
+  if (tid < D) atomicAdd(z + tid, zs[tid]);
 }
 
-// ---- the plain case (ReLU, no rotation, workspace given): ONE launch, partials of a few fat slices ---------------
+// ---- workspace given: ONE launch, partials of a few fat slices ----------------------------------------------------
 // Work item = (head, token slice, quadrant of L).  The evicted tokens of a head are cut into a FEW slices (about
 // 256 / (4 heads) of them), and the four workgroups of a (head, slice) share its tokens: each accumulates one
 // 64 x 64 quadrant L[64a .. , 64b ..] over the slice, reading the matching halves of the K and V rows.  The four
@@ -318,11 +283,12 @@ typedef short s16x8 __attribute__((ext_vector_type(8)));
 constexpr int QT = 32;                  // tokens per tile
 constexpr int QROW = 128;               // bytes per token row of a tile (64 features)
 constexpr int QTILE = QT * QROW;        // bytes of one tile of one tensor
-constexpr int QSLOT = 4 * QTILE;        // a ring slot: a pair of tiles (even, odd) of both tensors, 64 tokens
 constexpr int QNT = 512;                // threads per workgroup: two groups of four wavefronts (even / odd tiles),
                                         // one 32 x 32 tile of the quadrant per wavefront
-constexpr int LSTR = 68;                // floats per row of the staged 64 x 64 block (16-byte aligned rows)
-constexpr int QUADS = 4;
+constexpr int QRUN = 8;                 // pairs of tiles (512 tokens) that are summed for themselves where keys are rounded
+// a ring slot: a pair of tiles (even, odd) of K and of one or two halves of V, 64 tokens; rotation: 2 KB of tables a wavefront
+constexpr int slot_bytes(int nv, int map) { return 2 * (1 + nv) * QTILE + (map >= 2 ? 2 * 8 * 1024 : 0); }
+constexpr int block_stride(int nv) { return 64 * nv + 4; }   // floats per row of the staged block (16-byte aligned rows)
 
 __device__ __forceinline__ bf16x8 tr_frag64(const char* tile, uint32_t base, int ft, int t2) {
   const char* p0 = tile + (base ^ (64u * ft)) + 2048 * t2;
@@ -332,23 +298,32 @@ __device__ __forceinline__ bf16x8 tr_frag64(const char* tile, uint32_t base, int
   return __builtin_bit_cast(bf16x8, both);
 }
 
-template <int kRing>
+// kMap: 0 = ReLU of unrotated keys, formed on the fragments; 1 = ELU + 1 of unrotated keys; 2 = ReLU, 3 = ELU + 1 of rotated
+// keys.  With a map every lane transforms the 16 bytes of K that it transferred itself, in place in LDS, as soon as its own
+// transfers of the pair have landed (the tables' rows have the geometry of K's and travel beside them, every lane's cosines
+// and sines to a place of its own), and the barrier that follows is the one there was.
+// NV: 64-column halves of the value features that a workgroup accumulates (1: a quadrant of L, 2: a half)
+template <int kRing, int kMap, int NV>
 __global__ __launch_bounds__(QNT) void absorb_quad_kernel(float* __restrict__ state, bf16_t* __restrict__ planes,
                                                           unsigned long long* __restrict__ counters,
                                                           float* __restrict__ partials, const bf16_t* __restrict__ K,
                                                           const bf16_t* __restrict__ V, int n, int head_stride,
                                                           int tokens_per_slice, int slices, int BH,
-                                                          unsigned long long tag) {
-  extern __shared__ __attribute__((aligned(16))) char smem[];   // kRing x 2 x (K tile, V tile); later the staged block
-  static_assert(kRing * QSLOT >= (64 * LSTR + 64) * 4, "the staged block must fit in the ring");
-  static_assert(2 * (kRing - 2) <= 63, "vmcnt holds six bits");
+                                                          unsigned long long tag, const float* __restrict__ cosv,
+                                                          const float* __restrict__ sinv) {
+  extern __shared__ __attribute__((aligned(16))) char smem[];   // kRing x 2 x (K tile, V tile) (and tables); later the staged block
+  constexpr int SLOT = slot_bytes(NV, kMap), GROUP = (1 + NV) * QTILE, TABLES = 2 * GROUP;
+  constexpr int PER = 1 + NV + (kMap >= 2 ? 2 : 0);   // transfers of a wavefront per pair
+  constexpr int PARTS = 4 / NV, LSTR = block_stride(NV);
+  static_assert(kRing * SLOT >= (64 * LSTR + 64 + 8 * 64) * 4, "the staged block must fit in the ring");
+  static_assert(PER * (kRing - 1) <= 63, "vmcnt holds six bits");
   __shared__ int s_last;
-  // consecutive workgroup ids go to consecutive XCDs: the four quadrants of a (head, slice) share one
+  // consecutive workgroup ids go to consecutive XCDs: the parts of a (head, slice) share one
   const int xcd = blockIdx.x & 7, slot = blockIdx.x >> 3;
-  const int item = xcd + 8 * (slot >> 2), quad = slot & 3;
+  const int item = xcd + 8 * (slot / PARTS), quad = slot % PARTS;
   if (item >= BH * slices) return;
   const int bh = item / slices, slice = item - bh * slices;
-  const int qa = quad >> 1, qb = quad & 1;   // key-feature half, value-feature half
+  const int qa = NV == 1 ? quad >> 1 : quad, qb = NV == 1 ? quad & 1 : 0;   // key-feature half, first value-feature half
   const int t0 = slice * tokens_per_slice;
   const int t1 = min(n, t0 + tokens_per_slice);
   const int npairs = (t1 - t0 + 2 * QT - 1) / (2 * QT);
@@ -364,7 +339,8 @@ __global__ __launch_bounds__(QNT) void absorb_quad_kernel(float* __restrict__ st
   const int unit = (lane & 7) ^ (4 * ((row >> 1) & 1));
   const int k_off = row * (D * 2) + 128 * qa + 16 * unit;
   const int v_off = row * (D * 2) + 128 * qb + 16 * unit;
-  const uint32_t lds0 = (uint32_t)(uintptr_t)smem + grp * (2 * QTILE) + 1024 * (wave & 3);
+  const uint32_t lds0 = (uint32_t)(uintptr_t)smem + grp * GROUP + 1024 * (wave & 3);
+  const uint32_t lds_tab = (uint32_t)(uintptr_t)smem + TABLES + 2048 * wave;
   const uint64_t kbase = reinterpret_cast<uint64_t>(K + (size_t)bh * head_stride * D);
   const uint64_t vbase = reinterpret_cast<uint64_t>(V + (size_t)bh * head_stride * D);
   auto fetch = [&](int c) {   // pair c of the slice into slot c mod kRing; rows past t1 (and whole tiles) as zeros
@@ -374,11 +350,24 @@ __global__ __launch_bounds__(QNT) void absorb_quad_kernel(float* __restrict__ st
     const uint64_t va = vbase + (uint64_t)(left > 0 ? first : 0) * (D * 2);
     const i32x4 kd = {(int)(uint32_t)ka, (int)(uint32_t)(ka >> 32), left > 0 ? left : 0, 0x00020000};
     const i32x4 vd = {(int)(uint32_t)va, (int)(uint32_t)(va >> 32), left > 0 ? left : 0, 0x00020000};
-    const uint32_t dst = lds0 + (uint32_t)(c % kRing) * QSLOT;
+    const uint32_t dst = lds0 + (uint32_t)(c % kRing) * SLOT;
     asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds"
                  :: "s"(dst), "v"(k_off), "s"(kd) : "memory", "m0");
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds"
-                 :: "s"(dst + QTILE), "v"(v_off), "s"(vd) : "memory", "m0");
+#pragma unroll
+    for (int v = 0; v < NV; ++v)
+      asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds"
+                   :: "s"(dst + QTILE * (1 + v)), "v"(v_off + 128 * v), "s"(vd) : "memory", "m0");
+    if constexpr (kMap >= 2) {   // (a table row is 64 floats: the bytes of a key's row, pair p under features 2 p, 2 p + 1 of its half)
+      const uint32_t tdst = lds_tab + (uint32_t)(c % kRing) * SLOT;
+      const uint64_t ca = reinterpret_cast<uint64_t>(cosv) + (uint64_t)(left > 0 ? first : 0) * (D * 2);
+      const uint64_t sa = reinterpret_cast<uint64_t>(sinv) + (uint64_t)(left > 0 ? first : 0) * (D * 2);
+      const i32x4 cd = {(int)(uint32_t)ca, (int)(uint32_t)(ca >> 32), left > 0 ? left : 0, 0x00020000};
+      const i32x4 sd = {(int)(uint32_t)sa, (int)(uint32_t)(sa >> 32), left > 0 ? left : 0, 0x00020000};
+      asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds"
+                   :: "s"(tdst), "v"(k_off), "s"(cd) : "memory", "m0");
+      asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds"
+                   :: "s"(tdst + 1024), "v"(k_off), "s"(sd) : "memory", "m0");
+    }
   };
   // operand address of a lane inside a tile: the 16-lane group g reads 4 token rows x 16 features, lane j of it
   // supplies the 8-byte chunk (row 4 h + j / 4, features 4 (j % 4) .. + 4) and receives feature 16 (g & 1) + j
@@ -390,22 +379,84 @@ __global__ __launch_bounds__(QNT) void absorb_quad_kernel(float* __restrict__ st
     tb = key_l * QROW + 64 * ((key_l >> 1) & 1) + 16 * low2 + 8 * (j & 1);   // ^ 64 ft, + 1024 x + 2048 t2
   }
 
-  f32x16 acc;
+  f32x16 acc[NV];
 #pragma unroll
-  for (int r = 0; r < 16; ++r) acc[r] = 0.0f;
+  for (int v = 0; v < NV; ++v) acc[v] = {};
   float zacc = 0.0f;   // sum over this lane's tokens of phi(k) for key feature 64 qa + 32 wa + l32
   const s16x8 zero8 = {0, 0, 0, 0, 0, 0, 0, 0};
-  bf16x8 kf[2], vf[2];   // fragments of the tile read in the previous trip (zeros before the first)
+  bf16x8 kf[2], vf[2][NV];   // fragments of the tile read in the previous trip (zeros before the first)
 #pragma unroll
-  for (int t2 = 0; t2 < 2; ++t2) kf[t2] = vf[t2] = __builtin_bit_cast(bf16x8, zero8);
+  for (int t2 = 0; t2 < 2; ++t2) {
+    kf[t2] = __builtin_bit_cast(bf16x8, zero8);
+#pragma unroll
+    for (int v = 0; v < NV; ++v) vf[t2][v] = kf[t2];
+  }
+  // With a map the sums of QRUN pairs meet the slice's once, so that the rounding does not grow with the slice.  Against 64 bits,
+  // features exact in bf16, ELU keys of 13 heads x 6400 tokens / rotated ones of 12 x 23400 / of 256 x 6000: 4.7e-8 / 7.6e-8 / 8.6e-8
+  // (slices of runs of 320 tokens, added by a launch of their own: 5.1e-8 / 8.5e-8 / 9.2e-8).
+  f32x16 whole[NV];
+  float z_run[8], z_whole[8];
+  if constexpr (kMap != 0) {
+#pragma unroll
+    for (int v = 0; v < NV; ++v) whole[v] = {};
+#pragma unroll
+    for (int e = 0; e < 8; ++e) z_run[e] = z_whole[e] = 0.0f;
+  }
+  // phi and the rotation of the lane's own sixteen bytes of pair c's keys
+  auto transform = [&](int c) {
+    constexpr int kPhi = kMap == 2 ? HF_PHI_RELU : HF_PHI_ELU1;
+    char* const own = smem + (c % kRing) * SLOT + grp * GROUP + 1024 * (wave & 3) + 16 * lane;
+    const uint4 raw = *reinterpret_cast<const uint4*>(own);
+    uint32_t w[4] = {raw.x, raw.y, raw.z, raw.w};
+    float cc[4], ss[4];
+    if constexpr (kMap >= 2) {
+      const char* tab = smem + (c % kRing) * SLOT + TABLES + 2048 * wave + 16 * lane;
+      const float4 c4 = *reinterpret_cast<const float4*>(tab), s4 = *reinterpret_cast<const float4*>(tab + 1024);
+      cc[0] = c4.x; cc[1] = c4.y; cc[2] = c4.z; cc[3] = c4.w;
+      ss[0] = s4.x; ss[1] = s4.y; ss[2] = s4.z; ss[3] = s4.w;
+    }
+    if (kPhi == HF_PHI_ELU1 && t0 + (2 * c + 2) * QT > t1) {   // (uniform) ELU + 1 of what does not exist: zero, as of -infinity
+      const bool live = t0 + (2 * c + grp) * QT + row < t1;
+#pragma unroll
+      for (int q = 0; q < 4; ++q) w[q] = live ? w[q] : 0xff80ff80u;
+    }
+    uint32_t o[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      float f0 = phi_apply(__uint_as_float(w[q] << 16), kPhi), f1 = phi_apply(__uint_as_float(w[q] & 0xffff0000u), kPhi);
+      z_run[2 * q] += f0;
+      z_run[2 * q + 1] += f1;
+      if constexpr (kMap >= 2) {
+        const float r0 = f0 * cc[q] - f1 * ss[q], r1 = f0 * ss[q] + f1 * cc[q];
+        f0 = r0;
+        f1 = r1;
+      }
+      o[q] = pack_bf16(f0, f1);
+    }
+    *reinterpret_cast<uint4*>(own) = make_uint4(o[0], o[1], o[2], o[3]);
+  };
+  auto end_run = [&]() {
+#pragma unroll
+    for (int v = 0; v < NV; ++v) { whole[v] += acc[v]; acc[v] = {}; }
+#pragma unroll
+    for (int e = 0; e < 8; ++e) { z_whole[e] += z_run[e]; z_run[e] = 0.0f; }
+  };
   auto contract = [&]() {
+    if constexpr (kMap != 0) {
+#pragma unroll
+      for (int t2 = 0; t2 < 2; ++t2)
+#pragma unroll
+        for (int v = 0; v < NV; ++v) acc[v] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[t2][v], kf[t2], acc[v], 0, 0, 0);
+      return;
+    }
 #pragma unroll
     for (int t2 = 0; t2 < 2; ++t2) {
       // ReLU of bf16 values as a packed signed-integer max with zero
       const bf16x8 a = __builtin_bit_cast(bf16x8, __builtin_elementwise_max(__builtin_bit_cast(s16x8, kf[t2]), zero8));
 #pragma unroll
       for (int e = 0; e < 8; ++e) zacc += static_cast<float>(a[e]);
-      acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[t2], a, acc, 0, 0, 0);   // L^T tile
+#pragma unroll
+      for (int v = 0; v < NV; ++v) acc[v] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(vf[t2][v], a, acc[v], 0, 0, 0);   // L^T tile
     }
   };
 
@@ -413,7 +464,7 @@ __global__ __launch_bounds__(QNT) void absorb_quad_kernel(float* __restrict__ st
   // at it now (the load is this wavefront's oldest request, so it has returned once at most the transfers issued
   // behind it are in flight) and claims it if the tag is another call's; whether this exchange or another
   // workgroup's wins does not matter.  Two round trips to memory, hidden behind the first tiles' latency.
-  unsigned long long* const ctr = counters + (size_t)bh * QUADS + quad;
+  unsigned long long* const ctr = counters + (size_t)bh * PARTS + quad;
   const bool claimer = tid == QNT - 64;
   unsigned long long seen = 0;
   if (claimer) asm volatile("global_load_dwordx2 %0, %1, off sc1" : "=&v"(seen) : "v"(ctr) : "memory");
@@ -422,27 +473,52 @@ __global__ __launch_bounds__(QNT) void absorb_quad_kernel(float* __restrict__ st
 #pragma unroll
   for (int c = 0; c < kRing - 1; ++c) fetch(c);
   if (claimer) {
-    asm volatile("s_waitcnt vmcnt(%1)" : "+v"(seen) : "n"(2 * (kRing - 1)) : "memory");
+    asm volatile("s_waitcnt vmcnt(%1)" : "+v"(seen) : "n"(PER * (kRing - 1)) : "memory");
     if ((seen >> 16) != tag)
       (void)__hip_atomic_compare_exchange_strong(ctr, &seen, tag << 16, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
                                                  __HIP_MEMORY_SCOPE_AGENT);
   }
-  for (int c = 0; c < npairs; ++c) {
-    asm volatile("s_waitcnt vmcnt(%0)" :: "n"(2 * (kRing - 2)) : "memory");   // this wavefront's rows of pair c
-    __syncthreads();              // ... and everybody's; everybody has read pair c - 1
-    fetch(c + kRing - 1);         // into the slot of pair c - 1
-    const char* tK = smem + (c % kRing) * QSLOT + grp * (2 * QTILE);
-    bf16x8 nk[2], nv[2];
+  auto frags = [&](int c, bf16x8 (&nk)[2], bf16x8 (&nv)[2][NV]) {
+    const char* tK = smem + (c % kRing) * SLOT + grp * GROUP;
 #pragma unroll
     for (int t2 = 0; t2 < 2; ++t2) {
       nk[t2] = tr_frag64(tK, tb, wa, t2);
-      nv[t2] = tr_frag64(tK + QTILE, tb, wb, t2);
-    }
-    contract();   // the previous trip's tile, while this trip's reads are on their way
 #pragma unroll
-    for (int t2 = 0; t2 < 2; ++t2) { kf[t2] = nk[t2]; vf[t2] = nv[t2]; }
+      for (int v = 0; v < NV; ++v) nv[t2][v] = tr_frag64(tK + QTILE * (NV == 1 ? 1 : 1 + wb), tb, NV == 1 ? wb : v, t2);
+    }
+  };
+  if constexpr (kMap == 0) {
+    for (int c = 0; c < npairs; ++c) {
+      asm volatile("s_waitcnt vmcnt(%0)" :: "n"(PER * (kRing - 2)) : "memory");   // this wavefront's rows of pair c
+      __syncthreads();              // ... and everybody's; everybody has read pair c - 1
+      fetch(c + kRing - 1);         // into the slot of pair c - 1
+      bf16x8 nk[2], nv[2][NV];
+      frags(c, nk, nv);
+      contract();   // the previous trip's tile, while this trip's reads are on their way
+#pragma unroll
+      for (int t2 = 0; t2 < 2; ++t2) {
+        kf[t2] = nk[t2];
+#pragma unroll
+        for (int v = 0; v < NV; ++v) vf[t2][v] = nv[t2][v];
+      }
+    }
+    contract();
+  } else {
+    asm volatile("s_waitcnt vmcnt(%0)" :: "n"(PER * (kRing - 2)) : "memory");
+    transform(0);
+    for (int c = 0; c < npairs; ++c) {
+      __syncthreads();              // everybody has transformed pair c and read pair c - 1
+      fetch(c + kRing - 1);         // into the slot of pair c - 1
+      frags(c, kf, vf);
+      asm volatile("s_waitcnt vmcnt(%0)" :: "n"(PER * (kRing - 2)) : "memory");   // this wavefront's rows of pair c + 1
+      transform(c + 1);                // while the fragments of pair c are on their way
+      contract();
+      if (c % QRUN == QRUN - 1) end_run();   // uniform
+    }
+    end_run();
+#pragma unroll
+    for (int v = 0; v < NV; ++v) acc[v] = whole[v];
   }
-  contract();
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // nothing may land in LDS once the ring's space is reused
   __syncthreads();
 
@@ -451,33 +527,60 @@ __global__ __launch_bounds__(QNT) void absorb_quad_kernel(float* __restrict__ st
   float* tile = reinterpret_cast<float*>(smem);   // [64 key features][LSTR]
   float* zs = tile + 64 * LSTR;                   // [64]
   zacc += __shfl_xor(zacc, 32, kWave);   // the two halves of a tile's tokens
-  float* trow = tile + (32 * wa + l32) * LSTR + 32 * wb + 4 * h;
+  float* const zpart = zs + 64;                   // kMap: [8 wavefronts][64]
+  if constexpr (kMap != 0) {
+    // lanes of one feature group: the row's bits 0 and 2, and bit 1, which swaps the halves of a row's units
+#pragma unroll
+    for (int e = 0; e < 8; ++e) {
+      float z = z_whole[e];
+      z += __shfl_xor(z, 8, kWave);
+      z += __shfl_xor(z, 32, kWave);
+      z += __shfl_xor(z, 20, kWave);
+      if (lane < 8) zpart[64 * wave + 8 * lane + e] = z;
+    }
+  }
+  float* trow = tile + (32 * wa + l32) * LSTR + 32 * NV * wb + 4 * h;   // + 32 v
   if (grp == 0) {
 #pragma unroll
-    for (int rq = 0; rq < 4; ++rq)
-      *reinterpret_cast<float4*>(trow + 8 * rq) = make_float4(acc[4 * rq], acc[4 * rq + 1], acc[4 * rq + 2], acc[4 * rq + 3]);
-    if (wb == 0 && h == 0) zs[32 * wa + l32] = zacc;
+    for (int v = 0; v < NV; ++v)
+#pragma unroll
+      for (int rq = 0; rq < 4; ++rq)
+        *reinterpret_cast<float4*>(trow + 32 * v + 8 * rq) =
+            make_float4(acc[v][4 * rq], acc[v][4 * rq + 1], acc[v][4 * rq + 2], acc[v][4 * rq + 3]);
+    if (kMap == 0 && wb == 0 && h == 0) zs[32 * wa + l32] = zacc;
   }
   __syncthreads();
   if (grp == 1) {
 #pragma unroll
-    for (int rq = 0; rq < 4; ++rq) {
-      float4 t = *reinterpret_cast<const float4*>(trow + 8 * rq);
-      t.x += acc[4 * rq]; t.y += acc[4 * rq + 1]; t.z += acc[4 * rq + 2]; t.w += acc[4 * rq + 3];
-      *reinterpret_cast<float4*>(trow + 8 * rq) = t;
-    }
-    if (wb == 0 && h == 0) zs[32 * wa + l32] += zacc;
+    for (int v = 0; v < NV; ++v)
+#pragma unroll
+      for (int rq = 0; rq < 4; ++rq) {
+        float4 t = *reinterpret_cast<const float4*>(trow + 32 * v + 8 * rq);
+        t.x += acc[v][4 * rq]; t.y += acc[v][4 * rq + 1]; t.z += acc[v][4 * rq + 2]; t.w += acc[v][4 * rq + 3];
+        *reinterpret_cast<float4*>(trow + 32 * v + 8 * rq) = t;
+      }
+    if (kMap == 0 && wb == 0 && h == 0) zs[32 * wa + l32] += zacc;
+  }
+  if (kMap != 0 && tid < 64) {
+    float z = zpart[tid];
+#pragma unroll
+    for (int w = 1; w < 8; ++w) z += zpart[64 * w + tid];
+    zs[tid] = z;
   }
   __syncthreads();
   // Partials are exchanged between workgroups on different XCDs, whose L2 caches do not see each other's lines:
   // they are written and read with device-scope accesses (they go through to memory; a device-scope FENCE would
   // instead write back and invalidate the whole L2 of the XCD, per workgroup: measured 45-120 us per launch).
   float* part = partials + ((size_t)bh * slices + slice) * PART;
-  const int er = tid >> 6, ec = tid & 63;   // a wavefront moves one 256-byte row piece; rows er + 8 p
+  const int er = tid >> 6, ec = tid & 63;   // a wavefront moves one 256-byte row piece: element p of a thread is row er + 8 (p / NV)
+  constexpr int NP8 = 8 * NV;
+  auto at = [&](int p) { return (size_t)(8 * (p / NV)) * D + 64 * (p % NV); };   // from the thread's first element
+  const size_t at0 = (size_t)(64 * qa + er) * D + 64 * qb + ec;
+  float* const mine = tile + er * LSTR + ec;                                     // the same element in the staged block
+  auto at_tile = [&](int p) { return 8 * (p / NV) * LSTR + 64 * (p % NV); };
 #pragma unroll
-  for (int p = 0; p < 8; ++p)
-    __hip_atomic_store(part + (64 * qa + er + 8 * p) * D + 64 * qb + ec, tile[(er + 8 * p) * LSTR + ec],
-                       __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  for (int p = 0; p < NP8; ++p)
+    __hip_atomic_store(part + at0 + at(p), mine[at_tile(p)], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   if (qb == 0 && tid < 64)
     __hip_atomic_store(part + D * D + 64 * qa + tid, zs[tid], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 
@@ -493,206 +596,181 @@ __global__ __launch_bounds__(QNT) void absorb_quad_kernel(float* __restrict__ st
   __syncthreads();
   if (!s_last) return;
 
-  // ---- the last workgroup of the quadrant: state += partials in slice order; planes of the updated quadrant
+  // ---- the last workgroup of the part: state += partials in slice order; planes of the updated part
   // (these loads come from memory, not from L2: all eight of a thread for up to four slices are in flight at once)
   const float* p0 = partials + (size_t)bh * slices * PART;
   float* Lq = state + (size_t)bh * D * D;
   // the slices are summed first and meet the state in ONE addition per call: over a long stream the state is much
   // larger than a chunk's contribution, and every addition at its magnitude costs a rounding of its size
-  float sum[8], old[8];
-  const size_t at0 = (size_t)(64 * qa + er) * D + 64 * qb + ec;   // + 8 p rows
+  float sum[NP8], old[NP8];
 #pragma unroll
-  for (int p = 0; p < 8; ++p) { old[p] = Lq[at0 + (size_t)8 * p * D]; sum[p] = 0.0f; }
+  for (int p = 0; p < NP8; ++p) { old[p] = Lq[at0 + at(p)]; sum[p] = 0.0f; }
   const bool zrow = qb == 0 && tid < 64;
   float* zq = state + (size_t)BH * D * D + (size_t)bh * D + 64 * qa + ec;
   const float zold = zrow ? *zq : 0.0f;
   float zsum = 0.0f;
-  constexpr int kBatch = 6;   // slices whose loads are in flight together (one round trip for the usual 4-6 slices)
-  for (int s0 = 0; s0 < slices; s0 += kBatch) {
-    float v[kBatch][8], zv[kBatch];
+  // slices whose loads are in flight together (one round trip for the usual 4-6 slices; with a map there may be more of them, and
+  // a batch is added in pairs, so that the rounding grows with the batches)
+  constexpr int kBatch = kMap ? 8 : 6;
+  const int batches = (slices + kBatch - 1) / kBatch, batch = kMap ? (slices + batches - 1) / batches : kBatch;   // (even ones)
+  for (int s0 = 0; s0 < slices; s0 += batch) {
+    float v[kBatch][NP8], zv[kBatch];
 #pragma unroll
     for (int u = 0; u < kBatch; ++u) {
       const float* ps = p0 + (size_t)min(s0 + u, slices - 1) * PART;   // (past the last slice: re-read, not added)
 #pragma unroll
-      for (int p = 0; p < 8; ++p)
-        v[u][p] = __hip_atomic_load(ps + at0 + (size_t)8 * p * D, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      for (int p = 0; p < NP8; ++p) v[u][p] = __hip_atomic_load(ps + at0 + at(p), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
       zv[u] = zrow ? __hip_atomic_load(ps + D * D + 64 * qa + ec, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0.0f;
     }
+    if constexpr (kMap != 0) {
 #pragma unroll
-    for (int u = 0; u < kBatch; ++u)
-      if (s0 + u < slices) {   // uniform; slice order
+      for (int u = 1; u < kBatch; ++u)
+        if (u >= batch || s0 + u >= slices) {   // uniform
 #pragma unroll
-        for (int p = 0; p < 8; ++p) sum[p] += v[u][p];
-        zsum += zv[u];
-      }
+          for (int p = 0; p < NP8; ++p) v[u][p] = 0.0f;
+          zv[u] = 0.0f;
+        }
+#pragma unroll
+      for (int step = 1; step < kBatch; step *= 2)
+#pragma unroll
+        for (int u = 0; u < kBatch; u += 2 * step) {
+#pragma unroll
+          for (int p = 0; p < NP8; ++p) v[u][p] += v[u + step][p];
+          zv[u] += zv[u + step];
+        }
+#pragma unroll
+      for (int p = 0; p < NP8; ++p) sum[p] += v[0][p];
+      zsum += zv[0];
+    } else {
+#pragma unroll
+      for (int u = 0; u < kBatch; ++u)
+        if (s0 + u < slices) {   // uniform; slice order
+#pragma unroll
+          for (int p = 0; p < NP8; ++p) sum[p] += v[u][p];
+          zsum += zv[u];
+        }
+    }
   }
 #pragma unroll
-  for (int p = 0; p < 8; ++p) sum[p] += old[p];
+  for (int p = 0; p < NP8; ++p) sum[p] += old[p];
   zsum += zold;
 #pragma unroll
-  for (int p = 0; p < 8; ++p) tile[(er + 8 * p) * LSTR + ec] = sum[p];
+  for (int p = 0; p < NP8; ++p) mine[at_tile(p)] = sum[p];
   __syncthreads();   // (the planes' transposed reads; in front of the state's stores so that all stores leave together)
 #pragma unroll
-  for (int p = 0; p < 8; ++p) Lq[at0 + (size_t)8 * p * D] = sum[p];
+  for (int p = 0; p < NP8; ++p) Lq[at0 + at(p)] = sum[p];
   if (zrow) *zq = zsum;
   if (planes != nullptr) {
     // planes[bh][plane][j][i]: thread (j, eighth) writes 8 consecutive key features i of value feature j
-    const int j = tid >> 3, i0 = 8 * (tid & 7);
-    uint32_t hw[4], lw[4];
 #pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const float v0 = tile[(i0 + 2 * q) * LSTR + j], v1 = tile[(i0 + 2 * q + 1) * LSTR + j];
-      const bf16_t h0 = f32_to_bf16(v0), h1 = f32_to_bf16(v1);
-      hw[q] = (uint32_t)h0 | ((uint32_t)h1 << 16);
-      lw[q] = (uint32_t)f32_to_bf16(v0 - bf16_to_f32(h0)) | ((uint32_t)f32_to_bf16(v1 - bf16_to_f32(h1)) << 16);
+    for (int v = 0; v < NV; ++v) {
+      const int j = 64 * v + (tid >> 3), i0 = 8 * (tid & 7);
+      uint32_t hw[4], lw[4];
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        const float v0 = tile[(i0 + 2 * q) * LSTR + j], v1 = tile[(i0 + 2 * q + 1) * LSTR + j];
+        const bf16_t h0 = f32_to_bf16(v0), h1 = f32_to_bf16(v1);
+        hw[q] = (uint32_t)h0 | ((uint32_t)h1 << 16);
+        lw[q] = (uint32_t)f32_to_bf16(v0 - bf16_to_f32(h0)) | ((uint32_t)f32_to_bf16(v1 - bf16_to_f32(h1)) << 16);
+      }
+      bf16_t* hi = planes + (size_t)bh * 2 * D * D + (size_t)(64 * qb + j) * D + 64 * qa + i0;
+      *reinterpret_cast<uint4*>(hi) = make_uint4(hw[0], hw[1], hw[2], hw[3]);
+      *reinterpret_cast<uint4*>(hi + D * D) = make_uint4(lw[0], lw[1], lw[2], lw[3]);
     }
-    bf16_t* hi = planes + (size_t)bh * 2 * D * D + (size_t)(64 * qb + j) * D + 64 * qa + i0;
-    *reinterpret_cast<uint4*>(hi) = make_uint4(hw[0], hw[1], hw[2], hw[3]);
-    *reinterpret_cast<uint4*>(hi + D * D) = make_uint4(lw[0], lw[1], lw[2], lw[3]);
   }
 }
 
-// state += sum over slices of the partials; one thread per 4 consecutive floats of a partial.
-// planes != NULL: the updated L also leaves as the two transposed bf16 planes (high part and remainder,
-// planes[bh][plane][j][i]) that the attention kernel's history epilogue multiplies with: the conversion rides
-// in the kernel that produces the state instead of running as a launch of its own before every attention call.
-__global__ __launch_bounds__(256) void absorb_reduce_kernel(float* __restrict__ state,
-                                                            const float* __restrict__ partials, int slices,
-                                                            int BH, bf16_t* __restrict__ planes) {
-  __shared__ float tile[8][D + 1];   // the block's 8 rows of L, for the transposed write
-  const int e4 = blockIdx.x * 256 + threadIdx.x;  // float4 index inside a partial
-  const int bh = blockIdx.y;
-  if (e4 >= PART / 4) return;   // (only in the block of z, which takes no part in the planes)
-  const float4* p = reinterpret_cast<const float4*>(partials + (size_t)bh * slices * PART) + e4;
-  float4 s = make_float4(0.f, 0.f, 0.f, 0.f);
-  int sl = 0;
-  for (; sl + 3 < slices; sl += 4) {  // four independent loads in flight
-    const float4 a = p[(size_t)sl * (PART / 4)], b = p[(size_t)(sl + 1) * (PART / 4)];
-    const float4 c = p[(size_t)(sl + 2) * (PART / 4)], d = p[(size_t)(sl + 3) * (PART / 4)];
-    s.x += (a.x + b.x) + (c.x + d.x);
-    s.y += (a.y + b.y) + (c.y + d.y);
-    s.z += (a.z + b.z) + (c.z + d.z);
-    s.w += (a.w + b.w) + (c.w + d.w);
-  }
-  for (; sl < slices; ++sl) {
-    const float4 a = p[(size_t)sl * (PART / 4)];
-    s.x += a.x; s.y += a.y; s.z += a.z; s.w += a.w;
-  }
-  const int e = 4 * e4;
-  float* dst = e < D * D ? state + (size_t)bh * D * D + e : state + (size_t)BH * D * D + (size_t)bh * D + (e - D * D);
-  float4 cur = *reinterpret_cast<float4*>(dst);
-  cur.x += s.x; cur.y += s.y; cur.z += s.z; cur.w += s.w;
-  *reinterpret_cast<float4*>(dst) = cur;
-  if (planes == nullptr || e >= D * D) return;   // uniform over a block: a block holds 8 whole rows of L, or z
-  {
-    const int r = threadIdx.x >> 5, c0 = 4 * (threadIdx.x & 31);
-    tile[r][c0] = cur.x; tile[r][c0 + 1] = cur.y; tile[r][c0 + 2] = cur.z; tile[r][c0 + 3] = cur.w;
-  }
-  __syncthreads();
-  const int j = threadIdx.x & (D - 1), half = threadIdx.x >> 7;   // column j, rows 4 half .. + 4 of the block
-  const int i0 = 8 * blockIdx.x + 4 * half;
-  uint32_t hw[2], lw[2];
-#pragma unroll
-  for (int q = 0; q < 2; ++q) {
-    const float v0 = tile[4 * half + 2 * q][j], v1 = tile[4 * half + 2 * q + 1][j];
-    const bf16_t h0 = f32_to_bf16(v0), h1 = f32_to_bf16(v1);
-    hw[q] = (uint32_t)h0 | ((uint32_t)h1 << 16);
-    lw[q] = (uint32_t)f32_to_bf16(v0 - bf16_to_f32(h0)) | ((uint32_t)f32_to_bf16(v1 - bf16_to_f32(h1)) << 16);
-  }
-  bf16_t* hi = planes + (size_t)bh * 2 * D * D + (size_t)j * D + i0;
-  *reinterpret_cast<uint2*>(hi) = make_uint2(hw[0], hw[1]);
-  *reinterpret_cast<uint2*>(hi + D * D) = make_uint2(lw[0], lw[1]);
-}
-
-// slice length (a multiple of the 64-token chunk) and slice count for n tokens: the register-staged kernel
-void slice_plan(int BH, int n, bool with_workspace, int& per, int& slices) {
-  if (with_workspace) {
-    // one run (320 tokens) per workgroup until there are ~4 workgroups per compute unit, then longer slices
-    const int max_slices = (1024 + BH - 1) / BH;
-    per = RUN;
-    if ((n + per - 1) / per > max_slices) per = ((n + max_slices - 1) / max_slices + RUN - 1) / RUN * RUN;
-  } else {
-    // atomics: fewer, longer slices (the atomic traffic is slices x state size)
-    const int max_slices = (160 + BH - 1) / BH;
-    per = (((n + max_slices - 1) / max_slices) + CH - 1) / CH * CH;
-    if (per < 2 * CH) per = 2 * CH;
-  }
+// without a workspace (atomics): few, long slices, multiples of the 64-token chunk (the atomic traffic is slices x state size)
+void slice_plan(int BH, int n, int& per, int& slices) {
+  const int max_slices = (160 + BH - 1) / BH;
+  per = (((n + max_slices - 1) / max_slices) + CH - 1) / CH * CH;
+  if (per < 2 * CH) per = 2 * CH;
   slices = (n + per - 1) / per;
-}
-
-// With a workspace the slices may be longer than that (never shorter: the workspace is sized for the plan above).  A compute unit
-// holds one workgroup, so a launch takes its rounds of 256 times a run's time per run of a slice and 0.85 of one for what surrounds
-// them: r runs a slice, the r of the least rounds * (r + 0.85).  (Fitted to 12 heads, 23400 rotated tokens: 83 us with one run
-// and four rounds, 70 with 2 and 2, 86 with 3 and 2, 63 with 4 and 1.)  12 heads x 9360: 39.6 -> 33.0 us, 40 x 4680 60.7 -> 48.0.
-void long_slices(int BH, int n, int& per, int& slices) {
-  const int r0 = per / RUN;
-  long long best = -1;
-  for (int r = r0; r < r0 + 64; ++r) {
-    const int sl = (n + r * RUN - 1) / (r * RUN);
-    const long long wgs = (long long)BH * sl, cost = (wgs > 1024 ? wgs * 100 / 256 : (wgs + 255) / 256 * 100) * (20 * r + 17);
-    if (best < 0 || cost < best) {   // (longer ones where that is a tenth or more: 40 heads x 54000, 0.95 of it, ran 4 % slower)
-      best = best < 0 ? cost * 9 / 10 : cost;
-      per = r * RUN;
-      slices = sl;
-    }
-    if (sl == 1) break;
-  }
 }
 
 // the quadrant kernel: about one workgroup per compute unit (4 quadrants x BH heads x slices ~ 256), slices of whole tiles
 struct QuadPlan {
   int per, slices;
+  int nv;   // 1: quadrants of L, 2: halves
   size_t counters_bytes, total_bytes;
 };
-QuadPlan quad_plan(int BH, int n, int want_slices) {
+QuadPlan plan_of(int BH, int n, int nv, int sl) {
   const int tiles = (n + 2 * QT - 1) / (2 * QT);   // pairs of tiles
-  int sl = want_slices > 0 ? want_slices : (256 + 2 * BH) / (QUADS * BH);
   if (sl < 1) sl = 1;
   if (sl > tiles) sl = tiles;
   if (sl > 4096) sl = 4096;   // the arrival counter holds 16 bits
   QuadPlan p;
+  p.nv = nv;
   p.per = (tiles + sl - 1) / sl * (2 * QT);
   p.slices = (n + p.per - 1) / p.per;
-  p.counters_bytes = ((size_t)BH * QUADS * sizeof(unsigned long long) + 255) & ~(size_t)255;
+  p.counters_bytes = ((size_t)BH * 4 * sizeof(unsigned long long) + 255) & ~(size_t)255;
   p.total_bytes = p.counters_bytes + (size_t)BH * p.slices * PART * sizeof(float);
   return p;
+}
+QuadPlan quad_plan(int BH, int n) { return plan_of(BH, n, 1, (256 + 2 * BH) / (4 * BH)); }
+// Rotated or ELU + 1 keys.  A compute unit holds one workgroup of rotated keys.  In a quadrant every key is transformed twice and every
+// row of the tables read by two workgroups; a half does both once and has twice the partials to add at its end.  Modelled in us,
+// rounds x (pairs of tiles a slice x 0.58 or 0.85 + 4.5) + 0.2 or 0.5 a slice; fitted to 12 heads x 4680 rotated tokens, quadrants /
+// halves 16.9 / 19.7 us, x 23400 50.7 / 43.2, 3 x 9000 15.9 / 22.1, 40 x 10800 98 / 58.  Against register-staged tiles and a launch
+// that adds the partials: 12 x 4680 23.4 -> 18.4 us, x 23400 64 -> 47 (ELU 57 -> 39), 2 x 321 14.6 -> 8.9, 256 x 6000 328 -> 202;
+// what a pair costs is the issue of some 150 instructions a wavefront, two wavefronts a SIMD.
+QuadPlan map_plan(int BH, int n) {
+  const int tiles = (n + 2 * QT - 1) / (2 * QT);
+  int best_nv = 1, best_sl = 1;
+  double least = 1e300;
+  for (int nv = 1; nv <= 2; ++nv)
+    for (int sl = 1; sl <= tiles && sl <= 128; ++sl) {
+      const int pairs = (tiles + sl - 1) / sl, used = (tiles + pairs - 1) / pairs;
+      const double rounds = (double)(((long long)BH * used * (4 / nv) + 255) / 256);
+      const double cost = rounds * (pairs * (nv == 1 ? 0.58 : 0.85) + 4.5) + used * (nv == 1 ? 0.2 : 0.5);
+      if (cost < least) { least = cost; best_nv = nv; best_sl = used; }
+    }
+  return plan_of(BH, n, best_nv, best_sl);
 }
 
 }  // namespace
 
 size_t absorb_mfma_workspace_bytes(const hf_config& c, int n) {
-  int per, slices;   // whichever kernel runs: the larger of the two plans
-  slice_plan(c.batch * c.heads, n, true, per, slices);
-  const size_t staged = (size_t)c.batch * c.heads * slices * PART * sizeof(float);
-  const size_t quad = quad_plan(c.batch * c.heads, n, 0).total_bytes;
-  return staged > quad ? staged : quad;
+  // A partial per 320 tokens, up to about four per compute unit and no shorter slices beyond: the size that callers have kept since
+  // slices were cut so.  Both plans are nearly always smaller; whichever runs has to fit.
+  const int BH = c.batch * c.heads, most = (1024 + BH - 1) / BH;
+  int per = RUN;
+  if ((n + per - 1) / per > most) per = ((n + most - 1) / most + RUN - 1) / RUN * RUN;
+  const size_t cut = (size_t)BH * ((n + per - 1) / per) * PART * sizeof(float);
+  const size_t quad = quad_plan(BH, n).total_bytes, map = map_plan(BH, n).total_bytes;
+  const size_t plan = quad > map ? quad : map;
+  return cut > plan ? cut : plan;
 }
 
-// ReLU without rotation, workspace given: one launch.  want_slices / ring: 0 = the plan's choice (other values:
-// tuning runs of a development harness)
-int launch_absorb_quad(const hf_config& c, float* state, const void* K, const void* V, int n, int head_stride,
-                       void* workspace, hipStream_t s, void* planes_out, int want_slices, int ring) {
+// workspace given: one launch
+static int launch_absorb_quad(const hf_config& c, float* state, const void* K, const void* V, int n, int head_stride,
+                              const float* cosv, const float* sinv, void* workspace, hipStream_t s, void* planes_out) {
   const int BH = c.batch * c.heads;
-  const QuadPlan p = quad_plan(BH, n, want_slices);
+  const int map = (cosv ? 2 : 0) + (c.phi != HF_PHI_RELU ? 1 : 0);
+  const QuadPlan p = map ? map_plan(BH, n) : quad_plan(BH, n);
   const int items = BH * p.slices;
-  const dim3 grid(8 * QUADS * ((items + 7) / 8));
-  // four slots of 64 tokens (64 KB of LDS, three in flight per workgroup) measured as fast as eight and leave
-  // room for a second workgroup per compute unit
-  const bool deep = ring >= 8;
+  const dim3 grid(8 * (4 / p.nv) * ((items + 7) / 8));
   unsigned long long* counters = static_cast<unsigned long long*>(workspace);
   float* partials = reinterpret_cast<float*>(static_cast<char*>(workspace) + p.counters_bytes);
   const unsigned long long tag = next_call_tag();
-#define HF_LAUNCH_QUAD(RING)                                                                                       \
+#define HF_LAUNCH_QUAD(RING, MAP, NV)                                                                                  \
   do {                                                                                                             \
     static LdsGrant grant;                                                                                         \
-    constexpr int lds = RING * QSLOT;                                                                              \
-    const int rc = grant_lds(grant, reinterpret_cast<const void*>(absorb_quad_kernel<RING>), lds, "the absorb kernel"); \
+    constexpr int lds = RING * slot_bytes(NV, MAP);                                                               \
+    const int rc = grant_lds(grant, reinterpret_cast<const void*>(absorb_quad_kernel<RING, MAP, NV>), lds, "the absorb kernel"); \
     if (rc != HF_OK) return rc;                                                                                    \
-    hipLaunchKernelGGL((absorb_quad_kernel<RING>), grid, dim3(QNT), lds, s, state, static_cast<bf16_t*>(planes_out), \
+    hipLaunchKernelGGL((absorb_quad_kernel<RING, MAP, NV>), grid, dim3(QNT), lds, s, state, static_cast<bf16_t*>(planes_out), \
                        counters, partials, static_cast<const bf16_t*>(K), static_cast<const bf16_t*>(V), n,        \
-                       head_stride, p.per, p.slices, BH, tag);                                                              \
+                       head_stride, p.per, p.slices, BH, tag, cosv, sinv);                                  \
   } while (0)
-  if (deep) HF_LAUNCH_QUAD(8); else HF_LAUNCH_QUAD(4);
+  // four slots (three in flight per workgroup); eight were no faster without tables, and with both halves of V and the tables
+  // three are what fits
+  if (map == 0) HF_LAUNCH_QUAD(4, 0, 1);
+  else if (p.nv == 1) {
+    if (map == 1) HF_LAUNCH_QUAD(4, 1, 1); else if (map == 2) HF_LAUNCH_QUAD(4, 2, 1); else HF_LAUNCH_QUAD(4, 3, 1);
+  } else {
+    if (map == 1) HF_LAUNCH_QUAD(4, 1, 2); else if (map == 2) HF_LAUNCH_QUAD(3, 2, 2); else HF_LAUNCH_QUAD(3, 3, 2);
+  }
 #undef HF_LAUNCH_QUAD
   return check_launch("hf_absorb_evicted");
 }
@@ -702,30 +780,23 @@ int launch_absorb_mfma(const hf_config& c, float* state, const void* K, const vo
                        hipStream_t s, void* planes_out) {
   const int BH = c.batch * c.heads;
   bf16_t* planes = static_cast<bf16_t*>(planes_out);   // NULL: the state alone
-  const bool use_ws = workspace != nullptr && workspace_bytes >= absorb_mfma_workspace_bytes(c, n);
-  const bool plain = (c.phi == HF_PHI_RELU) && cosv == nullptr;
-  if (plain && use_ws) return launch_absorb_quad(c, state, K, V, n, head_stride, workspace, s, planes_out, 0, 0);
+  if (workspace != nullptr && workspace_bytes >= absorb_mfma_workspace_bytes(c, n))
+    return launch_absorb_quad(c, state, K, V, n, head_stride, cosv, sinv, workspace, s, planes_out);
   int per, slices;
-  slice_plan(BH, n, use_ws, per, slices);
-  if (use_ws) long_slices(BH, n, per, slices);
-  float* partials = use_ws ? static_cast<float*>(workspace) : nullptr;
+  slice_plan(BH, n, per, slices);
   const bf16_t* Kp = static_cast<const bf16_t*>(K);
   const bf16_t* Vp = static_cast<const bf16_t*>(V);
-  const int heads_per_xcd = (BH + 7) / 8;
-  const dim3 grid(use_ws ? BH * slices : 8 * heads_per_xcd * slices);
-  if (plain) {
-    hipLaunchKernelGGL((absorb_mfma_kernel<true>), grid, dim3(NT), 0, s, state, partials, Kp, Vp, n, head_stride, per, cosv,
-                       sinv, c.phi, BH, slices);
+  const dim3 grid(8 * ((BH + 7) / 8) * slices);
+  if (c.phi == HF_PHI_RELU && cosv == nullptr) {
+    hipLaunchKernelGGL((absorb_mfma_kernel<true>), grid, dim3(NT), 0, s, state, Kp, Vp, n, head_stride, per, cosv, sinv, c.phi,
+                       BH, slices);
   } else {
-    hipLaunchKernelGGL((absorb_mfma_kernel<false>), grid, dim3(NT), 0, s, state, partials, Kp, Vp, n, head_stride, per, cosv,
-                       sinv, c.phi, BH, slices);
+    hipLaunchKernelGGL((absorb_mfma_kernel<false>), grid, dim3(NT), 0, s, state, Kp, Vp, n, head_stride, per, cosv, sinv, c.phi,
+                       BH, slices);
   }
   const int rc = check_launch("hf_absorb_evicted");
   if (rc != HF_OK) return rc;
-  if (!use_ws) return planes ? launch_state_planes(c, state, planes, s) : HF_OK;   // (atomics: no reduce kernel)
-  hipLaunchKernelGGL(absorb_reduce_kernel, dim3((PART / 4 + 255) / 256, BH), dim3(256), 0, s, state, partials,
-                     slices, BH, planes);
-  return check_launch("hf_absorb_evicted(reduce)");
+  return planes ? launch_state_planes(c, state, planes, s) : HF_OK;   // (atomics: nobody comes last)
 }
 
 }  // namespace hf
