@@ -580,7 +580,7 @@ __device__ __forceinline__ void absorb_role(char* smem, const AbsorbArgs& ab) {
           const float v0 = sum[8 * half + 2 * q], v1 = sum[8 * half + 2 * q + 1];
           const bf16_t h0 = f32_to_bf16(v0), h1 = f32_to_bf16(v1);
           hw[q] = (uint32_t)h0 | ((uint32_t)h1 << 16);
-          lw[q] = (uint32_t)f32_to_bf16(v0 - bf16_to_f32(h0)) | ((uint32_t)f32_to_bf16(v1 - bf16_to_f32(h1)) << 16);
+          lw[q] = pack_bf16(v0 - bf16_to_f32(h0), v1 - bf16_to_f32(h1));
         }
         bf16_t* hi = ab.planes_out + (size_t)bh * 2 * D * D + (size_t)j * D + i0 + 8 * half;
         *reinterpret_cast<uint4*>(hi) = make_uint4(hw[0], hw[1], hw[2], hw[3]);
@@ -966,7 +966,7 @@ __global__ __launch_bounds__(64 * NW * KS, 2) void attn_mfma_kernel(
       for (int u = 0; u < UB; ++u) {
         uint32_t w[4];
 #pragma unroll
-        for (int e = 0; e < 4; ++e) w[e] = (uint32_t)f32_to_bf16(x[u][2 * e]) | ((uint32_t)f32_to_bf16(x[u][2 * e + 1]) << 16);
+        for (int e = 0; e < 4; ++e) w[e] = pack_bf16(x[u][2 * e], x[u][2 * e + 1]);
         *reinterpret_cast<uint4*>(dst + (((u0 + ub + u) ^ (j & 15)) * 16)) = make_uint4(w[0], w[1], w[2], w[3]);
       }
     }
@@ -1058,8 +1058,8 @@ __global__ __launch_bounds__(64 * NW * KS, 2) void attn_mfma_kernel(
 #pragma unroll
       for (int rq = 0; rq < 4; ++rq) {
         uint2 w;
-        w.x = (uint32_t)f32_to_bf16(o[i][4 * rq]) | ((uint32_t)f32_to_bf16(o[i][4 * rq + 1]) << 16);
-        w.y = (uint32_t)f32_to_bf16(o[i][4 * rq + 2]) | ((uint32_t)f32_to_bf16(o[i][4 * rq + 3]) << 16);
+        w.x = pack_bf16(o[i][4 * rq], o[i][4 * rq + 1]);
+        w.y = pack_bf16(o[i][4 * rq + 2], o[i][4 * rq + 3]);
         *reinterpret_cast<uint2*>(stage + (32 * wave + l32) * OSTR + (32 * (dt0 + i) + 8 * rq + 4 * h) * 2) = w;
       }
     __syncthreads();

@@ -295,8 +295,8 @@ __global__ __launch_bounds__(64, 1) void attn_w64_kernel(
 #pragma unroll
       for (int rq = 0; rq < 4; ++rq) {
         uint2 w;
-        w.x = (uint32_t)f32_to_bf16(o[dt][qt][4 * rq] * inv) | ((uint32_t)f32_to_bf16(o[dt][qt][4 * rq + 1] * inv) << 16);
-        w.y = (uint32_t)f32_to_bf16(o[dt][qt][4 * rq + 2] * inv) | ((uint32_t)f32_to_bf16(o[dt][qt][4 * rq + 3] * inv) << 16);
+        w.x = pack_bf16(o[dt][qt][4 * rq] * inv, o[dt][qt][4 * rq + 1] * inv);
+        w.y = pack_bf16(o[dt][qt][4 * rq + 2] * inv, o[dt][qt][4 * rq + 3] * inv);
         *reinterpret_cast<uint2*>(stage + (32 * qt + l32) * OSTR + (32 * dt + 8 * rq + 4 * h) * 2) = w;
       }
   }

@@ -150,8 +150,8 @@ __device__ __forceinline__ void stage_rows(char* stage, int row, int h, const f3
 #pragma unroll
     for (int rq = 0; rq < 4; ++rq) {
       uint2 w;
-      w.x = (uint32_t)f32_to_bf16(acc[dt][4 * rq] * mul) | ((uint32_t)f32_to_bf16(acc[dt][4 * rq + 1] * mul) << 16);
-      w.y = (uint32_t)f32_to_bf16(acc[dt][4 * rq + 2] * mul) | ((uint32_t)f32_to_bf16(acc[dt][4 * rq + 3] * mul) << 16);
+      w.x = pack_bf16(acc[dt][4 * rq] * mul, acc[dt][4 * rq + 1] * mul);
+      w.y = pack_bf16(acc[dt][4 * rq + 2] * mul, acc[dt][4 * rq + 3] * mul);
       *reinterpret_cast<uint2*>(stage + row * OSTR + (32 * dt + 8 * rq + 4 * h) * 2) = w;
     }
 }

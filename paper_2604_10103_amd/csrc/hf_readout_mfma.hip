@@ -152,7 +152,7 @@ __global__ __launch_bounds__(256) void readout_mfma_kernel(
       for (int p = 0; p < 4; ++p) {
         const float a = __uint_as_float(w[p] << 16) + hh[2 * p];
         const float b = __uint_as_float(w[p] & 0xffff0000u) + hh[2 * p + 1];
-        out[p] = (uint32_t)f32_to_bf16(a) | ((uint32_t)f32_to_bf16(b) << 16);
+        out[p] = pack_bf16(a, b);
       }
       *reinterpret_cast<uint4*>(Oh + (size_t)(row0 + r) * D + col * 8) = make_uint4(out[0], out[1], out[2], out[3]);
     }

@@ -154,7 +154,7 @@ __global__ __launch_bounds__(NT, 1) void absorb_mfma_kernel(float* __restrict__ 
             z_run[2 * q] += f0;
             z_run[2 * q + 1] += f1;
             const float r0 = f0 * cc[q] - f1 * ss[q], r1 = f0 * ss[q] + f1 * cc[q];
-            kw[u][q] = (uint32_t)f32_to_bf16(r0) | ((uint32_t)f32_to_bf16(r1) << 16);
+            kw[u][q] = pack_bf16(r0, r1);
           }
         }
       }
@@ -671,7 +671,7 @@ __global__ __launch_bounds__(QNT) void absorb_quad_kernel(float* __restrict__ st
         const float v0 = tile[(i0 + 2 * q) * LSTR + j], v1 = tile[(i0 + 2 * q + 1) * LSTR + j];
         const bf16_t h0 = f32_to_bf16(v0), h1 = f32_to_bf16(v1);
         hw[q] = (uint32_t)h0 | ((uint32_t)h1 << 16);
-        lw[q] = (uint32_t)f32_to_bf16(v0 - bf16_to_f32(h0)) | ((uint32_t)f32_to_bf16(v1 - bf16_to_f32(h1)) << 16);
+        lw[q] = pack_bf16(v0 - bf16_to_f32(h0), v1 - bf16_to_f32(h1));
       }
       bf16_t* hi = planes + (size_t)bh * 2 * D * D + (size_t)(64 * qb + j) * D + 64 * qa + i0;
       *reinterpret_cast<uint4*>(hi) = make_uint4(hw[0], hw[1], hw[2], hw[3]);
