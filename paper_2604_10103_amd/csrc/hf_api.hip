@@ -816,6 +816,52 @@ static int step_one_launch(const hf_config* cfg, const void* Q, const void* Q_hi
                                 nullptr, kbar, block_idx, nullptr, pool_first, pool_end);
 }
 
+// The same for small fp32 streams (attn_wide_step_supported), whose kernel takes the fp32 state as it is.  ev: the chunk that the
+// launch absorbs into state_out beside the attention, or NULL.
+struct StepAbsorb {
+  const void *K, *V;
+  int n, stride;
+  const float *cos, *sin;
+  float* state_out;
+};
+static int step_wide_launch(const hf_config* cfg, const void* Q, const void* Q_hist, int32_t n_q, const void* K, const void* V,
+                            int32_t n_kv, int kv_first, int kv_end, int32_t* block_idx, const void* state_or_null,
+                            const float* rope_cos_q, const float* rope_sin_q, void* O, void* workspace, size_t workspace_bytes,
+                            void* stream, const StepAbsorb* ev, bool* done) {
+  *done = false;
+  if (!attn_wide_step_supported(*cfg, n_q, n_kv) || (ev && !attn_wide_step_absorbs(ev->n))) return HF_OK;
+  int k = 0;
+  HF_TRY(check_select_args(cfg, Q, n_q, K, n_kv, 0, block_idx, nullptr, &k));
+  HF_TRY(check_ptr(V, "V_win", true));
+  HF_TRY(check_ptr(O, "O", true));
+  if (!Q_hist) Q_hist = Q;
+  HF_TRY(check_ptr(Q_hist, "Q_hist", true));
+  HF_TRY(check_ptr(state_or_null, "state", false));
+  if (O == Q || O == Q_hist || O == K || O == V) { set_error("O must not alias an input"); return HF_ERR_SHAPE; }
+  if ((rope_cos_q == nullptr) != (rope_sin_q == nullptr)) {
+    set_error("rope_cos_q and rope_sin_q must both be given or both be NULL");
+    return HF_ERR_NULL;
+  }
+  HF_TRY(check_ptr(rope_cos_q, "rope_cos_q", false));
+  HF_TRY(check_ptr(rope_sin_q, "rope_sin_q", false));
+  const WorkspaceLayout w = workspace_layout(cfg, n_q, n_kv);
+  if (!workspace || workspace_bytes < w.total) {
+    set_error("workspace of %zu bytes needed, %zu given", w.total, workspace ? workspace_bytes : (size_t)0);
+    return HF_ERR_WORKSPACE;
+  }
+  if (reinterpret_cast<uintptr_t>(workspace) & 255u) { set_error("workspace is not 256-byte aligned"); return HF_ERR_ALIGN; }
+  float* kbar = reinterpret_cast<float*>(static_cast<char*>(workspace) + w.kbar);
+  hipStream_t s = static_cast<hipStream_t>(stream);
+  const bool own = attn_wide_step_pools(*cfg, kv_first, kv_end);
+  if (!own) HF_TRY(launch_pool_both(*cfg, nullptr, 0, 0, K, n_kv, cdiv(n_kv, cfg->block_kv), kv_first, kv_end, nullptr, kbar, s));
+  *done = true;
+  const StepAbsorb none = {};
+  const StepAbsorb& a = ev ? *ev : none;
+  return launch_attn_wide_step(*cfg, Q, Q_hist, n_q, K, V, n_kv, k, static_cast<const float*>(state_or_null), rope_cos_q, rope_sin_q,
+                               kbar, block_idx, own ? kv_first : 0, own ? kv_end : 0, O, a.K, a.V, a.n, a.stride, a.cos, a.sin,
+                               a.state_out, s);
+}
+
 int hf_stream_step(const hf_config* cfg, const hf_window* win, const void* Q, const void* Q_hist, int32_t n_q,
                    const void* K_win, const void* V_win, int32_t step_in_chunk, int32_t* block_idx,
                    const void* state_or_null, const float* rope_cos_q, const float* rope_sin_q, void* O,
@@ -835,6 +881,9 @@ int hf_stream_step(const hf_config* cfg, const hf_window* win, const void* Q, co
   bool done = false;
   HF_TRY(step_one_launch(cfg, Q, Q_hist, n_q, K_win, V_win, n_kv, reuse, cdiv(n_kv, cfg->block_kv), step_in_chunk, block_idx,
                          state_or_null, rope_cos_q, rope_sin_q, O, workspace, workspace_bytes, stream, &done));
+  if (done) return HF_OK;
+  HF_TRY(step_wide_launch(cfg, Q, Q_hist, n_q, K_win, V_win, n_kv, reuse, cdiv(n_kv, cfg->block_kv), block_idx, state_or_null,
+                          rope_cos_q, rope_sin_q, O, workspace, workspace_bytes, stream, nullptr, &done));
   if (done) return HF_OK;
   HF_TRY(hf_block_select_cached(cfg, Q, n_q, K_win, n_kv, reuse, block_idx, nullptr, workspace, workspace_bytes,
                                 stream));
@@ -913,6 +962,15 @@ int hf_ring_open_chunk(const hf_config* cfg, hf_ring* ring, void* K_cache, void*
   return HF_OK;
 }
 
+// the KV blocks that a step pools: all on the chunk's first, then those that touch the chunk's own slot
+struct RingBlocks { int first, end; };
+static RingBlocks ring_blocks(const hf_config* cfg, const hf_ring* ring, int32_t step_in_chunk, int32_t n_kv) {
+  const int t_n = cdiv(n_kv, cfg->block_kv), first = ring->n_sink + ring->cur_slot * ring->n_chunk;
+  if (step_in_chunk <= 0) return {0, t_n};
+  const int end = cdiv(first + ring->n_chunk, cfg->block_kv);
+  return {first / cfg->block_kv, end > t_n ? t_n : end};
+}
+
 int hf_ring_step(const hf_config* cfg, const hf_ring* ring, const void* Q, const void* Q_hist, const void* K_cache,
                  const void* V_cache, int32_t step_in_chunk, int32_t* block_idx, const void* state_or_null,
                  const float* rope_cos_q, const float* rope_sin_q, void* O, void* workspace, size_t workspace_bytes,
@@ -930,18 +988,14 @@ int hf_ring_step(const hf_config* cfg, const hf_ring* ring, const void* Q, const
     return HF_ERR_WORKSPACE;
   }
   if (reinterpret_cast<uintptr_t>(workspace) & 255u) { set_error("workspace is not 256-byte aligned"); return HF_ERR_ALIGN; }
-  // after the chunk's first step only the KV blocks that touch the chunk's own slot are pooled again
-  const int t_n = cdiv(n_kv, cfg->block_kv);
-  const int first = ring->n_sink + ring->cur_slot * ring->n_chunk;
-  int kv_first = 0, kv_end = t_n;
-  if (step_in_chunk > 0) {
-    kv_first = first / cfg->block_kv;
-    kv_end = cdiv(first + ring->n_chunk, cfg->block_kv);
-    if (kv_end > t_n) kv_end = t_n;
-  }
+  const RingBlocks blk = ring_blocks(cfg, ring, step_in_chunk, n_kv);
+  const int kv_first = blk.first, kv_end = blk.end;
   bool done = false;
   HF_TRY(step_one_launch(cfg, Q, Q_hist, n_q, K_cache, V_cache, n_kv, kv_first, kv_end, step_in_chunk, block_idx,
                          state_or_null, rope_cos_q, rope_sin_q, O, workspace, workspace_bytes, stream, &done));
+  if (done) return HF_OK;
+  HF_TRY(step_wide_launch(cfg, Q, Q_hist, n_q, K_cache, V_cache, n_kv, kv_first, kv_end, block_idx, state_or_null, rope_cos_q,
+                          rope_sin_q, O, workspace, workspace_bytes, stream, nullptr, &done));
   if (done) return HF_OK;
   char* ws = static_cast<char*>(workspace);
   HF_TRY(select_launches(cfg, Q, n_q, K_cache, n_kv, kv_first, k, block_idx, nullptr, reinterpret_cast<float*>(ws + w.qbar),
@@ -1010,13 +1064,8 @@ int hf_ring_last_step(const hf_config* cfg, hf_ring* ring, const void* Q, const 
     if (reinterpret_cast<uintptr_t>(workspace) & 255u) { set_error("workspace is not 256-byte aligned"); return HF_ERR_ALIGN; }
     char* ws = static_cast<char*>(workspace);
     float* kbar = reinterpret_cast<float*>(ws + w.kbar);
-    const int first = ring->n_sink + ring->cur_slot * ring->n_chunk;
-    int kv_first = 0, kv_end = t_n;
-    if (step_in_chunk > 0) {
-      kv_first = first / cfg->block_kv;
-      kv_end = cdiv(first + ring->n_chunk, cfg->block_kv);
-      if (kv_end > t_n) kv_end = t_n;
-    }
+    const RingBlocks blk = ring_blocks(cfg, ring, step_in_chunk, n_kv);
+    const int kv_first = blk.first, kv_end = blk.end;
     // (argument checks of the fused call first: nothing is launched if it is going to refuse)
     const size_t need = step_absorb_workspace_bytes(*cfg, n_q, ring->n_chunk);
     if (!step_workspace || step_workspace_bytes < need) {
@@ -1032,6 +1081,18 @@ int hf_ring_last_step(const hf_config* cfg, hf_ring* ring, const void* Q, const 
                             ring->n_chunk, cfg->kv_capacity, state_out, nullptr, step_workspace, step_workspace_bytes, stream,
                             pools_itself ? kv_first : 0, pools_itself ? kv_end : 0));
   } else {
+    // small fp32 streams: the step's launch with the absorbing workgroups
+    const RingBlocks blk = ring_blocks(cfg, ring, step_in_chunk, n_kv);
+    const StepAbsorb ev = {K_ev, V_ev, ring->n_chunk, cfg->kv_capacity, rope_cos_ev, rope_sin_ev, static_cast<float*>(state_out)};
+    bool done = false;
+    if (step_in_chunk < 0) { set_error("step_in_chunk must be >= 0"); return HF_ERR_SHAPE; }
+    HF_TRY(step_wide_launch(cfg, Q, Q_hist, n_q, K_cache, V_cache, n_kv, blk.first, blk.end, block_idx, state_or_null, rope_cos_q,
+                            rope_sin_q, O, workspace, workspace_bytes, stream, &ev, &done));
+    if (done) {
+      ring->absorbed_ahead = 1;
+      if (absorbed_out) *absorbed_out = 1;
+      return HF_OK;
+    }
     HF_TRY(hf_ring_step(cfg, ring, Q, Q_hist, K_cache, V_cache, step_in_chunk, block_idx, state_or_null, rope_cos_q,
                         rope_sin_q, O, workspace, workspace_bytes, stream));
     HF_TRY(launch_absorb_into(*cfg, static_cast<const float*>(state_or_null), static_cast<float*>(state_out), K_ev, V_ev,

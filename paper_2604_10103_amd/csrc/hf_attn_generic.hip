@@ -15,7 +15,8 @@
 
 #include <type_traits>
 
-#include "hf_f32_mfma.h"
+#include "hf_absorb_wide.h"
+#include "hf_pool.h"
 
 namespace hf {
 
@@ -23,21 +24,139 @@ namespace {
 
 constexpr int kTile = 16;    // keys per tile
 
-template <typename T, int D, int NQ, int KS>
-__global__ __launch_bounds__(256, 2) void attn_wide_kernel(const T* __restrict__ Q, const T* __restrict__ K,
+// What rides in the launch of a small stream's step: every workgroup selects the blocks of its rows itself, and workgroups of
+// their own absorb another chunk into another state buffer.  Each of these is at the cost of a launch otherwise, and eight
+// wavefronts share sixteen rows here instead of four.  A chunk, separate launches / this one: 2 heads of 64, 64 queries x 256 keys, blocks
+// of 16, two steps 24.2 -> 20.3 us, 4 heads, 768 x 3072, half of the blocks, two steps 87 -> 63, 8 heads of 128, 512 x 1536, four steps
+// 109 -> 102.  (What the history term reads, requested with the first keys: 1 us a step slower, the loop's keys are awaited behind
+// it; the values with the first keys and a wavefront's blocks together: no difference.)
+struct WideStep {
+  float* kbar_t;          // [BH][D/4][T_n][4] pooled keys; those of the blocks [kv_first, kv_end) are formed here and stored
+  int32_t* idx_out;       // [BH][T_m][k]
+  int kv_first, kv_end;
+  const void *K_ev, *V_ev;
+  int n_ev, ev_stride;
+  const float *cos_ev, *sin_ev, *state_in;
+  float* state_out;
+  int role_blocks, BH;    // the first workgroup ids (a multiple of eight) absorb
+};
+constexpr int kStepWaves = 8, kStepOwn = 16, kStepBlocks = 256;   // wavefronts; most blocks pooled in the launch, in the window
+
+// Eq. 4 and the Top-K for one query block by eight wavefronts; sums in the order of pool_kernel and select_rows, so that the list
+// is theirs.  The list is left at sel; scratch: D + 9 t_pad + 16 D floats at smem.
+template <typename T, int D>
+__device__ __forceinline__ void select_block(float* smem, int* sel, const T* Qh, int q0, int q1, const T* Kh, int n_kv, int bkv,
+                                             int t_n, int k, float* kbar_head, int kv_first, int kv_end, bool store,
+                                             int32_t* idx_row) {
+  using P = Pool<T, D>;
+  constexpr int E = P::E, CW = D / 32;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int t_pad = (t_n + 3) & ~3;
+  float* sq = smem;
+  float* part = sq + D;                 // [8][t_pad]
+  float* sc = part + kStepWaves * t_pad;
+  float* fresh = sc + t_pad;            // [kStepOwn][D]
+  __shared__ unsigned long long masks[kStepWaves];
+  const float4* kt = reinterpret_cast<const float4*>(kbar_head) + (size_t)wave * CW * t_n;
+  float4 kv[4][CW];                     // (requested first: what was pooled before is on its way while the rest is pooled)
+#pragma unroll
+  for (int u = 0; u < 4; ++u)
+    if (64 * u < t_n) {                 // uniform
+      const int j = min(lane + 64 * u, t_n - 1);
+#pragma unroll
+      for (int c = 0; c < CW; ++c) kv[u][c] = kt[(size_t)c * t_n + j];
+    }
+  const int sub = lane / P::LPR, col = (lane % P::LPR) * E;
+  for (int it = wave; it <= kv_end - kv_first; it += kStepWaves) {   // uniform; the last is the query block
+    const bool is_q = it == kv_end - kv_first;
+    const int blk = kv_first + it, r0 = is_q ? q0 : blk * bkv, r1 = is_q ? q1 : min(n_kv, r0 + bkv);
+    float acc[E];
+    P::mean((is_q ? Qh : Kh) + col, r0, r1, sub, acc);
+    if (sub == 0) {
+#pragma unroll
+      for (int e = 0; e < E; e += 4) {
+        const float4 v = make_float4(acc[e], acc[e + 1], acc[e + 2], acc[e + 3]);
+        *reinterpret_cast<float4*>((is_q ? sq : fresh + it * D) + col + e) = v;
+        if (!is_q && store) reinterpret_cast<float4*>(kbar_head)[(size_t)((col + e) / 4) * t_n + blk] = v;
+      }
+    }
+  }
+  if (tid < t_pad - t_n) sc[t_n + tid] = -INFINITY;   // never outranks a block
+  __syncthreads();
+  const float4* q4 = reinterpret_cast<const float4*>(sq) + wave * CW;
+#pragma unroll
+  for (int u = 0; u < 4; ++u) {
+    const int j = lane + 64 * u;
+    if (j < t_n) {
+      const bool mine = j >= kv_first && j < kv_end;
+      float a = 0.0f;
+#pragma unroll
+      for (int c = 0; c < CW; ++c) {
+        const float4 q = q4[c], x = mine ? *reinterpret_cast<const float4*>(fresh + (j - kv_first) * D + 4 * (wave * CW + c)) : kv[u][c];
+        a = fmaf(q.x, x.x, a); a = fmaf(q.y, x.y, a); a = fmaf(q.z, x.z, a); a = fmaf(q.w, x.w, a);
+      }
+      part[wave * t_pad + j] = a;
+    }
+  }
+  __syncthreads();
+  if (tid < t_n) {
+    const float* x = part + tid;
+    sc[tid] = ((x[0] + x[t_pad]) + (x[2 * t_pad] + x[3 * t_pad])) + ((x[4 * t_pad] + x[5 * t_pad]) + (x[6 * t_pad] + x[7 * t_pad]));
+  }
+  __syncthreads();
+  // a block's rank among the row's scores, equal ones by index; the list by ballots
+  bool keep = false;
+  if (tid < t_n) {
+    const float mine = sc[tid];
+    int rank = 0;
+    for (int o = 0; o < t_pad; o += 4) {
+      const float4 v = *reinterpret_cast<const float4*>(sc + o);
+      rank += (v.x > mine || (v.x == mine && o < tid)) ? 1 : 0;
+      rank += (v.y > mine || (v.y == mine && o + 1 < tid)) ? 1 : 0;
+      rank += (v.z > mine || (v.z == mine && o + 2 < tid)) ? 1 : 0;
+      rank += (v.w > mine || (v.w == mine && o + 3 < tid)) ? 1 : 0;
+    }
+    keep = rank < k;
+  }
+  const unsigned long long m = __ballot(keep);
+  if (lane == 0) masks[wave] = m;
+  __syncthreads();
+  int pos = __popcll(m & ((1ull << lane) - 1ull));
+  for (int w = 0; w < wave; ++w) pos += __popcll(masks[w]);
+  if (keep && pos < k) {
+    sel[pos] = tid;
+    if (idx_row) idx_row[pos] = tid;
+  }
+  __syncthreads();
+}
+
+template <typename T, int D, int NQ, int KS, int NWV, bool kSel>
+__global__ __launch_bounds__(64 * NWV, 2) void attn_wide_kernel(const T* __restrict__ Q, const T* __restrict__ K,
                                                            const T* __restrict__ V, const int32_t* __restrict__ idx, int k,
                                                            int n_q, int n_kv, int kv_stride, int bq, int bkv, int t_m,
                                                            int t_n, int chunks, int per_xcd, int total, float scale_log2e,
-                                                           WideHist hist, T* __restrict__ O) {
-  constexpr int WR = 4 / KS;             // wavefronts along the rows
+                                                           WideHist hist, WideStep step, T* __restrict__ O) {
+  constexpr int WR = NWV / KS;           // wavefronts along the rows
   constexpr int ROWS = WR * 16 * NQ;     // query rows of a workgroup
   constexpr int C = D / 16;              // row-form pieces of a token
   constexpr int F = D / 64;              // column-form pieces of a token
   constexpr int OST = D + 4;             // floats per row of a partial result in LDS (breaks the banks' period)
   extern __shared__ __attribute__((aligned(16))) float smem[];
   // one contiguous run of (head, query block, chunk of rows) per XCD: its L2 then holds the keys of few heads
-  const int item = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
-  if ((int)(blockIdx.x >> 3) >= per_xcd || item >= total) return;
+  int wg = blockIdx.x;
+  if constexpr (kSel) {
+    if (wg < step.role_blocks) {
+      constexpr int TILES = (D / 32) * (D / 32);
+      if (wg < step.BH * TILES)
+        absorb_tile<T, D>(smem, wg % TILES, 0, wg / TILES, step.state_in, step.state_out, static_cast<const T*>(step.K_ev),
+                          static_cast<const T*>(step.V_ev), step.n_ev, step.ev_stride, step.n_ev, step.cos_ev, step.sin_ev,
+                          hist.phi_kind, step.BH, 1);
+      return;
+    }
+    wg -= step.role_blocks;
+  }
+  const int item = (wg & 7) * per_xcd + (wg >> 3);
+  if ((wg >> 3) >= per_xcd || item >= total) return;
   const int bh = item / (t_m * chunks), in_head = item - bh * t_m * chunks;
   const int qb = in_head / chunks, chunk = in_head - qb * chunks;
   const int row0 = qb * bq + chunk * ROWS;
@@ -49,9 +168,10 @@ __global__ __launch_bounds__(256, 2) void attn_wide_kernel(const T* __restrict__
   const T* Kh = K + (size_t)bh * kv_stride * D;  // heads of a cache buffer are kv_stride tokens apart
   const T* Vh = V + (size_t)bh * kv_stride * D;
   const int32_t* row_idx = idx ? idx + ((size_t)bh * t_m + qb) * k : nullptr;
-  const int nsel = idx ? k : t_n;
+  const int nsel = kSel || idx ? k : t_n;
   const int subs = (bkv + kTile - 1) / kTile;
   const int ntiles = nsel * subs;
+  int* const sel = reinterpret_cast<int*>(smem + KS * ROWS * OST + ROWS * KS * 2);   // kSel: the list, behind everything else
 
   // rows past the block's end are computed on clamped addresses and never written
   int row[NQ];
@@ -63,6 +183,11 @@ __global__ __launch_bounds__(256, 2) void attn_wide_kernel(const T* __restrict__
 #pragma unroll
     for (int c = 0; c < C; ++c) qf[n][c] = load4<T>(qp + 16 * c) * scale_log2e;
   }
+
+  if constexpr (kSel)
+    select_block<T, D>(smem, sel, Q + (size_t)bh * n_q * D, qb * bq, q_end, Kh, n_kv, bkv, t_n, k,
+                       step.kbar_t + (size_t)bh * D * t_n, step.kv_first, step.kv_end, in_head == 0,
+                       chunk == 0 ? step.idx_out + ((size_t)bh * t_m + qb) * k : nullptr);
 
   f32x4 o[NQ][F][4];
   float m[NQ], l[NQ];
@@ -80,7 +205,7 @@ __global__ __launch_bounds__(256, 2) void attn_wide_kernel(const T* __restrict__
   // short block); the rows behind them read as zeros and their scores are -inf
   auto tile_at = [&](int t, int& first, int& cnt) {
     const int s = t / subs, sub = t - s * subs;
-    const int jb = row_idx ? row_idx[min(s, nsel - 1)] : s;
+    const int jb = kSel ? __builtin_amdgcn_readfirstlane(sel[min(s, nsel - 1)]) : row_idx ? row_idx[min(s, nsel - 1)] : s;
     const int st = jb * bkv + kTile * sub;
     const bool ok = s < nsel && (unsigned)jb < (unsigned)t_n;
     const int n = ok ? min(kTile, min(n_kv, (jb + 1) * bkv) - st) : 0;
@@ -377,7 +502,7 @@ __global__ __launch_bounds__(256, 2) void attn_wide_kernel(const T* __restrict__
             f32x4{o[n][f][0][r], o[n][f][1][r], o[n][f][2][r], o[n][f][3][r]} * den[n];
   }
   __syncthreads();
-  for (int e = threadIdx.x; e < ROWS * (D / 4); e += 256) {
+  for (int e = threadIdx.x; e < ROWS * (D / 4); e += 64 * NWV) {
     const int rr = e / (D / 4), c4 = e - rr * (D / 4);
     if (row0 + rr >= q_end) continue;
     f32x4 v = *reinterpret_cast<const f32x4*>(smem + (size_t)rr * OST + 4 * c4);
@@ -399,7 +524,7 @@ int launch_wide(const hf_config& c, const void* Q, int n_q, const void* K, const
   const int per_xcd = (int)((total + 7) / 8);
   const float scale = c.softmax_scale > 0.0f ? c.softmax_scale : 1.0f / sqrtf((float)c.head_dim);
   const size_t lds = KS > 1 ? ((size_t)KS * ROWS * (D + 4) + (size_t)ROWS * KS * 2) * sizeof(float) : 0;
-  auto kern = attn_wide_kernel<T, D, NQ, KS>;
+  auto kern = attn_wide_kernel<T, D, NQ, KS, 4, false>;
   if (lds > 64 * 1024) {
     static LdsGrant grant;   // (one per instantiation, i.e. per kernel)
     const int rc = grant_lds(grant, reinterpret_cast<const void*>(kern), (int)lds, "the fp32 attention kernel");
@@ -407,8 +532,37 @@ int launch_wide(const hf_config& c, const void* Q, int n_q, const void* K, const
   }
   hipLaunchKernelGGL(kern, dim3(8 * per_xcd), dim3(256), lds, s, static_cast<const T*>(Q), static_cast<const T*>(K),
                      static_cast<const T*>(V), idx, k, n_q, n_kv, kv_stride_of(c, n_kv), c.block_q, c.block_kv, t_m, t_n,
-                     chunks, per_xcd, (int)total, scale * 1.4426950408889634f, hist, static_cast<T*>(O));
+                     chunks, per_xcd, (int)total, scale * 1.4426950408889634f, hist, WideStep{}, static_cast<T*>(O));
   return check_launch("hf_hybrid_attn_fwd(attention)");
+}
+
+// the step of a small stream: sixteen rows a workgroup, eight wavefronts that share them
+template <int D>
+int launch_wide_step_d(const hf_config& c, const void* Q, int n_q, const void* K, const void* V, int n_kv, int k, void* O,
+                       const WideHist& hist, WideStep step, hipStream_t s) {
+  constexpr int ROWS = 16, KS = kStepWaves;
+  const int BH = c.batch * c.heads;
+  const int t_m = (n_q + c.block_q - 1) / c.block_q, t_n = (n_kv + c.block_kv - 1) / c.block_kv;
+  const int chunks = (c.block_q + ROWS - 1) / ROWS;
+  const long long total = (long long)BH * t_m * chunks;
+  const int per_xcd = (int)((total + 7) / 8);
+  const float scale = c.softmax_scale > 0.0f ? c.softmax_scale : 1.0f / sqrtf((float)c.head_dim);
+  constexpr int kFloats = KS * ROWS * (D + 4) + ROWS * KS * 2;
+  constexpr int lds = kFloats * (int)sizeof(float) + kStepBlocks * (int)sizeof(int);
+  static_assert(kFloats >= D + 9 * kStepBlocks + kStepOwn * D && lds >= kAbsorbLds, "selection and absorb use the same space");
+  step.BH = BH;
+  step.role_blocks = step.state_out ? (BH * (D / 32) * (D / 32) + 7) & ~7 : 0;
+  auto kern = attn_wide_kernel<float, D, 1, KS, kStepWaves, true>;
+  if (lds > 64 * 1024) {
+    static LdsGrant grant;
+    const int rc = grant_lds(grant, reinterpret_cast<const void*>(kern), lds, "the fp32 step kernel");
+    if (rc != HF_OK) return rc;
+  }
+  hipLaunchKernelGGL(kern, dim3(8 * per_xcd + step.role_blocks), dim3(64 * kStepWaves), lds, s, static_cast<const float*>(Q),
+                     static_cast<const float*>(K), static_cast<const float*>(V), nullptr, k, n_q, n_kv, kv_stride_of(c, n_kv),
+                     c.block_q, c.block_kv, t_m, t_n, chunks, per_xcd, (int)total, scale * 1.4426950408889634f, hist, step,
+                     static_cast<float*>(O));
+  return check_launch("hf_ring_step(selection, attention)");
 }
 
 // ---- fp32 storage, block_q and block_kv multiples of 32, few rows: tiles of 32 keys x 32 queries on the 32 x 32 x 2 instruction.
@@ -786,6 +940,49 @@ bool attn_w64_supported(const hf_config& c);
 
 // shapes whose attention kernel is the one of this file, which adds the history term itself
 bool attn_wide_taken(const hf_config& c) { return !attn_mfma_supported(c) && !attn_w64_supported(c); }
+
+// Steps of small fp32 streams as one launch: as many workgroups of sixteen rows as compute units at most.
+bool attn_wide_step_supported(const hf_config& c, int n_q, int n_kv) {
+  const int t_n = (n_kv + c.block_kv - 1) / c.block_kv;
+  return c.dtype == HF_F32 && attn_wide_taken(c) && t_n <= kStepBlocks && !attn_split_supported(c, n_q, n_kv) &&
+         (long long)c.batch * c.heads * ((n_q + c.block_q - 1) / c.block_q) * ((c.block_q + 15) / 16) <= 256;
+}
+// whether that launch pools the blocks [kv_first, kv_end) itself, every workgroup all of them
+bool attn_wide_step_pools(const hf_config&, int kv_first, int kv_end) { return kv_end - kv_first <= kStepOwn; }
+bool attn_wide_step_absorbs(int n_ev) { return n_ev <= kAbsorbOneSlice; }
+
+int launch_attn_wide_step(const hf_config& c, const void* Q, const void* Q_hist, int n_q, const void* K, const void* V, int n_kv, int k,
+                          const float* state, const float* cosq, const float* sinq, float* kbar_t, int32_t* idx_out, int kv_first,
+                          int kv_end, void* O, const void* K_ev, const void* V_ev, int n_ev, int ev_stride, const float* cos_ev,
+                          const float* sin_ev, float* state_out, hipStream_t s) {
+  const size_t d = c.head_dim;
+  WideHist h = {};
+  h.phi_kind = c.phi;
+  if (state) {
+    h.L = state;
+    h.z = state + (size_t)c.batch * c.heads * d * d;
+    h.cosq = cosq;
+    h.sinq = sinq;
+    h.q_hist = Q_hist;
+    h.eps = c.eps;
+    h.z_scale = c.z_scale;
+  }
+  WideStep st = {};
+  st.kbar_t = kbar_t;
+  st.idx_out = idx_out;
+  st.kv_first = kv_first;
+  st.kv_end = kv_end;
+  st.K_ev = K_ev;
+  st.V_ev = V_ev;
+  st.n_ev = n_ev;
+  st.ev_stride = ev_stride;
+  st.cos_ev = cos_ev;
+  st.sin_ev = sin_ev;
+  st.state_in = state;
+  st.state_out = state_out;
+  return c.head_dim == 128 ? launch_wide_step_d<128>(c, Q, n_q, K, V, n_kv, k, O, h, st, s)
+                           : launch_wide_step_d<64>(c, Q, n_q, K, V, n_kv, k, O, h, st, s);
+}
 
 int launch_attn_wide_hist(const hf_config& c, const void* Q, const void* Q_hist, int n_q, const void* K, const void* V,
                           int n_kv, const int32_t* idx, int k, const float* state, const float* cosq, const float* sinq,

@@ -160,6 +160,14 @@ int launch_attn_mfma_fused(const hf_config& c, const void* Q, int n_q, const voi
                            const float* kbar_t = nullptr, int32_t* idx_out = nullptr, float* scores_out = nullptr,
                            int pool_first = 0, int pool_end = 0,
                            const float* state = nullptr);   // L in place of planes (NULL then): rounded in the epilogue
+// steps of small fp32 streams: selection, attention and, state_out given, Eq. 2 for another chunk into it, in one launch
+bool attn_wide_step_supported(const hf_config& c, int n_q, int n_kv);
+bool attn_wide_step_pools(const hf_config& c, int kv_first, int kv_end);
+bool attn_wide_step_absorbs(int n_ev);
+int launch_attn_wide_step(const hf_config& c, const void* Q, const void* Q_hist, int n_q, const void* K, const void* V, int n_kv, int k,
+                          const float* state, const float* cosq, const float* sinq, float* kbar_t, int32_t* idx_out, int kv_first,
+                          int kv_end, void* O, const void* K_ev, const void* V_ev, int n_ev, int ev_stride, const float* cos_ev,
+                          const float* sin_ev, float* state_out, hipStream_t s);
 bool attn_rounds_state_itself(const hf_config& c, int n_q, int n_kv, bool dense);
 // kbar_t given (idx NULL): every workgroup selects its KV blocks itself (Eq. 4) and writes its list to idx_out; the blocks
 // [pool_first, pool_end) it pools itself and stores in kbar_t (only where attn_pools_itself says so)
