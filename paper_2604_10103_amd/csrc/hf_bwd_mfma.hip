@@ -198,6 +198,10 @@ __device__ __forceinline__ void mfma_from(f32x16& acc, const bf16x8 a, const bf1
 __device__ __forceinline__ void mfma_more(f32x16& acc, const bf16x8 a, const bf16x8& b) {   // acc += A B
   asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+v"(acc) : "v"(a), "a"(b));
 }
+// The scores that a loop's last trip forms belong to no tile: unused, their registers would be free to the compiler at once, while
+// the products (assembly, no wait states counted) are still to write them over whatever it put there.  Named behind the trip's
+// other products they stay reserved until those writes are done.
+__device__ __forceinline__ void outlive(const f32x16& s, const f32x16& p) { asm volatile("" :: "v"(s), "v"(p)); }
 // acc += A B, accumulator in the accumulation half, with a 1 KB transfer global -> LDS behind it (LDS address through
 // m0, written in front of the MFMA, which is the wait state that the transfer needs behind that write)
 __device__ __forceinline__ void mfma_acc_piece(f32x16& acc, const bf16x8 a, const bf16x8 b, const bool wait,
@@ -440,6 +444,7 @@ __device__ __forceinline__ void dq_rows(
         rows_read(p2, u);
         __builtin_amdgcn_sched_barrier(0);
       }
+      outlive(sn, dn);
     };
     // slot numbers are literals, hence four trips per turn of the loop; the last one to three tiles take two or
     // four more trips (a tile past the list is zeros)
@@ -880,6 +885,7 @@ __device__ __forceinline__ void dkv_keys(
       }
       __builtin_amdgcn_sched_barrier(0);
     }
+    outlive(sn, dn);
   };
   // slot numbers are literals, hence four trips per turn of the loop; the last one to three tiles take two or four
   // more trips (a tile past the list is zeros)
