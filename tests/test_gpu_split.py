@@ -310,6 +310,14 @@ def test_a_head_alone_and_among_many(dtype, d):
         assert ((O - outs[0][2]).norm() / O.norm()).item() <= (2e-6 if dtype == "f32" else 1e-3)
 
 
+# four groups of one value block, two of two at head_dim 128, two of one at 64, ragged rows: what keeps a query's features
+@pytest.mark.parametrize("case", [(66, 128, 64, 64, 65, 400, 1.0), (300, 128, 64, 64, 70, 200, 0.6), (300, 64, 64, 64, 70, 200, 0.6)],
+                         ids=lambda c: "-".join(map(str, c)))
+@pytest.mark.parametrize("phi", [hf.HF_PHI_RELU, hf.HF_PHI_ELU1])
+def test_history_without_rotation(case, phi):
+    test_forward_and_gradients(case, 4.0, phi, False)
+
+
 @pytest.mark.parametrize("heads,d,bkv", BAD)
 def test_sums_of_the_history_term(heads, d, bkv):
     """History term alone (no value in the window), positive terms.  A rounding at full size is off by 2.5e-8 of the result (2^-24
