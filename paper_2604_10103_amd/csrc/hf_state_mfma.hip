@@ -708,6 +708,15 @@ QuadPlan plan_of(int BH, int n, int nv, int sl) {
   return p;
 }
 QuadPlan quad_plan(int BH, int n) { return plan_of(BH, n, 1, (256 + 2 * BH) / (4 * BH)); }
+// What hf_absorb_workspace_bytes says: a partial per 320 tokens, up to about four per compute unit and no shorter slices beyond, the
+// size that callers have kept since slices were cut so.  Every plan fits it.
+size_t kept_bytes(int BH, int n) {
+  const int most = (1024 + BH - 1) / BH;
+  int per = RUN;
+  if ((n + per - 1) / per > most) per = ((n + most - 1) / most + RUN - 1) / RUN * RUN;
+  const size_t cut = (size_t)BH * ((n + per - 1) / per) * PART * sizeof(float), quad = quad_plan(BH, n).total_bytes;
+  return cut > quad ? cut : quad;
+}
 // Rotated or ELU + 1 keys.  A compute unit holds one workgroup of rotated keys.  In a quadrant every key is transformed twice and every
 // row of the tables read by two workgroups; a half does both once and has twice the partials to add at its end.  Modelled in us,
 // rounds x (pairs of tiles a slice x 0.58 or 0.85 + 4.5) + 0.2 or 0.5 a slice; fitted to 12 heads x 4680 rotated tokens, quadrants /
@@ -716,6 +725,7 @@ QuadPlan quad_plan(int BH, int n) { return plan_of(BH, n, 1, (256 + 2 * BH) / (4
 // what a pair costs is the issue of some 150 instructions a wavefront, two wavefronts a SIMD.
 QuadPlan map_plan(int BH, int n) {
   const int tiles = (n + 2 * QT - 1) / (2 * QT);
+  const size_t room = kept_bytes(BH, n);   // (holds one slice a head; of 280 sizes eight would take more, modelled 0.1 to 2 us faster)
   int best_nv = 1, best_sl = 1;
   double least = 1e300;
   for (int nv = 1; nv <= 2; ++nv)
@@ -723,24 +733,14 @@ QuadPlan map_plan(int BH, int n) {
       const int pairs = (tiles + sl - 1) / sl, used = (tiles + pairs - 1) / pairs;
       const double rounds = (double)(((long long)BH * used * (4 / nv) + 255) / 256);
       const double cost = rounds * (pairs * (nv == 1 ? 0.58 : 0.85) + 4.5) + used * (nv == 1 ? 0.2 : 0.5);
-      if (cost < least) { least = cost; best_nv = nv; best_sl = used; }
+      if (cost < least && plan_of(BH, n, nv, used).total_bytes <= room) { least = cost; best_nv = nv; best_sl = used; }
     }
   return plan_of(BH, n, best_nv, best_sl);
 }
 
 }  // namespace
 
-size_t absorb_mfma_workspace_bytes(const hf_config& c, int n) {
-  // A partial per 320 tokens, up to about four per compute unit and no shorter slices beyond: the size that callers have kept since
-  // slices were cut so.  Both plans are nearly always smaller; whichever runs has to fit.
-  const int BH = c.batch * c.heads, most = (1024 + BH - 1) / BH;
-  int per = RUN;
-  if ((n + per - 1) / per > most) per = ((n + most - 1) / most + RUN - 1) / RUN * RUN;
-  const size_t cut = (size_t)BH * ((n + per - 1) / per) * PART * sizeof(float);
-  const size_t quad = quad_plan(BH, n).total_bytes, map = map_plan(BH, n).total_bytes;
-  const size_t plan = quad > map ? quad : map;
-  return cut > plan ? cut : plan;
-}
+size_t absorb_mfma_workspace_bytes(const hf_config& c, int n) { return kept_bytes(c.batch * c.heads, n); }
 
 // workspace given: one launch
 static int launch_absorb_quad(const hf_config& c, float* state, const void* K, const void* V, int n, int head_stride,

@@ -421,6 +421,15 @@ def test_arguments_are_checked_in_their_order_before_the_device_is_asked(lib):
             call()
 
 
+@pytest.mark.parametrize("heads,n,partials,counters", [(40, 321, 80, 1280), (40, 700, 120, 0), (64, 500, 128, 0), (24, 1560, 120, 0)])
+@pytest.mark.parametrize("phi", [hf.HF_PHI_RELU, hf.HF_PHI_ELU1])
+def test_absorb_scratch_that_callers_have_kept_is_enough(lib, heads, n, partials, counters, phi):
+    """A partial state per 320 tokens of a head, or the counters and partials of the plan without a map: sizes where the plan of mapped
+    keys would rather have more."""
+    cfg = hf.make_config(1, heads, 128, "bf16", 64, 64, 0.25, phi=phi)
+    assert hf.hf_absorb_workspace_bytes(cfg, n) == partials * (128 * 128 + 128) * 4 + counters
+
+
 @pytest.mark.gpu
 def test_the_issue_rate_probe_refuses_strided_scratch(lib):
     with pytest.raises(ValueError, match="contiguous"):
