@@ -300,9 +300,11 @@ __device__ __forceinline__ int* select_in_workgroup(char* smem, const bf16_t* Qh
         ties_seen += __popcll(bal_eq);
       }
     };
-    // (uniform) the steps count only the keys that there are: with the normaliser's early request below 0.6 us of a launch, 3 heads x
-    // 400 queries x 1200 keys (19 blocks) over four steps 64.6 -> 62.2 us
-    switch ((t_n + 63) / 64) {
+    // (uniform) two groups: the steps count only the keys that there are.  With the normaliser's early request below 0.6 us of a
+    // launch, 3 heads x 400 queries x 1200 keys (19 blocks) over four steps 64.6 -> 62.2 us.  In full launches other workgroups' loops
+    // hide the search, and four forms of it cost 40 heads x 10800 x 21600 0.3 to 0.5 %.
+    if constexpr (KS == 1) top_k(std::integral_constant<int, 4>{});
+    else switch ((t_n + 63) / 64) {
       case 1: top_k(std::integral_constant<int, 1>{}); break;
       case 2: top_k(std::integral_constant<int, 2>{}); break;
       case 3: top_k(std::integral_constant<int, 3>{}); break;
