@@ -460,7 +460,7 @@ static int fwd_impl(const hf_config* cfg, const void* Q, const void* Q_hist, int
                     const void* V_win, int32_t n_kv, const int32_t* block_idx, int32_t k, const void* state_or_null,
                     const float* rope_cos_q, const float* rope_sin_q, void* O, bool save, void* O_local_out,
                     float* lse2_out, void* workspace, size_t workspace_bytes, void* stream,
-                    const void* planes_in = nullptr);
+                    const void* planes_in = nullptr, bool keep_planes = false);
 
 int hf_hybrid_attn_fwd_split(const hf_config* cfg, const void* Q, const void* Q_hist, int32_t n_q,
                              const void* K_win, const void* V_win, int32_t n_kv, const int32_t* block_idx,
@@ -651,7 +651,8 @@ int hf_hybrid_attn_fwd_save(const hf_config* cfg, const void* Q, const void* Q_h
 static int fwd_impl(const hf_config* cfg, const void* Q, const void* Q_hist, int32_t n_q, const void* K_win,
                     const void* V_win, int32_t n_kv, const int32_t* block_idx, int32_t k, const void* state_or_null,
                     const float* rope_cos_q, const float* rope_sin_q, void* O, bool save, void* O_local_out,
-                    float* lse2_out, void* workspace, size_t workspace_bytes, void* stream, const void* planes_in) {
+                    float* lse2_out, void* workspace, size_t workspace_bytes, void* stream, const void* planes_in,
+                    bool keep_planes) {
   HF_TRY(check_cfg(cfg));
   if (save) {
     HF_TRY(check_ptr(O_local_out, "O_local_out", true));
@@ -720,7 +721,8 @@ static int fwd_impl(const hf_config* cfg, const void* Q, const void* Q_hist, int
     char* planes = static_cast<char*>(workspace) + w.planes;
     const float* st = static_cast<const float*>(state_or_null);
     const size_t d = cfg->head_dim;
-    const bool direct = attn_rounds_state_itself(*cfg, n_q, n_kv, block_idx == nullptr);   // no planes, no launch for them
+    // no planes and no launch for them, unless the caller's later steps read them here (keep_planes)
+    const bool direct = !keep_planes && attn_rounds_state_itself(*cfg, n_q, n_kv, block_idx == nullptr);
     if (!direct) HF_TRY(launch_state_planes(*cfg, st, planes, s));
     return launch_attn_mfma_fused(*cfg, Q, n_q, K_win, V_win, n_kv, block_idx, k, direct ? nullptr : planes,
                                   st + (size_t)cfg->batch * cfg->heads * d * d, rope_cos_q, rope_sin_q, Q_hist, O, s,
@@ -862,6 +864,18 @@ static int step_wide_launch(const hf_config* cfg, const void* Q, const void* Q_h
                                a.state_out, s);
 }
 
+// A step's attention behind its selection launches.  The state is frozen during a chunk's steps: where the history term is formed
+// from bf16 planes, the first step leaves them in the workspace (which the selection has checked) and the later ones read them.
+static int step_attention(const hf_config* cfg, const void* Q, const void* Q_hist, int32_t n_q, const void* K, const void* V,
+                          int32_t n_kv, int32_t step_in_chunk, const int32_t* block_idx, int32_t k, const void* state_or_null,
+                          const float* rope_cos_q, const float* rope_sin_q, void* O, void* workspace, size_t workspace_bytes,
+                          void* stream) {
+  const bool kept = step_in_chunk > 0 && state_or_null && attn_mfma_fused_supported(*cfg) && !(cfg->flags & HF_FLAG_READOUT_KERNEL);
+  const char* planes = kept ? static_cast<const char*>(workspace) + workspace_layout(cfg, n_q, n_kv).planes : nullptr;
+  return fwd_impl(cfg, Q, Q_hist, n_q, K, V, n_kv, block_idx, k, state_or_null, rope_cos_q, rope_sin_q, O, false, nullptr, nullptr,
+                  workspace, workspace_bytes, stream, planes, step_in_chunk == 0);
+}
+
 int hf_stream_step(const hf_config* cfg, const hf_window* win, const void* Q, const void* Q_hist, int32_t n_q,
                    const void* K_win, const void* V_win, int32_t step_in_chunk, int32_t* block_idx,
                    const void* state_or_null, const float* rope_cos_q, const float* rope_sin_q, void* O,
@@ -888,15 +902,8 @@ int hf_stream_step(const hf_config* cfg, const hf_window* win, const void* Q, co
   HF_TRY(hf_block_select_cached(cfg, Q, n_q, K_win, n_kv, reuse, block_idx, nullptr, workspace, workspace_bytes,
                                 stream));
   const int32_t k = select_k_of(cfg, cdiv(n_kv, cfg->block_kv));
-  if (step_in_chunk > 0 && state_or_null && attn_mfma_fused_supported(*cfg) && !(cfg->flags & HF_FLAG_READOUT_KERNEL)) {
-    // the state is frozen during a chunk's denoising steps: its bf16 planes are as the chunk's first step left them
-    // in this workspace (which hf_block_select_cached has just checked for size and alignment)
-    const WorkspaceLayout w = workspace_layout(cfg, n_q, n_kv);
-    return fwd_impl(cfg, Q, Q_hist, n_q, K_win, V_win, n_kv, block_idx, k, state_or_null, rope_cos_q, rope_sin_q, O,
-                    false, nullptr, nullptr, nullptr, 0, stream, static_cast<char*>(workspace) + w.planes);
-  }
-  return hf_hybrid_attn_fwd_split(cfg, Q, Q_hist, n_q, K_win, V_win, n_kv, block_idx, k, state_or_null, rope_cos_q,
-                                  rope_sin_q, O, workspace, workspace_bytes, stream);
+  return step_attention(cfg, Q, Q_hist, n_q, K_win, V_win, n_kv, step_in_chunk, block_idx, k, state_or_null, rope_cos_q, rope_sin_q,
+                        O, workspace, workspace_bytes, stream);
 }
 
 static int check_ring(const hf_config* cfg, const hf_ring* r) {
@@ -1000,13 +1007,8 @@ int hf_ring_step(const hf_config* cfg, const hf_ring* ring, const void* Q, const
   char* ws = static_cast<char*>(workspace);
   HF_TRY(select_launches(cfg, Q, n_q, K_cache, n_kv, kv_first, k, block_idx, nullptr, reinterpret_cast<float*>(ws + w.qbar),
                          reinterpret_cast<float*>(ws + w.kbar), static_cast<hipStream_t>(stream), kv_end));
-  if (step_in_chunk > 0 && state_or_null && attn_mfma_fused_supported(*cfg) && !(cfg->flags & HF_FLAG_READOUT_KERNEL)) {
-    // the state is frozen during a chunk's steps: its bf16 planes are as the chunk's first step left them here
-    return fwd_impl(cfg, Q, Q_hist, n_q, K_cache, V_cache, n_kv, block_idx, k, state_or_null, rope_cos_q, rope_sin_q, O,
-                    false, nullptr, nullptr, nullptr, 0, stream, ws + w.planes);
-  }
-  return hf_hybrid_attn_fwd_split(cfg, Q, Q_hist, n_q, K_cache, V_cache, n_kv, block_idx, k, state_or_null, rope_cos_q,
-                                  rope_sin_q, O, workspace, workspace_bytes, stream);
+  return step_attention(cfg, Q, Q_hist, n_q, K_cache, V_cache, n_kv, step_in_chunk, block_idx, k, state_or_null, rope_cos_q,
+                        rope_sin_q, O, workspace, workspace_bytes, stream);
 }
 
 int hf_ring_last_step(const hf_config* cfg, hf_ring* ring, const void* Q, const void* Q_hist, const void* K_cache,

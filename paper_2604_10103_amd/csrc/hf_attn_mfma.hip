@@ -1268,6 +1268,8 @@ static DenseShape dense_shape(long long BH, int n_q, long long tiles) {
 // XCD's L2 instead of 32 KB of a plane, and no launch in front.  Launches of two or more groups of wavefronts and at most half the
 // chip's workgroups gain that launch (block selection + attention, 7 heads x 5 query blocks 16.7 -> 15.1 us, 5 x 38 36.0 -> 33.7,
 // 20 x 8 of 128 rows 30.5 -> 28.1), full ones gain nothing (12 x 74: 99.2 / 99.5), several rounds lose (30 x 74: 225 / 230).
+// A launch that does so leaves no planes in the workspace: the steps of streams and rings, which read them there after a chunk's
+// first one, ask for them (keep_planes of fwd_impl).
 bool attn_rounds_state_itself(const hf_config& c, int n_q, int n_kv, bool dense) {
   const long long bh = (long long)c.batch * c.heads, workgroups = bh * ((n_q + c.block_q - 1) / c.block_q);
   const long long tiles = (long long)((n_kv + c.block_kv - 1) / c.block_kv) * ((c.block_kv + TK - 1) / TK);
