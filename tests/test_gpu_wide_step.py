@@ -1,6 +1,6 @@
 """Steps of small fp32 streams as one launch (selection, attention, history term and the next eviction's absorb): blocks pooled in
 the launch and in front of it, windows of one to 256 KV blocks and past that, workgroups up to the limit and past it, blocks of more
-rows than a workgroup, ties.  Lists as the selection's own launches give them, outputs and states against those and the oracle."""
+rows than a workgroup, ties, rotated queries and evicted keys.  Lists as the selection's own launches give them, outputs and states against those and the oracle."""
 import numpy as np
 import pytest
 import torch
@@ -28,7 +28,7 @@ CASES = [  # heads, head_dim, block, tokens of a chunk, of the sink, slots, keep
 ]
 
 
-@pytest.mark.parametrize("state", [True, False])
+@pytest.mark.parametrize("state", [True, False, "rotated"])
 @pytest.mark.parametrize("case", CASES, ids=lambda c: "-".join(map(str, c)))
 def test_steps_of_a_full_ring(case, state):
     H, d, b, n, sink, slots, keep, phi = case
@@ -36,6 +36,10 @@ def test_steps_of_a_full_ring(case, state):
     phi = hf.HF_PHI_RELU if phi == "relu" else hf.HF_PHI_ELU1
     cfg, packed = (hf.make_config(1, H, d, "f32", b, b, keep, phi=phi, kv_capacity=c) for c in (n_kv, 0))
     K, V, Ke, Ve, *Qs = (wl.randn((1, H, m, d), 91_000 + i, 1.0, torch.float32) for i, m in enumerate((n_kv, n_kv, 40, 40, n, n, n)))
+    rot = state == "rotated"   # tables for the queries, which are others than the window's, and for the evicted chunk
+    tabs, tabs_ev = (wl.rope_tables(n, d, first_position=p) if rot else (None, None) for p in (3.0, 1.5))
+    (cq, sq), (ce, se) = ([None if t is None else t.to(DEV) for t in ts] for ts in (tabs, tabs_ev))
+    t64, te64 = (tuple(None if t is None else wl.to_f64(t) for t in ts) for ts in (tabs, tabs_ev))
     K[:, :, -1] = K[:, :, 0]
     if n_kv >= 6 * b:   # whole blocks alike: ties
         K[:, :, 2 * b:3 * b] = K[:, :, :b]
@@ -56,15 +60,17 @@ def test_steps_of_a_full_ring(case, state):
     for i, Q in enumerate(Qs):
         Qd, O, O2 = Q.to(DEV), *(torch.full(Q.shape, float("nan"), device=DEV) for _ in range(2))
         idx, idx2 = (torch.full((1, H, t_m, k), -1, dtype=torch.int32, device=DEV) for _ in range(2))
+        Qh = Q.flip(2).contiguous() if rot else None
+        Qhd = None if Qh is None else Qh.to(DEV)
         if i:   # the chunk's keys of this step
             Kd[:, :, at:] = Kd[:, :, at:].flip(3)
         if i < 2:
-            hf.hf_ring_step(cfg, ring, Qd, Kd, Vd, i, idx, st, O, ws)
+            hf.hf_ring_step(cfg, ring, Qd, Kd, Vd, i, idx, st, O, ws, cq, sq, Qhd)
         else:
-            assert hf.hf_ring_last_step(cfg, ring, Qd, Kd, Vd, i, idx, st, O, ws, st2, sws)
+            assert hf.hf_ring_last_step(cfg, ring, Qd, Kd, Vd, i, idx, st, O, ws, st2, sws, cq, sq, Qhd, ce, se)
         ws2 = byte(hf.hf_workspace_bytes(packed, n, n_kv))
         hf.hf_block_select(packed, Qd, Kd, idx2, None, ws2)
-        hf.hf_hybrid_attn_fwd(packed, Qd, Kd, Vd, idx2, st, O2, ws2)
+        hf.hf_hybrid_attn_fwd(packed, Qd, Kd, Vd, idx2, st, O2, ws2, cq, sq, Qhd)
         torch.cuda.synchronize()
         assert torch.equal(idx, idx2)
         for h in sorted({0, H - 1}):
@@ -73,13 +79,13 @@ def test_steps_of_a_full_ring(case, state):
             s0 = oracle_state([Ke[:, h:h + 1]], [Ve[:, h:h + 1]], d, phi=cfg.phi)[0] if state else None
             ref = orc.sparse_attention(one(Q), one(Kd), one(Vd), idx[0, h].cpu().numpy(), b, b)
             if state:
-                ref = ref + orc.history_readout(one(Q), *s0, cfg.phi, None, None, cfg.eps, cfg.z_scale)
+                ref = ref + orc.history_readout(one(Q if Qh is None else Qh), *s0, cfg.phi, *t64, cfg.eps, cfg.z_scale)
             assert rel_l2(wl.to_f64(O)[0, h], ref) <= F32_REL_L2
     L, z = split_state(st2, H, d)
     for h in sorted({0, H - 1}):
         s0 = oracle_state([Ke[:, h:h + 1]], [Ve[:, h:h + 1]], d, phi=cfg.phi)[0] if state else orc.state_zero(d)
         ke, ve = (wl.to_f64(t[0, h, sink:sink + n].cpu()) for t in (Kd, Vd))
-        Lr, zr = orc.state_absorb(*s0, ke, ve, cfg.phi)
+        Lr, zr = orc.state_absorb(*s0, ke, ve, cfg.phi, *te64)
         assert rel_l2(L[h], Lr) <= 1e-5 and rel_l2(z[h], zr) <= 1e-5
     assert ring.absorbed_ahead == 1
     assert np.isfinite(wl.to_f64(st2)).all()
