@@ -818,8 +818,9 @@ static int step_one_launch(const hf_config* cfg, const void* Q, const void* Q_hi
                                 nullptr, kbar, block_idx, nullptr, pool_first, pool_end);
 }
 
-// The same for small fp32 streams (attn_wide_step_supported), whose kernel takes the fp32 state as it is.  ev: the chunk that the
-// launch absorbs into state_out beside the attention, or NULL.
+// The same for small fp32 streams (attn_wide_step_supported, attn_wide_step_pays), whose kernel takes the fp32 state as it is.  ev:
+// the chunk that the launch absorbs into state_out beside the attention, or NULL; absorbs: the last step of the chunk has one
+// (ring_absorbs).
 struct StepAbsorb {
   const void *K, *V;
   int n, stride;
@@ -829,11 +830,12 @@ struct StepAbsorb {
 static int step_wide_launch(const hf_config* cfg, const void* Q, const void* Q_hist, int32_t n_q, const void* K, const void* V,
                             int32_t n_kv, int kv_first, int kv_end, int32_t* block_idx, const void* state_or_null,
                             const float* rope_cos_q, const float* rope_sin_q, void* O, void* workspace, size_t workspace_bytes,
-                            void* stream, const StepAbsorb* ev, bool* done) {
+                            void* stream, bool absorbs, const StepAbsorb* ev, bool* done) {
   *done = false;
-  if (!attn_wide_step_supported(*cfg, n_q, n_kv) || (ev && !attn_wide_step_absorbs(ev->n))) return HF_OK;
+  if (!attn_wide_step_supported(*cfg, n_q, n_kv) || (ev && !absorbs)) return HF_OK;
   int k = 0;
   HF_TRY(check_select_args(cfg, Q, n_q, K, n_kv, 0, block_idx, nullptr, &k));
+  if (!attn_wide_step_pays(*cfg, k, absorbs)) return HF_OK;
   HF_TRY(check_ptr(V, "V_win", true));
   HF_TRY(check_ptr(O, "O", true));
   if (!Q_hist) Q_hist = Q;
@@ -897,7 +899,7 @@ int hf_stream_step(const hf_config* cfg, const hf_window* win, const void* Q, co
                          state_or_null, rope_cos_q, rope_sin_q, O, workspace, workspace_bytes, stream, &done));
   if (done) return HF_OK;
   HF_TRY(step_wide_launch(cfg, Q, Q_hist, n_q, K_win, V_win, n_kv, reuse, cdiv(n_kv, cfg->block_kv), block_idx, state_or_null,
-                          rope_cos_q, rope_sin_q, O, workspace, workspace_bytes, stream, nullptr, &done));
+                          rope_cos_q, rope_sin_q, O, workspace, workspace_bytes, stream, false, nullptr, &done));
   if (done) return HF_OK;
   HF_TRY(hf_block_select_cached(cfg, Q, n_q, K_win, n_kv, reuse, block_idx, nullptr, workspace, workspace_bytes,
                                 stream));
@@ -978,6 +980,11 @@ static RingBlocks ring_blocks(const hf_config* cfg, const hf_ring* ring, int32_t
   return {first / cfg->block_kv, end > t_n ? t_n : end};
 }
 
+// whether the open chunk's last step (hf_ring_last_step) absorbs beside its attention where step_wide_launch takes it
+static bool ring_absorbs(const hf_config* cfg, const hf_ring* ring) {
+  return ring->n_filled == (cfg->kv_capacity - ring->n_sink) / ring->n_chunk && attn_wide_step_absorbs(*cfg, ring->n_chunk);
+}
+
 int hf_ring_step(const hf_config* cfg, const hf_ring* ring, const void* Q, const void* Q_hist, const void* K_cache,
                  const void* V_cache, int32_t step_in_chunk, int32_t* block_idx, const void* state_or_null,
                  const float* rope_cos_q, const float* rope_sin_q, void* O, void* workspace, size_t workspace_bytes,
@@ -1002,7 +1009,7 @@ int hf_ring_step(const hf_config* cfg, const hf_ring* ring, const void* Q, const
                          state_or_null, rope_cos_q, rope_sin_q, O, workspace, workspace_bytes, stream, &done));
   if (done) return HF_OK;
   HF_TRY(step_wide_launch(cfg, Q, Q_hist, n_q, K_cache, V_cache, n_kv, kv_first, kv_end, block_idx, state_or_null, rope_cos_q,
-                          rope_sin_q, O, workspace, workspace_bytes, stream, nullptr, &done));
+                          rope_sin_q, O, workspace, workspace_bytes, stream, ring_absorbs(cfg, ring), nullptr, &done));
   if (done) return HF_OK;
   char* ws = static_cast<char*>(workspace);
   HF_TRY(select_launches(cfg, Q, n_q, K_cache, n_kv, kv_first, k, block_idx, nullptr, reinterpret_cast<float*>(ws + w.qbar),
@@ -1089,7 +1096,7 @@ int hf_ring_last_step(const hf_config* cfg, hf_ring* ring, const void* Q, const 
     bool done = false;
     if (step_in_chunk < 0) { set_error("step_in_chunk must be >= 0"); return HF_ERR_SHAPE; }
     HF_TRY(step_wide_launch(cfg, Q, Q_hist, n_q, K_cache, V_cache, n_kv, blk.first, blk.end, block_idx, state_or_null, rope_cos_q,
-                            rope_sin_q, O, workspace, workspace_bytes, stream, &ev, &done));
+                            rope_sin_q, O, workspace, workspace_bytes, stream, ring_absorbs(cfg, ring), &ev, &done));
     if (done) {
       ring->absorbed_ahead = 1;
       if (absorbed_out) *absorbed_out = 1;

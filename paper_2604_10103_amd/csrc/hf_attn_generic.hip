@@ -941,15 +941,41 @@ bool attn_w64_supported(const hf_config& c);
 // shapes whose attention kernel is the one of this file, which adds the history term itself
 bool attn_wide_taken(const hf_config& c) { return !attn_mfma_supported(c) && !attn_w64_supported(c); }
 
-// Steps of small fp32 streams as one launch: as many workgroups of sixteen rows as compute units at most.
+// Steps of small fp32 streams as one launch: as many workgroups of sixteen rows as compute units at most.  Against selection and
+// attention as launches of their own it gains by eight wavefronts on a list instead of four, and pays for a query block's mean by one
+// wavefront of every workgroup, for the selection in front of the loop and for eight parts that meet.  A later step of one head,
+// separate launches / this one, us, by tiles of 16 keys in a list: head_dim 128, blocks of 16: 2 tiles 12.1 / 12.7, 10 17.1 / 17.6, 20
+// 21.6 / 21.8, 29 27.8 / 26.9, 64 38.7 / 33.6, 128 66.1 / 54.6; of 64: 4 12.9 / 13.5, 20 20.7 / 20.4, 40 29.3 / 26.3; head_dim 64,
+// blocks of 16: 1 8.7 / 8.2, 16 11.9 / 11.1 (at most 6 % slower anywhere: the first step of ten blocks of 256, 16 tiles, 15.2 / 16.0).
+// Where the chunk's last step absorbs beside its attention, that step saves more than the others lose (head_dim 128, 8 heads, 16
+// tokens: 15.7 / 13.0 the last, 12.8 / 12.9 the others; chunks of four steps 0.96 of the time in the mean of 83 sizes with lists that are
+// too short otherwise, 1.03 at most).  Sums are in another order: the rule looks at what all steps of a chunk have in common, so that
+// they run the same kernel, absorb or not.
 bool attn_wide_step_supported(const hf_config& c, int n_q, int n_kv) {
-  const int t_n = (n_kv + c.block_kv - 1) / c.block_kv;
-  return c.dtype == HF_F32 && attn_wide_taken(c) && t_n <= kStepBlocks && !attn_split_supported(c, n_q, n_kv) &&
+  return c.dtype == HF_F32 && attn_wide_taken(c) && (n_kv + c.block_kv - 1) / c.block_kv <= kStepBlocks &&
+         !attn_split_supported(c, n_q, n_kv) &&
          (long long)c.batch * c.heads * ((n_q + c.block_q - 1) / c.block_q) * ((c.block_q + 15) / 16) <= 256;
 }
-// whether that launch pools the blocks [kv_first, kv_end) itself, every workgroup all of them
-bool attn_wide_step_pools(const hf_config&, int kv_first, int kv_end) { return kv_end - kv_first <= kStepOwn; }
-bool attn_wide_step_absorbs(int n_ev) { return n_ev <= kAbsorbOneSlice; }
+bool attn_wide_step_pays(const hf_config& c, int k, bool absorbs) {
+  return absorbs || c.head_dim == 64 || k * ((c.block_kv + kTile - 1) / kTile) >= 25 + c.block_q / 12;
+}
+// Whether that launch pools the blocks [kv_first, kv_end) itself, every workgroup all of them, against a launch in front that pools each
+// block once: by the bytes that a compute unit reads, beyond those that seven wavefronts get through while the eighth forms the query
+// block's mean.  In the launch / in front of it, us: head_dim 128, 1 block of 64 (32 KB) 13.5 / 15.7, 8 (256 KB) 24.6 / 25.5; 12 of 128
+// (768 KB) 29.9 / 27.6; 16 of 256 (2 MB) 38.9 / 30.9; 2 of 1024 (1 MB) 43.7 / 55.1, 8 (4 MB) 74.0 / 59.1; head_dim 64, 2 of 256 (128 KB)
+// 12.2 / 15.2, 16 of 128 (512 KB) 15.6 / 14.5, 8 of 1024 (2 MB) 37.2 / 32.8.  Over 2324 sizes 0.06 % behind the better of the two.
+bool attn_wide_step_pools(const hf_config& c, int kv_first, int kv_end) {
+  const long long row = c.head_dim * (int)sizeof(float), bytes = (long long)(kv_end - kv_first) * c.block_kv * row;
+  return kv_end - kv_first <= kStepOwn && bytes <= 256 * 1024 + 5 * c.block_q * row;
+}
+// Whether its workgroups absorb a chunk of n_ev tokens: of few enough heads for about one round of the chip, as far as LDS goes (a
+// launch of its own has room for twice as many of them at head_dim 128).  The last step of a chunk, absorb behind it / in it, us,
+// head_dim 128, 16 tokens: 8 heads 15.7 / 13.0, 48 17.8 / 18.1, 64 18.4 / 19.7, 128 24.5 / 27.7, 256 36.9 / 46.4; one token: 48 17.2 /
+// 16.0, 64 17.5 / 18.0; head_dim 64, 256 heads 15.2 / 15.0.
+bool attn_wide_step_absorbs(const hf_config& c, int n_ev) {
+  const long long workgroups = (long long)c.batch * c.heads * (c.head_dim / 32) * (c.head_dim / 32);
+  return n_ev <= kAbsorbOneSlice && workgroups <= (c.head_dim == 128 ? 768 : 1024);
+}
 
 int launch_attn_wide_step(const hf_config& c, const void* Q, const void* Q_hist, int n_q, const void* K, const void* V, int n_kv, int k,
                           const float* state, const float* cosq, const float* sinq, float* kbar_t, int32_t* idx_out, int kv_first,

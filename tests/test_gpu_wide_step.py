@@ -1,6 +1,7 @@
 """Steps of small fp32 streams as one launch (selection, attention, history term and the next eviction's absorb): blocks pooled in
 the launch and in front of it, windows of one to 256 KV blocks and past that, workgroups up to the limit and past it, blocks of more
-rows than a workgroup, ties, rotated queries and evicted keys.  Lists as the selection's own launches give them, outputs and states against those and the oracle."""
+rows than a workgroup, ties, rotated queries and evicted keys; steps that absorb nothing, whose lists have to be long enough for it.
+Lists as the selection's own launches give them, outputs and states against those and the oracle."""
 import numpy as np
 import pytest
 import torch
@@ -24,6 +25,10 @@ CASES = [  # heads, head_dim, block, tokens of a chunk, of the sink, slots, keep
     (2, 128, 64, 70, 7, 3, 0.4, "elu"),       # four workgroups a block, two of them without a row in the last
     (4, 64, 16, 1024, 0, 2, 0.06, "relu"),    # 256 workgroups, the longest chunk absorbed beside them
     (1, 64, 16, 1025, 0, 2, 0.06, "relu"),    # one token more: absorbed by a launch of its own
+    (1, 64, 128, 1024, 0, 2, 0.15, "elu"),    # sixteen blocks of too many bytes: pooled in front on the first step, eight not
+    (1, 128, 48, 200, 0, 4, 0.3, "relu"),     # blocks that are no multiple of 32
+    (48, 128, 16, 16, 0, 4, 0.5, "relu"),     # as many absorbing workgroups as ride in the launch
+    (49, 128, 16, 16, 0, 28, 1.0, "relu"),    # one head more: absorbed by a launch of its own
     (5, 64, 16, 817, 0, 2, 0.06, "relu"),     # 260 workgroups: the separate launches
 ]
 
@@ -89,3 +94,32 @@ def test_steps_of_a_full_ring(case, state):
         assert rel_l2(L[h], Lr) <= 1e-5 and rel_l2(z[h], zr) <= 1e-5
     assert ring.absorbed_ahead == 1
     assert np.isfinite(wl.to_f64(st2)).all()
+
+
+# head_dim, block, window, tokens of the chunk, keep: lists on both sides of the line at head_dim 128 (26 tiles of 16 keys for blocks of
+# 16, 27 of 32, 35 of 128), every block or a part of them pooled in the launch
+STREAMS = [(128, 16, 400, 37, 1.0), (128, 16, 416, 37, 1.0), (128, 32, 416, 60, 1.0), (128, 32, 450, 60, 1.0), (128, 128, 500, 130, 1.0),
+           (128, 128, 640, 130, 1.0), (64, 16, 1552, 40, 0.01), (64, 16, 1552, 40, 0.25), (64, 256, 2000, 256, 0.1)]
+
+
+@pytest.mark.parametrize("case", STREAMS, ids=lambda c: "-".join(map(str, c)))
+def test_steps_that_absorb_nothing(case):
+    d, b, n_kv, n, keep = case
+    cfg, packed = (hf.make_config(1, 2, d, "f32", b, b, keep, kv_capacity=c) for c in (n_kv, 0))
+    K, V, Ke, Ve, *Qs = (wl.randn((1, 2, m, d), 95_000 + i, 1.0, torch.float32).to(DEV) for i, m in enumerate((n_kv, n_kv, 40, 40, n, n)))
+    st = torch.empty(hf.hf_state_bytes(cfg) // 4, dtype=torch.float32, device=DEV)
+    hf.hf_state_init(cfg, st)
+    hf.hf_absorb_evicted(packed, st, Ke, Ve)
+    ws, ws2 = (torch.full((hf.hf_workspace_bytes(cfg, n, n_kv),), 255, dtype=torch.uint8, device=DEV) for _ in range(2))   # (NaN)
+    win = hf.hf_window(0, n_kv)
+    for i, Q in enumerate(Qs):
+        O, O2 = (torch.full_like(Q, float("nan")) for _ in range(2))
+        idx, idx2 = (torch.full((1, 2, -(-n // b), hf.hf_select_k(cfg, n_kv)), -1, dtype=torch.int32, device=DEV) for _ in range(2))
+        if i:
+            K[:, :, -n:] = K[:, :, -n:].flip(3)
+        hf.hf_stream_step(cfg, win, Q, K, V, i, idx, st, O, ws)
+        hf.hf_block_select(packed, Q, K, idx2, None, ws2)
+        hf.hf_hybrid_attn_fwd(packed, Q, K, V, idx2, st, O2, ws2)
+        torch.cuda.synchronize()
+        assert torch.equal(idx, idx2)
+        assert rel_l2(wl.to_f64(O), wl.to_f64(O2)) <= F32_REL_L2
