@@ -98,6 +98,9 @@ __global__ __launch_bounds__(256) void rope_append_pool_kernel(const T* __restri
                                                                float* __restrict__ kbar_t) {
   constexpr int TPT = D / 8;         // threads per token
   constexpr int TOK = 256 / TPT;     // tokens per pass of the workgroup
+  // (where the tables are requested: bf16, 12 heads x 74 blocks of 64 in front of the keys 7.3 us, behind them 7.8; fp32 keys, twice as
+  // many loads a token, 2 heads x 19 blocks of 1024 1.16 of the time behind them)
+  constexpr bool kTablesFirst = HPW > 1 || sizeof(T) == 2;
   __shared__ float red[HPW][4][D];
   const int blk = blk0 + blockIdx.x, bh0 = blockIdx.y * HPW;
   const int t0 = blk * bkv, t1 = min(n_kv, t0 + bkv);
@@ -113,11 +116,12 @@ __global__ __launch_bounds__(256) void rope_append_pool_kernel(const T* __restri
     const bool fresh = t >= first && t < first + n_new;
     float x[HPW][8];
     float4 c4, s4;
+    auto tables = [&]() {
+      c4 = *reinterpret_cast<const float4*>(cosv + (size_t)(t - first) * (D / 2) + 4 * g);
+      s4 = *reinterpret_cast<const float4*>(sinv + (size_t)(t - first) * (D / 2) + 4 * g);
+    };
     if (fresh) {
-      if (cosv != nullptr) {
-        c4 = *reinterpret_cast<const float4*>(cosv + (size_t)(t - first) * (D / 2) + 4 * g);
-        s4 = *reinterpret_cast<const float4*>(sinv + (size_t)(t - first) * (D / 2) + 4 * g);
-      }
+      if (kTablesFirst && cosv != nullptr) tables();
 #pragma unroll
       for (int u = 0; u < HPW; ++u) {
         const T* src = X + ((size_t)min(bh0 + u, BH - 1) * n_new + (t - first)) * D + 8 * g;
@@ -137,6 +141,7 @@ __global__ __launch_bounds__(256) void rope_append_pool_kernel(const T* __restri
       if (fresh) {
         T* dst = Kwin + ((size_t)(bh0 + u) * kv_stride + t) * D + 8 * g;
         if (cosv != nullptr) {
+          if (!kTablesFirst) tables();
           const float cc[4] = {c4.x, c4.y, c4.z, c4.w}, ss[4] = {s4.x, s4.y, s4.z, s4.w};
 #pragma unroll
           for (int p = 0; p < 4; ++p) {
@@ -189,8 +194,13 @@ int launch_rope_append_pool(const hf_config& c, const void* X, int n_new, const 
   const int BH = c.batch * c.heads;
   const int t_n = (n_kv + c.block_kv - 1) / c.block_kv;
   const int blk0 = first / c.block_kv, blk1 = (first + n_new + c.block_kv - 1) / c.block_kv;   // blocks the new tokens touch
-  // two heads a workgroup where one would make many rounds of the chip: 40 heads x 113 blocks 46.2 -> 39.7 us, 12 x 74 7.6 -> 8.8
-  const bool pairs = (long long)(blk1 - blk0) * BH > 2048;
+  // Two heads a workgroup, whose tables are read once, where a workgroup of one would make rounds of the chip and has several passes over
+  // its block (256 threads hold 2048 values).  Rotated keys, one head / two a workgroup, us: bf16 at head_dim 128, 12 heads x 113
+  // blocks of 64 14.3 / 13.1, x 175 21.0 / 18.8, 40 heads x 37 11.3 / 12.5, x 113 38.0 / 34.1, x 175 69.9 / 56.4; of 128, 12 x 74 13.7 / 15.3,
+  // 12 x 113 26.0 / 22.6, 40 x 74 38.0 / 35.4; of 256, 12 x 113 52.0 / 41.6; of 16, 12 x 175 6.2 / 7.0, 40 x 175 13.7 / 16.7; fp32, 12 x
+  // 113 of 128 39.5 / 35.1, 40 x 113 of 64 70.7 / 63.4, of 16 15.0 / 16.8.  Copied keys have no tables to share: 1.0 to 1.1 of one head's time.
+  const int passes = c.block_kv * c.head_dim / 2048;
+  const bool pairs = cosv != nullptr && passes >= 4 && (long long)(blk1 - blk0) * BH > (passes >= 8 ? 1024 : 2048);
   const dim3 grid(blk1 - blk0, pairs ? (BH + 1) / 2 : BH);
   const int stride = kv_stride_of(c, n_kv);
 #define HF_LAUNCH_RAP_N(T, DD, N)                                                                                     \
