@@ -465,7 +465,8 @@ __global__ __launch_bounds__(QNT) void absorb_quad_kernel(float* __restrict__ st
   // behind it are in flight) and claims it if the tag is another call's; whether this exchange or another
   // workgroup's wins does not matter.  Two round trips to memory, hidden behind the first tiles' latency.
   unsigned long long* const ctr = counters + (size_t)bh * PARTS + quad;
-  const bool claimer = tid == QNT - 64;
+  const bool alone = slices == 1;   // one slice a head: nothing to exchange and nobody to wait for
+  const bool claimer = tid == QNT - 64 && !alone;
   unsigned long long seen = 0;
   if (claimer) asm volatile("global_load_dwordx2 %0, %1, off sc1" : "=&v"(seen) : "v"(ctr) : "memory");
   // every wavefront issues the same two requests per pair (tiles past the end have an empty descriptor), so the
@@ -578,23 +579,25 @@ __global__ __launch_bounds__(QNT) void absorb_quad_kernel(float* __restrict__ st
   const size_t at0 = (size_t)(64 * qa + er) * D + 64 * qb + ec;
   float* const mine = tile + er * LSTR + ec;                                     // the same element in the staged block
   auto at_tile = [&](int p) { return 8 * (p / NV) * LSTR + 64 * (p % NV); };
+  if (!alone) {   // uniform
 #pragma unroll
-  for (int p = 0; p < NP8; ++p)
-    __hip_atomic_store(part + at0 + at(p), mine[at_tile(p)], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  if (qb == 0 && tid < 64)
-    __hip_atomic_store(part + D * D + 64 * qa + tid, zs[tid], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    for (int p = 0; p < NP8; ++p)
+      __hip_atomic_store(part + at0 + at(p), mine[at_tile(p)], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    if (qb == 0 && tid < 64)
+      __hip_atomic_store(part + D * D + 64 * qa + tid, zs[tid], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 
-  // ---- arrival: every store above has been acknowledged before the workgroup draws its ticket
-  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-  __syncthreads();
-  if (tid == 0) {   // (the claim above has long been carried out: the wait behind the loop covers it)
-    const unsigned long long before = __hip_atomic_fetch_add(ctr, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    s_last = (int)(before & 0xffffull) + 1 == slices;
-    // the last one leaves the count at zero under this call's tag: a captured launch replays with the same tag
-    if (s_last) __hip_atomic_store(ctr, tag << 16, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    // ---- arrival: every store above has been acknowledged before the workgroup draws its ticket
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();
+    if (tid == 0) {   // (the claim above has long been carried out: the wait behind the loop covers it)
+      const unsigned long long before = __hip_atomic_fetch_add(ctr, 1ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      s_last = (int)(before & 0xffffull) + 1 == slices;
+      // the last one leaves the count at zero under this call's tag: a captured launch replays with the same tag
+      if (s_last) __hip_atomic_store(ctr, tag << 16, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    __syncthreads();
+    if (!s_last) return;
   }
-  __syncthreads();
-  if (!s_last) return;
 
   // ---- the last workgroup of the part: state += partials in slice order; planes of the updated part
   // (these loads come from memory, not from L2: all eight of a thread for up to four slices are in flight at once)
@@ -613,7 +616,12 @@ __global__ __launch_bounds__(QNT) void absorb_quad_kernel(float* __restrict__ st
   // a batch is added in pairs, so that the rounding grows with the batches)
   constexpr int kBatch = kMap ? 8 : 6;
   const int batches = (slices + kBatch - 1) / kBatch, batch = kMap ? (slices + batches - 1) / batches : kBatch;   // (even ones)
-  for (int s0 = 0; s0 < slices; s0 += batch) {
+  if (alone) {
+#pragma unroll
+    for (int p = 0; p < NP8; ++p) sum[p] += mine[at_tile(p)];
+    if (zrow) zsum += zs[ec];
+  }
+  for (int s0 = 0; s0 < slices && !alone; s0 += batch) {
     float v[kBatch][NP8], zv[kBatch];
 #pragma unroll
     for (int u = 0; u < kBatch; ++u) {

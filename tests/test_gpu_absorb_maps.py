@@ -1,4 +1,4 @@
-"""Rotated and ELU + 1 keys with a workspace (one launch, quadrants or halves of the state): counts of tokens around a tile and a
+"""Keys as they are, rotated or under ELU + 1 with a workspace (one launch, quadrants or halves of the state): counts of tokens around a tile and a
 pair of tiles, one slice and many, heads in one round of the chip and in several; the planes are those of the state.  Against
 the fp64 oracle."""
 import pytest
@@ -15,7 +15,7 @@ DEV = "cuda:0"
 
 
 @pytest.mark.parametrize("heads,n", [(1, 1), (2, 31), (3, 33), (1, 64), (2, 65), (130, 127), (300, 129), (1, 9000), (34, 3000), (64, 1290)])
-@pytest.mark.parametrize("phi,rope", [(hf.HF_PHI_ELU1, False), (hf.HF_PHI_RELU, True), (hf.HF_PHI_ELU1, True)])
+@pytest.mark.parametrize("phi,rope", [(hf.HF_PHI_RELU, False), (hf.HF_PHI_ELU1, False), (hf.HF_PHI_RELU, True), (hf.HF_PHI_ELU1, True)])
 def test_maps(heads, n, phi, rope):
     """A feature rounded to bf16 is off by 2^-9 of itself at most, 2^-9 / sqrt(3) in the mean, of either sign; z is not rounded.
     Twice, on a state that holds something: the second call finds the workspace as the first left it."""
