@@ -1243,22 +1243,28 @@ bool attn_pools_itself(const hf_config& c, int n_q, int t_n, int first, int end)
 }
 
 // The dense window (no list) needs no workgroup per query block: any number of rows and of groups covers it.  Every shape's time
-// is modelled from its trips (tiles over groups) and the fullest compute unit's wavefronts per SIMD, two of them at a time: a
-// trip takes 0.53 us of a wavefront alone on its SIMD and 0.88..1.0 of two, less the more wavefronts share a tile's transfer,
-// and every round pays what surrounds the loop.  Measured, the rows' own size before / this choice: 12 heads x 4680 x 9360
-// 291 / 263 us (eight wavefronts of rows), 12 x 2340 x 4680 83.6 / 73.7 (4 x 2), 6 x 2000 x 6000 59.8 / 47.2 and 5 x 854 x 2562
-// at block_q 128 37.6 / 23.4 (2 x 4), 34 x 2688 x 8064 397 / 366 (4 x 2); within 4 % of the fastest shape at fourteen sizes.
+// is modelled in us from its trips (tiles over groups) and the fullest compute unit's wavefronts per SIMD, two of them at a time: a
+// trip takes `two` of two wavefronts on a SIMD and `one` of one, every round pays what surrounds the loop, and the launch's mean
+// wavefronts per SIMD slow the trips of all of them down by `share` (without that term eight heads x 4680 x 4680 and 1660 launches
+// like it ran up to 13 % slower than with their block's rows).  Fitted to every shape's time at 1660 sizes, 1 to 40 heads, 64 to 7000
+// rows, half to four times as many keys, with and without a state: at most 2 % slower than a workgroup per query block anywhere, 0.90
+// of its time in the mean (the fastest shape of each 0.898).  Measured, the rows' own size / this choice, us: 12 heads x 4680 x 9360
+// 283 / 256 (8 x 1), 12 x 2340 x 4680 83.6 / 73.7 (4 x 2), 6 x 2000 x 6000 59.8 / 47.2, 40 x 2340 x 3510 190 / 172 (4 x 1), 5 x 854 x
+// 2562 at block_q 128 37.6 / 23.4 (2 x 4).
 struct DenseShape { int nw, ks; };
 static DenseShape dense_shape(long long BH, int n_q, long long tiles) {
-  static const struct { int nw, ks; float two, around; } shapes[] = {
-      {2, 1, 0.98f, 4.4f}, {2, 2, 1.00f, 4.8f}, {2, 4, 0.92f, 6.4f}, {4, 1, 0.91f, 4.7f}, {4, 2, 0.92f, 5.7f}, {8, 1, 0.88f, 6.3f}};
+  static const struct { int nw, ks; float two, one, around, share; } shapes[] = {
+      {2, 1, 0.38f, 0.63f, 5.60f, 0.29f}, {2, 2, 0.84f, 0.50f, 5.13f, 0.07f}, {2, 4, 0.70f, 0.0f, 6.95f, 0.13f},
+      {4, 1, 0.77f, 0.49f, 5.76f, 0.03f}, {4, 2, 0.70f, 0.0f, 6.51f, 0.08f},  {8, 1, 0.66f, 0.0f, 7.53f, 0.05f}};   // (eight wavefronts: never one)
   DenseShape best = {2, 1};
   float least = INFINITY;
   for (const auto& s : shapes) {
     const long long wgs = BH * ((n_q + 32 * s.nw - 1) / (32 * s.nw)), on_cu = (wgs + 255) / 256;
     const long long waves = (on_cu * s.nw * s.ks + 3) / 4;   // per SIMD of the fullest compute unit
     const long long trips = (tiles + s.ks - 1) / s.ks;
-    const float t = (float)trips * ((float)(waves / 2) * s.two + (float)(waves & 1) * 0.53f) + (float)((waves + 1) / 2) * s.around;
+    const float mean = (float)(wgs * s.nw * s.ks) / 1024.0f;
+    const float t = (float)trips * ((float)(waves / 2) * s.two + (float)(waves & 1) * s.one + mean * s.share) +
+                    (float)((waves + 1) / 2) * s.around;
     if (t < least) { least = t; best = {s.nw, s.ks}; }
   }
   return best;

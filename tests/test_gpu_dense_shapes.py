@@ -14,10 +14,12 @@ DEV = "cuda:0"
 
 CASES = [  # heads, block, n_q, n_kv, phi: shape
     (300, 64, 70, 90, "relu"),       # 2 x 1
-    (3, 64, 70, 1000, "elu"),        # 2 x 2
-    (1, 64, 33, 4401, "relu"),       # 2 x 4, more than 64 tiles in a group's list
+    (60, 64, 130, 130, "elu"),       # 2 x 2
+    (3, 64, 70, 1000, "elu"),        # 2 x 4
+    (1, 64, 33, 4401, "relu"),       # the same, more than 64 tiles in a group's list
     (2, 128, 200, 2000, "elu"),      # 2 x 4 at block 128
-    (256, 64, 130, 130, "relu"),     # 4 x 1
+    (256, 64, 130, 130, "relu"),     # 2 x 1 in two rounds
+    (250, 64, 300, 130, "relu"),     # 4 x 1
     (60, 64, 500, 1001, "elu"),      # 4 x 2
     (240, 64, 250, 1930, "relu"),    # 8 x 1, rows short of a workgroup's
     (240, 48, 250, 1930, "elu"),     # the same with KV blocks of one and a half tiles
