@@ -31,14 +31,18 @@
  *    select the block before it).
  *  - Launches of different sizes may take different kernels.  bf16 at head_dim 128: launches
  *    that would leave compute units idle let two groups of wavefronts share a query block's
- *    list.  bf16 at head_dim 64 and fp32: the rows of a workgroup and the groups that share
- *    a list follow the number of query rows in the launch and the length of the lists (at
- *    head_dim 64 also whether there is a state), and in fp32, with blocks that are multiples
- *    of 64 queries and 32 keys, so does the instruction: products are formed in fp32, or as
- *    six bf16 products of values split in three, off by 2^-24 of themselves at most.  A head
- *    on its own and the same head among many may therefore differ by the rounding of fp32
- *    products and sums (in bf16 a last bit here and there, in fp32 some 1e-6); block lists
- *    and scores are the same bits, and so are calls of one size with or without an absorb.
+ *    list; the dense window takes 64, 128 or 256 rows a workgroup, whose keys one, two or four
+ *    groups share, by a model of the launch.  bf16 at head_dim 64 and fp32: the rows of a
+ *    workgroup and the groups that share a list follow the number of query rows in the launch
+ *    and the length of the lists (at head_dim 64 also whether there is a state), and in fp32,
+ *    with blocks that are multiples of 64 queries and 32 keys, so does the instruction:
+ *    products are formed in fp32, or as six bf16 products of values split in three, off by
+ *    2^-24 of themselves at most.  A head on its own and the same head among many may
+ *    therefore differ by the rounding of fp32 products and sums (in bf16 a last bit here and
+ *    there, in fp32 some 1e-6), and so may a small fp32 step of a stream or ring
+ *    (hf_stream_step, hf_ring_step, hf_ring_last_step) and the separate calls of its size;
+ *    block lists and scores are the same bits, and so are calls of one size with or without
+ *    an absorb.
  *  - Return value: HF_OK (0) or a negative HF_ERR_* code; on error nothing was enqueued
  *    and hf_last_error() describes the problem.  No C++ exception crosses this boundary.
  *
@@ -144,8 +148,8 @@ HF_API int hf_absorb_workspace_bytes(const hf_config* cfg, int32_t n_tokens, siz
  * state from different streams are allowed only if the caller orders them).
  * workspace: optional scratch of >= hf_absorb_workspace_bytes(...) bytes, 256-byte aligned;
  * with it the partial sums of a head's token slices meet there and are added in a fixed order
- * (fast path: one launch for bf16, head_dim 128, ReLU, no rotation; results do not vary from run
- * to run), with NULL (or too small a buffer) they are added to the state with float atomics.
+ * (bf16, head_dim 128, either feature map, rotated or not: one launch; results do not vary from
+ * run to run), with NULL (or too small a buffer) they are added to the state with float atomics.
  * Same result up to fp32 summation order.  The workspace needs no initialisation; two calls that
  * may overlap in time must not share one. */
 HF_API int hf_absorb_evicted(const hf_config* cfg, void* state,
@@ -155,10 +159,11 @@ HF_API int hf_absorb_evicted(const hf_config* cfg, void* state,
 
 /* ---- The state's bf16 planes, kept by the caller (bf16, head_dim 128, block_q 64 or 128 only) ----------
  * The history term of Eq. 3 is evaluated on the matrix cores from two bf16 planes of L (high part and
- * remainder, transposed).  hf_hybrid_attn_fwd derives them from the state on every call; the state changes
- * only when tokens are absorbed (Eq. 2), so a caller may keep the planes next to the state instead:
- * hf_absorb_evicted_planes writes them from the kernel that writes the state, hf_hybrid_attn_fwd_planes
- * reads them.  Outputs are bit-identical to the ordinary calls.  The caller owns the buffer and the
+ * remainder, transposed).  hf_hybrid_attn_fwd derives them from the state on every call (small launches round
+ * the state inside the attention kernel instead, to the same bits); the state changes only when tokens are
+ * absorbed (Eq. 2), so a caller may keep the planes next to the state instead: hf_absorb_evicted_planes writes
+ * them from the kernel that writes the state, hf_hybrid_attn_fwd_planes reads them.  Outputs are bit-identical
+ * to the ordinary calls.  The caller owns the buffer and the
  * invariant: whatever else writes the state (hf_state_init, hf_state_fold_linear, hf_window_evict, a
  * copy) must be followed by hf_state_planes before the planes are used again. */
 
@@ -278,8 +283,9 @@ HF_API int hf_ring_step(const hf_config* cfg, const hf_ring* ring, const void* Q
  * state_out as the state from then on, absorbs nothing.  While a slot is still free the next chunk evicts nothing:
  * state_out is not written and *absorbed_out = 0 (the caller keeps `state`).
  * Where hf_step_fwd applies (bf16, head_dim 128, block_q 64 or 128, ReLU, no rotation of the absorbed keys, default
- * flags) the absorb runs in workgroups of the attention launch; elsewhere the state is copied and the chunk absorbed
- * by launches of their own behind the step.  state_or_null NULL with a full ring: the chunk starts a state from zero.
+ * flags), and in small fp32 rings (chunks of at most 1024 tokens), the absorb runs in workgroups of the attention
+ * launch; elsewhere the state is copied and the chunk absorbed by launches of their own behind the step.
+ * state_or_null NULL with a full ring: the chunk starts a state from zero.
  *   state_out        fp32 state buffer, must not overlap `state` or any other argument
  *   rope_*_ev        tables for the n_chunk absorbed tokens or both NULL (as hf_ring_open_chunk)
  *   step_workspace   >= max(hf_step_workspace_bytes(cfg, n_chunk, n_chunk), hf_absorb_workspace_bytes(cfg, n_chunk))

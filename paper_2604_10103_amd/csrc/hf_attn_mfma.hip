@@ -1223,7 +1223,7 @@ constexpr int kMfmaMaxKeys = 1 << 23;
 // workgroups takes as long as one of 1537).
 // hf_step_fwd, one / two groups: 2 heads x 15 blocks 27.7 / 25.6 us, 4 x 33 32.8 / 25.3, 6 x 43 48.3 / 38.0, 8 x 52 55.5 / 43.4,
 // 12 x 47 56.9 / 61.2, 16 x 66 128 / 120, 16 x 74 143 / 133, 24 x 74 196 / 206; block_q 128: 4 x 24 41.3 / 37.0, 8 x 36 73 / 90.
-// (Four groups of two wavefronts were never better than two.)
+// (Four groups of two wavefronts were not better than two at these sizes; the dense window takes them for few rows over many keys.)
 // Every launch counts two absorbing workgroups per head, also one that absorbs nothing: hf_step_fwd and hf_select_attn_fwd
 // then run the same instance for the same Q, K, V and give the same bits.  (The attending workgroups alone would send steps
 // of just one full round to two groups, whose absorbing workgroups wait for the round's end.)
@@ -1249,7 +1249,7 @@ bool attn_pools_itself(const hf_config& c, int n_q, int t_n, int first, int end)
 // like it ran up to 13 % slower than with their block's rows).  Fitted to every shape's time at 1660 sizes, 1 to 40 heads, 64 to 7000
 // rows, half to four times as many keys, with and without a state: at most 2 % slower than a workgroup per query block anywhere, 0.90
 // of its time in the mean (the fastest shape of each 0.898).  Measured, the rows' own size / this choice, us: 12 heads x 4680 x 9360
-// 283 / 256 (8 x 1), 12 x 2340 x 4680 83.6 / 73.7 (4 x 2), 6 x 2000 x 6000 59.8 / 47.2, 40 x 2340 x 3510 190 / 172 (4 x 1), 5 x 854 x
+// 285 / 252 (8 x 1), 12 x 2340 x 4680 83.6 / 73.7 (4 x 2), 6 x 2000 x 6000 59.8 / 47.2, 40 x 2340 x 3510 190 / 172 (4 x 1), 5 x 854 x
 // 2562 at block_q 128 37.6 / 23.4 (2 x 4).
 struct DenseShape { int nw, ks; };
 static DenseShape dense_shape(long long BH, int n_q, long long tiles) {

@@ -1,6 +1,6 @@
-"""Keys as they are, rotated or under ELU + 1 with a workspace (one launch, quadrants or halves of the state): counts of tokens around a tile and a
-pair of tiles, one slice and many, heads in one round of the chip and in several; the planes are those of the state.  Against
-the fp64 oracle."""
+"""Keys as they are, rotated or under ELU + 1 with a workspace (one launch, quadrants or halves of the state): counts of tokens around a
+tile and a pair of tiles, one slice (which exchanges nothing) and many, heads in one round of the chip and in several; the planes
+are those of the state.  Against the fp64 oracle."""
 import pytest
 import torch
 
