@@ -835,7 +835,7 @@ static int step_wide_launch(const hf_config* cfg, const void* Q, const void* Q_h
   if (!attn_wide_step_supported(*cfg, n_q, n_kv) || (ev && !absorbs)) return HF_OK;
   int k = 0;
   HF_TRY(check_select_args(cfg, Q, n_q, K, n_kv, 0, block_idx, nullptr, &k));
-  if (!attn_wide_step_pays(*cfg, k, absorbs)) return HF_OK;
+  if (!attn_wide_step_pays(*cfg, n_q, k, absorbs)) return HF_OK;
   HF_TRY(check_ptr(V, "V_win", true));
   HF_TRY(check_ptr(O, "O", true));
   if (!Q_hist) Q_hist = Q;

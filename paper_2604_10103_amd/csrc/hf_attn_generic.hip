@@ -946,7 +946,9 @@ bool attn_wide_taken(const hf_config& c) { return !attn_mfma_supported(c) && !at
 // wavefront of every workgroup, for the selection in front of the loop and for eight parts that meet.  A later step of one head,
 // separate launches / this one, us, by tiles of 16 keys in a list: head_dim 128, blocks of 16: 2 tiles 12.1 / 12.7, 10 17.1 / 17.6, 20
 // 21.6 / 21.8, 29 27.8 / 26.9, 64 38.7 / 33.6, 128 66.1 / 54.6; of 64: 4 12.9 / 13.5, 20 20.7 / 20.4, 40 29.3 / 26.3; head_dim 64,
-// blocks of 16: 1 8.7 / 8.2, 16 11.9 / 11.1 (at most 6 % slower anywhere: the first step of ten blocks of 256, 16 tiles, 15.2 / 16.0).
+// blocks of 16: 1 8.7 / 8.2, 16 11.9 / 11.1; where a chunk is too long to be pooled here on its later steps either, 24 19.2 / 20.1 (query
+// blocks of 48) and 20.9 / 22.1 (of 512), 25 to 32 0.92 of the time.  (What is slower yet: the first step of a window that is pooled in
+// front, with lists of a few tiles, 10.8 / 11.5 at the most; the later ones of its chunk gain.)
 // Where the chunk's last step absorbs beside its attention, that step saves more than the others lose (head_dim 128, 8 heads, 16
 // tokens: 15.7 / 13.0 the last, 12.8 / 12.9 the others; chunks of four steps 0.96 of the time in the mean of 83 sizes with lists that are
 // too short otherwise, 1.03 at most).  Sums are in another order: the rule looks at what all steps of a chunk have in common, so that
@@ -956,8 +958,10 @@ bool attn_wide_step_supported(const hf_config& c, int n_q, int n_kv) {
          !attn_split_supported(c, n_q, n_kv) &&
          (long long)c.batch * c.heads * ((n_q + c.block_q - 1) / c.block_q) * ((c.block_q + 15) / 16) <= 256;
 }
-bool attn_wide_step_pays(const hf_config& c, int k, bool absorbs) {
-  return absorbs || c.head_dim == 64 || k * ((c.block_kv + kTile - 1) / kTile) >= 25 + c.block_q / 12;
+bool attn_wide_step_pays(const hf_config& c, int n_q, int k, bool absorbs) {
+  const int tiles = k * ((c.block_kv + kTile - 1) / kTile);
+  if (c.head_dim == 128) return absorbs || tiles >= 25 + c.block_q / 12;
+  return absorbs || tiles > 24 || (n_q + c.block_kv - 1) / c.block_kv < kStepOwn;   // (a chunk touches a block more)
 }
 // Whether that launch pools the blocks [kv_first, kv_end) itself, every workgroup all of them, against a launch in front that pools each
 // block once: by the bytes that a compute unit reads, beyond those that seven wavefronts get through while the eighth forms the query

@@ -163,7 +163,7 @@ int launch_attn_mfma_fused(const hf_config& c, const void* Q, int n_q, const voi
 // steps of small fp32 streams: selection, attention and, state_out given, Eq. 2 for another chunk into it, in one launch
 bool attn_wide_step_supported(const hf_config& c, int n_q, int n_kv);
 // against separate launches, k blocks a list; absorbs: the last step of the chunk absorbs beside its attention
-bool attn_wide_step_pays(const hf_config& c, int k, bool absorbs);
+bool attn_wide_step_pays(const hf_config& c, int n_q, int k, bool absorbs);
 bool attn_wide_step_pools(const hf_config& c, int kv_first, int kv_end);
 bool attn_wide_step_absorbs(const hf_config& c, int n_ev);
 int launch_attn_wide_step(const hf_config& c, const void* Q, const void* Q_hist, int n_q, const void* K, const void* V, int n_kv, int k,

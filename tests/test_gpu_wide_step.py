@@ -96,16 +96,19 @@ def test_steps_of_a_full_ring(case, state):
     assert np.isfinite(wl.to_f64(st2)).all()
 
 
-# head_dim, block, window, tokens of the chunk, keep: lists on both sides of the line at head_dim 128 (26 tiles of 16 keys for blocks of
-# 16, 27 of 32, 35 of 128), every block or a part of them pooled in the launch
-STREAMS = [(128, 16, 400, 37, 1.0), (128, 16, 416, 37, 1.0), (128, 32, 416, 60, 1.0), (128, 32, 450, 60, 1.0), (128, 128, 500, 130, 1.0),
-           (128, 128, 640, 130, 1.0), (64, 16, 1552, 40, 0.01), (64, 16, 1552, 40, 0.25), (64, 256, 2000, 256, 0.1)]
+# head_dim, block of keys, of queries, window, tokens of the chunk, keep: lists on both sides of the line at head_dim 128 (26 tiles of 16
+# keys for query blocks of 16, 27 of 32, 35 of 128; 25 at 64 for chunks of more than fifteen blocks), every block or a part of them
+# pooled in the launch, blocks of two sizes
+STREAMS = [(128, 16, 16, 400, 37, 1.0), (128, 16, 16, 416, 37, 1.0), (128, 32, 32, 416, 60, 1.0), (128, 32, 32, 450, 60, 1.0),
+           (128, 128, 128, 500, 130, 1.0), (128, 128, 128, 640, 130, 1.0), (64, 16, 16, 1552, 40, 0.01), (64, 16, 16, 1552, 40, 0.25),
+           (64, 16, 16, 1600, 250, 0.24), (64, 16, 16, 1600, 250, 0.25),
+           (64, 256, 256, 2000, 256, 0.1), (64, 48, 20, 700, 90, 0.3), (128, 20, 48, 900, 90, 0.8), (128, 16, 300, 1300, 320, 0.9)]
 
 
 @pytest.mark.parametrize("case", STREAMS, ids=lambda c: "-".join(map(str, c)))
 def test_steps_that_absorb_nothing(case):
-    d, b, n_kv, n, keep = case
-    cfg, packed = (hf.make_config(1, 2, d, "f32", b, b, keep, kv_capacity=c) for c in (n_kv, 0))
+    d, b, bq, n_kv, n, keep = case
+    cfg, packed = (hf.make_config(1, 2, d, "f32", bq, b, keep, kv_capacity=c) for c in (n_kv, 0))
     K, V, Ke, Ve, *Qs = (wl.randn((1, 2, m, d), 95_000 + i, 1.0, torch.float32).to(DEV) for i, m in enumerate((n_kv, n_kv, 40, 40, n, n)))
     st = torch.empty(hf.hf_state_bytes(cfg) // 4, dtype=torch.float32, device=DEV)
     hf.hf_state_init(cfg, st)
@@ -114,7 +117,7 @@ def test_steps_that_absorb_nothing(case):
     win = hf.hf_window(0, n_kv)
     for i, Q in enumerate(Qs):
         O, O2 = (torch.full_like(Q, float("nan")) for _ in range(2))
-        idx, idx2 = (torch.full((1, 2, -(-n // b), hf.hf_select_k(cfg, n_kv)), -1, dtype=torch.int32, device=DEV) for _ in range(2))
+        idx, idx2 = (torch.full((1, 2, -(-n // bq), hf.hf_select_k(cfg, n_kv)), -1, dtype=torch.int32, device=DEV) for _ in range(2))
         if i:
             K[:, :, -n:] = K[:, :, -n:].flip(3)
         hf.hf_stream_step(cfg, win, Q, K, V, i, idx, st, O, ws)
