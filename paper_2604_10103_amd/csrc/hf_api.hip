@@ -141,7 +141,8 @@ static WorkspaceLayout workspace_layout(const hf_config* c, int n_q, int n_kv) {
 }
 
 struct BwdLayout {
-  size_t lse2, dvec, inv_cnt, inv_list, order, planes, total;  // byte offsets
+  size_t lse2, dvec, inv_cnt, inv_list, order, planes, total;  // byte offsets; total: what a call needs
+  size_t inv_slot, scores;                                     // behind it, for calls that store their scores
 };
 
 static BwdLayout bwd_layout(const hf_config* c, int n_q, int n_kv) {
@@ -155,6 +156,8 @@ static BwdLayout bwd_layout(const hf_config* c, int n_q, int n_kv) {
   w.order = w.inv_list + align256(bh * t_n * t_m * 4);   // launch order of the dK/dV workgroups (64 keys each):
   w.planes = w.order + align256(bh * t_n * cdiv(c->block_kv, 64) * 8 * 4);   // records of 8 words
   w.total = w.planes + align256(bwd_planes_bytes(*c));
+  w.inv_slot = w.total;
+  w.scores = w.inv_slot + align256(bh * t_n * t_m * 4);
   return w;
 }
 
@@ -1113,12 +1116,20 @@ int hf_ring_last_step(const hf_config* cfg, hf_ring* ring, const void* Q, const 
   return HF_OK;
 }
 
+// the bf16 gradient kernels (else those of fp32 arithmetic)
+static bool bwd_mfma_taken(const hf_config& c, bool saved) {
+  return bwd_mfma_supported(c) && (saved || !(c.flags & HF_FLAG_BWD_FP32_KERNELS));
+}
+
 int hf_bwd_workspace_bytes(const hf_config* cfg, int32_t n_q, int32_t n_kv, size_t* bytes_out) {
   HF_TRY(check_cfg(cfg));
   if (!bytes_out) { set_error("bytes_out is NULL"); return HF_ERR_NULL; }
   HF_TRY(check_tokens(n_q, "n_q"));
   HF_TRY(check_tokens(n_kv, "n_kv"));
-  *bytes_out = bwd_layout(cfg, n_q, n_kv).total;
+  const BwdLayout w = bwd_layout(cfg, n_q, n_kv);
+  const int t_n = cdiv(n_kv, cfg->block_kv), k = select_k_of(cfg, t_n);
+  const size_t scores = bwd_mfma_taken(*cfg, false) ? 0 : bwd_scores_bytes(*cfg, n_q, k < t_n ? k : t_n);
+  *bytes_out = scores ? w.scores + scores : w.total;
   return HF_OK;
 }
 
@@ -1215,7 +1226,7 @@ static int bwd_impl(const hf_config* cfg, const void* Q, const void* Q_hist, int
   int32_t* inv_list = block_idx ? reinterpret_cast<int32_t*>(ws + w.inv_list) : nullptr;
   const float* st = static_cast<const float*>(state_or_null);
 
-  const bool mfma = bwd_mfma_supported(*cfg) && (saved || !(cfg->flags & HF_FLAG_BWD_FP32_KERNELS));
+  const bool mfma = bwd_mfma_taken(*cfg, saved);
   if (split && !st) {
     const size_t bytes = (size_t)cfg->batch * cfg->heads * n_q * cfg->head_dim * esize(cfg);
     HF_TRY(launch_fill_zero(static_cast<float*>(dQ_hist), bytes / 4, s));
@@ -1224,16 +1235,21 @@ static int bwd_impl(const hf_config* cfg, const void* Q, const void* Q_hist, int
     // row statistics of the softmax and D = dO . O_local: saved by the forward pass (D then from the once rounded O_local),
     // or from a recomputed one (unrounded); the history branch rides in the dQ kernel's epilogue
     int32_t* order = block_idx && !(cfg->flags & HF_FLAG_DKV_INDEX_ORDER) ? reinterpret_cast<int32_t*>(ws + w.order) : nullptr;
-    HF_TRY(launch_bwd_prep(*cfg, block_idx, k, t_m, t_n, inv_cnt, inv_list, order, st, ws + w.planes, saved ? dO : nullptr,
+    HF_TRY(launch_bwd_prep(*cfg, block_idx, k, t_m, t_n, inv_cnt, inv_list, nullptr, order, st, ws + w.planes, saved ? dO : nullptr,
                            O_local, (long long)cfg->batch * cfg->heads * n_q, dvec, s));
     if (!saved) HF_TRY(launch_attn_mfma_stats(*cfg, Q, n_q, K_win, V_win, n_kv, block_idx, k, dO, lse2, dvec, s));
     return launch_bwd_mfma(*cfg, Q, n_q, K_win, V_win, n_kv, block_idx, k, dO, saved ? lse2_saved : lse2, dvec, inv_cnt, inv_list,
                            order, st, rope_cos_q, rope_sin_q, Q_hist, ws + w.planes, dQ, dQ_hist, dK, dV, s);
   }
-  HF_TRY(launch_bwd_prep(*cfg, block_idx, k, t_m, t_n, inv_cnt, inv_list, nullptr, nullptr, nullptr, nullptr, nullptr, 0, nullptr, s));
-  HF_TRY(launch_attn_wide_stats(*cfg, Q, n_q, K_win, V_win, n_kv, block_idx, k, dO, lse2, dvec, s));
-  return launch_bwd_generic(*cfg, Q, Q_hist, n_q, K_win, V_win, n_kv, block_idx, k, dO, lse2, dvec, inv_cnt, inv_list, st,
-                            rope_cos_q, rope_sin_q, dQ, st ? dQ_hist : nullptr, dK, dV, s);
+  // scores kept in the workspace where it has room for them (callers may have kept one of the size that has none), else every
+  // kernel forms its own, behind a forward pass for the statistics
+  const size_t score_bytes = bwd_scores_bytes(*cfg, n_q, k);
+  float* scores = score_bytes && workspace_bytes >= w.scores + score_bytes ? reinterpret_cast<float*>(ws + w.scores) : nullptr;
+  int32_t* inv_slot = scores && block_idx ? reinterpret_cast<int32_t*>(ws + w.inv_slot) : nullptr;
+  HF_TRY(launch_bwd_prep(*cfg, block_idx, k, t_m, t_n, inv_cnt, inv_list, inv_slot, nullptr, nullptr, nullptr, nullptr, nullptr, 0, nullptr, s));
+  if (!scores) HF_TRY(launch_attn_wide_stats(*cfg, Q, n_q, K_win, V_win, n_kv, block_idx, k, dO, lse2, dvec, s));
+  return launch_bwd_generic(*cfg, Q, Q_hist, n_q, K_win, V_win, n_kv, block_idx, k, dO, lse2, dvec, inv_cnt, inv_list, inv_slot,
+                            scores, st, rope_cos_q, rope_sin_q, dQ, st ? dQ_hist : nullptr, dK, dV, s);
 }
 
 int hf_rope_window_indices(int32_t i_newest, int32_t n_frames, int32_t t0, int32_t* idx_out) {

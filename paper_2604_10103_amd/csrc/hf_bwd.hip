@@ -11,6 +11,7 @@
 //     dQ_i = scale sum_j dS_ij k_j         dK_j = scale sum_i dS_ij q_i
 // dQ walks the index list of its query block; dK, dV walk the inverse list (the query blocks that
 // selected a KV block), so both accumulate in registers and nothing is added atomically.
+#include <float.h>
 #include <math.h>
 
 #include "hf_f32_mfma.h"
@@ -23,20 +24,26 @@ namespace {
 // the hits in order.
 __global__ __launch_bounds__(256) void invert_index_kernel(const int32_t* __restrict__ idx, int k, int t_m, int t_n,
                                                            int32_t* __restrict__ inv_cnt,
-                                                           int32_t* __restrict__ inv_list) {
+                                                           int32_t* __restrict__ inv_list,
+                                                           int32_t* __restrict__ inv_slot) {
   const int lane = threadIdx.x & 63;
   const int j = blockIdx.x * 4 + (threadIdx.x >> 6), bh = blockIdx.y;
   if (j >= t_n) return;
   const int32_t* rows = idx + (size_t)bh * t_m * k;
   int32_t* out = inv_list + ((size_t)bh * t_n + j) * t_m;
+  int32_t* slots = inv_slot ? inv_slot + ((size_t)bh * t_n + j) * t_m : nullptr;
   int cnt = 0;
   for (int i0 = 0; i0 < t_m; i0 += kWave) {
     const int i = i0 + lane;
-    bool hit = false;
+    int at = -1;
     if (i < t_m)
-      for (int s = 0; s < k; ++s) hit |= rows[(size_t)i * k + s] == j;   // by contract a row lists a block at most once
-    const unsigned long long mask = __ballot(hit);
-    if (hit) out[cnt + __popcll(mask & ((1ull << lane) - 1ull))] = i;
+      for (int s = 0; s < k; ++s) at = rows[(size_t)i * k + s] == j ? s : at;   // by contract a row lists a block at most once
+    const unsigned long long mask = __ballot(at >= 0);
+    if (at >= 0) {
+      const int place = cnt + __popcll(mask & ((1ull << lane) - 1ull));
+      out[place] = i;
+      if (slots) slots[place] = at;
+    }
     cnt += __popcll(mask);
   }
   if (lane == 0) inv_cnt[(size_t)bh * t_n + j] = cnt;
@@ -58,6 +65,7 @@ struct PrepArgs {
   int k, t_m, t_n;
   int order_wgs, invert_wgs, plane_wgs;
   int32_t *inv_cnt, *inv_list;   // [BH][t_n], [BH][t_n][t_m]
+  int32_t* inv_slot;             // [BH][t_n][t_m] or NULL: the block's place in the row of each query block on its list
   int slabs, items_per_xcd, total_items;
   int32_t* order;                // [8 items_per_xcd][kOrderRec]
   const float* state;
@@ -67,13 +75,11 @@ struct PrepArgs {
   float* dots;
 };
 
-// The inverse lists as bit masks in LDS: for KV blocks [b0, b0 + n) (numbered over all heads) one bit per query block that
-// selected it, 32 to a word.  One pass over the index rows of the heads they belong to, every entry on its own; a block's
-// list is then the positions of its bits, its length their number, and bit i stands at the number of bits below it.
-__device__ __forceinline__ void selected_by(uint32_t* mask, const PrepArgs& p, int b0, int n, int words) {
+// every entry of the index rows of the heads that KV blocks [b0, b0 + n) (numbered over all heads) belong to, every thread
+// its share: f(block - b0, query block, place in the row) for the entries that lie in the range
+template <typename F>
+__device__ __forceinline__ void each_entry(const PrepArgs& p, int b0, int n, F f) {
   const int tid = threadIdx.x;
-  for (int e = tid; e < n * words; e += kPrepThreads) mask[e] = 0;
-  __syncthreads();
   const int row_words = p.t_m * p.k;   // entries of a head
   const int h0 = b0 / p.t_n, entries = ((b0 + n - 1) / p.t_n - h0 + 1) * row_words;
   const int32_t* src = p.idx + (size_t)h0 * row_words;
@@ -92,9 +98,17 @@ __device__ __forceinline__ void selected_by(uint32_t* mask, const PrepArgs& p, i
         at += p.t_n;
       }
       const int j = entry[u], i = p.k == 1 ? e : (int)__umulhi((uint32_t)e, per_k);
-      if ((unsigned)j < (unsigned)p.t_n && (unsigned)(at + j) < (unsigned)n) atomicOr(&mask[(at + j) * words + (i >> 5)], 1u << (i & 31));
+      if ((unsigned)j < (unsigned)p.t_n && (unsigned)(at + j) < (unsigned)n) f(at + j, i, e - i * p.k);
     }
   }
+}
+
+// The inverse lists as bit masks in LDS: for KV blocks [b0, b0 + n) one bit per query block that selected it, 32 to a word.
+// A block's list is then the positions of its bits, its length their number, and bit i stands at the number of bits below it.
+__device__ __forceinline__ void selected_by(uint32_t* mask, const PrepArgs& p, int b0, int n, int words) {
+  for (int e = threadIdx.x; e < n * words; e += kPrepThreads) mask[e] = 0;
+  __syncthreads();
+  each_entry(p, b0, n, [&](int block, int i, int) { atomicOr(&mask[block * words + (i >> 5)], 1u << (i & 31)); });
   __syncthreads();
 }
 
@@ -186,6 +200,15 @@ __global__ __launch_bounds__(kPrepThreads) void bwd_prep_kernel(PrepArgs p) {
         below += __popcll(both);
       }
       if (lane == 0) p.inv_cnt[(size_t)wg * p.t_n + j] = below;
+    }
+    if (p.inv_slot) {
+      int32_t* const slots = p.inv_slot + (size_t)wg * p.t_n * p.t_m;
+      each_entry(p, wg * p.t_n, p.t_n, [&](int j, int i, int slot) {
+        const uint32_t* m = mask + j * words;
+        int below = __popc(m[i >> 5] & ((1u << (i & 31)) - 1u));
+        for (int w = 0; w < i >> 5; ++w) below += __popc(m[w]);
+        slots[(size_t)j * p.t_m + below] = slot;
+      });
     }
     return;
   }
@@ -299,48 +322,220 @@ __device__ __forceinline__ void add_parts_and_store(float* smem, const f32x4 (&a
   }
 }
 
-// ---- dQ: a workgroup per 16 NQ query rows; S^T and dP^T = V dO^T (row form), dS^T = P^T (dP^T - D), dQ^T += K^T dS^T
-// (column form), all on 16 x 16 x 4 fp32 products.  Q and dO wait in LDS (B operands, shared by the four wavefronts); the
-// keys' and values' pieces travel one product phase ahead, each into the registers of a piece that has just been used.
-// Bound by the fp32 matrix rate.  12 heads of 128, 1170 x 2340, k = 10 of 37 blocks of 64: 88 us (0.71 ms with one key per
-// lane and FMA arithmetic, plus 0.21 ms for the history branch's gradient as a kernel of its own).
+struct WideBwd {
+  const void *Q, *K, *V, *dO;
+  const int32_t* idx;                              // [BH][t_m][k] or NULL (dense: k = t_n)
+  int k, n_q, n_kv, kv_stride, bq, bkv, t_m, t_n;
+  int q_chunks, q_per_xcd, q_total;                // workgroups of the query side: chunks of a block, items of an XCD's share, items
+  int k_chunks, k_per_xcd, k_total;                // of the key side
+  float scale_log2e, scale;
+  float *lse2, *Dv;                                // [BH][n_q]
+  const int32_t *inv_cnt, *inv_list, *inv_slot;    // [BH][t_n], [BH][t_n][t_m]; dense: NULL
+  float* scores;                                   // stored scores, see bwd_scores_kernel
+  WideBwdHist hist;
+  void *dQ, *dK, *dV;
+};
+
+// Stored scores: a panel per (query block, place of its list), a panel's tiles of 16 queries x 16 keys row by row, a tile's S
+// [query][key] (times scale log2 e) and then its dP.
+constexpr int kScoreTile = 2 * 16 * 16;
+constexpr size_t kScoresMax = (size_t)2 << 30;
+__device__ __forceinline__ const float* score_tile(const WideBwd& a, int bh, int qb, int slot, int qi, int ki) {
+  const int qt = (a.bq + 15) / 16, kt = (a.bkv + 15) / 16;
+  return a.scores + ((((size_t)bh * a.t_m + qb) * a.k + slot) * (qt * kt) + qi * kt + ki) * kScoreTile;
+}
+
+// ---- S^T = K Q^T and dP^T = V dO^T, once for all three gradients: a workgroup per 16 NQ query rows, its four wavefronts
+// splitting the list; both go to memory as fp32 (score_tile), and lse2 and D = sum_j P_ij dP_ij leave with them, so that no
+// forward pass is formed again: five products of the forward's size instead of nine (two of the statistics, three for dQ, four
+// for dK and dV).  Statistics are a lane's own until the end: maximum, sum and weighted sum over the keys it holds.
 template <typename T, int D, int NQ>
-__global__ __launch_bounds__(64 * kParts, 2) void bwd_dq_wide_kernel(
-    const T* __restrict__ Q, const T* __restrict__ K, const T* __restrict__ V, const T* __restrict__ dO,
-    const int32_t* __restrict__ idx, int k, int n_q, int n_kv, int kv_stride, int bq, int bkv, int t_m, int t_n, int chunks,
-    int per_xcd, int total, float scale_log2e, float scale, const float* __restrict__ lse2, const float* __restrict__ Dv,
-    WideBwdHist hist, T* __restrict__ dQ) {
-  constexpr int ROWS = 16 * NQ, C = D / 16, F = D / 64, OST = D + 4;
-  extern __shared__ __attribute__((aligned(16))) float smem[];   // [ROWS][OST] Q, [ROWS][OST] dO; later four partial results
-  __shared__ float gpart[ROWS][kParts];
+__global__ __launch_bounds__(64 * kParts, 2) void bwd_scores_kernel(WideBwd a) {
+  constexpr int ROWS = 16 * NQ, C = D / 16, OST = D + 4;
+  extern __shared__ __attribute__((aligned(16))) float smem[];   // [ROWS][OST] Q, [ROWS][OST] dO
+  __shared__ float stat[3][kParts][ROWS];
   float* sQ = smem;
   float* sG = smem + ROWS * OST;
-  const int item = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
-  if ((int)(blockIdx.x >> 3) >= per_xcd || item >= total) return;
-  const int bh = item / (t_m * chunks), in_head = item - bh * t_m * chunks;
-  const int qb = in_head / chunks, row0 = qb * bq + (in_head - qb * chunks) * ROWS;
+  const int wg = blockIdx.x, item = (wg & 7) * a.q_per_xcd + (wg >> 3);
+  if ((wg >> 3) >= a.q_per_xcd || item >= a.q_total) return;
+  const int n_q = a.n_q, n_kv = a.n_kv, bq = a.bq, bkv = a.bkv, t_n = a.t_n;
+  const int bh = item / (a.t_m * a.q_chunks), in_head = item - bh * a.t_m * a.q_chunks;
+  const int qb = in_head / a.q_chunks, row0 = qb * bq + (in_head - qb * a.q_chunks) * ROWS;
   const int q_end = min(n_q, (qb + 1) * bq);
   if (row0 >= q_end) return;
   const int lane = threadIdx.x & 63, kz = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int l16 = lane & 15, g = lane >> 4;
-  const T* Kh = K + (size_t)bh * kv_stride * D;
-  const T* Vh = V + (size_t)bh * kv_stride * D;
-  const int32_t* row_idx = idx ? idx + ((size_t)bh * t_m + qb) * k : nullptr;
-  const int nsel = idx ? k : t_n, subs = (bkv + 15) / 16, ntiles = nsel * subs;
-
+  const T* __restrict__ Q = static_cast<const T*>(a.Q);
+  const T* __restrict__ dO = static_cast<const T*>(a.dO);
+  const T* __restrict__ Kh = static_cast<const T*>(a.K) + (size_t)bh * a.kv_stride * D;
+  const T* __restrict__ Vh = static_cast<const T*>(a.V) + (size_t)bh * a.kv_stride * D;
+  const int32_t* __restrict__ row_idx = a.idx ? a.idx + ((size_t)bh * a.t_m + qb) * a.k : nullptr;
+  const int nsel = a.idx ? a.k : t_n, subs = (bkv + 15) / 16, ntiles = nsel * subs;
+  const int qt = (bq + 15) / 16, qi0 = (row0 - qb * bq) / 16;
   for (int e = threadIdx.x; e < ROWS * (D / 4); e += 64 * kParts) {
     const int rr = e / (D / 4), c4 = e - rr * (D / 4);
     const size_t off = ((size_t)bh * n_q + min(row0 + rr, n_q - 1)) * D + 4 * c4;
-    *reinterpret_cast<f32x4*>(sQ + rr * OST + 4 * c4) = load4<T>(Q + off) * scale_log2e;
+    *reinterpret_cast<f32x4*>(sQ + rr * OST + 4 * c4) = load4<T>(Q + off) * a.scale_log2e;
     *reinterpret_cast<f32x4*>(sG + rr * OST + 4 * c4) = load4<T>(dO + off);
   }
+  __syncthreads();
+  auto tile_at = [&](int t, int& first, int& cnt) {   // cnt 0: past the list, an index out of range, or no such keys
+    const int s = t / subs, sub = t - s * subs;
+    const int jb = row_idx ? row_idx[min(s, nsel - 1)] : s;
+    const int st = jb * bkv + 16 * sub;
+    const bool ok = s < nsel && (unsigned)jb < (unsigned)t_n;
+    const int n = ok ? min(16, min(n_kv, (jb + 1) * bkv) - st) : 0;
+    cnt = n > 0 ? n : 0;
+    first = n > 0 ? st : 0;
+  };
+  constexpr int B = sizeof(T);
+  int row_at = (l16 * D + 4 * g) * B;   // rows behind a tile's last real key read as zeros
+  Piece<T> kr[C], vr[C];
+  int first, cnt, first_n, cnt_n;
+  tile_at(kz, first, cnt);
+  {
+    const __amdgpu_buffer_rsrc_t k_rows = tile_rows<T, D>(Kh, first, cnt), v_rows = tile_rows<T, D>(Vh, first, cnt);
+#pragma unroll
+    for (int c = 0; c < C; ++c) {
+      kr[c].load(k_rows, row_at + 16 * c * B);
+      vr[c].load(v_rows, row_at + 16 * c * B);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  }
+  float m[NQ], l[NQ], d[NQ];
+#pragma unroll
+  for (int n = 0; n < NQ; ++n) {
+    m[n] = -FLT_MAX;
+    l[n] = d[n] = 0.0f;
+  }
+  const float* bq0 = sQ + l16 * OST + 4 * g;
+  const float* bg0 = sG + l16 * OST + 4 * g;
+  for (int t = kz; t < ntiles; t += kParts) {
+    asm volatile("" : "+v"(row_at));   // (opaque here, or its sums leave the loop as registers instead of immediates)
+    tile_at(t + kParts, first_n, cnt_n);
+    const __amdgpu_buffer_rsrc_t kn_rows = tile_rows<T, D>(Kh, first_n, cnt_n), vn_rows = tile_rows<T, D>(Vh, first_n, cnt_n);
+    f32x4 s[NQ], p[NQ];
+#pragma unroll
+    for (int n = 0; n < NQ; ++n) s[n] = p[n] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+    for (int c = 0; c < C; ++c) {
+      const f32x4 ka = kr[c].get(), va = vr[c].get();
+      f32x4 b[NQ], gg[NQ];
+#pragma unroll
+      for (int n = 0; n < NQ; ++n) {
+        b[n] = *reinterpret_cast<const f32x4*>(bq0 + 16 * n * OST + 16 * c);
+        gg[n] = *reinterpret_cast<const f32x4*>(bg0 + 16 * n * OST + 16 * c);
+      }
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+#pragma unroll
+        for (int n = 0; n < NQ; ++n) {
+          s[n] = mfma_f32(ka[e], b[n][e], s[n]);
+          p[n] = mfma_f32(va[e], gg[n][e], p[n]);
+        }
+      kr[c].load(kn_rows, row_at + 16 * c * B);
+      vr[c].load(vn_rows, row_at + 16 * c * B);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    if (cnt > 0) {   // uniform
+      const int slot = t / subs;
+#pragma unroll
+      for (int n = 0; n < NQ; ++n) {
+        if (qi0 + n < qt) {
+          float* tile = const_cast<float*>(score_tile(a, bh, qb, slot, qi0 + n, t - slot * subs)) + 16 * l16 + 4 * g;
+          *reinterpret_cast<f32x4*>(tile) = s[n];
+          *reinterpret_cast<f32x4*>(tile + kScoreTile / 2) = p[n];
+        }
+        if (cnt < 16)
+#pragma unroll
+          for (int r = 0; r < 4; ++r) s[n][r] = 4 * g + r < cnt ? s[n][r] : -__builtin_inff();
+        const float top = fmaxf(fmaxf(fmaxf(s[n][0], s[n][1]), fmaxf(s[n][2], s[n][3])), m[n]);
+        const float kept = __builtin_amdgcn_exp2f(m[n] - top);
+        float sum = 0.0f, weighted = 0.0f;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          const float w = __builtin_amdgcn_exp2f(s[n][r] - top);
+          sum += w;
+          weighted = fmaf(w, p[n][r], weighted);
+        }
+        l[n] = fmaf(l[n], kept, sum);
+        d[n] = fmaf(d[n], kept, weighted);
+        m[n] = top;
+      }
+    }
+    cnt = cnt_n;
+  }
+#pragma unroll
+  for (int n = 0; n < NQ; ++n) {
+    const float top = column_max(m[n]), w = __builtin_amdgcn_exp2f(m[n] - top);
+    const float sum = column_sum(l[n] * w), weighted = column_sum(d[n] * w);
+    if (g == 0) {
+      stat[0][kz][16 * n + l16] = top;
+      stat[1][kz][16 * n + l16] = sum;
+      stat[2][kz][16 * n + l16] = weighted;
+    }
+  }
+  __syncthreads();
+  const int rr = threadIdx.x;
+  if (rr < ROWS && row0 + rr < q_end) {
+    float top = stat[0][0][rr], sum = 0.0f, weighted = 0.0f;
+#pragma unroll
+    for (int u = 1; u < kParts; ++u) top = fmaxf(top, stat[0][u][rr]);
+#pragma unroll
+    for (int u = 0; u < kParts; ++u) {
+      const float w = __builtin_amdgcn_exp2f(stat[0][u][rr] - top);
+      sum = fmaf(stat[1][u][rr], w, sum);
+      weighted = fmaf(stat[2][u][rr], w, weighted);
+    }
+    const size_t at = (size_t)bh * n_q + row0 + rr;
+    a.lse2[at] = top + __builtin_amdgcn_logf(sum);
+    a.Dv[at] = weighted / sum;
+  }
+}
+
+// ---- dQ: a workgroup per 16 NQ query rows; S^T and dP^T = V dO^T (row form), dS^T = P^T (dP^T - D), dQ^T += K^T dS^T
+// (column form), all on 16 x 16 x 4 fp32 products.  Q and dO wait in LDS (B operands, shared by the four wavefronts); the
+// keys' and values' pieces travel one product phase ahead, each into the registers of a piece that has just been used.
+// kStored: S and dP come from bwd_scores_kernel, the products are dQ's alone.  Bound by the fp32 matrix rate.  12 heads of
+// 128, 1170 x 2340, k = 10 of 37 blocks of 64, on its own: 88 us (0.71 ms with one key per lane and FMA arithmetic, plus
+// 0.21 ms for the history branch's gradient as a kernel of its own).
+template <typename T, int D, int NQ, bool kStored>
+__device__ __forceinline__ void dq_role(const WideBwd& a, int wg, float* __restrict__ smem) {
+  constexpr int ROWS = 16 * NQ, C = D / 16, F = D / 64, OST = D + 4;
+  __shared__ float gpart[ROWS][kParts];
+  float* sQ = smem;                 // [ROWS][OST] Q, [ROWS][OST] dO; later four partial results
+  float* sG = smem + ROWS * OST;
+  const T* __restrict__ Q = static_cast<const T*>(a.Q);
+  const T* __restrict__ dO = static_cast<const T*>(a.dO);
+  const int k = a.k, n_q = a.n_q, n_kv = a.n_kv, bq = a.bq, bkv = a.bkv, t_m = a.t_m, t_n = a.t_n;
+  const WideBwdHist& hist = a.hist;
+  const int item = (wg & 7) * a.q_per_xcd + (wg >> 3);
+  if ((wg >> 3) >= a.q_per_xcd || item >= a.q_total) return;
+  const int bh = item / (t_m * a.q_chunks), in_head = item - bh * t_m * a.q_chunks;
+  const int qb = in_head / a.q_chunks, row0 = qb * bq + (in_head - qb * a.q_chunks) * ROWS;
+  const int q_end = min(n_q, (qb + 1) * bq);
+  if (row0 >= q_end) return;
+  const int lane = threadIdx.x & 63, kz = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int l16 = lane & 15, g = lane >> 4;
+  const T* __restrict__ Kh = static_cast<const T*>(a.K) + (size_t)bh * a.kv_stride * D;
+  const T* __restrict__ Vh = static_cast<const T*>(a.V) + (size_t)bh * a.kv_stride * D;
+  const int32_t* __restrict__ row_idx = a.idx ? a.idx + ((size_t)bh * t_m + qb) * k : nullptr;
+  const int nsel = a.idx ? k : t_n, subs = (bkv + 15) / 16, ntiles = nsel * subs;
+
+  if (!kStored || hist.L)   // (uniform; with stored scores only the history branch reads them)
+    for (int e = threadIdx.x; e < ROWS * (D / 4); e += 64 * kParts) {
+      const int rr = e / (D / 4), c4 = e - rr * (D / 4);
+      const size_t off = ((size_t)bh * n_q + min(row0 + rr, n_q - 1)) * D + 4 * c4;
+      if (!kStored) *reinterpret_cast<f32x4*>(sQ + rr * OST + 4 * c4) = load4<T>(Q + off) * a.scale_log2e;
+      *reinterpret_cast<f32x4*>(sG + rr * OST + 4 * c4) = load4<T>(dO + off);
+    }
   float lse[NQ], dv[NQ];
   f32x4 dq[NQ][F][4];
 #pragma unroll
   for (int n = 0; n < NQ; ++n) {
     const size_t at = (size_t)bh * n_q + min(row0 + 16 * n + l16, n_q - 1);
-    lse[n] = lse2[at];
-    dv[n] = Dv[at];
+    lse[n] = a.lse2[at];
+    dv[n] = a.Dv[at];
 #pragma unroll
     for (int f = 0; f < F; ++f)
 #pragma unroll
@@ -357,81 +552,134 @@ __global__ __launch_bounds__(64 * kParts, 2) void bwd_dq_wide_kernel(
     cnt = n > 0 ? n : 0;
     first = n > 0 ? st : 0;
   };
-  Piece<T> kr[C], vr[C], kc[4][F];
-  int first, cnt, first_n, cnt_n;
-  tile_at(kz, first, cnt);
-  constexpr int B = sizeof(T);
-  int row_at = (l16 * D + 4 * g) * B, col_at = (4 * g * D + 4 * l16) * B;   // rows behind a tile's last real key read as zeros
-  __amdgpu_buffer_rsrc_t k_rows = tile_rows<T, D>(Kh, first, cnt);
-  {
-    const __amdgpu_buffer_rsrc_t v_rows = tile_rows<T, D>(Vh, first, cnt);
-#pragma unroll
-    for (int c = 0; c < C; ++c) {
-      kr[c].load(k_rows, row_at + 16 * c * B);
-      vr[c].load(v_rows, row_at + 16 * c * B);
-      __builtin_amdgcn_sched_barrier(0);   // (requests are awaited in order: in this order here and in the loop)
-    }
-  }
   const float* bq0 = sQ + l16 * OST + 4 * g;
   const float* bg0 = sG + l16 * OST + 4 * g;
-  for (int t = kz; t < ntiles; t += kParts) {
-    asm volatile("" : "+v"(row_at), "+v"(col_at));   // (opaque here, or their sums leave the loop as registers instead of immediates)
-    tile_at(t + kParts, first_n, cnt_n);
-    const __amdgpu_buffer_rsrc_t kn_rows = tile_rows<T, D>(Kh, first_n, cnt_n), vn_rows = tile_rows<T, D>(Vh, first_n, cnt_n);
+  if constexpr (kStored) {
+    // S and dP of a tile lie where bwd_scores_kernel left them, four keys of a query to a lane: what the B operand takes.
+    const int qt = (bq + 15) / 16, qi0 = (row0 - qb * bq) / 16;
+    constexpr int B = sizeof(T);
+    int col_at = (4 * g * D + 4 * l16) * B, tile_lane = (16 * l16 + 4 * g) * 4;
+    Piece<T> kc[4][F];
     f32x4 s[NQ], p[NQ];
-#pragma unroll
-    for (int n = 0; n < NQ; ++n) s[n] = p[n] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
-#pragma unroll
-    for (int c = 0; c < C; ++c) {
-      const f32x4 a = kr[c].get(), v = vr[c].get();
-      f32x4 b[NQ], gg[NQ];
+    auto request_scores = [&](int t, int cnt) {
+      const int slot = t / subs, sub = t - slot * subs;
 #pragma unroll
       for (int n = 0; n < NQ; ++n) {
-        b[n] = *reinterpret_cast<const f32x4*>(bq0 + 16 * n * OST + 16 * c);
-        gg[n] = *reinterpret_cast<const f32x4*>(bg0 + 16 * n * OST + 16 * c);
+        const float* tile = score_tile(a, bh, qb, min(slot, nsel - 1), min(qi0 + n, qt - 1), sub);
+        const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(tile), 0, cnt > 0 ? kScoreTile * 4 : 0, 0x00020000);
+        s[n] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(r, tile_lane, 0, 0));
+        p[n] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(r, tile_lane + kScoreTile * 2, 0, 0));
       }
+    };
+    int first, cnt, first_n, cnt_n;
+    tile_at(kz, first, cnt);
+    request_scores(kz, __builtin_amdgcn_readfirstlane(cnt));
+    {
+      const __amdgpu_buffer_rsrc_t k_rows = tile_rows<T, D>(Kh, first, cnt);
 #pragma unroll
-      for (int e = 0; e < 4; ++e)
+      for (int u = 0; u < 4 * F; ++u) kc[u / F][u % F].load(k_rows, col_at + (u / F * D + 64 * (u % F)) * B);
+    }
+    for (int t = kz; t < ntiles; t += kParts) {
+      asm volatile("" : "+v"(col_at), "+v"(tile_lane));   // (as above)
+      f32x4 ds[NQ];
+#pragma unroll
+      for (int n = 0; n < NQ; ++n)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          const float d = __builtin_amdgcn_exp2f(s[n][r] - lse[n]) * (p[n][r] - dv[n]);
+          ds[n][r] = 4 * g + r < cnt ? d : 0.0f;   // zero for a key that does not exist
+        }
+      tile_at(t + kParts, first_n, cnt_n);
+      request_scores(t + kParts, __builtin_amdgcn_readfirstlane(cnt_n));
+      const __amdgpu_buffer_rsrc_t kn_rows = tile_rows<T, D>(Kh, first_n, cnt_n);
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int u = 0; u < 4 * F; ++u) {
+        const f32x4 ka = kc[u / F][u % F].get();
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+#pragma unroll
+          for (int n = 0; n < NQ; ++n) dq[n][u % F][e] = mfma_f32(ka[e], ds[n][u / F], dq[n][u % F][e]);
+        kc[u / F][u % F].load(kn_rows, col_at + (u / F * D + 64 * (u % F)) * B);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      cnt = cnt_n;
+    }
+  } else {
+    Piece<T> kr[C], vr[C], kc[4][F];
+    int first, cnt, first_n, cnt_n;
+    tile_at(kz, first, cnt);
+    constexpr int B = sizeof(T);
+    int row_at = (l16 * D + 4 * g) * B, col_at = (4 * g * D + 4 * l16) * B;   // rows behind a tile's last real key read as zeros
+    __amdgpu_buffer_rsrc_t k_rows = tile_rows<T, D>(Kh, first, cnt);
+    {
+      const __amdgpu_buffer_rsrc_t v_rows = tile_rows<T, D>(Vh, first, cnt);
+#pragma unroll
+      for (int c = 0; c < C; ++c) {
+        kr[c].load(k_rows, row_at + 16 * c * B);
+        vr[c].load(v_rows, row_at + 16 * c * B);
+        __builtin_amdgcn_sched_barrier(0);   // (requests are awaited in order: in this order here and in the loop)
+      }
+    }
+    for (int t = kz; t < ntiles; t += kParts) {
+      asm volatile("" : "+v"(row_at), "+v"(col_at));   // (opaque here, or their sums leave the loop as registers instead of immediates)
+      tile_at(t + kParts, first_n, cnt_n);
+      const __amdgpu_buffer_rsrc_t kn_rows = tile_rows<T, D>(Kh, first_n, cnt_n), vn_rows = tile_rows<T, D>(Vh, first_n, cnt_n);
+      f32x4 s[NQ], p[NQ];
+#pragma unroll
+      for (int n = 0; n < NQ; ++n) s[n] = p[n] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+      for (int c = 0; c < C; ++c) {
+        const f32x4 a = kr[c].get(), v = vr[c].get();
+        f32x4 b[NQ], gg[NQ];
 #pragma unroll
         for (int n = 0; n < NQ; ++n) {
-          s[n] = mfma_f32(a[e], b[n][e], s[n]);
-          p[n] = mfma_f32(v[e], gg[n][e], p[n]);
+          b[n] = *reinterpret_cast<const f32x4*>(bq0 + 16 * n * OST + 16 * c);
+          gg[n] = *reinterpret_cast<const f32x4*>(bg0 + 16 * n * OST + 16 * c);
         }
 #pragma unroll
-      for (int u = c * 4 * F / C; u < (c + 1) * 4 * F / C; ++u) kc[u / F][u % F].load(k_rows, col_at + (u / F * D + 64 * (u % F)) * B);
-      __builtin_amdgcn_sched_barrier(0);
-    }
-    // dS = P (dP - D); zero for a key that does not exist
+        for (int e = 0; e < 4; ++e)
 #pragma unroll
-    for (int n = 0; n < NQ; ++n)
+          for (int n = 0; n < NQ; ++n) {
+            s[n] = mfma_f32(a[e], b[n][e], s[n]);
+            p[n] = mfma_f32(v[e], gg[n][e], p[n]);
+          }
 #pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const float ds = __builtin_amdgcn_exp2f(s[n][r] - lse[n]) * (p[n][r] - dv[n]);
-        s[n][r] = 4 * g + r < cnt ? ds : 0.0f;
+        for (int u = c * 4 * F / C; u < (c + 1) * 4 * F / C; ++u) kc[u / F][u % F].load(k_rows, col_at + (u / F * D + 64 * (u % F)) * B);
+        __builtin_amdgcn_sched_barrier(0);
       }
+      // dS = P (dP - D); zero for a key that does not exist
 #pragma unroll
-    for (int u = 0; u < 4 * F; ++u) {
-      const f32x4 a = kc[u / F][u % F].get();
+      for (int n = 0; n < NQ; ++n)
 #pragma unroll
-      for (int e = 0; e < 4; ++e)
+        for (int r = 0; r < 4; ++r) {
+          const float ds = __builtin_amdgcn_exp2f(s[n][r] - lse[n]) * (p[n][r] - dv[n]);
+          s[n][r] = 4 * g + r < cnt ? ds : 0.0f;
+        }
 #pragma unroll
-        for (int n = 0; n < NQ; ++n) dq[n][u % F][e] = mfma_f32(a[e], s[n][u / F], dq[n][u % F][e]);
+      for (int u = 0; u < 4 * F; ++u) {
+        const f32x4 a = kc[u / F][u % F].get();
 #pragma unroll
-      for (int c = u * C / (4 * F); c < (u + 1) * C / (4 * F); ++c) {
-        kr[c].load(kn_rows, row_at + 16 * c * B);
-        vr[c].load(vn_rows, row_at + 16 * c * B);
+        for (int e = 0; e < 4; ++e)
+#pragma unroll
+          for (int n = 0; n < NQ; ++n) dq[n][u % F][e] = mfma_f32(a[e], s[n][u / F], dq[n][u % F][e]);
+#pragma unroll
+        for (int c = u * C / (4 * F); c < (u + 1) * C / (4 * F); ++c) {
+          kr[c].load(kn_rows, row_at + 16 * c * B);
+          vr[c].load(vn_rows, row_at + 16 * c * B);
+        }
+        __builtin_amdgcn_sched_barrier(0);
       }
-      __builtin_amdgcn_sched_barrier(0);
+      k_rows = kn_rows;
+      cnt = cnt_n;
     }
-    k_rows = kn_rows;
-    cnt = cnt_n;
   }
 #pragma unroll
   for (int n = 0; n < NQ; ++n)
 #pragma unroll
     for (int f = 0; f < F; ++f)
 #pragma unroll
-      for (int e = 0; e < 4; ++e) dq[n][f][e] *= scale;
+      for (int e = 0; e < 4; ++e) dq[n][f][e] *= a.scale;
   __syncthreads();   // Q and dO are read no more as operands of the loop
 
   if (hist.L) {
@@ -564,45 +812,37 @@ __global__ __launch_bounds__(64 * kParts, 2) void bwd_dq_wide_kernel(
     }
     __syncthreads();
   }
-  add_parts_and_store<T, D, NQ>(smem, dq, 1.0f, kz, l16, g, dQ + ((size_t)bh * n_q + row0) * D, q_end - row0);
+  add_parts_and_store<T, D, NQ>(smem, dq, 1.0f, kz, l16, g, static_cast<T*>(a.dQ) + ((size_t)bh * n_q + row0) * D, q_end - row0);
 }
 
 // ---- dK, dV: a workgroup per 16 NK keys of a KV block, its four wavefronts taking every fourth 16-row tile of the query
 // blocks on the inverse list.  S = Q K^T, dP = dO V^T (row form; K and V wait in LDS), P = 2^(S - lse2), dS = P (dP - D),
 // dV^T += dO^T P, dK^T += Q^T dS (column form).  Bound by the fp32 matrix rate, at the same shape 118 us (1.01 ms with one
 // query per lane and FMA arithmetic).
-template <typename T, int D, int NK>
-__global__ __launch_bounds__(64 * kParts, 2) void bwd_dkv_wide_kernel(
-    const T* __restrict__ Q, const T* __restrict__ K, const T* __restrict__ V, const T* __restrict__ dO,
-    const int32_t* __restrict__ inv_cnt, const int32_t* __restrict__ inv_list, int n_q, int n_kv, int kv_stride, int bq,
-    int bkv, int t_m, int t_n, int chunks, int per_xcd, int total, float scale_log2e, float scale,
-    const float* __restrict__ lse2, const float* __restrict__ Dv, T* __restrict__ dK, T* __restrict__ dV) {
+template <typename T, int D, int NK, bool kStored>
+__device__ __forceinline__ void dkv_role(const WideBwd& a, int wg, float* __restrict__ smem) {
   constexpr int ROWS = 16 * NK, C = D / 16, F = D / 64, OST = D + 4;
-  extern __shared__ __attribute__((aligned(16))) float smem[];   // [ROWS][OST] K, [ROWS][OST] V; later four partial results
-  float* sK = smem;
+  float* sK = smem;                 // [ROWS][OST] K, [ROWS][OST] V; later four partial results
   float* sV = smem + ROWS * OST;
-  const int item = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
-  if ((int)(blockIdx.x >> 3) >= per_xcd || item >= total) return;
-  const int bh = item / (t_n * chunks), in_head = item - bh * t_n * chunks;
-  const int jb = in_head / chunks, key0 = jb * bkv + (in_head - jb * chunks) * ROWS;
+  const T* __restrict__ K = static_cast<const T*>(a.K);
+  const T* __restrict__ V = static_cast<const T*>(a.V);
+  const int n_q = a.n_q, n_kv = a.n_kv, kv_stride = a.kv_stride, bq = a.bq, bkv = a.bkv, t_m = a.t_m, t_n = a.t_n;
+  const int item = (wg & 7) * a.k_per_xcd + (wg >> 3);
+  if ((wg >> 3) >= a.k_per_xcd || item >= a.k_total) return;
+  const int bh = item / (t_n * a.k_chunks), in_head = item - bh * t_n * a.k_chunks;
+  const int jb = in_head / a.k_chunks, key0 = jb * bkv + (in_head - jb * a.k_chunks) * ROWS;
   const int k_end = min(n_kv, (jb + 1) * bkv);
   if (key0 >= k_end) return;
   const int lane = threadIdx.x & 63, kz = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int l16 = lane & 15, g = lane >> 4;
-  const T* Qh = Q + (size_t)bh * n_q * D;
-  const T* Gh = dO + (size_t)bh * n_q * D;
-  const float* lseh = lse2 + (size_t)bh * n_q;
-  const float* dvh = Dv + (size_t)bh * n_q;
-  const int n_lists = inv_cnt ? inv_cnt[(size_t)bh * t_n + jb] : t_m;   // no lists: every query block (dense)
-  const int32_t* list = inv_list ? inv_list + ((size_t)bh * t_n + jb) * t_m : nullptr;
+  const T* __restrict__ Qh = static_cast<const T*>(a.Q) + (size_t)bh * n_q * D;
+  const T* __restrict__ Gh = static_cast<const T*>(a.dO) + (size_t)bh * n_q * D;
+  const float* __restrict__ lseh = a.lse2 + (size_t)bh * n_q;
+  const float* __restrict__ dvh = a.Dv + (size_t)bh * n_q;
+  const int n_lists = a.inv_cnt ? a.inv_cnt[(size_t)bh * t_n + jb] : t_m;   // no lists: every query block (dense)
+  const int32_t* __restrict__ list = a.inv_list ? a.inv_list + ((size_t)bh * t_n + jb) * t_m : nullptr;
   const int subs = (bq + 15) / 16, ntiles = n_lists * subs;
 
-  for (int e = threadIdx.x; e < ROWS * (D / 4); e += 64 * kParts) {
-    const int rr = e / (D / 4), c4 = e - rr * (D / 4);
-    const size_t off = ((size_t)bh * kv_stride + min(key0 + rr, n_kv - 1)) * D + 4 * c4;
-    *reinterpret_cast<f32x4*>(sK + rr * OST + 4 * c4) = load4<T>(K + off) * scale_log2e;
-    *reinterpret_cast<f32x4*>(sV + rr * OST + 4 * c4) = load4<T>(V + off);
-  }
   f32x4 ak[NK][F][4], av[NK][F][4];
 #pragma unroll
   for (int n = 0; n < NK; ++n)
@@ -610,146 +850,269 @@ __global__ __launch_bounds__(64 * kParts, 2) void bwd_dkv_wide_kernel(
     for (int f = 0; f < F; ++f)
 #pragma unroll
       for (int e = 0; e < 4; ++e) ak[n][f][e] = av[n][f][e] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
-  __syncthreads();
 
-  auto tile_at = [&](int t, int& first, int& cnt) {   // cnt 0: past the list or past the last query
-    const int s = t / subs, sub = t - s * subs;
-    const int qb = s < n_lists ? (list ? list[s] : s) : 0;
-    const int st = qb * bq + 16 * sub;
-    const int n = s < n_lists ? min(16, min(n_q, (qb + 1) * bq) - st) : 0;
-    cnt = n > 0 ? n : 0;
-    first = n > 0 ? st : 0;
-  };
-  Piece<T> qr[C], gr[C], qc[4][F], gc[4][F];
-  int first, cnt, first_n, cnt_n;
-  tile_at(kz, first, cnt);
-  constexpr int B = sizeof(T);
-  int row_at = (l16 * D + 4 * g) * B, col_at = (4 * g * D + 4 * l16) * B;   // rows behind a tile's last real query read as zeros
-  __amdgpu_buffer_rsrc_t q_rows = tile_rows<T, D>(Qh, first, cnt), g_rows = tile_rows<T, D>(Gh, first, cnt);
-#pragma unroll
-  for (int c = 0; c < C; ++c) {
-    qr[c].load(q_rows, row_at + 16 * c * B);
-    gr[c].load(g_rows, row_at + 16 * c * B);
-    __builtin_amdgcn_sched_barrier(0);
-  }
-  const float* bk0 = sK + l16 * OST + 4 * g;
-  const float* bv0 = sV + l16 * OST + 4 * g;
-  for (int t = kz; t < ntiles; t += kParts) {
-    asm volatile("" : "+v"(row_at), "+v"(col_at));   // (opaque here, or their sums leave the loop as registers instead of immediates)
-    tile_at(t + kParts, first_n, cnt_n);
-    const __amdgpu_buffer_rsrc_t qn_rows = tile_rows<T, D>(Qh, first_n, cnt_n), gn_rows = tile_rows<T, D>(Gh, first_n, cnt_n);
-    float lse[4], dv[4];   // (of the tile's last query for those that do not exist: what they give is dropped)
-#pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      const int row = __builtin_amdgcn_readfirstlane(first) + min(4 * g + r, max(cnt - 1, 0));
-      lse[r] = lseh[row];
-      dv[r] = dvh[row];
-    }
-    f32x4 s[NK], p[NK];
-#pragma unroll
-    for (int n = 0; n < NK; ++n) s[n] = p[n] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
-#pragma unroll
-    for (int c = 0; c < C; ++c) {
-      const f32x4 a = qr[c].get(), v = gr[c].get();
-      f32x4 b[NK], gg[NK];
-#pragma unroll
-      for (int n = 0; n < NK; ++n) {
-        b[n] = *reinterpret_cast<const f32x4*>(bk0 + 16 * n * OST + 16 * c);
-        gg[n] = *reinterpret_cast<const f32x4*>(bv0 + 16 * n * OST + 16 * c);
-      }
-#pragma unroll
-      for (int e = 0; e < 4; ++e)
-#pragma unroll
-        for (int n = 0; n < NK; ++n) {
-          s[n] = mfma_f32(a[e], b[n][e], s[n]);
-          p[n] = mfma_f32(v[e], gg[n][e], p[n]);
-        }
-#pragma unroll
-      for (int u = c * 4 * F / C; u < (c + 1) * 4 * F / C; ++u) {
-        gc[u / F][u % F].load(g_rows, col_at + (u / F * D + 64 * (u % F)) * B);
-        qc[u / F][u % F].load(q_rows, col_at + (u / F * D + 64 * (u % F)) * B);
-      }
-      __builtin_amdgcn_sched_barrier(0);
-    }
-    // P and dS; zero for a query that does not exist
-#pragma unroll
-    for (int n = 0; n < NK; ++n)
+  if constexpr (kStored) {
+    const int32_t* __restrict__ slots = a.inv_slot ? a.inv_slot + ((size_t)bh * t_n + jb) * t_m : nullptr;
+    const int kt = (bkv + 15) / 16, ki0 = (key0 - jb * bkv) / 16;
+    constexpr int B = sizeof(T);
+    int col_at = (4 * g * D + 4 * l16) * B, tile_lane = (64 * g + l16) * 4;
+    // the list's entries are read a trip before their tile's rows are asked for (without a branch, which in the loop would
+    // have the accumulators kept twice; a dense window has some word read in their place)
+    const int32_t* __restrict__ some = reinterpret_cast<const int32_t*>(lseh);
+    auto entry = [&](int t, int& qb, int& slot) {
+      const int at = min(t / subs, max(n_lists - 1, 0)), from = list ? at : 0;
+      const int b = (list ? list : some)[from], sl = (list ? slots : some)[from];
+      qb = list ? b : at;
+      slot = list ? sl : jb;
+    };
+    auto tile_of = [&](int t, int qb, int& first, int& cnt) {   // cnt 0: past the list or past the last query
+      const int st = qb * bq + 16 * (t % subs);
+      const int n = t < ntiles ? min(16, min(n_q, (qb + 1) * bq) - st) : 0;
+      cnt = n > 0 ? n : 0;
+      first = n > 0 ? st : 0;
+    };
+    // half of a tile's pieces at a time (a whole tile's, and accumulators, weights and the next scores: 83 registers to scratch)
+    constexpr int AHEAD = 2 * F;
+    Piece<T> qc[AHEAD], gc[AHEAD];
+    float s[NK][4], p[NK][4], lse[4], dv[4];
+    auto request_scores = [&](int t, int qb, int slot, int first, int cnt) {
+      const __amdgpu_buffer_rsrc_t rl = tile_rows<float, 1>(lseh, first, cnt), rd = tile_rows<float, 1>(dvh, first, cnt);
 #pragma unroll
       for (int r = 0; r < 4; ++r) {
-        const bool real = 4 * g + r < cnt;
-        const float w = __builtin_amdgcn_exp2f(s[n][r] - lse[r]), ds = w * (p[n][r] - dv[r]);
-        s[n][r] = real ? w : 0.0f;
-        p[n][r] = real ? ds : 0.0f;
+        lse[r] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rl, 16 * g + 4 * r, 0, 0));
+        dv[r] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rd, 16 * g + 4 * r, 0, 0));
       }
 #pragma unroll
-    for (int u = 0; u < 4 * F; ++u) {
-      const f32x4 a = gc[u / F][u % F].get(), b = qc[u / F][u % F].get();
+      for (int n = 0; n < NK; ++n) {
+        const float* tile = score_tile(a, bh, qb, slot, t % subs, min(ki0 + n, kt - 1));
+        const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(tile), 0, cnt > 0 ? kScoreTile * 4 : 0, 0x00020000);
 #pragma unroll
-      for (int e = 0; e < 4; ++e)
-#pragma unroll
-        for (int n = 0; n < NK; ++n) {
-          av[n][u % F][e] = mfma_f32(a[e], s[n][u / F], av[n][u % F][e]);
-          ak[n][u % F][e] = mfma_f32(b[e], p[n][u / F], ak[n][u % F][e]);
+        for (int r = 0; r < 4; ++r) {   // a key to a lane, four queries: what the B operands take
+          s[n][r] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rs, tile_lane + 64 * r, 0, 0));
+          p[n][r] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rs, tile_lane + 64 * r + kScoreTile * 2, 0, 0));
         }
-#pragma unroll
-      for (int c = u * C / (4 * F); c < (u + 1) * C / (4 * F); ++c) {
-        qr[c].load(qn_rows, row_at + 16 * c * B);
-        gr[c].load(gn_rows, row_at + 16 * c * B);
       }
+    };
+    int first, cnt, qb, slot, qb_n, slot_n;
+    entry(kz, qb, slot);
+    entry(kz + kParts, qb_n, slot_n);
+    tile_of(kz, qb, first, cnt);
+    request_scores(kz, qb, slot, first, cnt);
+    __amdgpu_buffer_rsrc_t q_rows = tile_rows<T, D>(Qh, first, cnt), g_rows = tile_rows<T, D>(Gh, first, cnt);
+    {
+#pragma unroll
+      for (int u = 0; u < AHEAD; ++u) {
+        gc[u].load(g_rows, col_at + (u / F * D + 64 * (u % F)) * B);
+        qc[u].load(q_rows, col_at + (u / F * D + 64 * (u % F)) * B);
+      }
+    }
+    for (int t = kz; t < ntiles; t += kParts) {
+      asm volatile("" : "+v"(col_at), "+v"(tile_lane));   // (opaque here, or their sums leave the loop as registers instead of immediates)
+      // P and dS; zero for a query that does not exist
+#pragma unroll
+      for (int n = 0; n < NK; ++n)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          const bool real = 4 * g + r < cnt;
+          const float w = __builtin_amdgcn_exp2f(s[n][r] - lse[r]), ds = w * (p[n][r] - dv[r]);
+          s[n][r] = real ? w : 0.0f;
+          p[n][r] = real ? ds : 0.0f;
+        }
+      float sw[NK][4], pw[NK][4];
+#pragma unroll
+      for (int n = 0; n < NK; ++n)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          sw[n][r] = s[n][r];
+          pw[n][r] = p[n][r];
+        }
+      int first_n, cnt_n;
+      tile_of(t + kParts, qb_n, first_n, cnt_n);
+      const __amdgpu_buffer_rsrc_t qn_rows = tile_rows<T, D>(Qh, first_n, cnt_n), gn_rows = tile_rows<T, D>(Gh, first_n, cnt_n);
+#pragma unroll
+      for (int u = 0; u < 4 * F; ++u) {
+        if (u == 3 * F) {   // (three quarters of the weights are used up: their registers take the next tile's)
+          request_scores(t + kParts, qb_n, slot_n, first_n, cnt_n);
+          entry(t + 2 * kParts, qb_n, slot_n);
+        }
+        const f32x4 ga = gc[u % AHEAD].get(), qa = qc[u % AHEAD].get();
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+#pragma unroll
+          for (int n = 0; n < NK; ++n) {
+            av[n][u % F][e] = mfma_f32(ga[e], sw[n][u / F], av[n][u % F][e]);
+            ak[n][u % F][e] = mfma_f32(qa[e], pw[n][u / F], ak[n][u % F][e]);
+          }
+        const int v = (u + AHEAD) % (4 * F), at = col_at + (v / F * D + 64 * (v % F)) * B;
+        gc[u % AHEAD].load(u < AHEAD ? g_rows : gn_rows, at);
+        qc[u % AHEAD].load(u < AHEAD ? q_rows : qn_rows, at);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      cnt = cnt_n;
+      q_rows = qn_rows;
+      g_rows = gn_rows;
+    }
+  } else {
+    for (int e = threadIdx.x; e < ROWS * (D / 4); e += 64 * kParts) {
+      const int rr = e / (D / 4), c4 = e - rr * (D / 4);
+      const size_t off = ((size_t)bh * kv_stride + min(key0 + rr, n_kv - 1)) * D + 4 * c4;
+      *reinterpret_cast<f32x4*>(sK + rr * OST + 4 * c4) = load4<T>(K + off) * a.scale_log2e;
+      *reinterpret_cast<f32x4*>(sV + rr * OST + 4 * c4) = load4<T>(V + off);
+    }
+    __syncthreads();
+
+    auto tile_at = [&](int t, int& first, int& cnt) {   // cnt 0: past the list or past the last query
+      const int s = t / subs, sub = t - s * subs;
+      const int qb = s < n_lists ? (list ? list[s] : s) : 0;
+      const int st = qb * bq + 16 * sub;
+      const int n = s < n_lists ? min(16, min(n_q, (qb + 1) * bq) - st) : 0;
+      cnt = n > 0 ? n : 0;
+      first = n > 0 ? st : 0;
+    };
+    Piece<T> qr[C], gr[C], qc[4][F], gc[4][F];
+    int first, cnt, first_n, cnt_n;
+    tile_at(kz, first, cnt);
+    constexpr int B = sizeof(T);
+    int row_at = (l16 * D + 4 * g) * B, col_at = (4 * g * D + 4 * l16) * B;   // rows behind a tile's last real query read as zeros
+    __amdgpu_buffer_rsrc_t q_rows = tile_rows<T, D>(Qh, first, cnt), g_rows = tile_rows<T, D>(Gh, first, cnt);
+#pragma unroll
+    for (int c = 0; c < C; ++c) {
+      qr[c].load(q_rows, row_at + 16 * c * B);
+      gr[c].load(g_rows, row_at + 16 * c * B);
       __builtin_amdgcn_sched_barrier(0);
     }
-    first = first_n;
-    q_rows = qn_rows;
-    g_rows = gn_rows;
-    cnt = cnt_n;
+    const float* bk0 = sK + l16 * OST + 4 * g;
+    const float* bv0 = sV + l16 * OST + 4 * g;
+    for (int t = kz; t < ntiles; t += kParts) {
+      asm volatile("" : "+v"(row_at), "+v"(col_at));   // (opaque here, or their sums leave the loop as registers instead of immediates)
+      tile_at(t + kParts, first_n, cnt_n);
+      const __amdgpu_buffer_rsrc_t qn_rows = tile_rows<T, D>(Qh, first_n, cnt_n), gn_rows = tile_rows<T, D>(Gh, first_n, cnt_n);
+      float lse[4], dv[4];   // (of the tile's last query for those that do not exist: what they give is dropped)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int row = __builtin_amdgcn_readfirstlane(first) + min(4 * g + r, max(cnt - 1, 0));
+        lse[r] = lseh[row];
+        dv[r] = dvh[row];
+      }
+      f32x4 s[NK], p[NK];
+#pragma unroll
+      for (int n = 0; n < NK; ++n) s[n] = p[n] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll
+      for (int c = 0; c < C; ++c) {
+        const f32x4 a = qr[c].get(), v = gr[c].get();
+        f32x4 b[NK], gg[NK];
+#pragma unroll
+        for (int n = 0; n < NK; ++n) {
+          b[n] = *reinterpret_cast<const f32x4*>(bk0 + 16 * n * OST + 16 * c);
+          gg[n] = *reinterpret_cast<const f32x4*>(bv0 + 16 * n * OST + 16 * c);
+        }
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+#pragma unroll
+          for (int n = 0; n < NK; ++n) {
+            s[n] = mfma_f32(a[e], b[n][e], s[n]);
+            p[n] = mfma_f32(v[e], gg[n][e], p[n]);
+          }
+#pragma unroll
+        for (int u = c * 4 * F / C; u < (c + 1) * 4 * F / C; ++u) {
+          gc[u / F][u % F].load(g_rows, col_at + (u / F * D + 64 * (u % F)) * B);
+          qc[u / F][u % F].load(q_rows, col_at + (u / F * D + 64 * (u % F)) * B);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      // P and dS; zero for a query that does not exist
+#pragma unroll
+      for (int n = 0; n < NK; ++n)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          const bool real = 4 * g + r < cnt;
+          const float w = __builtin_amdgcn_exp2f(s[n][r] - lse[r]), ds = w * (p[n][r] - dv[r]);
+          s[n][r] = real ? w : 0.0f;
+          p[n][r] = real ? ds : 0.0f;
+        }
+#pragma unroll
+      for (int u = 0; u < 4 * F; ++u) {
+        const f32x4 a = gc[u / F][u % F].get(), b = qc[u / F][u % F].get();
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+#pragma unroll
+          for (int n = 0; n < NK; ++n) {
+            av[n][u % F][e] = mfma_f32(a[e], s[n][u / F], av[n][u % F][e]);
+            ak[n][u % F][e] = mfma_f32(b[e], p[n][u / F], ak[n][u % F][e]);
+          }
+#pragma unroll
+        for (int c = u * C / (4 * F); c < (u + 1) * C / (4 * F); ++c) {
+          qr[c].load(qn_rows, row_at + 16 * c * B);
+          gr[c].load(gn_rows, row_at + 16 * c * B);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      first = first_n;
+      q_rows = qn_rows;
+      g_rows = gn_rows;
+      cnt = cnt_n;
+    }
   }
-  __syncthreads();   // K and V are read no more
+  if (!kStored) __syncthreads();   // K and V are read no more
   const size_t out = ((size_t)bh * kv_stride + key0) * D;
-  add_parts_and_store<T, D, NK>(smem, ak, scale, kz, l16, g, dK + out, k_end - key0);
+  add_parts_and_store<T, D, NK>(smem, ak, a.scale, kz, l16, g, static_cast<T*>(a.dK) + out, k_end - key0);
   __syncthreads();
-  add_parts_and_store<T, D, NK>(smem, av, 1.0f, kz, l16, g, dV + out, k_end - key0);
+  add_parts_and_store<T, D, NK>(smem, av, 1.0f, kz, l16, g, static_cast<T*>(a.dV) + out, k_end - key0);
 }
 
-template <typename T, int D, int N>
-int launch_bwd_wide(const hf_config& c, const void* Q, int n_q, const void* K, const void* V, int n_kv, const int32_t* idx,
-                    int k, const void* dO, const float* lse2, const float* Dv, const int32_t* inv_cnt, const int32_t* inv_list,
-                    const WideBwdHist& hist, void* dQ, void* dK, void* dV, bool keys, hipStream_t s) {
-  constexpr int ROWS = 16 * N;
-  const int BH = c.batch * c.heads;
-  const int t_m = (n_q + c.block_q - 1) / c.block_q, t_n = (n_kv + c.block_kv - 1) / c.block_kv;
-  const float scale = c.softmax_scale > 0.0f ? c.softmax_scale : 1.0f / sqrtf((float)c.head_dim);
-  const float sl2 = scale * 1.4426950408889634f;
-  const int kvs = kv_stride_of(c, n_kv);
-  const int chunks = ((keys ? c.block_kv : c.block_q) + ROWS - 1) / ROWS;
-  const long long total = (long long)BH * (keys ? t_n : t_m) * chunks;
-  if (total > (1ll << 30)) { set_error("too many blocks"); return HF_ERR_SHAPE; }
-  const int per_xcd = (int)((total + 7) / 8);
-  constexpr int lds = kParts * ROWS * (D + 4) * (int)sizeof(float);
-  const dim3 grid(8 * per_xcd), block(64 * kParts);
-  const T *q = static_cast<const T*>(Q), *kk = static_cast<const T*>(K), *v = static_cast<const T*>(V), *g = static_cast<const T*>(dO);
-  const void* fn = keys ? reinterpret_cast<const void*>(bwd_dkv_wide_kernel<T, D, N>)
-                        : reinterpret_cast<const void*>(bwd_dq_wide_kernel<T, D, N>);
+template <typename T, int D, int NQ>
+__global__ __launch_bounds__(64 * kParts, 2) void bwd_dq_wide_kernel(WideBwd a) {
+  extern __shared__ __attribute__((aligned(16))) float smem[];
+  dq_role<T, D, NQ, false>(a, blockIdx.x, smem);
+}
+template <typename T, int D, int NK>
+__global__ __launch_bounds__(64 * kParts, 2) void bwd_dkv_wide_kernel(WideBwd a) {
+  extern __shared__ __attribute__((aligned(16))) float smem[];
+  dkv_role<T, D, NK, false>(a, blockIdx.x, smem);
+}
+// from stored scores, dK and dV's workgroups and behind them dQ's in one launch
+template <typename T, int D, int NQ, int NK>
+__global__ __launch_bounds__(64 * kParts, 2) void bwd_stored_kernel(WideBwd a) {
+  extern __shared__ __attribute__((aligned(16))) float smem[];
+  const int key_wgs = 8 * a.k_per_xcd;
+  if ((int)blockIdx.x < key_wgs)
+    dkv_role<T, D, NK, true>(a, blockIdx.x, smem);
+  else
+    dq_role<T, D, NQ, true>(a, blockIdx.x - key_wgs, smem);
+}
+
+template <int D>
+int launch_wide(const void* fn, LdsGrant& grant, long long wgs, int rows, WideBwd& a, hipStream_t s) {
+  const int lds = rows * (D + 4) * (int)sizeof(float);
   if (lds > 64 * 1024) {
-    static LdsGrant grants[2];
-    const int rc = grant_lds(grants[keys], fn, lds, "the fp32 backward kernels");
+    const int rc = grant_lds(grant, fn, lds, "the fp32 backward kernels");
     if (rc != HF_OK) return rc;
   }
-  if (keys)
-    hipLaunchKernelGGL((bwd_dkv_wide_kernel<T, D, N>), grid, block, lds, s, q, kk, v, g, inv_cnt, inv_list, n_q, n_kv, kvs,
-                       c.block_q, c.block_kv, t_m, t_n, chunks, per_xcd, (int)total, sl2, scale, lse2, Dv,
-                       static_cast<T*>(dK), static_cast<T*>(dV));
-  else
-    hipLaunchKernelGGL((bwd_dq_wide_kernel<T, D, N>), grid, block, lds, s, q, kk, v, g, idx, k, n_q, n_kv, kvs, c.block_q,
-                       c.block_kv, t_m, t_n, chunks, per_xcd, (int)total, sl2, scale, lse2, Dv, hist, static_cast<T*>(dQ));
+  void* args[] = {&a};
+  (void)hipLaunchKernel(fn, dim3((unsigned)wgs), dim3(64 * kParts), args, lds, s);
   return check_launch("hf_hybrid_attn_bwd(dQ, dK, dV)");
+}
+
+template <typename T, int D, int NQ, int NK>
+int launch_bwd_wide(WideBwd& a, hipStream_t s) {
+  static LdsGrant grants[4];
+  constexpr int N = NQ > NK ? NQ : NK;
+  const long long q_wgs = 8ll * a.q_per_xcd, k_wgs = 8ll * a.k_per_xcd;
+  int rc;
+  if (a.scores) {
+    if ((rc = launch_wide<D>(reinterpret_cast<const void*>(bwd_scores_kernel<T, D, NQ>), grants[0], q_wgs, 2 * 16 * NQ, a, s)) != HF_OK) return rc;
+    return launch_wide<D>(reinterpret_cast<const void*>(bwd_stored_kernel<T, D, NQ, NK>), grants[1], q_wgs + k_wgs, kParts * 16 * N, a, s);
+  }
+  if ((rc = launch_wide<D>(reinterpret_cast<const void*>(bwd_dq_wide_kernel<T, D, NQ>), grants[2], q_wgs, kParts * 16 * NQ, a, s)) != HF_OK) return rc;
+  return launch_wide<D>(reinterpret_cast<const void*>(bwd_dkv_wide_kernel<T, D, NK>), grants[3], k_wgs, kParts * 16 * NK, a, s);
 }
 
 }  // namespace
 
-// idx given: the inverse lists, and with order given the dK/dV items' launch order; state given: planes (bf16, head_dim 128);
+// idx given: the inverse lists (inv_slot given: with places), and with order given the dK/dV items' launch order; state given: planes (bf16, head_dim 128);
 // A given: row dots (likewise).
 int launch_bwd_prep(const hf_config& c, const int32_t* idx, int k, int t_m, int t_n, int32_t* inv_cnt, int32_t* inv_list,
-                    int32_t* order, const float* state, void* planes, const void* A, const void* B, long long rows,
+                    int32_t* inv_slot, int32_t* order, const float* state, void* planes, const void* A, const void* B, long long rows,
                     float* dots, hipStream_t s) {
   constexpr size_t kPrepLds = 150 * 1024;   // granted to the kernel below
   const int BH = c.batch * c.heads;
@@ -760,6 +1123,7 @@ int launch_bwd_prep(const hf_config& c, const int32_t* idx, int k, int t_m, int 
   p.t_n = t_n;
   p.inv_cnt = inv_cnt;
   p.inv_list = inv_list;
+  p.inv_slot = inv_slot;
   size_t lds = 0;
   bool order_behind = false;
   const int slabs = (c.block_kv + 63) / 64;
@@ -782,7 +1146,8 @@ int launch_bwd_prep(const hf_config& c, const int32_t* idx, int k, int t_m, int 
         if (need > lds) lds = need;
       }
     } else {
-      hipLaunchKernelGGL(invert_index_kernel, dim3((t_n + 3) / 4, BH), dim3(256), 0, s, idx, k, t_m, t_n, inv_cnt, inv_list);
+      hipLaunchKernelGGL(invert_index_kernel, dim3((t_n + 3) / 4, BH), dim3(256), 0, s, idx, k, t_m, t_n, inv_cnt, inv_list,
+                         inv_slot);
     }
     order_behind = order && !p.order_wgs;
   }
@@ -817,14 +1182,36 @@ int launch_bwd_prep(const hf_config& c, const int32_t* idx, int k, int t_m, int 
   return check_launch("hf_hybrid_attn_bwd(lists, planes, D)");
 }
 
-// dQ (with the history branch where a state is given), then dK and dV.  32 rows or keys per workgroup, 16 where a block has
+// Bytes of the stored scores of a call with lists of k blocks; 0: products are formed again instead.
+size_t bwd_scores_bytes(const hf_config& c, int n_q, int k) {
+  const size_t t_m = (n_q + c.block_q - 1) / c.block_q, qt = (c.block_q + 15) / 16, kt = (c.block_kv + 15) / 16;
+  const size_t bytes = (size_t)c.batch * c.heads * t_m * k * qt * kt * (kScoreTile * sizeof(float));
+  return bytes <= kScoresMax ? bytes : 0;
+}
+
+// dQ (with the history branch where a state is given), dK and dV.  32 rows or keys per workgroup, 16 where a block has
 // no more (or would leave over a quarter of the 32 empty): the second half of the products would be work on nothing.
+// scores given: room for them; NULL: lse2 and Dv are there already.
 int launch_bwd_generic(const hf_config& c, const void* Q, const void* Q_hist, int n_q, const void* K, const void* V, int n_kv,
-                       const int32_t* idx, int k, const void* dO, const float* lse2, const float* Dv,
-                       const int32_t* inv_cnt, const int32_t* inv_list, const float* state, const float* cosq,
+                       const int32_t* idx, int k, const void* dO, float* lse2, float* Dv, const int32_t* inv_cnt,
+                       const int32_t* inv_list, const int32_t* inv_slot, float* scores, const float* state, const float* cosq,
                        const float* sinq, void* dQ, void* dQ_hist, void* dK, void* dV, hipStream_t s) {
-  WideBwdHist h = {};
+  WideBwd a = {};
+  a.Q = Q; a.K = K; a.V = V; a.dO = dO;
+  a.idx = idx;
+  a.k = k; a.n_q = n_q; a.n_kv = n_kv;
+  a.kv_stride = kv_stride_of(c, n_kv);
+  a.bq = c.block_q; a.bkv = c.block_kv;
+  a.t_m = (n_q + c.block_q - 1) / c.block_q;
+  a.t_n = (n_kv + c.block_kv - 1) / c.block_kv;
+  a.scale = c.softmax_scale > 0.0f ? c.softmax_scale : 1.0f / sqrtf((float)c.head_dim);
+  a.scale_log2e = a.scale * 1.4426950408889634f;
+  a.lse2 = lse2; a.Dv = Dv;
+  a.inv_cnt = inv_cnt; a.inv_list = inv_list; a.inv_slot = inv_slot;
+  a.scores = scores;
+  a.dQ = dQ; a.dK = dK; a.dV = dV;
   if (state) {
+    WideBwdHist& h = a.hist;
     h.L = state;
     h.z = state + (size_t)c.batch * c.heads * c.head_dim * c.head_dim;
     h.cosq = cosq;
@@ -835,23 +1222,27 @@ int launch_bwd_generic(const hf_config& c, const void* Q, const void* Q_hist, in
     h.z_scale = c.z_scale;
     h.phi_kind = c.phi;
   }
-  for (int keys = 0; keys < 2; ++keys) {
-    const int b = keys ? c.block_kv : c.block_q;
-    const bool two = (b + 31) / 32 * 32 * 3 <= b * 4;
-    int rc;
-#define HF_BWD_WIDE(T, DD, N)                                                                                          \
-  rc = launch_bwd_wide<T, DD, N>(c, Q, n_q, K, V, n_kv, idx, k, dO, lse2, Dv, inv_cnt, inv_list, h, dQ, dK, dV, keys != 0, s)
-    if (c.dtype == HF_F32) {
-      if (c.head_dim == 128) { if (two) HF_BWD_WIDE(float, 128, 2); else HF_BWD_WIDE(float, 128, 1); }
-      else { if (two) HF_BWD_WIDE(float, 64, 2); else HF_BWD_WIDE(float, 64, 1); }
-    } else {
-      if (c.head_dim == 128) { if (two) HF_BWD_WIDE(bf16_t, 128, 2); else HF_BWD_WIDE(bf16_t, 128, 1); }
-      else { if (two) HF_BWD_WIDE(bf16_t, 64, 2); else HF_BWD_WIDE(bf16_t, 64, 1); }
-    }
-#undef HF_BWD_WIDE
-    if (rc != HF_OK) return rc;
+  auto two = [](int b) { return (b + 31) / 32 * 32 * 3 <= b * 4; };
+  const bool q2 = two(c.block_q), k2 = two(c.block_kv);
+  const int q_rows = q2 ? 32 : 16, k_rows = k2 ? 32 : 16;
+  a.q_chunks = (c.block_q + q_rows - 1) / q_rows;
+  a.k_chunks = (c.block_kv + k_rows - 1) / k_rows;
+  const long long BH = (long long)c.batch * c.heads, q_total = BH * a.t_m * a.q_chunks, k_total = BH * a.t_n * a.k_chunks;
+  if (q_total > (1ll << 30) || k_total > (1ll << 30)) { set_error("too many blocks"); return HF_ERR_SHAPE; }
+  a.q_total = (int)q_total;
+  a.k_total = (int)k_total;
+  a.q_per_xcd = (int)((q_total + 7) / 8);
+  a.k_per_xcd = (int)((k_total + 7) / 8);
+#define HF_BWD_WIDE(T, DD)                                                                     \
+  return q2 ? (k2 ? launch_bwd_wide<T, DD, 2, 2>(a, s) : launch_bwd_wide<T, DD, 2, 1>(a, s))  \
+            : (k2 ? launch_bwd_wide<T, DD, 1, 2>(a, s) : launch_bwd_wide<T, DD, 1, 1>(a, s))
+  if (c.dtype == HF_F32) {
+    if (c.head_dim == 128) HF_BWD_WIDE(float, 128);
+    HF_BWD_WIDE(float, 64);
   }
-  return HF_OK;
+  if (c.head_dim == 128) HF_BWD_WIDE(bf16_t, 128);
+  HF_BWD_WIDE(bf16_t, 64);
+#undef HF_BWD_WIDE
 }
 
 }  // namespace hf
