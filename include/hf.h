@@ -462,7 +462,10 @@ HF_API int hf_hybrid_attn_fwd_save(const hf_config* cfg, const void* Q_local, co
                        void* O, void* O_local_out, float* lse2_out,
                        void* workspace, size_t workspace_bytes, void* stream);
 
-/* Bytes of scratch hf_hybrid_attn_bwd needs for these sizes.  Host-only. */
+/* Bytes of scratch hf_hybrid_attn_bwd takes for these sizes.  Host-only.  Outside bf16 at head_dim 128 with block_q 64 or 128
+ * (or with HF_FLAG_BWD_FP32_KERNELS) they hold two fp32 numbers per (query, key of its list), blocks rounded up to multiples
+ * of sixteen, where that is 2 GiB at most: what the three gradients have in common is then formed once.  A workspace without
+ * that room (a refusal names the least size) is accepted as well: every gradient forms its own. */
 HF_API int hf_bwd_workspace_bytes(const hf_config* cfg, int32_t n_q, int32_t n_kv, size_t* bytes_out);
 
 /* Gradients of O = O_local + O_hist (Eq. 5, 3, 6) for the step of the training algorithm that runs with

@@ -1231,11 +1231,11 @@ static int bwd_impl(const hf_config* cfg, const void* Q, const void* Q_hist, int
     const size_t bytes = (size_t)cfg->batch * cfg->heads * n_q * cfg->head_dim * esize(cfg);
     HF_TRY(launch_fill_zero(static_cast<float*>(dQ_hist), bytes / 4, s));
   }
+  int32_t* order = block_idx && !(cfg->flags & HF_FLAG_DKV_INDEX_ORDER) ? reinterpret_cast<int32_t*>(ws + w.order) : nullptr;
   if (mfma) {
     // row statistics of the softmax and D = dO . O_local: saved by the forward pass (D then from the once rounded O_local),
     // or from a recomputed one (unrounded); the history branch rides in the dQ kernel's epilogue
-    int32_t* order = block_idx && !(cfg->flags & HF_FLAG_DKV_INDEX_ORDER) ? reinterpret_cast<int32_t*>(ws + w.order) : nullptr;
-    HF_TRY(launch_bwd_prep(*cfg, block_idx, k, t_m, t_n, inv_cnt, inv_list, nullptr, order, st, ws + w.planes, saved ? dO : nullptr,
+    HF_TRY(launch_bwd_prep(*cfg, block_idx, k, t_m, t_n, inv_cnt, inv_list, nullptr, order, cdiv(cfg->block_kv, 64), st, ws + w.planes, saved ? dO : nullptr,
                            O_local, (long long)cfg->batch * cfg->heads * n_q, dvec, s));
     if (!saved) HF_TRY(launch_attn_mfma_stats(*cfg, Q, n_q, K_win, V_win, n_kv, block_idx, k, dO, lse2, dvec, s));
     return launch_bwd_mfma(*cfg, Q, n_q, K_win, V_win, n_kv, block_idx, k, dO, saved ? lse2_saved : lse2, dvec, inv_cnt, inv_list,
@@ -1246,10 +1246,11 @@ static int bwd_impl(const hf_config* cfg, const void* Q, const void* Q_hist, int
   const size_t score_bytes = bwd_scores_bytes(*cfg, n_q, k);
   float* scores = score_bytes && workspace_bytes >= w.scores + score_bytes ? reinterpret_cast<float*>(ws + w.scores) : nullptr;
   int32_t* inv_slot = scores && block_idx ? reinterpret_cast<int32_t*>(ws + w.inv_slot) : nullptr;
-  HF_TRY(launch_bwd_prep(*cfg, block_idx, k, t_m, t_n, inv_cnt, inv_list, inv_slot, nullptr, nullptr, nullptr, nullptr, nullptr, 0, nullptr, s));
+  HF_TRY(launch_bwd_prep(*cfg, block_idx, k, t_m, t_n, inv_cnt, inv_list, inv_slot, scores ? order : nullptr, 1, nullptr, nullptr, nullptr,
+                         nullptr, 0, nullptr, s));
   if (!scores) HF_TRY(launch_attn_wide_stats(*cfg, Q, n_q, K_win, V_win, n_kv, block_idx, k, dO, lse2, dvec, s));
   return launch_bwd_generic(*cfg, Q, Q_hist, n_q, K_win, V_win, n_kv, block_idx, k, dO, lse2, dvec, inv_cnt, inv_list, inv_slot,
-                            scores, st, rope_cos_q, rope_sin_q, dQ, st ? dQ_hist : nullptr, dK, dV, s);
+                            order, scores, st, rope_cos_q, rope_sin_q, dQ, st ? dQ_hist : nullptr, dK, dV, s);
 }
 
 int hf_rope_window_indices(int32_t i_newest, int32_t n_frames, int32_t t0, int32_t* idx_out) {

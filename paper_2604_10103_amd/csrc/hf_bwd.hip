@@ -5,7 +5,8 @@
 // arithmetic on the fp32 matrix instruction, hf_f32_mfma.h) and the small helpers shared with the bf16 path.
 //
 // With P recomputed from the saved row statistic lse2 = log2 sum_j 2^(c s_ij) (c = scale log2 e):
-//     D_i  = dO_i . O_local_i      (from the recomputed forward pass, before O_local is rounded)
+//     D_i  = dO_i . O_local_i = sum_j P_ij dP_ij   (with stored scores the sum; else the product, from the recomputed forward
+//                                                    pass, before O_local is rounded)
 //     dV_j = sum_i P_ij dO_i               dP_ij = dO_i . v_j
 //     dS_ij = P_ij (dP_ij - D_i)
 //     dQ_i = scale sum_j dS_ij k_j         dK_j = scale sum_i dS_ij q_i
@@ -296,28 +297,41 @@ struct WideBwdHist {
 
 constexpr int kParts = 4;   // wavefronts of a workgroup: they share its rows (keys) and split the list between them
 
-// the parts of a [16 N][D] result (column-form accumulators) meet in LDS; whole rows are stored
-template <typename T, int D, int N>
-__device__ __forceinline__ void add_parts_and_store(float* smem, const f32x4 (&acc)[N][D / 64][4], float mul, int kz, int l16,
-                                                    int g, T* dst, int rows) {
-  constexpr int OST = D + 4, F = D / 64;
+constexpr int kStoredWaves = 8;   // of a workgroup that works from stored scores
+
+// The parts of a [16 N][D] result (column-form accumulators, FW pieces of 64 features from 64 f0 on) meet in LDS, AT_ONCE of
+// PARTS at a time: [AT_ONCE][16 N][D + 4].  on_top (uniform): the first's place holds something that is added to.
+template <int D, int N, int PARTS, int AT_ONCE, int FW>
+__device__ __forceinline__ void add_parts(float* smem, const f32x4 (&acc)[N][FW][4], float mul, bool on_top, int part, int f0, int l16,
+                                          int g) {
+  constexpr int OST = D + 4, TURNS = PARTS / AT_ONCE;
+  float* const own = smem + ((part % AT_ONCE) * 16 * N + l16) * OST + 64 * f0 + 16 * g;
 #pragma unroll
-  for (int n = 0; n < N; ++n) {
-    float* p = smem + ((size_t)kz * 16 * N + 16 * n + l16) * OST + 16 * g;
+  for (int turn = TURNS - 1; turn >= 0; --turn) {
+    if (part / AT_ONCE == turn)   // uniform
 #pragma unroll
-    for (int f = 0; f < F; ++f)
+      for (int n = 0; n < N; ++n)
 #pragma unroll
-      for (int r = 0; r < 4; ++r)
-        *reinterpret_cast<f32x4*>(p + 64 * f + 4 * r) =
-            f32x4{acc[n][f][0][r], acc[n][f][1][r], acc[n][f][2][r], acc[n][f][3][r]} * mul;
+        for (int f = 0; f < FW; ++f)
+#pragma unroll
+          for (int r = 0; r < 4; ++r) {
+            f32x4* const at = reinterpret_cast<f32x4*>(own + 16 * n * OST + 64 * f + 4 * r);
+            const f32x4 v = f32x4{acc[n][f][0][r], acc[n][f][1][r], acc[n][f][2][r], acc[n][f][3][r]} * mul;
+            *at = turn < TURNS - 1 || (on_top && part % AT_ONCE == 0) ? v + *at : v;
+          }
+    __syncthreads();
   }
-  __syncthreads();
-  for (int e = threadIdx.x; e < 16 * N * (D / 4); e += 64 * kParts) {
+}
+// ... and whole rows are stored
+template <typename T, int D, int N, int AT_ONCE, int WAVES>
+__device__ __forceinline__ void store_parts(const float* smem, T* dst, int rows) {
+  constexpr int OST = D + 4;
+  for (int e = threadIdx.x; e < 16 * N * (D / 4); e += 64 * WAVES) {
     const int rr = e / (D / 4), c4 = e - rr * (D / 4);
     if (rr >= rows) continue;
     f32x4 v = *reinterpret_cast<const f32x4*>(smem + (size_t)rr * OST + 4 * c4);
 #pragma unroll
-    for (int u = 1; u < kParts; ++u) v += *reinterpret_cast<const f32x4*>(smem + ((size_t)u * 16 * N + rr) * OST + 4 * c4);
+    for (int u = 1; u < AT_ONCE; ++u) v += *reinterpret_cast<const f32x4*>(smem + ((size_t)u * 16 * N + rr) * OST + 4 * c4);
     store4<T>(dst + (size_t)rr * D + 4 * c4, v);
   }
 }
@@ -328,6 +342,7 @@ struct WideBwd {
   int k, n_q, n_kv, kv_stride, bq, bkv, t_m, t_n;
   int q_chunks, q_per_xcd, q_total;                // workgroups of the query side: chunks of a block, items of an XCD's share, items
   int k_chunks, k_per_xcd, k_total;                // of the key side
+  const int32_t* order;                            // stored scores: KV blocks, longest list first (records of kOrderRec), or NULL
   float scale_log2e, scale;
   float *lse2, *Dv;                                // [BH][n_q]
   const int32_t *inv_cnt, *inv_list, *inv_slot;    // [BH][t_n], [BH][t_n][t_m]; dense: NULL
@@ -339,21 +354,26 @@ struct WideBwd {
 // Stored scores: a panel per (query block, place of its list), a panel's tiles of 16 queries x 16 keys row by row, a tile's S
 // [query][key] (times scale log2 e) and then its dP.
 constexpr int kScoreTile = 2 * 16 * 16;
-constexpr size_t kScoresMax = (size_t)2 << 30;
+constexpr size_t kScoresMax = (size_t)2 << 30;   // (24 heads of 64, 1458 x 4374, half of the keys, 1.2 GB: 981 us forming them again, 849 stored)
 __device__ __forceinline__ const float* score_tile(const WideBwd& a, int bh, int qb, int slot, int qi, int ki) {
   const int qt = (a.bq + 15) / 16, kt = (a.bkv + 15) / 16;
   return a.scores + ((((size_t)bh * a.t_m + qb) * a.k + slot) * (qt * kt) + qi * kt + ki) * kScoreTile;
 }
 
-// ---- S^T = K Q^T and dP^T = V dO^T, once for all three gradients: a workgroup per 16 NQ query rows, its four wavefronts
+// ---- S^T = K Q^T and dP^T = V dO^T, once for all three gradients: a workgroup per 16 NQ query rows, its eight wavefronts
 // splitting the list; both go to memory as fp32 (score_tile), and lse2 and D = sum_j P_ij dP_ij leave with them, so that no
 // forward pass is formed again: five products of the forward's size instead of nine (two of the statistics, three for dQ, four
 // for dK and dV).  Statistics are a lane's own until the end: maximum, sum and weighted sum over the keys it holds.
+// Bound by the fp32 matrix rate at the clock it holds (2.0 GHz): 12 heads of 128, 1170 x 2340, k = 10 of 37 blocks of 64: 59 us,
+// the pipes 66 % busy while a compute unit has work (456 workgroups leave 14 % of them idle); with the gradients behind it (98)
+// instead of statistics (42), dQ (93) and dK, dV (122): 74 training steps 0.60 to 0.87 of the time, 0.69 in the mean.  Errors
+// against 64 bits are no larger (dQ 6.1e-7 -> 6.0e-7, with four times the queries 2.8e-6 -> 1.4e-6).
+constexpr int kScoreParts = 8;
 template <typename T, int D, int NQ>
-__global__ __launch_bounds__(64 * kParts, 2) void bwd_scores_kernel(WideBwd a) {
+__global__ __launch_bounds__(64 * kScoreParts, 4) void bwd_scores_kernel(WideBwd a) {
   constexpr int ROWS = 16 * NQ, C = D / 16, OST = D + 4;
   extern __shared__ __attribute__((aligned(16))) float smem[];   // [ROWS][OST] Q, [ROWS][OST] dO
-  __shared__ float stat[3][kParts][ROWS];
+  __shared__ float stat[3][kScoreParts][ROWS];
   float* sQ = smem;
   float* sG = smem + ROWS * OST;
   const int wg = blockIdx.x, item = (wg & 7) * a.q_per_xcd + (wg >> 3);
@@ -372,7 +392,7 @@ __global__ __launch_bounds__(64 * kParts, 2) void bwd_scores_kernel(WideBwd a) {
   const int32_t* __restrict__ row_idx = a.idx ? a.idx + ((size_t)bh * a.t_m + qb) * a.k : nullptr;
   const int nsel = a.idx ? a.k : t_n, subs = (bkv + 15) / 16, ntiles = nsel * subs;
   const int qt = (bq + 15) / 16, qi0 = (row0 - qb * bq) / 16;
-  for (int e = threadIdx.x; e < ROWS * (D / 4); e += 64 * kParts) {
+  for (int e = threadIdx.x; e < ROWS * (D / 4); e += 64 * kScoreParts) {
     const int rr = e / (D / 4), c4 = e - rr * (D / 4);
     const size_t off = ((size_t)bh * n_q + min(row0 + rr, n_q - 1)) * D + 4 * c4;
     *reinterpret_cast<f32x4*>(sQ + rr * OST + 4 * c4) = load4<T>(Q + off) * a.scale_log2e;
@@ -410,9 +430,9 @@ __global__ __launch_bounds__(64 * kParts, 2) void bwd_scores_kernel(WideBwd a) {
   }
   const float* bq0 = sQ + l16 * OST + 4 * g;
   const float* bg0 = sG + l16 * OST + 4 * g;
-  for (int t = kz; t < ntiles; t += kParts) {
+  for (int t = kz; t < ntiles; t += kScoreParts) {
     asm volatile("" : "+v"(row_at));   // (opaque here, or its sums leave the loop as registers instead of immediates)
-    tile_at(t + kParts, first_n, cnt_n);
+    tile_at(t + kScoreParts, first_n, cnt_n);
     const __amdgpu_buffer_rsrc_t kn_rows = tile_rows<T, D>(Kh, first_n, cnt_n), vn_rows = tile_rows<T, D>(Vh, first_n, cnt_n);
     f32x4 s[NQ], p[NQ];
 #pragma unroll
@@ -441,14 +461,14 @@ __global__ __launch_bounds__(64 * kParts, 2) void bwd_scores_kernel(WideBwd a) {
       const int slot = t / subs;
 #pragma unroll
       for (int n = 0; n < NQ; ++n) {
+        if (cnt < 16)   // keys that do not exist: probability zero
+#pragma unroll
+          for (int r = 0; r < 4; ++r) s[n][r] = 4 * g + r < cnt ? s[n][r] : -__builtin_inff();
         if (qi0 + n < qt) {
           float* tile = const_cast<float*>(score_tile(a, bh, qb, slot, qi0 + n, t - slot * subs)) + 16 * l16 + 4 * g;
           *reinterpret_cast<f32x4*>(tile) = s[n];
           *reinterpret_cast<f32x4*>(tile + kScoreTile / 2) = p[n];
         }
-        if (cnt < 16)
-#pragma unroll
-          for (int r = 0; r < 4; ++r) s[n][r] = 4 * g + r < cnt ? s[n][r] : -__builtin_inff();
         const float top = fmaxf(fmaxf(fmaxf(s[n][0], s[n][1]), fmaxf(s[n][2], s[n][3])), m[n]);
         const float kept = __builtin_amdgcn_exp2f(m[n] - top);
         float sum = 0.0f, weighted = 0.0f;
@@ -480,16 +500,157 @@ __global__ __launch_bounds__(64 * kParts, 2) void bwd_scores_kernel(WideBwd a) {
   if (rr < ROWS && row0 + rr < q_end) {
     float top = stat[0][0][rr], sum = 0.0f, weighted = 0.0f;
 #pragma unroll
-    for (int u = 1; u < kParts; ++u) top = fmaxf(top, stat[0][u][rr]);
+    for (int u = 1; u < kScoreParts; ++u) top = fmaxf(top, stat[0][u][rr]);
 #pragma unroll
-    for (int u = 0; u < kParts; ++u) {
+    for (int u = 0; u < kScoreParts; ++u) {
       const float w = __builtin_amdgcn_exp2f(stat[0][u][rr] - top);
       sum = fmaf(stat[1][u][rr], w, sum);
       weighted = fmaf(stat[2][u][rr], w, weighted);
     }
     const size_t at = (size_t)bh * n_q + row0 + rr;
-    a.lse2[at] = top + __builtin_amdgcn_logf(sum);
-    a.Dv[at] = weighted / sum;
+    const bool none = sum == 0.0f;   // no key at all (an empty list): probabilities are zero
+    a.lse2[at] = none ? __builtin_inff() : top + __builtin_amdgcn_logf(sum);
+    a.Dv[at] = none ? 0.0f : weighted / sum;
+  }
+}
+
+// Gradient of the history branch with respect to its queries, for the workgroup's rows (dO in sG; sQ is written): to dq_hist
+// where it is given, else sink(n, f, pr, r, v0, v1) has the values of row 16 n + l % 16, features 64 f + 16 (l / 16) + 4 r + 2 pr, + 1.
+template <typename T, int D, int NQ, int WAVES, typename Sink>
+__device__ __forceinline__ void history_gradient(const WideBwdHist& hist, int bh, int row0, int q_end, int n_q, int kz, int l16,
+                                                 int g, float* sQ, const float* sG, Sink sink) {
+  constexpr int ROWS = 16 * NQ, C = D / 16, F = D / 64, OST = D + 4;
+  constexpr int SPLIT = WAVES / (2 * F), NP = (NQ + SPLIT - 1) / SPLIT;   // wavefronts that share the rows; sixteens of rows of one
+  __shared__ float gpart[ROWS][2 * F], dpart[ROWS][WAVES];
+  const float* bq0 = sQ + l16 * OST + 4 * g;
+  const float* bg0 = sG + l16 * OST + 4 * g;
+  // Wavefront kz computes, for its rows, the value features (of num) and key features (of the gradient) 64 f + 4 i + 2 pr and
+  // + 1: one rotation pair in one lane
+  const float* L = hist.L + (size_t)bh * D * D;
+  const float* z = hist.z + (size_t)bh * D;
+  const T* qh = static_cast<const T*>(hist.q_hist);
+#pragma unroll
+  for (int n = 0; n < NQ; ++n) {   // every wavefront its share of the features: R(phi(q)) into Q's place, its part of phi(q).z
+    const size_t qrow = (size_t)min(row0 + 16 * n + l16, n_q - 1);
+    float acc = 0.0f;
+#pragma unroll
+    for (int u = 0; u < (C + WAVES - 1) / WAVES; ++u) {
+      const int c = kz + WAVES * u;
+      if (C % WAVES && c >= C) break;   // uniform
+      f32x4 x = load4<T>(qh + ((size_t)bh * n_q + qrow) * D + 16 * c + 4 * g);
+      const f32x4 zz = *reinterpret_cast<const f32x4*>(z + 16 * c + 4 * g);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        x[e] = phi_apply(x[e], hist.phi_kind);
+        acc = fmaf(x[e], zz[e], acc);
+      }
+      if (hist.cosq) {
+        const size_t at = qrow * (D / 2) + 8 * c + 2 * g;
+        const f32x2 cs = *reinterpret_cast<const f32x2*>(hist.cosq + at), sn = *reinterpret_cast<const f32x2*>(hist.sinq + at);
+        x = rotate4(x, cs[0], sn[0], cs[1], sn[1]);
+      }
+      *reinterpret_cast<f32x4*>(sQ + (16 * n + l16) * OST + 16 * c + 4 * g) = x;
+    }
+    acc = column_sum(acc);
+    if (g == 0) dpart[16 * n + l16][kz] = acc;
+  }
+  __syncthreads();
+  const int f0 = (kz >> 1) % F, pr = kz & 1, n0 = kz / (2 * F) * NP;
+  const bool active = n0 < NQ;   // uniform
+  float den[NP];
+#pragma unroll
+  for (int n = 0; n < NP; ++n) {
+    float acc = 0.0f;
+#pragma unroll
+    for (int u = 0; u < (C < WAVES ? C : WAVES); ++u) acc += dpart[16 * min(n0 + n, NQ - 1) + l16][u];
+    den[n] = 1.0f / (hist.z_scale * acc + hist.eps);   // (the reciprocal from here on)
+  }
+  if (active) {
+    f32x4 num[NP][2];
+#pragma unroll
+    for (int n = 0; n < NP; ++n) num[n][0] = num[n][1] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+#pragma unroll 2
+    for (int c = 0; c < C; ++c) {
+      f32x2 a[4];
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+        a[r] = *reinterpret_cast<const f32x2*>(L + (size_t)(16 * c + 4 * g + r) * D + 64 * f0 + 4 * l16 + 2 * pr);
+#pragma unroll
+      for (int n = 0; n < NP; ++n) {
+        const f32x4 b = *reinterpret_cast<const f32x4*>(bq0 + 16 * (n0 + n) * OST + 16 * c);
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          num[n][0] = mfma_f32(a[r][0], b[r], num[n][0]);
+          num[n][1] = mfma_f32(a[r][1], b[r], num[n][1]);
+        }
+      }
+    }
+#pragma unroll
+    for (int n = 0; n < NP; ++n) {
+      float acc = 0.0f;
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const f32x2 x = *reinterpret_cast<const f32x2*>(sG + (16 * (n0 + n) + l16) * OST + 64 * f0 + 16 * g + 4 * r + 2 * pr);
+        acc = fmaf(num[n][0][r], x[0], fmaf(num[n][1][r], x[1], acc));
+      }
+      acc = column_sum(acc);
+      if (g == 0) gpart[16 * (n0 + n) + l16][kz % (2 * F)] = acc;
+    }
+  }
+  __syncthreads();
+  if (active) {
+    f32x4 tt[NP][2];
+#pragma unroll
+    for (int n = 0; n < NP; ++n) tt[n][0] = tt[n][1] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+    const float* La = L + (size_t)(64 * f0 + 4 * l16 + 2 * pr) * D + 4 * g;
+#pragma unroll 2
+    for (int c = 0; c < C; ++c) {
+      const f32x4 a0 = *reinterpret_cast<const f32x4*>(La + 16 * c), a1 = *reinterpret_cast<const f32x4*>(La + D + 16 * c);
+#pragma unroll
+      for (int n = 0; n < NP; ++n) {
+        const f32x4 b = *reinterpret_cast<const f32x4*>(bg0 + 16 * (n0 + n) * OST + 16 * c);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          tt[n][0] = mfma_f32(a0[e], b[e], tt[n][0]);
+          tt[n][1] = mfma_f32(a1[e], b[e], tt[n][1]);
+        }
+      }
+    }
+#pragma unroll
+    for (int n = 0; n < NP; ++n) {
+      const int rr = row0 + 16 * (n0 + n) + l16;
+      const size_t qrow = (size_t)min(rr, n_q - 1);
+      float gn = 0.0f;
+#pragma unroll
+      for (int u = 0; u < 2 * F; ++u) gn += gpart[16 * (n0 + n) + l16][u];
+      const float dden = -gn * den[n] * den[n] * hist.z_scale;
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int feat = 64 * f0 + 16 * g + 4 * r + 2 * pr;
+        float t0 = tt[n][0][r] * den[n], t1 = tt[n][1][r] * den[n];
+        if (hist.cosq) {   // the opposite angle
+          const float cs = hist.cosq[qrow * (D / 2) + feat / 2], sn = hist.sinq[qrow * (D / 2) + feat / 2];
+          const float u0 = t0 * cs + t1 * sn;
+          t1 = t1 * cs - t0 * sn;
+          t0 = u0;
+        }
+        const T* qp = qh + ((size_t)bh * n_q + qrow) * D + feat;
+        const float q0 = Elem<T>::load(qp), q1 = Elem<T>::load(qp + 1);
+        const bool relu = hist.phi_kind == HF_PHI_RELU;
+        const float d0 = q0 > 0.0f ? 1.0f : (relu ? 0.0f : __expf(q0)), d1 = q1 > 0.0f ? 1.0f : (relu ? 0.0f : __expf(q1));
+        const f32x2 zz = *reinterpret_cast<const f32x2*>(z + feat);
+        const float v0 = fmaf(dden, zz[0], t0) * d0, v1 = fmaf(dden, zz[1], t1) * d1;
+        if (hist.dq_hist) {
+          if (rr < q_end) {
+            T* dst = static_cast<T*>(hist.dq_hist) + ((size_t)bh * n_q + rr) * D + feat;
+            Elem<T>::store(dst, v0);
+            Elem<T>::store(dst + 1, v1);
+          }
+        } else {
+          sink(n0 + n, f0, pr, r, v0, v1);
+        }
+      }
+    }
   }
 }
 
@@ -501,9 +662,10 @@ __global__ __launch_bounds__(64 * kParts, 2) void bwd_scores_kernel(WideBwd a) {
 // 0.21 ms for the history branch's gradient as a kernel of its own).
 template <typename T, int D, int NQ, bool kStored>
 __device__ __forceinline__ void dq_role(const WideBwd& a, int wg, float* __restrict__ smem) {
-  constexpr int ROWS = 16 * NQ, C = D / 16, F = D / 64, OST = D + 4;
-  __shared__ float gpart[ROWS][kParts];
-  float* sQ = smem;                 // [ROWS][OST] Q, [ROWS][OST] dO; later four partial results
+  // with stored scores the wavefronts split a head's features as well as the list
+  constexpr int ROWS = 16 * NQ, F = D / 64, OST = D + 4, WAVES = kStored ? kStoredWaves : kParts, FW = kStored ? 1 : F;
+  constexpr int PARTS = WAVES * FW / F, AT_ONCE = kStored ? 2 : PARTS;
+  float* sQ = smem;                 // [ROWS][OST] Q, [ROWS][OST] dO; later partial results
   float* sG = smem + ROWS * OST;
   const T* __restrict__ Q = static_cast<const T*>(a.Q);
   const T* __restrict__ dO = static_cast<const T*>(a.dO);
@@ -517,49 +679,61 @@ __device__ __forceinline__ void dq_role(const WideBwd& a, int wg, float* __restr
   if (row0 >= q_end) return;
   const int lane = threadIdx.x & 63, kz = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int l16 = lane & 15, g = lane >> 4;
+  const int part = kz % PARTS, f_own = kz / PARTS;   // (f_own: the first of the wavefront's FW pieces of 64 features)
   const T* __restrict__ Kh = static_cast<const T*>(a.K) + (size_t)bh * a.kv_stride * D;
   const T* __restrict__ Vh = static_cast<const T*>(a.V) + (size_t)bh * a.kv_stride * D;
   const int32_t* __restrict__ row_idx = a.idx ? a.idx + ((size_t)bh * t_m + qb) * k : nullptr;
   const int nsel = a.idx ? k : t_n, subs = (bkv + 15) / 16, ntiles = nsel * subs;
 
   if (!kStored || hist.L)   // (uniform; with stored scores only the history branch reads them)
-    for (int e = threadIdx.x; e < ROWS * (D / 4); e += 64 * kParts) {
+    for (int e = threadIdx.x; e < ROWS * (D / 4); e += 64 * WAVES) {
       const int rr = e / (D / 4), c4 = e - rr * (D / 4);
       const size_t off = ((size_t)bh * n_q + min(row0 + rr, n_q - 1)) * D + 4 * c4;
       if (!kStored) *reinterpret_cast<f32x4*>(sQ + rr * OST + 4 * c4) = load4<T>(Q + off) * a.scale_log2e;
       *reinterpret_cast<f32x4*>(sG + rr * OST + 4 * c4) = load4<T>(dO + off);
     }
+  __syncthreads();
+
   float lse[NQ], dv[NQ];
-  f32x4 dq[NQ][F][4];
+  f32x4 dq[NQ][FW][4];
 #pragma unroll
   for (int n = 0; n < NQ; ++n) {
     const size_t at = (size_t)bh * n_q + min(row0 + 16 * n + l16, n_q - 1);
     lse[n] = a.lse2[at];
     dv[n] = a.Dv[at];
-#pragma unroll
-    for (int f = 0; f < F; ++f)
-#pragma unroll
-      for (int e = 0; e < 4; ++e) dq[n][f][e] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
   }
-  __syncthreads();
-
+  auto zero = [&]() {
+#pragma unroll
+    for (int n = 0; n < NQ; ++n)
+#pragma unroll
+      for (int f = 0; f < FW; ++f)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) dq[n][f][e] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+  };
   auto tile_at = [&](int t, int& first, int& cnt) {   // cnt 0: past the list, an index out of range, or no such keys
     const int s = t / subs, sub = t - s * subs;
-    const int jb = row_idx ? row_idx[min(s, nsel - 1)] : s;
+    // (no branch, which in the loop would have the accumulators kept twice: a dense window has some word read in its place)
+    const int e = (row_idx ? row_idx : reinterpret_cast<const int32_t*>(a.lse2))[row_idx ? min(s, nsel - 1) : 0];
+    const int jb = row_idx ? e : s;
     const int st = jb * bkv + 16 * sub;
     const bool ok = s < nsel && (unsigned)jb < (unsigned)t_n;
     const int n = ok ? min(16, min(n_kv, (jb + 1) * bkv) - st) : 0;
     cnt = n > 0 ? n : 0;
     first = n > 0 ? st : 0;
   };
-  const float* bq0 = sQ + l16 * OST + 4 * g;
-  const float* bg0 = sG + l16 * OST + 4 * g;
   if constexpr (kStored) {
+    if (hist.L) {   // first, into Q's place, while the accumulators' registers are free
+      history_gradient<T, D, NQ, WAVES>(hist, bh, row0, q_end, n_q, kz, l16, g, sQ, sG, [&](int n, int f, int pr, int r, float v0, float v1) {
+        *reinterpret_cast<f32x2*>(sQ + (16 * n + l16) * OST + 64 * f + 16 * g + 4 * r + 2 * pr) = f32x2{v0, v1};
+      });
+      __syncthreads();
+    }
+    zero();
     // S and dP of a tile lie where bwd_scores_kernel left them, four keys of a query to a lane: what the B operand takes.
     const int qt = (bq + 15) / 16, qi0 = (row0 - qb * bq) / 16;
     constexpr int B = sizeof(T);
-    int col_at = (4 * g * D + 4 * l16) * B, tile_lane = (16 * l16 + 4 * g) * 4;
-    Piece<T> kc[4][F];
+    int col_at = (4 * g * D + 64 * f_own + 4 * l16) * B, tile_lane = (16 * l16 + 4 * g) * 4;
+    Piece<T> kc[4];
     f32x4 s[NQ], p[NQ];
     auto request_scores = [&](int t, int cnt) {
       const int slot = t / subs, sub = t - slot * subs;
@@ -571,41 +745,40 @@ __device__ __forceinline__ void dq_role(const WideBwd& a, int wg, float* __restr
         p[n] = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(r, tile_lane + kScoreTile * 2, 0, 0));
       }
     };
-    int first, cnt, first_n, cnt_n;
-    tile_at(kz, first, cnt);
-    request_scores(kz, __builtin_amdgcn_readfirstlane(cnt));
-    {
-      const __amdgpu_buffer_rsrc_t k_rows = tile_rows<T, D>(Kh, first, cnt);
+    int first, cnt;
+    tile_at(part, first, cnt);
+    request_scores(part, __builtin_amdgcn_readfirstlane(cnt));
+    const __amdgpu_buffer_rsrc_t k_rows = tile_rows<T, D>(Kh, first, cnt);
 #pragma unroll
-      for (int u = 0; u < 4 * F; ++u) kc[u / F][u % F].load(k_rows, col_at + (u / F * D + 64 * (u % F)) * B);
-    }
-    for (int t = kz; t < ntiles; t += kParts) {
-      asm volatile("" : "+v"(col_at), "+v"(tile_lane));   // (as above)
-      f32x4 ds[NQ];
+    for (int u = 0; u < 4; ++u) kc[u].load(k_rows, col_at + u * D * B);
+    for (int t = part; t < ntiles; t += PARTS) {
+      asm volatile("" : "+v"(col_at), "+v"(tile_lane));   // (opaque here, or their sums leave the loop as registers instead of immediates)
+      f32x4 ds[NQ];   // zero for a key that does not exist: its S is -inf, or the tile has none
 #pragma unroll
-      for (int n = 0; n < NQ; ++n)
+      for (int n = 0; n < NQ; ++n) {
+        const float off = cnt > 0 ? lse[n] : __builtin_inff();
 #pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          const float d = __builtin_amdgcn_exp2f(s[n][r] - lse[n]) * (p[n][r] - dv[n]);
-          ds[n][r] = 4 * g + r < cnt ? d : 0.0f;   // zero for a key that does not exist
-        }
-      tile_at(t + kParts, first_n, cnt_n);
-      request_scores(t + kParts, __builtin_amdgcn_readfirstlane(cnt_n));
-      const __amdgpu_buffer_rsrc_t kn_rows = tile_rows<T, D>(Kh, first_n, cnt_n);
-      __builtin_amdgcn_sched_barrier(0);
+        for (int r = 0; r < 4; ++r) ds[n][r] = __builtin_amdgcn_exp2f(s[n][r] - off) * (p[n][r] - dv[n]);
+      }
+      tile_at(t + PARTS, first, cnt);
+      const __amdgpu_buffer_rsrc_t kn_rows = tile_rows<T, D>(Kh, first, cnt);
 #pragma unroll
-      for (int u = 0; u < 4 * F; ++u) {
-        const f32x4 ka = kc[u / F][u % F].get();
+      for (int u = 0; u < 4; ++u) {
+        if (u == 2) request_scores(t + PARTS, __builtin_amdgcn_readfirstlane(cnt));
+        const f32x4 ka = kc[u].get();
 #pragma unroll
         for (int e = 0; e < 4; ++e)
 #pragma unroll
-          for (int n = 0; n < NQ; ++n) dq[n][u % F][e] = mfma_f32(ka[e], ds[n][u / F], dq[n][u % F][e]);
-        kc[u / F][u % F].load(kn_rows, col_at + (u / F * D + 64 * (u % F)) * B);
+          for (int n = 0; n < NQ; ++n) dq[n][0][e] = mfma_f32(ka[e], ds[n][u], dq[n][0][e]);
+        kc[u].load(kn_rows, col_at + u * D * B);
         __builtin_amdgcn_sched_barrier(0);
       }
-      cnt = cnt_n;
     }
   } else {
+    zero();
+    const float* bq0 = sQ + l16 * OST + 4 * g;
+    const float* bg0 = sG + l16 * OST + 4 * g;
+    constexpr int C = D / 16;
     Piece<T> kr[C], vr[C], kc[4][F];
     int first, cnt, first_n, cnt_n;
     tile_at(kz, first, cnt);
@@ -677,149 +850,37 @@ __device__ __forceinline__ void dq_role(const WideBwd& a, int wg, float* __restr
 #pragma unroll
   for (int n = 0; n < NQ; ++n)
 #pragma unroll
-    for (int f = 0; f < F; ++f)
+    for (int f = 0; f < FW; ++f)
 #pragma unroll
       for (int e = 0; e < 4; ++e) dq[n][f][e] *= a.scale;
   __syncthreads();   // Q and dO are read no more as operands of the loop
 
-  if (hist.L) {
-    // ---- wavefront kz < 2 F computes, for every row, the value features (of num) and key features (of the gradient)
-    // 64 f + 4 i + 2 pr and + 1, f = kz / 2, pr = kz % 2: one rotation pair in one lane
-    const float* L = hist.L + (size_t)bh * D * D;
-    const float* z = hist.z + (size_t)bh * D;
-    const T* qh = static_cast<const T*>(hist.q_hist);
-    float den[NQ];
+  if constexpr (!kStored) {
+    if (hist.L) {
+      history_gradient<T, D, NQ, WAVES>(hist, bh, row0, q_end, n_q, kz, l16, g, sQ, sG, [&](int n, int f0, int pr, int r, float v0, float v1) {
 #pragma unroll
-    for (int n = 0; n < NQ; ++n) {
-      const size_t qrow = (size_t)min(row0 + 16 * n + l16, n_q - 1);
-      float acc = 0.0f;
+        for (int m = 0; m < NQ; ++m)   // (constant indices into the accumulators)
 #pragma unroll
-      for (int c = 0; c < C; ++c) {
-        f32x4 x = load4<T>(qh + ((size_t)bh * n_q + qrow) * D + 16 * c + 4 * g);
-        const f32x4 zz = *reinterpret_cast<const f32x4*>(z + 16 * c + 4 * g);
+          for (int f = 0; f < FW; ++f)
 #pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          x[e] = phi_apply(x[e], hist.phi_kind);
-          acc = fmaf(x[e], zz[e], acc);
-        }
-        if (c % kParts == kz) {   // uniform: R(phi(q)) into Q's place, every wavefront its share
-          if (hist.cosq) {
-            const size_t at = qrow * (D / 2) + 8 * c + 2 * g;
-            const f32x2 cs = *reinterpret_cast<const f32x2*>(hist.cosq + at), sn = *reinterpret_cast<const f32x2*>(hist.sinq + at);
-            x = rotate4(x, cs[0], sn[0], cs[1], sn[1]);
-          }
-          *reinterpret_cast<f32x4*>(sQ + (16 * n + l16) * OST + 16 * c + 4 * g) = x;
-        }
-      }
-      den[n] = 1.0f / (hist.z_scale * column_sum(acc) + hist.eps);   // (the reciprocal from here on)
+            for (int q = 0; q < 2; ++q)
+              if (m == n && f == f0 && q == pr) {
+                dq[m][f][2 * q][r] += v0;
+                dq[m][f][2 * q + 1][r] += v1;
+              }
+      });
+      __syncthreads();
     }
-    __syncthreads();
-    const int f0 = kz >> 1, pr = kz & 1;
-    const bool active = kz < 2 * F;   // uniform
-    if (active) {
-      f32x4 num[NQ][2];
-#pragma unroll
-      for (int n = 0; n < NQ; ++n) num[n][0] = num[n][1] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
-#pragma unroll 2
-      for (int c = 0; c < C; ++c) {
-        f32x2 a[4];
-#pragma unroll
-        for (int r = 0; r < 4; ++r)
-          a[r] = *reinterpret_cast<const f32x2*>(L + (size_t)(16 * c + 4 * g + r) * D + 64 * f0 + 4 * l16 + 2 * pr);
-#pragma unroll
-        for (int n = 0; n < NQ; ++n) {
-          const f32x4 b = *reinterpret_cast<const f32x4*>(bq0 + 16 * n * OST + 16 * c);
-#pragma unroll
-          for (int r = 0; r < 4; ++r) {
-            num[n][0] = mfma_f32(a[r][0], b[r], num[n][0]);
-            num[n][1] = mfma_f32(a[r][1], b[r], num[n][1]);
-          }
-        }
-      }
-#pragma unroll
-      for (int n = 0; n < NQ; ++n) {
-        float acc = 0.0f;
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          const f32x2 x = *reinterpret_cast<const f32x2*>(sG + (16 * n + l16) * OST + 64 * f0 + 16 * g + 4 * r + 2 * pr);
-          acc = fmaf(num[n][0][r], x[0], fmaf(num[n][1][r], x[1], acc));
-        }
-        acc = column_sum(acc);
-        if (g == 0) gpart[16 * n + l16][kz] = acc;
-      }
-    }
-    __syncthreads();
-    if (active) {
-      f32x4 tt[NQ][2];
-#pragma unroll
-      for (int n = 0; n < NQ; ++n) tt[n][0] = tt[n][1] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
-      const float* La = L + (size_t)(64 * f0 + 4 * l16 + 2 * pr) * D + 4 * g;
-#pragma unroll 2
-      for (int c = 0; c < C; ++c) {
-        const f32x4 a0 = *reinterpret_cast<const f32x4*>(La + 16 * c), a1 = *reinterpret_cast<const f32x4*>(La + D + 16 * c);
-#pragma unroll
-        for (int n = 0; n < NQ; ++n) {
-          const f32x4 b = *reinterpret_cast<const f32x4*>(bg0 + 16 * n * OST + 16 * c);
-#pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            tt[n][0] = mfma_f32(a0[e], b[e], tt[n][0]);
-            tt[n][1] = mfma_f32(a1[e], b[e], tt[n][1]);
-          }
-        }
-      }
-#pragma unroll
-      for (int n = 0; n < NQ; ++n) {
-        const int rr = row0 + 16 * n + l16;
-        const size_t qrow = (size_t)min(rr, n_q - 1);
-        float gn = 0.0f;
-#pragma unroll
-        for (int u = 0; u < 2 * F; ++u) gn += gpart[16 * n + l16][u];
-        const float dden = -gn * den[n] * den[n] * hist.z_scale;
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          const int feat = 64 * f0 + 16 * g + 4 * r + 2 * pr;
-          float t0 = tt[n][0][r] * den[n], t1 = tt[n][1][r] * den[n];
-          if (hist.cosq) {   // the opposite angle
-            const float cs = hist.cosq[qrow * (D / 2) + feat / 2], sn = hist.sinq[qrow * (D / 2) + feat / 2];
-            const float u0 = t0 * cs + t1 * sn;
-            t1 = t1 * cs - t0 * sn;
-            t0 = u0;
-          }
-          const T* qp = qh + ((size_t)bh * n_q + qrow) * D + feat;
-          const float q0 = Elem<T>::load(qp), q1 = Elem<T>::load(qp + 1);
-          const bool relu = hist.phi_kind == HF_PHI_RELU;
-          const float d0 = q0 > 0.0f ? 1.0f : (relu ? 0.0f : __expf(q0)), d1 = q1 > 0.0f ? 1.0f : (relu ? 0.0f : __expf(q1));
-          const f32x2 zz = *reinterpret_cast<const f32x2*>(z + feat);
-          const float v0 = fmaf(dden, zz[0], t0) * d0, v1 = fmaf(dden, zz[1], t1) * d1;
-          if (hist.dq_hist) {
-            if (rr < q_end) {
-              T* dst = static_cast<T*>(hist.dq_hist) + ((size_t)bh * n_q + rr) * D + feat;
-              Elem<T>::store(dst, v0);
-              Elem<T>::store(dst + 1, v1);
-            }
-          } else {
-#pragma unroll
-            for (int f = 0; f < F; ++f)   // (constant indices into the accumulators)
-#pragma unroll
-              for (int q = 0; q < 2; ++q)
-                if (f == f0 && q == pr) {
-                  dq[n][f][2 * q][r] += v0;
-                  dq[n][f][2 * q + 1][r] += v1;
-                }
-          }
-        }
-      }
-    }
-    __syncthreads();
   }
-  add_parts_and_store<T, D, NQ>(smem, dq, 1.0f, kz, l16, g, static_cast<T*>(a.dQ) + ((size_t)bh * n_q + row0) * D, q_end - row0);
+  add_parts<D, NQ, PARTS, AT_ONCE, FW>(smem, dq, 1.0f, kStored && hist.L && !hist.dq_hist, part, f_own, l16, g);
+  store_parts<T, D, NQ, AT_ONCE, WAVES>(smem, static_cast<T*>(a.dQ) + ((size_t)bh * n_q + row0) * D, q_end - row0);
 }
 
 // ---- dK, dV: a workgroup per 16 NK keys of a KV block, its four wavefronts taking every fourth 16-row tile of the query
 // blocks on the inverse list.  S = Q K^T, dP = dO V^T (row form; K and V wait in LDS), P = 2^(S - lse2), dS = P (dP - D),
 // dV^T += dO^T P, dK^T += Q^T dS (column form).  Bound by the fp32 matrix rate, at the same shape 118 us (1.01 ms with one
 // query per lane and FMA arithmetic).
-template <typename T, int D, int NK, bool kStored>
+template <typename T, int D, int NK>
 __device__ __forceinline__ void dkv_role(const WideBwd& a, int wg, float* __restrict__ smem) {
   constexpr int ROWS = 16 * NK, C = D / 16, F = D / 64, OST = D + 4;
   float* sK = smem;                 // [ROWS][OST] K, [ROWS][OST] V; later four partial results
@@ -851,213 +912,235 @@ __device__ __forceinline__ void dkv_role(const WideBwd& a, int wg, float* __rest
 #pragma unroll
       for (int e = 0; e < 4; ++e) ak[n][f][e] = av[n][f][e] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
 
-  if constexpr (kStored) {
-    const int32_t* __restrict__ slots = a.inv_slot ? a.inv_slot + ((size_t)bh * t_n + jb) * t_m : nullptr;
-    const int kt = (bkv + 15) / 16, ki0 = (key0 - jb * bkv) / 16;
-    constexpr int B = sizeof(T);
-    int col_at = (4 * g * D + 4 * l16) * B, tile_lane = (64 * g + l16) * 4;
-    // the list's entries are read a trip before their tile's rows are asked for (without a branch, which in the loop would
-    // have the accumulators kept twice; a dense window has some word read in their place)
-    const int32_t* __restrict__ some = reinterpret_cast<const int32_t*>(lseh);
-    auto entry = [&](int t, int& qb, int& slot) {
-      const int at = min(t / subs, max(n_lists - 1, 0)), from = list ? at : 0;
-      const int b = (list ? list : some)[from], sl = (list ? slots : some)[from];
-      qb = list ? b : at;
-      slot = list ? sl : jb;
-    };
-    auto tile_of = [&](int t, int qb, int& first, int& cnt) {   // cnt 0: past the list or past the last query
-      const int st = qb * bq + 16 * (t % subs);
-      const int n = t < ntiles ? min(16, min(n_q, (qb + 1) * bq) - st) : 0;
-      cnt = n > 0 ? n : 0;
-      first = n > 0 ? st : 0;
-    };
-    // half of a tile's pieces at a time (a whole tile's, and accumulators, weights and the next scores: 83 registers to scratch)
-    constexpr int AHEAD = 2 * F;
-    Piece<T> qc[AHEAD], gc[AHEAD];
-    float s[NK][4], p[NK][4], lse[4], dv[4];
-    auto request_scores = [&](int t, int qb, int slot, int first, int cnt) {
-      const __amdgpu_buffer_rsrc_t rl = tile_rows<float, 1>(lseh, first, cnt), rd = tile_rows<float, 1>(dvh, first, cnt);
-#pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        lse[r] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rl, 16 * g + 4 * r, 0, 0));
-        dv[r] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rd, 16 * g + 4 * r, 0, 0));
-      }
-#pragma unroll
-      for (int n = 0; n < NK; ++n) {
-        const float* tile = score_tile(a, bh, qb, slot, t % subs, min(ki0 + n, kt - 1));
-        const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(const_cast<float*>(tile), 0, cnt > 0 ? kScoreTile * 4 : 0, 0x00020000);
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {   // a key to a lane, four queries: what the B operands take
-          s[n][r] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rs, tile_lane + 64 * r, 0, 0));
-          p[n][r] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rs, tile_lane + 64 * r + kScoreTile * 2, 0, 0));
-        }
-      }
-    };
-    int first, cnt, qb, slot, qb_n, slot_n;
-    entry(kz, qb, slot);
-    entry(kz + kParts, qb_n, slot_n);
-    tile_of(kz, qb, first, cnt);
-    request_scores(kz, qb, slot, first, cnt);
-    __amdgpu_buffer_rsrc_t q_rows = tile_rows<T, D>(Qh, first, cnt), g_rows = tile_rows<T, D>(Gh, first, cnt);
-    {
-#pragma unroll
-      for (int u = 0; u < AHEAD; ++u) {
-        gc[u].load(g_rows, col_at + (u / F * D + 64 * (u % F)) * B);
-        qc[u].load(q_rows, col_at + (u / F * D + 64 * (u % F)) * B);
-      }
-    }
-    for (int t = kz; t < ntiles; t += kParts) {
-      asm volatile("" : "+v"(col_at), "+v"(tile_lane));   // (opaque here, or their sums leave the loop as registers instead of immediates)
-      // P and dS; zero for a query that does not exist
-#pragma unroll
-      for (int n = 0; n < NK; ++n)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          const bool real = 4 * g + r < cnt;
-          const float w = __builtin_amdgcn_exp2f(s[n][r] - lse[r]), ds = w * (p[n][r] - dv[r]);
-          s[n][r] = real ? w : 0.0f;
-          p[n][r] = real ? ds : 0.0f;
-        }
-      float sw[NK][4], pw[NK][4];
-#pragma unroll
-      for (int n = 0; n < NK; ++n)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          sw[n][r] = s[n][r];
-          pw[n][r] = p[n][r];
-        }
-      int first_n, cnt_n;
-      tile_of(t + kParts, qb_n, first_n, cnt_n);
-      const __amdgpu_buffer_rsrc_t qn_rows = tile_rows<T, D>(Qh, first_n, cnt_n), gn_rows = tile_rows<T, D>(Gh, first_n, cnt_n);
-#pragma unroll
-      for (int u = 0; u < 4 * F; ++u) {
-        if (u == 3 * F) {   // (three quarters of the weights are used up: their registers take the next tile's)
-          request_scores(t + kParts, qb_n, slot_n, first_n, cnt_n);
-          entry(t + 2 * kParts, qb_n, slot_n);
-        }
-        const f32x4 ga = gc[u % AHEAD].get(), qa = qc[u % AHEAD].get();
-#pragma unroll
-        for (int e = 0; e < 4; ++e)
-#pragma unroll
-          for (int n = 0; n < NK; ++n) {
-            av[n][u % F][e] = mfma_f32(ga[e], sw[n][u / F], av[n][u % F][e]);
-            ak[n][u % F][e] = mfma_f32(qa[e], pw[n][u / F], ak[n][u % F][e]);
-          }
-        const int v = (u + AHEAD) % (4 * F), at = col_at + (v / F * D + 64 * (v % F)) * B;
-        gc[u % AHEAD].load(u < AHEAD ? g_rows : gn_rows, at);
-        qc[u % AHEAD].load(u < AHEAD ? q_rows : qn_rows, at);
-        __builtin_amdgcn_sched_barrier(0);
-      }
-      cnt = cnt_n;
-      q_rows = qn_rows;
-      g_rows = gn_rows;
-    }
-  } else {
-    for (int e = threadIdx.x; e < ROWS * (D / 4); e += 64 * kParts) {
-      const int rr = e / (D / 4), c4 = e - rr * (D / 4);
-      const size_t off = ((size_t)bh * kv_stride + min(key0 + rr, n_kv - 1)) * D + 4 * c4;
-      *reinterpret_cast<f32x4*>(sK + rr * OST + 4 * c4) = load4<T>(K + off) * a.scale_log2e;
-      *reinterpret_cast<f32x4*>(sV + rr * OST + 4 * c4) = load4<T>(V + off);
-    }
-    __syncthreads();
+  for (int e = threadIdx.x; e < ROWS * (D / 4); e += 64 * kParts) {
+    const int rr = e / (D / 4), c4 = e - rr * (D / 4);
+    const size_t off = ((size_t)bh * kv_stride + min(key0 + rr, n_kv - 1)) * D + 4 * c4;
+    *reinterpret_cast<f32x4*>(sK + rr * OST + 4 * c4) = load4<T>(K + off) * a.scale_log2e;
+    *reinterpret_cast<f32x4*>(sV + rr * OST + 4 * c4) = load4<T>(V + off);
+  }
+  __syncthreads();
 
-    auto tile_at = [&](int t, int& first, int& cnt) {   // cnt 0: past the list or past the last query
-      const int s = t / subs, sub = t - s * subs;
-      const int qb = s < n_lists ? (list ? list[s] : s) : 0;
-      const int st = qb * bq + 16 * sub;
-      const int n = s < n_lists ? min(16, min(n_q, (qb + 1) * bq) - st) : 0;
-      cnt = n > 0 ? n : 0;
-      first = n > 0 ? st : 0;
-    };
-    Piece<T> qr[C], gr[C], qc[4][F], gc[4][F];
-    int first, cnt, first_n, cnt_n;
-    tile_at(kz, first, cnt);
-    constexpr int B = sizeof(T);
-    int row_at = (l16 * D + 4 * g) * B, col_at = (4 * g * D + 4 * l16) * B;   // rows behind a tile's last real query read as zeros
-    __amdgpu_buffer_rsrc_t q_rows = tile_rows<T, D>(Qh, first, cnt), g_rows = tile_rows<T, D>(Gh, first, cnt);
+  auto tile_at = [&](int t, int& first, int& cnt) {   // cnt 0: past the list or past the last query
+    const int s = t / subs, sub = t - s * subs;
+    const int qb = s < n_lists ? (list ? list[s] : s) : 0;
+    const int st = qb * bq + 16 * sub;
+    const int n = s < n_lists ? min(16, min(n_q, (qb + 1) * bq) - st) : 0;
+    cnt = n > 0 ? n : 0;
+    first = n > 0 ? st : 0;
+  };
+  Piece<T> qr[C], gr[C], qc[4][F], gc[4][F];
+  int first, cnt, first_n, cnt_n;
+  tile_at(kz, first, cnt);
+  constexpr int B = sizeof(T);
+  int row_at = (l16 * D + 4 * g) * B, col_at = (4 * g * D + 4 * l16) * B;   // rows behind a tile's last real query read as zeros
+  __amdgpu_buffer_rsrc_t q_rows = tile_rows<T, D>(Qh, first, cnt), g_rows = tile_rows<T, D>(Gh, first, cnt);
+#pragma unroll
+  for (int c = 0; c < C; ++c) {
+    qr[c].load(q_rows, row_at + 16 * c * B);
+    gr[c].load(g_rows, row_at + 16 * c * B);
+    __builtin_amdgcn_sched_barrier(0);
+  }
+  const float* bk0 = sK + l16 * OST + 4 * g;
+  const float* bv0 = sV + l16 * OST + 4 * g;
+  for (int t = kz; t < ntiles; t += kParts) {
+    asm volatile("" : "+v"(row_at), "+v"(col_at));   // (opaque here, or their sums leave the loop as registers instead of immediates)
+    tile_at(t + kParts, first_n, cnt_n);
+    const __amdgpu_buffer_rsrc_t qn_rows = tile_rows<T, D>(Qh, first_n, cnt_n), gn_rows = tile_rows<T, D>(Gh, first_n, cnt_n);
+    float lse[4], dv[4];   // (of the tile's last query for those that do not exist: what they give is dropped)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const int row = __builtin_amdgcn_readfirstlane(first) + min(4 * g + r, max(cnt - 1, 0));
+      lse[r] = lseh[row];
+      dv[r] = dvh[row];
+    }
+    f32x4 s[NK], p[NK];
+#pragma unroll
+    for (int n = 0; n < NK; ++n) s[n] = p[n] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
 #pragma unroll
     for (int c = 0; c < C; ++c) {
-      qr[c].load(q_rows, row_at + 16 * c * B);
-      gr[c].load(g_rows, row_at + 16 * c * B);
-      __builtin_amdgcn_sched_barrier(0);
-    }
-    const float* bk0 = sK + l16 * OST + 4 * g;
-    const float* bv0 = sV + l16 * OST + 4 * g;
-    for (int t = kz; t < ntiles; t += kParts) {
-      asm volatile("" : "+v"(row_at), "+v"(col_at));   // (opaque here, or their sums leave the loop as registers instead of immediates)
-      tile_at(t + kParts, first_n, cnt_n);
-      const __amdgpu_buffer_rsrc_t qn_rows = tile_rows<T, D>(Qh, first_n, cnt_n), gn_rows = tile_rows<T, D>(Gh, first_n, cnt_n);
-      float lse[4], dv[4];   // (of the tile's last query for those that do not exist: what they give is dropped)
+      const f32x4 a = qr[c].get(), v = gr[c].get();
+      f32x4 b[NK], gg[NK];
 #pragma unroll
-      for (int r = 0; r < 4; ++r) {
-        const int row = __builtin_amdgcn_readfirstlane(first) + min(4 * g + r, max(cnt - 1, 0));
-        lse[r] = lseh[row];
-        dv[r] = dvh[row];
+      for (int n = 0; n < NK; ++n) {
+        b[n] = *reinterpret_cast<const f32x4*>(bk0 + 16 * n * OST + 16 * c);
+        gg[n] = *reinterpret_cast<const f32x4*>(bv0 + 16 * n * OST + 16 * c);
       }
-      f32x4 s[NK], p[NK];
 #pragma unroll
-      for (int n = 0; n < NK; ++n) s[n] = p[n] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
-#pragma unroll
-      for (int c = 0; c < C; ++c) {
-        const f32x4 a = qr[c].get(), v = gr[c].get();
-        f32x4 b[NK], gg[NK];
+      for (int e = 0; e < 4; ++e)
 #pragma unroll
         for (int n = 0; n < NK; ++n) {
-          b[n] = *reinterpret_cast<const f32x4*>(bk0 + 16 * n * OST + 16 * c);
-          gg[n] = *reinterpret_cast<const f32x4*>(bv0 + 16 * n * OST + 16 * c);
+          s[n] = mfma_f32(a[e], b[n][e], s[n]);
+          p[n] = mfma_f32(v[e], gg[n][e], p[n]);
         }
 #pragma unroll
-        for (int e = 0; e < 4; ++e)
-#pragma unroll
-          for (int n = 0; n < NK; ++n) {
-            s[n] = mfma_f32(a[e], b[n][e], s[n]);
-            p[n] = mfma_f32(v[e], gg[n][e], p[n]);
-          }
-#pragma unroll
-        for (int u = c * 4 * F / C; u < (c + 1) * 4 * F / C; ++u) {
-          gc[u / F][u % F].load(g_rows, col_at + (u / F * D + 64 * (u % F)) * B);
-          qc[u / F][u % F].load(q_rows, col_at + (u / F * D + 64 * (u % F)) * B);
-        }
-        __builtin_amdgcn_sched_barrier(0);
+      for (int u = c * 4 * F / C; u < (c + 1) * 4 * F / C; ++u) {
+        gc[u / F][u % F].load(g_rows, col_at + (u / F * D + 64 * (u % F)) * B);
+        qc[u / F][u % F].load(q_rows, col_at + (u / F * D + 64 * (u % F)) * B);
       }
-      // P and dS; zero for a query that does not exist
-#pragma unroll
-      for (int n = 0; n < NK; ++n)
-#pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          const bool real = 4 * g + r < cnt;
-          const float w = __builtin_amdgcn_exp2f(s[n][r] - lse[r]), ds = w * (p[n][r] - dv[r]);
-          s[n][r] = real ? w : 0.0f;
-          p[n][r] = real ? ds : 0.0f;
-        }
-#pragma unroll
-      for (int u = 0; u < 4 * F; ++u) {
-        const f32x4 a = gc[u / F][u % F].get(), b = qc[u / F][u % F].get();
-#pragma unroll
-        for (int e = 0; e < 4; ++e)
-#pragma unroll
-          for (int n = 0; n < NK; ++n) {
-            av[n][u % F][e] = mfma_f32(a[e], s[n][u / F], av[n][u % F][e]);
-            ak[n][u % F][e] = mfma_f32(b[e], p[n][u / F], ak[n][u % F][e]);
-          }
-#pragma unroll
-        for (int c = u * C / (4 * F); c < (u + 1) * C / (4 * F); ++c) {
-          qr[c].load(qn_rows, row_at + 16 * c * B);
-          gr[c].load(gn_rows, row_at + 16 * c * B);
-        }
-        __builtin_amdgcn_sched_barrier(0);
-      }
-      first = first_n;
-      q_rows = qn_rows;
-      g_rows = gn_rows;
-      cnt = cnt_n;
+      __builtin_amdgcn_sched_barrier(0);
     }
+    // P and dS; zero for a query that does not exist
+#pragma unroll
+    for (int n = 0; n < NK; ++n)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const bool real = 4 * g + r < cnt;
+        const float w = __builtin_amdgcn_exp2f(s[n][r] - lse[r]), ds = w * (p[n][r] - dv[r]);
+        s[n][r] = real ? w : 0.0f;
+        p[n][r] = real ? ds : 0.0f;
+      }
+#pragma unroll
+    for (int u = 0; u < 4 * F; ++u) {
+      const f32x4 a = gc[u / F][u % F].get(), b = qc[u / F][u % F].get();
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+#pragma unroll
+        for (int n = 0; n < NK; ++n) {
+          av[n][u % F][e] = mfma_f32(a[e], s[n][u / F], av[n][u % F][e]);
+          ak[n][u % F][e] = mfma_f32(b[e], p[n][u / F], ak[n][u % F][e]);
+        }
+#pragma unroll
+      for (int c = u * C / (4 * F); c < (u + 1) * C / (4 * F); ++c) {
+        qr[c].load(qn_rows, row_at + 16 * c * B);
+        gr[c].load(gn_rows, row_at + 16 * c * B);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    first = first_n;
+    q_rows = qn_rows;
+    g_rows = gn_rows;
+    cnt = cnt_n;
   }
-  if (!kStored) __syncthreads();   // K and V are read no more
+  __syncthreads();   // K and V are read no more
   const size_t out = ((size_t)bh * kv_stride + key0) * D;
-  add_parts_and_store<T, D, NK>(smem, ak, a.scale, kz, l16, g, static_cast<T*>(a.dK) + out, k_end - key0);
+  add_parts<D, NK, kParts, kParts, F>(smem, ak, a.scale, false, kz, 0, l16, g);
+  store_parts<T, D, NK, kParts, kParts>(smem, static_cast<T*>(a.dK) + out, k_end - key0);
   __syncthreads();
-  add_parts_and_store<T, D, NK>(smem, av, 1.0f, kz, l16, g, static_cast<T*>(a.dV) + out, k_end - key0);
+  add_parts<D, NK, kParts, kParts, F>(smem, av, 1.0f, false, kz, 0, l16, g);
+  store_parts<T, D, NK, kParts, kParts>(smem, static_cast<T*>(a.dV) + out, k_end - key0);
+}
+
+// ---- dK, dV from stored scores: a workgroup per 16 NK keys of a KV block, half of its wavefronts for each of the two (half of the
+// accumulators a wavefront: four of them on a SIMD).
+template <typename T, int D, int NK>
+__device__ __forceinline__ void dkv_stored_role(const WideBwd& a, int wg, float* __restrict__ smem) {
+  constexpr int ROWS = 16 * NK, F = D / 64, OST = D + 4;
+  const int n_q = a.n_q, n_kv = a.n_kv, kv_stride = a.kv_stride, bq = a.bq, bkv = a.bkv, t_m = a.t_m, t_n = a.t_n;
+  const int place = wg >> 3, chunk = place % a.k_chunks, block = (wg & 7) * (a.k_per_xcd / a.k_chunks) + place / a.k_chunks;
+  if (place >= a.k_per_xcd || block >= a.k_total / a.k_chunks) return;
+  const int32_t* rec = a.order ? a.order + (size_t)block * kOrderRec : nullptr;
+  const int item = rec ? rec[0] : block, bh = item / t_n, jb = item - bh * t_n, key0 = jb * bkv + chunk * ROWS;
+  const int k_end = min(n_kv, (jb + 1) * bkv);
+  if (key0 >= k_end) return;
+  const int lane = threadIdx.x & 63, kz = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int l16 = lane & 15, g = lane >> 4;
+  constexpr int PARTS = kStoredWaves / 2;
+  const int part = kz % PARTS;
+  const bool keys = kz >= PARTS;     // the first half: dV^T += dO^T P; the second: dK^T += Q^T dS
+  const T* __restrict__ Xh = static_cast<const T*>(keys ? a.Q : a.dO) + (size_t)bh * n_q * D;
+  const float* __restrict__ lseh = a.lse2 + (size_t)bh * n_q;
+  const float* __restrict__ dvh = a.Dv + (size_t)bh * n_q;
+  const int n_lists = rec ? rec[1] : a.inv_cnt ? a.inv_cnt[item] : t_m;   // no lists: every query block (dense)
+  const int32_t* __restrict__ list = a.inv_list ? a.inv_list + ((size_t)bh * t_n + jb) * t_m : nullptr;
+  const int subs = (bq + 15) / 16, ntiles = n_lists * subs;
+
+  f32x4 acc[NK][F][4];
+#pragma unroll
+  for (int n = 0; n < NK; ++n)
+#pragma unroll
+    for (int f = 0; f < F; ++f)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) acc[n][f][e] = f32x4{0.0f, 0.0f, 0.0f, 0.0f};
+  const int32_t* __restrict__ slots = a.inv_slot ? a.inv_slot + ((size_t)bh * t_n + jb) * t_m : nullptr;
+  const int kt = (bkv + 15) / 16, ki0 = (key0 - jb * bkv) / 16;
+  constexpr int B = sizeof(T);
+  int col_at = (4 * g * D + 4 * l16) * B, tile_lane = (64 * g + l16) * 4;
+  // the list's entries are read a trip before their tile's rows are asked for (without a branch, which in the loop would
+  // have the accumulators kept twice; a dense window has some word read in their place)
+  const int32_t* __restrict__ some = reinterpret_cast<const int32_t*>(lseh);
+  auto entry = [&](int t, int& qb, int& slot) {
+    const int at = min(t / subs, max(n_lists - 1, 0)), from = list ? at : 0;
+    const int b = (list ? list : some)[from], sl = (list ? slots : some)[from];
+    qb = list ? b : at;
+    slot = list ? sl : jb;
+  };
+  auto tile_of = [&](int t, int qb, int& first, int& cnt) {   // cnt 0: past the list or past the last query
+    const int st = qb * bq + 16 * (t % subs);
+    const int n = t < ntiles ? min(16, min(n_q, (qb + 1) * bq) - st) : 0;
+    cnt = n > 0 ? n : 0;
+    first = n > 0 ? st : 0;
+  };
+  // (half of a tile's pieces at a time: with a whole tile's the registers of four workgroups a compute unit do not suffice)
+  constexpr int AHEAD = 2 * F;
+  Piece<T> xc[AHEAD];
+  float s[NK][4], p[NK][4], lse[4], dv[4];
+  auto request_scores = [&](int t, int qb, int slot, int first, int cnt) {
+    const __amdgpu_buffer_rsrc_t rl = tile_rows<float, 1>(lseh, first, cnt), rd = tile_rows<float, 1>(dvh, first, cnt);
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      lse[r] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rl, 16 * g + 4 * r, 0, 0));
+      dv[r] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rd, 16 * g + 4 * r, 0, 0));
+    }
+#pragma unroll
+    for (int n = 0; n < NK; ++n) {
+      const float* tile = score_tile(a, bh, qb, slot, t % subs, min(ki0 + n, kt - 1));
+      // (dV takes S alone: what lies behind it reads as zeros, without a request to memory)
+      const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
+          const_cast<float*>(tile), 0, cnt > 0 ? kScoreTile * (keys ? 4 : 2) : 0, 0x00020000);
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {   // a key to a lane, four queries: what the B operands take
+        s[n][r] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rs, tile_lane + 64 * r, 0, 0));
+        p[n][r] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rs, tile_lane + 64 * r + kScoreTile * 2, 0, 0));
+      }
+    }
+  };
+  int first, cnt, qb, slot, qb_n, slot_n;
+  entry(part, qb, slot);
+  entry(part + PARTS, qb_n, slot_n);
+  tile_of(part, qb, first, cnt);
+  request_scores(part, qb, slot, first, cnt);
+  __amdgpu_buffer_rsrc_t x_rows = tile_rows<T, D>(Xh, first, cnt);
+#pragma unroll
+  for (int u = 0; u < AHEAD; ++u) xc[u].load(x_rows, col_at + (u / F * D + 64 * (u % F)) * B);
+  for (int t = part; t < ntiles; t += PARTS) {
+    asm volatile("" : "+v"(col_at), "+v"(tile_lane));   // (opaque here, or their sums leave the loop as registers instead of immediates)
+    float w[NK][4];   // P (P (0 + 1)) or dS = P (dP - D)
+#pragma unroll
+    for (int r = 0; r < 4; ++r) {
+      const bool real = 4 * g + r < cnt;
+      const float off = keys ? dv[r] : -1.0f;
+#pragma unroll
+      for (int n = 0; n < NK; ++n) {
+        const float v = __builtin_amdgcn_exp2f(s[n][r] - lse[r]) * (p[n][r] - off);
+        w[n][r] = real ? v : 0.0f;   // zero for a query that does not exist
+      }
+    }
+    int first_n, cnt_n;
+    tile_of(t + PARTS, qb_n, first_n, cnt_n);
+    const __amdgpu_buffer_rsrc_t xn_rows = tile_rows<T, D>(Xh, first_n, cnt_n);
+#pragma unroll
+    for (int u = 0; u < 4 * F; ++u) {
+      if (u == 3 * F) {   // (three quarters of the weights are used up: their registers take the next tile's)
+        request_scores(t + PARTS, qb_n, slot_n, first_n, cnt_n);
+        entry(t + 2 * PARTS, qb_n, slot_n);
+      }
+      const f32x4 xa = xc[u % AHEAD].get();
+#pragma unroll
+      for (int e = 0; e < 4; ++e)
+#pragma unroll
+        for (int n = 0; n < NK; ++n) acc[n][u % F][e] = mfma_f32(xa[e], w[n][u / F], acc[n][u % F][e]);
+      const int v = (u + AHEAD) % (4 * F), at = col_at + (v / F * D + 64 * (v % F)) * B;
+      xc[u % AHEAD].load(u < AHEAD ? x_rows : xn_rows, at);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+    cnt = cnt_n;
+    x_rows = xn_rows;
+  }
+  float* const own = smem + (keys ? 2 * ROWS * OST : 0);
+  add_parts<D, NK, PARTS, 2, F>(own, acc, keys ? a.scale : 1.0f, false, part, 0, l16, g);
+  const size_t out = ((size_t)bh * kv_stride + key0) * D;
+  store_parts<T, D, NK, 2, kStoredWaves>(smem, static_cast<T*>(a.dV) + out, k_end - key0);
+  store_parts<T, D, NK, 2, kStoredWaves>(smem + 2 * ROWS * OST, static_cast<T*>(a.dK) + out, k_end - key0);
 }
 
 template <typename T, int D, int NQ>
@@ -1068,28 +1151,31 @@ __global__ __launch_bounds__(64 * kParts, 2) void bwd_dq_wide_kernel(WideBwd a) 
 template <typename T, int D, int NK>
 __global__ __launch_bounds__(64 * kParts, 2) void bwd_dkv_wide_kernel(WideBwd a) {
   extern __shared__ __attribute__((aligned(16))) float smem[];
-  dkv_role<T, D, NK, false>(a, blockIdx.x, smem);
+  dkv_role<T, D, NK>(a, blockIdx.x, smem);
 }
-// from stored scores, dK and dV's workgroups and behind them dQ's in one launch
+// From stored scores, dQ's workgroups and behind them dK and dV's, longest list first, in one launch: bound by the fp32 matrix
+// rate and by how evenly the last workgroups end.  At the sizes of bwd_scores_kernel 112 us with dK and dV in index order in
+// front and two workgroups of four wavefronts a compute unit, 105 with dQ in front, 96..103 ordered, 98 with eight wavefronts a
+// workgroup (half the chain each).  Scores and rows read from one place of the caches instead of their own: no faster.
 template <typename T, int D, int NQ, int NK>
-__global__ __launch_bounds__(64 * kParts, 2) void bwd_stored_kernel(WideBwd a) {
+__global__ __launch_bounds__(64 * kStoredWaves, 4) void bwd_stored_kernel(WideBwd a) {
   extern __shared__ __attribute__((aligned(16))) float smem[];
-  const int key_wgs = 8 * a.k_per_xcd;
-  if ((int)blockIdx.x < key_wgs)
-    dkv_role<T, D, NK, true>(a, blockIdx.x, smem);
+  const int q_wgs = 8 * a.q_per_xcd;
+  if ((int)blockIdx.x < q_wgs)
+    dq_role<T, D, NQ, true>(a, blockIdx.x, smem);
   else
-    dq_role<T, D, NQ, true>(a, blockIdx.x - key_wgs, smem);
+    dkv_stored_role<T, D, NK>(a, blockIdx.x - q_wgs, smem);
 }
 
 template <int D>
-int launch_wide(const void* fn, LdsGrant& grant, long long wgs, int rows, WideBwd& a, hipStream_t s) {
+int launch_wide(const void* fn, LdsGrant& grant, long long wgs, int waves, int rows, WideBwd& a, hipStream_t s) {
   const int lds = rows * (D + 4) * (int)sizeof(float);
   if (lds > 64 * 1024) {
     const int rc = grant_lds(grant, fn, lds, "the fp32 backward kernels");
     if (rc != HF_OK) return rc;
   }
   void* args[] = {&a};
-  (void)hipLaunchKernel(fn, dim3((unsigned)wgs), dim3(64 * kParts), args, lds, s);
+  (void)hipLaunchKernel(fn, dim3((unsigned)wgs), dim3(64 * waves), args, lds, s);
   return check_launch("hf_hybrid_attn_bwd(dQ, dK, dV)");
 }
 
@@ -1100,19 +1186,20 @@ int launch_bwd_wide(WideBwd& a, hipStream_t s) {
   const long long q_wgs = 8ll * a.q_per_xcd, k_wgs = 8ll * a.k_per_xcd;
   int rc;
   if (a.scores) {
-    if ((rc = launch_wide<D>(reinterpret_cast<const void*>(bwd_scores_kernel<T, D, NQ>), grants[0], q_wgs, 2 * 16 * NQ, a, s)) != HF_OK) return rc;
-    return launch_wide<D>(reinterpret_cast<const void*>(bwd_stored_kernel<T, D, NQ, NK>), grants[1], q_wgs + k_wgs, kParts * 16 * N, a, s);
+    if ((rc = launch_wide<D>(reinterpret_cast<const void*>(bwd_scores_kernel<T, D, NQ>), grants[0], q_wgs, kScoreParts, 2 * 16 * NQ, a, s)) != HF_OK) return rc;
+    return launch_wide<D>(reinterpret_cast<const void*>(bwd_stored_kernel<T, D, NQ, NK>), grants[1], q_wgs + k_wgs, kStoredWaves, 4 * 16 * N, a, s);
   }
-  if ((rc = launch_wide<D>(reinterpret_cast<const void*>(bwd_dq_wide_kernel<T, D, NQ>), grants[2], q_wgs, kParts * 16 * NQ, a, s)) != HF_OK) return rc;
-  return launch_wide<D>(reinterpret_cast<const void*>(bwd_dkv_wide_kernel<T, D, NK>), grants[3], k_wgs, kParts * 16 * NK, a, s);
+  if ((rc = launch_wide<D>(reinterpret_cast<const void*>(bwd_dq_wide_kernel<T, D, NQ>), grants[2], q_wgs, kParts, kParts * 16 * NQ, a, s)) != HF_OK) return rc;
+  return launch_wide<D>(reinterpret_cast<const void*>(bwd_dkv_wide_kernel<T, D, NK>), grants[3], k_wgs, kParts, kParts * 16 * NK, a, s);
 }
 
 }  // namespace
 
-// idx given: the inverse lists (inv_slot given: with places), and with order given the dK/dV items' launch order; state given: planes (bf16, head_dim 128);
+// idx given: the inverse lists (inv_slot given: with places), and with order given the launch order of the dK/dV
+// items, `slabs` to a KV block; state given: planes (bf16, head_dim 128);
 // A given: row dots (likewise).
 int launch_bwd_prep(const hf_config& c, const int32_t* idx, int k, int t_m, int t_n, int32_t* inv_cnt, int32_t* inv_list,
-                    int32_t* inv_slot, int32_t* order, const float* state, void* planes, const void* A, const void* B, long long rows,
+                    int32_t* inv_slot, int32_t* order, int slabs, const float* state, void* planes, const void* A, const void* B, long long rows,
                     float* dots, hipStream_t s) {
   constexpr size_t kPrepLds = 150 * 1024;   // granted to the kernel below
   const int BH = c.batch * c.heads;
@@ -1126,7 +1213,6 @@ int launch_bwd_prep(const hf_config& c, const int32_t* idx, int k, int t_m, int 
   p.inv_slot = inv_slot;
   size_t lds = 0;
   bool order_behind = false;
-  const int slabs = (c.block_kv + 63) / 64;
   const long long items = (long long)BH * t_n * slabs, share = (items + 7) / 8;
   if (order && items > (1ll << 29)) { set_error("too many blocks"); return HF_ERR_SHAPE; }
   if (idx) {
@@ -1194,8 +1280,8 @@ size_t bwd_scores_bytes(const hf_config& c, int n_q, int k) {
 // scores given: room for them; NULL: lse2 and Dv are there already.
 int launch_bwd_generic(const hf_config& c, const void* Q, const void* Q_hist, int n_q, const void* K, const void* V, int n_kv,
                        const int32_t* idx, int k, const void* dO, float* lse2, float* Dv, const int32_t* inv_cnt,
-                       const int32_t* inv_list, const int32_t* inv_slot, float* scores, const float* state, const float* cosq,
-                       const float* sinq, void* dQ, void* dQ_hist, void* dK, void* dV, hipStream_t s) {
+                       const int32_t* inv_list, const int32_t* inv_slot, const int32_t* order, float* scores, const float* state,
+                       const float* cosq, const float* sinq, void* dQ, void* dQ_hist, void* dK, void* dV, hipStream_t s) {
   WideBwd a = {};
   a.Q = Q; a.K = K; a.V = V; a.dO = dO;
   a.idx = idx;
@@ -1208,6 +1294,7 @@ int launch_bwd_generic(const hf_config& c, const void* Q, const void* Q_hist, in
   a.scale_log2e = a.scale * 1.4426950408889634f;
   a.lse2 = lse2; a.Dv = Dv;
   a.inv_cnt = inv_cnt; a.inv_list = inv_list; a.inv_slot = inv_slot;
+  a.order = order;
   a.scores = scores;
   a.dQ = dQ; a.dK = dK; a.dV = dV;
   if (state) {
@@ -1232,7 +1319,7 @@ int launch_bwd_generic(const hf_config& c, const void* Q, const void* Q_hist, in
   a.q_total = (int)q_total;
   a.k_total = (int)k_total;
   a.q_per_xcd = (int)((q_total + 7) / 8);
-  a.k_per_xcd = (int)((k_total + 7) / 8);
+  a.k_per_xcd = (int)((k_total / a.k_chunks + 7) / 8) * a.k_chunks;   // (whole blocks)
 #define HF_BWD_WIDE(T, DD)                                                                     \
   return q2 ? (k2 ? launch_bwd_wide<T, DD, 2, 2>(a, s) : launch_bwd_wide<T, DD, 2, 1>(a, s))  \
             : (k2 ? launch_bwd_wide<T, DD, 1, 2>(a, s) : launch_bwd_wide<T, DD, 1, 1>(a, s))

@@ -204,12 +204,12 @@ int launch_bwd_mfma(const hf_config& c, const void* Q, int n_q, const void* K, c
 // inverse lists, launch order of the dK/dV items, bf16 planes of the state, row dots: what is asked for, in one launch
 constexpr int kOrderRec = 8;   // words per record of the launch order
 int launch_bwd_prep(const hf_config& c, const int32_t* idx, int k, int t_m, int t_n, int32_t* inv_cnt, int32_t* inv_list,
-                    int32_t* inv_slot, int32_t* order, const float* state, void* planes, const void* A, const void* B, long long rows,
+                    int32_t* inv_slot, int32_t* order, int slabs, const float* state, void* planes, const void* A, const void* B, long long rows,
                     float* dots, hipStream_t s);
 int launch_bwd_generic(const hf_config& c, const void* Q, const void* Q_hist, int n_q, const void* K, const void* V, int n_kv,
                        const int32_t* idx, int k, const void* dO, float* lse2, float* Dv, const int32_t* inv_cnt,
-                       const int32_t* inv_list, const int32_t* inv_slot, float* scores, const float* state, const float* cosq,
-                       const float* sinq, void* dQ, void* dQ_hist, void* dK, void* dV, hipStream_t s);
+                       const int32_t* inv_list, const int32_t* inv_slot, const int32_t* order, float* scores, const float* state,
+                       const float* cosq, const float* sinq, void* dQ, void* dQ_hist, void* dK, void* dV, hipStream_t s);
 size_t bwd_scores_bytes(const hf_config& c, int n_q, int k);
 int launch_rope_tables(const int32_t* frame_idx, int n_frames, int height, int width, int pairs_t, int pairs_h,
                        int pairs_w, double theta, int temporal_only, float* cosv, float* sinv, hipStream_t s);
