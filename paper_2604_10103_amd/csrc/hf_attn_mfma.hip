@@ -109,10 +109,12 @@ constexpr int kSelMaxBlocks = kMaxFusedSelectBlocks;
 // pool_kernel) and keeps the means in LDS, and the one of the head's first query block stores them for later calls.  Launches
 // of few workgroups last as long as their chain, and a launch of its own for some hundred keys is 3 us and a gap of it: a ring chunk
 // of four steps with 3 heads x 400 queries, 7 blocks to pool, 68.8 -> 65.1 us, with 40 heads x 128 queries, 2 blocks, 62.1 -> 56.5.
-template <int NW, int KS, bool kPool>
+//
+// `under` runs behind the scores: what it requests arrives under the Top-K, where the pooled keys' registers are free again.
+template <int NW, int KS, bool kPool, typename Under>
 __device__ __forceinline__ int* select_in_workgroup(char* smem, const bf16_t* Qh, int q0, int n_q, const float* kbar_head,
                                                     int t_n, int k, int32_t* idx_row, float* scores_row, const bf16_t* Kh,
-                                                    int n_kv, int bkv, int pool_first, int pool_end) {
+                                                    int n_kv, int bkv, int pool_first, int pool_end, Under under) {
   constexpr int NT = 64 * NW * KS, BQ = 32 * NW, G = 4 * NW, CW = D / 4 / NW;
   constexpr int E = 8 / KS;             // features of a thread of the q-bar sums
   typedef __bf16 row_piece __attribute__((ext_vector_type(E)));
@@ -240,6 +242,7 @@ __device__ __forceinline__ int* select_in_workgroup(char* smem, const bf16_t* Qh
     for (int u = 0; u < U; ++u)
       if (j0 + 64 * KS * u < t_n) part[slice * t_pad + j0 + 64 * KS * u] = a0[u] + a1[u];
   }
+  under();
   __syncthreads();
 
   if (t_n <= 256) {
@@ -599,6 +602,17 @@ __device__ __forceinline__ void absorb_role(char* smem, const AbsorbArgs& ab) {
   }
 }
 
+// The kernel's arguments span five lines of the scalar cache.  The compiler loads each where it is used, so a workgroup's chain
+// stood still at every line it met for the first time; here all of them are fetched together, with the first (3 heads x 400 queries
+// over four steps 61.8 -> 60.3 us).  A dense window's launch has nothing to win by it (40 heads x 576: 29.0 -> 29.5).
+__device__ __forceinline__ void warm_arguments() {
+  const void* const args = (const void*)__builtin_amdgcn_kernarg_segment_ptr();
+  int t0, t1, t2, t3, t4;
+  asm volatile("s_load_dword %0, %5, 0x0\n\ts_load_dword %1, %5, 0x40\n\ts_load_dword %2, %5, 0x80\n\ts_load_dword %3, %5, 0xc0\n\t"
+               "s_load_dword %4, %5, 0x100\n\ts_waitcnt lgkmcnt(0)"
+               : "=&s"(t0), "=&s"(t1), "=&s"(t2), "=&s"(t3), "=&s"(t4) : "s"(args));
+}
+
 // kSel: 1 = the workgroup first selects its KV blocks itself (Eq. 4 from hist.kbar_t, list to hist.idx_out), 2 = and pools
 // some of them first; the first ab.role_blocks workgroup ids (a multiple of eight) absorb evicted tokens instead (absorb_role)
 // KS: groups of NW wavefronts that share the query block, group g the tiles g, g + KS, ... of its list; their partial (m, l, O)
@@ -619,6 +633,7 @@ __global__ __launch_bounds__(64 * NW * KS, 2) void attn_mfma_kernel(
   // (the staged output of eight wavefronts' rows is larger than their tiles)
   __shared__ __attribute__((aligned(16))) char smem[KS * GB > BQ * OSTR ? KS * GB : BQ * OSTR];
 
+  if constexpr (kSel != 0) warm_arguments();
   // consecutive workgroup ids go to consecutive XCDs: give every XCD one contiguous run of
   // (head, query block) items so that its L2 sees few heads
   if constexpr (kSel) {
@@ -646,22 +661,36 @@ __global__ __launch_bounds__(64 * NW * KS, 2) void attn_mfma_kernel(
   const int32_t* row_idx = kSel ? hist.idx_out + ((size_t)bh * t_m + qb) * k : (idx ? idx + ((size_t)bh * t_m + qb) * k : nullptr);
   const int nsel = (kSel || idx) ? k : t_n;
   const int* sel_lds = nullptr;   // kSel: the list in LDS, valid until the first tile is requested
+  // ---- this lane's query row as B-operand fragments (d = 16 s + 8 h .. +8).  They have to have arrived before the first tile is
+  // requested: the compiler does not count the tiles' transfers, and a wait for the fragments behind them is one for all of them.
+  const int q_row = qb * BQ + 32 * wave + l32;
+  bf16x8 qf[8];
+  constexpr bool kDenEarly = KS > 1 && kFused == 1;   // the history term's denominator is formed while the first tiles travel
+  float4 z_of[kDenEarly ? 16 : 1];
+  auto request_rows = [&]() {
+    const bf16_t* qp = Qh + (size_t)min(q_row, n_q - 1) * D + 8 * h;
+#pragma unroll
+    for (int s = 0; s < 8; ++s) qf[s] = *reinterpret_cast<const bf16x8*>(qp + 16 * s);
+    if constexpr (kDenEarly) {
+      const float* zv = hist.zvec + (size_t)bh * D + 8 * h;
+#pragma unroll
+      for (int s = 0; s < 16; ++s) z_of[s] = *reinterpret_cast<const float4*>(zv + 16 * (s >> 1) + 4 * (s & 1));
+    }
+  };
+  // (the state's plane, 256 lines of 128 bytes, is brought to the L2 while the chain in front of it runs)
+  uint32_t plane_line = 0;
+  if constexpr (KS > 1 && (kFused == 1 || kFused == 2)) {
+    if (hist.planes) plane_line = reinterpret_cast<const uint32_t*>(hist.planes + (size_t)bh * 2 * D * D)[32 * (tid & 255)];
+  }
   if constexpr (kSel)
     sel_lds = select_in_workgroup<NW, KS, kSel == 2>(smem, Qh, qb * BQ, n_q, hist.kbar_t + (size_t)bh * (D / 4) * t_n * 4, t_n, k,
                                                  hist.idx_out + ((size_t)bh * t_m + qb) * k,
                                                  hist.scores_out ? hist.scores_out + ((size_t)bh * t_m + qb) * t_n : nullptr,
-                                                 Kh, n_kv, bkv, hist.pool_first, hist.pool_end);
+                                                 Kh, n_kv, bkv, hist.pool_first, hist.pool_end, request_rows);
+  else
+    request_rows();
   const int subs = (bkv + TK - 1) / TK;
   const int ntiles = (nsel * subs + KS - 1) / KS;   // every group the same number: the barriers are the workgroup's
-
-  // ---- this lane's query row as B-operand fragments (d = 16 s + 8 h .. +8)
-  const int q_row = qb * BQ + 32 * wave + l32;
-  bf16x8 qf[8];
-  {
-    const bf16_t* qp = Qh + (size_t)min(q_row, n_q - 1) * D + 8 * h;
-#pragma unroll
-    for (int s = 0; s < 8; ++s) qf[s] = *reinterpret_cast<const bf16x8*>(qp + 16 * s);
-  }
 
   f32x16 o[4];
 #pragma unroll
@@ -695,6 +724,15 @@ __global__ __launch_bounds__(64 * NW * KS, 2) void attn_mfma_kernel(
   if (KS > 1) {
     const int jb = kSel ? sel_lds[0] : (row_idx ? row_idx[0] : 0);
     if ((unsigned)jb < (unsigned)t_n) valid_head = min(TK, min(n_kv, (jb + 1) * bkv) - jb * bkv);
+  }
+  asm volatile("" :: "v"(plane_line));
+  if constexpr (kSel != 0) {   // (a given list's first entries are awaited in any case, a dense window's tiles wait for nothing)
+#pragma unroll
+    for (int s = 0; s < 8; ++s) asm volatile("" : "+v"(qf[s]));
+    if constexpr (kDenEarly) {
+#pragma unroll
+      for (int s = 0; s < 16; ++s) asm volatile("" : "+v"(z_of[s].x), "+v"(z_of[s].y), "+v"(z_of[s].z), "+v"(z_of[s].w));
+    }
   }
   if (kSel) __syncthreads();   // every wavefront has its descriptors before a tile lands on the list
   auto next_tile = [&](int& start, int& valid) {
@@ -774,7 +812,23 @@ __global__ __launch_bounds__(64 * NW * KS, 2) void attn_mfma_kernel(
     dma_tile(k_desc, sK_lds + 2 * KTILE, start_b, k_lane_off);
     next_tile(start_c, valid3);
   }
-  asm volatile("s_waitcnt vmcnt(%0)" :: "n"(2 * CPT) : "memory");   // K and V of tile 0 (K of tiles 1, 2 may fly)
+  float den = 0.0f;   // phi(q) . z
+  auto relu_of = [](const bf16x8 q) {   // of a bf16 value as a packed integer max: the fragments stay exact
+    typedef short s16x8 __attribute__((ext_vector_type(8)));
+    const s16x8 zero8 = {0, 0, 0, 0, 0, 0, 0, 0};
+    return __builtin_bit_cast(bf16x8, __builtin_elementwise_max(__builtin_bit_cast(s16x8, q), zero8));
+  };
+  auto den_add = [&](const bf16x8 f, const float4 z0, const float4 z1) {
+    den += static_cast<float>(f[0]) * z0.x + static_cast<float>(f[1]) * z0.y + static_cast<float>(f[2]) * z0.z +
+           static_cast<float>(f[3]) * z0.w + static_cast<float>(f[4]) * z1.x + static_cast<float>(f[5]) * z1.y +
+           static_cast<float>(f[6]) * z1.z + static_cast<float>(f[7]) * z1.w;
+  };
+  if constexpr (kDenEarly) {
+#pragma unroll
+    for (int s = 0; s < 8; ++s) den_add(relu_of(qf[s]), z_of[2 * s], z_of[2 * s + 1]);
+    asm volatile("" : "+v"(den));   // (here, not behind the loop)
+  }
+  asm volatile("s_waitcnt vmcnt(%0)" :: "n"(3 * CPT) : "memory");   // K of tile 0 (the rest may fly)
   __syncthreads();
   bf16x8 kf[8];   // K operand fragments of the tile whose scores come next
 #pragma unroll
@@ -979,14 +1033,6 @@ __global__ __launch_bounds__(64 * NW * KS, 2) void attn_mfma_kernel(
     }
     dma_plane(0);
   };
-  // (two groups: the normaliser too travels under their meeting)
-  constexpr bool kZEarly = KS > 1 && kFused == 1;   // (with rotation tables the registers do not hold both)
-  float4 z_of[kZEarly ? 16 : 1];
-  if constexpr (kZEarly) {
-    const float* zv = hist.zvec + (size_t)bh * D + 8 * h;
-#pragma unroll
-    for (int s = 0; s < 16; ++s) z_of[s] = *reinterpret_cast<const float4*>(zv + 16 * (s >> 1) + 4 * (s & 1));
-  }
   if (KS > 1) {
     if (kFused == 1 || kFused == 2) first_plane();
     // ---- the groups' parts of a row meet: 16-byte pieces [block of another group][wavefront][quad][lane], row statistics
@@ -1065,12 +1111,19 @@ __global__ __launch_bounds__(64 * NW * KS, 2) void attn_mfma_kernel(
         *reinterpret_cast<uint2*>(stage + (32 * wave + l32) * OSTR + (32 * (dt0 + i) + 8 * rq + 4 * h) * 2) = w;
       }
     __syncthreads();
+    int t = tid;
+    asm volatile("" : "+v"(t));   // (the pieces' addresses are formed here, not kept over the loop)
+    u32x4 piece[(BQ * 16) / NT];   // (all reads before the first store's branch)
 #pragma unroll
     for (int i = 0; i < (BQ * 16) / NT; ++i) {
-      const int c = tid + NT * i, row = c >> 4, col = c & 15;
-      if (qb * BQ + row < n_q)
-        *reinterpret_cast<uint4*>(dst_head + (size_t)(qb * BQ + row) * D + col * 8) =
-            *reinterpret_cast<const uint4*>(stage + row * OSTR + col * 16);
+      const int c = t + NT * i;
+      piece[i] = *reinterpret_cast<const u32x4*>(stage + (c >> 4) * OSTR + (c & 15) * 16);
+    }
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int i = 0; i < (BQ * 16) / NT; ++i) {
+      const int c = t + NT * i, row = c >> 4, col = c & 15;
+      if (qb * BQ + row < n_q) *reinterpret_cast<u32x4*>(dst_head + (size_t)(qb * BQ + row) * D + col * 8) = piece[i];
     }
   };
   if (kFused != 3) {
@@ -1118,20 +1171,13 @@ __global__ __launch_bounds__(64 * NW * KS, 2) void attn_mfma_kernel(
     // L2-resident plane(s) through LDS.
     if (KS == 1) first_plane();
     const float* zv = hist.zvec + (size_t)bh * D + 8 * h;
-    float den = 0.0f;
     if (kFused == 1) {
-      // ReLU of a bf16 value as a packed integer max: the fragments stay exact
-      typedef short s16x8 __attribute__((ext_vector_type(8)));
-      const s16x8 zero8 = {0, 0, 0, 0, 0, 0, 0, 0};
 #pragma unroll
       for (int s = 0; s < 8; ++s) {
-        qf[s] = __builtin_bit_cast(bf16x8, __builtin_elementwise_max(__builtin_bit_cast(s16x8, qf[s]), zero8));
-        const float4 z0 = kZEarly ? z_of[kZEarly ? 2 * s : 0] : *reinterpret_cast<const float4*>(zv + 16 * s);
-        const float4 z1 = kZEarly ? z_of[kZEarly ? 2 * s + 1 : 0] : *reinterpret_cast<const float4*>(zv + 16 * s + 4);
-        den += static_cast<float>(qf[s][0]) * z0.x + static_cast<float>(qf[s][1]) * z0.y +
-               static_cast<float>(qf[s][2]) * z0.z + static_cast<float>(qf[s][3]) * z0.w +
-               static_cast<float>(qf[s][4]) * z1.x + static_cast<float>(qf[s][5]) * z1.y +
-               static_cast<float>(qf[s][6]) * z1.z + static_cast<float>(qf[s][7]) * z1.w;
+        asm volatile("" : "+v"(qf[s]));   // (or the features formed for the denominator stay in registers over the loop)
+        qf[s] = relu_of(qf[s]);
+        if constexpr (!kDenEarly)
+          den_add(qf[s], *reinterpret_cast<const float4*>(zv + 16 * s), *reinterpret_cast<const float4*>(zv + 16 * s + 4));
       }
     } else {
       // any feature map, optional rotation of adjacent feature pairs: phi in fp32, the denominator from
@@ -1186,13 +1232,20 @@ __global__ __launch_bounds__(64 * NW * KS, 2) void attn_mfma_kernel(
       }
       asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
       __syncthreads();
+      constexpr int SB = ND == 4 ? 4 : 8;   // steps whose fragments are read before their products: sixteen reads in flight
 #pragma unroll
-      for (int s = 0; s < 8; ++s)
+      for (int s0 = 0; s0 < 8; s0 += SB) {
+        bf16x8 a[SB][ND];
 #pragma unroll
-        for (int i = 0; i < ND; ++i) {
-          const bf16x8 a = *reinterpret_cast<const bf16x8*>(sK + k_addr[s] + i * KTILE);
-          o[i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, qf[s], o[i], 0, 0, 0);
-        }
+        for (int s = 0; s < SB; ++s)
+#pragma unroll
+          for (int i = 0; i < ND; ++i) a[s][i] = *reinterpret_cast<const bf16x8*>(sK + k_addr[s0 + s] + i * KTILE);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int s = 0; s < SB; ++s)
+#pragma unroll
+          for (int i = 0; i < ND; ++i) o[i] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[s][i], qf[s0 + s], o[i], 0, 0, 0);
+      }
     }
     const float inv_den = 1.0f / den_eps;
 #pragma unroll
