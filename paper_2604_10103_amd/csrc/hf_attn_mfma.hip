@@ -394,6 +394,7 @@ struct AbsorbArgs {
   const bf16_t* K;         // [BH][stride][d] tokens to absorb (first n of every head)
   const bf16_t* V;
   int n, stride, slices, role_blocks, BH;
+  int halves;              // absorb_half instead: two workgroups a head, each with all tokens and half of the value features
   const float* state_in;   // L [BH][d][d] then z [BH][d]
   float* state_out;
   bf16_t* planes_out;      // [BH][2][d][d] or NULL
@@ -602,6 +603,158 @@ __device__ __forceinline__ void absorb_role(char* smem, const AbsorbArgs& ab) {
   }
 }
 
+// The same without an exchange, for evicted chunks of few slices in launches of few workgroups: such a launch lasts as long as its
+// longest chain, and the partials' way through memory (stores, their acknowledgement, the ticket, loads) is 3 us of one.  A
+// workgroup walks all of a head's tokens for half of the value features and adds its sums to the state where they lie.  Sums keep
+// the terms and the order that absorb_role gives them: slice for slice, the slices' sums in order, then the state.
+template <int NW>
+__device__ __forceinline__ void absorb_half(char* smem, const AbsorbArgs& ab) {
+  constexpr int IB = NW == 2 ? 2 : 1;        // 32-row blocks of key features per wavefront
+  constexpr int JB = NW == 8 ? 1 : 2;        // 32-column blocks of value features per wavefront
+  constexpr int PARTB = 16 * KSTR, STAGE = 2 * PARTB, NSTG = 5;   // stages as in absorb_role
+  constexpr int RPS = (STAGE / 1024) / NW;
+  typedef int i32x4 __attribute__((ext_vector_type(4)));
+  typedef short s16x4 __attribute__((ext_vector_type(4)));
+  typedef short s16x8 __attribute__((ext_vector_type(8)));
+  const int wg = blockIdx.x;
+  if (wg >= 2 * ab.BH) return;               // (padding up to a multiple of eight workgroup ids)
+  const int bh = wg >> 1, half = wg & 1;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int l32 = lane & 31, h = lane >> 5;
+  const int nst = (ab.n + 15) / 16;
+  const int ib0 = NW == 8 ? wave & 3 : IB * wave, jb0 = 2 * half + (NW == 8 ? wave >> 2 : 0);   // (scalar)
+
+  const uint64_t kbase = reinterpret_cast<uint64_t>(ab.K + (size_t)bh * ab.stride * D);
+  const uint64_t vbase = reinterpret_cast<uint64_t>(ab.V + (size_t)bh * ab.stride * D);
+  const int head_bytes = ab.n * (D * 2);
+  const uint32_t lds0 = (uint32_t)(uintptr_t)smem;
+  int lane_off[RPS];
+#pragma unroll
+  for (int q = 0; q < RPS; ++q) {
+    const int r = 4 * ((wave + NW * q) & 3) + (lane >> 4), u = lane & 15;
+    lane_off[q] = r * (D * 2) + ((u ^ (((r & 3) << 2) | ((r >> 2) & 3))) * 16);
+  }
+  auto fetch = [&](int c) {   // 16 tokens into slot c mod NSTG; past the last one an empty descriptor
+    const int skip = __builtin_amdgcn_readfirstlane(c * 16) * (D * 2);
+    const int left = c < nst ? min(head_bytes - skip, 16 * D * 2) : 0;
+    const uint32_t slot = lds0 + (uint32_t)(c % NSTG) * STAGE;
+#pragma unroll
+    for (int q = 0; q < RPS; ++q) {
+      const int piece = wave + NW * q;        // pieces 0..3 of K, 4..7 of V
+      const uint64_t base = (piece >> 2 ? vbase : kbase) + (uint64_t)(uint32_t)(left > 0 ? skip : 0);
+      const i32x4 d2 = {(int)(uint32_t)base, (int)(uint32_t)(base >> 32), left, 0x00020000};
+      const uint32_t dst = slot + (piece >> 2) * PARTB + 4 * (piece & 3) * KSTR;
+      asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds"
+                   :: "s"(dst), "v"(lane_off[q]), "s"(d2) : "memory", "m0");
+    }
+  };
+  const int j16 = lane & 15, grp16 = lane >> 4;
+  const int key_l = 4 * h + (j16 >> 2);
+  const int w_l = (4 * (key_l & 3)) | ((2 * (grp16 & 1) + ((j16 & 3) >> 1)) ^ h);
+  const uint32_t rd = key_l * KSTR + w_l * 16 + 8 * (j16 & 1);
+  auto frag = [&](const char* part, int dt) {
+    const char* p = part + (rd ^ (64u * dt));
+    const char* q = part + ((rd ^ (64u * dt)) ^ 32u) + 2048;
+    const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((s16x4 __attribute__((address_space(3)))*)(p));
+    const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((s16x4 __attribute__((address_space(3)))*)(q));
+    const s16x8 both = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
+    return both;
+  };
+  // what the sums are added to is on its way before the tokens
+  const float* Lin = ab.state_in + (size_t)bh * D * D;
+  const size_t zat = (size_t)ab.BH * D * D + (size_t)bh * D;
+  auto row_of = [&](int ib, int r) { return 32 * (ib0 + ib) + 8 * (r >> 2) + 4 * h + (r & 3); };   // accumulator element -> key feature
+  f32x16 old[IB][JB], zold[IB];
+#pragma unroll
+  for (int ib = 0; ib < IB; ++ib)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      zold[ib][r] = ab.state_in[zat + row_of(ib, r)];
+#pragma unroll
+      for (int jb = 0; jb < JB; ++jb) old[ib][jb][r] = Lin[row_of(ib, r) * D + 32 * (jb0 + jb) + l32];
+    }
+#pragma unroll
+  for (int c = 0; c < NSTG - 1; ++c) fetch(c);
+
+  const s16x8 zero8 = {0, 0, 0, 0, 0, 0, 0, 0};
+  const s16x8 ones8 = {0x3f80, 0x3f80, 0x3f80, 0x3f80, 0x3f80, 0x3f80, 0x3f80, 0x3f80};   // bf16 1.0
+  f32x16 sum[IB][JB], zsum[IB], acc[IB][JB], zacc[IB];
+#pragma unroll
+  for (int ib = 0; ib < IB; ++ib)
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      zsum[ib][r] = zacc[ib][r] = 0.0f;
+#pragma unroll
+      for (int jb = 0; jb < JB; ++jb) sum[ib][jb][r] = acc[ib][jb][r] = 0.0f;
+    }
+  for (int sl = 0, c = 0; sl < ab.slices; ++sl) {
+    const int end = (int)((long long)(sl + 1) * nst / ab.slices);
+    for (; c < end; ++c) {
+      asm volatile("s_waitcnt vmcnt(%0)" :: "n"(RPS * (NSTG - 2)) : "memory");   // this wavefront's rows of stage c
+      __syncthreads();             // ... and everybody's; everybody has read stage c - 1
+      fetch(c + NSTG - 1);         // into the slot of stage c - 1
+      const char* st = smem + (c % NSTG) * STAGE;
+      bf16x8 a[IB], b[JB];
+#pragma unroll
+      for (int ib = 0; ib < IB; ++ib)
+        a[ib] = __builtin_bit_cast(bf16x8, __builtin_elementwise_max(frag(st, ib0 + ib), zero8));
+#pragma unroll
+      for (int jb = 0; jb < JB; ++jb) b[jb] = __builtin_bit_cast(bf16x8, frag(st + PARTB, jb0 + jb));
+#pragma unroll
+      for (int ib = 0; ib < IB; ++ib) {
+#pragma unroll
+        for (int jb = 0; jb < JB; ++jb) acc[ib][jb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[ib], b[jb], acc[ib][jb], 0, 0, 0);
+        zacc[ib] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[ib], __builtin_bit_cast(bf16x8, ones8), zacc[ib], 0, 0, 0);
+      }
+    }
+#pragma unroll
+    for (int ib = 0; ib < IB; ++ib)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        zsum[ib][r] += zacc[ib][r];
+        zacc[ib][r] = 0.0f;
+#pragma unroll
+        for (int jb = 0; jb < JB; ++jb) { sum[ib][jb][r] += acc[ib][jb][r]; acc[ib][jb][r] = 0.0f; }
+      }
+  }
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // (requests past the last token were empty)
+
+  float* Lout = ab.state_out + (size_t)bh * D * D;
+#pragma unroll
+  for (int ib = 0; ib < IB; ++ib) {
+#pragma unroll
+    for (int jb = 0; jb < JB; ++jb) {
+      const int j = 32 * (jb0 + jb) + l32;
+#pragma unroll
+      for (int r = 0; r < 16; ++r) {
+        sum[ib][jb][r] += old[ib][jb][r];
+        Lout[row_of(ib, r) * D + j] = sum[ib][jb][r];
+      }
+      if (ab.planes_out) {
+        bf16_t* const hi = ab.planes_out + (size_t)bh * 2 * D * D + (size_t)j * D;
+#pragma unroll
+        for (int rq = 0; rq < 4; ++rq) {
+          uint32_t hw[2], lw[2];
+#pragma unroll
+          for (int q = 0; q < 2; ++q) {
+            const float v0 = sum[ib][jb][4 * rq + 2 * q], v1 = sum[ib][jb][4 * rq + 2 * q + 1];
+            const bf16_t h0 = f32_to_bf16(v0), h1 = f32_to_bf16(v1);
+            hw[q] = (uint32_t)h0 | ((uint32_t)h1 << 16);
+            lw[q] = pack_bf16(v0 - bf16_to_f32(h0), v1 - bf16_to_f32(h1));
+          }
+          *reinterpret_cast<uint2*>(hi + row_of(ib, 4 * rq)) = make_uint2(hw[0], hw[1]);
+          *reinterpret_cast<uint2*>(hi + D * D + row_of(ib, 4 * rq)) = make_uint2(lw[0], lw[1]);
+        }
+      }
+    }
+    if (l32 == 0 && jb0 == 0) {
+#pragma unroll
+      for (int r = 0; r < 16; ++r) ab.state_out[zat + row_of(ib, r)] = zsum[ib][r] + zold[ib][r];
+    }
+  }
+}
+
 // The kernel's arguments span five lines of the scalar cache.  The compiler loads each where it is used, so a workgroup's chain
 // stood still at every line it met for the first time; here all of them are fetched together, with the first (3 heads x 400 queries
 // over four steps 61.8 -> 60.3 us).  A dense window's launch has nothing to win by it (40 heads x 576: 29.0 -> 29.5).
@@ -638,7 +791,8 @@ __global__ __launch_bounds__(64 * NW * KS, 2) void attn_mfma_kernel(
   // (head, query block) items so that its L2 sees few heads
   if constexpr (kSel) {
     if ((int)blockIdx.x < ab.role_blocks) {
-      absorb_role<NW * KS>(smem, ab);
+      if (KS > 1 && ab.halves) absorb_half<NW * KS>(smem, ab);
+      else absorb_role<NW * KS>(smem, ab);
       return;
     }
   }
@@ -1445,6 +1599,12 @@ int launch_attn_mfma_fused(const hf_config& c, const void* Q, int n_q, const voi
   return launch_attn_mfma_impl(c, Q, n_q, K, V, n_kv, idx, k, &h, O, s);
 }
 
+// Which launches absorb by absorb_half: those of two groups of wavefronts, which last as long as their longest chain, up to this
+// many tokens.  hf_pool_keys + hf_step_fwd, slices that meet in memory / halves: 2 heads x 320 tokens 18.9 / 13.0 us, 12 x 512
+// 21.1 / 15.1, 6 x 768 21.4 / 18.3, 12 x 1024 23.8 / 22.7; where the attention's own chain is as long, alike (2 x 1024 with 20 of 48
+// blocks 22.9 / 23.0).  At 1300 tokens the walk over all of them is the longer one (2 heads 21.7 / 25.8).
+constexpr int kHalvesMaxTokens = 1024;
+
 // Workgroups that absorb next to the ones that attend: how many token slices per head, given what the attending
 // workgroups leave free of the chip's slots (256 compute units; 4 workgroups of two wavefronts or 2 of four each)
 int step_absorb_slices(const hf_config& c, int n_q, int n_ev) {
@@ -1457,6 +1617,11 @@ int step_absorb_slices(const hf_config& c, int n_q, int n_ev) {
   const int by_len = (n_ev + 255) / 256;       // a slice should hold some hundred tokens
   if (s > by_len) s = by_len;
   return s < 1 ? 1 : s;
+}
+
+static bool absorbs_in_halves(const hf_config& c, int n_q, int n_ev) {
+  const long long attending = (long long)c.batch * c.heads * ((n_q + c.block_q - 1) / c.block_q);
+  return key_groups(c, attending) > 1 && n_ev <= kHalvesMaxTokens;
 }
 
 size_t step_absorb_workspace_bytes(const hf_config& c, int n_q, int n_ev) {
@@ -1478,7 +1643,8 @@ int launch_attn_mfma_step(const hf_config& c, const void* Q, int n_q, const void
   ab.n = n_ev;
   ab.stride = ev_stride;
   ab.slices = step_absorb_slices(c, n_q, n_ev);
-  ab.role_blocks = (BH * ab.slices + 7) & ~7;
+  ab.halves = absorbs_in_halves(c, n_q, n_ev);
+  ab.role_blocks = (BH * (ab.halves ? 2 : ab.slices) + 7) & ~7;
   ab.BH = BH;
   ab.state_in = state_in;
   ab.state_out = state_out;
