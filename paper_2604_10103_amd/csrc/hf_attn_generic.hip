@@ -28,8 +28,11 @@ constexpr int kTile = 16;    // keys per tile
 // their own absorb another chunk into another state buffer.  Each of these is at the cost of a launch otherwise, and eight
 // wavefronts share sixteen rows here instead of four.  A chunk, separate launches / this one: 2 heads of 64, 64 queries x 256 keys, blocks
 // of 16, two steps 24.2 -> 20.3 us, 4 heads, 768 x 3072, half of the blocks, two steps 87 -> 63, 8 heads of 128, 512 x 1536, four steps
-// 109 -> 102.  (What the history term reads, requested with the first keys: 1 us a step slower, the loop's keys are awaited behind
-// it; the values with the first keys and a wavefront's blocks together: no difference.)
+// 109 -> 102.  What such a launch takes is its longest chain: with the rows to pool requested together, a list by every wavefront for
+// itself and the history term's operands requested under it, 2 heads of 64, 64 x 256, two steps 20.4 -> 18.8 us, 24 rings of such sizes
+// 0.93 of the time in the mean.  (The same operands requested in front of the selection: 20.1, the rows to pool wait behind them; with
+// the first keys: 1 us a step slower; the window's lines brought to the L2 under the Top-K: 19.8; the values with the first keys and a
+// wavefront's blocks together: no difference.)
 struct WideStep {
   float* kbar_t;          // [BH][D/4][T_n][4] pooled keys; those of the blocks [kv_first, kv_end) are formed here and stored
   int32_t* idx_out;       // [BH][T_m][k]
@@ -43,11 +46,12 @@ struct WideStep {
 constexpr int kStepWaves = 8, kStepOwn = 16, kStepBlocks = 256;   // wavefronts; most blocks pooled in the launch, in the window
 
 // Eq. 4 and the Top-K for one query block by eight wavefronts; sums in the order of pool_kernel and select_rows, so that the list
-// is theirs.  The list is left at sel; scratch: D + 9 t_pad + 16 D floats at smem.
-template <typename T, int D>
+// is theirs.  The list is left at sel; scratch: D + 9 t_pad + 16 D floats at smem.  `under` runs behind the scores: what it requests
+// arrives under the Top-K (in front, the rows to pool wait behind it).
+template <typename T, int D, typename Under>
 __device__ __forceinline__ void select_block(float* smem, int* sel, const T* Qh, int q0, int q1, const T* Kh, int n_kv, int bkv,
                                              int t_n, int k, float* kbar_head, int kv_first, int kv_end, bool store,
-                                             int32_t* idx_row) {
+                                             int32_t* idx_row, Under under) {
   using P = Pool<T, D>;
   constexpr int E = P::E, CW = D / 32;
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -67,11 +71,15 @@ __device__ __forceinline__ void select_block(float* smem, int* sel, const T* Qh,
       for (int c = 0; c < CW; ++c) kv[u][c] = kt[(size_t)c * t_n + j];
     }
   const int sub = lane / P::LPR, col = (lane % P::LPR) * E;
-  for (int it = wave; it <= kv_end - kv_first; it += kStepWaves) {   // uniform; the last is the query block
-    const bool is_q = it == kv_end - kv_first;
-    const int blk = kv_first + it, r0 = is_q ? q0 : blk * bkv, r1 = is_q ? q1 : min(n_kv, r0 + bkv);
-    float acc[E];
-    P::mean((is_q ? Qh : Kh) + col, r0, r1, sub, acc);
+  // a wavefront's items are every eighth block to pool, the last one the query block
+  const int items = kv_end - kv_first + 1;
+  auto rows_of = [&](int it, bool& is_q, int& r0, int& r1) {
+    is_q = it == items - 1;
+    r0 = is_q ? q0 : (kv_first + it) * bkv;
+    r1 = is_q ? q1 : min(n_kv, r0 + bkv);
+  };
+  auto keep_mean = [&](int it, bool is_q, const float (&acc)[E]) {
+    const int blk = kv_first + it;
     if (sub == 0) {
 #pragma unroll
       for (int e = 0; e < E; e += 4) {
@@ -79,6 +87,34 @@ __device__ __forceinline__ void select_block(float* smem, int* sel, const T* Qh,
         *reinterpret_cast<float4*>((is_q ? sq : fresh + it * D) + col + e) = v;
         if (!is_q && store) reinterpret_cast<float4*>(kbar_head)[(size_t)((col + e) / 4) * t_n + blk] = v;
       }
+    }
+  };
+  if (max(bkv, q1 - q0) <= P::kFew) {   // (uniform) short blocks: all of a wavefront's rows are requested before the first mean
+    constexpr int MAXI = (kStepOwn + 1 + kStepWaves - 1) / kStepWaves;
+    float v[MAXI][8][E];
+#pragma unroll
+    for (int i = 0; i < MAXI; ++i)
+      if (wave + kStepWaves * i < items) {   // uniform
+        bool is_q; int r0, r1;
+        rows_of(wave + kStepWaves * i, is_q, r0, r1);
+        P::request((is_q ? Qh : Kh) + col, r0, r1, sub, v[i]);
+      }
+#pragma unroll
+    for (int i = 0; i < MAXI; ++i)
+      if (wave + kStepWaves * i < items) {
+        bool is_q; int r0, r1;
+        float acc[E];
+        rows_of(wave + kStepWaves * i, is_q, r0, r1);
+        P::mean_of(v[i], r0, r1, sub, acc);
+        keep_mean(wave + kStepWaves * i, is_q, acc);
+      }
+  } else {
+    for (int it = wave; it < items; it += kStepWaves) {   // uniform
+      bool is_q; int r0, r1;
+      float acc[E];
+      rows_of(it, is_q, r0, r1);
+      P::mean((is_q ? Qh : Kh) + col, r0, r1, sub, acc);
+      keep_mean(it, is_q, acc);
     }
   }
   if (tid < t_pad - t_n) sc[t_n + tid] = -INFINITY;   // never outranks a block
@@ -98,10 +134,30 @@ __device__ __forceinline__ void select_block(float* smem, int* sel, const T* Qh,
       part[wave * t_pad + j] = a;
     }
   }
+  under();
   __syncthreads();
+  auto score_of = [&](int j) {
+    const float* x = part + j;
+    return ((x[0] + x[t_pad]) + (x[2 * t_pad] + x[3 * t_pad])) + ((x[4 * t_pad] + x[5 * t_pad]) + (x[6 * t_pad] + x[7 * t_pad]));
+  };
+  if (t_n <= 64) {
+    // every wavefront for itself, a lane a block, by the same comparisons: all write the same list, and nobody waits for anybody
+    const float mine = score_of(min(lane, t_n - 1));
+    int rank = 0;
+    for (int o = 0; o < t_n; ++o) {
+      const float v = __uint_as_float(__builtin_amdgcn_readlane(__float_as_uint(mine), o));
+      rank += (v > mine || (v == mine && o < lane)) ? 1 : 0;
+    }
+    const bool keep = lane < t_n && rank < k;
+    const int pos = __popcll(__ballot(keep) & ((1ull << lane) - 1ull));
+    if (keep && pos < k) {
+      sel[pos] = lane;
+      if (idx_row && wave == 0) idx_row[pos] = lane;
+    }
+    return;   // (what the workgroup leaves at smem next lies behind this scratch or a barrier)
+  }
   if (tid < t_n) {
-    const float* x = part + tid;
-    sc[tid] = ((x[0] + x[t_pad]) + (x[2 * t_pad] + x[3 * t_pad])) + ((x[4 * t_pad] + x[5 * t_pad]) + (x[6 * t_pad] + x[7 * t_pad]));
+    sc[tid] = score_of(tid);
   }
   __syncthreads();
   // a block's rank among the row's scores, equal ones by index; the list by ballots
@@ -142,6 +198,7 @@ __global__ __launch_bounds__(64 * NWV, 2) void attn_wide_kernel(const T* __restr
   constexpr int F = D / 64;              // column-form pieces of a token
   constexpr int OST = D + 4;             // floats per row of a partial result in LDS (breaks the banks' period)
   extern __shared__ __attribute__((aligned(16))) float smem[];
+  if constexpr (kSel) warm_arguments();
   // one contiguous run of (head, query block, chunk of rows) per XCD: its L2 then holds the keys of few heads
   int wg = blockIdx.x;
   if constexpr (kSel) {
@@ -177,17 +234,88 @@ __global__ __launch_bounds__(64 * NWV, 2) void attn_wide_kernel(const T* __restr
   int row[NQ];
   f32x4 qf[NQ][C];
 #pragma unroll
-  for (int n = 0; n < NQ; ++n) {
-    row[n] = row0 + 16 * (wr * NQ + n) + l16;
-    const T* qp = Q + ((size_t)bh * n_q + min(row[n], n_q - 1)) * D + 4 * g;
+  for (int n = 0; n < NQ; ++n) row[n] = row0 + 16 * (wr * NQ + n) + l16;
+  auto request_queries = [&]() {
 #pragma unroll
-    for (int c = 0; c < C; ++c) qf[n][c] = load4<T>(qp + 16 * c) * scale_log2e;
-  }
-
-  if constexpr (kSel)
+    for (int n = 0; n < NQ; ++n) {
+      const T* qp = Q + ((size_t)bh * n_q + min(row[n], n_q - 1)) * D + 4 * g;
+#pragma unroll
+      for (int c = 0; c < C; ++c) qf[n][c] = load4<T>(qp + 16 * c) * scale_log2e;
+    }
+  };
+  // The history term's features and denominator.  Selecting at D = 64: formed in front of the loop while the first keys travel, from
+  // operands requested in front of the selection; elsewhere the registers are the selection's and the loop's.
+  constexpr bool kHistEarly = kSel && D == 64;
+  f32x4 ph[NQ][C], zz[kHistEarly ? C : 1];
+  float den[NQ];
+  const float* const z = hist.z + (size_t)bh * D + 4 * g;
+  auto request_history = [&]() {
+    const T* qh = static_cast<const T*>(hist.q_hist);
+    // (all loads first, one uniform choice of the feature map: a branch for every feature kept the loads apart)
+#pragma unroll
+    for (int n = 0; n < NQ; ++n)
+#pragma unroll
+      for (int c = 0; c < C; ++c) ph[n][c] = load4<T>(qh + ((size_t)bh * n_q + min(row[n], n_q - 1)) * D + 16 * c + 4 * g);
+    if constexpr (kHistEarly) {
+#pragma unroll
+      for (int c = 0; c < C; ++c) zz[c] = *reinterpret_cast<const f32x4*>(z + 16 * c);
+    }
+  };
+  auto form_history = [&]() {   // R(phi(q)) and z_scale phi(q).z + eps
+    if (hist.phi_kind == HF_PHI_RELU) {
+#pragma unroll
+      for (int n = 0; n < NQ; ++n)
+#pragma unroll
+        for (int c = 0; c < C; ++c)
+#pragma unroll
+          for (int e = 0; e < 4; ++e) ph[n][c][e] = phi_apply(ph[n][c][e], HF_PHI_RELU);
+    } else {
+#pragma unroll
+      for (int n = 0; n < NQ; ++n)
+#pragma unroll
+        for (int c = 0; c < C; ++c)
+#pragma unroll
+          for (int e = 0; e < 4; ++e) ph[n][c][e] = phi_apply(ph[n][c][e], HF_PHI_ELU1);
+    }
+#pragma unroll
+    for (int n = 0; n < NQ; ++n) {
+      const size_t qrow = (size_t)min(row[n], n_q - 1);
+      float acc = 0.0f;
+#pragma unroll
+      for (int c = 0; c < C; ++c) {
+        f32x4 zc;
+        if constexpr (kHistEarly) zc = zz[c];
+        else zc = *reinterpret_cast<const f32x4*>(z + 16 * c);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) acc = fmaf(ph[n][c][e], zc[e], acc);
+      }
+      if (hist.cosq) {
+#pragma unroll
+        for (int c = 0; c < C; ++c) {
+          const size_t at = qrow * (D / 2) + 8 * c + 2 * g;
+          const float2 cs = *reinterpret_cast<const float2*>(hist.cosq + at), sn = *reinterpret_cast<const float2*>(hist.sinq + at);
+          ph[n][c] = rotate4(ph[n][c], cs.x, sn.x, cs.y, sn.y);
+        }
+      }
+      den[n] = hist.z_scale * column_sum(acc) + hist.eps;
+    }
+  };
+  float warm_l = 0.0f;
+  auto under = [&]() {
+    request_queries();
+    if (hist.L) {
+      // (the state, D^2 / 32 lines of 128 bytes, is brought to the L2 ahead of its use)
+      static_assert(!kSel || D * D / 32 <= 64 * NWV, "a line a thread");
+      warm_l = hist.L[(size_t)bh * D * D + 32 * (threadIdx.x & (D * D / 32 - 1))];
+      if constexpr (kHistEarly) request_history();
+    }
+  };
+  if constexpr (!kSel) request_queries();
+  else
     select_block<T, D>(smem, sel, Q + (size_t)bh * n_q * D, qb * bq, q_end, Kh, n_kv, bkv, t_n, k,
                        step.kbar_t + (size_t)bh * D * t_n, step.kv_first, step.kv_end, in_head == 0,
-                       chunk == 0 ? step.idx_out + ((size_t)bh * t_m + qb) * k : nullptr);
+                       chunk == 0 ? step.idx_out + ((size_t)bh * t_m + qb) * k : nullptr, under);
+  if constexpr (kSel) asm volatile("" :: "v"(warm_l));
 
   f32x4 o[NQ][F][4];
   float m[NQ], l[NQ];
@@ -299,6 +427,9 @@ __global__ __launch_bounds__(64 * NWV, 2) void attn_wide_kernel(const T* __restr
   tile_at(kz, first_v, cnt);
   load_k(first_v, cnt);
   tile_at(kz + KS, first_k, cnt_k);
+  if constexpr (kHistEarly) {
+    if (hist.L) form_history();
+  }
   scores();
   load_k(first_k, cnt_k);
   __builtin_amdgcn_sched_barrier(0);   // (requests are awaited in order: values behind keys, here as in the loop)
@@ -325,6 +456,18 @@ __global__ __launch_bounds__(64 * NWV, 2) void attn_wide_kernel(const T* __restr
     maxima(cnt);
   }
 
+  // (kSel: a wavefront takes at most one run of 16 key features of the history term; its part of L travels under the meeting)
+  f32x4 lv_of[kSel ? 4 : 1][kSel ? F : 1];
+  if constexpr (kSel) {
+    static_assert(C <= KS, "one run a wavefront");
+    if (hist.L && kz < C) {   // uniform
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+#pragma unroll
+        for (int f = 0; f < F; ++f)
+          lv_of[r][f] = *reinterpret_cast<const f32x4*>(hist.L + (size_t)bh * D * D + 4 * l16 + (size_t)(16 * kz + 4 * g + r) * D + 64 * f);
+    }
+  }
   // ---- weights of the KS parts of a row: w = 2^(m_part - m) / l
   float w[NQ];
 #pragma unroll
@@ -359,56 +502,17 @@ __global__ __launch_bounds__(64 * NWV, 2) void attn_wide_kernel(const T* __restr
 #pragma unroll
   for (int n = 0; n < NQ; ++n) w[n] = l[n] > 0.0f ? w[n] / l[n] : 0.0f;   // a row without a single real key: O_local = 0
 
-  float den[NQ];
-#pragma unroll
-  for (int n = 0; n < NQ; ++n) den[n] = 1.0f;
   if (hist.L) {
     // ---- O += R(phi(q)) L / (z_scale phi(q).z + eps) (Eq. 3, 6): O_local is scaled by the denominator, the products add
     // the numerator to the same accumulators (L in column form, its key features in the place of tokens), one division
     // at the end.  Each of the KS wavefronts takes every KS-th run of 16 key features.
     const float* L = hist.L + (size_t)bh * D * D + 4 * l16;
-    const float* z = hist.z + (size_t)bh * D + 4 * g;
-    const T* qh = static_cast<const T*>(hist.q_hist);
-    f32x4 ph[NQ][C];
-    // (all loads first, one uniform choice of the feature map: a branch for every feature kept the loads apart)
-#pragma unroll
-    for (int n = 0; n < NQ; ++n)
-#pragma unroll
-      for (int c = 0; c < C; ++c) ph[n][c] = load4<T>(qh + ((size_t)bh * n_q + min(row[n], n_q - 1)) * D + 16 * c + 4 * g);
-    if (hist.phi_kind == HF_PHI_RELU) {
-#pragma unroll
-      for (int n = 0; n < NQ; ++n)
-#pragma unroll
-        for (int c = 0; c < C; ++c)
-#pragma unroll
-          for (int e = 0; e < 4; ++e) ph[n][c][e] = phi_apply(ph[n][c][e], HF_PHI_RELU);
-    } else {
-#pragma unroll
-      for (int n = 0; n < NQ; ++n)
-#pragma unroll
-        for (int c = 0; c < C; ++c)
-#pragma unroll
-          for (int e = 0; e < 4; ++e) ph[n][c][e] = phi_apply(ph[n][c][e], HF_PHI_ELU1);
+    if constexpr (!kHistEarly) {
+      request_history();
+      form_history();
     }
 #pragma unroll
     for (int n = 0; n < NQ; ++n) {
-      const size_t qrow = (size_t)min(row[n], n_q - 1);
-      float acc = 0.0f;
-#pragma unroll
-      for (int c = 0; c < C; ++c) {
-        const f32x4 zz = *reinterpret_cast<const f32x4*>(z + 16 * c);
-#pragma unroll
-        for (int e = 0; e < 4; ++e) acc = fmaf(ph[n][c][e], zz[e], acc);
-      }
-      if (hist.cosq) {
-#pragma unroll
-        for (int c = 0; c < C; ++c) {
-          const size_t at = qrow * (D / 2) + 8 * c + 2 * g;
-          const float2 cs = *reinterpret_cast<const float2*>(hist.cosq + at), sn = *reinterpret_cast<const float2*>(hist.sinq + at);
-          ph[n][c] = rotate4(ph[n][c], cs.x, sn.x, cs.y, sn.y);
-        }
-      }
-      den[n] = hist.z_scale * column_sum(acc) + hist.eps;
       w[n] *= den[n];
 #pragma unroll
       for (int f = 0; f < F; ++f)
@@ -422,7 +526,10 @@ __global__ __launch_bounds__(64 * NWV, 2) void attn_wide_kernel(const T* __restr
 #pragma unroll
       for (int r = 0; r < 4; ++r)
 #pragma unroll
-        for (int f = 0; f < F; ++f) lv[r][f] = *reinterpret_cast<const f32x4*>(L + (size_t)(16 * c + 4 * g + r) * D + 64 * f);
+        for (int f = 0; f < F; ++f) {
+          if constexpr (kSel) lv[r][f] = lv_of[r][f];
+          else lv[r][f] = *reinterpret_cast<const f32x4*>(L + (size_t)(16 * c + 4 * g + r) * D + 64 * f);
+        }
 #pragma unroll
       for (int r = 0; r < 4; ++r)
 #pragma unroll
@@ -436,11 +543,13 @@ __global__ __launch_bounds__(64 * NWV, 2) void attn_wide_kernel(const T* __restr
     for (int n = 0; n < NQ; ++n) den[n] = 1.0f / den[n];
   } else {
 #pragma unroll
-    for (int n = 0; n < NQ; ++n)
+    for (int n = 0; n < NQ; ++n) {
+      den[n] = 1.0f;
 #pragma unroll
       for (int f = 0; f < F; ++f)
 #pragma unroll
         for (int e = 0; e < 4; ++e) o[n][f][e] *= w[n];
+    }
   }
 
   if (hist.lse2) {

@@ -755,17 +755,6 @@ __device__ __forceinline__ void absorb_half(char* smem, const AbsorbArgs& ab) {
   }
 }
 
-// The kernel's arguments span five lines of the scalar cache.  The compiler loads each where it is used, so a workgroup's chain
-// stood still at every line it met for the first time; here all of them are fetched together, with the first (3 heads x 400 queries
-// over four steps 61.8 -> 60.3 us).  A dense window's launch has nothing to win by it (40 heads x 576: 29.0 -> 29.5).
-__device__ __forceinline__ void warm_arguments() {
-  const void* const args = (const void*)__builtin_amdgcn_kernarg_segment_ptr();
-  int t0, t1, t2, t3, t4;
-  asm volatile("s_load_dword %0, %5, 0x0\n\ts_load_dword %1, %5, 0x40\n\ts_load_dword %2, %5, 0x80\n\ts_load_dword %3, %5, 0xc0\n\t"
-               "s_load_dword %4, %5, 0x100\n\ts_waitcnt lgkmcnt(0)"
-               : "=&s"(t0), "=&s"(t1), "=&s"(t2), "=&s"(t3), "=&s"(t4) : "s"(args));
-}
-
 // kSel: 1 = the workgroup first selects its KV blocks itself (Eq. 4 from hist.kbar_t, list to hist.idx_out), 2 = and pools
 // some of them first; the first ab.role_blocks workgroup ids (a multiple of eight) absorb evicted tokens instead (absorb_role)
 // KS: groups of NW wavefronts that share the query block, group g the tiles g, g + KS, ... of its list; their partial (m, l, O)

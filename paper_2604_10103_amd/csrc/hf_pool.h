@@ -1,9 +1,20 @@
-// Pooled means of a block's rows (Eq. 4), shared by the kernels that form them (internal).
+// Pooled means of a block's rows (Eq. 4), shared by the kernels that form them, and what selecting kernels begin with (internal).
 #pragma once
 
 #include "hf_common.h"
 
 namespace hf {
+
+// For kernels of more than 256 bytes of arguments, which span five lines of the scalar cache: the compiler loads each where it is used, so a workgroup's chain
+// stood still at every line it met for the first time; here all of them are fetched together, with the first (3 heads x 400 queries
+// over four steps 61.8 -> 60.3 us).  A dense window's launch has nothing to win by it (40 heads x 576: 29.0 -> 29.5).
+__device__ __forceinline__ void warm_arguments() {
+  const void* const args = (const void*)__builtin_amdgcn_kernarg_segment_ptr();
+  int t0, t1, t2, t3, t4;
+  asm volatile("s_load_dword %0, %5, 0x0\n\ts_load_dword %1, %5, 0x40\n\ts_load_dword %2, %5, 0x80\n\ts_load_dword %3, %5, 0xc0\n\t"
+               "s_load_dword %4, %5, 0x100\n\ts_waitcnt lgkmcnt(0)"
+               : "=&s"(t0), "=&s"(t1), "=&s"(t2), "=&s"(t3), "=&s"(t4) : "s"(args));
+}
 
 // Mean of the rows [r0, r1) of X (rows of D elements from base, which points at the lane's columns), by one wavefront: what the
 // lanes with sub = 0 return are the E columns of theirs.
@@ -44,11 +55,40 @@ struct Pool {
 #pragma unroll
         for (int e = 0; e < E; ++e) acc[e] += r + u * RPP < r1 ? v[u][e] : 0.0f;
     }
+    finish(r1 - r0, acc);
+  }
+  // The same mean of at most kFew rows in two halves, so that the rows of several blocks can be requested before the first is summed.
+  static constexpr int kFew = 8 * RPP;
+  static __device__ __forceinline__ void request(const T* __restrict__ base, int r0, int r1, int sub, float (&v)[8][E]) {
+#pragma unroll
+    for (int u = 0; u < 8; ++u) load16B<T>(base + (size_t)min(r0 + sub + u * RPP, r1 - 1) * D, v[u]);
+  }
+  static __device__ __forceinline__ void mean_of(const float (&v)[8][E], int r0, int r1, int sub, float (&acc)[E]) {
+#pragma unroll
+    for (int e = 0; e < E; ++e) acc[e] = 0.0f;
+#pragma unroll
+    for (int u = 0; u < 8; ++u)
+#pragma unroll
+      for (int e = 0; e < E; ++e) acc[e] += r0 + sub + u * RPP < r1 ? v[u][e] : 0.0f;
+    finish(r1 - r0, acc);
+  }
+
+ private:
+  static __device__ __forceinline__ void finish(int rows, float (&acc)[E]) {
 #pragma unroll
     for (int o = LPR; o < kWave; o <<= 1)
 #pragma unroll
-      for (int e = 0; e < E; ++e) acc[e] += __shfl_xor(acc[e], o, kWave);
-    const float inv = 1.0f / (float)(r1 - r0);
+      for (int e = 0; e < E; ++e) {
+        // (rows of sixteen and halves of the wavefront by the vector unit; through the LDS each of them is a round trip)
+        if (o < 16) {
+          acc[e] += __shfl_xor(acc[e], o, kWave);
+        } else {
+          const uint32_t a = __float_as_uint(acc[e]);
+          const auto sw = o == 16 ? __builtin_amdgcn_permlane16_swap(a, a, false, false) : __builtin_amdgcn_permlane32_swap(a, a, false, false);
+          acc[e] = __uint_as_float(sw[0]) + __uint_as_float(sw[1]);
+        }
+      }
+    const float inv = 1.0f / (float)rows;
 #pragma unroll
     for (int e = 0; e < E; ++e) acc[e] *= inv;
   }
