@@ -775,7 +775,8 @@ __global__ __launch_bounds__(64 * NW * KS, 2) void attn_mfma_kernel(
   // (the staged output of eight wavefronts' rows is larger than their tiles)
   __shared__ __attribute__((aligned(16))) char smem[KS * GB > BQ * OSTR ? KS * GB : BQ * OSTR];
 
-  if constexpr (kSel != 0) warm_arguments();
+  static_assert(5 * sizeof(void*) + 11 * sizeof(int) + sizeof(HistArgs) + sizeof(AbsorbArgs) >= 260, "five lines of arguments");
+  if constexpr (kSel != 0) warm_arguments<5>();
   // consecutive workgroup ids go to consecutive XCDs: give every XCD one contiguous run of
   // (head, query block) items so that its L2 sees few heads
   if constexpr (kSel) {

@@ -5,15 +5,23 @@
 
 namespace hf {
 
-// For kernels of more than 256 bytes of arguments, which span five lines of the scalar cache: the compiler loads each where it is used, so a workgroup's chain
-// stood still at every line it met for the first time; here all of them are fetched together, with the first (3 heads x 400 queries
-// over four steps 61.8 -> 60.3 us).  A dense window's launch has nothing to win by it (40 heads x 576: 29.0 -> 29.5).
+// A kernel's arguments of at least 64 (kLines - 1) + 4 bytes (hidden ones not counted) span kLines lines of the scalar cache.  The compiler loads each where it is
+// used, so a workgroup's chain stood still at every line it met for the first time; here all of them are fetched together, with the
+// first (3 heads x 400 queries over four steps 61.8 -> 60.3 us).  A dense window's launch has nothing to win by it (40 heads x 576:
+// 29.0 -> 29.5).
+template <int kLines>
 __device__ __forceinline__ void warm_arguments() {
+  static_assert(kLines == 4 || kLines == 5, "four or five lines");
   const void* const args = (const void*)__builtin_amdgcn_kernarg_segment_ptr();
   int t0, t1, t2, t3, t4;
-  asm volatile("s_load_dword %0, %5, 0x0\n\ts_load_dword %1, %5, 0x40\n\ts_load_dword %2, %5, 0x80\n\ts_load_dword %3, %5, 0xc0\n\t"
-               "s_load_dword %4, %5, 0x100\n\ts_waitcnt lgkmcnt(0)"
-               : "=&s"(t0), "=&s"(t1), "=&s"(t2), "=&s"(t3), "=&s"(t4) : "s"(args));
+  if constexpr (kLines == 5)
+    asm volatile("s_load_dword %0, %5, 0x0\n\ts_load_dword %1, %5, 0x40\n\ts_load_dword %2, %5, 0x80\n\ts_load_dword %3, %5, 0xc0\n\t"
+                 "s_load_dword %4, %5, 0x100\n\ts_waitcnt lgkmcnt(0)"
+                 : "=&s"(t0), "=&s"(t1), "=&s"(t2), "=&s"(t3), "=&s"(t4) : "s"(args));
+  else
+    asm volatile("s_load_dword %0, %4, 0x0\n\ts_load_dword %1, %4, 0x40\n\ts_load_dword %2, %4, 0x80\n\ts_load_dword %3, %4, 0xc0\n\t"
+                 "s_waitcnt lgkmcnt(0)"
+                 : "=&s"(t0), "=&s"(t1), "=&s"(t2), "=&s"(t3) : "s"(args));
 }
 
 // Mean of the rows [r0, r1) of X (rows of D elements from base, which points at the lane's columns), by one wavefront: what the
