@@ -308,8 +308,10 @@ __global__ __launch_bounds__(512) void score_select3_kernel(const float* __restr
 // Pooling and selection in one launch, for heads with little to pool: every workgroup pools its own three query blocks and ALL
 // of the head's KV blocks in [kv_first, kv_end) (the others' means are read), the sums in the order of pool_kernel, and selects
 // from LDS.  The first workgroup of a head stores the keys' means for later calls.
+// In fp32 four wavefronts a SIMD, 128 registers: pool_select_supported counts on two workgroups a compute unit, and with 130 there
+// is one.
 template <typename T, int D>
-__global__ __launch_bounds__(512) void pool_select_kernel(const T* __restrict__ Q, int n_q, int bq, int t_m,
+__global__ __launch_bounds__(512, sizeof(T) == 4 ? 4 : 2) void pool_select_kernel(const T* __restrict__ Q, int n_q, int bq, int t_m,
                                                           const T* __restrict__ K, int n_kv, int kv_stride, int bkv, int t_n,
                                                           int kv_first, int kv_end, int k, float* __restrict__ qbar,
                                                           float* __restrict__ kbar_t, int32_t* __restrict__ idx,
