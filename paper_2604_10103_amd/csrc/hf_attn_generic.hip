@@ -186,6 +186,36 @@ __device__ __forceinline__ void select_block(float* smem, int* sel, const T* Qh,
   __syncthreads();
 }
 
+// phi of a history term's queries (one uniform choice of the feature map: a branch for every feature kept the loads apart)
+template <int NQ, int C>
+__device__ __forceinline__ void apply_phi(f32x4 (&ph)[NQ][C], int phi_kind) {
+  if (phi_kind == HF_PHI_RELU) {
+#pragma unroll
+    for (int n = 0; n < NQ; ++n)
+#pragma unroll
+      for (int c = 0; c < C; ++c)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) ph[n][c][e] = phi_apply(ph[n][c][e], HF_PHI_RELU);
+  } else {
+#pragma unroll
+    for (int n = 0; n < NQ; ++n)
+#pragma unroll
+      for (int c = 0; c < C; ++c)
+#pragma unroll
+        for (int e = 0; e < 4; ++e) ph[n][c][e] = phi_apply(ph[n][c][e], HF_PHI_ELU1);
+  }
+}
+// R f of a row's features
+template <int D>
+__device__ __forceinline__ void rotate_features(f32x4 (&ph)[D / 16], const WideHist& hist, size_t qrow, int g) {
+#pragma unroll
+  for (int c = 0; c < D / 16; ++c) {
+    const size_t at = qrow * (D / 2) + 8 * c + 2 * g;
+    const float2 cs = *reinterpret_cast<const float2*>(hist.cosq + at), sn = *reinterpret_cast<const float2*>(hist.sinq + at);
+    ph[c] = rotate4(ph[c], cs.x, sn.x, cs.y, sn.y);
+  }
+}
+
 template <typename T, int D, int NQ, int KS, int NWV, bool kSel>
 __global__ __launch_bounds__(64 * NWV, 2) void attn_wide_kernel(const T* __restrict__ Q, const T* __restrict__ K,
                                                            const T* __restrict__ V, const int32_t* __restrict__ idx, int k,
@@ -233,89 +263,52 @@ __global__ __launch_bounds__(64 * NWV, 2) void attn_wide_kernel(const T* __restr
   // rows past the block's end are computed on clamped addresses and never written
   int row[NQ];
   f32x4 qf[NQ][C];
+  if constexpr (!kSel) {
 #pragma unroll
-  for (int n = 0; n < NQ; ++n) row[n] = row0 + 16 * (wr * NQ + n) + l16;
-  auto request_queries = [&]() {
+  for (int n = 0; n < NQ; ++n) {
+    row[n] = row0 + 16 * (wr * NQ + n) + l16;
+    const T* qp = Q + ((size_t)bh * n_q + min(row[n], n_q - 1)) * D + 4 * g;
 #pragma unroll
-    for (int n = 0; n < NQ; ++n) {
-      const T* qp = Q + ((size_t)bh * n_q + min(row[n], n_q - 1)) * D + 4 * g;
-#pragma unroll
-      for (int c = 0; c < C; ++c) qf[n][c] = load4<T>(qp + 16 * c) * scale_log2e;
-    }
-  };
-  // The history term's features and denominator.  Selecting at D = 64: formed in front of the loop while the first keys travel, from
-  // operands requested in front of the selection; elsewhere the registers are the selection's and the loop's.
+    for (int c = 0; c < C; ++c) qf[n][c] = load4<T>(qp + 16 * c) * scale_log2e;
+  }
+  }
+  // Selecting, the queries are requested under the selection, at D = 64 with the history term's operands: its features and denominator
+  // are formed in front of the loop then, while the first keys travel (elsewhere the registers are the selection's and the loop's).
+  // What the other instances do stands apart from it, so that they are compiled as if there were no selection.
   constexpr bool kHistEarly = kSel && D == 64;
-  f32x4 ph[NQ][C], zz[kHistEarly ? C : 1];
-  float den[NQ];
-  const float* const z = hist.z + (size_t)bh * D + 4 * g;
-  auto request_history = [&]() {
-    const T* qh = static_cast<const T*>(hist.q_hist);
-    // (all loads first, one uniform choice of the feature map: a branch for every feature kept the loads apart)
+  f32x4 ph_early[kHistEarly ? NQ : 1][C], zz[kHistEarly ? C : 1];
+  float den_early[kHistEarly ? NQ : 1];
+  if constexpr (kSel) {
+    float warm_l = 0.0f;
+    auto under = [&]() {
 #pragma unroll
-    for (int n = 0; n < NQ; ++n)
+      for (int n = 0; n < NQ; ++n) {
+        row[n] = row0 + 16 * (wr * NQ + n) + l16;
+        const T* qp = Q + ((size_t)bh * n_q + min(row[n], n_q - 1)) * D + 4 * g;
 #pragma unroll
-      for (int c = 0; c < C; ++c) ph[n][c] = load4<T>(qh + ((size_t)bh * n_q + min(row[n], n_q - 1)) * D + 16 * c + 4 * g);
-    if constexpr (kHistEarly) {
-#pragma unroll
-      for (int c = 0; c < C; ++c) zz[c] = *reinterpret_cast<const f32x4*>(z + 16 * c);
-    }
-  };
-  auto form_history = [&]() {   // R(phi(q)) and z_scale phi(q).z + eps
-    if (hist.phi_kind == HF_PHI_RELU) {
-#pragma unroll
-      for (int n = 0; n < NQ; ++n)
-#pragma unroll
-        for (int c = 0; c < C; ++c)
-#pragma unroll
-          for (int e = 0; e < 4; ++e) ph[n][c][e] = phi_apply(ph[n][c][e], HF_PHI_RELU);
-    } else {
-#pragma unroll
-      for (int n = 0; n < NQ; ++n)
-#pragma unroll
-        for (int c = 0; c < C; ++c)
-#pragma unroll
-          for (int e = 0; e < 4; ++e) ph[n][c][e] = phi_apply(ph[n][c][e], HF_PHI_ELU1);
-    }
-#pragma unroll
-    for (int n = 0; n < NQ; ++n) {
-      const size_t qrow = (size_t)min(row[n], n_q - 1);
-      float acc = 0.0f;
-#pragma unroll
-      for (int c = 0; c < C; ++c) {
-        f32x4 zc;
-        if constexpr (kHistEarly) zc = zz[c];
-        else zc = *reinterpret_cast<const f32x4*>(z + 16 * c);
-#pragma unroll
-        for (int e = 0; e < 4; ++e) acc = fmaf(ph[n][c][e], zc[e], acc);
+        for (int c = 0; c < C; ++c) qf[n][c] = load4<T>(qp + 16 * c) * scale_log2e;
       }
-      if (hist.cosq) {
+      if (hist.L) {
+        // (the state, D^2 / 32 lines of 128 bytes, is brought to the L2 ahead of its use)
+        static_assert(!kSel || D * D / 32 <= 64 * NWV, "a line a thread");
+        warm_l = hist.L[(size_t)bh * D * D + 32 * (threadIdx.x & (D * D / 32 - 1))];
+        if constexpr (kHistEarly) {
+          const T* qh = static_cast<const T*>(hist.q_hist);
+          const float* z = hist.z + (size_t)bh * D + 4 * g;
 #pragma unroll
-        for (int c = 0; c < C; ++c) {
-          const size_t at = qrow * (D / 2) + 8 * c + 2 * g;
-          const float2 cs = *reinterpret_cast<const float2*>(hist.cosq + at), sn = *reinterpret_cast<const float2*>(hist.sinq + at);
-          ph[n][c] = rotate4(ph[n][c], cs.x, sn.x, cs.y, sn.y);
+          for (int n = 0; n < NQ; ++n)
+#pragma unroll
+            for (int c = 0; c < C; ++c) ph_early[n][c] = load4<T>(qh + ((size_t)bh * n_q + min(row[n], n_q - 1)) * D + 16 * c + 4 * g);
+#pragma unroll
+          for (int c = 0; c < C; ++c) zz[c] = *reinterpret_cast<const f32x4*>(z + 16 * c);
         }
       }
-      den[n] = hist.z_scale * column_sum(acc) + hist.eps;
-    }
-  };
-  float warm_l = 0.0f;
-  auto under = [&]() {
-    request_queries();
-    if (hist.L) {
-      // (the state, D^2 / 32 lines of 128 bytes, is brought to the L2 ahead of its use)
-      static_assert(!kSel || D * D / 32 <= 64 * NWV, "a line a thread");
-      warm_l = hist.L[(size_t)bh * D * D + 32 * (threadIdx.x & (D * D / 32 - 1))];
-      if constexpr (kHistEarly) request_history();
-    }
-  };
-  if constexpr (!kSel) request_queries();
-  else
+    };
     select_block<T, D>(smem, sel, Q + (size_t)bh * n_q * D, qb * bq, q_end, Kh, n_kv, bkv, t_n, k,
                        step.kbar_t + (size_t)bh * D * t_n, step.kv_first, step.kv_end, in_head == 0,
                        chunk == 0 ? step.idx_out + ((size_t)bh * t_m + qb) * k : nullptr, under);
-  if constexpr (kSel) asm volatile("" :: "v"(warm_l));
+    asm volatile("" :: "v"(warm_l));
+  }
 
   f32x4 o[NQ][F][4];
   float m[NQ], l[NQ];
@@ -428,7 +421,19 @@ __global__ __launch_bounds__(64 * NWV, 2) void attn_wide_kernel(const T* __restr
   load_k(first_v, cnt);
   tile_at(kz + KS, first_k, cnt_k);
   if constexpr (kHistEarly) {
-    if (hist.L) form_history();
+    if (hist.L) {
+      apply_phi(ph_early, hist.phi_kind);
+#pragma unroll
+      for (int n = 0; n < NQ; ++n) {
+        float acc = 0.0f;
+#pragma unroll
+        for (int c = 0; c < C; ++c)
+#pragma unroll
+          for (int e = 0; e < 4; ++e) acc = fmaf(ph_early[n][c][e], zz[c][e], acc);
+        if (hist.cosq) rotate_features<D>(ph_early[n], hist, (size_t)min(row[n], n_q - 1), g);
+        den_early[n] = hist.z_scale * column_sum(acc) + hist.eps;
+      }
+    }
   }
   scores();
   load_k(first_k, cnt_k);
@@ -502,17 +507,42 @@ __global__ __launch_bounds__(64 * NWV, 2) void attn_wide_kernel(const T* __restr
 #pragma unroll
   for (int n = 0; n < NQ; ++n) w[n] = l[n] > 0.0f ? w[n] / l[n] : 0.0f;   // a row without a single real key: O_local = 0
 
+  float den[NQ];
+#pragma unroll
+  for (int n = 0; n < NQ; ++n) den[n] = 1.0f;
   if (hist.L) {
     // ---- O += R(phi(q)) L / (z_scale phi(q).z + eps) (Eq. 3, 6): O_local is scaled by the denominator, the products add
     // the numerator to the same accumulators (L in column form, its key features in the place of tokens), one division
     // at the end.  Each of the KS wavefronts takes every KS-th run of 16 key features.
     const float* L = hist.L + (size_t)bh * D * D + 4 * l16;
-    if constexpr (!kHistEarly) {
-      request_history();
-      form_history();
+    const float* z = hist.z + (size_t)bh * D + 4 * g;
+    const T* qh = static_cast<const T*>(hist.q_hist);
+    f32x4 ph[NQ][C];
+    if constexpr (!kHistEarly) {   // (all loads first)
+#pragma unroll
+      for (int n = 0; n < NQ; ++n)
+#pragma unroll
+        for (int c = 0; c < C; ++c) ph[n][c] = load4<T>(qh + ((size_t)bh * n_q + min(row[n], n_q - 1)) * D + 16 * c + 4 * g);
+      apply_phi(ph, hist.phi_kind);
     }
 #pragma unroll
     for (int n = 0; n < NQ; ++n) {
+      if constexpr (kHistEarly) {
+#pragma unroll
+        for (int c = 0; c < C; ++c) ph[n][c] = ph_early[n][c];
+        den[n] = den_early[n];
+      } else {
+        const size_t qrow = (size_t)min(row[n], n_q - 1);
+        float acc = 0.0f;
+#pragma unroll
+        for (int c = 0; c < C; ++c) {
+          const f32x4 zc = *reinterpret_cast<const f32x4*>(z + 16 * c);
+#pragma unroll
+          for (int e = 0; e < 4; ++e) acc = fmaf(ph[n][c][e], zc[e], acc);
+        }
+        if (hist.cosq) rotate_features<D>(ph[n], hist, qrow, g);
+        den[n] = hist.z_scale * column_sum(acc) + hist.eps;
+      }
       w[n] *= den[n];
 #pragma unroll
       for (int f = 0; f < F; ++f)
@@ -543,13 +573,11 @@ __global__ __launch_bounds__(64 * NWV, 2) void attn_wide_kernel(const T* __restr
     for (int n = 0; n < NQ; ++n) den[n] = 1.0f / den[n];
   } else {
 #pragma unroll
-    for (int n = 0; n < NQ; ++n) {
-      den[n] = 1.0f;
+    for (int n = 0; n < NQ; ++n)
 #pragma unroll
       for (int f = 0; f < F; ++f)
 #pragma unroll
         for (int e = 0; e < 4; ++e) o[n][f][e] *= w[n];
-    }
   }
 
   if (hist.lse2) {

@@ -52,3 +52,11 @@ def kernels():
 def test_two_fp32_selecting_workgroups_share_a_compute_unit(kernels, d):
     """512 threads are two wavefronts a SIMD, of 512 registers."""
     assert kernels[f"pool_select_kernel<float, {d}>"][".vgpr_count"] <= 128
+
+
+@pytest.mark.parametrize("instance,registers", [("bf16, 128, 1, 4, 4", 154), ("bf16, 64, 1, 4, 4", 84), ("float, 128, 1, 4, 4", 163),
+                                                ("float, 64, 1, 4, 4", 99)])
+def test_attention_without_selection_pays_nothing_for_it(kernels, instance, registers):
+    """The instances for lists that are given share their source with the selecting ones: the counts from before they did."""
+    name = f"attn_wide_kernel<{instance}, false>".replace("bf16", "unsigned short")
+    assert kernels[name][".vgpr_count"] <= registers
