@@ -811,28 +811,33 @@ __global__ __launch_bounds__(64 * NW * KS, 2) void attn_mfma_kernel(
   bf16x8 qf[8];
   constexpr bool kDenEarly = KS > 1 && kFused == 1;   // the history term's denominator is formed while the first tiles travel
   float4 z_of[kDenEarly ? 16 : 1];
-  auto request_rows = [&]() {
-    const bf16_t* qp = Qh + (size_t)min(q_row, n_q - 1) * D + 8 * h;
+  auto request_z = [&]() {
+    const float* zv = hist.zvec + (size_t)bh * D + 8 * h;
 #pragma unroll
-    for (int s = 0; s < 8; ++s) qf[s] = *reinterpret_cast<const bf16x8*>(qp + 16 * s);
-    if constexpr (kDenEarly) {
-      const float* zv = hist.zvec + (size_t)bh * D + 8 * h;
-#pragma unroll
-      for (int s = 0; s < 16; ++s) z_of[s] = *reinterpret_cast<const float4*>(zv + 16 * (s >> 1) + 4 * (s & 1));
-    }
+    for (int s = 0; s < 16; ++s) z_of[s] = *reinterpret_cast<const float4*>(zv + 16 * (s >> 1) + 4 * (s & 1));
   };
   // (the state's plane, 256 lines of 128 bytes, is brought to the L2 while the chain in front of it runs)
   uint32_t plane_line = 0;
   if constexpr (KS > 1 && (kFused == 1 || kFused == 2)) {
     if (hist.planes) plane_line = reinterpret_cast<const uint32_t*>(hist.planes + (size_t)bh * 2 * D * D)[32 * (tid & 255)];
   }
-  if constexpr (kSel)
+  // (a query's loads stand here for either: as a lambda that both call they cost full launches of lists with rotated queries four spills)
+  if constexpr (kSel) {
     sel_lds = select_in_workgroup<NW, KS, kSel == 2>(smem, Qh, qb * BQ, n_q, hist.kbar_t + (size_t)bh * (D / 4) * t_n * 4, t_n, k,
                                                  hist.idx_out + ((size_t)bh * t_m + qb) * k,
                                                  hist.scores_out ? hist.scores_out + ((size_t)bh * t_m + qb) * t_n : nullptr,
-                                                 Kh, n_kv, bkv, hist.pool_first, hist.pool_end, request_rows);
-  else
-    request_rows();
+                                                 Kh, n_kv, bkv, hist.pool_first, hist.pool_end, [&]() {
+      const bf16_t* qp = Qh + (size_t)min(q_row, n_q - 1) * D + 8 * h;
+#pragma unroll
+      for (int s = 0; s < 8; ++s) qf[s] = *reinterpret_cast<const bf16x8*>(qp + 16 * s);
+      if constexpr (kDenEarly) request_z();
+    });
+  } else {
+    const bf16_t* qp = Qh + (size_t)min(q_row, n_q - 1) * D + 8 * h;
+#pragma unroll
+    for (int s = 0; s < 8; ++s) qf[s] = *reinterpret_cast<const bf16x8*>(qp + 16 * s);
+    if constexpr (kDenEarly) request_z();
+  }
   const int subs = (bkv + TK - 1) / TK;
   const int ntiles = (nsel * subs + KS - 1) / KS;   // every group the same number: the barriers are the workgroup's
 
@@ -869,7 +874,7 @@ __global__ __launch_bounds__(64 * NW * KS, 2) void attn_mfma_kernel(
     const int jb = kSel ? sel_lds[0] : (row_idx ? row_idx[0] : 0);
     if ((unsigned)jb < (unsigned)t_n) valid_head = min(TK, min(n_kv, (jb + 1) * bkv) - jb * bkv);
   }
-  asm volatile("" :: "v"(plane_line));
+  if constexpr (KS > 1 && (kFused == 1 || kFused == 2)) asm volatile("" :: "v"(plane_line));
   if constexpr (kSel != 0) {   // (a given list's first entries are awaited in any case, a dense window's tiles wait for nothing)
 #pragma unroll
     for (int s = 0; s < 8; ++s) asm volatile("" : "+v"(qf[s]));
@@ -1263,7 +1268,7 @@ __global__ __launch_bounds__(64 * NW * KS, 2) void attn_mfma_kernel(
       const int c = t + NT * i;
       piece[i] = *reinterpret_cast<const u32x4*>(stage + (c >> 4) * OSTR + (c & 15) * 16);
     }
-    __builtin_amdgcn_sched_barrier(0);
+    if constexpr (kSel != 0 || kFused != 2) __builtin_amdgcn_sched_barrier(0);   // (there the registers do not hold them)
 #pragma unroll
     for (int i = 0; i < (BQ * 16) / NT; ++i) {
       const int c = t + NT * i, row = c >> 4, col = c & 15;

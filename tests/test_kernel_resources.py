@@ -60,3 +60,10 @@ def test_attention_without_selection_pays_nothing_for_it(kernels, instance, regi
     """The instances for lists that are given share their source with the selecting ones: the counts from before they did."""
     name = f"attn_wide_kernel<{instance}, false>".replace("bf16", "unsigned short")
     assert kernels[name][".vgpr_count"] <= registers
+
+
+@pytest.mark.parametrize("instance,spilled", [("2, 2, 0, 1", 4), ("4, 2, 0, 1", 3), ("8, 2, 0, 1", 3), ("2, 0, 1, 1", 7), ("2, 1, 1, 1", 9),
+                                              ("2, 2, 1, 1", 16), ("4, 2, 1, 1", 3), ("2, 1, 1, 2", 0), ("4, 1, 1, 2", 0)])
+def test_registers_that_the_bf16_attention_spills(kernels, instance, spilled):
+    """Full launches of rotated queries and of selecting workgroups spill a few around their loop; nobody spills more."""
+    assert kernels[f"attn_mfma_kernel<{instance}>"][".vgpr_spill_count"] <= spilled
