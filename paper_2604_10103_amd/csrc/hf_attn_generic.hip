@@ -113,7 +113,7 @@ __device__ __forceinline__ void select_block(float* smem, int* sel, const T* Qh,
       bool is_q; int r0, r1;
       float acc[E];
       rows_of(it, is_q, r0, r1);
-      P::mean((is_q ? Qh : Kh) + col, r0, r1, sub, acc);
+      P::template mean<true>((is_q ? Qh : Kh) + col, r0, r1, sub, acc);
       keep_mean(it, is_q, acc);
     }
   }

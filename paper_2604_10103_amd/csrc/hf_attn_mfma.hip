@@ -143,7 +143,7 @@ __device__ __forceinline__ int* select_in_workgroup(char* smem, const bf16_t* Qh
     const int sub = lane / P::LPR, col = (lane % P::LPR) * P::E;
     for (int b = pool_first + wave; b < pool_end; b += NW * KS) {
       float acc[P::E];
-      P::mean(Kh + col, b * bkv, min(n_kv, (b + 1) * bkv), sub, acc);
+      P::template mean<true>(Kh + col, b * bkv, min(n_kv, (b + 1) * bkv), sub, acc);
       if (sub == 0) {
 #pragma unroll
         for (int e = 0; e < P::E; e += 4) {

@@ -31,6 +31,8 @@ struct Pool {
   static constexpr int E = Elem<T>::kPer16B;  // elements per 16-byte load
   static constexpr int LPR = D / E;           // lanes covering one row
   static constexpr int RPP = kWave / LPR;     // rows per pass of the wavefront
+  // kVector: how the lanes' sums meet, see finish
+  template <bool kVector>
   static __device__ __forceinline__ void mean(const T* __restrict__ base, int r0, int r1, int sub, float (&acc)[E]) {
 #pragma unroll
     for (int e = 0; e < E; ++e) acc[e] = 0.0f;
@@ -63,7 +65,7 @@ struct Pool {
 #pragma unroll
         for (int e = 0; e < E; ++e) acc[e] += r + u * RPP < r1 ? v[u][e] : 0.0f;
     }
-    finish(r1 - r0, acc);
+    finish<kVector>(r1 - r0, acc);
   }
   // The same mean of at most kFew rows in two halves, so that the rows of several blocks can be requested before the first is summed.
   static constexpr int kFew = 8 * RPP;
@@ -78,17 +80,20 @@ struct Pool {
     for (int u = 0; u < 8; ++u)
 #pragma unroll
       for (int e = 0; e < E; ++e) acc[e] += r0 + sub + u * RPP < r1 ? v[u][e] : 0.0f;
-    finish(r1 - r0, acc);
+    finish<true>(r1 - r0, acc);
   }
 
  private:
+  // Rows of sixteen and halves of the wavefront by the vector unit where a chain of steps waits for the sum (through the LDS each of
+  // them is a round trip); launches that do nothing but pool have other wavefronts to run meanwhile and the vector unit busy with
+  // sums: there through the LDS (fp32, 3 heads of 128, 922 x 2766: selection 7.35 us by the vector unit, 7.23 so).
+  template <bool kVector>
   static __device__ __forceinline__ void finish(int rows, float (&acc)[E]) {
 #pragma unroll
     for (int o = LPR; o < kWave; o <<= 1)
 #pragma unroll
       for (int e = 0; e < E; ++e) {
-        // (rows of sixteen and halves of the wavefront by the vector unit; through the LDS each of them is a round trip)
-        if (o < 16) {
+        if (!kVector || o < 16) {
           acc[e] += __shfl_xor(acc[e], o, kWave);
         } else {
           const uint32_t a = __float_as_uint(acc[e]);

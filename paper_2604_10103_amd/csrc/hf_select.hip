@@ -48,7 +48,7 @@ __global__ __launch_bounds__(256) void pool_kernel(const T* __restrict__ Q, int 
   const int r0 = blk * b, r1 = min(n, r0 + b);
   const int sub = lane / P::LPR, col = (lane % P::LPR) * E;
   float acc[E];
-  P::mean(X + (size_t)bh * (is_q ? n_q : kv_stride) * D + col, r0, r1, sub, acc);
+  P::template mean<false>(X + (size_t)bh * (is_q ? n_q : kv_stride) * D + col, r0, r1, sub, acc);
   if (sub == 0) {
 #pragma unroll
     for (int e = 0; e < E; e += 4) {
@@ -308,10 +308,9 @@ __global__ __launch_bounds__(512) void score_select3_kernel(const float* __restr
 // Pooling and selection in one launch, for heads with little to pool: every workgroup pools its own three query blocks and ALL
 // of the head's KV blocks in [kv_first, kv_end) (the others' means are read), the sums in the order of pool_kernel, and selects
 // from LDS.  The first workgroup of a head stores the keys' means for later calls.
-// In fp32 four wavefronts a SIMD, 128 registers: pool_select_supported counts on two workgroups a compute unit, and with 130 there
-// is one.
+// pool_select_supported counts on two workgroups a compute unit in fp32, four wavefronts a SIMD: 128 registers at most.
 template <typename T, int D>
-__global__ __launch_bounds__(512, sizeof(T) == 4 ? 4 : 2) void pool_select_kernel(const T* __restrict__ Q, int n_q, int bq, int t_m,
+__global__ __launch_bounds__(512) void pool_select_kernel(const T* __restrict__ Q, int n_q, int bq, int t_m,
                                                           const T* __restrict__ K, int n_kv, int kv_stride, int bkv, int t_n,
                                                           int kv_first, int kv_end, int k, float* __restrict__ qbar,
                                                           float* __restrict__ kbar_t, int32_t* __restrict__ idx,
@@ -339,7 +338,7 @@ __global__ __launch_bounds__(512, sizeof(T) == 4 ? 4 : 2) void pool_select_kerne
     const int blk = is_q ? min(row0 + it, t_m - 1) : it - kRows + kv_first;   // rows past the end repeat the last one
     const int n = is_q ? n_q : n_kv, b = is_q ? bq : bkv, r0 = blk * b;
     float acc[E];
-    P::mean((is_q ? Q + (size_t)bh * n_q * D : K + (size_t)bh * kv_stride * D) + col, r0, min(n, r0 + b), sub, acc);
+    P::template mean<false>((is_q ? Q + (size_t)bh * n_q * D : K + (size_t)bh * kv_stride * D) + col, r0, min(n, r0 + b), sub, acc);
     if (sub == 0) {
 #pragma unroll
       for (int e = 0; e < E; e += 4) {
