@@ -1594,11 +1594,17 @@ int launch_attn_mfma_fused(const hf_config& c, const void* Q, int n_q, const voi
   return launch_attn_mfma_impl(c, Q, n_q, K, V, n_kv, idx, k, &h, O, s);
 }
 
-// Which launches absorb by absorb_half: those of two groups of wavefronts, which last as long as their longest chain, up to this
-// many tokens.  hf_pool_keys + hf_step_fwd, slices that meet in memory / halves: 2 heads x 320 tokens 18.9 / 13.0 us, 12 x 512
-// 21.1 / 15.1, 6 x 768 21.4 / 18.3, 12 x 1024 23.8 / 22.7; where the attention's own chain is as long, alike (2 x 1024 with 20 of 48
-// blocks 22.9 / 23.0).  At 1300 tokens the walk over all of them is the longer one (2 heads 21.7 / 25.8).
-constexpr int kHalvesMaxTokens = 1024;
+// Which launches absorb by absorb_half: those of two groups of wavefronts, which last as long as their longest chain, up to as many
+// tokens as a workgroup walks while slices of them are summed and meet in memory.  hf_step_fwd with 512 keys, slices / halves, blocks
+// of 64 (a workgroup has four wavefronts): 2 heads x 64 queries, 512 tokens 16.3 / 11.2 us, 768 17.3 / 14.7, 896 17.4 / 16.5,
+// 1024 17.9 / 18.0; 12 x 128, 1024 19.2 / 18.4; 40 x 128, 1024 21.3 / 18.9; at 1300 tokens 2 heads 21.7 / 25.8.  Blocks of 128 (a
+// walk takes as long, but eight wavefronts sum a slice; with many heads many slices meet in memory): 2 x 64, 512
+// tokens 16.5 / 12.0, 768 16.9 / 15.3, 896 16.8 / 17.3, 1024 17.2 / 18.9; 12 x 128, 896 17.4 / 17.6, 1024 17.8 / 19.3; 40 x 128, 896
+// 19.5 / 17.9, 1024 20.2 / 19.5.
+static int halves_max_tokens(const hf_config& c) {
+  const long long heads = (long long)c.batch * c.heads;
+  return c.block_q == 64 || heads >= 40 ? 1024 : 824 + 5 * (int)heads;
+}
 
 // Workgroups that absorb next to the ones that attend: how many token slices per head, given what the attending
 // workgroups leave free of the chip's slots (256 compute units; 4 workgroups of two wavefronts or 2 of four each)
@@ -1616,7 +1622,7 @@ int step_absorb_slices(const hf_config& c, int n_q, int n_ev) {
 
 static bool absorbs_in_halves(const hf_config& c, int n_q, int n_ev) {
   const long long attending = (long long)c.batch * c.heads * ((n_q + c.block_q - 1) / c.block_q);
-  return key_groups(c, attending) > 1 && n_ev <= kHalvesMaxTokens;
+  return key_groups(c, attending) > 1 && n_ev <= halves_max_tokens(c);
 }
 
 size_t step_absorb_workspace_bytes(const hf_config& c, int n_q, int n_ev) {
