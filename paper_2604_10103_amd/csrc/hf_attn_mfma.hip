@@ -809,16 +809,12 @@ __global__ __launch_bounds__(64 * NW * KS, 2) void attn_mfma_kernel(
   // requested: the compiler does not count the tiles' transfers, and a wait for the fragments behind them is one for all of them.
   const int q_row = qb * BQ + 32 * wave + l32;
   bf16x8 qf[8];
-  constexpr bool kDenEarly = KS > 1 && kFused == 1;   // the history term's denominator is formed while the first tiles travel
+  // Selecting, two groups form the history term's denominator while the first tiles travel and bring the state's plane to the L2 under
+  // the Top-K; with a given list both only delay the first tile (3 heads x 400 queries, blocks of 128 13.5 / 13.2 us, of 64 9.9 / 9.7)
+  constexpr bool kDenEarly = kSel != 0 && KS > 1 && kFused == 1, kPlaneEarly = kSel != 0 && KS > 1 && (kFused == 1 || kFused == 2);
   float4 z_of[kDenEarly ? 16 : 1];
-  auto request_z = [&]() {
-    const float* zv = hist.zvec + (size_t)bh * D + 8 * h;
-#pragma unroll
-    for (int s = 0; s < 16; ++s) z_of[s] = *reinterpret_cast<const float4*>(zv + 16 * (s >> 1) + 4 * (s & 1));
-  };
-  // (the state's plane, 256 lines of 128 bytes, is brought to the L2 while the chain in front of it runs)
-  uint32_t plane_line = 0;
-  if constexpr (KS > 1 && (kFused == 1 || kFused == 2)) {
+  uint32_t plane_line = 0;   // (of the plane's 256 lines of 128 bytes)
+  if constexpr (kPlaneEarly) {
     if (hist.planes) plane_line = reinterpret_cast<const uint32_t*>(hist.planes + (size_t)bh * 2 * D * D)[32 * (tid & 255)];
   }
   // (a query's loads stand here for either: as a lambda that both call they cost full launches of lists with rotated queries four spills)
@@ -830,13 +826,16 @@ __global__ __launch_bounds__(64 * NW * KS, 2) void attn_mfma_kernel(
       const bf16_t* qp = Qh + (size_t)min(q_row, n_q - 1) * D + 8 * h;
 #pragma unroll
       for (int s = 0; s < 8; ++s) qf[s] = *reinterpret_cast<const bf16x8*>(qp + 16 * s);
-      if constexpr (kDenEarly) request_z();
+      if constexpr (kDenEarly) {
+        const float* zv = hist.zvec + (size_t)bh * D + 8 * h;
+#pragma unroll
+        for (int s = 0; s < 16; ++s) z_of[s] = *reinterpret_cast<const float4*>(zv + 16 * (s >> 1) + 4 * (s & 1));
+      }
     });
   } else {
     const bf16_t* qp = Qh + (size_t)min(q_row, n_q - 1) * D + 8 * h;
 #pragma unroll
     for (int s = 0; s < 8; ++s) qf[s] = *reinterpret_cast<const bf16x8*>(qp + 16 * s);
-    if constexpr (kDenEarly) request_z();
   }
   const int subs = (bkv + TK - 1) / TK;
   const int ntiles = (nsel * subs + KS - 1) / KS;   // every group the same number: the barriers are the workgroup's
@@ -874,7 +873,7 @@ __global__ __launch_bounds__(64 * NW * KS, 2) void attn_mfma_kernel(
     const int jb = kSel ? sel_lds[0] : (row_idx ? row_idx[0] : 0);
     if ((unsigned)jb < (unsigned)t_n) valid_head = min(TK, min(n_kv, (jb + 1) * bkv) - jb * bkv);
   }
-  if constexpr (KS > 1 && (kFused == 1 || kFused == 2)) asm volatile("" :: "v"(plane_line));
+  if constexpr (kPlaneEarly) asm volatile("" :: "v"(plane_line));
   if constexpr (kSel != 0) {   // (a given list's first entries are awaited in any case, a dense window's tiles wait for nothing)
 #pragma unroll
     for (int s = 0; s < 8; ++s) asm volatile("" : "+v"(qf[s]));
