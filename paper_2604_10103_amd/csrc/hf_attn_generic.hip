@@ -228,7 +228,10 @@ __global__ __launch_bounds__(64 * NWV, 2) void attn_wide_kernel(const T* __restr
   constexpr int F = D / 64;              // column-form pieces of a token
   constexpr int OST = D + 4;             // floats per row of a partial result in LDS (breaks the banks' period)
   extern __shared__ __attribute__((aligned(16))) float smem[];
-  if constexpr (kSel) warm_arguments<4>();   // (256 bytes)
+  if constexpr (kSel) {
+    static_assert(5 * sizeof(void*) + 11 * sizeof(int) + sizeof(WideHist) + sizeof(WideStep) >= 196, "four lines of arguments");
+    warm_arguments<4>();
+  }
   // one contiguous run of (head, query block, chunk of rows) per XCD: its L2 then holds the keys of few heads
   int wg = blockIdx.x;
   if constexpr (kSel) {

@@ -609,7 +609,7 @@ __device__ __forceinline__ void absorb_role(char* smem, const AbsorbArgs& ab) {
 // the terms and the order that absorb_role gives them: slice for slice, the slices' sums in order, then the state.
 template <int NW>
 __device__ __forceinline__ void absorb_half(char* smem, const AbsorbArgs& ab) {
-  constexpr int IB = NW == 2 ? 2 : 1;        // 32-row blocks of key features per wavefront
+  static_assert(NW == 4 || NW == 8, "two groups of two or four wavefronts");
   constexpr int JB = NW == 8 ? 1 : 2;        // 32-column blocks of value features per wavefront
   constexpr int PARTB = 16 * KSTR, STAGE = 2 * PARTB, NSTG = 5;   // stages as in absorb_role
   constexpr int RPS = (STAGE / 1024) / NW;
@@ -623,7 +623,7 @@ __device__ __forceinline__ void absorb_half(char* smem, const AbsorbArgs& ab) {
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int l32 = lane & 31, h = lane >> 5;
   const int nst = (ab.n + 15) / 16;
-  const int ib0 = NW == 8 ? wave & 3 : IB * wave, jb0 = 2 * half + (NW == 8 ? wave >> 2 : 0);   // (scalar)
+  const int ib = wave & 3, jb0 = 2 * half + (NW == 8 ? wave >> 2 : 0);   // (scalar)
 
   const uint64_t kbase = reinterpret_cast<uint64_t>(ab.K + (size_t)bh * ab.stride * D);
   const uint64_t vbase = reinterpret_cast<uint64_t>(ab.V + (size_t)bh * ab.stride * D);
@@ -664,30 +664,26 @@ __device__ __forceinline__ void absorb_half(char* smem, const AbsorbArgs& ab) {
   // what the sums are added to is on its way before the tokens
   const float* Lin = ab.state_in + (size_t)bh * D * D;
   const size_t zat = (size_t)ab.BH * D * D + (size_t)bh * D;
-  auto row_of = [&](int ib, int r) { return 32 * (ib0 + ib) + 8 * (r >> 2) + 4 * h + (r & 3); };   // accumulator element -> key feature
-  f32x16 old[IB][JB], zold[IB];
+  auto row_of = [&](int r) { return 32 * ib + 8 * (r >> 2) + 4 * h + (r & 3); };   // accumulator element -> key feature
+  f32x16 old[JB], zold;
 #pragma unroll
-  for (int ib = 0; ib < IB; ++ib)
+  for (int r = 0; r < 16; ++r) {
+    zold[r] = ab.state_in[zat + row_of(r)];
 #pragma unroll
-    for (int r = 0; r < 16; ++r) {
-      zold[ib][r] = ab.state_in[zat + row_of(ib, r)];
-#pragma unroll
-      for (int jb = 0; jb < JB; ++jb) old[ib][jb][r] = Lin[row_of(ib, r) * D + 32 * (jb0 + jb) + l32];
-    }
+    for (int jb = 0; jb < JB; ++jb) old[jb][r] = Lin[row_of(r) * D + 32 * (jb0 + jb) + l32];
+  }
 #pragma unroll
   for (int c = 0; c < NSTG - 1; ++c) fetch(c);
 
   const s16x8 zero8 = {0, 0, 0, 0, 0, 0, 0, 0};
   const s16x8 ones8 = {0x3f80, 0x3f80, 0x3f80, 0x3f80, 0x3f80, 0x3f80, 0x3f80, 0x3f80};   // bf16 1.0
-  f32x16 sum[IB][JB], zsum[IB], acc[IB][JB], zacc[IB];
+  f32x16 sum[JB], zsum, acc[JB], zacc;
 #pragma unroll
-  for (int ib = 0; ib < IB; ++ib)
+  for (int r = 0; r < 16; ++r) {
+    zsum[r] = zacc[r] = 0.0f;
 #pragma unroll
-    for (int r = 0; r < 16; ++r) {
-      zsum[ib][r] = zacc[ib][r] = 0.0f;
-#pragma unroll
-      for (int jb = 0; jb < JB; ++jb) sum[ib][jb][r] = acc[ib][jb][r] = 0.0f;
-    }
+    for (int jb = 0; jb < JB; ++jb) sum[jb][r] = acc[jb][r] = 0.0f;
+  }
   for (int sl = 0, c = 0; sl < ab.slices; ++sl) {
     const int end = (int)((long long)(sl + 1) * nst / ab.slices);
     for (; c < end; ++c) {
@@ -695,63 +691,53 @@ __device__ __forceinline__ void absorb_half(char* smem, const AbsorbArgs& ab) {
       __syncthreads();             // ... and everybody's; everybody has read stage c - 1
       fetch(c + NSTG - 1);         // into the slot of stage c - 1
       const char* st = smem + (c % NSTG) * STAGE;
-      bf16x8 a[IB], b[JB];
-#pragma unroll
-      for (int ib = 0; ib < IB; ++ib)
-        a[ib] = __builtin_bit_cast(bf16x8, __builtin_elementwise_max(frag(st, ib0 + ib), zero8));
+      const bf16x8 a = __builtin_bit_cast(bf16x8, __builtin_elementwise_max(frag(st, ib), zero8));
+      bf16x8 b[JB];
 #pragma unroll
       for (int jb = 0; jb < JB; ++jb) b[jb] = __builtin_bit_cast(bf16x8, frag(st + PARTB, jb0 + jb));
 #pragma unroll
-      for (int ib = 0; ib < IB; ++ib) {
-#pragma unroll
-        for (int jb = 0; jb < JB; ++jb) acc[ib][jb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[ib], b[jb], acc[ib][jb], 0, 0, 0);
-        zacc[ib] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[ib], __builtin_bit_cast(bf16x8, ones8), zacc[ib], 0, 0, 0);
-      }
+      for (int jb = 0; jb < JB; ++jb) acc[jb] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b[jb], acc[jb], 0, 0, 0);
+      zacc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, __builtin_bit_cast(bf16x8, ones8), zacc, 0, 0, 0);
     }
 #pragma unroll
-    for (int ib = 0; ib < IB; ++ib)
+    for (int r = 0; r < 16; ++r) {
+      zsum[r] += zacc[r];
+      zacc[r] = 0.0f;
 #pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        zsum[ib][r] += zacc[ib][r];
-        zacc[ib][r] = 0.0f;
-#pragma unroll
-        for (int jb = 0; jb < JB; ++jb) { sum[ib][jb][r] += acc[ib][jb][r]; acc[ib][jb][r] = 0.0f; }
-      }
+      for (int jb = 0; jb < JB; ++jb) { sum[jb][r] += acc[jb][r]; acc[jb][r] = 0.0f; }
+    }
   }
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // (requests past the last token were empty)
 
   float* Lout = ab.state_out + (size_t)bh * D * D;
 #pragma unroll
-  for (int ib = 0; ib < IB; ++ib) {
+  for (int jb = 0; jb < JB; ++jb) {
+    const int j = 32 * (jb0 + jb) + l32;
 #pragma unroll
-    for (int jb = 0; jb < JB; ++jb) {
-      const int j = 32 * (jb0 + jb) + l32;
+    for (int r = 0; r < 16; ++r) {
+      sum[jb][r] += old[jb][r];
+      Lout[row_of(r) * D + j] = sum[jb][r];
+    }
+    if (ab.planes_out) {
+      bf16_t* const hi = ab.planes_out + (size_t)bh * 2 * D * D + (size_t)j * D;
 #pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        sum[ib][jb][r] += old[ib][jb][r];
-        Lout[row_of(ib, r) * D + j] = sum[ib][jb][r];
-      }
-      if (ab.planes_out) {
-        bf16_t* const hi = ab.planes_out + (size_t)bh * 2 * D * D + (size_t)j * D;
+      for (int rq = 0; rq < 4; ++rq) {
+        uint32_t hw[2], lw[2];
 #pragma unroll
-        for (int rq = 0; rq < 4; ++rq) {
-          uint32_t hw[2], lw[2];
-#pragma unroll
-          for (int q = 0; q < 2; ++q) {
-            const float v0 = sum[ib][jb][4 * rq + 2 * q], v1 = sum[ib][jb][4 * rq + 2 * q + 1];
-            const bf16_t h0 = f32_to_bf16(v0), h1 = f32_to_bf16(v1);
-            hw[q] = (uint32_t)h0 | ((uint32_t)h1 << 16);
-            lw[q] = pack_bf16(v0 - bf16_to_f32(h0), v1 - bf16_to_f32(h1));
-          }
-          *reinterpret_cast<uint2*>(hi + row_of(ib, 4 * rq)) = make_uint2(hw[0], hw[1]);
-          *reinterpret_cast<uint2*>(hi + D * D + row_of(ib, 4 * rq)) = make_uint2(lw[0], lw[1]);
+        for (int q = 0; q < 2; ++q) {
+          const float v0 = sum[jb][4 * rq + 2 * q], v1 = sum[jb][4 * rq + 2 * q + 1];
+          const bf16_t h0 = f32_to_bf16(v0), h1 = f32_to_bf16(v1);
+          hw[q] = (uint32_t)h0 | ((uint32_t)h1 << 16);
+          lw[q] = pack_bf16(v0 - bf16_to_f32(h0), v1 - bf16_to_f32(h1));
         }
+        *reinterpret_cast<uint2*>(hi + row_of(4 * rq)) = make_uint2(hw[0], hw[1]);
+        *reinterpret_cast<uint2*>(hi + D * D + row_of(4 * rq)) = make_uint2(lw[0], lw[1]);
       }
     }
-    if (l32 == 0 && jb0 == 0) {
+  }
+  if (l32 == 0 && jb0 == 0) {
 #pragma unroll
-      for (int r = 0; r < 16; ++r) ab.state_out[zat + row_of(ib, r)] = zsum[ib][r] + zold[ib][r];
-    }
+    for (int r = 0; r < 16; ++r) ab.state_out[zat + row_of(r)] = zsum[r] + zold[r];
   }
 }
 
@@ -781,8 +767,13 @@ __global__ __launch_bounds__(64 * NW * KS, 2) void attn_mfma_kernel(
   // (head, query block) items so that its L2 sees few heads
   if constexpr (kSel) {
     if ((int)blockIdx.x < ab.role_blocks) {
-      if (KS > 1 && ab.halves) absorb_half<NW * KS>(smem, ab);
-      else absorb_role<NW * KS>(smem, ab);
+      if constexpr (KS > 1) {   // (launch_attn_mfma_step asks for halves in such launches alone)
+        if (ab.halves) {
+          absorb_half<NW * KS>(smem, ab);
+          return;
+        }
+      }
+      absorb_role<NW * KS>(smem, ab);
       return;
     }
   }
@@ -810,7 +801,7 @@ __global__ __launch_bounds__(64 * NW * KS, 2) void attn_mfma_kernel(
   const int q_row = qb * BQ + 32 * wave + l32;
   bf16x8 qf[8];
   // Selecting, two groups form the history term's denominator while the first tiles travel and bring the state's plane to the L2 under
-  // the Top-K; with a given list both only delay the first tile (3 heads x 400 queries, blocks of 128 13.5 / 13.2 us, of 64 9.9 / 9.7)
+  // the Top-K; with a given list both only delay the first tile (3 heads x 400 queries, blocks of 128 13.5 / 13.2 us, of 64 alike)
   constexpr bool kDenEarly = kSel != 0 && KS > 1 && kFused == 1, kPlaneEarly = kSel != 0 && KS > 1 && (kFused == 1 || kFused == 2);
   float4 z_of[kDenEarly ? 16 : 1];
   uint32_t plane_line = 0;   // (of the plane's 256 lines of 128 bytes)
