@@ -508,9 +508,10 @@ __global__ __launch_bounds__(64 * kScoreParts, 4) void bwd_scores_kernel(WideBwd
       weighted = fmaf(stat[2][u][rr], w, weighted);
     }
     const size_t at = (size_t)bh * n_q + row0 + rr;
-    const bool none = sum == 0.0f;   // no key at all (an empty list): probabilities are zero
-    a.lse2[at] = none ? __builtin_inff() : top + __builtin_amdgcn_logf(sum);
-    a.Dv[at] = none ? 0.0f : weighted / sum;
+    // no key at all (an empty list), or a sum that is no number: probabilities are zero, so that the row adds nothing to the values'
+    // gradients of its other keys, as where every kernel forms its own scores
+    a.lse2[at] = sum > 0.0f ? top + __builtin_amdgcn_logf(sum) : __builtin_inff();
+    a.Dv[at] = sum == 0.0f ? 0.0f : weighted / sum;
   }
 }
 
