@@ -462,11 +462,17 @@ HF_API int hf_hybrid_attn_fwd_save(const hf_config* cfg, const void* Q_local, co
                        void* O, void* O_local_out, float* lse2_out,
                        void* workspace, size_t workspace_bytes, void* stream);
 
-/* Bytes of scratch hf_hybrid_attn_bwd takes for these sizes.  Host-only.  Outside bf16 at head_dim 128 with block_q 64 or 128
- * (or with HF_FLAG_BWD_FP32_KERNELS) they hold two fp32 numbers per (query, key of its list), blocks rounded up to multiples
- * of sixteen, where that is 2 GiB at most: what the three gradients have in common is then formed once.  A workspace without
- * that room (a refusal names the least size) is accepted as well: every gradient forms its own. */
+/* Bytes of scratch hf_hybrid_attn_bwd makes use of for these sizes.  Host-only.  They do not shrink as n_q or n_kv grow: a workspace
+ * for the largest call serves every smaller one.  Outside bf16 at head_dim 128 with block_q 64 or 128 (or with
+ * HF_FLAG_BWD_FP32_KERNELS) they hold, up to 2 GiB, two fp32 numbers per (query, key of a list of the config's length), blocks rounded
+ * up to multiples of sixteen, so that what the three gradients have in common is formed once.  Any size from
+ * hf_bwd_least_workspace_bytes on is accepted: with less room, and for longer lists (block_idx NULL with keep_ratio < 1 among them),
+ * as many heads at a time as it holds, or, where these would leave compute units idle, every gradient forms its own.  The two ways
+ * differ by the rounding of fp32 sums. */
 HF_API int hf_bwd_workspace_bytes(const hf_config* cfg, int32_t n_q, int32_t n_kv, size_t* bytes_out);
+
+/* Bytes of scratch that hf_hybrid_attn_bwd cannot do without.  Host-only. */
+HF_API int hf_bwd_least_workspace_bytes(const hf_config* cfg, int32_t n_q, int32_t n_kv, size_t* bytes_out);
 
 /* Gradients of O = O_local + O_hist (Eq. 5, 3, 6) for the step of the training algorithm that runs with
  * gradients enabled.  That algorithm builds the KV cache and the linear state with gradients disabled, so
@@ -483,7 +489,7 @@ HF_API int hf_bwd_workspace_bytes(const hf_config* cfg, int32_t n_q, int32_t n_k
  *   dK, dV   out, laid out like K_win, V_win (heads kv_capacity tokens apart if cfg->kv_capacity is set;
  *            only the first n_kv tokens of a head are written): gradients with respect to every key and
  *            value of the window; keys of blocks that no query block selected get zeros.
- *   workspace >= hf_bwd_workspace_bytes(...) bytes, 256-byte aligned.
+ *   workspace hf_bwd_workspace_bytes(...) bytes, and at least hf_bwd_least_workspace_bytes(...), 256-byte aligned.
  * fp32 arithmetic on the recomputed probabilities, one rounding to cfg->dtype per output element.
  * Outputs must not alias inputs or each other. */
 HF_API int hf_hybrid_attn_bwd(const hf_config* cfg, const void* Q, const void* Q_hist, int32_t n_q,

@@ -118,6 +118,7 @@ def load():
     lib.hf_hybrid_attn_fwd_split.argtypes = [CP, P, P, I, P, P, I, P, I, P, P, P, P, P, SZ, P]
     lib.hf_hybrid_attn_fwd_save.argtypes = [CP, P, P, I, P, P, I, P, I, P, P, P, P, P, P, P, SZ, P]
     lib.hf_bwd_workspace_bytes.argtypes = [CP, I, I, ctypes.POINTER(SZ)]
+    lib.hf_bwd_least_workspace_bytes.argtypes = [CP, I, I, ctypes.POINTER(SZ)]
     lib.hf_hybrid_attn_bwd.argtypes = [CP, P, P, I, P, P, I, P, I, P, P, P, P, P, P, P, P, P, SZ, P]
     lib.hf_hybrid_attn_bwd_saved.argtypes = [CP, P, P, I, P, P, I, P, I, P, P, P, P, P, P, P, P, P, P, P, SZ, P]
     lib.hf_rope_window_indices.argtypes = [I, I, I, ctypes.POINTER(I)]
@@ -130,7 +131,7 @@ def load():
                  "hf_block_select", "hf_block_select_cached", "hf_block_select_static", "hf_hybrid_attn_fwd",
                  "hf_hybrid_attn_fwd_split",
                  "hf_rope_window_indices", "hf_rope_tables", "hf_rope_apply", "hf_window_evict", "hf_stream_open_chunk",
-                 "hf_stream_step", "hf_bwd_workspace_bytes", "hf_hybrid_attn_bwd", "hf_state_planes_bytes",
+                 "hf_stream_step", "hf_bwd_workspace_bytes", "hf_bwd_least_workspace_bytes", "hf_hybrid_attn_bwd", "hf_state_planes_bytes",
                  "hf_state_planes", "hf_absorb_evicted_planes", "hf_hybrid_attn_fwd_planes", "hf_probe_mfma_bf16",
                  "hf_ring_open_chunk", "hf_ring_step", "hf_pooled_keys_bytes", "hf_pool_keys", "hf_select_attn_fwd",
                  "hf_step_workspace_bytes", "hf_step_fwd", "hf_rope_append_keys", "hf_ring_last_step"):
@@ -381,6 +382,13 @@ def hf_ring_step(cfg: hf_config, ring: hf_ring, Q, K_cache, V_cache, step_in_chu
 def hf_bwd_workspace_bytes(cfg: hf_config, n_q: int, n_kv: int) -> int:
     out = ctypes.c_size_t(0)
     _check(load().hf_bwd_workspace_bytes(ctypes.byref(cfg), n_q, n_kv, ctypes.byref(out)))
+    return out.value
+
+
+def hf_bwd_least_workspace_bytes(cfg: hf_config, n_q: int, n_kv: int) -> int:
+    """The least that hf_hybrid_attn_bwd takes (hf_bwd_workspace_bytes: what it makes use of)."""
+    out = ctypes.c_size_t(0)
+    _check(load().hf_bwd_least_workspace_bytes(ctypes.byref(cfg), n_q, n_kv, ctypes.byref(out)))
     return out.value
 
 

@@ -1128,8 +1128,16 @@ int hf_bwd_workspace_bytes(const hf_config* cfg, int32_t n_q, int32_t n_kv, size
   HF_TRY(check_tokens(n_kv, "n_kv"));
   const BwdLayout w = bwd_layout(cfg, n_q, n_kv);
   const int t_n = cdiv(n_kv, cfg->block_kv), k = select_k_of(cfg, t_n);
-  const size_t scores = bwd_mfma_taken(*cfg, false) ? 0 : bwd_scores_bytes(*cfg, n_q, k < t_n ? k : t_n);
-  *bytes_out = scores ? w.scores + scores : w.total;
+  *bytes_out = bwd_mfma_taken(*cfg, false) ? w.total : w.scores + bwd_scores_room(*cfg, n_q, k < t_n ? k : t_n);
+  return HF_OK;
+}
+
+int hf_bwd_least_workspace_bytes(const hf_config* cfg, int32_t n_q, int32_t n_kv, size_t* bytes_out) {
+  HF_TRY(check_cfg(cfg));
+  if (!bytes_out) { set_error("bytes_out is NULL"); return HF_ERR_NULL; }
+  HF_TRY(check_tokens(n_q, "n_q"));
+  HF_TRY(check_tokens(n_kv, "n_kv"));
+  *bytes_out = bwd_layout(cfg, n_q, n_kv).total;
   return HF_OK;
 }
 
@@ -1241,16 +1249,39 @@ static int bwd_impl(const hf_config* cfg, const void* Q, const void* Q_hist, int
     return launch_bwd_mfma(*cfg, Q, n_q, K_win, V_win, n_kv, block_idx, k, dO, saved ? lse2_saved : lse2, dvec, inv_cnt, inv_list,
                            order, st, rope_cos_q, rope_sin_q, Q_hist, ws + w.planes, dQ, dQ_hist, dK, dV, s);
   }
-  // scores kept in the workspace where it has room for them (callers may have kept one of the size that has none), else every
-  // kernel forms its own, behind a forward pass for the statistics
-  const size_t score_bytes = bwd_scores_bytes(*cfg, n_q, k);
-  float* scores = score_bytes && workspace_bytes >= w.scores + score_bytes ? reinterpret_cast<float*>(ws + w.scores) : nullptr;
-  int32_t* inv_slot = scores && block_idx ? reinterpret_cast<int32_t*>(ws + w.inv_slot) : nullptr;
-  HF_TRY(launch_bwd_prep(*cfg, block_idx, k, t_m, t_n, inv_cnt, inv_list, inv_slot, scores ? order : nullptr, 1, nullptr, nullptr, nullptr,
-                         nullptr, 0, nullptr, s));
-  if (!scores) HF_TRY(launch_attn_wide_stats(*cfg, Q, n_q, K_win, V_win, n_kv, block_idx, k, dO, lse2, dvec, s));
-  return launch_bwd_generic(*cfg, Q, Q_hist, n_q, K_win, V_win, n_kv, block_idx, k, dO, lse2, dvec, inv_cnt, inv_list, inv_slot,
-                            order, scores, st, rope_cos_q, rope_sin_q, dQ, st ? dQ_hist : nullptr, dK, dV, s);
+  // scores kept in the workspace, of as many heads at a time as it has room for; where that is none (callers may have kept a
+  // workspace of the least size), every kernel forms its own, behind a forward pass for the statistics
+  const int BH = cfg->batch * cfg->heads, d = cfg->head_dim;
+  const int at_once = workspace_bytes > w.scores ? bwd_scores_heads(*cfg, n_q, n_kv, k, workspace_bytes - w.scores) : 0;
+  const float* zvec = st ? st + (size_t)BH * d * d : nullptr;
+  if (!at_once) {
+    HF_TRY(launch_bwd_prep(*cfg, block_idx, k, t_m, t_n, inv_cnt, inv_list, nullptr, nullptr, 1, nullptr, nullptr, nullptr, nullptr, 0,
+                           nullptr, s));
+    HF_TRY(launch_attn_wide_stats(*cfg, Q, n_q, K_win, V_win, n_kv, block_idx, k, dO, lse2, dvec, s));
+    return launch_bwd_generic(*cfg, Q, Q_hist, n_q, K_win, V_win, n_kv, block_idx, k, dO, lse2, dvec, inv_cnt, inv_list, nullptr,
+                              nullptr, nullptr, st, zvec, rope_cos_q, rope_sin_q, dQ, st ? dQ_hist : nullptr, dK, dV, s);
+  }
+  float* scores = reinterpret_cast<float*>(ws + w.scores);
+  int32_t* inv_slot = block_idx ? reinterpret_cast<int32_t*>(ws + w.inv_slot) : nullptr;
+  const size_t es = esize(cfg), q_head = (size_t)n_q * d * es, kv_head = (size_t)kv_stride_of(*cfg, n_kv) * d * es;
+  auto in = [](const void* p, size_t bytes) { return static_cast<const char*>(p) + bytes; };
+  auto out = [](void* p, size_t bytes) { return static_cast<char*>(p) + bytes; };
+  const int groups = cdiv(BH, at_once);
+  for (int g = 0, h = 0; g < groups; ++g) {   // a call of its own on the heads [h, h + n), one after another through the same scratch
+    const int n = (int)((long long)(g + 1) * BH / groups) - h;
+    hf_config c = *cfg;
+    c.batch = 1;
+    c.heads = n;
+    const int32_t* idx = block_idx ? block_idx + (size_t)h * t_m * k : nullptr;
+    HF_TRY(launch_bwd_prep(c, idx, k, t_m, t_n, inv_cnt, inv_list, inv_slot, order, 1, nullptr, nullptr, nullptr, nullptr, 0, nullptr, s));
+    HF_TRY(launch_bwd_generic(c, in(Q, h * q_head), in(Q_hist, h * q_head), n_q, in(K_win, h * kv_head), in(V_win, h * kv_head), n_kv, idx,
+                              k, in(dO, h * q_head), lse2, dvec, inv_cnt, inv_list, inv_slot, order, scores,
+                              st ? st + (size_t)h * d * d : nullptr, st ? zvec + (size_t)h * d : nullptr, rope_cos_q, rope_sin_q,
+                              out(dQ, h * q_head), st && dQ_hist ? out(dQ_hist, h * q_head) : nullptr, out(dK, h * kv_head),
+                              out(dV, h * kv_head), s));
+    h += n;
+  }
+  return HF_OK;
 }
 
 int hf_rope_window_indices(int32_t i_newest, int32_t n_frames, int32_t t0, int32_t* idx_out) {

@@ -354,7 +354,7 @@ struct WideBwd {
 // Stored scores: a panel per (query block, place of its list), a panel's tiles of 16 queries x 16 keys row by row, a tile's S
 // [query][key] (times scale log2 e) and then its dP.
 constexpr int kScoreTile = 2 * 16 * 16;
-constexpr size_t kScoresMax = (size_t)2 << 30;   // (24 heads of 64, 1458 x 4374, half of the keys, 1.2 GB: 981 us forming them again, 849 stored)
+constexpr size_t kScoresRoom = (size_t)2 << 30;   // most that a workspace holds of them
 __device__ __forceinline__ const float* score_tile(const WideBwd& a, int bh, int qb, int slot, int qi, int ki) {
   const int qt = (a.bq + 15) / 16, kt = (a.bkv + 15) / 16;
   return a.scores + ((((size_t)bh * a.t_m + qb) * a.k + slot) * (qt * kt) + qi * kt + ki) * kScoreTile;
@@ -1269,20 +1269,42 @@ int launch_bwd_prep(const hf_config& c, const int32_t* idx, int k, int t_m, int 
   return check_launch("hf_hybrid_attn_bwd(lists, planes, D)");
 }
 
-// Bytes of the stored scores of a call with lists of k blocks; 0: products are formed again instead.
-size_t bwd_scores_bytes(const hf_config& c, int n_q, int k) {
+// Room for the stored scores, in a workspace of the size that callers are told.  It never shrinks as a call grows, so that one of the
+// largest size serves the smaller ones, and ends at kScoresRoom: longer calls go through it a few heads at a time.
+static size_t head_scores(const hf_config& c, int n_q, int k) {   // bytes of a head's
   const size_t t_m = (n_q + c.block_q - 1) / c.block_q, qt = (c.block_q + 15) / 16, kt = (c.block_kv + 15) / 16;
-  const size_t bytes = (size_t)c.batch * c.heads * t_m * k * qt * kt * (kScoreTile * sizeof(float));
-  return bytes <= kScoresMax ? bytes : 0;
+  return t_m * k * qt * kt * (kScoreTile * sizeof(float));
 }
 
-// dQ (with the history branch where a state is given), dK and dV.  32 rows or keys per workgroup, 16 where a block has
-// no more (or would leave over a quarter of the 32 empty): the second half of the products would be work on nothing.
+size_t bwd_scores_room(const hf_config& c, int n_q, int k) {
+  const size_t all = (size_t)c.batch * c.heads * head_scores(c, n_q, k);
+  return all < kScoresRoom ? all : kScoresRoom;
+}
+
+// 32 rows or keys a workgroup, 16 where a block has no more (or would leave over a quarter of the 32 empty): the second half of
+// the products would be work on nothing
+static int wide_rows(int block) { return (block + 31) / 32 * 32 * 3 <= block * 4 ? 32 : 16; }
+
+// Heads whose scores are stored at a time, 0: none.  All that there is room for, in groups of a size, where the smallest has a
+// query-side workgroup for every compute unit; with less, forming the products again for all heads at once is faster.  Products again /
+// heads at a time, us: 12 heads of 128, 1170 x 2340, 38 workgroups a head: 244 / three 276, four 213, six 182, all 145; over every
+// block 665 / three 709, four 537, all 452; 24 of 64, 1458 x 4374, half of the blocks, 46: 795 / three 910, four 756, eight 650, all
+// 671; 12 of 64, 2000 x 4000, blocks of 128, 64: 283 / three 284, four 240, all 201; 12 of 128, 4680 x 9360, 148: 2410 / one 2433, two
+// 2162, three 1832, all 1696; 24 of 64 in bf16, 148: 2643 / one 3137, two 2587, three 2119, twelve 1999.  Short blocks, whose tiles are
+// padded to sixteen either way: 4 heads of 128, 64 x 128 in blocks of one 73 / all 50, 12, 600 x 600 in blocks of 4 749 / all 492.
+int bwd_scores_heads(const hf_config& c, int n_q, int n_kv, int k, size_t room) {
+  const size_t BH = (size_t)c.batch * c.heads, fit = room / head_scores(c, n_q, k);
+  if (fit >= BH) return (int)BH;
+  const size_t q_rows = wide_rows(c.block_q), wgs = (n_q + c.block_q - 1) / c.block_q * ((c.block_q + q_rows - 1) / q_rows);
+  return fit && BH / ((BH + fit - 1) / fit) * wgs >= 256 ? (int)fit : 0;
+}
+
+// dQ (with the history branch where a state, L and z, is given), dK and dV.
 // scores given: room for them; NULL: lse2 and Dv are there already.
 int launch_bwd_generic(const hf_config& c, const void* Q, const void* Q_hist, int n_q, const void* K, const void* V, int n_kv,
                        const int32_t* idx, int k, const void* dO, float* lse2, float* Dv, const int32_t* inv_cnt,
                        const int32_t* inv_list, const int32_t* inv_slot, const int32_t* order, float* scores, const float* state,
-                       const float* cosq, const float* sinq, void* dQ, void* dQ_hist, void* dK, void* dV, hipStream_t s) {
+                       const float* zvec, const float* cosq, const float* sinq, void* dQ, void* dQ_hist, void* dK, void* dV, hipStream_t s) {
   WideBwd a = {};
   a.Q = Q; a.K = K; a.V = V; a.dO = dO;
   a.idx = idx;
@@ -1301,7 +1323,7 @@ int launch_bwd_generic(const hf_config& c, const void* Q, const void* Q_hist, in
   if (state) {
     WideBwdHist& h = a.hist;
     h.L = state;
-    h.z = state + (size_t)c.batch * c.heads * c.head_dim * c.head_dim;
+    h.z = zvec;
     h.cosq = cosq;
     h.sinq = sinq;
     h.q_hist = Q_hist;
@@ -1310,9 +1332,8 @@ int launch_bwd_generic(const hf_config& c, const void* Q, const void* Q_hist, in
     h.z_scale = c.z_scale;
     h.phi_kind = c.phi;
   }
-  auto two = [](int b) { return (b + 31) / 32 * 32 * 3 <= b * 4; };
-  const bool q2 = two(c.block_q), k2 = two(c.block_kv);
-  const int q_rows = q2 ? 32 : 16, k_rows = k2 ? 32 : 16;
+  const int q_rows = wide_rows(c.block_q), k_rows = wide_rows(c.block_kv);
+  const bool q2 = q_rows == 32, k2 = k_rows == 32;
   a.q_chunks = (c.block_q + q_rows - 1) / q_rows;
   a.k_chunks = (c.block_kv + k_rows - 1) / k_rows;
   const long long BH = (long long)c.batch * c.heads, q_total = BH * a.t_m * a.q_chunks, k_total = BH * a.t_n * a.k_chunks;

@@ -209,8 +209,9 @@ int launch_bwd_prep(const hf_config& c, const int32_t* idx, int k, int t_m, int 
 int launch_bwd_generic(const hf_config& c, const void* Q, const void* Q_hist, int n_q, const void* K, const void* V, int n_kv,
                        const int32_t* idx, int k, const void* dO, float* lse2, float* Dv, const int32_t* inv_cnt,
                        const int32_t* inv_list, const int32_t* inv_slot, const int32_t* order, float* scores, const float* state,
-                       const float* cosq, const float* sinq, void* dQ, void* dQ_hist, void* dK, void* dV, hipStream_t s);
-size_t bwd_scores_bytes(const hf_config& c, int n_q, int k);
+                       const float* zvec, const float* cosq, const float* sinq, void* dQ, void* dQ_hist, void* dK, void* dV, hipStream_t s);
+size_t bwd_scores_room(const hf_config& c, int n_q, int k);                              // bytes that a workspace should have for scores
+int bwd_scores_heads(const hf_config& c, int n_q, int n_kv, int k, size_t room);         // heads whose scores are stored at a time
 int launch_rope_tables(const int32_t* frame_idx, int n_frames, int height, int width, int pairs_t, int pairs_h,
                        int pairs_w, double theta, int temporal_only, float* cosv, float* sinv, hipStream_t s);
 int launch_rope_apply(const hf_config& c, const void* X, int n, const float* cosv, const float* sinv, void* Y,
