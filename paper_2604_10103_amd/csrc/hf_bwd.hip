@@ -1293,10 +1293,14 @@ static int wide_rows(int block) { return (block + 31) / 32 * 32 * 3 <= block * 4
 // 2162, three 1832, all 1696; 24 of 64 in bf16, 148: 2643 / one 3137, two 2587, three 2119, twelve 1999.  Short blocks, whose tiles are
 // padded to sixteen either way: 4 heads of 128, 64 x 128 in blocks of one 73 / all 50, 12, 600 x 600 in blocks of 4 749 / all 492.
 int bwd_scores_heads(const hf_config& c, int n_q, int n_kv, int k, size_t room) {
-  const size_t BH = (size_t)c.batch * c.heads, fit = room / head_scores(c, n_q, k);
+  const size_t BH = (size_t)c.batch * c.heads, q_rows = wide_rows(c.block_q), k_rows = wide_rows(c.block_kv);
+  const size_t q_wgs = (n_q + c.block_q - 1) / c.block_q * ((c.block_q + q_rows - 1) / q_rows);
+  const size_t k_chunks = (c.block_kv + k_rows - 1) / k_rows, k_wgs = (n_kv + c.block_kv - 1) / c.block_kv * k_chunks;
+  // (a launch has less than 2^32 threads, and both sides are rounded up to eight shares)
+  const size_t most = (((size_t)1 << 32) / (64 * kStoredWaves) - 8 - 8 * k_chunks) / (q_wgs + k_wgs);
+  const size_t fit = room / head_scores(c, n_q, k) < most ? room / head_scores(c, n_q, k) : most;
   if (fit >= BH) return (int)BH;
-  const size_t q_rows = wide_rows(c.block_q), wgs = (n_q + c.block_q - 1) / c.block_q * ((c.block_q + q_rows - 1) / q_rows);
-  return fit && BH / ((BH + fit - 1) / fit) * wgs >= 256 ? (int)fit : 0;
+  return fit && BH / ((BH + fit - 1) / fit) * q_wgs >= 256 ? (int)fit : 0;
 }
 
 // dQ (with the history branch where a state, L and z, is given), dK and dV.

@@ -87,3 +87,19 @@ def test_heads_a_few_at_a_time(dtype, d, b, dense):
         assert (room == 0xFF).all() and (behind == 0xFF).all()
         for a, r in zip(got, want):
             assert rel_l2(wl.to_f64(a), wl.to_f64(r)) <= (8e-3 if dtype == "bf16" else 5e-5), n
+
+
+@pytest.mark.parametrize("heads,n_kv", [(1, (1 << 23) + 100), (4, (1 << 21) + 100)])
+def test_more_key_blocks_than_a_launch_of_eight_wavefronts_has_workgroups(heads, n_kv):
+    """2^23 workgroups of 512 threads are 2^32 threads, more than a launch may have; of 256 they fit.  One query, one key on its list:
+    P = 1, so that dV of that key is dO and all else is zero."""
+    cfg = hf.make_config(1, heads, 64, "f32", 1, 1, 0.5)
+    Q, dO = (torch.randn((1, heads, 1, 64), device=DEV, generator=torch.Generator(DEV).manual_seed(s)) for s in (1, 2))
+    K = torch.ones((1, heads, n_kv, 64), device=DEV)
+    idx = torch.full((1, heads, 1, 1), n_kv - 3, dtype=torch.int32, device=DEV)
+    ws = torch.empty(hf.hf_bwd_workspace_bytes(cfg, 1, n_kv), dtype=torch.uint8, device=DEV)
+    dQ, dK, dV = torch.full_like(Q, 7.0), torch.full_like(K, 7.0), torch.full_like(K, 7.0)
+    hf.hf_hybrid_attn_bwd(cfg, Q, K, K, idx, None, dO, dQ, dK, dV, ws)
+    torch.cuda.synchronize()
+    assert dQ.abs().max() <= 1e-6 and dK.abs().max() <= 1e-5
+    assert torch.allclose(dV[:, :, n_kv - 3], dO[:, :, 0], rtol=1e-6) and (dV[:, :, :n_kv - 3] == 0).all() and (dV[:, :, n_kv - 2:] == 0).all()
