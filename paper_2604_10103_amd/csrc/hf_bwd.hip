@@ -324,9 +324,9 @@ __device__ __forceinline__ void add_parts(float* smem, const f32x4 (&acc)[N][FW]
 }
 // ... and whole rows are stored
 template <typename T, int D, int N, int AT_ONCE, int WAVES>
-__device__ __forceinline__ void store_parts(const float* smem, T* dst, int rows) {
+__device__ __forceinline__ void store_parts(const float* smem, T* dst, int rows, int tid) {
   constexpr int OST = D + 4;
-  for (int e = threadIdx.x; e < 16 * N * (D / 4); e += 64 * WAVES) {
+  for (int e = tid; e < 16 * N * (D / 4); e += 64 * WAVES) {
     const int rr = e / (D / 4), c4 = e - rr * (D / 4);
     if (rr >= rows) continue;
     f32x4 v = *reinterpret_cast<const f32x4*>(smem + (size_t)rr * OST + 4 * c4);
@@ -874,7 +874,7 @@ __device__ __forceinline__ void dq_role(const WideBwd& a, int wg, float* __restr
     }
   }
   add_parts<D, NQ, PARTS, AT_ONCE, FW>(smem, dq, 1.0f, kStored && hist.L && !hist.dq_hist, part, f_own, l16, g);
-  store_parts<T, D, NQ, AT_ONCE, WAVES>(smem, static_cast<T*>(a.dQ) + ((size_t)bh * n_q + row0) * D, q_end - row0);
+  store_parts<T, D, NQ, AT_ONCE, WAVES>(smem, static_cast<T*>(a.dQ) + ((size_t)bh * n_q + row0) * D, q_end - row0, threadIdx.x);
 }
 
 // ---- dK, dV: a workgroup per 16 NK keys of a KV block, its four wavefronts taking every fourth 16-row tile of the query
@@ -1015,10 +1015,10 @@ __device__ __forceinline__ void dkv_role(const WideBwd& a, int wg, float* __rest
   __syncthreads();   // K and V are read no more
   const size_t out = ((size_t)bh * kv_stride + key0) * D;
   add_parts<D, NK, kParts, kParts, F>(smem, ak, a.scale, false, kz, 0, l16, g);
-  store_parts<T, D, NK, kParts, kParts>(smem, static_cast<T*>(a.dK) + out, k_end - key0);
+  store_parts<T, D, NK, kParts, kParts>(smem, static_cast<T*>(a.dK) + out, k_end - key0, threadIdx.x);
   __syncthreads();
   add_parts<D, NK, kParts, kParts, F>(smem, av, 1.0f, false, kz, 0, l16, g);
-  store_parts<T, D, NK, kParts, kParts>(smem, static_cast<T*>(a.dV) + out, k_end - key0);
+  store_parts<T, D, NK, kParts, kParts>(smem, static_cast<T*>(a.dV) + out, k_end - key0, threadIdx.x);
 }
 
 // ---- dK, dV from stored scores: a workgroup per 16 NK keys of a KV block, half of its wavefronts for each of the two (half of the
@@ -1026,6 +1026,7 @@ __device__ __forceinline__ void dkv_role(const WideBwd& a, int wg, float* __rest
 template <typename T, int D, int NK>
 __device__ __forceinline__ void dkv_stored_role(const WideBwd& a, int wg, float* __restrict__ smem) {
   constexpr int ROWS = 16 * NK, F = D / 64, OST = D + 4;
+  constexpr bool kTight = NK * F == 4;   // all 128 registers are in use: the loop keeps one for what a lane's four queries follow from
   const int n_q = a.n_q, n_kv = a.n_kv, kv_stride = a.kv_stride, bq = a.bq, bkv = a.bkv, t_m = a.t_m, t_n = a.t_n;
   const int place = wg >> 3, chunk = place % a.k_chunks, block = (wg & 7) * (a.k_per_xcd / a.k_chunks) + place / a.k_chunks;
   if (place >= a.k_per_xcd || block >= a.k_total / a.k_chunks) return;
@@ -1055,7 +1056,7 @@ __device__ __forceinline__ void dkv_stored_role(const WideBwd& a, int wg, float*
   const int32_t* __restrict__ slots = a.inv_slot ? a.inv_slot + ((size_t)bh * t_n + jb) * t_m : nullptr;
   const int kt = (bkv + 15) / 16, ki0 = (key0 - jb * bkv) / 16;
   constexpr int B = sizeof(T);
-  int col_at = (4 * g * D + 4 * l16) * B, tile_lane = (64 * g + l16) * 4;
+  int col_at = (4 * g * D + 4 * l16) * B, tile_lane = (64 * g + l16) * 4, g16 = 16 * g;
   // the list's entries are read a trip before their tile's rows are asked for (without a branch, which in the loop would
   // have the accumulators kept twice; a dense window has some word read in their place)
   const int32_t* __restrict__ some = reinterpret_cast<const int32_t*>(lseh);
@@ -1079,8 +1080,8 @@ __device__ __forceinline__ void dkv_stored_role(const WideBwd& a, int wg, float*
     const __amdgpu_buffer_rsrc_t rl = tile_rows<float, 1>(lseh, first, cnt), rd = tile_rows<float, 1>(dvh, first, cnt);
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
-      lse[r] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rl, 16 * g + 4 * r, 0, 0));
-      dv[r] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rd, 16 * g + 4 * r, 0, 0));
+      lse[r] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rl, (kTight ? g16 : 16 * g) + 4 * r, 0, 0));
+      dv[r] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rd, (kTight ? g16 : 16 * g) + 4 * r, 0, 0));
     }
 #pragma unroll
     for (int n = 0; n < NK; ++n) {
@@ -1104,11 +1105,12 @@ __device__ __forceinline__ void dkv_stored_role(const WideBwd& a, int wg, float*
 #pragma unroll
   for (int u = 0; u < AHEAD; ++u) xc[u].load(x_rows, col_at + (u / F * D + 64 * (u % F)) * B);
   for (int t = part; t < ntiles; t += PARTS) {
+    if constexpr (kTight) asm volatile("" : "+v"(g16));
     asm volatile("" : "+v"(col_at), "+v"(tile_lane));   // (opaque here, or their sums leave the loop as registers instead of immediates)
     float w[NK][4];   // P (P (0 + 1)) or dS = P (dP - D)
 #pragma unroll
     for (int r = 0; r < 4; ++r) {
-      const bool real = 4 * g + r < cnt;
+      const bool real = kTight ? g16 < 4 * (cnt - r) : 4 * g + r < cnt;
       const float off = keys ? dv[r] : -1.0f;
 #pragma unroll
       for (int n = 0; n < NK; ++n) {
@@ -1138,10 +1140,17 @@ __device__ __forceinline__ void dkv_stored_role(const WideBwd& a, int wg, float*
     x_rows = xn_rows;
   }
   float* const own = smem + (keys ? 2 * ROWS * OST : 0);
-  add_parts<D, NK, PARTS, 2, F>(own, acc, keys ? a.scale : 1.0f, false, part, 0, l16, g);
+  int tid = threadIdx.x, l_end = l16, g_end = g;
+  if constexpr (kTight) {   // (formed again instead of kept over the loop)
+    const int again = __builtin_amdgcn_mbcnt_hi(~0u, __builtin_amdgcn_mbcnt_lo(~0u, 0u));
+    tid = 64 * kz + again;
+    l_end = again & 15;
+    g_end = again >> 4;
+  }
+  add_parts<D, NK, PARTS, 2, F>(own, acc, keys ? a.scale : 1.0f, false, part, 0, l_end, g_end);
   const size_t out = ((size_t)bh * kv_stride + key0) * D;
-  store_parts<T, D, NK, 2, kStoredWaves>(smem, static_cast<T*>(a.dV) + out, k_end - key0);
-  store_parts<T, D, NK, 2, kStoredWaves>(smem + 2 * ROWS * OST, static_cast<T*>(a.dK) + out, k_end - key0);
+  store_parts<T, D, NK, 2, kStoredWaves>(smem, static_cast<T*>(a.dV) + out, k_end - key0, tid);
+  store_parts<T, D, NK, 2, kStoredWaves>(smem + 2 * ROWS * OST, static_cast<T*>(a.dK) + out, k_end - key0, tid);
 }
 
 template <typename T, int D, int NQ>

@@ -67,3 +67,9 @@ def test_attention_without_selection_pays_nothing_for_it(kernels, instance, regi
 def test_registers_that_the_bf16_attention_spills(kernels, instance, spilled):
     """Full launches of rotated queries and of selecting workgroups spill a few around their loop; nobody spills more."""
     assert kernels[f"attn_mfma_kernel<{instance}>"][".vgpr_spill_count"] <= spilled
+
+
+def test_gradients_from_stored_scores_use_no_scratch(kernels):
+    names = [n for n in kernels if n.startswith(("bwd_stored_kernel<", "bwd_scores_kernel<"))]
+    assert len(names) == 24
+    assert {n: kernels[n][".private_segment_fixed_size"] for n in names} == dict.fromkeys(names, 0)
