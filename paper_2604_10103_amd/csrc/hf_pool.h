@@ -22,6 +22,9 @@ __device__ __forceinline__ void warm_arguments() {
     asm volatile("s_load_dword %0, %4, 0x0\n\ts_load_dword %1, %4, 0x40\n\ts_load_dword %2, %4, 0x80\n\ts_load_dword %3, %4, 0xc0\n\t"
                  "s_waitcnt lgkmcnt(0)"
                  : "=&s"(t0), "=&s"(t1), "=&s"(t2), "=&s"(t3) : "s"(args));
+  // (awaited in their block; read as well, as an output that nobody reads counts as free)
+  asm volatile("" :: "s"(t0), "s"(t1), "s"(t2), "s"(t3));
+  if constexpr (kLines == 5) asm volatile("" :: "s"(t4));
 }
 
 // Mean of the rows [r0, r1) of X (rows of D elements from base, which points at the lane's columns), by one wavefront: what the
