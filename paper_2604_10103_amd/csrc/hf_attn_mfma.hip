@@ -808,7 +808,7 @@ __global__ __launch_bounds__(64 * NW * KS, 2) void attn_mfma_kernel(
   if constexpr (kPlaneEarly) {
     if (hist.planes) plane_line = reinterpret_cast<const uint32_t*>(hist.planes + (size_t)bh * 2 * D * D)[32 * (tid & 255)];
   }
-  // (a query's loads stand here for either: as a lambda that both call they cost full launches of lists with rotated queries four spills)
+  // (a query's loads stand here twice: as one lambda for both they cost full launches of lists with rotated queries four more spills)
   if constexpr (kSel) {
     sel_lds = select_in_workgroup<NW, KS, kSel == 2>(smem, Qh, qb * BQ, n_q, hist.kbar_t + (size_t)bh * (D / 4) * t_n * 4, t_n, k,
                                                  hist.idx_out + ((size_t)bh * t_m + qb) * k,
@@ -928,8 +928,8 @@ __global__ __launch_bounds__(64 * NW * KS, 2) void attn_mfma_kernel(
   const int w_l = (4 * (key_l & 3)) | ((2 * (grp16 & 1) + ((j16 & 3) >> 1)) ^ h);   // swizzled unit for dt = 0, x = 0
   const uint32_t v_rd = key_l * KSTR + w_l * 16 + 8 * (j16 & 1);   // ^ (64 dt) ^ (32 x), + 4096 t2 + 2048 x
 
-  // ---- prologue: K and V of tile 0 land (K of tiles 1 and 2 are on their way), the K fragments of tile 0 are
-  // read into registers
+  // ---- prologue: K of tile 0 lands (its V, awaited in the first tile's step, and K of tiles 1 and 2 are on their way), the K
+  // fragments of tile 0 are read into registers
   typedef short s16x4 __attribute__((ext_vector_type(4)));
   uint32_t k_addr[8], v_addr[4][2];
 #pragma unroll

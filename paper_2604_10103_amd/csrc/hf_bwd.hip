@@ -364,10 +364,10 @@ __device__ __forceinline__ const float* score_tile(const WideBwd& a, int bh, int
 // splitting the list; both go to memory as fp32 (score_tile), and lse2 and D = sum_j P_ij dP_ij leave with them, so that no
 // forward pass is formed again: five products of the forward's size instead of nine (two of the statistics, three for dQ, four
 // for dK and dV).  Statistics are a lane's own until the end: maximum, sum and weighted sum over the keys it holds.
-// Bound by the fp32 matrix rate at the clock it holds (2.0 GHz): 12 heads of 128, 1170 x 2340, k = 10 of 37 blocks of 64: 59 us,
-// the pipes 66 % busy while a compute unit has work (456 workgroups leave 14 % of them idle); with the gradients behind it (98)
-// instead of statistics (42), dQ (93) and dK, dV (122): 74 training steps 0.60 to 0.87 of the time, 0.69 in the mean.  Errors
-// against 64 bits are no larger (dQ 6.1e-7 -> 6.0e-7, with four times the queries 2.8e-6 -> 1.4e-6).
+// Bound by the fp32 matrix rate at the clock it holds (2.0 GHz): 12 heads of 128, 1170 x 2340, k = 10 of 37 blocks of 64: 58 us,
+// the pipes 66 % busy while a compute unit has work (456 workgroups for 512 places); with the gradients behind it (95) instead of
+// statistics (42), dQ (93) and dK, dV (122): 74 training steps 0.60 to 0.87 of the time, 0.69 in the mean.  Errors against 64 bits
+// are no larger (dQ 6.1e-7 -> 6.0e-7, with four times the queries 2.8e-6 -> 1.4e-6).
 constexpr int kScoreParts = 8;
 template <typename T, int D, int NQ>
 __global__ __launch_bounds__(64 * kScoreParts, 4) void bwd_scores_kernel(WideBwd a) {
