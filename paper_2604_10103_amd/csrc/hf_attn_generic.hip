@@ -268,12 +268,12 @@ __global__ __launch_bounds__(64 * NWV, 2) void attn_wide_kernel(const T* __restr
   f32x4 qf[NQ][C];
   if constexpr (!kSel) {
 #pragma unroll
-  for (int n = 0; n < NQ; ++n) {
-    row[n] = row0 + 16 * (wr * NQ + n) + l16;
-    const T* qp = Q + ((size_t)bh * n_q + min(row[n], n_q - 1)) * D + 4 * g;
+    for (int n = 0; n < NQ; ++n) {
+      row[n] = row0 + 16 * (wr * NQ + n) + l16;
+      const T* qp = Q + ((size_t)bh * n_q + min(row[n], n_q - 1)) * D + 4 * g;
 #pragma unroll
-    for (int c = 0; c < C; ++c) qf[n][c] = load4<T>(qp + 16 * c) * scale_log2e;
-  }
+      for (int c = 0; c < C; ++c) qf[n][c] = load4<T>(qp + 16 * c) * scale_log2e;
+    }
   }
   // Selecting, the queries are requested under the selection, at D = 64 with the history term's operands: its features and denominator
   // are formed in front of the loop then, while the first keys travel (elsewhere the registers are the selection's and the loop's).
